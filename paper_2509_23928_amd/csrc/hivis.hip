@@ -2,11 +2,13 @@
 // The C ABI is declared and documented in include/hivis.h.
 #include "hivis.h"
 #include "hivis_kernels.h"
+#include "hivis_gemm.h"
 #include "hivis_fused.h"
 #include "hivis_tree.h"
 
 #include <hip/hip_ext.h>
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -78,7 +80,6 @@ struct hivis_ctx {
     float *u = nullptr, *dout = nullptr;
     float *feat = nullptr;      // [B][max_text][d] true features of prompt text rows (prefill only)
     float *attn_ws = nullptr; size_t attn_ws_floats = 0;
-    float* zero_blk = nullptr;           // 1 KiB of zeros: the K blocks past the end in the large-tile prefill GEMM
     int* rows_cnt = nullptr; int rows_cnt_n = 0;      // arrival counters of the key-split attention launched outside a phase program (zero between launches)
     float *logits_v = nullptr, *logits_d = nullptr, *logits_p = nullptr;
     int32_t *row_tok = nullptr, *drafts = nullptr, *ttok = nullptr, *nacc = nullptr, *out_tok = nullptr, *next_tok = nullptr;
@@ -101,7 +102,6 @@ struct hivis_ctx {
     float* rope_tab = nullptr; float* pm = nullptr; int* pi = nullptr; unsigned* bar = nullptr;
     float* fattn_ws = nullptr; size_t fattn_ws_floats = 0;
     struct Program { hivis::Phase* dev = nullptr; int n = 0; std::vector<hivis::Phase>* host = nullptr; };
-    bool tall_big = true; int tall_big_fill = 70;   // prefill GEMMs: the 128 x 256 tile when its workgroups fill at least this percentage of their rounds over the CUs
     int attn_shared_min = 128;           // rows per sequence from which a causal pass uses the shared-tile attention kernel (128 rows per workgroup)
     int keys_per_split = 192;            // attention: cached keys per workgroup (one or two 16-key tiles per wavefront) before the key range is split further
     bool attn_elect = true;              // key splits merged by the workgroup that arrives last (false: by a merge launch)
@@ -454,7 +454,7 @@ int target_forward(hivis_ctx* c, int seq0, int nseq, int m, const int* base, int
             Parts pend{nullptr, 0, 0};
             for (int l = 0; l < g.n_layers; ++l)
                 if (int rc = layer_forward_wide<WT>(c, c->layers[l], c->tkv[l], c->x, pend, base, offset, seq0, nseq, m, tr, &pend)) return rc;
-            if (pend.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, pend.p, pend.n, M, g.d, g.d, c->proj, g.d);
+            if (pend.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, pend, g.d, g.d, c->proj, g.d);
             const int nout_w = M - first_out_row;
             if (nout_w > 0)
                 hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(nout_w), dim3(256), 0, c->stream, c->x + (size_t)first_out_row * g.d, g.d,
@@ -490,7 +490,7 @@ int drafter_forward(hivis_ctx* c, const float* cat, int seq0, int nseq, int m, i
         if constexpr (sizeof(WT) == 2) {
             Parts pend{nullptr, 0, 0};
             if (int rc = layer_forward_wide<WT>(c, c->draft, c->dkv, c->u, pend, c->dlen, offset, seq0, nseq, m, tr, &pend)) return rc;
-            if (pend.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, pend.p, pend.n, M, d, d, c->proj, d);
+            if (pend.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, pend, d, d, c->proj, d);
         }
     } else if (int rc = layer_forward<WT>(c, c->draft, c->dkv, c->u, nullptr, c->dlen, offset, seq0, nseq, m, max_keys, tr)) return rc;
     hipLaunchKernelGGL(add_rows_kernel, dim3(M), dim3(256), 0, c->stream, (const float*)c->u, d, (const float*)c->proj, d, out, ldo, d);
@@ -921,8 +921,6 @@ int fused_setup(hivis_ctx* c) {
     { const char* pe = getenv("HIVIS_PERSISTENT"); c->persistent = pe && pe[0] == '1'; }
     { const char* we = getenv("HIVIS_WIDE_GEMM"); c->no_wide_gemm = we && we[0] == '0'; }
     { const char* we = getenv("HIVIS_WIDE_MIN"); if (we && atoi(we) >= 1) c->wide_min = atoi(we); }
-    { const char* be = getenv("HIVIS_TALL_BIG"); if (be) c->tall_big = be[0] != '0'; }
-    { const char* be = getenv("HIVIS_TALL_BIG_FILL"); if (be && atoi(be) >= 0 && atoi(be) <= 100) c->tall_big_fill = atoi(be); }
     { const char* ke = getenv("HIVIS_ATTN_SHARED_MIN"); if (ke && atoi(ke) >= 1) c->attn_shared_min = atoi(ke); }
     { const char* ke = getenv("HIVIS_KEYS_PER_SPLIT"); if (ke && atoi(ke) >= 16) c->keys_per_split = atoi(ke); }
     { const char* ee = getenv("HIVIS_ATTN_ELECT"); if (ee) c->attn_elect = ee[0] == '1'; }
@@ -940,79 +938,84 @@ int fused_setup(hivis_ctx* c) {
 }
 
 
-// ---- whole-prompt prefill (bf16 models): tall MFMA GEMMs over all rows of a sequence --------------------------
-int tall_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy) {
-    const int kblks = K / 32, row_tiles = (M + 7) / 8, ntiles = N / 16;
-    const size_t nfrag = (size_t)row_tiles * kblks * 64;
-    // A == nullptr: the producing row kernel has already written the fragments to c->pf_frag
-    if (A) hipLaunchKernelGGL(pack_afrag_kernel, dim3((unsigned)std::min<size_t>((nfrag + 255) / 256, 65535)), dim3(256), 0, c->stream, A, lda, M, kblks, c->pf_frag);
-    // LDS-tiled kernel: 64 real rows x 256 columns per workgroup when that still gives >= 2 workgroups per CU, else x 128
-    const int macro_rows = (row_tiles + 7) / 8;
-    // grid: (column blocks rounded up to a multiple of the 8 XCDs) x row blocks, 1-D (see the kernel's mapping)
-    // large tile (128 real rows x 256 columns, one workgroup per CU) where it fills the CUs in whole rounds well enough
-    {
-        const int big_rows = (row_tiles + 15) / 16, big_cols = (ntiles + 15) / 16;
-        const long wgs = (long)big_rows * big_cols;
-        const long rounds = (wgs + c->num_cu - 1) / c->num_cu;
-        // rows padded to 128 must not waste more than rows padded to 64 would (832 rows: 7.7% against 0)
-        const bool rows_ok = c->tall_big_fill == 0 || big_rows * 128 - M <= macro_rows * 64 - M + M / 32;
-        if (c->tall_big && M >= 128 && rows_ok && wgs * 100 >= rounds * c->num_cu * c->tall_big_fill) {
-            static bool attr = false;
-            if (!attr) { HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_big_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, 3 * 32 * 1024)); attr = true; }
-            // patches of RB x CB blocks, dealt to the 8 XCDs (the kernel's mapping)
-            const int npr = (big_rows + 7) / 8, RB = (big_rows + npr - 1) / npr, CB = std::max(1, 32 / RB);
-            const int npatch = ((big_rows + RB - 1) / RB) * ((big_cols + CB - 1) / CB);
-            const int grid = ((npatch + 7) / 8) * 8 * RB * CB;
-            hipLaunchKernelGGL((gemm_tall_big_kernel<8>), dim3(grid), dim3(256), 3 * 32 * 1024, c->stream,
-                               (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, (const v4u_t*)c->zero_blk);
-            HIP_TRY(c, hipGetLastError());
-            return HIVIS_OK;
+// ---- GEMMs on activation fragments (bf16 models) --------------------------------------------------------------
+// K-slice partials of a GEMM (kept and grown on demand)
+int splitk_space(hivis_ctx* c, size_t floats) {
+    if (floats <= c->splitk_floats) return HIVIS_OK;
+    if (int rc = dev_alloc(c, &c->splitk_ws, floats)) return rc;
+    c->splitk_floats = floats;
+    return HIVIS_OK;
+}
+void launch_pack(hivis_ctx* c, const float* A, int lda, int M, int kblks) {
+    const size_t chunks = (size_t)((M + 15) / 16) * kblks * 64;
+    hipLaunchKernelGGL(pack_afrag_kernel, dim3((unsigned)std::min<size_t>((chunks + 255) / 256, 65535)), dim3(256), 0, c->stream, A, lda, M, kblks, c->pf_frag);
+}
+
+// Column tiles per wavefront and K slices of a tall GEMM: the pair with the least estimated time.  A workgroup (one per CU)
+// takes 0.066 us per K block and column tile when it runs alone and about 1.3 times that when all CUs work (the card's
+// power limit), plus 7 us to start and finish; slices cost their partial sums, written once and read once.  (Measured at 640 rows,
+// K = 4096: 22016 columns 430 tiles 181 us / 495 tiles 172 us / 575 tiles, a third round, 205 us; 4096 columns as 80 tiles 75 us,
+// as 3 x 80 tiles 39 us.)
+struct TallPlan { int cw, ksplit; };
+TallPlan tall_plan(const hivis_ctx* c, int M, int kblks, int ntiles, bool may_split) {
+    TallPlan best{8, 1};
+    double best_us = 1e30;
+    const int nrow = (M + TALL_ROWS - 1) / TALL_ROWS;
+    for (int cw = 8; cw >= 6; --cw)
+        for (int S = 1; S <= (may_split ? 8 : 1); ++S) {
+            const int kper = (kblks + S - 1) / S;
+            if (S > 1 && ((S - 1) * kper >= kblks || kper < 8)) continue;        // no empty slice, no tiny ones
+            const double tiles = (double)nrow * ((ntiles + 2 * cw - 1) / (2 * cw)) * S;
+            const double rounds = std::ceil(tiles / c->num_cu), fill = tiles / (rounds * c->num_cu);
+            double us = rounds * (kper * 0.066 * cw * (0.8 + 0.5 * fill) + 7.0);
+            if (S > 1) us += 2.0 * S * M * ntiles * 16 * 4.0 / 4.0e6;
+            if (us < best_us - 1e-9) { best_us = us; best = {cw, S}; }
         }
-    }
-    if ((size_t)macro_rows * ((ntiles + 15) / 16) >= (size_t)2 * c->num_cu) {
-        const int ncol8 = (((ntiles + 15) / 16) + 7) & ~7;
-        hipLaunchKernelGGL((gemm_tall_lds_kernel<8>), dim3(ncol8 * macro_rows), dim3(256), 2 * 24 * 1024, c->stream,
-                           (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, 1, (float*)nullptr);
-    } else {
-        const int ncol8 = (((ntiles + 7) / 8) + 7) & ~7;
-        hipLaunchKernelGGL((gemm_tall_lds_kernel<4>), dim3(ncol8 * macro_rows), dim3(256), 2 * 16 * 1024, c->stream,
-                           (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, 1, (float*)nullptr);
-    }
+    return best;
+}
+
+// M rows (any number) x N columns.  A == nullptr: the producing row kernel has already written the fragments to c->pf_frag.
+// defer != nullptr: K slices may be used, and *defer describes the result for the consuming row kernel (slices or Y).
+int tall_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer = nullptr) {
+    const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;
+    if (A) launch_pack(c, A, lda, M, kblks);
+    const TallPlan pl = tall_plan(c, M, kblks, ntiles, defer != nullptr);
+    if (pl.ksplit > 1) { if (int rc = splitk_space(c, (size_t)pl.ksplit * M * ldy)) return rc; }
+    const int nrow = (row_tiles + TALL_ROWS / 16 - 1) / (TALL_ROWS / 16), tiles = nrow * ((ntiles + 2 * pl.cw - 1) / (2 * pl.cw)) * pl.ksplit;
+#define HIVIS_TALL(CW_)                                                                                                              \
+    hipLaunchKernelGGL((gemm_tall_kernel<CW_>), dim3(8 * ((tiles + 7) / 8)), dim3(TALL_THREADS), tall_lds_bytes<CW_>(), c->stream,   \
+                       (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, pl.ksplit, c->splitk_ws)
+    if (pl.cw == 8) HIVIS_TALL(8);
+    else if (pl.cw == 7) HIVIS_TALL(7);
+    else HIVIS_TALL(6);
+#undef HIVIS_TALL
+    if (defer) *defer = Parts{pl.ksplit > 1 ? c->splitk_ws : Y, pl.ksplit, (size_t)M * ldy};
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
 
-// 33..64 rows (tree verify) in ONE pass over the weights: the LDS-tiled MFMA kernel of the prefill with the K range cut
-// into slices, so that a few hundred workgroups stream the weights (a workgroup owns 64 rows x 128 columns x one slice;
-// the activation fragments it needs are re-read by the column blocks only, not by every workgroup as in the skinny kernel).
-// A == nullptr: the fragments are already in c->pf_frag (written by the producing row kernel).  defer != nullptr: the
-// slice partials are not reduced here; *defer describes them for the consuming row kernel.
+// 11..64 rows in ONE pass over the weights (gemm_wide_kernel).  A == nullptr: the fragments are already in c->pf_frag
+// (written by the producing row kernel).  defer != nullptr: the slice partials are not reduced here; *defer describes
+// them for the consuming row kernel.
 int wide_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer) {
-    const int kblks = K / 32, row_tiles = (M + 7) / 8, ntiles = N / 16;
-    const size_t nfrag = (size_t)row_tiles * kblks * 64;
-    if (A) hipLaunchKernelGGL(pack_afrag_kernel, dim3((unsigned)std::min<size_t>((nfrag + 255) / 256, 65535)), dim3(256), 0, c->stream, A, lda, M, kblks, c->pf_frag);
-    const int ncol = (ntiles + 7) / 8, ncol8 = (ncol + 7) & ~7;         // 8 column tiles per workgroup
+    const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;
+    if (A) launch_pack(c, A, lda, M, kblks);
+    const int ncol = (ntiles + 7) / 8;                                  // 8 column tiles per workgroup
     // about 3 workgroups per CU and at most 16 slices (swept at 61 rows: 256/384/512/768/1024 workgroups, 8/16 slices;
     // 256-column tiles with half the slices were no faster, at 61 rows and at 32)
     int S = std::max(1, std::min(16, 3 * c->num_cu / ncol));
     while (S > 1 && ((S - 1) * ((kblks + S - 1) / S) >= kblks || (kblks + S - 1) / S < 4)) --S;     // no empty slice, >= 4 K blocks each
-    float* part = nullptr;
-    if (S > 1) {
-        const size_t need = (size_t)S * M * ldy;
-        if (need > c->splitk_floats) {
-            if (int rc = dev_alloc(c, &c->splitk_ws, need)) return rc;
-            c->splitk_floats = need;
-        }
-        part = c->splitk_ws;
-    }
-    if (row_tiles <= 4)      // at most 32 rows: 4 row tiles per workgroup, half the fragment traffic and MFMA work
-        hipLaunchKernelGGL((gemm_tall_lds_kernel<4, 4, 2>), dim3(ncol8 * S), dim3(256), 2 * 12 * 1024, c->stream,
+    if (S > 1) { if (int rc = splitk_space(c, (size_t)S * M * ldy)) return rc; }
+    float* part = S > 1 ? c->splitk_ws : nullptr;
+    if (row_tiles <= 2)      // at most 32 rows: 2 row tiles per workgroup, half the fragment traffic and MFMA work
+        hipLaunchKernelGGL((gemm_wide_kernel<1>), dim3(ncol * S), dim3(256), 2 * 12 * 1024, c->stream,
                            (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
     else
-        hipLaunchKernelGGL((gemm_tall_lds_kernel<4, 4>), dim3(ncol8 * S), dim3(256), 2 * 16 * 1024, c->stream,
+        hipLaunchKernelGGL((gemm_wide_kernel<2>), dim3(ncol * S), dim3(256), 2 * 16 * 1024, c->stream,
                            (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
-    if (defer) { defer->p = S > 1 ? part : Y; defer->n = S; defer->stride = (size_t)M * ldy; }
-    else if (S > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, (const float*)part, S, M, N, ldy, Y, ldy);
+    const Parts res{S > 1 ? part : Y, S, (size_t)M * ldy};
+    if (defer) *defer = res;
+    else if (S > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, res, N, ldy, Y, ldy);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
@@ -1025,7 +1028,7 @@ int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* 
     typedef typename KVType<WT>::type KT;
     const hivis_config& g = c->cfg;
     const int M = nseq * m, d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, F = g.ffn;
-    const int nqkv = qd + 2 * kd, Mp = ((M + 7) / 8) * 8;
+    const int nqkv = qd + 2 * kd, Mp = ((M + 15) / 16) * 16;
     Parts pq{}, po{}, pg{};
     hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, h, d, pending, d, M, (const WT*)L.norm1, c->pf_frag, d, g.rms_eps);
     if (int rc = wide_gemm(c, nullptr, 0, M, d, L.wqkv, nqkv, c->qkv, nqkv, &pq)) return rc;
@@ -1038,9 +1041,17 @@ int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* 
     if (int rc = wide_gemm(c, att_frag ? nullptr : c->att, qd, M, qd, L.wo, d, c->proj, d, &po)) return rc;
     hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, h, d, po, d, M, (const WT*)L.norm2, c->pf_frag, d, g.rms_eps);
     if (int rc = wide_gemm(c, nullptr, 0, M, d, L.wgu, 2 * F, c->gu, 2 * F, &pg)) return rc;
-    hipLaunchKernelGGL(wide_silu_frag_kernel, dim3(Mp / 8, std::min(64, (F / 8 + 31) / 32)), dim3(256), 0, c->stream, pg, M, F, c->pf_frag);
+    hipLaunchKernelGGL(wide_silu_frag_kernel, dim3(Mp / 16, std::min(64, (F / 8 + 15) / 16)), dim3(256), 0, c->stream, pg, M, F, c->pf_frag);
     if (int rc = wide_gemm(c, nullptr, 0, M, F, L.wd, d, c->proj, d, out_pending)) return rc;
     HIP_TRY(c, hipGetLastError());
+    return HIVIS_OK;
+}
+
+// the tall GEMM kernels use more LDS than a launch gets without asking
+int tall_setup(hivis_ctx* c) {
+    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<8>()));
+    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<7>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<7>()));
+    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<6>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<6>()));
     return HIVIS_OK;
 }
 
@@ -1049,36 +1060,40 @@ int prefill_target_tall(hivis_ctx* c, int b, int v, int l) {
     typedef typename KVType<WT>::type KT;
     const hivis_config& g = c->cfg;
     const int M = v + l, d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, F = g.ffn, nqkv = qd + 2 * kd;
-    const int Mp = ((M + 7) / 8) * 8;
+    const int Mp = ((M + 15) / 16) * 16;
     hipLaunchKernelGGL((prefill_rows_kernel<WT>), dim3(M), dim3(256), 0, c->stream, (const WT*)c->vis + (size_t)b * g.max_vis * d, v,
                        (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), 0, c->pf_x, d);
-    const float* pending = nullptr;
+    Parts pend{nullptr, 0, 0}, proj{};
     for (int l_ = 0; l_ < g.n_layers; ++l_) {
         const LayerDev& L = c->layers[l_];
         const KVDev& kv = c->tkv[l_];
-        // residual add + RMSNorm write the GEMM's A fragments directly (rows padded to whole tiles), SiLU * up likewise
-        const bool direct = d <= 8192 && d % 8 == 0 && F % 32 == 0;
-        const Parts pend{pending, 1, 0};
+        // residual add + RMSNorm write the GEMM's A fragments directly (rows padded to whole tiles), SiLU * up likewise; the
+        // O and down projections come as K slices, which the residual add sums.  (Rows wider than the norm kernel's registers:
+        // the row kernels of the decode passes, one result each.)
+        const bool direct = d <= 8192;
         if (direct) hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, c->pf_x, d, pend, d, M, (const WT*)L.norm1, c->pf_frag, d, g.rms_eps);
-        else hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, c->stream, c->pf_x, d, pending, d, (const WT*)L.norm1, c->pf_a, d, d, g.rms_eps);
+        else hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, c->stream, c->pf_x, d, pend.p, d, (const WT*)L.norm1, c->pf_a, d, d, g.rms_eps);
         if (int rc = tall_gemm(c, direct ? nullptr : c->pf_a, d, M, d, L.wqkv, nqkv, c->pf_qkv, nqkv)) return rc;
         hipLaunchKernelGGL((rope_append_kernel<KT>), dim3(M, row_chunks(M)), dim3(256), 0, c->stream, c->pf_qkv, g.n_q_heads, g.n_kv_heads, g.head_dim, (const int*)c->zeros, 0, b, M, (KT*)kv.k, (KT*)kv.v, kv.maxL, g.rope_theta, (const int*)nullptr, (const float*)L.bqkv, (const float*)c->rope_tab, g.max_vis + g.max_text);
         if (c->fused) { if (int rc = attention_rows_mfma<WT>(c, c->pf_qkv, nqkv, kv, c->zeros, 0, b, 1, M, c->pf_att, qd)) return rc; }
         else if (int rc = attention<WT>(c, c->pf_qkv, nqkv, kv, c->zeros, 0, b, 1, M, M, c->pf_att, qd)) return rc;
-        if (int rc = tall_gemm(c, c->pf_att, qd, M, qd, L.wo, d, c->pf_proj, d)) return rc;
-        const Parts proj{c->pf_proj, 1, 0};
+        if (int rc = tall_gemm(c, c->pf_att, qd, M, qd, L.wo, d, c->pf_proj, d, direct ? &proj : nullptr)) return rc;
         if (direct) hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, c->pf_x, d, proj, d, M, (const WT*)L.norm2, c->pf_frag, d, g.rms_eps);
         else hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, c->stream, c->pf_x, d, (const float*)c->pf_proj, d, (const WT*)L.norm2, c->pf_a, d, d, g.rms_eps);
         if (int rc = tall_gemm(c, direct ? nullptr : c->pf_a, d, M, d, L.wgu, 2 * F, c->pf_gu, 2 * F)) return rc;
         if (direct) {
             const Parts gu{c->pf_gu, 1, 0};
-            hipLaunchKernelGGL(wide_silu_frag_kernel, dim3(Mp / 8, std::min(64, (F / 8 + 31) / 32)), dim3(256), 0, c->stream, gu, M, F, c->pf_frag);
+            hipLaunchKernelGGL(wide_silu_frag_kernel, dim3(Mp / 16, std::min(64, (F / 8 + 15) / 16)), dim3(256), 0, c->stream, gu, M, F, c->pf_frag);
         } else hipLaunchKernelGGL(silu_mul_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, (const float*)c->pf_gu, c->pf_act, F);
-        if (int rc = tall_gemm(c, direct ? nullptr : c->pf_act, F, M, F, L.wd, d, c->pf_proj, d)) return rc;
-        pending = c->pf_proj;
+        pend = Parts{c->pf_proj, 1, 0};
+        if (int rc = tall_gemm(c, direct ? nullptr : c->pf_act, F, M, F, L.wd, d, c->pf_proj, d, direct ? &pend : nullptr)) return rc;
+    }
+    if (pend.n > 1) {       // only the text rows' sums are needed
+        const Parts text{pend.p + (size_t)v * d, pend.n, pend.stride};
+        hipLaunchKernelGGL(splitk_reduce_kernel, dim3(l, row_chunks(l)), dim3(256), 0, c->stream, text, d, d, c->pf_proj + (size_t)v * d, d);
     }
     // features of the text rows: final norm of (x + last MLP delta)
-    hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(l), dim3(256), 0, c->stream, c->pf_x + (size_t)v * d, d, pending + (size_t)v * d, d,
+    hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(l), dim3(256), 0, c->stream, c->pf_x + (size_t)v * d, d, (const float*)c->pf_proj + (size_t)v * d, d,
                        (const WT*)c->final_norm, c->feat + (size_t)b * g.max_text * d, d, d, g.rms_eps);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
@@ -1534,8 +1549,6 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     if ((rc = dev_alloc(c, &c->tlen, B))) return rc;
     if ((rc = dev_alloc(c, &c->dlen, B))) return rc;
     if ((rc = dev_alloc(c, &c->zeros, B))) return rc;
-    if ((rc = dev_alloc(c, &c->zero_blk, 256))) return rc;
-    HIP_TRY(c, hipMemset(c->zero_blk, 0, 256 * sizeof(float)));
     HIP_TRY(c, hipMemset(c->zeros, 0, B * sizeof(int)));
     if ((rc = dev_alloc(c, &c->text, (size_t)B * c->text_stride))) return rc;
     HIP_TRY(c, hipMemset(c->text, 0, (size_t)B * c->text_stride * sizeof(int32_t)));
@@ -1553,7 +1566,8 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     if ((rc = dev_alloc(c, &c->dout, (size_t)R * d))) return rc;
     if ((rc = dev_alloc(c, &c->feat, (size_t)B * g.max_text * d))) return rc;
     if (sizeof(WT) == 2) {
-        const int PR = (g.max_vis + g.max_text + 7) & ~7;
+        if ((rc = tall_setup(c))) return rc;
+        const int PR = (g.max_vis + g.max_text + 15) & ~15;        // whole row tiles
         c->pf_rows = PR;
         const size_t kmax = std::max({(size_t)d, (size_t)qd, (size_t)F});
         if ((rc = dev_alloc(c, &c->pf_x, (size_t)PR * d))) return rc;

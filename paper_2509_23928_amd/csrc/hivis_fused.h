@@ -18,7 +18,7 @@
 // (drafted token ids) are read with agent-scope loads.
 #pragma once
 #include <type_traits>
-#include "hivis_kernels.h"
+#include "hivis_gemm.h"
 
 namespace hivis {
 
@@ -747,8 +747,8 @@ __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, in
     lds_barrier();
     HIVIS_AMARK(4)
     if (sh.nsplit == 1 && frag_out != nullptr) {
-        // the attention rows go straight out as A fragments of the O projection (K = ldo, bf16 hi/lo split, layout of
-        // pack_afrag_kernel): 8 consecutive dims of one row per thread and trip
+        // the attention rows go straight out as activation fragments of the O projection (K = ldo; layout: hivis_gemm.h):
+        // 8 consecutive dims of one row per thread and trip
         for (int idx = threadIdx.x; idx < R * (HD / 8); idx += FUSED_NT) {
             const int r = idx / (HD / 8), c0 = (idx % (HD / 8)) * 8;
             float mx = -INFINITY;

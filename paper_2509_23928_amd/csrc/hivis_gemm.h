@@ -1,0 +1,331 @@
+// Dense MFMA GEMM of the prefill (hundreds to thousands of activation rows, bf16 weights) and its operand layout.
+#pragma once
+#include "hivis_kernels.h"
+
+namespace hivis {
+
+// ------------------------------------------------------------------------------------------
+// Activation fragments.  Every fp32 activation is split into a bf16 high and a bf16 low part (about 16 mantissa bits).  A
+// row tile holds 16 rows; for each block of 32 k-values it has one 1 KiB fragment block of high parts followed by one of
+// low parts:
+//   frag[((row / 16) * kblks + k / 32) * 2 + part][lane] (16 bytes), lane = row % 16 + 16 * ((k / 8) % 4), 8 k-values each
+// which is the operand layout of the 16x16x32 MFMA and the mirror image of the weights' streaming layout.  Both parts are
+// multiplied into the SAME accumulators, so a wavefront's 128 accumulator registers cover 64 x 128 real outputs and one
+// weight fragment serves two MFMAs per row tile.
+// ------------------------------------------------------------------------------------------
+__device__ __forceinline__ size_t afrag_at(int kblks, int row, int k) {
+    return (((size_t)(row >> 4) * kblks + (k >> 5)) * 2) * 64 + (row & 15) + 16 * ((k >> 3) & 3);
+}
+// 8 consecutive values x[0..8) of row `row` at k (a multiple of 8) -> the high and the low chunk
+__device__ __forceinline__ void store_afrag8(uint4* __restrict__ frag, int kblks, int row, int k, const float (&x)[8], bool zero) {
+    const size_t at = afrag_at(kblks, row, k);
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        f32_to_bf16x2_hilo(x[2 * e], x[2 * e + 1], hi[e], lo[e]);
+        if (zero) { hi[e] = 0u; lo[e] = 0u; }
+    }
+    frag[at] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    frag[at + 64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+}
+
+// rows of fp32 -> fragments; rows >= M of the last row tile become zeros
+__global__ void pack_afrag_kernel(const float* __restrict__ A, int lda, int M, int kblks, uint4* __restrict__ out) {
+    const size_t total = (size_t)((M + 15) / 16) * 16 * kblks * 4;        // one thread per chunk of 8 values
+    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
+        // 16 rows x 4 chunks of one K block are one 1 KiB block: consecutive threads write consecutive 16-byte pieces
+        const int i = (int)(idx & 15), g = (int)((idx >> 4) & 3);
+        const size_t blk = idx >> 6;
+        const int kb = (int)(blk % (size_t)kblks), row = (int)(blk / (size_t)kblks) * 16 + i, k = kb * 32 + g * 8;
+        const float4* p = reinterpret_cast<const float4*>(A + (size_t)min(row, M - 1) * lda + k);
+        const float4 x0 = p[0], x1 = p[1];
+        const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+        store_afrag8(out, kblks, row, k, x, row >= M);
+    }
+}
+
+// A GEMM result as K-slice partials: value = sum over s < n of p[s * stride + index], in that order
+struct Parts { const float* p; int n; size_t stride; };
+
+// B slices per trip, their loads issued together (a one-load-per-trip loop costs a memory round trip per slice)
+template <int B>
+__device__ __forceinline__ void parts_add(float4& a, const Parts& ps, size_t idx, int s0) {
+    for (int s = s0; s < ps.n; s += B) {
+        float4 v[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) v[j] = *reinterpret_cast<const float4*>(ps.p + (size_t)min(s + j, ps.n - 1) * ps.stride + idx);
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+            if (s + j < ps.n) { a.x += v[j].x; a.y += v[j].y; a.z += v[j].z; a.w += v[j].w; }
+    }
+}
+__device__ __forceinline__ float4 parts_load4(const Parts& ps, size_t idx) {
+    float4 a = *reinterpret_cast<const float4*>(ps.p + idx);
+    if (ps.n <= 4) parts_add<3>(a, ps, idx, 1);       // slices 1..3 in one trip
+    else parts_add<8>(a, ps, idx, 1);
+    return a;
+}
+
+// Y[r][c] = sum of the partials, rows gridDim.x, c < N (N a multiple of 4)
+__global__ void splitk_reduce_kernel(Parts ps, int N, int ldp, float* __restrict__ Y, int ldy) {
+    const int row = blockIdx.x;
+    for (int c4 = blockIdx.y * blockDim.x + threadIdx.x; c4 < N / 4; c4 += gridDim.y * blockDim.x)
+        *reinterpret_cast<float4*>(Y + (size_t)row * ldy + 4 * c4) = parts_load4(ps, (size_t)row * ldp + 4 * c4);
+}
+
+typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
+
+// One 1 KiB block from memory straight to LDS (no registers): lane l's 16 bytes go to lds[l].
+__device__ __forceinline__ void block_to_lds(const v4u_t* src, v4u_t* lds) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
+// ------------------------------------------------------------------------------------------
+// Tall GEMM: 128 rows x 32 CW columns per workgroup of 8 wavefronts.  They are two groups of four, one wavefront of each
+// group per SIMD; the first group multiplies the even K blocks of the tile, the second the odd ones, and at the end they
+// exchange halves of their sums through LDS.  The groups work in opposite phases separated by barriers: while one multiplies
+// a K block (8 CW MFMAs per wavefront, operands in registers), the other reads its next fragments from LDS and
+// requests a later block, so the matrix pipeline of every SIMD always has a wavefront that issues nothing but MFMAs.
+// Blocks go from memory to LDS directly (they are in fragment order already) into a ring of four K blocks.  A wavefront
+// owns 64 rows x 16 CW columns: 4 x CW accumulator tiles; the weights are the MFMA's A operand, so that a lane ends up with
+// four consecutive columns of one row.
+// Matrix bound: with random data the MFMAs alone run at 2.0 PFLOP/s on this card (2.46 on zeros, it is power that
+// limits them), a library product of 8192^3 at 1.10.  640 rows, K = 4096, high and low parts counted: 22016 columns 249 ->
+// 172 us (1.35 PFLOP/s), 12288 columns 127 -> 94 us (1.37); 3008 x 22016: 1090 -> 813 us (1.33).  The version with the requests
+// at the head of the multiplication phase took 203 and 107 us; groups owning row halves instead of K blocks (256-row
+// tiles) were no faster at 3008 rows and left too few tiles at 640.
+// ------------------------------------------------------------------------------------------
+constexpr int TALL_THREADS = 512, TALL_ROWS = 128;
+template <int CW> constexpr int tall_lds_bytes() { return 4 * (16 + 2 * CW) * 1024; }
+
+#define HIVIS_PHASE_END(wait_)                               \
+    do {                                                     \
+        __builtin_amdgcn_sched_barrier(0);                   \
+        asm volatile("s_waitcnt " wait_ "\n\ts_barrier" ::: "memory"); \
+        __builtin_amdgcn_sched_barrier(0);                   \
+    } while (0)
+
+// ksplit > 1: the K range is cut into slices, slice s writes its sums to part[s][M][ldy] and the consumer adds them
+template <int CW>
+__global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t* __restrict__ Af, int row_tiles, int kblks,
+                                                                   const v4u_t* __restrict__ Wp, int ntiles, float* __restrict__ Y, int ldy,
+                                                                   int M, int ksplit, float* __restrict__ part) {
+    constexpr int RT = TALL_ROWS / 16, CT = 2 * CW;       // row and column tiles of the workgroup
+    constexpr int NA = 2 * RT, NBLK = NA + CT;            // blocks of one K block
+    constexpr int PER = (NBLK + 3) / 4;                   // blocks each wavefront of a group fetches per K block
+    static_assert(PER == 7 || PER == 8, "the counted waits below");
+    extern __shared__ __align__(16) v4u_t tall_lds[];     // [4 K blocks][NBLK][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wave >> 2, w4 = wave & 3;
+    // Tiles are numbered so that neighbours share operands (up to 8 row blocks of one column block, then the next column
+    // block; K slices outermost) and every XCD (workgroup L runs on XCD L % 8) takes one contiguous range of them: its L2
+    // sees a compact patch of row and column blocks.
+    const int ncol = (ntiles + CT - 1) / CT, nrow = (row_tiles + RT - 1) / RT;
+    const int total = ncol * nrow * ksplit, chunk = (total + 7) / 8;
+    const int slot = blockIdx.x / 8, id = (blockIdx.x % 8) * chunk + slot;
+    if (slot >= chunk || id >= total) return;
+    const int split = id / (ncol * nrow), tid = id % (ncol * nrow);
+    const int npanel = (nrow + 7) / 8, prows = (nrow + npanel - 1) / npanel;
+    const int panel = tid / (prows * ncol), inp = tid - panel * prows * ncol, pr = min(prows, nrow - panel * prows);
+    const int rblk = panel * prows + inp % pr, cblk = inp / pr;
+    const int kper = (kblks + ksplit - 1) / ksplit, kbeg = split * kper, nkb = min(kblks, kbeg + kper) - kbeg;
+    if (ksplit > 1) Y = part + (size_t)split * M * ldy;
+    const int rt_wg = rblk * RT, ct_wg = cblk * CT;
+
+    // the blocks this wavefront fetches per K block: id b < NA is the high / low part b & 1 of row tile b / 2, else column
+    // tile b - NA (tiles outside the matrix are replaced by the last one: their results are not stored)
+    const v4u_t* src[PER];
+    int inc[PER], dst[PER];                               // distance to the same block of the next K block; place in the stage
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int b = min(w4 + 4 * i, NBLK - 1);
+        const bool isa = b < NA;
+        src[i] = isa ? Af + (((size_t)min(rt_wg + (b >> 1), row_tiles - 1) * kblks + kbeg) * 2 + (b & 1)) * 64
+                     : Wp + ((size_t)min(ct_wg + (b - NA), ntiles - 1) * kblks + kbeg) * 64;
+        inc[i] = isa ? 128 : 64;
+        dst[i] = b * 64;
+    }
+#define HIVIS_TALL_FETCH(kb_)                                                                                      \
+    do {                                                                                                           \
+        v4u_t* to_ = tall_lds + (size_t)((kb_) & 3) * NBLK * 64;                                                    \
+        _Pragma("unroll") for (int i = 0; i < PER; ++i) block_to_lds(src[i] + (size_t)(kb_) * inc[i] + lane, to_ + dst[i]); \
+    } while (0)
+    // step s of group g is K block 2 s + g
+    const int nsteps = (nkb + 1) / 2, mine = (nkb + 1 - grp) / 2;
+    if (grp == 1) {
+        HIVIS_TALL_FETCH(0);
+        if (nkb > 2) HIVIS_TALL_FETCH(2);
+    } else if (nkb > 1) HIVIS_TALL_FETCH(1);
+
+    f32x4_t acc[4][CW];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < CW; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int wr = w4 >> 1, wc = w4 & 1;                  // this wavefront's 4 row tiles and CW column tiles
+    v4u_t fa[2][4], fb[CW];
+
+    HIVIS_PHASE_END("vmcnt(0)");
+    if (grp == 1) HIVIS_PHASE_END("lgkmcnt(0)");          // the second group runs one phase behind
+    for (int s = 0; s < nsteps; ++s) {
+        // Memory phase: the fragments of this step, then the request for a block of the OTHER group, whose stage that group
+        // read one phase ago.  The block requested in this group's previous memory phase has had three phases to arrive; it is
+        // waited for here, one phase before the other group reads it.
+        if (s < mine) {
+            const v4u_t* at = tall_lds + (size_t)((2 * s + grp) & 3) * NBLK * 64 + lane;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { fa[0][r] = at[(size_t)(2 * (wr * 4 + r)) * 64]; fa[1][r] = at[(size_t)(2 * (wr * 4 + r) + 1) * 64]; }
+#pragma unroll
+            for (int c = 0; c < CW; ++c) fb[c] = at[(size_t)(NA + wc * CW + c) * 64];
+        }
+        const int nk = 2 * s + 3 + grp;
+        __builtin_amdgcn_sched_barrier(0);
+        if (nk < nkb) {
+            HIVIS_TALL_FETCH(nk);
+            if constexpr (PER == 7) HIVIS_PHASE_END("vmcnt(7) lgkmcnt(0)"); else HIVIS_PHASE_END("vmcnt(8) lgkmcnt(0)");
+        } else HIVIS_PHASE_END("vmcnt(0) lgkmcnt(0)");
+        // multiplication phase
+        if (s < mine) {
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int c = 0; c < CW; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[c]), __builtin_bit_cast(bf16x8_t, fa[p][r]), acc[r][c], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+        }
+        HIVIS_PHASE_END("lgkmcnt(0)");
+    }
+    if (grp == 0) HIVIS_PHASE_END("lgkmcnt(0)");
+#undef HIVIS_TALL_FETCH
+
+    // the groups swap halves of their partial sums: group 0 finishes column tiles [0, CH), group 1 the rest
+    constexpr int CH = (CW + 1) / 2;
+    v4u_t* ex = tall_lds + lane;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < CW; ++c)
+            if ((c < CH) == (grp == 1)) ex[(size_t)((w4 * 4 + r) * CW + c) * 64] = __builtin_bit_cast(v4u_t, acc[r][c]);
+    HIVIS_PHASE_END("lgkmcnt(0)");
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < CW; ++c)
+            if ((c < CH) == (grp == 0)) acc[r][c] += __builtin_bit_cast(f32x4_t, ex[(size_t)((w4 * 4 + r) * CW + c) * 64]);
+    const int row0 = (rt_wg + wr * 4) * 16 + (lane & 15), col0 = (ct_wg + wc * CW) * 16 + 4 * (lane >> 4);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = row0 + 16 * r;
+        if (row >= M) continue;
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+            if ((c < CH) != (grp == 0) || ct_wg + wc * CW + c >= ntiles) continue;
+            *reinterpret_cast<f32x4_t*>(Y + (size_t)row * ldy + col0 + 16 * c) = acc[r][c];
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// Wide GEMM (9..64 activation rows: the weights are streamed once).  A workgroup of 2 x 2 wavefronts computes 2 RTW row
+// tiles (32 or 64 rows) x 128 columns of one K slice: slice s writes its partial sums to part[s][M][ldy] and the
+// consuming row kernel adds them.  Per K block the workgroup copies its blocks from memory to LDS through registers,
+// NSET K blocks ahead (the bytes in flight per workgroup set the bandwidth); two LDS stages, one LDS-only barrier per block.
+// ------------------------------------------------------------------------------------------
+template <int RTW>
+__global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const v4u_t* __restrict__ Af, int row_tiles, int kblks,
+                                                          const v4u_t* __restrict__ Wp, int ntiles, float* __restrict__ Y,
+                                                          int ldy, int M, int ksplit, float* __restrict__ part) {
+    constexpr int CTW = 4, NSET = 4;
+    constexpr int NA = 4 * RTW, NB = 2 * CTW, NBLK = NA + NB;     // (a row tile is a high and a low block)
+    constexpr int PER_WAVE = NBLK / 4;
+    static_assert(NBLK % 4 == 0, "blocks are dealt evenly to the 4 wavefronts");
+    extern __shared__ __align__(16) v4u_t tall_lds[];      // [2 stages][NBLK][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave >> 1, wc = wave & 1;
+    // the K slices of a column block on different XCDs, neighbouring column blocks on one
+    const int ncol = (ntiles + NB - 1) / NB;
+    const int split = blockIdx.x % ksplit, cblk = blockIdx.x / ksplit;
+    if (cblk >= ncol) return;
+    const int kper = (kblks + ksplit - 1) / ksplit, kb0 = split * kper;
+    const int nkb = min(kblks, kb0 + kper) - kb0;            // >= 1: the host picks ksplit so that no slice is empty
+    if (nkb <= 0) return;
+    if (ksplit > 1) Y = part + (size_t)split * M * ldy;
+    const int ct_wg = cblk * NB;
+    const v4u_t* src[PER_WAVE];
+    int inc[PER_WAVE];
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+        const int b = wave + 4 * i;
+        const bool isa = b < NA;
+        // out-of-range tiles are replaced by in-range ones (clamped index); their results are never stored
+        src[i] = (isa ? Af + (((size_t)min(b >> 1, row_tiles - 1) * kblks + kb0) * 2 + (b & 1)) * 64
+                      : Wp + ((size_t)min(ct_wg + (b - NA), ntiles - 1) * kblks + kb0) * 64) + lane;
+        inc[i] = isa ? 128 : 64;
+    }
+    f32x4_t acc[RTW][CTW];
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+        for (int c = 0; c < CTW; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    v4u_t st[NSET][PER_WAVE];
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) st[0][i] = src[i][0];
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) tall_lds[(size_t)(wave + 4 * i) * 64 + lane] = st[0][i];
+#pragma unroll
+    for (int b = 1; b <= NSET; ++b) {
+        if (b < nkb) {
+#pragma unroll
+            for (int i = 0; i < PER_WAVE; ++i) st[b % NSET][i] = src[i][(size_t)b * inc[i]];
+        }
+    }
+    lds_barrier();
+    for (int kb0_ = 0; kb0_ < nkb; kb0_ += NSET) {
+#pragma unroll
+        for (int u = 0; u < NSET; ++u) {
+            // one K block: multiply block kb from its LDS stage, park block kb+1 (register set (u+1) % NSET) in the other
+            // stage, request block kb+1+NSET into that set
+            const int kb = kb0_ + u;
+            if (kb < nkb) {
+                const v4u_t* cur = tall_lds + (size_t)(kb & 1) * NBLK * 64;
+                v4u_t* nxt = tall_lds + (size_t)((kb + 1) & 1) * NBLK * 64;
+                v4u_t a[2][RTW], b[CTW];
+#pragma unroll
+                for (int r = 0; r < RTW; ++r) { a[0][r] = cur[(size_t)(2 * (wr * RTW + r)) * 64 + lane]; a[1][r] = cur[(size_t)(2 * (wr * RTW + r) + 1) * 64 + lane]; }
+#pragma unroll
+                for (int c = 0; c < CTW; ++c) b[c] = cur[(size_t)(NA + wc * CTW + c) * 64 + lane];
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+                        for (int c = 0; c < CTW; ++c)
+                            acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[c]), __builtin_bit_cast(bf16x8_t, a[p][r]), acc[r][c], 0, 0, 0);
+                if (kb + 1 < nkb) {
+#pragma unroll
+                    for (int i = 0; i < PER_WAVE; ++i) nxt[(size_t)(wave + 4 * i) * 64 + lane] = st[(u + 1) % NSET][i];
+                    if (kb + 1 + NSET < nkb) {
+#pragma unroll
+                        for (int i = 0; i < PER_WAVE; ++i) st[(u + 1) % NSET][i] = src[i][(size_t)(kb + 1 + NSET) * inc[i]];
+                    }
+                }
+                lds_barrier();
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < RTW; ++r) {
+        const int row = (wr * RTW + r) * 16 + (lane & 15);
+        if (row >= M) continue;
+#pragma unroll
+        for (int c = 0; c < CTW; ++c) {
+            const int ct = ct_wg + wc * CTW + c;
+            if (ct < ntiles) *reinterpret_cast<f32x4_t*>(Y + (size_t)row * ldy + ct * 16 + 4 * (lane >> 4)) = acc[r][c];
+        }
+    }
+}
+
+}  // namespace hivis

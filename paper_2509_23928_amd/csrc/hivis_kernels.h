@@ -415,302 +415,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const float* __res
 }
 
 // ------------------------------------------------------------------------------------------
-// Tall GEMM for prefill (hundreds to thousands of rows; a true dense contraction -> MFMA bound).
-// The activation rows are first converted once into MFMA A fragments (bf16 hi/lo split, 8 real rows
-// per 16-row tile, same layout as load_afrag) and stored as [row tile][K block][64 lanes] x 16 bytes,
-// the mirror image of the weights' streaming layout.  Each wavefront then owns RT row tiles x CT column
-// tiles and walks K, loading RT + CT fragments (16 bytes per lane each, fully coalesced) per RT*CT MFMAs;
-// the 4 wavefronts of a workgroup form a 2 x 2 arrangement so that neighbours share fragments through L1.
-// ------------------------------------------------------------------------------------------
-__global__ void pack_afrag_kernel(const float* __restrict__ A, int lda, int M, int kblks, uint4* __restrict__ out) {
-    const int row_tiles = (M + 7) / 8;
-    const size_t total = (size_t)row_tiles * kblks * 64;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-        const int lane = (int)(idx & 63);
-        const size_t blk = idx >> 6;
-        const int kb = (int)(blk % (size_t)kblks), tt = (int)(blk / (size_t)kblks);
-        bf16x8_t f;
-        load_afrag(f, A, lda, M, tt, kb, lane);
-        out[idx] = __builtin_bit_cast(uint4, f);
-    }
-}
-
-// 8 consecutive values x[0..8) of row `row` at k0 (a multiple of 8) -> the two fragment chunks (high and low parts)
-__device__ __forceinline__ void store_afrag8(uint4* __restrict__ frag, int kblks, int row, int k0, const float (&x)[8], bool zero) {
-    const int tt = row >> 3, rr = row & 7, i_hi = 4 * (rr >> 1) + (rr & 1);
-    const size_t base = ((size_t)tt * kblks + (k0 >> 5)) * 64 + ((k0 >> 3) & 3) * 16;
-    uint32_t hi[4], lo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        f32_to_bf16x2_hilo(x[2 * e], x[2 * e + 1], hi[e], lo[e]);
-        if (zero) { hi[e] = 0u; lo[e] = 0u; }
-    }
-    frag[base + i_hi] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    frag[base + i_hi + 2] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-}
-
-// Tall GEMM of the prefill: a workgroup of 2 x 2 wavefronts computes 8 row tiles x 2*CTW column tiles (64 real rows x
-// 32*CTW columns); each wavefront owns 4 x CTW MFMA tiles.  Per K block the workgroup copies the 8 A blocks and 2*CTW B blocks
-// (1 KiB each, already in fragment order) from global memory to LDS once, and the wavefronts read their fragments with
-// 128-bit LDS reads (lane-contiguous: conflict-free), so the L1 sees each block once per workgroup instead of once per
-// wavefront (a register-only version, 8 fragment loads per 16 MFMAs per wavefront, was bound by L1 fill bandwidth).
-// Two LDS stages; the global loads of K block k+1 are in flight while block k is multiplied; one LDS-only barrier per block.
-typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
-template <int CTW, int NSET = 2, int RTW = 4>
-__global__ __launch_bounds__(256, 2) void gemm_tall_lds_kernel(const v4u_t* __restrict__ Af, int row_tiles, int kblks,
-                                                             const v4u_t* __restrict__ Wp, int ntiles, float* __restrict__ Y,
-                                                             int ldy, int M, int ksplit, float* __restrict__ part) {
-    // RTW = row tiles per wavefront: 4 (64 real rows per workgroup), or 2 for passes of at most 32 rows
-    constexpr int NA = 2 * RTW, NB = 2 * CTW;    // A / B blocks per K block and workgroup
-    constexpr int NBLK = NA + NB;
-    constexpr int PER_WAVE = NBLK / 4;           // blocks each wavefront copies per K block
-    static_assert(NBLK % 4 == 0, "blocks are dealt evenly to the 4 wavefronts");
-    extern __shared__ __align__(16) v4u_t tall_lds[];      // [2 stages][NBLK][64]
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
-    // 1-D grid, XCD-aware: workgroup L runs on XCD L % 8 (round-robin dispatch) and each XCD has its own L2.  The nrow
-    // workgroups that share one block of weight columns are given consecutive slots of ONE XCD, so the weights come
-    // from HBM once and from that L2 nrow-1 times (with a plain 2-D grid every XCD fetched its own copy: 10x the bytes).
-    // ksplit > 1 (few rows, weight-streaming regime): the K range is cut into ksplit slices, one workgroup each, so that
-    // enough workgroups stream the weights; slice s writes its partial sums to part[s][M][ldy] and a second kernel adds them.
-    const int ncol = (ntiles + NB - 1) / NB, nrow = (row_tiles + NA - 1) / NA;
-    const int split = blockIdx.x % ksplit, bid = blockIdx.x / ksplit;
-    const int xcd = bid % 8, slot = bid / 8;
-    const int cblk = 8 * (slot / nrow) + xcd, rblk = slot % nrow;
-    if (cblk >= ncol) return;
-    const int kper = (kblks + ksplit - 1) / ksplit, kb0 = split * kper;
-    const int nkb = min(kblks, kb0 + kper) - kb0;            // >= 1: the host picks ksplit so that no slice is empty
-    if (nkb <= 0) return;
-    if (ksplit > 1) Y = part + (size_t)split * M * ldy;
-    const int rt_wg = rblk * NA, ct_wg = cblk * NB;
-    // the blocks this wavefront copies: block id b = wave + 4 i; b < NA is an A block (row tile rt_wg + b), else a B block
-    const v4u_t* src[PER_WAVE];
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) {
-        const int b = wave + 4 * i;
-        // out-of-range tiles are replaced by in-range ones (clamped index); their results are never stored
-        src[i] = (b < NA) ? Af + ((size_t)min(rt_wg + b, row_tiles - 1) * kblks + kb0) * 64 + lane
-                          : Wp + ((size_t)min(ct_wg + (b - NA), ntiles - 1) * kblks + kb0) * 64 + lane;
-    }
-    f32x4_t acc[RTW][CTW];
-#pragma unroll
-    for (int r = 0; r < RTW; ++r)
-#pragma unroll
-        for (int c = 0; c < CTW; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // Global loads run NSET K blocks ahead of the multiplication: block kb+1 waits in register set (kb+1) % NSET while
-    // blocks kb+2 .. kb+NSET are in flight in the other sets.  NSET = 2 for the prefill (one block is ~0.4 us of MFMA
-    // work, a little less than an L2 round trip); NSET = 4 in the few-row weight-streaming regime, where the MFMA work
-    // per block is small and the bytes in flight per workgroup set the bandwidth.
-    v4u_t st[NSET][PER_WAVE];
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) st[0][i] = src[i][0];
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) tall_lds[(size_t)(wave + 4 * i) * 64 + lane] = st[0][i];
-#pragma unroll
-    for (int b = 1; b <= NSET; ++b) {
-        if (b < nkb) {
-#pragma unroll
-            for (int i = 0; i < PER_WAVE; ++i) st[b % NSET][i] = src[i][(size_t)b * 64];
-        }
-    }
-    lds_barrier();
-    for (int kb0_ = 0; kb0_ < nkb; kb0_ += NSET) {
-#pragma unroll
-        for (int u = 0; u < NSET; ++u) {
-            // one K block: multiply block kb from its LDS stage, park block kb+1 (register set (u+1) % NSET) in the other
-            // stage, request block kb+1+NSET into that set
-            const int kb = kb0_ + u;
-            if (kb < nkb) {
-                const v4u_t* cur = tall_lds + (size_t)(kb & 1) * NBLK * 64;
-                v4u_t* nxt = tall_lds + (size_t)((kb + 1) & 1) * NBLK * 64;
-                v4u_t a[RTW], b[CTW];
-#pragma unroll
-                for (int r = 0; r < RTW; ++r) a[r] = cur[(size_t)(wr * RTW + r) * 64 + lane];
-#pragma unroll
-                for (int c = 0; c < CTW; ++c) b[c] = cur[(size_t)(NA + wc * CTW + c) * 64 + lane];
-#pragma unroll
-                for (int r = 0; r < RTW; ++r)
-#pragma unroll
-                    for (int c = 0; c < CTW; ++c)
-                        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[r]), __builtin_bit_cast(bf16x8_t, b[c]), acc[r][c], 0, 0, 0);
-                if (kb + 1 < nkb) {
-#pragma unroll
-                    for (int i = 0; i < PER_WAVE; ++i) nxt[(size_t)(wave + 4 * i) * 64 + lane] = st[(u + 1) % NSET][i];
-                    if (kb + 1 + NSET < nkb) {
-#pragma unroll
-                        for (int i = 0; i < PER_WAVE; ++i) st[(u + 1) % NSET][i] = src[i][(size_t)(kb + 1 + NSET) * 64];
-                    }
-                }
-                lds_barrier();
-            }
-        }
-    }
-    const int j = lane & 15, a4 = lane >> 4;
-#pragma unroll
-    for (int r = 0; r < RTW; ++r) {
-        const int rt = rt_wg + wr * RTW + r;
-        if (rt >= row_tiles) continue;
-        const int row = rt * 8 + 2 * a4;
-#pragma unroll
-        for (int c = 0; c < CTW; ++c) {
-            const int ct = ct_wg + wc * CTW + c;
-            if (ct >= ntiles) continue;
-            const int col = ct * 16 + j;
-            if (row < M) Y[(size_t)row * ldy + col] = acc[r][c][0] + acc[r][c][2];
-            if (row + 1 < M) Y[(size_t)(row + 1) * ldy + col] = acc[r][c][1] + acc[r][c][3];
-        }
-    }
-}
-
-// Tall GEMM, large tile: a workgroup of 2 x 2 wavefronts computes 16 row tiles x 16 column tiles (128 real rows x 256
-// columns), each wavefront 8 x 8 MFMA tiles whose 256 accumulator registers leave room for ONE wavefront per SIMD, so
-// the wavefront has to overlap its own latencies.  Step kb (one K block): park block kb+2 in LDS (three stages), request
-// block kb+5 from memory into the register set that just became free (three sets: a block has three steps to arrive),
-// read the A fragments of block kb+1 into the second fragment set, all spread over the 64 MFMAs of block kb, whose
-// operands were read earlier; one LDS-only barrier per step.  The steps are branch-free (so that the
-// loads in flight can be counted) and unrolled by six (register sets are static); past the last K block they multiply a
-// block of zeros (`zero`, 1 KiB) instead.
-template <int CTW>
-__global__ __launch_bounds__(256, 1) void gemm_tall_big_kernel(const v4u_t* __restrict__ Af, int row_tiles, int kblks,
-                                                             const v4u_t* __restrict__ Wp, int ntiles, float* __restrict__ Y,
-                                                             int ldy, int M, const v4u_t* __restrict__ zero) {
-    constexpr int RTW = 8, NA = 2 * RTW, NB = 2 * CTW, NBLK = NA + NB, PER_WAVE = NBLK / 4;
-    static_assert(NBLK % 4 == 0, "blocks are dealt evenly to the 4 wavefronts");
-    extern __shared__ __align__(16) v4u_t big_lds[];       // [3 stages][NBLK][64]
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
-    // XCD-aware 1-D grid (workgroup L runs on XCD L % 8, one workgroup per CU, 32 CUs per XCD): the workgroups an XCD runs
-    // at one time form a compact patch of RB row blocks x CB column blocks, so that per K block the XCD's L2 is asked for
-    // RB + CB different 16 KiB operand blocks instead of ~RB * CB (with one column block per XCD, every activation block
-    // came from beyond the L2 for a single use).  The weights of a column block are then fetched by nrow / RB XCDs, which
-    // HBM has room for in this compute-bound regime.  Patch p of the (row, column) block space goes to XCD p % 8.
-    const int ncol = (ntiles + NB - 1) / NB, nrow = (row_tiles + NA - 1) / NA;
-    const int npr_ = (nrow + 7) / 8, RB = (nrow + npr_ - 1) / npr_, CB = max(1, 32 / RB), S = RB * CB;    // row blocks dealt evenly to the patches
-    const int prow = (nrow + RB - 1) / RB;
-    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    const int patch = (slot / S) * 8 + xcd, within = slot % S;
-    const int rblk = (patch % prow) * RB + within % RB, cblk = (patch / prow) * CB + within / RB;
-    if (cblk >= ncol || rblk >= nrow) return;
-    const int rt_wg = rblk * NA, ct_wg = cblk * NB;
-    const v4u_t* src[PER_WAVE];
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) {
-        const int b = wave + 4 * i;
-        // (wavefront-uniform: the lane is added at the access, so the bases stay in scalar registers)
-        src[i] = (b < NA) ? Af + ((size_t)min(rt_wg + b, row_tiles - 1) * kblks) * 64
-                          : Wp + ((size_t)min(ct_wg + (b - NA), ntiles - 1) * kblks) * 64;
-    }
-    f32x4_t acc[RTW][CTW];
-#pragma unroll
-    for (int r = 0; r < RTW; ++r)
-#pragma unroll
-        for (int c = 0; c < CTW; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    v4u_t st[3][PER_WAVE];                  // blocks on their way from memory to LDS: block j waits in set j % 3
-    // A fragments of the block being multiplied (set kb % 2) and of the next one; the B fragments are single-buffered (a
-    // second set does not fit beside three staging sets): each is read two columns before the column that uses it, and
-    // the MFMAs run column-major
-    v4u_t fa[2][RTW], fb[CTW];
-#define HIVIS_BIG_LOAD(set_, blk_)                                                                         \
-    {                                                                                                      \
-        const int j_ = (blk_);                                                                             \
-        _Pragma("unroll") for (int i = 0; i < PER_WAVE; ++i) { const v4u_t* p_ = (j_ < kblks) ? src[i] + (size_t)j_ * 64 : zero; st[set_][i] = p_[lane]; } \
-    }
-#define HIVIS_BIG_PARK(set_, stage_)                                                                       \
-    {                                                                                                      \
-        v4u_t* dst_ = big_lds + (size_t)(stage_) * NBLK * 64;                                               \
-        _Pragma("unroll") for (int i = 0; i < PER_WAVE; ++i) dst_[(size_t)(wave + 4 * i) * 64 + lane] = st[set_][i]; \
-    }
-#define HIVIS_BIG_AFRAGS(fs_, stage_)                                                                      \
-    {                                                                                                      \
-        const v4u_t* s_ = big_lds + (size_t)(stage_) * NBLK * 64;                                           \
-        _Pragma("unroll") for (int r = 0; r < RTW; ++r) fa[fs_][r] = s_[(size_t)(wr * RTW + r) * 64 + lane]; \
-    }
-    // prologue: blocks 0 and 1 into stages 0 and 1, blocks 2, 3, 4 requested, fragments of block 0 read
-    HIVIS_BIG_LOAD(0, 0)
-    HIVIS_BIG_LOAD(1, 1)
-    HIVIS_BIG_PARK(0, 0)
-    HIVIS_BIG_PARK(1, 1)
-    HIVIS_BIG_LOAD(2, 2)
-    HIVIS_BIG_LOAD(0, 3)
-    HIVIS_BIG_LOAD(1, 4)
-    lds_barrier();
-    HIVIS_BIG_AFRAGS(0, 0)
-    fb[0] = big_lds[(size_t)(NA + wc * CTW + 0) * 64 + lane];
-    fb[1] = big_lds[(size_t)(NA + wc * CTW + 1) * 64 + lane];
-    // nothing may be pending on the LDS counter when the loop is entered: inside it the fragments read during one step
-    // are only awaited at that step's barrier, after its MFMAs have been issued
-    lds_barrier();
-    int stage2 = 2, stage1 = 1, stage0 = 0; // (kb + 2) % 3, (kb + 1) % 3, kb % 3
-    for (int kb0 = 0; kb0 < kblks; kb0 += 6) {
-#pragma unroll
-        for (int u = 0; u < 6; ++u) {
-            const int kb = kb0 + u;
-            // The step's memory instructions are spread over its MFMAs, one of each kind per column of 8 MFMAs (issued in
-            // one lump at the start they kept the matrix pipeline idle: a lone wavefront issues nothing else meanwhile):
-            //   park piece c of block kb+2 in its stage (last read, as block kb-1, two barriers ago), request the same
-            //   piece of block kb+5 into the freed registers, read A fragment c of block kb+1 (in LDS since the previous
-            //   barrier) and the B fragment needed two columns later (of block kb+1 for the last two columns).
-            const v4u_t* s0_ = big_lds + (size_t)stage0 * NBLK * 64;
-            const v4u_t* s1_ = big_lds + (size_t)stage1 * NBLK * 64;
-            v4u_t* s2_ = big_lds + (size_t)stage2 * NBLK * 64;
-            const v4u_t* nsrc_[PER_WAVE];
-#pragma unroll
-            for (int i = 0; i < PER_WAVE; ++i) nsrc_[i] = (kb + 5 < kblks) ? src[i] + (size_t)(kb + 5) * 64 : zero;
-#pragma unroll
-            for (int c = 0; c < CTW; ++c) {
-                static_assert(CTW == PER_WAVE && RTW == CTW, "one piece of every kind per column");
-                s2_[(size_t)(wave + 4 * c) * 64 + lane] = st[(u + 2) % 3][c];
-                st[(u + 2) % 3][c] = nsrc_[c][lane];
-                fa[(u + 1) % 2][c] = s1_[(size_t)(wr * RTW + c) * 64 + lane];
-                fb[(c + 2) % CTW] = (c + 2 < CTW ? s0_ : s1_)[(size_t)(NA + wc * CTW + (c + 2) % CTW) * 64 + lane];
-#pragma unroll
-                for (int r = 0; r < RTW; ++r)
-                    // accumulators pinned to the accumulation registers (the register allocator otherwise keeps them in
-                    // ordinary registers and copies each tile in and out around every MFMA)
-                    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[r][c]) : "v"(fa[u % 2][r]), "v"(fb[c]));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            lds_barrier();
-            stage0 = stage1; stage1 = stage2; stage2 = (stage2 == 2) ? 0 : stage2 + 1;
-        }
-    }
-#undef HIVIS_BIG_LOAD
-#undef HIVIS_BIG_PARK
-#undef HIVIS_BIG_AFRAGS
-    // the last MFMA results are read below by ordinary moves: let the matrix pipeline drain first (the compiler does not
-    // see an MFMA inside the asm statements, so it inserts no wait states of its own)
-    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    const int j = lane & 15, a4 = lane >> 4;
-#pragma unroll
-    for (int r = 0; r < RTW; ++r) {
-        const int rt = rt_wg + wr * RTW + r;
-        if (rt >= row_tiles) continue;
-        const int row = rt * 8 + 2 * a4;
-#pragma unroll
-        for (int c = 0; c < CTW; ++c) {
-            const int ct = ct_wg + wc * CTW + c;
-            if (ct >= ntiles) continue;
-            const int col = ct * 16 + j;
-            if (row < M) Y[(size_t)row * ldy + col] = acc[r][c][0] + acc[r][c][2];
-            if (row + 1 < M) Y[(size_t)(row + 1) * ldy + col] = acc[r][c][1] + acc[r][c][3];
-        }
-    }
-}
-
-// Y[r][c] = sum over the K slices of part[s][r][c] (fixed order), r < M, c < N (N a multiple of 4).
-__global__ void splitk_reduce_kernel(const float* __restrict__ part, int ksplit, int M, int N, int ldp, float* __restrict__ Y, int ldy) {
-    const int row = blockIdx.x;
-    for (int c4 = blockIdx.y * blockDim.x + threadIdx.x; c4 < N / 4; c4 += gridDim.y * blockDim.x) {
-        float4 acc = *reinterpret_cast<const float4*>(part + (size_t)row * ldp + 4 * c4);
-        for (int s = 1; s < ksplit; ++s) {
-            const float4 v = *reinterpret_cast<const float4*>(part + ((size_t)s * M + row) * ldp + 4 * c4);
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-        }
-        *reinterpret_cast<float4*>(Y + (size_t)row * ldy + 4 * c4) = acc;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
 // Row-wise small kernels (activations are a few rows of fp32; these are launch-bound, not
 // bandwidth-bound)
 // ------------------------------------------------------------------------------------------

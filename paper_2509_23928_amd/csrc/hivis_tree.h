@@ -6,7 +6,7 @@
 // is the sum of the log-probabilities along its path.  Everything that decides an index (top-k, expansion set,
 // candidate set, acceptance walk) orders by (score descending, index ascending), so results are unique.
 #pragma once
-#include "hivis_kernels.h"
+#include "hivis_gemm.h"
 
 namespace hivis {
 
@@ -294,31 +294,9 @@ __global__ void tree_finish_kernel(const float* __restrict__ dout, const int32_t
 // ------------------------------------------------------------------------------------------
 // Row-wise kernels of the 33..64-row passes (bf16 models).  They read a GEMM result as the sum of its K-slice partials
 // (value = sum over s < nparts of p[s * pstride + index], fixed order) and, where the consumer is the next split-K GEMM,
-// write its A operand directly as MFMA fragments (bf16 hi/lo split, layout of pack_afrag_kernel:
-// frag[(row tile * kblks + kb) * 64 + lane], lane = 16 g + i holds k = 32 kb + 8 g .. +8 of row 8 tt + 2 (i >> 2) + (i & 1),
-// i & 2 selecting the low part), so neither the reduction nor the fragment packing is a launch of its own.
+// write its A operand directly as activation fragments (layout: hivis_gemm.h), so neither the reduction nor the fragment
+// packing is a launch of its own.
 // ------------------------------------------------------------------------------------------
-struct Parts { const float* p; int n; size_t stride; };
-
-// B slices per trip, their loads issued together (a one-load-per-trip loop costs a memory round trip per slice)
-template <int B>
-__device__ __forceinline__ void parts_add(float4& a, const Parts& ps, size_t idx, int s0) {
-    for (int s = s0; s < ps.n; s += B) {
-        float4 v[B];
-#pragma unroll
-        for (int j = 0; j < B; ++j) v[j] = *reinterpret_cast<const float4*>(ps.p + (size_t)min(s + j, ps.n - 1) * ps.stride + idx);
-#pragma unroll
-        for (int j = 0; j < B; ++j)
-            if (s + j < ps.n) { a.x += v[j].x; a.y += v[j].y; a.z += v[j].z; a.w += v[j].w; }
-    }
-}
-__device__ __forceinline__ float4 parts_load4(const Parts& ps, size_t idx) {
-    float4 a = *reinterpret_cast<const float4*>(ps.p + idx);
-    if (ps.n <= 4) parts_add<3>(a, ps, idx, 1);       // slices 1..3 in one trip
-    else parts_add<8>(a, ps, idx, 1);
-    return a;
-}
-
 // h[row] += delta (sum of partials, optional); fragments of h[row] * gain / sqrt(mean(h^2) + eps).  One workgroup of 1024
 // threads per row of the padded row range (rows >= M write zero fragments); d <= 8192, d % 8 == 0.  A thread owns 4
 // consecutive columns and requests all slices of them at once (up to 16 loads in flight: with 8 columns per thread and
@@ -380,25 +358,23 @@ __global__ __launch_bounds__(WNORM_NT) void wide_add_norm_frag_kernel(float* __r
             f32_to_bf16x2_hilo(hi4.x, hi4.y, wh[2], wl[2]);
             f32_to_bf16x2_hilo(hi4.z, hi4.w, wh[3], wl[3]);
             const int k0 = 8 * (gi >> 1);
-            const int tt = row >> 3, r8 = row & 7, i_hi = 4 * (r8 >> 1) + (r8 & 1);
-            const size_t base = ((size_t)tt * kblks + (k0 >> 5)) * 64 + ((k0 >> 3) & 3) * 16;
             uint4 w4 = odd ? make_uint4(wl[0], wl[1], wl[2], wl[3]) : make_uint4(wh[0], wh[1], wh[2], wh[3]);
             if (!live) w4 = make_uint4(0u, 0u, 0u, 0u);
-            frag[base + i_hi + (odd ? 2 : 0)] = w4;
+            frag[afrag_at(kblks, row, k0) + (odd ? 64 : 0)] = w4;
         }
     }
 }
 
 // act = silu(gate) * up from the interleaved gate|up result (sum of partials), written as fragments of the down projection.
-// grid (row tiles of 8 rows, column chunks), 256 threads; F % 8 == 0.  Eight consecutive threads serve the eight rows of
-// the tile for one group of 8 activations: together they write one whole 256-byte piece of a fragment block (a thread
+// grid (row tiles of 16 rows, column chunks), 256 threads; F % 8 == 0.  Sixteen consecutive threads serve the sixteen rows
+// of the tile for one group of 8 activations: together they write whole 256-byte pieces of the fragment blocks (a thread
 // per (row, group) in row-major order scattered 16-byte stores over the buffer: 137 us for a 3008-row prefill layer).
 __global__ void wide_silu_frag_kernel(Parts gu, int M, int F, uint4* __restrict__ frag) {
-    const int row = blockIdx.x * 8 + (threadIdx.x & 7), kblks = F / 32;
+    const int row = blockIdx.x * 16 + (threadIdx.x & 15), kblks = F / 32;
     const bool live = row < M;
     const int rr = min(row, M - 1);
-    const int per = blockDim.x >> 3;
-    for (int gi = blockIdx.y * per + (threadIdx.x >> 3); gi < F / 8; gi += gridDim.y * per) {
+    const int per = blockDim.x >> 4;
+    for (int gi = blockIdx.y * per + (threadIdx.x >> 4); gi < F / 8; gi += gridDim.y * per) {
         const size_t o = (size_t)rr * 2 * F + (size_t)gi * 16;
         const float4 g0 = parts_load4(gu, o), g1 = parts_load4(gu, o + 4), u0 = parts_load4(gu, o + 8), u1 = parts_load4(gu, o + 12);
         const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w}, u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};

@@ -1,0 +1,60 @@
+"""Prefill of bf16 models at the row counts and widths where its kernels change tiles, K slices or route, against the
+CPU oracle.  Every row of the prompt reaches what is compared: the prompt's logits and the drafter's pending hidden state
+attend to all rows' cached keys and values."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import HivisOracle
+
+pytestmark = pytest.mark.gpu
+
+# Activations keep 16 mantissa bits between kernels (high + low bf16 part): every GEMM input carries a relative error of at
+# most 2^-17, uncorrelated between elements, so a result's relative 2-norm error grows by at most that per contraction in
+# the chain.  Two target layers and the drafter are 4 x 3 contractions plus fusion FC and LM head: 14 * 2^-17 = 1.1e-4.
+REL = 14 * 2.0 ** -17
+
+
+def rel(a, b):
+    return float(np.linalg.norm(np.asarray(a, np.float64) - b) / np.linalg.norm(b))
+
+
+def check_prefill(cfg, seed=0):
+    from paper_2509_23928_amd import Hivis
+    w = synth.make_weights(cfg, seed=seed)
+    vis, ids = synth.make_prompt(cfg, seed=seed)
+    hv = Hivis(cfg, w)
+    first = hv.prefill(vis, ids)
+    logits, hidden = hv.get_logits(2), hv.get_hidden(1)
+    for b in range(cfg.batch):
+        o = HivisOracle(cfg, w)
+        x, ref = o.prefill(vis[b], ids[b])
+        assert rel(logits[b], ref) <= REL
+        assert int(first[b]) == x
+        assert rel(hidden[b], o.f_next) <= REL
+    hv.close()
+
+
+def cfg_of(**kw):
+    base = dict(name="shapes", n_layers=2, d=256, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=704, vocab=512, dtype="bf16",
+                n_vis=0, n_text=1, K=3, batch=1, gen_tokens=0, gen_cycles=1)
+    base.update(kw)
+    return synth.HivisConfig(**base)
+
+
+@pytest.mark.parametrize("n_vis,n_text", [(0, 1), (0, 7), (0, 9), (3, 7), (0, 16), (0, 17), (30, 3), (0, 33), (0, 64), (64, 1), (0, 65), (17, 110),
+                                          (0, 128), (100, 29), (0, 257), (383, 130)])
+def test_row_counts(n_vis, n_text):
+    check_prefill(cfg_of(n_vis=n_vis, n_text=n_text))
+
+
+@pytest.mark.parametrize("kw", [
+    dict(n_vis=1900, n_text=100, ffn=2048),                        # gate|up in one round of 256-column tiles
+    dict(n_vis=1931, n_text=17, ffn=1792),                         # ... of 224-column tiles
+    dict(n_vis=150, n_text=33, d=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, ffn=2720),      # K slices in the O and down projections
+    dict(n_vis=70, n_text=5, d=96, n_q_heads=3, n_kv_heads=1, head_dim=64, ffn=32),            # fewer columns and K blocks than one tile
+    dict(n_vis=75, n_text=9, batch=3), dict(n_vis=0, n_text=5, batch=3), dict(n_vis=1, n_text=40, batch=2, qkv_bias=True),
+    dict(n_vis=200, n_text=3, qkv_bias=True, n_q_heads=8, n_kv_heads=1),
+], ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
+def test_widths(kw):
+    check_prefill(cfg_of(**kw))
