@@ -90,10 +90,10 @@ struct hivis_ctx {
     float *u_draft = nullptr, *u_acc = nullptr, *u_res = nullptr;   // uniform numbers of the sampling calls: [B][k_max], [B][k_max] (row stride K), [B]
     float inv_temp = 1.0f; bool drafts_sampled = false;             // set by hivis_draft_sample; hivis_accept_sample needs the drafter's distributions
     void* vis = nullptr;        // staging for vis_embeds [B][max_vis][d]
-    // whole-prompt prefill buffers (bf16 models): all v+l rows of one sequence per layer
+    // whole-prompt prefill buffers (bf16 models): all v+l rows of one or several sequences per layer
     int pf_rows = 0;
-    float *pf_x = nullptr, *pf_a = nullptr, *pf_qkv = nullptr, *pf_att = nullptr, *pf_proj = nullptr, *pf_gu = nullptr, *pf_act = nullptr;
-    uint4* pf_frag = nullptr;
+    float *pf_x = nullptr, *pf_xt = nullptr, *pf_a = nullptr, *pf_qkv = nullptr, *pf_att = nullptr, *pf_proj = nullptr, *pf_gu = nullptr;
+    uint4 *pf_frag = nullptr, *pf_frag2 = nullptr;      // activation fragments: of d / q_dim wide rows, and of the MLP's inner rows
     std::vector<int32_t> h_ids;
 
     // persistent-kernel path (passes of at most one MFMA tile of rows)
@@ -255,7 +255,8 @@ int upload_layer(hivis_ctx* c, const hivis_layer_weights& w, void* staging, Laye
 // column chunks per row for the row-wise kernels: few rows -> split every row over several workgroups
 static inline int row_chunks(int rows) { return rows >= 256 ? 1 : std::max(1, std::min(8, 256 / std::max(rows, 1))); }
 
-int wide_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, hivis::Parts* defer = nullptr);
+void launch_pack(hivis_ctx* c, const float* A, int lda, int M, int kblks);
+int wide_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, int ldy, hivis::Parts* defer = nullptr);
 template <typename WT>
 int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* h, hivis::Parts pending, const int* base,
                        int offset, int seq0, int nseq, int m, TreeRows tr, hivis::Parts* out_pending);
@@ -264,8 +265,10 @@ int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* 
 template <typename WT>
 int gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, int epi) {
     if (M < 1 || M > MAX_ROWS) return fail(c, HIVIS_EINVAL, "gemm rows %d out of range", M);
-    if (sizeof(WT) == 2 && M >= c->wide_min && c->pf_frag && c->pf_rows >= MAX_ROWS && ldy == N && epi == EPI_STORE && !c->no_wide_gemm)
-        return wide_gemm(c, A, lda, M, K, Wp, N, Y, ldy);
+    if (sizeof(WT) == 2 && M >= c->wide_min && c->pf_frag && c->pf_rows >= MAX_ROWS && ldy == N && epi == EPI_STORE && !c->no_wide_gemm) {
+        launch_pack(c, A, lda, M, K / 32);
+        return wide_gemm(c, c->pf_frag, M, K, Wp, N, Y, ldy);
+    }
     if (M > CHAIN_MAX_ROWS) {            // wider passes (tree verify)
         // fp32 models: one launch per 32 rows
         for (int r0 = 0; r0 < M; r0 += CHAIN_MAX_ROWS)
@@ -306,7 +309,7 @@ int gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, i
 
 template <typename WT>
 int attention(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int* base, int offset, int seq0, int nseq,
-              int m, int max_keys, float* out, int ldo, const unsigned long long* tmask = nullptr) {
+              int m, int max_keys, float* out, int ldo, const unsigned long long* tmask = nullptr, int qrows = 0) {
     typedef typename KVType<WT>::type KT;
     const hivis_config& g = c->cfg;
     AttnShape sh{};
@@ -315,7 +318,7 @@ int attention(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int*
     if (m >= ATT_RMAX) { sh.mi = ATT_RMAX; sh.gh = 1; }
     else { sh.mi = m; sh.gh = std::max(1, std::min(group, ATT_RMAX / m)); }
     sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
-    sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.nwaves = 4; sh.tmask = tmask;
+    sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.qrows = qrows; sh.nwaves = 4; sh.tmask = tmask;
     const int items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
     // enough workgroups to occupy the chip, at most one 64-key tile per wavefront slot
     const int tiles = (max_keys + 63) / 64;
@@ -342,23 +345,26 @@ AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, 
 // keys, no key split), launched once over all items.  Rows of sequence seq0 + s sit at positions base[seq0 + s] + offset + i.
 template <typename WT>
 int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int* base, int offset, int seq0, int nseq, int m,
-                        float* out, int ldo, const unsigned long long* tmask = nullptr, uint4* frag_out = nullptr, bool* wrote_frag = nullptr) {
+                        float* out, int ldo, const unsigned long long* tmask = nullptr, uint4* frag_out = nullptr, bool* wrote_frag = nullptr, int qrows = 0) {
     // frag_out / wrote_frag (optional): where the kernel chosen can, the rows go out as A fragments of the next GEMM
     // (K = ldo) instead of fp32 rows, and *wrote_frag says so
     if (wrote_frag) *wrote_frag = false;
     const hivis_config& g = c->cfg;
     typedef typename KVType<WT>::type KT;
     if constexpr (std::is_same<KT, f16_t>::value) {
-        if (m >= c->attn_shared_min && tmask == nullptr) {
-            // long causal row ranges (prefill): 128 rows of one head per workgroup, key tiles shared through LDS
+        // long causal row ranges (prefill): 128 rows of one head per workgroup, key tiles shared through LDS.  Too few such
+        // workgroups leave CUs idle (the last 128 of 3008 rows, 32 heads: 240 us): 16 rows per workgroup then.
+        const long shared_items = (long)nseq * g.n_q_heads * ((m + ATTN_SHARED_ROWS - 1) / ATTN_SHARED_ROWS);
+        if (m >= c->attn_shared_min && 2 * shared_items >= c->num_cu && tmask == nullptr && frag_out && wrote_frag) {
             AttnShape sh{};
             sh.Hq = g.n_q_heads; sh.Hkv = g.n_kv_heads; sh.m = m; sh.mi = ATTN_SHARED_ROWS; sh.gh = 1;
             sh.n_hblk = g.n_q_heads / g.n_kv_heads; sh.n_rblk = (m + ATTN_SHARED_ROWS - 1) / ATTN_SHARED_ROWS;
-            sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.nwaves = FUSED_NW; sh.nsplit = 1; sh.tmask = nullptr;
+            sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.qrows = qrows; sh.nwaves = FUSED_NW; sh.nsplit = 1; sh.tmask = nullptr;
             const int items = nseq * g.n_q_heads * sh.n_rblk;
             const size_t lds = attn_shared_lds_bytes(g.head_dim);
-            if (g.head_dim == 128) hipLaunchKernelGGL((attn_rows_shared_kernel<128>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, out, ldo);
-            else hipLaunchKernelGGL((attn_rows_shared_kernel<64>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, out, ldo);
+            if (g.head_dim == 128) hipLaunchKernelGGL((attn_rows_shared_kernel<128>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, ldo, frag_out);
+            else hipLaunchKernelGGL((attn_rows_shared_kernel<64>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, ldo, frag_out);
+            *wrote_frag = true;
             HIP_TRY(c, hipGetLastError());
             return HIVIS_OK;
         }
@@ -370,7 +376,7 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
             if (m >= ATTN_ROWS_RM) { sh.mi = ATTN_ROWS_RM; sh.gh = 1; }
             else { sh.mi = m; sh.gh = std::max(1, std::min(group, ATTN_ROWS_RM / m)); }
             sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
-            sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.nwaves = FUSED_NW; sh.nsplit = 1; sh.tmask = tmask;
+            sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.qrows = qrows; sh.nwaves = FUSED_NW; sh.nsplit = 1; sh.tmask = tmask;
             const int items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
             const size_t lds = fused_attn_mfma_lds_floats(g.head_dim, FUSED_NW, ATTN_ROWS_RM) * sizeof(float);
             uint4* frag = (frag_out && wrote_frag && ldo % 32 == 0) ? frag_out : nullptr;
@@ -392,7 +398,7 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
     Phase ph{};
     ph.type = PH_ATTN;
     ph.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, ldq, &items);
-    ph.att.seq0 = seq0; ph.att.nsplit = 1; ph.att.tmask = tmask; ph.att.flags = c->attn_flags;
+    ph.att.seq0 = seq0; ph.att.nsplit = 1; ph.att.tmask = tmask; ph.att.flags = c->attn_flags; ph.att.qrows = qrows;
     ph.att_items = items;
     ph.A = q; ph.kc = kv.k; ph.vc = kv.v; ph.maxL = kv.maxL; ph.base = base; ph.offset = offset;
     ph.Y = out; ph.ldy = ldo; ph.ws = nullptr; ph.cnt = nullptr;
@@ -956,10 +962,9 @@ void launch_pack(hivis_ctx* c, const float* A, int lda, int M, int kblks) {
 // power limit), plus 7 us to start and finish; slices cost their partial sums, written once and read once.  (Measured at 640 rows,
 // K = 4096: 22016 columns 430 tiles 181 us / 495 tiles 172 us / 575 tiles, a third round, 205 us; 4096 columns as 80 tiles 75 us,
 // as 3 x 80 tiles 39 us.)
-struct TallPlan { int cw, ksplit; };
+struct TallPlan { int cw, ksplit; double us; };
 TallPlan tall_plan(const hivis_ctx* c, int M, int kblks, int ntiles, bool may_split) {
-    TallPlan best{8, 1};
-    double best_us = 1e30;
+    TallPlan best{8, 1, 1e30};
     const int nrow = (M + TALL_ROWS - 1) / TALL_ROWS;
     for (int cw = 8; cw >= 6; --cw)
         for (int S = 1; S <= (may_split ? 8 : 1); ++S) {
@@ -969,37 +974,39 @@ TallPlan tall_plan(const hivis_ctx* c, int M, int kblks, int ntiles, bool may_sp
             const double rounds = std::ceil(tiles / c->num_cu), fill = tiles / (rounds * c->num_cu);
             double us = rounds * (kper * 0.066 * cw * (0.8 + 0.5 * fill) + 7.0);
             if (S > 1) us += 2.0 * S * M * ntiles * 16 * 4.0 / 4.0e6;
-            if (us < best_us - 1e-9) { best_us = us; best = {cw, S}; }
+            if (us < best.us - 1e-9) best = {cw, S, us};
         }
     return best;
 }
 
-// M rows (any number) x N columns.  A == nullptr: the producing row kernel has already written the fragments to c->pf_frag.
-// defer != nullptr: K slices may be used, and *defer describes the result for the consuming row kernel (slices or Y).
-int tall_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer = nullptr) {
+template <int EPI>
+int launch_tall(hivis_ctx* c, const TallPlan& pl, const uint4* frag, int M, int K, const uint4* Wp, int N, TallOut o) {
     const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;
-    if (A) launch_pack(c, A, lda, M, kblks);
-    const TallPlan pl = tall_plan(c, M, kblks, ntiles, defer != nullptr);
-    if (pl.ksplit > 1) { if (int rc = splitk_space(c, (size_t)pl.ksplit * M * ldy)) return rc; }
-    const int nrow = (row_tiles + TALL_ROWS / 16 - 1) / (TALL_ROWS / 16), tiles = nrow * ((ntiles + 2 * pl.cw - 1) / (2 * pl.cw)) * pl.ksplit;
-#define HIVIS_TALL(CW_)                                                                                                              \
-    hipLaunchKernelGGL((gemm_tall_kernel<CW_>), dim3(8 * ((tiles + 7) / 8)), dim3(TALL_THREADS), tall_lds_bytes<CW_>(), c->stream,   \
-                       (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, pl.ksplit, c->splitk_ws)
+    if (pl.ksplit > 1) { if (int rc = splitk_space(c, (size_t)pl.ksplit * M * o.ldy)) return rc; o.part = c->splitk_ws; }
+    const int tiles = ((M + TALL_ROWS - 1) / TALL_ROWS) * ((ntiles + 2 * pl.cw - 1) / (2 * pl.cw)) * pl.ksplit;
+#define HIVIS_TALL(CW_)                                                                                                                    \
+    hipLaunchKernelGGL((gemm_tall_kernel<CW_, EPI>), dim3(8 * ((tiles + 7) / 8)), dim3(TALL_THREADS), tall_lds_bytes<CW_>(), c->stream,    \
+                       (const v4u_t*)frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, M, pl.ksplit, o)
     if (pl.cw == 8) HIVIS_TALL(8);
     else if (pl.cw == 7) HIVIS_TALL(7);
     else HIVIS_TALL(6);
 #undef HIVIS_TALL
-    if (defer) *defer = Parts{pl.ksplit > 1 ? c->splitk_ws : Y, pl.ksplit, (size_t)M * ldy};
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
+// these kernels use more LDS than a launch gets without asking
+template <int EPI>
+int tall_setup(hivis_ctx* c) {
+    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<8, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<8>()));
+    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<7, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<7>()));
+    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<6, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<6>()));
+    return HIVIS_OK;
+}
 
-// 11..64 rows in ONE pass over the weights (gemm_wide_kernel).  A == nullptr: the fragments are already in c->pf_frag
-// (written by the producing row kernel).  defer != nullptr: the slice partials are not reduced here; *defer describes
-// them for the consuming row kernel.
-int wide_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer) {
+// Up to 64 rows in ONE pass over the weights (gemm_wide_kernel).  defer != nullptr: the slice partials are not reduced here;
+// *defer describes them for the consuming row kernel.
+int wide_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer) {
     const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;
-    if (A) launch_pack(c, A, lda, M, kblks);
     const int ncol = (ntiles + 7) / 8;                                  // 8 column tiles per workgroup
     // about 3 workgroups per CU and at most 16 slices (swept at 61 rows: 256/384/512/768/1024 workgroups, 8/16 slices;
     // 256-column tiles with half the slices were no faster, at 61 rows and at 32)
@@ -1009,13 +1016,85 @@ int wide_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* 
     float* part = S > 1 ? c->splitk_ws : nullptr;
     if (row_tiles <= 2)      // at most 32 rows: 2 row tiles per workgroup, half the fragment traffic and MFMA work
         hipLaunchKernelGGL((gemm_wide_kernel<1>), dim3(ncol * S), dim3(256), 2 * 12 * 1024, c->stream,
-                           (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
+                           (const v4u_t*)frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
     else
         hipLaunchKernelGGL((gemm_wide_kernel<2>), dim3(ncol * S), dim3(256), 2 * 16 * 1024, c->stream,
-                           (const v4u_t*)c->pf_frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
+                           (const v4u_t*)frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
     const Parts res{S > 1 ? part : Y, S, (size_t)M * ldy};
     if (defer) *defer = res;
     else if (S > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, res, N, ldy, Y, ldy);
+    HIP_TRY(c, hipGetLastError());
+    return HIVIS_OK;
+}
+
+// Any number of rows; the result is *out: K slices, or the one result in Y (row stride N).
+int rows_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, Parts* out) {
+    if (M <= MAX_ROWS) return wide_gemm(c, frag, M, K, Wp, N, Y, N, out);
+    const TallPlan pl = tall_plan(c, M, K / 32, N / 16, true);
+    TallOut o{}; o.Y = Y; o.ldy = N;
+    if (int rc = launch_tall<TALL_STORE>(c, pl, frag, M, K, Wp, N, o)) return rc;
+    *out = Parts{pl.ksplit > 1 ? c->splitk_ws : Y, pl.ksplit, (size_t)M * N};
+    return HIVIS_OK;
+}
+
+// The q|k|v and the gate|up product end in the GEMM itself (TALL_QKV / TALL_SILU) unless K slices win back more than the row
+// kernel costs (ROW_KERNEL_US: its launch and ramp; its traffic is in the slices' estimate).  At most 64 rows: slices.
+constexpr double ROW_KERNEL_US = 8.0;
+bool tall_fused(const hivis_ctx* c, int M, int kblks, int ntiles, TallPlan* pl) {
+    if (M <= MAX_ROWS) return false;
+    *pl = tall_plan(c, M, kblks, ntiles, false);
+    return pl->us <= tall_plan(c, M, kblks, ntiles, true).us + ROW_KERNEL_US;
+}
+
+// M = nseq * m rows: q (rotated) to q_out [M][q_dim], k and v of sequence seq0 + s to its cache rows base[seq0 + s] + offset ..
+template <typename WT>
+int rows_qkv(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const uint4* frag, const int* base, int offset, int seq0, int nseq, int m,
+             TreeRows tr, float* scratch, float* q_out) {
+    typedef typename KVType<WT>::type KT;
+    const hivis_config& g = c->cfg;
+    const int M = nseq * m, d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, nqkv = qd + 2 * kd, npos = g.max_vis + g.max_text;
+    TallPlan pl;
+    if (base == c->zeros && offset == 0 && !tr.pos_delta && tall_fused(c, M, d / 32, nqkv / 16, &pl)) {
+        TallOut o{};
+        o.Y = q_out; o.ldy = qd; o.bias = L.bqkv; o.rope = c->rope_tab; o.npos = npos; o.seq0 = seq0; o.m = m;
+        o.qd = qd; o.kd = kd; o.HD = g.head_dim; o.Hkv = g.n_kv_heads; o.maxL = kv.maxL; o.kc = (f16_t*)kv.k; o.vc = (f16_t*)kv.v;
+        return launch_tall<TALL_QKV>(c, pl, frag, M, d, L.wqkv, nqkv, o);
+    }
+    Parts p{};
+    if (int rc = rows_gemm(c, frag, M, d, L.wqkv, nqkv, scratch, &p)) return rc;
+    hipLaunchKernelGGL((wide_rope_append_kernel<KT>), dim3(M, M <= MAX_ROWS ? 8 : row_chunks(M)), dim3(256), 0, c->stream, p, q_out, qd, g.n_q_heads, g.n_kv_heads, g.head_dim,
+                       base, offset, seq0, m, (KT*)kv.k, (KT*)kv.v, kv.maxL, g.rope_theta, tr.pos_delta, (const float*)L.bqkv, (const float*)c->rope_tab, npos);
+    HIP_TRY(c, hipGetLastError());
+    return HIVIS_OK;
+}
+
+// gate|up product and SiLU(gate) * up of M rows: fragments (in the layout of the down projection) to frag_out
+int rows_gateup(hivis_ctx* c, const LayerDev& L, const uint4* frag, int M, float* scratch, uint4* frag_out) {
+    const int d = c->cfg.d, F = c->cfg.ffn;
+    TallPlan pl;
+    if (tall_fused(c, M, d / 32, 2 * F / 16, &pl)) {
+        TallOut o{}; o.frag = frag_out; o.kblks_out = F / 32;
+        return launch_tall<TALL_SILU>(c, pl, frag, M, d, L.wgu, 2 * F, o);
+    }
+    Parts p{};
+    if (int rc = rows_gemm(c, frag, M, d, L.wgu, 2 * F, scratch, &p)) return rc;
+    hipLaunchKernelGGL(wide_silu_frag_kernel, dim3((M + 15) / 16, std::min(64, (F / 8 + 15) / 16)), dim3(256), 0, c->stream, p, M, F, frag_out);
+    HIP_TRY(c, hipGetLastError());
+    return HIVIS_OK;
+}
+
+// h += delta (if any), then fragments of RMSNorm(h) to c->pf_frag
+template <typename WT>
+int rows_norm(hivis_ctx* c, float* h, const Parts& delta, int M, const void* gain) {
+    const int d = c->cfg.d;
+    if (d <= 4 * WNORM_NT * WNORM_GROUPS) {
+        hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3((M + 15) / 16 * 16), dim3(WNORM_NT), 0, c->stream, h, d, delta, d, M, (const WT*)gain, c->pf_frag, d, c->cfg.rms_eps);
+    } else {                // rows wider than that kernel's registers
+        if (delta.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, delta, d, d, c->pf_proj, d);
+        const float* one = delta.n > 1 ? c->pf_proj : delta.p;
+        hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, c->stream, h, d, one, d, (const WT*)gain, c->pf_a, d, d, c->cfg.rms_eps);
+        launch_pack(c, c->pf_a, d, M, d / 32);
+    }
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
@@ -1025,76 +1104,84 @@ int wide_gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* 
 template <typename WT>
 int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* h, Parts pending, const int* base,
                        int offset, int seq0, int nseq, int m, TreeRows tr, Parts* out_pending) {
-    typedef typename KVType<WT>::type KT;
     const hivis_config& g = c->cfg;
-    const int M = nseq * m, d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, F = g.ffn;
-    const int nqkv = qd + 2 * kd, Mp = ((M + 15) / 16) * 16;
-    Parts pq{}, po{}, pg{};
-    hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, h, d, pending, d, M, (const WT*)L.norm1, c->pf_frag, d, g.rms_eps);
-    if (int rc = wide_gemm(c, nullptr, 0, M, d, L.wqkv, nqkv, c->qkv, nqkv, &pq)) return rc;
-    hipLaunchKernelGGL((wide_rope_append_kernel<KT>), dim3(M, 8), dim3(256), 0, c->stream, pq, c->qkv, nqkv, g.n_q_heads, g.n_kv_heads, g.head_dim, base, offset, seq0, m,
-                       (KT*)kv.k, (KT*)kv.v, kv.maxL, g.rope_theta, tr.pos_delta, (const float*)L.bqkv, (const float*)c->rope_tab, g.max_vis + g.max_text);
+    const int M = nseq * m, d = g.d, qd = g.n_q_heads * g.head_dim, F = g.ffn;
+    Parts po{};
+    if (int rc = rows_norm<WT>(c, h, pending, M, L.norm1)) return rc;
+    if (int rc = rows_qkv<WT>(c, L, kv, c->pf_frag, base, offset, seq0, nseq, m, tr, c->pf_qkv, c->qkv)) return rc;
     // (the attention writes the O projection's fragments itself where its kernel can; rows beyond M of the last row tile
-    // then keep whatever the buffer held: an MFMA output row depends on its own A row only, and those rows are never stored)
+    // then keep whatever the buffer held: an MFMA output row depends on its own activation row only, and those rows are never stored)
     bool att_frag = false;
-    if (int rc = attention_rows_mfma<WT>(c, c->qkv, nqkv, kv, base, offset, seq0, nseq, m, c->att, qd, tr.mask, c->pf_frag, &att_frag)) return rc;
-    if (int rc = wide_gemm(c, att_frag ? nullptr : c->att, qd, M, qd, L.wo, d, c->proj, d, &po)) return rc;
-    hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, h, d, po, d, M, (const WT*)L.norm2, c->pf_frag, d, g.rms_eps);
-    if (int rc = wide_gemm(c, nullptr, 0, M, d, L.wgu, 2 * F, c->gu, 2 * F, &pg)) return rc;
-    hipLaunchKernelGGL(wide_silu_frag_kernel, dim3(Mp / 16, std::min(64, (F / 8 + 15) / 16)), dim3(256), 0, c->stream, pg, M, F, c->pf_frag);
-    if (int rc = wide_gemm(c, nullptr, 0, M, F, L.wd, d, c->proj, d, out_pending)) return rc;
+    if (int rc = attention_rows_mfma<WT>(c, c->qkv, qd, kv, base, offset, seq0, nseq, m, c->att, qd, tr.mask, c->pf_frag, &att_frag)) return rc;
+    if (!att_frag) launch_pack(c, c->att, qd, M, qd / 32);
+    if (int rc = rows_gemm(c, c->pf_frag, M, qd, L.wo, d, c->proj, &po)) return rc;
+    if (int rc = rows_norm<WT>(c, h, po, M, L.norm2)) return rc;
+    if (int rc = rows_gateup(c, L, c->pf_frag, M, c->gu, c->pf_frag2)) return rc;
+    return rows_gemm(c, c->pf_frag2, M, F, L.wd, d, c->proj, out_pending);
+}
+
+// ---- whole-prompt prefill (bf16 models): all rows of one or several sequences per layer -------------------------
+// Second half of a layer, after q, k and v: attention, O projection, MLP on the last n rows of each of nseq sequences (their q rows:
+// q, qrows rows apart from one sequence to the next; positions offset ..).  h [nseq * n][d]: their residual rows.
+template <typename WT>
+int rows_attn_mlp(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const float* q, int qrows, int offset, int seq0, int nseq, int n,
+                  float* h, Parts* out_pending) {
+    const hivis_config& g = c->cfg;
+    const int M = nseq * n, d = g.d, qd = g.n_q_heads * g.head_dim, F = g.ffn;
+    bool att_frag = false;
+    if (c->fused) { if (int rc = attention_rows_mfma<WT>(c, q, qd, kv, c->zeros, offset, seq0, nseq, n, c->pf_att, qd, nullptr, c->pf_frag, &att_frag, qrows)) return rc; }
+    else if (int rc = attention<WT>(c, q, qd, kv, c->zeros, offset, seq0, nseq, n, offset + n, c->pf_att, qd, nullptr, qrows)) return rc;
+    if (!att_frag) launch_pack(c, c->pf_att, qd, M, qd / 32);
+    Parts po{};
+    if (int rc = rows_gemm(c, c->pf_frag, M, qd, L.wo, d, c->pf_proj, &po)) return rc;
+    if (int rc = rows_norm<WT>(c, h, po, M, L.norm2)) return rc;
+    if (int rc = rows_gateup(c, L, c->pf_frag, M, c->pf_gu, c->pf_frag2)) return rc;
+    return rows_gemm(c, c->pf_frag2, M, F, L.wd, d, c->pf_proj, out_pending);
+}
+
+template <typename WT>
+int prefill_target_tall(hivis_ctx* c, int b0, int nseq, int v, int l) {
+    const hivis_config& g = c->cfg;
+    const int m = v + l, M = nseq * m, d = g.d, qd = g.n_q_heads * g.head_dim;
+    hipLaunchKernelGGL((prefill_rows_kernel<WT>), dim3(m, nseq), dim3(256), 0, c->stream, (const WT*)c->vis + (size_t)b0 * g.max_vis * d, (size_t)g.max_vis * d, v,
+                       (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b0 * c->text_stride), c->text_stride, 0, c->pf_x, d);
+    Parts pend{nullptr, 0, 0};
+    float* h = c->pf_x;
+    for (int l_ = 0; l_ < g.n_layers; ++l_) {
+        const LayerDev& L = c->layers[l_];
+        if (int rc = rows_norm<WT>(c, h, pend, M, L.norm1)) return rc;
+        if (int rc = rows_qkv<WT>(c, L, c->tkv[l_], c->pf_frag, c->zeros, 0, b0, nseq, m, TreeRows(), c->pf_gu, c->pf_qkv)) return rc;
+        // the last layer's output is read at the text rows only: behind its keys and values nothing needs the visual rows
+        const int first = l_ + 1 == g.n_layers ? v : 0, n = m - first;
+        if (first) { hipLaunchKernelGGL(tail_rows_kernel, dim3(n, nseq), dim3(256), 0, c->stream, (const float*)h, m, first, c->pf_xt, d); h = c->pf_xt; }
+        if (int rc = rows_attn_mlp<WT>(c, L, c->tkv[l_], c->pf_qkv + (size_t)first * qd, m, first, b0, nseq, n, h, &pend)) return rc;
+    }
+    // features of the text rows (h now holds l rows per sequence): final norm of (h + last MLP delta)
+    if (pend.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(nseq * l, row_chunks(nseq * l)), dim3(256), 0, c->stream, pend, d, d, c->pf_proj, d);
+    for (int s = 0; s < nseq; ++s)
+        hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(l), dim3(256), 0, c->stream, h + (size_t)s * l * d, d, (const float*)c->pf_proj + (size_t)s * l * d, d,
+                           (const WT*)c->final_norm, c->feat + (size_t)(b0 + s) * g.max_text * d, d, d, g.rms_eps);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
 
-// the tall GEMM kernels use more LDS than a launch gets without asking
-int tall_setup(hivis_ctx* c) {
-    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<8>()));
-    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<7>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<7>()));
-    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<6>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<6>()));
-    return HIVIS_OK;
-}
-
+// Drafter prefill over the l text rows of nseq sequences: rows [f^j ; Embed(x_{j+1})] through the fusion FC, + rho_0, then the
+// drafter's layer.  Only the last row's output is ever read (f'_1 of the coming round): the other rows end at their keys and values.
 template <typename WT>
-int prefill_target_tall(hivis_ctx* c, int b, int v, int l) {
-    typedef typename KVType<WT>::type KT;
+int prefill_drafter_tall(hivis_ctx* c, int b0, int nseq, int l) {
     const hivis_config& g = c->cfg;
-    const int M = v + l, d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, F = g.ffn, nqkv = qd + 2 * kd;
-    const int Mp = ((M + 15) / 16) * 16;
-    hipLaunchKernelGGL((prefill_rows_kernel<WT>), dim3(M), dim3(256), 0, c->stream, (const WT*)c->vis + (size_t)b * g.max_vis * d, v,
-                       (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), 0, c->pf_x, d);
-    Parts pend{nullptr, 0, 0}, proj{};
-    for (int l_ = 0; l_ < g.n_layers; ++l_) {
-        const LayerDev& L = c->layers[l_];
-        const KVDev& kv = c->tkv[l_];
-        // residual add + RMSNorm write the GEMM's A fragments directly (rows padded to whole tiles), SiLU * up likewise; the
-        // O and down projections come as K slices, which the residual add sums.  (Rows wider than the norm kernel's registers:
-        // the row kernels of the decode passes, one result each.)
-        const bool direct = d <= 8192;
-        if (direct) hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, c->pf_x, d, pend, d, M, (const WT*)L.norm1, c->pf_frag, d, g.rms_eps);
-        else hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, c->stream, c->pf_x, d, pend.p, d, (const WT*)L.norm1, c->pf_a, d, d, g.rms_eps);
-        if (int rc = tall_gemm(c, direct ? nullptr : c->pf_a, d, M, d, L.wqkv, nqkv, c->pf_qkv, nqkv)) return rc;
-        hipLaunchKernelGGL((rope_append_kernel<KT>), dim3(M, row_chunks(M)), dim3(256), 0, c->stream, c->pf_qkv, g.n_q_heads, g.n_kv_heads, g.head_dim, (const int*)c->zeros, 0, b, M, (KT*)kv.k, (KT*)kv.v, kv.maxL, g.rope_theta, (const int*)nullptr, (const float*)L.bqkv, (const float*)c->rope_tab, g.max_vis + g.max_text);
-        if (c->fused) { if (int rc = attention_rows_mfma<WT>(c, c->pf_qkv, nqkv, kv, c->zeros, 0, b, 1, M, c->pf_att, qd)) return rc; }
-        else if (int rc = attention<WT>(c, c->pf_qkv, nqkv, kv, c->zeros, 0, b, 1, M, M, c->pf_att, qd)) return rc;
-        if (int rc = tall_gemm(c, c->pf_att, qd, M, qd, L.wo, d, c->pf_proj, d, direct ? &proj : nullptr)) return rc;
-        if (direct) hipLaunchKernelGGL((wide_add_norm_frag_kernel<WT>), dim3(Mp), dim3(WNORM_NT), 0, c->stream, c->pf_x, d, proj, d, M, (const WT*)L.norm2, c->pf_frag, d, g.rms_eps);
-        else hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, c->stream, c->pf_x, d, (const float*)c->pf_proj, d, (const WT*)L.norm2, c->pf_a, d, d, g.rms_eps);
-        if (int rc = tall_gemm(c, direct ? nullptr : c->pf_a, d, M, d, L.wgu, 2 * F, c->pf_gu, 2 * F)) return rc;
-        if (direct) {
-            const Parts gu{c->pf_gu, 1, 0};
-            hipLaunchKernelGGL(wide_silu_frag_kernel, dim3(Mp / 16, std::min(64, (F / 8 + 15) / 16)), dim3(256), 0, c->stream, gu, M, F, c->pf_frag);
-        } else hipLaunchKernelGGL(silu_mul_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, (const float*)c->pf_gu, c->pf_act, F);
-        pend = Parts{c->pf_proj, 1, 0};
-        if (int rc = tall_gemm(c, direct ? nullptr : c->pf_act, F, M, F, L.wd, d, c->pf_proj, d, direct ? &pend : nullptr)) return rc;
-    }
-    if (pend.n > 1) {       // only the text rows' sums are needed
-        const Parts text{pend.p + (size_t)v * d, pend.n, pend.stride};
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3(l, row_chunks(l)), dim3(256), 0, c->stream, text, d, d, c->pf_proj + (size_t)v * d, d);
-    }
-    // features of the text rows: final norm of (x + last MLP delta)
-    hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(l), dim3(256), 0, c->stream, c->pf_x + (size_t)v * d, d, (const float*)c->pf_proj + (size_t)v * d, d,
-                       (const WT*)c->final_norm, c->feat + (size_t)b * g.max_text * d, d, d, g.rms_eps);
+    const int M = nseq * l, d = g.d, qd = g.n_q_heads * g.head_dim;
+    const float* table = c->emb_w2;          // Embed(x) w2 of every token: the FC then multiplies f alone
+    const int K = table ? d : 2 * d;
+    hipLaunchKernelGGL((fuse_frag_kernel<WT>), dim3((M + 15) / 16 * 16), dim3(256), 0, c->stream, (const float*)(c->feat + (size_t)b0 * g.max_text * d), g.max_text, l, M,
+                       (const int32_t*)(c->text + (size_t)b0 * c->text_stride), c->text_stride, (const WT*)c->embed, table, (const WT*)c->rho, c->pf_x, c->pf_frag, d);
+    Parts p{};
+    if (int rc = rows_gemm(c, c->pf_frag, M, K, table ? c->fuse_w1 : c->fuse_w, d, c->pf_proj, &p)) return rc;
+    if (int rc = rows_norm<WT>(c, c->pf_x, p, M, c->draft.norm1)) return rc;
+    if (int rc = rows_qkv<WT>(c, c->draft, c->dkv, c->pf_frag, c->zeros, 0, b0, nseq, l, TreeRows(), c->pf_gu, c->pf_qkv)) return rc;
+    hipLaunchKernelGGL(tail_rows_kernel, dim3(1, nseq), dim3(256), 0, c->stream, (const float*)c->pf_x, l, l - 1, c->pf_xt, d);
+    if (int rc = rows_attn_mlp<WT>(c, c->draft, c->dkv, c->pf_qkv + (size_t)(l - 1) * qd, l, l - 1, b0, nseq, 1, c->pf_xt, &p)) return rc;
+    hipLaunchKernelGGL(add_parts_kernel, dim3(nseq, row_chunks(nseq)), dim3(256), 0, c->stream, (const float*)c->pf_xt, p, d, c->catD + (size_t)b0 * 2 * d, 2 * d);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
@@ -1151,15 +1238,16 @@ int do_prefill(hivis_ctx* c, const void* vis_embeds, int v, const int32_t* text_
     if (c->bar) hipLaunchKernelGGL(set_ints_kernel, dim3(1), dim3(64), 0, c->stream, (int*)c->bar, 2, 0);
 
     const int total = v + l;
-    for (int b = 0; b < B; ++b) {
-        if (c->pf_rows >= total) {
-            if (int rc = prefill_target_tall<WT>(c, b, v, l)) return rc;
-            continue;
-        }
+    const bool tall = sizeof(WT) == 2;                       // bf16 models: whole prompts; else chunks of the decode passes' size
+    const int per = tall ? std::max(1, std::min(B, c->pf_rows / total)) : 1;
+    if constexpr (sizeof(WT) == 2)
+        for (int b = 0; b < B; b += per)
+            if (int rc = prefill_target_tall<WT>(c, b, std::min(per, B - b), v, l)) return rc;
+    for (int b = 0; b < B && !tall; ++b) {
         for (int p0 = 0; p0 < total; p0 += CHAIN_MAX_ROWS) {
             const int m = std::min(CHAIN_MAX_ROWS, total - p0);
-            hipLaunchKernelGGL((prefill_rows_kernel<WT>), dim3(m), dim3(256), 0, c->stream, (const WT*)c->vis + (size_t)b * g.max_vis * d, v,
-                               (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), p0, c->x, d);
+            hipLaunchKernelGGL((prefill_rows_kernel<WT>), dim3(m), dim3(256), 0, c->stream, (const WT*)c->vis + (size_t)b * g.max_vis * d, (size_t)0, v,
+                               (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), 0, p0, c->x, d);
             const int first_out = std::max(0, v - p0);       // rows of this chunk before the first text row produce no feature
             float* out = c->feat + ((size_t)b * g.max_text + std::max(0, p0 - v)) * d;
             if (int rc = target_forward<WT>(c, b, 1, m, c->zeros, p0, p0 + m, out, d, std::min(first_out, m))) return rc;
@@ -1171,7 +1259,10 @@ int do_prefill(hivis_ctx* c, const void* vis_embeds, int v, const int32_t* text_
     if (sample) hipLaunchKernelGGL(sample_rows_kernel, dim3(B), dim3(SAMPLE_NT), 0, c->stream, (const float*)c->logits_p, g.vocab, c->inv_temp, (const float*)c->u_res, 1, c->text + l, c->text_stride);
     else hipLaunchKernelGGL(argmax_kernel, dim3(B), dim3(256), 0, c->stream, (const float*)c->logits_p, g.vocab, c->text + l, c->text_stride, c->bad);
     // drafter prefill over the l text positions: rows [f^j ; Embed(x_{j+1})] + rho_0
-    for (int b = 0; b < B; ++b) {
+    if constexpr (sizeof(WT) == 2)
+        for (int b = 0; b < B; b += per)
+            if (int rc = prefill_drafter_tall<WT>(c, b, std::min(per, B - b), l)) return rc;
+    for (int b = 0; b < B && !tall; ++b) {
         for (int j0 = 0; j0 < l; j0 += CHAIN_MAX_ROWS) {
             const int m = std::min(CHAIN_MAX_ROWS, l - j0);
             hipLaunchKernelGGL((fuse_rows_kernel<WT>), dim3(m), dim3(256), 0, c->stream, (const float*)(c->feat + (size_t)b * g.max_text * d),
@@ -1476,7 +1567,9 @@ int build_embed_fc_table(hivis_ctx* c, const hivis_weights* w) {
         for (int r0 = 0; r0 < V && !rc; r0 += R) {
             const int n = std::min(R, V - r0);
             hipLaunchKernelGGL((rows_to_f32_kernel<WT>), dim3(1024), dim3(256), 0, c->stream, (const WT*)c->embed + (size_t)r0 * d, (size_t)n * d, c->pf_x);
-            rc = tall_gemm(c, c->pf_x, d, n, d, w2p, d, table + (size_t)r0 * d, d);
+            launch_pack(c, c->pf_x, d, n, d / 32);
+            TallOut o{}; o.Y = table + (size_t)r0 * d; o.ldy = d;
+            rc = launch_tall<TALL_STORE>(c, tall_plan(c, n, d / 32, d / 16, false), c->pf_frag, n, d, w2p, d, o);
         }
         if (rc) break;
         if (hipStreamSynchronize(c->stream) != hipSuccess) { rc = fail(c, HIVIS_EHIP, "building the embedding table of the fusion FC failed"); break; }
@@ -1566,29 +1659,19 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     if ((rc = dev_alloc(c, &c->dout, (size_t)R * d))) return rc;
     if ((rc = dev_alloc(c, &c->feat, (size_t)B * g.max_text * d))) return rc;
     if (sizeof(WT) == 2) {
-        if ((rc = tall_setup(c))) return rc;
-        const int PR = (g.max_vis + g.max_text + 15) & ~15;        // whole row tiles
+        if ((rc = tall_setup<TALL_STORE>(c)) || (rc = tall_setup<TALL_SILU>(c)) || (rc = tall_setup<TALL_QKV>(c))) return rc;
+        // rows of the prefill buffers: the longest prompt, or as many sequences at a time as fit 4096 rows
+        const int one = g.max_vis + g.max_text;
+        const int PR = (std::max(one, std::min(B * one, 4096)) + 15) & ~15;        // whole row tiles
         c->pf_rows = PR;
-        const size_t kmax = std::max({(size_t)d, (size_t)qd, (size_t)F});
         if ((rc = dev_alloc(c, &c->pf_x, (size_t)PR * d))) return rc;
-        if ((rc = dev_alloc(c, &c->pf_a, (size_t)PR * d))) return rc;
-        if ((rc = dev_alloc(c, &c->pf_qkv, (size_t)PR * (qd + 2 * kd)))) return rc;
-        if ((rc = dev_alloc(c, &c->pf_att, (size_t)PR * qd))) return rc;
+        if ((rc = dev_alloc(c, &c->pf_xt, (size_t)std::min(PR, B * g.max_text) * d))) return rc;
+        if (d > 4 * WNORM_NT * WNORM_GROUPS && (rc = dev_alloc(c, &c->pf_a, (size_t)PR * d))) return rc;
+        if ((rc = dev_alloc(c, &c->pf_qkv, std::max((size_t)PR * qd, (size_t)R * (qd + 2 * kd))))) return rc;
         if ((rc = dev_alloc(c, &c->pf_proj, (size_t)PR * d))) return rc;
-        if ((rc = dev_alloc(c, &c->pf_gu, (size_t)PR * 2 * F))) return rc;
-        if ((rc = dev_alloc(c, &c->pf_act, (size_t)PR * F))) return rc;
-        if ((rc = dev_alloc(c, &c->pf_frag, (size_t)PR * kmax / 4))) return rc;      // PR*kmax*4 bytes in 16-byte units
-    }
-    // attention workspace: (items * nsplit) work groups x 4 wave slots x RMAX rows x (hd + 2) floats, where
-    // items * nsplit <= 2 * num_cu + items and items <= max(2, B) * n_q_heads
-    {
-        size_t max_items = (size_t)std::max({2, B, MAX_ROWS / ATT_RMAX}) * g.n_q_heads;
-        if (c->pf_rows) max_items = std::max(max_items, (size_t)g.n_q_heads * ((c->pf_rows + ATT_RMAX - 1) / ATT_RMAX));
-        c->attn_ws_floats = (2 * (size_t)c->num_cu + max_items) * 4 * ATT_RMAX * (g.head_dim + 2);
-        if ((rc = dev_alloc(c, &c->attn_ws, c->attn_ws_floats))) return rc;
-        c->rows_cnt_n = std::max(2, B) * g.n_q_heads;
-        if ((rc = dev_alloc(c, &c->rows_cnt, (size_t)c->rows_cnt_n))) return rc;
-        HIP_TRY(c, hipMemset(c->rows_cnt, 0, (size_t)c->rows_cnt_n * sizeof(int)));
+        if ((rc = dev_alloc(c, &c->pf_gu, (size_t)R * std::max(2 * F, qd + 2 * kd)))) return rc;      // (more rows: finished in the GEMM, or K slices)
+        if ((rc = dev_alloc(c, &c->pf_frag, (size_t)PR * std::max(2 * d, qd) / 4))) return rc;      // 4 bytes per value, in 16-byte units
+        if ((rc = dev_alloc(c, &c->pf_frag2, (size_t)PR * F / 4))) return rc;
     }
     if ((rc = dev_alloc(c, &c->logits_v, (size_t)R * V))) return rc;
     if ((rc = dev_alloc(c, &c->logits_d, (size_t)g.k_max * B * V))) return rc;
@@ -1617,6 +1700,20 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
         HIP_TRY(c, hipGetLastError());
     }
     if ((rc = fused_setup<WT>(c))) return rc;
+    // (attention rows of a whole-prompt pass: as fragments except from passes of at most 8 rows per sequence, and HIVIS_FUSED=0)
+    if (c->pf_rows && (rc = dev_alloc(c, &c->pf_att, (size_t)(c->fused ? B * FUSED_RMAX : c->pf_rows) * qd))) return rc;
+    // attention workspace: (items * nsplit) work groups x 4 wave slots x RMAX rows x (hd + 2) floats, where
+    // items * nsplit <= 2 * num_cu + items and items <= max(2, B) * n_q_heads
+    {
+        size_t max_items = (size_t)std::max({2, B, MAX_ROWS / ATT_RMAX}) * g.n_q_heads;
+        // (whole-prompt passes use it with HIVIS_FUSED=0 only)
+        if (c->pf_rows && !c->fused) max_items = std::max(max_items, (size_t)g.n_q_heads * ((c->pf_rows + ATT_RMAX - 1) / ATT_RMAX + B));
+        c->attn_ws_floats = (2 * (size_t)c->num_cu + max_items) * 4 * ATT_RMAX * (g.head_dim + 2);
+        if ((rc = dev_alloc(c, &c->attn_ws, c->attn_ws_floats))) return rc;
+        c->rows_cnt_n = std::max(2, B) * g.n_q_heads;
+        if ((rc = dev_alloc(c, &c->rows_cnt, (size_t)c->rows_cnt_n))) return rc;
+        HIP_TRY(c, hipMemset(c->rows_cnt, 0, (size_t)c->rows_cnt_n * sizeof(int)));
+    }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     if ((rc = build_embed_fc_table<WT>(c, w))) return rc;
     return HIVIS_OK;

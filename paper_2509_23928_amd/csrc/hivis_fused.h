@@ -942,7 +942,7 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
     {
         const int rq = min(n16, R - 1);
         const int hh = kvh * group + h0 + rq / ni, i = i0 + rq % ni;
-        const float* qrow = q + (size_t)(sl * sh.m + i) * sh.ldq + (size_t)hh * HD + g * 8;
+        const float* qrow = q + (size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + g * 8;
         const float scale = (n16 < R) ? rsqrtf((float)HD) : 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -1086,7 +1086,8 @@ __host__ __device__ constexpr size_t attn_shared_lds_bytes(int hd) { return 2 * 
 
 template <int HD>
 __global__ __launch_bounds__(FUSED_NT) void attn_rows_shared_kernel(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
-                                                                    const int* __restrict__ base, AttnShape sh, float* __restrict__ out, int ldo) {
+                                                                    const int* __restrict__ base, AttnShape sh, int ldo, uint4* __restrict__ frag_out) {
+    // (the rows go out as activation fragments of the O projection, K = ldo)
     extern __shared__ __align__(16) float attn_shared_lds[];
     constexpr int HALFB = HD * 2, ROWB = HD * 4, KS = HD / 32, NB = HD / 16, NCH = ROWB / 16;
     constexpr int VSTRIDE = ROWB + 32, KSTRIDE = ROWB + 16;
@@ -1129,7 +1130,7 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_shared_kernel(const float*
 
     f16x8_t qh[KS], ql[KS];
     {
-        const float* qrow = q + (size_t)(sl * sh.m + i0 + min(r, ni - 1)) * sh.ldq + (size_t)hh * HD + g * 8;
+        const float* qrow = q + (size_t)attn_qrow(sh, sl, i0 + min(r, ni - 1)) * sh.ldq + (size_t)hh * HD + g * 8;
         const float scale = valid ? rsqrtf((float)HD) : 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -1212,10 +1213,9 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_shared_kernel(const float*
     lsum += __shfl_xor(lsum, 32, 64);
     if (valid) {
         const float inv = 1.f / lsum;
-        float* orow = out + (size_t)(sl * sh.m + i0 + r) * ldo + (size_t)hh * HD + 4 * g;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
-            *reinterpret_cast<float4*>(orow + nb * 16) = make_float4(acc[nb][0] * inv, acc[nb][1] * inv, acc[nb][2] * inv, acc[nb][3] * inv);
+            store_afrag4(frag_out, ldo / 32, sl * sh.m + i0 + r, hh * HD + nb * 16 + 4 * g, acc[nb][0] * inv, acc[nb][1] * inv, acc[nb][2] * inv, acc[nb][3] * inv);
     }
 }
 
@@ -1280,7 +1280,7 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
     for (int idx = threadIdx.x; idx < R * HD; idx += FUSED_NT) {
         const int r = idx / HD, c = idx % HD;
         const int hh = kvh * group + h0 + r / ni, i = i0 + r % ni;
-        qs[idx] = q[(size_t)(sl * sh.m + i) * sh.ldq + (size_t)hh * HD + c] * scale;
+        qs[idx] = q[(size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + c] * scale;
     }
     lds_barrier();
     HIVIS_AMARK(2)

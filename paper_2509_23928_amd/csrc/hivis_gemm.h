@@ -28,6 +28,15 @@ __device__ __forceinline__ void store_afrag8(uint4* __restrict__ frag, int kblks
     frag[at] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
     frag[at + 64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
 }
+// 4 consecutive values of row `row` at k (a multiple of 4) -> half of the high and of the low chunk
+__device__ __forceinline__ void store_afrag4(uint4* __restrict__ frag, int kblks, int row, int k, float a, float b, float c, float d) {
+    uint2* at = reinterpret_cast<uint2*>(frag + afrag_at(kblks, row, k)) + ((k >> 2) & 1);
+    uint2 hi, lo;
+    f32_to_bf16x2_hilo(a, b, hi.x, lo.x);
+    f32_to_bf16x2_hilo(c, d, hi.y, lo.y);
+    at[0] = hi;
+    at[128] = lo;
+}
 
 // rows of fp32 -> fragments; rows >= M of the last row tile become zeros
 __global__ void pack_afrag_kernel(const float* __restrict__ A, int lda, int M, int kblks, uint4* __restrict__ out) {
@@ -96,7 +105,8 @@ __device__ __forceinline__ void block_to_lds(const v4u_t* src, v4u_t* lds) {
 // tiles) were no faster at 3008 rows and left too few tiles at 640.
 // ------------------------------------------------------------------------------------------
 constexpr int TALL_THREADS = 512, TALL_ROWS = 128;
-template <int CW> constexpr int tall_lds_bytes() { return 4 * (16 + 2 * CW) * 1024; }
+// (a ring of four K blocks; at the end one area of 64 rows x 64 columns per wavefront)
+template <int CW> constexpr int tall_lds_bytes() { return 4 * (16 + 2 * CW) > 128 ? 4 * (16 + 2 * CW) * 1024 : 128 * 1024; }
 
 #define HIVIS_PHASE_END(wait_)                               \
     do {                                                     \
@@ -105,11 +115,103 @@ template <int CW> constexpr int tall_lds_bytes() { return 4 * (16 + 2 * CW) * 10
         __builtin_amdgcn_sched_barrier(0);                   \
     } while (0)
 
-// ksplit > 1: the K range is cut into slices, slice s writes its sums to part[s][M][ldy] and the consumer adds them
-template <int CW>
+// What becomes of the result:
+//   TALL_STORE  fp32 rows; ksplit > 1: the K range is cut into slices, slice s writes its sums to part[s][M][ldy] and the
+//               consumer adds them
+//   TALL_SILU   W = gate|up (8 + 8 columns per tile): silu(gate) * up leaves as activation fragments of the down projection
+//   TALL_QKV    W = q|k|v of whole prompts: bias and rotary embedding applied; q leaves as fp32 rows, k and v go to the cache
+//               (row of sequence seq0 + row / m at position row % m)
+// (the fp32 rows of gate|up and q|k|v were the largest results of a layer: writing them here and reading them in a row kernel
+// cost 20 + 22 us per layer at 640 rows and 112 + 103 us at 3008, beside the GEMMs' own stores)
+enum { TALL_STORE = 0, TALL_SILU = 1, TALL_QKV = 2 };
+struct TallOut {
+    float* Y; int ldy;
+    float* part;
+    uint4* frag; int kblks_out;
+    const float* bias; const float* rope; int npos;       // [q_dim + 2 kv_dim] or null; table of (cos, sin) per position and pair
+    int seq0, m, qd, kd, HD, Hkv, maxL;
+    f16_t *kc, *vc;
+};
+
+// A wavefront's finished 64 rows x NT column tiles, in its own LDS area as [64][4 NT] pieces of four columns (piece p of row
+// r at p ^ (r & 15) of 16, so that neither side conflicts), to memory: consecutive lanes take consecutive pieces of a row,
+// or for fragments the 16 rows of a chunk, so that stores cover whole 128-byte lines (straight from the accumulators a
+// store touched 16 rows, 32 bytes of each in the cache: q|k|v of 640 rows 115 us against 94 us for plain rows).
+template <int NT, int EPI>
+__device__ __forceinline__ void tall_write(const TallOut& o, const v4u_t* area, int row0, int ct0, int M, int ntiles, float* Y, int lane) {
+    if constexpr (EPI == TALL_SILU) {
+        for (int it = lane; it < 64 * NT; it += 64) {
+            const int r = (it & 15) + 16 * (it / (16 * NT)), t = (it >> 4) % NT, row = row0 + r;
+            f32x4_t p[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = __builtin_bit_cast(f32x4_t, area[r * 16 + ((4 * t + e) ^ (r & 15))]);
+            if (row < M && ct0 + t < ntiles) {
+                float y[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { const float ga = p[e >> 2][e & 3], up = p[2 + (e >> 2)][e & 3]; y[e] = ga / (1.0f + expf(-ga)) * up; }
+                store_afrag8(o.frag, o.kblks_out, row, 8 * (ct0 + t), y, false);
+            }
+        }
+    } else {
+        // a lane keeps one piece (four columns) and walks the rows, RPI rows per trip
+        constexpr int P = 4 * NT, RPI = 64 / P, TRIPS = (64 + RPI - 1) / RPI;
+        const int p = lane % P, col = ct0 * 16 + 4 * p;
+        int r = lane / P;
+        if (r >= RPI || ct0 + (p >> 2) >= ntiles) return;
+        if constexpr (EPI == TALL_STORE) {
+#pragma unroll 4
+            for (int i = 0; i < TRIPS; ++i, r += RPI)
+                if (r < 64 && row0 + r < M) *reinterpret_cast<v4u_t*>(Y + (size_t)(row0 + r) * o.ldy + col) = area[r * 16 + (p ^ (r & 15))];
+        } else {
+            const bool isq = col < o.qd, isk = !isq && col < o.qd + o.kd;
+            const int head = (col - (isq ? 0 : isk ? o.qd : o.qd + o.kd)) / o.HD, c = col % o.HD;
+            f32x4_t bias = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (o.bias) bias = *reinterpret_cast<const f32x4_t*>(o.bias + col);
+            int s = (row0 + r) / o.m, pos = row0 + r - s * o.m;
+            typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
+            // (four rows per trip, their table entries requested together: one memory round trip per row cost 13 us per tile)
+            constexpr int U = 4;
+            for (int i = 0; i < TRIPS; i += U) {
+                f32x4_t t[U], x[U];
+                int sq[U], ps[U], rw[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    sq[u] = o.seq0 + s; ps[u] = pos; rw[u] = r;
+                    t[u] = *reinterpret_cast<const f32x4_t*>(o.rope + (size_t)min(pos, o.npos - 1) * o.HD + c);
+                    x[u] = __builtin_bit_cast(f32x4_t, area[min(r, 63) * 16 + (p ^ (r & 15))]);
+                    r += RPI; pos += RPI;
+                    while (pos >= o.m) { pos -= o.m; ++s; }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (rw[u] >= 64 || row0 + rw[u] >= M) continue;
+                    f32x4_t y = x[u] + bias;
+                    if (isq || isk) {
+                        // columns 2i, 2i+1 of a head are the rotary pair (i, i + HD/2); two pairs
+                        const f32x4_t z = y;
+                        y[0] = (float)((double)z[0] * (double)t[u][0] - (double)z[1] * (double)t[u][1]);
+                        y[1] = (float)((double)z[1] * (double)t[u][0] + (double)z[0] * (double)t[u][1]);
+                        y[2] = (float)((double)z[2] * (double)t[u][2] - (double)z[3] * (double)t[u][3]);
+                        y[3] = (float)((double)z[3] * (double)t[u][2] + (double)z[2] * (double)t[u][3]);
+                    }
+                    if (isq) *reinterpret_cast<f32x4_t*>(o.Y + (size_t)(row0 + rw[u]) * o.ldy + col) = y;
+                    else {
+                        f16_t* dst = (isk ? o.kc : o.vc) + (((size_t)sq[u] * o.Hkv + head) * o.maxL + ps[u]) * o.HD * 2 + c;
+                        h4_t hi, lo;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { hi[e] = (f16_t)fminf(fmaxf(y[e], -65504.f), 65504.f); lo[e] = (f16_t)(y[e] - (float)hi[e]); }
+                        *reinterpret_cast<h4_t*>(dst) = hi;
+                        *reinterpret_cast<h4_t*>(dst + o.HD) = lo;
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <int CW, int EPI>
 __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t* __restrict__ Af, int row_tiles, int kblks,
-                                                                   const v4u_t* __restrict__ Wp, int ntiles, float* __restrict__ Y, int ldy,
-                                                                   int M, int ksplit, float* __restrict__ part) {
+                                                                   const v4u_t* __restrict__ Wp, int ntiles, int M, int ksplit, TallOut o) {
     constexpr int RT = TALL_ROWS / 16, CT = 2 * CW;       // row and column tiles of the workgroup
     constexpr int NA = 2 * RT, NBLK = NA + CT;            // blocks of one K block
     constexpr int PER = (NBLK + 3) / 4;                   // blocks each wavefront of a group fetches per K block
@@ -129,7 +231,6 @@ __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t*
     const int panel = tid / (prows * ncol), inp = tid - panel * prows * ncol, pr = min(prows, nrow - panel * prows);
     const int rblk = panel * prows + inp % pr, cblk = inp / pr;
     const int kper = (kblks + ksplit - 1) / ksplit, kbeg = split * kper, nkb = min(kblks, kbeg + kper) - kbeg;
-    if (ksplit > 1) Y = part + (size_t)split * M * ldy;
     const int rt_wg = rblk * RT, ct_wg = cblk * CT;
 
     // the blocks this wavefront fetches per K block: id b < NA is the high / low part b & 1 of row tile b / 2, else column
@@ -215,17 +316,23 @@ __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t*
 #pragma unroll
         for (int c = 0; c < CW; ++c)
             if ((c < CH) == (grp == 0)) acc[r][c] += __builtin_bit_cast(f32x4_t, ex[(size_t)((w4 * 4 + r) * CW + c) * 64]);
-    const int row0 = (rt_wg + wr * 4) * 16 + (lane & 15), col0 = (ct_wg + wc * CW) * 16 + 4 * (lane >> 4);
+    float* const Y = (EPI == TALL_STORE && ksplit > 1) ? o.part + (size_t)split * M * o.ldy : o.Y;
+    HIVIS_PHASE_END("lgkmcnt(0)");                        // every exchanged tile has been read
+    v4u_t* const area = tall_lds + (size_t)wave * 64 * 16;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = row0 + 16 * r;
-        if (row >= M) continue;
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int c = 0; c < CW; ++c) {
-            if ((c < CH) != (grp == 0) || ct_wg + wc * CW + c >= ntiles) continue;
-            *reinterpret_cast<f32x4_t*>(Y + (size_t)row * ldy + col0 + 16 * c) = acc[r][c];
-        }
-    }
+        for (int c = 0; c < CW; ++c)
+            if ((c < CH) == (grp == 0)) {
+                const int rr = 16 * r + (lane & 15), p = 4 * (c < CH ? c : c - CH) + (lane >> 4);
+                area[rr * 16 + (p ^ (rr & 15))] = __builtin_bit_cast(v4u_t, acc[r][c]);
+            }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int row0 = (rt_wg + wr * 4) * 16, ct0 = ct_wg + wc * CW;
+    if (grp == 0) tall_write<CH, EPI>(o, area, row0, ct0, M, ntiles, Y, lane);
+    else tall_write<CW - CH, EPI>(o, area, row0, ct0 + CH, M, ntiles, Y, lane);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -648,6 +648,7 @@ struct AttnShape {
     int n_hblk, n_rblk;      // ceil(group/gh), ceil(m/mi)
     int seq0, offset, maxL, nsplit;
     int ldq;                 // row stride of the q buffer
+    int qrows;               // rows between two sequences in the q buffer (0: m)
     int nwaves;              // wavefronts per workgroup working on one (item, split)
     int flags;               // bit 0: the election of the merging workgroup relies on agent-scope stores, loads and the
                              //        arrival counter alone (clear: an agent-scope release / acquire fence pair around it as well);
@@ -659,6 +660,7 @@ struct AttnShape {
     // set in tmask[i] (its ancestors among the tree rows and itself), instead of the causal rule
     const unsigned long long* tmask;
 };
+__device__ __forceinline__ int attn_qrow(const AttnShape& sh, int sl, int i) { return sl * (sh.qrows ? sh.qrows : sh.m) + i; }
 // visibility of key `key` for a row with causal limit qpos (tm, tb: the row's tree mask and the tree's first slot)
 __device__ __forceinline__ bool attn_visible(bool tree, int key, int qpos, unsigned long long tm, int tb) {
     if (!tree) return key <= qpos;
@@ -706,7 +708,7 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
     for (int idx = threadIdx.x; idx < R * HD; idx += nthreads) {
         const int r = idx / HD, c = idx % HD;
         const int hh = kvh * group + h0 + r / ni, i = i0 + r % ni;
-        qs[idx] = q[(size_t)(sl * sh.m + i) * sh.ldq + (size_t)hh * HD + c] * scale;
+        qs[idx] = q[(size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + c] * scale;
     }
     lds_barrier();
 
@@ -949,13 +951,21 @@ __global__ void gather_rows_kernel(const WT* __restrict__ table, const int32_t* 
     for (int c = threadIdx.x; c < d; c += blockDim.x) out[(size_t)row * ldo + c] = to_f32(src[c]);
 }
 
-// Prefill input rows of one sequence: position p < v -> visual embedding p, else Embed(text[p - v]).
+// Prefill input rows of sequences blockIdx.y: position p < v -> visual embedding p, else Embed(text[p - v]).
 template <typename WT>
-__global__ void prefill_rows_kernel(const WT* __restrict__ vis, int v, const WT* __restrict__ table,
-                                    const int32_t* __restrict__ text, int p0, float* __restrict__ out, int d) {
-    const int p = p0 + blockIdx.x;
-    const WT* src = (p < v) ? vis + (size_t)p * d : table + (size_t)text[p - v] * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) out[(size_t)blockIdx.x * d + c] = to_f32(src[c]);
+__global__ void prefill_rows_kernel(const WT* __restrict__ vis, size_t vis_stride, int v, const WT* __restrict__ table,
+                                    const int32_t* __restrict__ text, int text_stride, int p0, float* __restrict__ out, int d) {
+    const int p = p0 + blockIdx.x, s = blockIdx.y;
+    const WT* src = (p < v) ? vis + s * vis_stride + (size_t)p * d : table + (size_t)text[(size_t)s * text_stride + p - v] * d;
+    float* o = out + ((size_t)s * gridDim.x + blockIdx.x) * d;
+    for (int c = threadIdx.x; c < d; c += blockDim.x) o[c] = to_f32(src[c]);
+}
+
+// dst row s * n + i = src row s * m + first + i (n rows of each of gridDim.y sequences)
+__global__ void tail_rows_kernel(const float* __restrict__ src, int m, int first, float* __restrict__ dst, int d) {
+    const float4* a = reinterpret_cast<const float4*>(src + ((size_t)blockIdx.y * m + first + blockIdx.x) * d);
+    float4* o = reinterpret_cast<float4*>(dst + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * d);
+    for (int c = threadIdx.x; c < d / 4; c += blockDim.x) o[c] = a[c];
 }
 
 // Fusion input rows [f_j ; Embed(x_{j+1})] for drafter prefill rows j0.. of one sequence.

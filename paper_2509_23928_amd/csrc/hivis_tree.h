@@ -302,12 +302,12 @@ __global__ void tree_finish_kernel(const float* __restrict__ dout, const int32_t
 // consecutive columns and requests all slices of them at once (up to 16 loads in flight: with 8 columns per thread and
 // 8 slices per trip the kernel paid four memory round trips per row); two neighbouring lanes then hold the 8 values of
 // one fragment chunk, exchange them, and the even lane writes the chunk's high parts, the odd lane its low parts.
-constexpr int WNORM_NT = 1024;
+constexpr int WNORM_NT = 1024, WNORM_GROUPS = 2;
 template <typename WT>
 __global__ __launch_bounds__(WNORM_NT) void wide_add_norm_frag_kernel(float* __restrict__ h, int ldh, Parts delta, int ldd, int M,
                                                                   const WT* __restrict__ gain, uint4* __restrict__ frag, int d, float eps) {
     __shared__ float part[WNORM_NT / 64];
-    constexpr int MAXG = 2;                         // groups of 4 values per thread
+    constexpr int MAXG = WNORM_GROUPS;              // groups of 4 values per thread
     const int row = blockIdx.x, ng = d / 4, kblks = d / 32;
     const bool live = row < M;
     const int rr = min(row, M - 1);
@@ -362,6 +362,38 @@ __global__ __launch_bounds__(WNORM_NT) void wide_add_norm_frag_kernel(float* __r
             if (!live) w4 = make_uint4(0u, 0u, 0u, 0u);
             frag[afrag_at(kblks, row, k0) + (odd ? 64 : 0)] = w4;
         }
+    }
+}
+
+// Fusion FC input of a drafter prefill: row s * l + j (j < l) is [f^j ; Embed(x_{j+1})] of sequence s as fragments, and its
+// residual row starts as rho_0 (feat: `fstride` rows per sequence; text: x of the sequence, tstride apart).  With the table
+// Embed(x) w2 (tab) the fragments hold f^j alone and the residual row starts as rho_0 + tab[x_{j+1}].  Rows >= M: zero fragments.
+template <typename WT>
+__global__ void fuse_frag_kernel(const float* __restrict__ feat, int fstride, int l, int M, const int32_t* __restrict__ text, int tstride,
+                                 const WT* __restrict__ table, const float* __restrict__ tab, const WT* __restrict__ rho,
+                                 float* __restrict__ h, uint4* __restrict__ frag, int d) {
+    const int row = blockIdx.x;
+    const bool live = row < M;
+    const int rr = min(row, M - 1), s = rr / l, j = rr - s * l;
+    const float* f = feat + ((size_t)s * fstride + j) * d;
+    const int tok = text[(size_t)s * tstride + j + 1];
+    const int K = tab ? d : 2 * d;
+    for (int k = 8 * threadIdx.x; k < K; k += 8 * blockDim.x) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = k < d ? f[k + e] : to_f32(table[(size_t)tok * d + k - d + e]);
+        store_afrag8(frag, K / 32, row, k, x, !live);
+    }
+    if (live)
+        for (int k = threadIdx.x; k < d; k += blockDim.x) h[(size_t)row * d + k] = to_f32(rho[k]) + (tab ? tab[(size_t)tok * d + k] : 0.f);
+}
+
+// out row = h row + sum of the partials (d a multiple of 4)
+__global__ void add_parts_kernel(const float* __restrict__ h, Parts ps, int d, float* __restrict__ out, int ldo) {
+    const int row = blockIdx.x;
+    for (int c4 = blockIdx.y * blockDim.x + threadIdx.x; c4 < d / 4; c4 += gridDim.y * blockDim.x) {
+        const float4 a = *reinterpret_cast<const float4*>(h + (size_t)row * d + 4 * c4), b = parts_load4(ps, (size_t)row * d + 4 * c4);
+        *reinterpret_cast<float4*>(out + (size_t)row * ldo + 4 * c4) = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
     }
 }
 
