@@ -98,7 +98,7 @@ struct hivis_ctx {
 
     // persistent-kernel path (passes of at most one MFMA tile of rows)
     bool fused = false;
-    int fused_grid = 0; size_t fused_lds = 0;
+    int fused_grid = 0; size_t fused_lds = 0, fused_lds_w = 0;      // LDS of a phase launch; of the bf16w kernels
     float* rope_tab = nullptr; float* pm = nullptr; int* pi = nullptr; unsigned* bar = nullptr;
     float* fattn_ws = nullptr; size_t fattn_ws_floats = 0;
     struct Program { hivis::Phase* dev = nullptr; int n = 0; std::vector<hivis::Phase>* host = nullptr; };
@@ -115,6 +115,8 @@ struct hivis_ctx {
     int tk = 0, tdepth = 0, tn = 0;                       // top-k, depth, candidates of the current tree
     int vrows = 0;                                        // rows of the last verify pass (chain: B*(K+1); tree: N+1)
     float *tH = nullptr, *tlogits = nullptr, *tcat = nullptr, *troll = nullptr;
+    int32_t* ttok_rows = nullptr;                         // tokens of a level's rows
+    float* tree_pool[17] = {};                            // buffers of tree_rows_program by row count (allocated at first use)
     float *tcand_v = nullptr, *tseg = nullptr; int32_t* tcand_i = nullptr; int tnseg = 0;   // per-segment top-k candidates and (max, sum) partials   // hidden rows, their logits, level inputs, re-feed inputs
     void** kv_ptrs = nullptr; void* kv_staging = nullptr;
     float* splitk_ws = nullptr; size_t splitk_floats = 0; bool no_wide_gemm = false; int wide_min = 11;   // measured: 10-row passes faster on the skinny kernels, 12-row passes on the split-K layer   // K-slice partials of the wide GEMM; HIVIS_WIDE_GEMM=0 disables it
@@ -508,8 +510,10 @@ int drafter_forward(hivis_ctx* c, const float* cat, int seq0, int nseq, int m, i
 // ---- persistent-kernel path --------------------------------------------------------------------
 enum { PROG_VERIFY = 0, PROG_DRAFT = 1, PROG_ROLL = 2, PROG_DRAFT_SAMPLE = 3 };
 
+// Rows a phase program takes: one MFMA tile; bf16 models, one launch per phase: up to 16, through the bf16w kernels (a
+// 12-row verify pass of the 7B widths as a program: see the table at gemm_phase's bf16w configuration).
 template <typename WT>
-bool fused_rows_ok(int M) { return M <= WTraits<WT>::ROWS; }
+bool fused_rows_ok(const hivis_ctx* c, int M) { return M <= (sizeof(WT) == 2 && !c->persistent ? WTraits<bf16w_t>::ROWS : WTraits<WT>::ROWS); }
 
 AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, int ldq, int* items_out) {
     const hivis_config& g = c->cfg;
@@ -745,8 +749,12 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         if (do_prof) { ppl.prof2 = pp.prof2 + (size_t)p * 8; if (p >= n / 2 && p < n / 2 + 8) ppl.prof3 = c->prof + 4096 * 11 + (size_t)(p - n / 2) * 4096; }
         // kev0/kev1 (null unless this launch is timed) are attached to the dispatch itself: they read the kernel's own
         // start and end timestamps, with no marker packets before or after it in the queue
-#define HIVIS_LAUNCH(TY, EP) do { if (single) hipExtLaunchKernelGGL((phase_kernel<WT, TY, EP, true>), dim3(grid), dim3(FUSED_NT), c->fused_lds, c->stream, kev0, kev1, 0, ph, ppl); \
-                              else hipExtLaunchKernelGGL((phase_kernel<WT, TY, EP, false>), dim3(grid), dim3(FUSED_NT), c->fused_lds, c->stream, kev0, kev1, 0, ph, ppl); } while (0)
+        // (bf16w has GEMM kernels only: the other phases work on fp32 rows)
+        typedef typename std::conditional<std::is_same<WT, bf16w_t>::value, bf16_t, WT>::type RT;
+        const size_t lds = ph.type == PH_GEMM && std::is_same<WT, bf16w_t>::value ? c->fused_lds_w : c->fused_lds;
+#define HIVIS_LAUNCH(TY, EP) do { typedef typename std::conditional<TY == PH_GEMM, WT, RT>::type KT_; \
+                              if (single) hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, true>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); \
+                              else hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, false>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); } while (0)
         const bool single = ph.type == PH_GEMM && ph.epi != FEPI_LOGITS && ph.epi != FEPI_SILU && ph.epi != FEPI_QKV && ph.N / 16 <= grid;   // one tile per workgroup at most
         const bool kmatch = kind == PROG_VERIFY && ph.type == PH_GEMM && ph.epi == c->ktime_epi;
         const int64_t kseq = kmatch ? c->ktime_seen++ : 0;
@@ -761,13 +769,14 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         switch (ph.type) {
         case PH_GEMM:
             switch (ph.epi) {
-            case FEPI_STORE: HIVIS_LAUNCH(PH_GEMM, FEPI_STORE); break;
             case FEPI_ADD_TO: HIVIS_LAUNCH(PH_GEMM, FEPI_ADD_TO); break;
             case FEPI_ADDVEC: HIVIS_LAUNCH(PH_GEMM, FEPI_ADDVEC); break;
             case FEPI_QKV:
-                if (ph.add_rows && pp.M <= 2) HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB);
-                else if (ph.add_rows) HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB4);
-                else HIVIS_LAUNCH(PH_GEMM, FEPI_QKV);
+                if constexpr (!std::is_same<WT, bf16w_t>::value) {      // (table rows are added for at most four sequences)
+                    if (ph.add_rows && pp.M <= 2) { HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB); break; }
+                    if (ph.add_rows) { HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB4); break; }
+                }
+                HIVIS_LAUNCH(PH_GEMM, FEPI_QKV);
                 break;
             case FEPI_SILU: HIVIS_LAUNCH(PH_GEMM, FEPI_SILU); break;
             default: HIVIS_LAUNCH(PH_GEMM, FEPI_LOGITS); break;
@@ -802,6 +811,9 @@ int run_program(hivis_ctx* c, int kind, int K, int nseq, int m) {
     pp.prof = do_prof ? c->prof : nullptr;
     pp.prof2 = do_prof ? c->prof + 4096 * 3 : nullptr;
     if (!c->persistent) {
+        if constexpr (std::is_same<WT, bf16_t>::value) {
+            if (pp.M > WTraits<WT>::ROWS) return launch_phases<bf16w_t>(c, pg.host->data(), pg.n, kind, K, pp, false);
+        }
         if (int rc = launch_phases<WT>(c, pg.host->data(), pg.n, kind, K, pp, do_prof)) return rc;
         if (do_prof) {
             // developer aid: timestamps (100 MHz) that workgroup 0 of each launch wrote, for one layer in the middle
@@ -905,7 +917,7 @@ int fused_setup(hivis_ctx* c) {
     const hivis_config& g = c->cfg;
     const char* env = getenv("HIVIS_FUSED");
     if (env && env[0] == '0') { c->fused = false; return HIVIS_OK; }
-    const size_t gemm_f = fused_gemm_lds_floats(FusedCfg<WT>::NW, FusedCfg<WT>::G, TR::RPL, FusedCfg<WT>::KBW);
+    const size_t gemm_f = fused_gemm_lds_floats(FusedCfg<WT>::NW, FusedCfg<WT>::G, TR::RPL, FusedCfg<WT>::KBW, FUSED_CHUNK<WT>);
     const size_t attn_f = std::max(fused_attn_lds_floats(g.head_dim, FUSED_NW, FUSED_RMAX), fused_attn_mfma_lds_floats(g.head_dim, FUSED_NW, FUSED_RMAX));
     c->fused_lds = std::max(gemm_f, attn_f) * sizeof(float);
     // the attribute is per kernel, not per context: contexts with different head sizes may be alive together, so it only grows
@@ -913,16 +925,25 @@ int fused_setup(hivis_ctx* c) {
     lds_limit = std::max(lds_limit, c->fused_lds);
     HIP_TRY(c, hipFuncSetAttribute((const void*)fused_pass_kernel<WT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
     {
-        const void* ks[] = {(const void*)phase_kernel<WT, PH_GEMM, FEPI_STORE, false>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADD_TO, false>,
+        const void* ks[] = {(const void*)phase_kernel<WT, PH_GEMM, FEPI_ADD_TO, false>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADDVEC, false>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV, false>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB, false>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB4, false>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_SILU, false>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, false>,
-                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_STORE, true>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADD_TO, true>,
+                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADD_TO, true>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADDVEC, true>,
                             (const void*)phase_kernel<WT, PH_ATTN, 0, false>, (const void*)phase_kernel<WT, PH_ATTN_MERGE, 0, false>,
                             (const void*)phase_kernel<WT, PH_PREP, 0, false>, (const void*)phase_kernel<WT, PH_NORM_ROWS, 0, false>,
                             (const void*)phase_kernel<WT, PH_ARGMAX, 0, false>, (const void*)phase_kernel<WT, PH_SAMPLE, 0, false>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
+    }
+    if constexpr (std::is_same<WT, bf16_t>::value) {
+        typedef FusedCfg<bf16w_t> CW;
+        c->fused_lds_w = fused_gemm_lds_floats(CW::NW, CW::G, WTraits<bf16w_t>::RPL, CW::KBW, FUSED_CHUNK<bf16w_t>) * sizeof(float);
+        const void* ks[] = {(const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_ADD_TO, false>, (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_ADD_TO, true>,
+                            (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_ADDVEC, false>, (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_ADDVEC, true>,
+                            (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_QKV, false>, (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_SILU, false>,
+                            (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_LOGITS, false>};
+        for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->fused_lds_w));
     }
     { const char* pe = getenv("HIVIS_PERSISTENT"); c->persistent = pe && pe[0] == '1'; }
     { const char* we = getenv("HIVIS_WIDE_GEMM"); c->no_wide_gemm = we && we[0] == '0'; }
@@ -1294,7 +1315,7 @@ int do_draft(hivis_ctx* c, int K, bool sample) {
     const hivis_config& g = c->cfg;
     const int B = g.batch, d = g.d, V = g.vocab;
     PhaseTimer pt(c, 1);
-    if (c->fused && fused_rows_ok<WT>(B)) {
+    if (c->fused && fused_rows_ok<WT>(c, B)) {
         if (int rc = run_program<WT>(c, sample ? PROG_DRAFT_SAMPLE : PROG_DRAFT, K, B, 1)) return rc;
         pt.stop();
         return HIVIS_OK;
@@ -1324,7 +1345,7 @@ int do_verify(hivis_ctx* c) {
     int max_keys = 0;
     for (int b = 0; b < B; ++b) max_keys = std::max(max_keys, c->h_tlen[b]);
     hipLaunchKernelGGL(verify_tokens_kernel, dim3(1), dim3(64), 0, c->stream, (const int32_t*)c->text, c->text_stride, (const int*)c->dlen, (const int32_t*)c->drafts, g.k_max, K, c->row_tok, B);
-    if (c->fused && fused_rows_ok<WT>(M)) {
+    if (c->fused && fused_rows_ok<WT>(c, M)) {
         if (int rc = run_program<WT>(c, PROG_VERIFY, K, B, K + 1)) return rc;
         pt.stop();
         return HIVIS_OK;
@@ -1354,7 +1375,7 @@ int do_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool sample) {
                            (const int*)c->dlen, c->tlen, c->nacc, c->out_tok, c->next_tok);
     // roll-forward: K+1 rows per sequence [g_i ; Embed(token after row i)] + rho_0 through the drafter at positions
     // dlen..dlen+K; rows beyond n_b are computed but become dead (the drafter length advances by n_b+1 only).
-    if (c->fused && fused_rows_ok<WT>(M)) {
+    if (c->fused && fused_rows_ok<WT>(c, M)) {
         if (int rc = run_program<WT>(c, PROG_ROLL, K, B, K + 1)) return rc;
     } else {
         for (int b = 0; b < B; ++b)
@@ -1417,6 +1438,7 @@ int tree_setup(hivis_ctx* c) {
     if ((rc = dev_alloc(c, &c->tH, (size_t)(R + 1) * d))) return rc;
     if ((rc = dev_alloc(c, &c->tlogits, (size_t)(R + 1) * V))) return rc;
     if ((rc = dev_alloc(c, &c->tcat, (size_t)TREE_MAX_TOPK * 2 * d))) return rc;
+    if ((rc = dev_alloc(c, &c->ttok_rows, TREE_MAX_TOPK))) return rc;
     if ((rc = dev_alloc(c, &c->troll, (size_t)(D + 1) * 2 * d))) return rc;
     c->tnseg = (V + TOPK_SEG - 1) / TOPK_SEG;
     if ((rc = dev_alloc(c, &c->tcand_v, (size_t)TREE_MAX_TOPK * c->tnseg * TREE_MAX_TOPK))) return rc;
@@ -1444,6 +1466,59 @@ int tree_setup(hivis_ctx* c) {
     return HIVIS_OK;
 }
 
+PassParams tree_pass(const hivis_ctx* c, int m) {
+    const hivis_config& g = c->cfg;
+    PassParams pp{};
+    pp.M = m; pp.nseq = 1; pp.m = m; pp.d = g.d; pp.Hq = g.n_q_heads; pp.Hkv = g.n_kv_heads; pp.hd = g.head_dim; pp.F = g.ffn; pp.V = g.vocab;
+    pp.eps = g.rms_eps; pp.theta = g.rope_theta; pp.inv_temp = c->inv_temp; pp.bar = c->bar; pp.bad = c->bad; pp.spin_limit = 1u << 22;
+    return pp;
+}
+
+// m <= 16 rows of a draft tree (or of its re-feed) through the fusion FC + rho_idx and the drafter's layer as a phase list, one launch per
+// phase: inputs cat [m][2d] = hidden row | embedding and the rows' tokens (tok); layer output to out [m][d]; lm_out (optional): its
+// logits.  The list's buffers are one pool per row count, kept: the passes of a call follow each other on the stream.
+template <typename WT>
+int tree_rows_program(hivis_ctx* c, int m, const float* cat, const int32_t* tok, int rho_idx, int offset, TreeRows tr, float* out, float* lm_out) {
+    const hivis_config& g = c->cfg;
+    const int d = g.d, V = g.vocab;
+    auto build = [&](Pool& pool, std::vector<Phase>& P) {
+        float* u = pool.take((size_t)m * d);
+        Phase fu{}; fu.type = PH_GEMM; fu.pro = PRO_PLAIN; fu.epi = FEPI_ADDVEC; fu.K = 2 * d; fu.N = d; fu.W = c->fuse_w; fu.A = cat; fu.lda = 2 * d;
+        fu.Y = u; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = rho_idx;
+        if (c->emb_w2) { fu.add_rows = c->emb_w2; fu.K = d; fu.W = c->fuse_w1; fu.tok = tok; fu.tok_sseq = 0; fu.tok_srow = 1; }      // embedding half from the table
+        P.push_back(fu);
+        const size_t l0 = P.size();
+        int ld = d;
+        layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, offset, 1, m, out, d, &ld, false, c->attn_elect);
+        for (size_t i = l0; i < P.size(); ++i) { P[i].pos_delta = tr.pos_delta; P[i].att.tmask = tr.mask; }
+        float* pm = pool.take((size_t)m * c->fused_grid); int* pi = (int*)pool.take((size_t)m * c->fused_grid);
+        if (lm_out) {
+            Phase lm{}; lm.type = PH_GEMM; lm.pro = PRO_PLAIN; lm.epi = FEPI_LOGITS; lm.K = d; lm.N = V; lm.W = c->lm_head; lm.A = out; lm.lda = d;
+            lm.Y = lm_out; lm.ldy = V; lm.pm = pm; lm.pi = pi;
+            P.push_back(lm);
+        }
+    };
+    float*& base = c->tree_pool[m];
+    if (!base) {
+        std::vector<Phase> sizes;
+        Pool count;
+        build(count, sizes);
+        if (int rc = dev_alloc(c, &base, count.used)) return rc;
+        HIP_TRY(c, hipMemset(base, 0, count.used * sizeof(float)));            // (the arrival counters start at zero)
+    }
+    std::vector<Phase> P;
+    Pool pool; pool.base = base;
+    build(pool, P);
+    const PassParams pp = tree_pass(c, m);
+    if constexpr (std::is_same<WT, bf16_t>::value) {
+        if (m > WTraits<WT>::ROWS || tr.pos_delta) return launch_phases<bf16w_t>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
+    }
+    return launch_phases<WT>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
+}
+// the phase attention of fp32 models takes no ancestor mask: those keep the stand-alone kernels
+template <typename WT>
+bool tree_program_ok(const hivis_ctx* c, int m) { return sizeof(WT) == 2 && c->fused && !c->persistent && m <= WTraits<bf16w_t>::ROWS; }
+
 // Pool of k + (depth-1) k^2 nodes, level by level; then the N best-scored candidates and their verify rows.
 template <typename WT>
 int do_tree_draft(hivis_ctx* c, int k, int depth, int N) {
@@ -1466,11 +1541,15 @@ int do_tree_draft(hivis_ctx* c, int k, int depth, int N) {
         const int n_prev = (j - 1) * k, row0 = 1 + n_prev;
         const int32_t* E = t.expand + n_prev;
         hipLaunchKernelGGL(tree_expand_kernel, dim3(1), dim3(256), 0, c->stream, lo, n, k, n_prev, j, t);
-        hipLaunchKernelGGL((tree_cat_kernel<WT>), dim3(k), dim3(256), 0, c->stream, E, t, (const float*)c->tH, (const WT*)c->embed, c->tcat, d);
+        hipLaunchKernelGGL((tree_cat_kernel<WT>), dim3(k), dim3(256), 0, c->stream, E, t, (const float*)c->tH, (const WT*)c->embed, c->tcat, c->ttok_rows, d);
         TreeRows tr; tr.pos_delta = t.dpos + n_prev; tr.mask = t.dmask + n_prev;
-        if (int rc = drafter_forward<WT>(c, c->tcat, 0, 1, k, std::min(j, g.n_resid - 1), n_prev, c->h_dlen[0] + n_prev + k,
-                                         c->tH + (size_t)row0 * d, d, tr)) return rc;
-        if (int rc = gemm<WT>(c, c->tH + (size_t)row0 * d, d, k, d, c->lm_head, V, c->tlogits + (size_t)row0 * V, V, EPI_STORE)) return rc;
+        float* hid = c->tH + (size_t)row0 * d; float* lg = c->tlogits + (size_t)row0 * V;
+        if (tree_program_ok<WT>(c, k)) {
+            if (int rc = tree_rows_program<WT>(c, k, c->tcat, c->ttok_rows, std::min(j, g.n_resid - 1), n_prev, tr, hid, lg)) return rc;
+        } else {
+            if (int rc = drafter_forward<WT>(c, c->tcat, 0, 1, k, std::min(j, g.n_resid - 1), n_prev, c->h_dlen[0] + n_prev + k, hid, d, tr)) return rc;
+            if (int rc = gemm<WT>(c, hid, d, k, d, c->lm_head, V, lg, V, EPI_STORE)) return rc;
+        }
         const int first = lo + n;
         hipLaunchKernelGGL(tree_topk_part_kernel, dim3(k, nseg), dim3(TOPK_NT), 0, c->stream, (const float*)(c->tlogits + (size_t)row0 * V), V, k, c->tcand_v, c->tcand_i, c->tseg);
         hipLaunchKernelGGL(tree_children_kernel, dim3(k), dim3(CHILD_NT), child_lds, c->stream, (const float*)c->tcand_v, (const int32_t*)c->tcand_i, (const float*)c->tseg, nseg, k, first,
@@ -1519,7 +1598,8 @@ int do_tree_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool samp
     // drafter: every tree row is dropped (its length never advanced); depth+1 rows rebuilt from the true features
     hipLaunchKernelGGL((tree_roll_cat_kernel<WT>), dim3(depth + 1), dim3(256), 0, c->stream, (const float*)c->catT, 2 * d, (const int32_t*)t.path,
                        (const int32_t*)t.next_tok, (const WT*)c->embed, c->troll, d);
-    if (int rc = drafter_forward<WT>(c, c->troll, 0, 1, depth + 1, 0, 0, c->h_dlen[0] + depth + 1, c->dout, d)) return rc;
+    if (tree_program_ok<WT>(c, depth + 1)) { if (int rc = tree_rows_program<WT>(c, depth + 1, c->troll, t.next_tok, 0, 0, TreeRows(), c->dout, nullptr)) return rc; }
+    else if (int rc = drafter_forward<WT>(c, c->troll, 0, 1, depth + 1, 0, 0, c->h_dlen[0] + depth + 1, c->dout, d)) return rc;
     hipLaunchKernelGGL(tree_finish_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)c->dout, (const int32_t*)t.result, c->catD, c->dlen, c->tlen, d);
     HIP_TRY(c, hipGetLastError());
     pt.stop();

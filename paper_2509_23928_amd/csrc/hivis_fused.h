@@ -58,6 +58,7 @@ struct Phase {
     int ncand;
     void* kc; void* vc; int maxL;          // QKV epilogue / ATTN: cache of this layer
     const int* base; int offset;           // row positions: base[seq] + offset + i
+    const int* pos_delta;                  // QKV, optional (rows of a draft tree, one sequence): rotary position base[0] + pos_delta[row]; the cache slot stays
     const int32_t* ids; int id_sseq, id_srow;      // PREP: token of row (seq, i) = ids[seq*id_sseq + i*id_srow] (ids may be null: no gather)
     int32_t* tok_out; int o_sseq, o_srow;          // ARGMAX: destination of the greedy token of row (seq, i)
     AttnShape att; int att_items;                  // ATTN / ATTN_MERGE
@@ -116,13 +117,17 @@ template <typename WT> struct FusedCfg;
 constexpr int FUSED_NW = 8, FUSED_NT = FUSED_NW * 64;
 template <> struct FusedCfg<bf16_t> { static constexpr int KBW = 8, G = 8, NW = FUSED_NW; };
 template <> struct FusedCfg<float> { static constexpr int KBW = 8, G = 4, NW = FUSED_NW; };
-constexpr int FUSED_U = 8;
-constexpr int FUSED_QM = 8;       // activation rows staged per lane per pass (bf16: rows q; fp32: rows 2 q + lane / 32)
+// 9..16 rows: half the K blocks per unit, so that twice the rows' staging registers and twice the fragments still fit
+template <> struct FusedCfg<bf16w_t> { static constexpr int KBW = 4, G = 8, NW = FUSED_NW; };
+constexpr int FUSED_QM = 8;       // activation rows staged per lane per pass (bf16: rows q; fp32 and bf16w: rows 2 q + lane / 32)
+// fragment blocks of one K block in the LDS chunk: 16 operand rows (bf16w: high and low blocks)
+template <typename WT> constexpr int FUSED_CHUNK = 4 * 16;
+template <> constexpr int FUSED_CHUNK<bf16w_t> = 4 * 32;
 
 // LDS of a GEMM phase (floats): cross-wave reduction [NW][TILE] | reduced tiles [TILE] | ssq partials [NW][16]
 // | inv_rms [16] | A chunk of one K pass in MFMA fragment order [NW*KBW blocks][4][RU] x 16 bytes
-__host__ __device__ constexpr size_t fused_gemm_lds_floats(int NW, int G, int RPL, int KBW) {
-    return (size_t)NW * G * 64 * RPL + (size_t)G * 64 * RPL + (size_t)NW * 16 + 16 + (size_t)NW * KBW * 4 * 16 * 4;
+__host__ __device__ constexpr size_t fused_gemm_lds_floats(int NW, int G, int RPL, int KBW, int chunk) {
+    return (size_t)NW * G * 64 * RPL + (size_t)G * 64 * RPL + (size_t)NW * 16 + 16 + (size_t)NW * KBW * chunk * 4;
 }
 
 // Four consecutive RMSNorm gains as loaded (raw bits of the weight type); converted to float where they are used
@@ -134,6 +139,7 @@ template <> struct Gain4<bf16_t> {
         return __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
     }
 };
+template <> struct Gain4<bf16w_t> : Gain4<bf16_t> {};
 template <> struct Gain4<float> {
     typedef float4 type;
     static __device__ __forceinline__ float get(const float4& g, int e) { return e == 0 ? g.x : e == 1 ? g.y : e == 2 ? g.z : g.w; }
@@ -144,6 +150,7 @@ __device__ __forceinline__ float4 load4_f32(const bf16_t* p) {
     const uint2 u = *reinterpret_cast<const uint2*>(p);
     return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
 }
+__device__ __forceinline__ float4 load4_f32(const bf16w_t* p) { return load4_f32(reinterpret_cast<const bf16_t*>(p)); }
 __device__ __forceinline__ float4 load4_f32(const float* p) { return *reinterpret_cast<const float4*>(p); }
 
 // K blocks of pass p that wavefront `wave` owns.  A full pass gives every wavefront KBW consecutive blocks; a ragged
@@ -160,11 +167,12 @@ template <int NW, int KBW> __device__ __forceinline__ int unit_nkb(int kblks, in
 }
 
 // Loads of one unit: the wavefront's K blocks [kb0, kb0+nkb) of tile `tile`.
-__device__ __forceinline__ void issue_unit(uint4 (&wb)[FUSED_U], const uint4* __restrict__ W, int kblks, int tile, int kb0,
+template <int U>
+__device__ __forceinline__ void issue_unit(uint4 (&wb)[U], const uint4* __restrict__ W, int kblks, int tile, int kb0,
                                            int nkb, int lane) {
     const uint4* p = W + ((size_t)tile * kblks + kb0) * 64 + lane;
 #pragma unroll
-    for (int j = 0; j < FUSED_U; ++j)
+    for (int j = 0; j < U; ++j)
         if (j < nkb) wb[j] = p[(size_t)j * 64]; else wb[j] = make_uint4(0, 0, 0, 0);
 }
 
@@ -190,9 +198,28 @@ __device__ __forceinline__ void stage_store(float, uint4* chunk, int RU, int row
     const int kb = kl >> 4, g = (kl & 15) >> 2;
     chunk[(kb * 4 + g) * RU + row] = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
 }
-__device__ __forceinline__ void frag_from(bf16x8_t& f, const uint4& u) { f = __builtin_bit_cast(bf16x8_t, u); }
-__device__ __forceinline__ void frag_from(float4& f, const uint4& u) {
-    f = make_float4(__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w));
+__device__ __forceinline__ void stage_store(bf16w_t, uint4* chunk, int RU, int row, int kl, const float (&x)[4]) {
+    const int kb = kl >> 5, g = (kl & 31) >> 3, e0 = kl & 7;
+    const int slot = (kb * 4 + g) * 2 * RU + row;
+    uint32_t h01, l01, h23, l23;
+    f32_to_bf16x2_hilo(x[0], x[1], h01, l01);
+    f32_to_bf16x2_hilo(x[2], x[3], h23, l23);
+    *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(chunk + slot) + e0) = make_uint2(h01, h23);
+    *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(chunk + slot + RU) + e0) = make_uint2(l01, l23);
+}
+// fragment of K block j (lane group g, operand row i) from the chunk; zero where the wavefront has no such block
+__device__ __forceinline__ void frag_load(bf16x8_t& f, const uint4* chunk, int j, int g, int RU, int i, bool on) {
+    const uint4 u = chunk[(j * 4 + g) * RU + i];
+    f = __builtin_bit_cast(bf16x8_t, on ? u : make_uint4(0, 0, 0, 0));
+}
+__device__ __forceinline__ void frag_load(HiLoFrag& f, const uint4* chunk, int j, int g, int RU, int i, bool on) {
+    const uint4 h = chunk[(j * 4 + g) * 2 * RU + i], l = chunk[(j * 4 + g) * 2 * RU + RU + i];
+    f.hi = __builtin_bit_cast(bf16x8_t, on ? h : make_uint4(0, 0, 0, 0));
+    f.lo = __builtin_bit_cast(bf16x8_t, on ? l : make_uint4(0, 0, 0, 0));
+}
+__device__ __forceinline__ void frag_load(float4& f, const uint4* chunk, int j, int g, int RU, int i, bool on) {
+    const uint4 u = chunk[(j * 4 + g) * RU + i];
+    f = on ? make_float4(__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)) : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // Greedy tokens without a launch of their own: after a workgroup of the LM-head phase has stored its per-row
@@ -227,6 +254,12 @@ __device__ __forceinline__ void lm_head_elect(const Phase& ph, const PassParams&
     if (threadIdx.x == 0) st_wt(ph.cnt, 0);
 }
 
+// rotary position of a row relative to its sequence's cache length (bf16w: passes over the rows of a draft tree as well)
+template <typename WT> __device__ __forceinline__ int rope_offset(const Phase& ph, const PassParams& pp, int row) {
+    if constexpr (std::is_same<WT, bf16w_t>::value) { if (ph.pos_delta) return ph.pos_delta[row]; }
+    return ph.offset + row % pp.m;
+}
+
 // GEMM phase of the persistent kernel (rows <= one MFMA tile).  Work split as in gemm_skinny_kernel: the
 // workgroup owns a contiguous range of 16-column tiles and covers all of K; in K pass p wavefront w owns
 // blocks [(p*NW + w)*KBW, +KBW) of every tile.
@@ -239,8 +272,8 @@ __device__ __forceinline__ void lm_head_elect(const Phase& ph, const PassParams&
 //    a tile group, a pass or the phase: the last unit of a phase loads the first unit of the NEXT GEMM phase
 //    (`head`), so those loads are in flight while the workgroup waits at the grid barrier.
 template <typename WT, int EPI, bool SINGLE>
-__device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp, float* __restrict__ lds, uint4 (&head)[FUSED_U],
-                           bool& head_valid, uint4 (&wb1)[FUSED_U], bool& wb1_valid, int pidx) {
+__device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp, float* __restrict__ lds, uint4 (&head)[FusedCfg<WT>::KBW],
+                           bool& head_valid, uint4 (&wb1)[FusedCfg<WT>::KBW], bool& wb1_valid, int pidx) {
 #define HIVIS_MARK(k) if (pp.prof2 && blockIdx.x == 0 && threadIdx.x == 0) pp.prof2[pidx * 8 + (k)] = wall_clock64();
     typedef WTraits<WT> TR;
     typedef typename AFrag<WT>::type afrag_t;
@@ -251,8 +284,8 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     constexpr int G = (!SINGLE && (EPI < 0 || EPI == FEPI_LOGITS || EPI == FEPI_SILU)) ? FusedCfg<WT>::G : FusedCfg<WT>::G / 2;
     // rows staged per lane and pass; the table-add QKV variants serve draft steps of at most two / four sequences and stage
     // that many rows only (with eight, their second set of row registers spills)
-    constexpr int U = FUSED_U, QM = (EPI == FEPI_QKV_TAB) ? 2 : (EPI == FEPI_QKV_TAB4) ? 4 : FUSED_QM, NT = FUSED_NT;
-    static_assert(KBW == U && (G % 2) == 0, "one unit per tile slice; tiles are processed in pairs");
+    constexpr int U = KBW, QM = (EPI == FEPI_QKV_TAB) ? 2 : (EPI == FEPI_QKV_TAB4) ? 4 : FUSED_QM, NT = FUSED_NT;
+    static_assert((G % 2) == 0, "tiles are processed in pairs");
     constexpr int TILE = G * 64 * RPL;
     constexpr int SLOTS = TILE / NT;         // epilogue slots per thread (all of the same row and column-in-tile)
     static_assert(TILE % NT == 0, "whole epilogue slots per thread");
@@ -291,7 +324,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     // reads its fragments back; no workgroup barrier is involved, so the eight wavefronts stream independently until the
     // cross-wavefront reduction at the end (with workgroup-wide staging every pass waited twice for the slowest one).
     const int col4 = lane % SL4, row0 = lane / SL4;
-    uint4* slice = chunk + (size_t)wave * (KBW * 4 * 16);               // [KBW blocks][4][RU] x 16 bytes of this wavefront
+    uint4* slice = chunk + (size_t)wave * (KBW * FUSED_CHUNK<WT>);      // [KBW blocks][4][RU] x 16 bytes of this wavefront
     float ssq_acc[QM];
 #pragma unroll
     for (int q = 0; q < QM; ++q) ssq_acc[q] = 0.f;
@@ -386,8 +419,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                                     \
         const int i_ = min(lane & 15, RU - 1), g4_ = lane >> 4;                                                    \
         _Pragma("unroll") for (int j = 0; j < KBW; ++j) {                                                          \
-            const uint4 u_ = slice[(j * 4 + g4_) * RU + i_];                                                       \
-            frag_from(af[j], (j < nkb_) ? u_ : make_uint4(0, 0, 0, 0));                                            \
+            frag_load(af[j], slice, j, g4_, RU, i_, j < nkb_);                                                     \
         }                                                                                                          \
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                                     \
         __builtin_amdgcn_wave_barrier();                                                                           \
@@ -518,7 +550,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             else if (epi == FEPI_QKV) {
                 const int p2 = (col % pp.hd) >> 1;
                 const int seq_ = row / pp.m;
-                const int pos_ = min((ph.att.nbase > 0 ? ph.att.base_val[seq_] : ph.base[seq_]) + ph.offset + row % pp.m, ph.maxL - 1);
+                const int pos_ = min((ph.att.nbase > 0 ? ph.att.base_val[seq_] : ph.base[seq_]) + rope_offset<WT>(ph, pp, row), ph.maxL - 1);
                 const float2 cs_ = *reinterpret_cast<const float2*>(ph.rope + ((size_t)pos_ * (pp.hd / 2) + p2) * 2);
                 epi_a[sl] = cs_.x; epi_b[sl] = cs_.y;
             }
@@ -1399,8 +1431,8 @@ __device__ __forceinline__ void attn_wg_merge(const float* __restrict__ ws, cons
 
 // One phase, executed by the calling grid (every workgroup calls this with the same arguments).
 template <typename WT, int TYPE, int EPI, bool SINGLE>
-__device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp, float* __restrict__ lds, uint4 (&head)[FUSED_U],
-                                          bool& head_valid, uint4 (&wb1)[FUSED_U], bool& wb1_valid, int p) {
+__device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp, float* __restrict__ lds, uint4 (&head)[FusedCfg<WT>::KBW],
+                                          bool& head_valid, uint4 (&wb1)[FusedCfg<WT>::KBW], bool& wb1_valid, int p) {
     typedef typename KVType<WT>::type KT;
     const int type = (TYPE >= 0) ? TYPE : ph.type;
     switch (type) {
@@ -1497,7 +1529,7 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
 template <typename WT>
 __global__ __launch_bounds__(FUSED_NT) void fused_pass_kernel(PassParams pp) {
     extern __shared__ __align__(16) float lds[];
-    uint4 head[FUSED_U], wb1[FUSED_U];   // weight blocks prefetched for the next GEMM phase (in flight across barriers)
+    uint4 head[FusedCfg<WT>::KBW], wb1[FusedCfg<WT>::KBW];   // weight blocks prefetched for the next GEMM phase (in flight across barriers)
     bool head_valid = false, wb1_valid = false;
     for (int p = 0; p < pp.nphases; ++p) {
         const Phase& ph = pp.phases[p];
@@ -1530,7 +1562,7 @@ template <typename WT, int TYPE, int EPI, bool SINGLE>
 __global__ __launch_bounds__(FUSED_NT) void phase_kernel(Phase ph, PassParams pp) {
     extern __shared__ __align__(16) float lds[];
     kernarg_warm<sizeof(Phase) + sizeof(PassParams)>();
-    uint4 head[FUSED_U], wb1[FUSED_U];
+    uint4 head[FusedCfg<WT>::KBW], wb1[FusedCfg<WT>::KBW];
     bool head_valid = false, wb1_valid = false;
     if (pp.prof3 && threadIdx.x == 0) {
         pp.prof3[blockIdx.x * 4] = wall_clock64();

@@ -38,6 +38,10 @@ typedef _Float16 f16_t;                                   // IEEE half: KV-cache
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return bf16_to_f32(x); }
 __device__ __forceinline__ float to_f32(f16_t x) { return (float)x; }
+// bf16 storage in the phase kernels of passes of 9..16 rows: the high and the low parts of 16 rows are two MFMA operands
+// that add into the same accumulators (bf16_t: both parts of 8 rows are the 16 rows of one operand)
+struct bf16w_t { uint16_t bits; };
+__device__ __forceinline__ float to_f32(bf16w_t x) { return bf16_to_f32(x.bits); }
 __device__ __forceinline__ void from_f32(float& dst, float x) { dst = x; }
 __device__ __forceinline__ void from_f32(bf16_t& dst, float x) { dst = f32_to_bf16(x); }
 __device__ __forceinline__ void from_f32(f16_t& dst, float x) {   // round to nearest even, saturating
@@ -95,6 +99,7 @@ __device__ __forceinline__ void st_wt_kv_pair(_Float16* row, int HD, int c, floa
 // parity tolerance, with q and the probabilities rounded to half contributing as much again.
 template <typename WT> struct KVType;
 template <> struct KVType<bf16_t> { typedef f16_t type; };
+template <> struct KVType<bf16w_t> { typedef f16_t type; };
 template <> struct KVType<float> { typedef float type; };
 // elements of storage per cached value (row width = HD * KVW)
 template <typename KT> struct KVWidth { static constexpr int W = 1; };
@@ -152,6 +157,9 @@ template <> struct WTraits<bf16_t> {
     static constexpr int EPL = 8;      // elements per lane per block
     static constexpr int ROWS = 8;     // real activation rows per MFMA tile (hi/lo split)
     static constexpr int RPL = 2;      // real output rows per lane
+};
+template <> struct WTraits<bf16w_t> {
+    static constexpr int KB = 32, EPL = 8, ROWS = 16, RPL = 4;
 };
 template <> struct WTraits<float> {
     static constexpr int KB = 16;
@@ -224,6 +232,8 @@ __global__ void pack_weights_kernel(PackSrc src, int K, int N, uint4* __restrict
 template <typename WT> struct AFrag;
 template <> struct AFrag<bf16_t> { typedef bf16x8_t type; };
 template <> struct AFrag<float> { typedef float4 type; };
+struct HiLoFrag { bf16x8_t hi, lo; };
+template <> struct AFrag<bf16w_t> { typedef HiLoFrag type; };
 
 // A fragment of tile tt, block kb for this lane.  a_scale (optional, per k) multiplies the
 // activation before the hi/lo split (used to apply an RMSNorm gain on the fly).
@@ -301,6 +311,11 @@ __device__ __forceinline__ void mfma_block(f32x4_t& d, const float4& a, const ui
     d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, __uint_as_float(w.y), d, 0, 0, 0);
     d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(w.z), d, 0, 0, 0);
     d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(w.w), d, 0, 0, 0);
+}
+
+__device__ __forceinline__ void mfma_block(f32x4_t& d, const HiLoFrag& a, const uint4& w) {
+    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.hi, __builtin_bit_cast(bf16x8_t, w), d, 0, 0, 0);
+    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.lo, __builtin_bit_cast(bf16x8_t, w), d, 0, 0, 0);
 }
 
 // Epilogue modes of the skinny GEMM

@@ -157,11 +157,12 @@ __global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, 
     t.dpos[slot] = level - 1;
 }
 
-// Fusion input rows of one level: [hidden row the node was drawn from ; Embed(node token)].
+// Fusion input rows of one level: [hidden row the node was drawn from ; Embed(node token)], and the nodes' tokens.
 template <typename WT>
 __global__ void tree_cat_kernel(const int32_t* __restrict__ expand_row, TreeDev t, const float* __restrict__ H,
-                                const WT* __restrict__ table, float* __restrict__ cat, int d) {
+                                const WT* __restrict__ table, float* __restrict__ cat, int32_t* __restrict__ tok, int d) {
     const int r = blockIdx.x, node = expand_row[r];
+    if (threadIdx.x == 0) tok[r] = t.pool_tok[node];
     const float* h = H + (size_t)t.pool_hid[node] * d;
     const WT* e = table + (size_t)t.pool_tok[node] * d;
     float* o = cat + (size_t)r * 2 * d;
