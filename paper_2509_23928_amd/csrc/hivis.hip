@@ -83,6 +83,7 @@ struct hivis_ctx {
     int* rows_cnt = nullptr; int rows_cnt_n = 0;      // arrival counters of the key-split attention launched outside a phase program (zero between launches)
     float *logits_v = nullptr, *logits_d = nullptr, *logits_p = nullptr;
     int32_t *row_tok = nullptr, *drafts = nullptr, *ttok = nullptr, *nacc = nullptr, *out_tok = nullptr, *next_tok = nullptr;
+    float* am_v = nullptr; int* am_i = nullptr;      // greedy candidates per row and segment (launch_argmax)
     int32_t* h_result = nullptr;         // pinned host mirror of [nacc | out_tok | abort flag | bad-logits flag]
     int* bad = nullptr;                  // device flag: a greedy-token kernel met a row without a finite maximum (cleared by hivis_prefill)
     bool rng_seeded = false; unsigned long long rng_seed = 0, rng_calls = 0;   // device-side uniforms (hivis_rng_seed): Philox key and draw-call count
@@ -264,6 +265,13 @@ int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* 
                        int offset, int seq0, int nseq, int m, TreeRows tr, hivis::Parts* out_pending);
 
 // ---- launches --------------------------------------------------------------------------------
+// greedy token of each of `rows` rows of logits: row r's to out[(r / m) * sseq + r % m]
+void launch_argmax(hivis_ctx* c, const float* logits, int rows, int32_t* out, int m, int sseq) {
+    const int V = c->cfg.vocab, nseg = (V + ARGMAX_SEG - 1) / ARGMAX_SEG;
+    hipLaunchKernelGGL(argmax_part_kernel, dim3(rows, nseg), dim3(256), 0, c->stream, logits, V, c->am_v, c->am_i);
+    hipLaunchKernelGGL(argmax_final_kernel, dim3(rows), dim3(64), 0, c->stream, (const float*)c->am_v, (const int*)c->am_i, nseg, V, out, m, sseq, c->bad);
+}
+
 template <typename WT>
 int gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, int epi) {
     if (M < 1 || M > MAX_ROWS) return fail(c, HIVIS_EINVAL, "gemm rows %d out of range", M);
@@ -586,6 +594,9 @@ float* layer_phases(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const Layer
     return h2;
 }
 
+// greedy candidates per row of an LM-head phase: its workgroups (a single-launch program always runs the whole grid)
+int lm_candidates(const hivis_ctx* c, int N, bool persistent) { return persistent ? c->fused_grid : std::min(c->fused_grid, N / 16); }
+
 template <typename WT>
 void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>& P, bool persistent, bool elect) {
     const hivis_config& g = c->cfg;
@@ -611,7 +622,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
         if (lm_elect) lm.cnt = (int*)pool.take(1);         // zero from the pool's memset; the reducing workgroup re-zeroes it
         P.push_back(lm);
         if (!lm_elect) {
-            Phase am{}; am.type = PH_ARGMAX; am.tok_out = c->ttok; am.o_sseq = g.k_max + 1; am.o_srow = 1; am.pm = lm.pm; am.pi = lm.pi; am.N = G;
+            Phase am{}; am.type = PH_ARGMAX; am.tok_out = c->ttok; am.o_sseq = g.k_max + 1; am.o_srow = 1; am.pm = lm.pm; am.pi = lm.pi; am.N = lm_candidates(c, lm.N, persistent);
             P.push_back(am);
         }
     } else if (kind == PROG_DRAFT || kind == PROG_DRAFT_SAMPLE) {
@@ -633,7 +644,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
             if (in_lm) lm.cnt = (int*)pool.take(1);
             P.push_back(lm);
             if (!in_lm && !in_fc) {
-                Phase am{}; am.type = PH_ARGMAX; am.tok_out = c->drafts + (i - 1); am.o_sseq = g.k_max; am.o_srow = 0; am.pm = lm.pm; am.pi = lm.pi; am.N = G;
+                Phase am{}; am.type = PH_ARGMAX; am.tok_out = c->drafts + (i - 1); am.o_sseq = g.k_max; am.o_srow = 0; am.pm = lm.pm; am.pi = lm.pi; am.N = lm_candidates(c, lm.N, persistent);
                 if (kind == PROG_DRAFT_SAMPLE) {     // the token is drawn from softmax(logits / T) instead (uniforms [B][k_max], column i-1)
                     am.type = PH_SAMPLE; am.A = lm.Y; am.lda = V; am.u = c->u_draft; am.u_sseq = g.k_max; am.u_idx = i - 1;
                 }
@@ -647,7 +658,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
                 if (fold) {
                     fu.emb = c->embed; fu.tok = c->drafts + (i - 1); fu.tok_sseq = g.k_max; fu.tok_srow = 0;
                     if (c->emb_w2) { fu.emb = nullptr; fu.add_rows = c->emb_w2; fu.K = d; fu.W = c->fuse_w1; }     // embedding half from the table
-                    if (in_fc) { fu.tok = nullptr; fu.pm = lm.pm; fu.pi = lm.pi; fu.ncand = G; fu.tok_out = c->drafts + (i - 1); fu.o_sseq = g.k_max; fu.o_srow = 0; }
+                    if (in_fc) { fu.tok = nullptr; fu.pm = lm.pm; fu.pi = lm.pi; fu.ncand = lm_candidates(c, lm.N, persistent); fu.tok_out = c->drafts + (i - 1); fu.o_sseq = g.k_max; fu.o_srow = 0; }
                 }
                 else {
                     Phase pr{}; pr.type = PH_PREP; pr.ids = c->drafts + (i - 1); pr.id_sseq = g.k_max; pr.id_srow = 0; pr.gain = c->embed;
@@ -656,10 +667,11 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
                 }
                 if (!ext) P.push_back(fu);
                 const size_t qi = P.size();
+                const int ncand = lm_candidates(c, lm.N, persistent);
                 layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, i - 1, B, 1, cat_next, 2 * d, &ld, persistent, elect);
                 if (ext) {      // the layer's first phase (QKV): rows = u_part + table[token], tokens from this step's candidates, u written back
                     Phase& q = P[qi];
-                    q.A = u_part; q.lda = d; q.add_rows = c->emb_w2; q.wb = u; q.tok = nullptr; q.pm = lm.pm; q.pi = lm.pi; q.ncand = G;
+                    q.A = u_part; q.lda = d; q.add_rows = c->emb_w2; q.wb = u; q.tok = nullptr; q.pm = lm.pm; q.pi = lm.pi; q.ncand = ncand;
                     q.tok_out = c->drafts + (i - 1); q.o_sseq = g.k_max; q.o_srow = 0;
                 }
                 cat = cat_next;
@@ -744,7 +756,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         else if (ph.type == PH_NORM_ROWS) grid = std::min(grid, pp.M);
         else if (ph.type == PH_ARGMAX) grid = std::min(grid, (pp.M + FUSED_NW - 1) / FUSED_NW);
         else if (ph.type == PH_SAMPLE) grid = std::min(grid, pp.M);
-        else if (ph.type == PH_GEMM && ph.epi != FEPI_LOGITS) grid = std::min(grid, ph.N / 16);
+        else if (ph.type == PH_GEMM) grid = std::min(grid, ph.N / 16);      // (the LM head's number of greedy candidates per row: lm_candidates)
         PassParams ppl = pp;
         if (do_prof) { ppl.prof2 = pp.prof2 + (size_t)p * 8; if (p >= n / 2 && p < n / 2 + 8) ppl.prof3 = c->prof + 4096 * 11 + (size_t)(p - n / 2) * 4096; }
         // kev0/kev1 (null unless this launch is timed) are attached to the dispatch itself: they read the kernel's own
@@ -1278,7 +1290,7 @@ int do_prefill(hivis_ctx* c, const void* vis_embeds, int v, const int32_t* text_
     // first token x_{l+1}: LM head on the last text row of every sequence
     if (int rc = gemm<WT>(c, c->feat + (size_t)(l - 1) * d, g.max_text * d, B, d, c->lm_head, g.vocab, c->logits_p, g.vocab, EPI_STORE)) return rc;
     if (sample) hipLaunchKernelGGL(sample_rows_kernel, dim3(B), dim3(SAMPLE_NT), 0, c->stream, (const float*)c->logits_p, g.vocab, c->inv_temp, (const float*)c->u_res, 1, c->text + l, c->text_stride);
-    else hipLaunchKernelGGL(argmax_kernel, dim3(B), dim3(256), 0, c->stream, (const float*)c->logits_p, g.vocab, c->text + l, c->text_stride, c->bad);
+    else launch_argmax(c, c->logits_p, B, c->text + l, 1, c->text_stride);
     // drafter prefill over the l text positions: rows [f^j ; Embed(x_{j+1})] + rho_0
     if constexpr (sizeof(WT) == 2)
         for (int b = 0; b < B; b += per)
@@ -1326,9 +1338,9 @@ int do_draft(hivis_ctx* c, int K, bool sample) {
         float* lg = c->logits_d + (size_t)(i - 1) * B * V;
         if (int rc = gemm<WT>(c, c->catD, 2 * d, B, d, c->lm_head, V, lg, V, EPI_STORE)) return rc;
         if (sample) hipLaunchKernelGGL(sample_rows_kernel, dim3(B), dim3(SAMPLE_NT), 0, c->stream, (const float*)lg, V, c->inv_temp, (const float*)(c->u_draft + (i - 1)), g.k_max, c->drafts + (i - 1), g.k_max);
-        else hipLaunchKernelGGL(argmax_kernel, dim3(B), dim3(256), 0, c->stream, (const float*)lg, V, c->drafts + (i - 1), g.k_max, c->bad);
+        else launch_argmax(c, lg, B, c->drafts + (i - 1), 1, g.k_max);
         if (i < K) {
-            hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(B), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)(c->drafts + (i - 1)), g.k_max, c->catD + d, 2 * d, d);
+            hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(B), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)(c->drafts + (i - 1)), 1, g.k_max, c->catD + d, 2 * d, d);
             if (int rc = drafter_forward<WT>(c, c->catD, 0, B, 1, std::min(i, g.n_resid - 1), i - 1, max_keys + i, c->catD, 2 * d)) return rc;
         }
     }
@@ -1350,12 +1362,11 @@ int do_verify(hivis_ctx* c) {
         pt.stop();
         return HIVIS_OK;
     }
-    hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(M), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)c->row_tok, 1, c->x, d, d);
+    hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(M), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)c->row_tok, M, 0, c->x, d, d);
     if (int rc = target_forward<WT>(c, 0, B, K + 1, c->tlen, 0, max_keys + K + 1, c->catT, 2 * d, 0)) return rc;
     if (int rc = gemm<WT>(c, c->catT, 2 * d, M, d, c->lm_head, V, c->logits_v, V, EPI_STORE)) return rc;
     // target's greedy token after each row: ttok[b][i], row stride k_max+1
-    for (int b = 0; b < B; ++b)
-        hipLaunchKernelGGL(argmax_kernel, dim3(K + 1), dim3(256), 0, c->stream, (const float*)(c->logits_v + (size_t)b * (K + 1) * V), V, c->ttok + (size_t)b * (g.k_max + 1), 1, c->bad);
+    launch_argmax(c, c->logits_v, M, c->ttok, K + 1, g.k_max + 1);
     HIP_TRY(c, hipGetLastError());
     pt.stop();
     return HIVIS_OK;
@@ -1378,9 +1389,7 @@ int do_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool sample) {
     if (c->fused && fused_rows_ok<WT>(c, M)) {
         if (int rc = run_program<WT>(c, PROG_ROLL, K, B, K + 1)) return rc;
     } else {
-        for (int b = 0; b < B; ++b)
-            hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(K + 1), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)(c->next_tok + (size_t)b * (g.k_max + 1)), 1,
-                               c->catT + (size_t)b * (K + 1) * 2 * d + d, 2 * d, d);
+        hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(M), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)c->next_tok, K + 1, g.k_max + 1, c->catT + d, 2 * d, d);
         int max_keys = 0;
         for (int b = 0; b < B; ++b) max_keys = std::max(max_keys, c->h_dlen[b]);
         if (int rc = drafter_forward<WT>(c, c->catT, 0, B, K + 1, 0, 0, max_keys + K + 1, c->dout, d)) return rc;
@@ -1540,11 +1549,12 @@ int do_tree_draft(hivis_ctx* c, int k, int depth, int N) {
     for (int j = 1; j < depth; ++j) {
         const int n_prev = (j - 1) * k, row0 = 1 + n_prev;
         const int32_t* E = t.expand + n_prev;
-        hipLaunchKernelGGL(tree_expand_kernel, dim3(1), dim3(256), 0, c->stream, lo, n, k, n_prev, j, t);
-        hipLaunchKernelGGL((tree_cat_kernel<WT>), dim3(k), dim3(256), 0, c->stream, E, t, (const float*)c->tH, (const WT*)c->embed, c->tcat, c->ttok_rows, d);
+        const bool program = tree_program_ok<WT>(c, k);
+        hipLaunchKernelGGL((tree_expand_kernel<WT>), dim3(k), dim3(256), 0, c->stream, lo, n, k, n_prev, j, t, (const float*)c->tH,
+                           program && c->emb_w2 ? (const WT*)nullptr : (const WT*)c->embed, c->tcat, c->ttok_rows, d);
         TreeRows tr; tr.pos_delta = t.dpos + n_prev; tr.mask = t.dmask + n_prev;
         float* hid = c->tH + (size_t)row0 * d; float* lg = c->tlogits + (size_t)row0 * V;
-        if (tree_program_ok<WT>(c, k)) {
+        if (program) {
             if (int rc = tree_rows_program<WT>(c, k, c->tcat, c->ttok_rows, std::min(j, g.n_resid - 1), n_prev, tr, hid, lg)) return rc;
         } else {
             if (int rc = drafter_forward<WT>(c, c->tcat, 0, 1, k, std::min(j, g.n_resid - 1), n_prev, c->h_dlen[0] + n_prev + k, hid, d, tr)) return rc;
@@ -1568,11 +1578,11 @@ int do_tree_verify(hivis_ctx* c) {
     const int d = g.d, V = g.vocab, M = c->tn + 1;
     PhaseTimer pt(c, 2);
     const TreeDev& t = c->tree;
-    hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(M), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)t.row_tok, 1, c->x, d, d);
+    hipLaunchKernelGGL((gather_rows_kernel<WT>), dim3(M), dim3(256), 0, c->stream, (const WT*)c->embed, (const int32_t*)t.row_tok, M, 0, c->x, d, d);
     TreeRows tr; tr.pos_delta = t.row_depth; tr.mask = t.vmask;
     if (int rc = target_forward<WT>(c, 0, 1, M, c->tlen, 0, c->h_tlen[0] + M, c->catT, 2 * d, 0, tr)) return rc;
     if (int rc = gemm<WT>(c, c->catT, 2 * d, M, d, c->lm_head, V, c->logits_v, V, EPI_STORE)) return rc;
-    hipLaunchKernelGGL(argmax_kernel, dim3(M), dim3(256), 0, c->stream, (const float*)c->logits_v, V, t.ttok, 1, c->bad);
+    launch_argmax(c, c->logits_v, M, t.ttok, M, 0);
     HIP_TRY(c, hipGetLastError());
     pt.stop();
     c->vrows = M;
@@ -1596,9 +1606,10 @@ int do_tree_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool samp
         hipLaunchKernelGGL((tree_kv_gather_kernel<KT>), dim3(depth, 2 * g.n_layers), dim3(256), 0, c->stream, (KT* const*)c->kv_ptrs, c->tkv[0].maxL,
                            g.n_kv_heads, g.head_dim * KVWidth<KT>::W, (const int*)c->tlen, (const int32_t*)t.result, (const int32_t*)t.path, depth, (KT*)c->kv_staging, scatter);
     // drafter: every tree row is dropped (its length never advanced); depth+1 rows rebuilt from the true features
+    const bool program = tree_program_ok<WT>(c, depth + 1);
     hipLaunchKernelGGL((tree_roll_cat_kernel<WT>), dim3(depth + 1), dim3(256), 0, c->stream, (const float*)c->catT, 2 * d, (const int32_t*)t.path,
-                       (const int32_t*)t.next_tok, (const WT*)c->embed, c->troll, d);
-    if (tree_program_ok<WT>(c, depth + 1)) { if (int rc = tree_rows_program<WT>(c, depth + 1, c->troll, t.next_tok, 0, 0, TreeRows(), c->dout, nullptr)) return rc; }
+                       (const int32_t*)t.next_tok, program && c->emb_w2 ? (const WT*)nullptr : (const WT*)c->embed, c->troll, d);
+    if (program) { if (int rc = tree_rows_program<WT>(c, depth + 1, c->troll, t.next_tok, 0, 0, TreeRows(), c->dout, nullptr)) return rc; }
     else if (int rc = drafter_forward<WT>(c, c->troll, 0, 1, depth + 1, 0, 0, c->h_dlen[0] + depth + 1, c->dout, d)) return rc;
     hipLaunchKernelGGL(tree_finish_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)c->dout, (const int32_t*)t.result, c->catD, c->dlen, c->tlen, d);
     HIP_TRY(c, hipGetLastError());
@@ -1756,6 +1767,7 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     if ((rc = dev_alloc(c, &c->logits_v, (size_t)R * V))) return rc;
     if ((rc = dev_alloc(c, &c->logits_d, (size_t)g.k_max * B * V))) return rc;
     if ((rc = dev_alloc(c, &c->logits_p, (size_t)B * V))) return rc;
+    { const size_t n = (size_t)std::max(R, B) * ((V + ARGMAX_SEG - 1) / ARGMAX_SEG); if ((rc = dev_alloc(c, &c->am_v, n)) || (rc = dev_alloc(c, &c->am_i, n))) return rc; }
     if ((rc = dev_alloc(c, &c->row_tok, R))) return rc;
     if ((rc = dev_alloc(c, &c->drafts, (size_t)B * g.k_max))) return rc;
     if ((rc = dev_alloc(c, &c->ttok, (size_t)B * (g.k_max + 1)))) return rc;

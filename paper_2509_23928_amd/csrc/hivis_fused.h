@@ -145,14 +145,6 @@ template <> struct Gain4<float> {
     static __device__ __forceinline__ float get(const float4& g, int e) { return e == 0 ? g.x : e == 1 ? g.y : e == 2 ? g.z : g.w; }
 };
 
-// four consecutive values of the weight dtype as floats
-__device__ __forceinline__ float4 load4_f32(const bf16_t* p) {
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
-    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
-}
-__device__ __forceinline__ float4 load4_f32(const bf16w_t* p) { return load4_f32(reinterpret_cast<const bf16_t*>(p)); }
-__device__ __forceinline__ float4 load4_f32(const float* p) { return *reinterpret_cast<const float4*>(p); }
-
 // K blocks of pass p that wavefront `wave` owns.  A full pass gives every wavefront KBW consecutive blocks; a ragged
 // last pass is dealt out evenly (ceil(rest / NW) blocks each), so that no wavefront streams a whole unit more than the
 // others (with K = 11008 the last pass has 24 blocks: 3 per wavefront instead of 8 for three of them).
@@ -572,6 +564,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             for (int q = 0; q < QM; ++q) {
 #pragma unroll
                 for (int h = 0; h < RS; ++h) {
+                    if (q * RS + h >= M) continue;           // (uniform: a draft step of one row reduces one row's sum)
                     const float s = wave_sum(row0 == h ? ssq_acc[q] : 0.f);
                     if (lane == 0) ssq_w[wave * 16 + q * RS + h] = s;
                 }
@@ -1251,7 +1244,9 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_shared_kernel(const float*
     }
 }
 
-template <typename KT, int HD, int RM>
+// RC: rows an item holds at most.  With one (a draft step) nothing tests r < R, and no wait sits behind every LDS read and
+// cross-lane step of an unrolled row (8.4 -> 6.7 us; always working on 8 rows instead of testing: 10.9 us for 5).
+template <typename KT, int HD, int RM, int RC>
 __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, const KT* __restrict__ kc, const KT* __restrict__ vc,
                                                 const int* __restrict__ base, const AttnShape& sh, int item_id, int split,
                                                 float* __restrict__ lds, float* __restrict__ ws, int* __restrict__ cnt,
@@ -1317,9 +1312,9 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
     lds_barrier();
     HIVIS_AMARK(2)
 
-    float mrun[RM], lrun[RM], acc[RM][CH];
+    float mrun[RC], lrun[RC], acc[RC][CH];
 #pragma unroll
-    for (int r = 0; r < RM; ++r) {
+    for (int r = 0; r < RC; ++r) {
         mrun[r] = -INFINITY; lrun[r] = 0.f;
 #pragma unroll
         for (int e = 0; e < CH; ++e) acc[r][e] = 0.f;
@@ -1333,16 +1328,16 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
         for (int t = 0; t < VT; ++t) vraw[t] = vnext[t];
         if (kb + 16 * NW < k1) HIVIS_ATTN_LOADS(kb + 16 * NW)
         // ---- scores of (key kk, all rows): this lane's quarter, then summed over the 4 quarter lanes
-        float s[RM];
+        float s[RC];
 #pragma unroll
-        for (int r = 0; r < RM; ++r) s[r] = 0.f;
+        for (int r = 0; r < RC; ++r) s[r] = 0.f;
 #pragma unroll
         for (int j = 0; j < KL; ++j) {
             float kf[CH];
             decode_chunk(kraw[j], kf, KT());
 #pragma unroll
-            for (int r = 0; r < RM; ++r) {
-                if (r < R) {
+            for (int r = 0; r < RC; ++r) {
+                if (RC == 1 || r < R) {
                     const float* qr = qs + r * HD + quarter * QD + j * CH;
 #pragma unroll
                     for (int e = 0; e < CH; ++e) s[r] += qr[e] * kf[e];
@@ -1351,8 +1346,8 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
         }
         const int key = kb + kk;
 #pragma unroll
-        for (int r = 0; r < RM; ++r) {
-            if (r < R) {
+        for (int r = 0; r < RC; ++r) {
+            if (RC == 1 || r < R) {
                 float sv = quad_sum(s[r]);                // the 4 lanes of a key hold its 4 quarter dot products
                 const int qpos = pos0 + i0 + r % ni;
                 if (key >= k1 || key > qpos) sv = -INFINITY;
@@ -1380,8 +1375,8 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
             decode_chunk(vraw[t], vf, KT());
             const int kl = t * KPI + vks;                // key within the 16 (its p is 0 if masked)
 #pragma unroll
-            for (int r = 0; r < RM; ++r) {
-                if (r < R) {
+            for (int r = 0; r < RC; ++r) {
+                if (RC == 1 || r < R) {
                     const float p = pw[r * 16 + kl];
 #pragma unroll
                     for (int e = 0; e < CH; ++e) acc[r][e] += p * vf[e];
@@ -1395,8 +1390,8 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
     HIVIS_AMARK(3)
     // ---- per-wavefront partial -> LDS (sum over the lanes that share a chunk / over all lanes for l)
 #pragma unroll
-    for (int r = 0; r < RM; ++r) {
-        if (r < R) {
+    for (int r = 0; r < RC; ++r) {
+        if (RC == 1 || r < R) {
             const float lsum = wave_sum(lrun[r]);
 #pragma unroll
             for (int e = 0; e < CH; ++e) {
@@ -1451,8 +1446,13 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
                 if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2, ph.frag);
                 else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2, ph.frag);
             } else {
-                if (pp.hd == 128) attn_wg_partial<KT, 128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2);
-                else attn_wg_partial<KT, 64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2);
+                // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
+                const bool one = ph.att.gh * ph.att.mi == 1;
+#define HIVIS_ATTN_F32(HD_, RC_) attn_wg_partial<KT, HD_, FUSED_RMAX, RC_>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2)
+                if (pp.hd == 128) { if (one) HIVIS_ATTN_F32(128, 1); else HIVIS_ATTN_F32(128, FUSED_RMAX); }
+                else if (one) HIVIS_ATTN_F32(64, 1);
+                else HIVIS_ATTN_F32(64, FUSED_RMAX);
+#undef HIVIS_ATTN_F32
             }
         }
     } break;

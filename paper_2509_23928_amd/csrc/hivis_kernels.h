@@ -48,6 +48,14 @@ __device__ __forceinline__ void from_f32(f16_t& dst, float x) {   // round to ne
     dst = (f16_t)fminf(fmaxf(x, -65504.f), 65504.f);
 }
 
+// four consecutive values of the weight dtype as floats
+__device__ __forceinline__ float4 load4_f32(const bf16_t* p) {
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
+}
+__device__ __forceinline__ float4 load4_f32(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 load4_f32(const bf16w_t* p) { return load4_f32(reinterpret_cast<const bf16_t*>(p)); }
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding global
 // load of the wavefront, which would drain the weight prefetch pipeline at each use.
 __device__ __forceinline__ void lds_barrier() {
@@ -720,10 +728,12 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
     const float scale = rsqrtf((float)HD);
     float* pw = pw_all + (size_t)wave * RM * 64;
 
-    for (int idx = threadIdx.x; idx < R * HD; idx += nthreads) {
-        const int r = idx / HD, c = idx % HD;
+    // All RM rows take part in everything below (the ones past R as zeros, never stored): a test of r < R at each of the
+    // unrolled rows put a wait behind every LDS read (a 32-row chunk of the 256-wide model: 55 us, now 20).
+    for (int idx = threadIdx.x; idx < RM * HD; idx += nthreads) {
+        const int r = min(idx / HD, R - 1), c = idx % HD;
         const int hh = kvh * group + h0 + r / ni, i = i0 + r % ni;
-        qs[idx] = q[(size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + c] * scale;
+        qs[idx] = idx / HD < R ? q[(size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + c] * scale : 0.f;
     }
     lds_barrier();
 
@@ -759,17 +769,15 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
                 }
 #pragma unroll
                 for (int r = 0; r < RM; ++r) {
-                    if (r < R) {
-                        const float* qr = qs + r * HD + c * CH;
+                    const float* qr = qs + r * HD + c * CH;
 #pragma unroll
-                        for (int e = 0; e < CH; ++e) s[r] += qr[e] * kf[e];
-                    }
+                    for (int e = 0; e < CH; ++e) s[r] += qr[e] * kf[e];
                 }
             }
         }
 #pragma unroll
         for (int r = 0; r < RM; ++r) {
-            if (r < R) {
+            {
                 const int qpos = pos0 + i0 + r % ni;
                 const bool tree = sh.tmask != nullptr;
                 const unsigned long long tm = tree ? sh.tmask[sl * sh.m + i0 + r % ni] : 0ull;
@@ -792,19 +800,24 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // (eight keys at a time; the probabilities of keys past the tile's end are zero)
         const int nk = min(64, nkeys - ti * 64);
-        for (int jj = 0; jj < nk; ++jj) {
-            float vf[DPL];
-            const ST* vrow = vbase + (size_t)(ti * 64 + jj) * HD * KW;
+        for (int j0 = 0; j0 < nk; j0 += 8) {
+            float vf[8][DPL];
 #pragma unroll
-            for (int e = 0; e < DPL; ++e) vf[e] = kv_get(vrow, HD, lane * DPL + e);
+            for (int u = 0; u < 8; ++u) {
+                const ST* vrow = vbase + (size_t)(ti * 64 + min(j0 + u, nk - 1)) * HD * KW;
+#pragma unroll
+                for (int e = 0; e < DPL; ++e) vf[u][e] = kv_get(vrow, HD, lane * DPL + e);
+            }
 #pragma unroll
             for (int r = 0; r < RM; ++r) {
-                if (r < R) {
-                    const float p = pw[r * 64 + jj];
+                const float4 p0 = *reinterpret_cast<const float4*>(pw + r * 64 + j0), p1 = *reinterpret_cast<const float4*>(pw + r * 64 + j0 + 4);
+                const float p8[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
 #pragma unroll
-                    for (int e = 0; e < DPL; ++e) acc[r][e] += p * vf[e];
-                }
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int e = 0; e < DPL; ++e) acc[r][e] += p8[u] * vf[u][e];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -862,7 +875,7 @@ template <typename ST, int HD>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restrict__ q, const ST* __restrict__ kc,
                                                             const ST* __restrict__ vc, const int* __restrict__ base,
                                                             AttnShape sh, float* __restrict__ ws) {
-    __shared__ float lds[attn_lds_floats(HD, 4)];
+    __shared__ __align__(16) float lds[attn_lds_floats(HD, 4)];
     attn_item_partial<ST, HD, ATT_RMAX>(q, kc, vc, base, sh, blockIdx.x, blockIdx.y, lds, ws);
 }
 
@@ -912,28 +925,29 @@ __global__ __launch_bounds__(512) void calib_stream_kernel(const uint4* __restri
 // ------------------------------------------------------------------------------------------
 // Token id forced into [0, V-1] (an id outside it can only come from a row without a greedy token, see argmax_kernel)
 __host__ __device__ __forceinline__ int clamp_token(int id, int V) { return id < 0 ? 0 : (id >= V ? V - 1 : id); }
-// Greedy token per row: index of the largest logit, lowest index on ties.  One workgroup per row.
-// A row in which no logit compares greater than -inf (all NaN, or all -inf) has no greedy token: the stored id is
-// clamped into [0, V-1] so that nothing downstream indexes a table out of bounds, and *bad (if given) is set to 1.
-__global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ logits, int V, int32_t* __restrict__ out,
-                                                      int out_stride, int* __restrict__ bad) {
+// Greedy token per row: index of the largest logit, lowest index on ties.  Two launches: a workgroup per 4096-logit segment of
+// a row (16 consecutive-per-wavefront values per thread, requested together), then a wavefront per row over its segments; a
+// workgroup per whole row was a chain of memory round trips (15 us at V = 32000, 64 us at 152064, against 5 + 3).
+// A row in which no logit compares greater than or equal to -inf (all NaN) has no greedy token: the stored id is clamped into
+// [0, V-1] so that nothing downstream indexes a table out of bounds, and *bad (if given) is set to 1.
+// Row r's token goes to out[(r / m) * sseq + r % m].
+constexpr int ARGMAX_SEG = 4096;
+__global__ __launch_bounds__(256) void argmax_part_kernel(const float* __restrict__ logits, int V, float* __restrict__ pv, int* __restrict__ pi) {
     __shared__ float bv[4];
     __shared__ int bi[4];
-    const int row = blockIdx.x;
-    const float* l = logits + (size_t)row * V;
+    const int row = blockIdx.x, seg = blockIdx.y;
+    const float4* l = reinterpret_cast<const float4*>(logits + (size_t)row * V);
+    float4 x[4];
+    // (V is a multiple of 16; a clamped duplicate of the last element changes nothing)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = l[min(seg * (ARGMAX_SEG / 4) + 256 * u + (int)threadIdx.x, V / 4 - 1)];
     float best = -INFINITY; int besti = 0x7FFFFFFF;
-    // eight independent loads per trip (a one-load-per-trip loop pays a memory round trip per trip: 39 us for the 61
-    // rows of a tree verify pass); a thread still sees its columns in ascending order, so ties keep the lowest index
-    constexpr int U = 8;
-    for (int c0 = threadIdx.x; c0 < V; c0 += 256 * U) {
-        float x[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = l[min(c0 + 256 * u, V - 1)];
+    for (int u = 0; u < 4; ++u) {
+        const int c = 4 * min(seg * (ARGMAX_SEG / 4) + 256 * u + (int)threadIdx.x, V / 4 - 1);
+        const float y[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int c = c0 + 256 * u;
-            if (c < V && (x[u] > best || (x[u] == best && c < besti))) { best = x[u]; besti = c; }
-        }
+        for (int e = 0; e < 4; ++e) if (y[e] > best || (y[e] == best && c + e < besti)) { best = y[e]; besti = c + e; }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -945,8 +959,25 @@ __global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ l
     if (threadIdx.x == 0) {
         for (int w = 1; w < 4; ++w)
             if (bv[w] > best || (bv[w] == best && bi[w] < besti)) { best = bv[w]; besti = bi[w]; }
+        pv[(size_t)row * gridDim.y + seg] = best; pi[(size_t)row * gridDim.y + seg] = besti;
+    }
+}
+__global__ __launch_bounds__(64) void argmax_final_kernel(const float* __restrict__ pv, const int* __restrict__ pi, int nseg, int V, int32_t* __restrict__ out,
+                                                          int m, int sseq, int* __restrict__ bad) {
+    const int row = blockIdx.x;
+    float best = -INFINITY; int besti = 0x7FFFFFFF;
+    for (int s = threadIdx.x; s < nseg; s += 64) {
+        const float v = pv[(size_t)row * nseg + s]; const int i = pi[(size_t)row * nseg + s];
+        if (v > best || (v == best && i < besti)) { best = v; besti = i; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(best, o, 64); const int oi = __shfl_xor(besti, o, 64);
+        if (ov > best || (ov == best && oi < besti)) { best = ov; besti = oi; }
+    }
+    if (threadIdx.x == 0) {
         if (bad && (unsigned)besti >= (unsigned)V) *bad = 1;
-        out[(size_t)row * out_stride] = clamp_token(besti, V);
+        out[(size_t)(row / m) * sseq + row % m] = clamp_token(besti, V);
     }
 }
 
@@ -957,13 +988,13 @@ __global__ void rows_to_f32_kernel(const WT* __restrict__ src, size_t n, float* 
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) dst[i] = to_f32(src[i]);
 }
 
-// rows[r][0..d) = table[ids[r]]  (embedding gather, converted to fp32)
+// rows[r][0..d) = table[ids[(r / m) * sseq + r % m]]  (embedding gather, converted to fp32; d a multiple of 16)
 template <typename WT>
-__global__ void gather_rows_kernel(const WT* __restrict__ table, const int32_t* __restrict__ ids, int id_stride,
+__global__ void gather_rows_kernel(const WT* __restrict__ table, const int32_t* __restrict__ ids, int m, int sseq,
                                    float* __restrict__ out, int ldo, int d) {
     const int row = blockIdx.x;
-    const WT* src = table + (size_t)ids[(size_t)row * id_stride] * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) out[(size_t)row * ldo + c] = to_f32(src[c]);
+    const WT* src = table + (size_t)ids[(size_t)(row / m) * sseq + row % m] * d;
+    for (int c = 4 * threadIdx.x; c < d; c += 4 * blockDim.x) *reinterpret_cast<float4*>(out + (size_t)row * ldo + c) = load4_f32(src + c);
 }
 
 // Prefill input rows of sequences blockIdx.y: position p < v -> visual embedding p, else Embed(text[p - v]).
@@ -973,7 +1004,7 @@ __global__ void prefill_rows_kernel(const WT* __restrict__ vis, size_t vis_strid
     const int p = p0 + blockIdx.x, s = blockIdx.y;
     const WT* src = (p < v) ? vis + s * vis_stride + (size_t)p * d : table + (size_t)text[(size_t)s * text_stride + p - v] * d;
     float* o = out + ((size_t)s * gridDim.x + blockIdx.x) * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) o[c] = to_f32(src[c]);
+    for (int c = 4 * threadIdx.x; c < d; c += 4 * blockDim.x) *reinterpret_cast<float4*>(o + c) = load4_f32(src + c);
 }
 
 // dst row s * n + i = src row s * m + first + i (n rows of each of gridDim.y sequences)
@@ -1112,18 +1143,25 @@ __device__ __forceinline__ int block_sample_inverse_cdf(WF wf, int V, float u, f
     int found = 0x7FFFFFFF;
     if (wave == wsel) {
         float run = base;
-        for (int r = s0; r < s1; r += 64) {
-            const int j = r + lane;
-            const float w = (j < s1) ? wf(j) : 0.f;
-            float incl = w;
+        // (eight steps' weights requested together: a step per trip was a memory round trip per 64 elements)
+        for (int r8 = s0; r8 < s1 && found == 0x7FFFFFFF; r8 += 64 * 8) {
+            float w8[8];
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const float up = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += up;
+            for (int k = 0; k < 8; ++k) w8[k] = wf(min(r8 + 64 * k + lane, V - 1));
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int r = r8 + 64 * k, j = r + lane;
+                if (r >= s1 || found != 0x7FFFFFFF) continue;
+                float incl = (j < s1) ? w8[k] : 0.f;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const float up = __shfl_up(incl, o, 64);
+                    if (lane >= o) incl += up;
+                }
+                const unsigned long long hit = __ballot(run + incl > target && j < s1);
+                if (hit) found = r + (int)__builtin_ctzll(hit);
+                else run += __shfl(incl, 63, 64);
             }
-            const unsigned long long hit = __ballot(run + incl > target && j < s1);
-            if (hit) { found = r + (int)__builtin_ctzll(hit); break; }
-            run += __shfl(incl, 63, 64);
         }
         if (found == 0x7FFFFFFF) {            // rounding: the segment total said "here", the in-order walk did not get there
             int lp = last_pos;
@@ -1137,26 +1175,42 @@ __device__ __forceinline__ int block_sample_inverse_cdf(WF wf, int V, float u, f
     return min(max(found, 0), V - 1);
 }
 
-// softmax statistics of one row at inverse temperature it: maximum of x*it and the sum of exp(x*it - max)
+// softmax statistics of two rows at inverse temperature it: maximum of x*it and the sum of exp(x*it - max) of each; the
+// two rows' loads travel together
 template <int NT>
-__device__ __forceinline__ void block_softmax_stats(const float* __restrict__ x, int V, float it, float* smf, float* mx, float* sum) {
-    float m = block_row_max<NT>(x, V, it, smf);
-    float s = 0.f;
+__device__ __forceinline__ void block_softmax_stats2(const float* __restrict__ x, const float* __restrict__ y, int V, float it, float* smf,
+                                                     float (&mx)[2], float (&sum)[2]) {
+    float m0 = -INFINITY, m1 = -INFINITY;
     for (int j = threadIdx.x; j < V; j += NT * 8) {
-        float x8[8];
+        float x8[8], y8[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x8[k] = x[min(j + NT * k, V - 1)];
+        for (int k = 0; k < 8; ++k) { x8[k] = x[min(j + NT * k, V - 1)]; y8[k] = y[min(j + NT * k, V - 1)]; }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) if (j + NT * k < V) s += expf(x8[k] * it - m);
+        for (int k = 0; k < 8; ++k) { m0 = fmaxf(m0, x8[k] * it); m1 = fmaxf(m1, y8[k] * it); }
     }
-    s = wave_sum(s);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) smf[threadIdx.x >> 6] = s;
-    __syncthreads();
-    float total = 0.f;
+    m0 = block_reduce_max<NT>(m0, smf);
+    m1 = block_reduce_max<NT>(m1, smf);
+    float s0 = 0.f, s1 = 0.f;
+    for (int j = threadIdx.x; j < V; j += NT * 8) {
+        float x8[8], y8[8];
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) total += smf[w];
-    *mx = m; *sum = total;
+        for (int k = 0; k < 8; ++k) { x8[k] = x[min(j + NT * k, V - 1)]; y8[k] = y[min(j + NT * k, V - 1)]; }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) if (j + NT * k < V) { s0 += expf(x8[k] * it - m0); s1 += expf(y8[k] * it - m1); }
+    }
+    s0 = wave_sum(s0); s1 = wave_sum(s1);
+    float tot[2] = {s0, s1};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) smf[threadIdx.x >> 6] = tot[q];
+        __syncthreads();
+        float total = 0.f;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) total += smf[w];
+        sum[q] = total;
+    }
+    mx[0] = m0; mx[1] = m1;
 }
 
 // One token per row drawn from softmax(logits / T) with the row's uniform number.  One workgroup per row.
@@ -1200,9 +1254,9 @@ __global__ __launch_bounds__(ACCEPT_NT) void accept_sample_kernel(const int32_t*
         const float* lp = vlogits + ((size_t)b * (K + 1) + i) * V;
         const float* lq = dlogits + ((size_t)i * B + b) * V;
         const int x = min(max(drafts[b * kmax + i], 0), V - 1);
-        float mp, sp, mq, sq;
-        block_softmax_stats<ACCEPT_NT>(lp, V, inv_temp, smf, &mp, &sp);
-        block_softmax_stats<ACCEPT_NT>(lq, V, inv_temp, smf, &mq, &sq);
+        float mxs[2], sums[2];
+        block_softmax_stats2<ACCEPT_NT>(lp, lq, V, inv_temp, smf, mxs, sums);
+        const float mp = mxs[0], mq = mxs[1], sp = sums[0], sq = sums[1];
         const float px = expf(lp[x] * inv_temp - mp) / sp, qx = expf(lq[x] * inv_temp - mq) / sq;
         if (u_acc[b * K + i] * qx < px) continue;
         // rejected: does p - q have a positive part at all?

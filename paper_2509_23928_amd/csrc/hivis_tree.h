@@ -31,79 +31,100 @@ struct TreeDev {
     int32_t* result;                    // [1 + depth+1] accepted length | emitted tokens (-1 padded)
 };
 
-// (value, index) maximum over the workgroup under the order (value descending, index ascending); every thread gets it.
-template <int NT>
-__device__ __forceinline__ void block_best(float& v, int& i, float* smf, int* smi) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(v, o, 64); const int oi = __shfl_xor(i, o, 64);
-        if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) { smf[threadIdx.x >> 6] = v; smi[threadIdx.x >> 6] = i; }
-    __syncthreads();
-    v = smf[0]; i = smi[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) {
-        const float ov = smf[w]; const int oi = smi[w];
-        if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
-    }
-}
-
 // Children of the rows of one level, in two kernels.  Row r of `logits` is the drafter's distribution behind node
 // expand_row[r] (or behind the root if expand_row is null); its k most probable tokens (best first) become pool nodes
 // first + r k + q with score = parent score + log softmax.
-//  1. tree_topk_part_kernel, grid (rows, segments): a workgroup holds one segment of <= 4096 logits in registers
-//     (8 per thread, loaded once), writes the segment's (max, sum of exp) and its k best (value, index) pairs; round q
-//     picks the best element not yet taken under the order (value descending, index ascending).
-//  2. tree_children_kernel, one workgroup per row: log-normaliser from the segment partials (fixed order), the k best
-//     of the segments' candidates by rank counting, pool entries written.
+//  1. tree_topk_part_kernel, grid (rows, segments): a workgroup holds one segment of <= 4096 logits in registers (8 per
+//     thread, loaded once), writes the segment's (max, sum of exp) and its k best (value, index) pairs.  In every wavefront the
+//     lanes' own maxima are ranked by counting; what does not reach the k-th of them cannot be among the k best, and the
+//     few survivors of all wavefronts are ranked by counting.
+//  2. tree_children_kernel, one workgroup per row: log-normaliser from the segment partials (fixed order), the k best of the
+//     segments' candidates by the same two steps, pool entries written.
+// (k rounds of a workgroup-wide maximum took 19 us, k rounds of a wavefront's 14; ranking all candidates behind serial loads of
+// the partials 12 us for 8 segments and 54 us for 38.)
 constexpr int TOPK_NT = 512, TOPK_PER = 8, TOPK_SEG = TOPK_NT * TOPK_PER;
+// (value, index) order of everything below: value descending, index ascending
+__device__ __forceinline__ bool before(float av, int ai, float bv, int bi) { return av > bv || (av == bv && ai < bi); }
+// How many of the n entries (value v[c * stride], index i[c * stride]) in LDS come before (mv, mi).  Eight reads are in flight
+// at a time: one per trip waited for each (100 clocks an entry: 5 us for 100 of them).
+__device__ __forceinline__ int rank_of(const float* v, const int* i, int n, int stride, float mv, int mi) {
+    int rank = 0;
+    for (int c = 0; c < n; c += 8) {
+        float vv[8]; int ii[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { const int at = min(c + u, n - 1) * stride; vv[u] = v[at]; ii[u] = i[at]; }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += (c + u < n && before(vv[u], ii[u], mv, mi)) ? 1 : 0;
+    }
+    return rank;
+}
+// ... entries whose index is their place
+__device__ __forceinline__ int rank_of(const float* v, int n, float mv, int mi) {
+    int rank = 0;
+    for (int c = 0; c < n; c += 8) {
+        float vv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) vv[u] = v[min(c + u, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += (c + u < n && before(vv[u], c + u, mv, mi)) ? 1 : 0;
+    }
+    return rank;
+}
+
 __global__ __launch_bounds__(TOPK_NT) void tree_topk_part_kernel(const float* __restrict__ logits, int V, int k,
                                                                  float* __restrict__ cand_v, int32_t* __restrict__ cand_i,
                                                                  float* __restrict__ seg_ms) {
-    __shared__ float smf[TOPK_NT / 64];
-    __shared__ int smi[TOPK_NT / 64];
+    constexpr int NWV = TOPK_NT / 64, MAXS = NWV * TREE_MAX_TOPK * TOPK_PER;      // survivors: at most k lanes per wavefront
+    constexpr int NONE = 0x7FFFFFFF;
+    __shared__ float smf[NWV], lv[TOPK_NT], thr_v[NWV], sv[MAXS];
+    __shared__ int li[TOPK_NT], thr_i[NWV], si[MAXS], cnt;
     const int r = blockIdx.x, seg = blockIdx.y, nseg = gridDim.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float* x = logits + (size_t)r * V;
-    const int j0 = seg * TOPK_SEG;
+    const int j0 = seg * TOPK_SEG + threadIdx.x;            // element e of a thread: j0 + 512 e
     float v[TOPK_PER];
 #pragma unroll
-    for (int e = 0; e < TOPK_PER; ++e) {
-        const int j = j0 + e * TOPK_NT + threadIdx.x;
-        v[e] = j < V ? x[j] : -INFINITY;
-    }
-    float m = v[0];
+    for (int e = 0; e < TOPK_PER; ++e) v[e] = x[min(j0 + TOPK_NT * e, V - 1)];
+    if (threadIdx.x == 0) cnt = 0;
+    if (lane == 0) { thr_v[wave] = -INFINITY; thr_i[wave] = NONE; }
+    // this thread's best element (a NaN is none)
+    float bv = -INFINITY; int bi = NONE;
 #pragma unroll
-    for (int e = 1; e < TOPK_PER; ++e) m = fmaxf(m, v[e]);
-    m = block_reduce_max<TOPK_NT>(m, smf);                  // the segment is never empty (the host sizes the grid)
+    for (int e = 0; e < TOPK_PER; ++e) {
+        const int j = j0 + TOPK_NT * e;
+        if (j < V && before(v[e], j, bv, bi)) { bv = v[e]; bi = j; }
+    }
+    lv[threadIdx.x] = bv; li[threadIdx.x] = bi;
+    const float m = block_reduce_max<TOPK_NT>(bv, smf);     // the segment is never empty (the host sizes the grid)
     float sum = 0.f;
 #pragma unroll
-    for (int e = 0; e < TOPK_PER; ++e) sum += expf(v[e] - m);       // exp(-inf) = 0 for the padding
+    for (int e = 0; e < TOPK_PER; ++e) sum += j0 + TOPK_NT * e < V ? expf(v[e] - m) : 0.f;
     sum = wave_sum(sum);
+    const int rank = rank_of(lv + wave * 64, li + wave * 64, 64, 1, bv, bi);
+    if (rank == k - 1 && bi != NONE) { thr_v[wave] = bv; thr_i[wave] = bi; }
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) smf[threadIdx.x >> 6] = sum;
+    if (lane == 0) smf[wave] = sum;
+    const float tv = thr_v[wave]; const int ti = thr_i[wave];
+#pragma unroll
+    for (int e = 0; e < TOPK_PER; ++e) {
+        const int j = j0 + TOPK_NT * e;
+        if (j < V && v[e] == v[e] && !before(tv, ti, v[e], j)) { const int at = atomicAdd(&cnt, 1); sv[at] = v[e]; si[at] = j; }
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         float total = 0.f;
-        for (int w = 0; w < TOPK_NT / 64; ++w) total += smf[w];
+        for (int w = 0; w < NWV; ++w) total += smf[w];
         seg_ms[((size_t)r * nseg + seg) * 2] = m; seg_ms[((size_t)r * nseg + seg) * 2 + 1] = total;
     }
-    for (int q = 0; q < k; ++q) {
-        float bv = -INFINITY; int bi = 0x7FFFFFFF;
-#pragma unroll
-        for (int e = 0; e < TOPK_PER; ++e) {
-            const int j = j0 + e * TOPK_NT + threadIdx.x;
-            if (j < V && (v[e] > bv || (v[e] == bv && j < bi))) { bv = v[e]; bi = j; }
-        }
-        block_best<TOPK_NT>(bv, bi, smf, smi);
-#pragma unroll
-        for (int e = 0; e < TOPK_PER; ++e) if (j0 + e * TOPK_NT + (int)threadIdx.x == bi) v[e] = -INFINITY;   // taken (logits are finite)
-        if (threadIdx.x == 0) {
-            const size_t o = ((size_t)r * nseg + seg) * k + q;
-            cand_v[o] = bv; cand_i[o] = bi;                    // a segment shorter than k pads with (-inf, INT_MAX)
-        }
+    const size_t o = ((size_t)r * nseg + seg) * k;
+    const int live = cnt;
+    for (int i = threadIdx.x; i < live; i += TOPK_NT) {
+        const float mv = sv[i]; const int mi = si[i];
+        const int rk = rank_of(sv, si, live, 1, mv, mi);
+        if (rk < k) { cand_v[o + rk] = mv; cand_i[o + rk] = mi; }
     }
+    // a segment with fewer than k elements pads with (-inf, INT_MAX)
+    if ((int)threadIdx.x < k && (int)threadIdx.x >= live) { cand_v[o + threadIdx.x] = -INFINITY; cand_i[o + threadIdx.x] = NONE; }
 }
 
 constexpr int CHILD_NT = 256;
@@ -111,62 +132,91 @@ __global__ __launch_bounds__(CHILD_NT) void tree_children_kernel(const float* __
                                                                  const float* __restrict__ seg_ms, int nseg, int k, int first,
                                                                  const int32_t* __restrict__ expand_row, int depth, int hid_row0,
                                                                  TreeDev t) {
-    extern __shared__ float child_lds[];                     // [nseg * k] values, [nseg * k] indices
-    const int r = blockIdx.x, n = nseg * k;
+    // Candidates that reach the k-th best of the segments' maxima lie in at most k segments (with fewer than k segments: in
+    // all of them): at most k * k
+    constexpr int MAXS = TREE_MAX_TOPK * TREE_MAX_TOPK, NONE = 0x7FFFFFFF;
+    extern __shared__ float child_lds[];                     // [nseg k] values, [nseg k] indices
+    __shared__ float sv[MAXS], thr_v, lz;
+    __shared__ int si[MAXS], thr_i, cnt;
+    const int r = blockIdx.x, n = nseg * k, lane = threadIdx.x & 63;
     float* cv = child_lds; int* ci = reinterpret_cast<int*>(child_lds + n);
+    const float* ms = seg_ms + (size_t)r * nseg * 2;
+    const int parent = expand_row ? expand_row[r] : -1;      // (requested before anything waits)
     for (int i = threadIdx.x; i < n; i += CHILD_NT) { cv[i] = cand_v[(size_t)r * n + i]; ci[i] = cand_i[(size_t)r * n + i]; }
-    __syncthreads();
-    // log-normaliser: every thread adds the segments in the same order
-    float mx = -INFINITY;
-    for (int s = 0; s < nseg; ++s) mx = fmaxf(mx, seg_ms[((size_t)r * nseg + s) * 2]);
-    float sum = 0.f;
-    for (int s = 0; s < nseg; ++s) sum += seg_ms[((size_t)r * nseg + s) * 2 + 1] * expf(seg_ms[((size_t)r * nseg + s) * 2] - mx);
-    const float logz = mx + logf(sum);
-    const int parent = expand_row ? expand_row[r] : -1;
+    if (threadIdx.x == 0) { thr_v = -INFINITY; thr_i = NONE; cnt = 0; }
     const float pscore = parent >= 0 ? t.pool_score[parent] : 0.f;
+    if (threadIdx.x < 64) {
+        float mx = -INFINITY, sum = 0.f;
+        for (int s = lane; s < nseg; s += 64) mx = fmaxf(mx, ms[2 * s]);
+        mx = wave_max(mx);
+        for (int s = lane; s < nseg; s += 64) sum += ms[2 * s + 1] * expf(ms[2 * s] - mx);
+        sum = wave_sum(sum);
+        if (lane == 0) lz = mx + logf(sum);
+    }
+    __syncthreads();
+    if (nseg >= k)
+        for (int s = threadIdx.x; s < nseg; s += CHILD_NT) {
+            const float mv = cv[s * k]; const int mi = ci[s * k];
+            const int rank = rank_of(cv, ci, nseg, k, mv, mi);
+            if (rank == k - 1 && mi != NONE) { thr_v = mv; thr_i = mi; }
+        }
+    __syncthreads();
+    const float tv = thr_v; const int ti = thr_i;
     for (int i = threadIdx.x; i < n; i += CHILD_NT) {
         const float vi = cv[i]; const int ii = ci[i];
-        int rank = 0;
-        for (int j = 0; j < n; ++j) rank += (cv[j] > vi || (cv[j] == vi && ci[j] < ii)) ? 1 : 0;
-        if (rank < k && ii != 0x7FFFFFFF) {
+        if (ii == NONE || before(tv, ti, vi, ii)) continue;
+        const int at = atomicAdd(&cnt, 1);
+        if (at < MAXS) { sv[at] = vi; si[at] = ii; }
+    }
+    __syncthreads();
+    const int live = min(cnt, MAXS);
+    for (int i = threadIdx.x; i < live; i += CHILD_NT) {
+        const float vi = sv[i]; const int ii = si[i];
+        const int rank = rank_of(sv, si, live, 1, vi, ii);
+        if (rank < k) {
             const int node = first + r * k + rank;
             t.pool_tok[node] = ii; t.pool_par[node] = parent; t.pool_depth[node] = depth; t.pool_hid[node] = hid_row0 + r;
-            t.pool_score[node] = pscore + (vi - logz);
+            t.pool_score[node] = pscore + (vi - lz);
             t.pool_slot[node] = -1;
         }
     }
 }
 
 // The k best-scored of the n nodes [lo, lo + n) of one level become the drafter's tree rows n_prev .. n_prev + k - 1
-// (rank order).  One workgroup, n <= 256.
-__global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, int n_prev, int level, TreeDev t) {
-    __shared__ float s[256];
-    const int i = threadIdx.x;
-    s[i] = i < n ? t.pool_score[lo + i] : -INFINITY;
-    __syncthreads();
-    if (i >= n) return;
-    const float si = s[i];
-    int rank = 0;
-    for (int j = 0; j < n; ++j) rank += (s[j] > si || (s[j] == si && j < i)) ? 1 : 0;
-    if (rank >= k) return;
-    const int slot = n_prev + rank, node = lo + i;
-    t.expand[(level - 1) * k + rank] = node;
-    t.pool_slot[node] = slot;
-    const int parent = t.pool_par[node];      // expanded at the level before (or the root): its row and mask already exist
-    t.dmask[slot] = (parent >= 0 ? t.dmask[t.pool_slot[parent]] : 0ull) | (1ull << slot);
-    t.dpos[slot] = level - 1;
-}
-
-// Fusion input rows of one level: [hidden row the node was drawn from ; Embed(node token)], and the nodes' tokens.
+// (rank order), and row rank's fusion input [hidden row the node was drawn from ; Embed(node token)] is written to cat, its token
+// to tok.  One workgroup per rank, n <= 256: each ranks all nodes (a launch of its own for that cost more than the k-fold
+// counting).  table == nullptr: the embedding half is not needed (it comes from the fusion FC's table).
 template <typename WT>
-__global__ void tree_cat_kernel(const int32_t* __restrict__ expand_row, TreeDev t, const float* __restrict__ H,
-                                const WT* __restrict__ table, float* __restrict__ cat, int32_t* __restrict__ tok, int d) {
-    const int r = blockIdx.x, node = expand_row[r];
-    if (threadIdx.x == 0) tok[r] = t.pool_tok[node];
-    const float* h = H + (size_t)t.pool_hid[node] * d;
-    const WT* e = table + (size_t)t.pool_tok[node] * d;
-    float* o = cat + (size_t)r * 2 * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) { o[c] = h[c]; o[d + c] = to_f32(e[c]); }
+__global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, int n_prev, int level, TreeDev t, const float* __restrict__ H,
+                                                          const WT* __restrict__ table, float* __restrict__ cat, int32_t* __restrict__ tok, int d) {
+    __shared__ float s[256];
+    __shared__ int pick[2];                  // hidden row, token
+    const int i = threadIdx.x, want = blockIdx.x;
+    s[i] = i < n ? t.pool_score[lo + i] : -INFINITY;
+    if (i == 0) { pick[0] = 0; pick[1] = 0; }          // (stays so only with NaN scores, where ranks are no permutation)
+    __syncthreads();
+    if (i < n) {
+        const float si = s[i];
+        const int rank = rank_of(s, n, si, i);
+        if (rank == want) {
+            const int slot = n_prev + rank, node = lo + i;
+            t.expand[(level - 1) * k + rank] = node;
+            t.pool_slot[node] = slot;
+            const int parent = t.pool_par[node];      // expanded at the level before (or the root): its row and mask already exist
+            t.dmask[slot] = (parent >= 0 ? t.dmask[t.pool_slot[parent]] : 0ull) | (1ull << slot);
+            t.dpos[slot] = level - 1;
+            pick[0] = t.pool_hid[node]; pick[1] = t.pool_tok[node];
+            tok[rank] = pick[1];
+        }
+    }
+    __syncthreads();
+    const float4* h = reinterpret_cast<const float4*>(H + (size_t)pick[0] * d);
+    float* o = cat + (size_t)want * 2 * d;
+    for (int c = i; c < d / 4; c += 256) reinterpret_cast<float4*>(o)[c] = h[c];
+    if (table) {
+        const WT* e = table + (size_t)pick[1] * d;
+        for (int c = i; c < d; c += 256) o[d + c] = to_f32(e[c]);
+    }
 }
 
 // Candidates: the N best-scored pool nodes, in pool order; verify rows 1..N (row 0 = root = the last known token).
@@ -175,6 +225,7 @@ __global__ __launch_bounds__(1024) void tree_select_kernel(int P, int N, const i
                                                            const int* __restrict__ dlen, TreeDev t) {
     __shared__ float s[TREE_MAX_POOL];
     __shared__ short rowof[TREE_MAX_POOL];      // verify row of a pool node, 0 if not a candidate
+    __shared__ int count[32];                   // candidates per 64 pool nodes
     for (int i = threadIdx.x; i < P; i += 1024) s[i] = t.pool_score[i];
     __syncthreads();
     bool chosen[2] = {false, false};
@@ -182,19 +233,17 @@ __global__ __launch_bounds__(1024) void tree_select_kernel(int P, int N, const i
         const int i = threadIdx.x + e * 1024;
         if (i >= P) continue;
         const float si = s[i];
-        int rank = 0;
-        for (int j = 0; j < P; ++j) rank += (s[j] > si || (s[j] == si && j < i)) ? 1 : 0;
-        chosen[e] = rank < N;
+        chosen[e] = rank_of(s, P, si, i) < N;
     }
-    for (int e = 0; e < 2; ++e) { const int i = threadIdx.x + e * 1024; if (i < P) rowof[i] = chosen[e] ? 1 : 0; }
-    __syncthreads();
+    // rows are numbered in pool order: candidates below this one, from the wavefronts' counts and a ballot
     int myrow[2] = {0, 0};
     for (int e = 0; e < 2; ++e) {
-        const int i = threadIdx.x + e * 1024;
-        if (i >= P || !chosen[e]) continue;
-        int below = 0;
-        for (int j = 0; j < i; ++j) below += rowof[j] ? 1 : 0;
-        myrow[e] = below + 1;
+        const unsigned long long hit = __ballot(chosen[e]);
+        if ((threadIdx.x & 63) == 0) count[e * 16 + (threadIdx.x >> 6)] = (int)__popcll(hit);
+        __syncthreads();
+        int below = (int)__popcll(hit & ((1ull << (threadIdx.x & 63)) - 1));
+        for (int w = 0; w < e * 16 + (int)(threadIdx.x >> 6); ++w) below += count[w];
+        if (chosen[e]) myrow[e] = below + 1;
     }
     __syncthreads();
     for (int e = 0; e < 2; ++e) { const int i = threadIdx.x + e * 1024; if (i < P) rowof[i] = (short)myrow[e]; }
@@ -272,16 +321,19 @@ __global__ void tree_kv_gather_kernel(KT* const* __restrict__ kv, int maxL, int 
 }
 
 // Re-feed rows after acceptance: [true feature of path row e ; Embed(token after it)], e = 0..depth (rows beyond the
-// accepted length repeat the last one and are dead).  g: verify features, row stride ldg.
+// accepted length repeat the last one and are dead).  g: verify features, row stride ldg.  table == nullptr as above.
 template <typename WT>
 __global__ void tree_roll_cat_kernel(const float* __restrict__ g, int ldg, const int32_t* __restrict__ path,
                                      const int32_t* __restrict__ next_tok, const WT* __restrict__ table,
                                      float* __restrict__ cat, int d) {
     const int e = blockIdx.x;
-    const float* f = g + (size_t)path[e] * ldg;
-    const WT* em = table + (size_t)next_tok[e] * d;
+    const float4* f = reinterpret_cast<const float4*>(g + (size_t)path[e] * ldg);
     float* o = cat + (size_t)e * 2 * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) { o[c] = f[c]; o[d + c] = to_f32(em[c]); }
+    for (int c = threadIdx.x; c < d / 4; c += blockDim.x) reinterpret_cast<float4*>(o)[c] = f[c];
+    if (table) {
+        const WT* em = table + (size_t)next_tok[e] * d;
+        for (int c = threadIdx.x; c < d; c += blockDim.x) o[d + c] = to_f32(em[c]);
+    }
 }
 
 // After the re-feed: pending hidden state = drafter output at row n; both caches keep n + 1 more rows.
