@@ -362,18 +362,28 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
     const hivis_config& g = c->cfg;
     typedef typename KVType<WT>::type KT;
     if constexpr (std::is_same<KT, f16_t>::value) {
-        // long causal row ranges (prefill): 128 rows of one head per workgroup, key tiles shared through LDS.  Too few such
-        // workgroups leave CUs idle (the last 128 of 3008 rows, 32 heads: 240 us): 16 rows per workgroup then.
-        const long shared_items = (long)nseq * g.n_q_heads * ((m + ATTN_SHARED_ROWS - 1) / ATTN_SHARED_ROWS);
-        if (m >= c->attn_shared_min && 2 * shared_items >= c->num_cu && tmask == nullptr && frag_out && wrote_frag) {
+        // long causal row ranges (prefill): key tiles shared by a workgroup through LDS.  Too few such workgroups leave CUs idle
+        // (the last 128 of 3008 rows, 32 heads: 240 us): 16 rows per workgroup then.
+        const long items2 = (long)nseq * g.n_q_heads * ((m + 127) / 128);
+        if (m >= c->attn_shared_min && 2 * items2 >= c->num_cu && tmask == nullptr && frag_out && wrote_frag) {
+            // two workgroups of 128 rows fit a CU; where there are fewer of them, 64 rows each (640 rows x 32 heads: 35 us, 46 with 128)
+            const bool large = items2 >= 2 * c->num_cu;
+            const int rows = large ? 128 : 64, nw = rows / 16;
             AttnShape sh{};
-            sh.Hq = g.n_q_heads; sh.Hkv = g.n_kv_heads; sh.m = m; sh.mi = ATTN_SHARED_ROWS; sh.gh = 1;
-            sh.n_hblk = g.n_q_heads / g.n_kv_heads; sh.n_rblk = (m + ATTN_SHARED_ROWS - 1) / ATTN_SHARED_ROWS;
-            sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.qrows = qrows; sh.nwaves = FUSED_NW; sh.nsplit = 1; sh.tmask = nullptr;
+            sh.Hq = g.n_q_heads; sh.Hkv = g.n_kv_heads; sh.m = m; sh.mi = rows; sh.gh = 1;
+            sh.n_hblk = g.n_q_heads / g.n_kv_heads; sh.n_rblk = (m + rows - 1) / rows;
+            sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.qrows = qrows; sh.nwaves = nw; sh.nsplit = 1; sh.tmask = nullptr;
             const int items = nseq * g.n_q_heads * sh.n_rblk;
             const size_t lds = attn_shared_lds_bytes(g.head_dim);
-            if (g.head_dim == 128) hipLaunchKernelGGL((attn_rows_shared_kernel<128>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, ldo, frag_out);
-            else hipLaunchKernelGGL((attn_rows_shared_kernel<64>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, ldo, frag_out);
+#define HIVIS_SHARED(HD_, NW_)                                                                                                             \
+    do {                                                                                                                                   \
+        if (lds > 64 * 1024) HIP_TRY(c, hipFuncSetAttribute((const void*)attn_rows_shared_kernel<HD_, NW_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+        hipLaunchKernelGGL((attn_rows_shared_kernel<HD_, NW_>), dim3(items), dim3(64 * NW_), lds, c->stream, q, (const f16_t*)kv.k,        \
+                           (const f16_t*)kv.v, base, sh, ldo, frag_out);                                                                   \
+    } while (0)
+            if (g.head_dim == 128) { if (large) HIVIS_SHARED(128, 8); else HIVIS_SHARED(128, 4); }
+            else { if (large) HIVIS_SHARED(64, 8); else HIVIS_SHARED(64, 4); }
+#undef HIVIS_SHARED
             *wrote_frag = true;
             HIP_TRY(c, hipGetLastError());
             return HIVIS_OK;

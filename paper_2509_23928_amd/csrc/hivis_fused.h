@@ -1100,24 +1100,34 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_kernel(const float* __rest
     attn_wg_mfma<HD, ATTN_ROWS_RM>(q, kc, vc, base, sh, item, 0, attn_rows_lds, nullptr, nullptr, out, ldo, nullptr, frag_out);
 }
 
-// Attention of long row ranges (prefill): the published flash-attention work split.  A workgroup owns 128 consecutive
-// rows of ONE query head, 16 per wavefront, and walks the keys in tiles of 16 that the whole workgroup loads once and
-// shares through LDS (two buffers, one workgroup barrier per tile), so a cached row is fetched once per 128 query rows
-// instead of once per 16; every wavefront keeps its own running maximum / sum / accumulator, and nothing is merged
-// across wavefronts.  Arithmetic per tile is exactly attn_wg_mfma's (hi/lo operands, three MFMA per product).
+// Attention of long row ranges (prefill): the published flash-attention work split.  A workgroup of NW wavefronts owns
+// 16 NW consecutive rows of ONE query head, 16 per wavefront, and walks the keys in tiles of 32 that the whole workgroup
+// loads once and shares through LDS (two buffers, one workgroup barrier per tile); every wavefront keeps its own running
+// maximum / sum / accumulator, and nothing is merged across wavefronts.  Operands are hi/lo pairs and each product is three
+// MFMA, as in attn_wg_mfma; the two 16-key score tiles of a trip lie side by side in the K dimension of the value product
+// (lane group g: keys 4 g .. + 3 of each, V^T read in that order), so that it runs as 16x16x32 MFMA as well.
+// Bound by the vector instructions and LDS latencies of a trip (scaling the sums, maximum across lanes, splitting the
+// probabilities), not by the MFMAs or the cache's rows: 32 keys per trip halve what a trip costs per key, and tiles that every row sees
+// skip the comparisons.
+// Per layer, 16-key trips and 128 rows per workgroup everywhere before -> now: 640 rows x 32 heads 46 -> 35 us, 3008 x 32
+// 328 -> 275, 1120 x 28 heads of 4 key heads 77 -> 56, two sequences of 378 x 32 heads of 64 22 -> 16.  Slower (485 us at 3008): 32 rows per
+// wavefront, tiles straight to LDS in a ring of four (too many registers; skipping the loads altogether changed nothing).
 // Items: heads vary fastest, row blocks run from the last (most keys) to the first.
-constexpr int ATTN_SHARED_ROWS = 16 * FUSED_NW;
-__host__ __device__ constexpr size_t attn_shared_lds_bytes(int hd) { return 2 * 16 * ((size_t)hd * 4 + 16 + (size_t)hd * 4 + 32); }
+constexpr int ATTN_SHARED_KEYS = 32;
+__host__ __device__ constexpr size_t attn_shared_lds_bytes(int hd) { return 2 * ATTN_SHARED_KEYS * ((size_t)hd * 4 + 16 + (size_t)hd * 4 + 32); }
 
-template <int HD>
-__global__ __launch_bounds__(FUSED_NT) void attn_rows_shared_kernel(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
-                                                                    const int* __restrict__ base, AttnShape sh, int ldo, uint4* __restrict__ frag_out) {
+template <int HD, int NW>
+__global__ __launch_bounds__(64 * NW, NW / 2) void attn_rows_shared_kernel(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
+                                                                           const int* __restrict__ base, AttnShape sh, int ldo, uint4* __restrict__ frag_out) {
     // (the rows go out as activation fragments of the O projection, K = ldo)
     extern __shared__ __align__(16) float attn_shared_lds[];
+    constexpr int ROWS = 16 * NW, NT = 64 * NW, TK = ATTN_SHARED_KEYS;
     constexpr int HALFB = HD * 2, ROWB = HD * 4, KS = HD / 32, NB = HD / 16, NCH = ROWB / 16;
     constexpr int VSTRIDE = ROWB + 32, KSTRIDE = ROWB + 16;
-    constexpr int KTB = 16 * KSTRIDE, BUFB = KTB + 16 * VSTRIDE;
-    static_assert(16 * NCH <= FUSED_NT, "one 16-key tile is loaded by one instruction of the workgroup");
+    constexpr int KTB = TK * KSTRIDE, BUFB = KTB + TK * VSTRIDE;
+    constexpr int LK = NT / NCH, PER = TK / LK;                      // keys the workgroup loads per instruction; instructions per tile
+    constexpr int GB = NW == 8 ? 2 : 4;                              // 16-dim blocks whose products are interleaved
+    static_assert(LK * NCH == NT && PER * LK == TK, "a tile is loaded by whole instructions of the workgroup");
     char* bufs = reinterpret_cast<char*>(attn_shared_lds);          // [2][K tile | V tile]
 
     const int group = sh.Hq / sh.Hkv;
@@ -1129,27 +1139,26 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_shared_kernel(const float*
     const int sl = item / nh_total;
     const int kvh = hh / group;
     const int seq = sh.seq0 + sl;
-    const int i0 = rblk * ATTN_SHARED_ROWS, ni = min(ATTN_SHARED_ROWS, sh.m - i0);
-    const int pos0 = (sh.nbase > 0 ? sh.base_val[sl] : base[seq]) + sh.offset;
+    const int i0 = rblk * ROWS, ni = min(ROWS, sh.m - i0);
+    const int pos0 = __builtin_amdgcn_readfirstlane((sh.nbase > 0 ? sh.base_val[sl] : base[seq]) + sh.offset);       // (a scalar: branches on it are uniform)
     const int nkeys = min(pos0 + i0 + ni, sh.maxL);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n16 = lane & 15, g = lane >> 4;
     const int r = 16 * wave + n16;
     const bool valid = r < ni;
     const bool active = 16 * wave < ni;                              // uniform per wavefront
-    const int wq_max = pos0 + i0 + min(16 * wave + 15, ni - 1);      // last position any row of this wavefront may see
+    const int wq_min = pos0 + i0 + 16 * wave, wq_max = pos0 + i0 + min(16 * wave + 15, ni - 1);     // positions of its first and last row
 
     const char* kbase = reinterpret_cast<const char*>(kc) + ((size_t)seq * sh.Hkv + kvh) * sh.maxL * ROWB;
     const char* vbase = reinterpret_cast<const char*>(vc) + ((size_t)seq * sh.Hkv + kvh) * sh.maxL * ROWB;
-    const int tid = threadIdx.x;
-    const bool loader = tid < 16 * NCH;
-    const int lkey = min(tid / NCH, 15), lch = tid % NCH;
-    u32x4_t knext, vnext;
+    const int lkey = threadIdx.x / NCH, lch = threadIdx.x % NCH;
+    u32x4_t knext[PER], vnext[PER];
+    // (keys beyond the last are replaced by it: masked below)
 #define HIVIS_SHARED_LOADS(kb_)                                                                 \
-    {                                                                                           \
-        const size_t off_ = (size_t)min((kb_) + lkey, nkeys - 1) * ROWB + lch * 16;             \
-        knext = *reinterpret_cast<const u32x4_t*>(kbase + off_);                                \
-        vnext = *reinterpret_cast<const u32x4_t*>(vbase + off_);                                \
+    _Pragma("unroll") for (int i = 0; i < PER; ++i) {                                           \
+        const size_t off_ = (size_t)min((kb_) + lkey + i * LK, nkeys - 1) * ROWB + lch * 16;    \
+        knext[i] = *reinterpret_cast<const u32x4_t*>(kbase + off_);                             \
+        vnext[i] = *reinterpret_cast<const u32x4_t*>(vbase + off_);                             \
     }
     HIVIS_SHARED_LOADS(0)
 
@@ -1176,61 +1185,91 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_shared_kernel(const float*
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    for (int kb = 0, t = 0; kb < nkeys; kb += 16, ++t) {
-        char* kt = bufs + (t & 1) * BUFB;
-        char* vt = kt + KTB;
-        // tile t -> LDS buffer t % 2 (its last readers, of tile t - 2, are behind the barrier of tile t - 1); request tile t + 1
-        if (loader) {
-            *reinterpret_cast<u32x4_t*>(kt + lkey * KSTRIDE + lch * 16) = knext;
-            *reinterpret_cast<u32x4_t*>(vt + lkey * VSTRIDE + lch * 16) = vnext;
-        }
-        HIVIS_SHARED_LOADS(min(kb + 16, nkeys - 1))
-        lds_barrier();
-        if (!active || kb > wq_max) continue;                    // uniform: no row of this wavefront sees the tile
-        f32x4_t st = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // tile t -> LDS buffer t % 2 (its last readers, of tile t - 2, are behind the barrier of tile t - 1); request tile t + 1
+#define HIVIS_SHARED_TILE()                                                                                         \
+    char* kt = bufs + (t & 1) * BUFB;                                                                               \
+    char* vt = kt + KTB;                                                                                            \
+    _Pragma("unroll") for (int i = 0; i < PER; ++i) {                                                               \
+        *reinterpret_cast<u32x4_t*>(kt + (lkey + i * LK) * KSTRIDE + lch * 16) = knext[i];                          \
+        *reinterpret_cast<u32x4_t*>(vt + (lkey + i * LK) * VSTRIDE + lch * 16) = vnext[i];                          \
+    }                                                                                                               \
+    HIVIS_SHARED_LOADS(kb + TK)                                                                                     \
+    lds_barrier();
+    int kb = 0, t = 0;
+    const int kend = active ? min(nkeys, wq_max + 1) : 0;            // (uniform; no row of this wavefront sees the tiles behind it)
+    for (; kb < kend; kb += TK, ++t) {
+        HIVIS_SHARED_TILE()
+        f32x4_t st[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const f16x8_t kh = *reinterpret_cast<const f16x8_t*>(kt + n16 * KSTRIDE + ks * 64 + g * 16);
-            const f16x8_t kl = *reinterpret_cast<const f16x8_t*>(kt + n16 * KSTRIDE + HALFB + ks * 64 + g * 16);
-            st = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[ks], st, 0, 0, 0);
-            st = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, ql[ks], st, 0, 0, 0);
-            st = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[ks], st, 0, 0, 0);
-        }
-        float sv[4], tmax = -INFINITY;
+            f16x8_t kh[2], kl[2];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int key = kb + 4 * g + rr;
-            sv[rr] = (key < nkeys && key <= qpos) ? st[rr] : -INFINITY;
-            tmax = fmaxf(tmax, sv[rr]);
+            for (int u = 0; u < 2; ++u) {
+                const char* src = kt + (16 * u + n16) * KSTRIDE + ks * 64 + g * 16;
+                kh[u] = *reinterpret_cast<const f16x8_t*>(src);
+                kl[u] = *reinterpret_cast<const f16x8_t*>(src + HALFB);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) st[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl[u], qh[ks], st[u], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) st[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh[u], ql[ks], st[u], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) st[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh[u], qh[ks], st[u], 0, 0, 0);
         }
+        // this lane: keys kb + 16 u + 4 g + 0..3 of row r
+        float sv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sv[e] = st[e >> 2][e & 3];
+        if (kb + TK > nkeys || kb + TK - 1 > wq_min) {               // uniform: some row does not see some key of the tile
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int key = kb + 16 * (e >> 2) + 4 * g + (e & 3);
+                sv[e] = ((key < nkeys) & (key <= qpos)) ? sv[e] : -INFINITY;
+            }
+        }
+        float tmax = sv[0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) tmax = fmaxf(tmax, sv[e]);
         tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
         tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
         const float mnew = fmaxf(mrun, tmax);
         const float mref = (mnew == -INFINITY) ? 0.f : mnew;
         const float alpha = __expf(mrun - mref);
-        float p[4], psum = 0.f;
+        float psum = 0.f;
+        f16x8_t pbh, pbl;
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) { p[rr] = __expf(sv[rr] - mref); psum += p[rr]; }
+        for (int e = 0; e < 8; ++e) {
+            const float p = __expf(sv[e] - mref);
+            psum += p;
+            pbh[e] = (_Float16)p; pbl[e] = (_Float16)(p - (float)pbh[e]);
+        }
         mrun = mnew;
         lrun = lrun * alpha + psum;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) acc[nb] *= alpha;
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) acc[nb][rr] *= alpha;
-        }
-        f16x4_t pbh, pbl;
+        for (int n0 = 0; n0 < NB; n0 += GB) {
+            f16x8_t v[GB][2];                                        // hi, lo: keys 4 g + 0..3 of both 16-key halves (transposing reads, see attn_wg_mfma)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) { pbh[rr] = (_Float16)p[rr]; pbl[rr] = (_Float16)(p[rr] - (float)pbh[rr]); }
+            for (int b = 0; b < GB; ++b)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const char* src = vt + (4 * g + (n16 >> 2)) * VSTRIDE + (nb * 16 + 4 * (n16 & 3)) * 2;
-            const s16x4_t rh = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src));
-            const s16x4_t rl = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src + HALFB));
-            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, rl), pbh, acc[nb], 0, 0, 0);
-            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, rh), pbl, acc[nb], 0, 0, 0);
-            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, rh), pbh, acc[nb], 0, 0, 0);
+                for (int p = 0; p < 2; ++p) {
+                    const char* src = vt + (4 * g + (n16 >> 2)) * VSTRIDE + ((n0 + b) * 16 + 4 * (n16 & 3)) * 2 + p * HALFB;
+                    typedef unsigned long long u64x2_t __attribute__((ext_vector_type(2)));
+                    u64x2_t x;
+                    x[0] = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src)));
+                    x[1] = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(src + 16 * VSTRIDE)));
+                    v[b][p] = __builtin_bit_cast(f16x8_t, x);
+                }
+#pragma unroll
+            for (int o = 0; o < 3; ++o)                              // lo.hi + hi.lo + hi.hi
+#pragma unroll
+                for (int b = 0; b < GB; ++b)
+                    acc[n0 + b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(v[b][o == 0], o == 1 ? pbl : pbh, acc[n0 + b], 0, 0, 0);
         }
     }
+    for (; kb < nkeys; kb += TK, ++t) { HIVIS_SHARED_TILE() }
+#undef HIVIS_SHARED_TILE
 #undef HIVIS_SHARED_LOADS
     // this lane holds dims 16 nb + 4 (lane/16) + 0..3 of row r; the row's sum of weights is spread over the four lane groups
     float lsum = lrun;

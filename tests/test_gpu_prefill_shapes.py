@@ -58,3 +58,13 @@ def test_row_counts(n_vis, n_text):
 ], ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
 def test_widths(kw):
     check_prefill(cfg_of(**kw))
+
+
+# the shared-tile attention: 64 rows per workgroup from 128 workgroups of 128 rows on, 128 rows from 512 on; last blocks of a few
+# rows, key counts around the 32-key tile, and a prompt whose last block is one row
+@pytest.mark.parametrize("kw", [dict(n_vis=513, n_text=32, n_q_heads=32, n_kv_heads=4), dict(n_vis=500, n_text=13, n_q_heads=32, n_kv_heads=32, head_dim=128),
+                                dict(n_vis=380, n_text=33, n_q_heads=32, n_kv_heads=8, batch=4), dict(n_vis=350, n_text=35, n_q_heads=32, n_kv_heads=2, head_dim=128, batch=4),
+                                dict(n_vis=480, n_text=32, n_q_heads=48, n_kv_heads=6, batch=3)],
+                         ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
+def test_shared_attention(kw):
+    check_prefill(cfg_of(**kw))
