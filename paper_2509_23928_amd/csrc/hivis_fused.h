@@ -1557,7 +1557,12 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
         for (int row = blockIdx.x; row < pp.M; row += gridDim.x) {
             float* smf = lds; int* smi = reinterpret_cast<int*>(lds + 16);
             const float u = ph.u[(row / pp.m) * ph.u_sseq + ph.u_idx];
-            const int tok = block_sample_softmax<FUSED_NT>(ph.A + (size_t)row * ph.lda, pp.V, pp.inv_temp, u, smf, smi);
+            // (the row's maximum from the greedy candidates of the LM head before it: one pass over the logits less)
+            const float* x = ph.A + (size_t)row * ph.lda;
+            float m = -INFINITY;
+            for (int w = threadIdx.x; w < ph.N; w += FUSED_NT) m = fmaxf(m, ph.pm[(size_t)row * ph.N + w]);
+            m = block_reduce_max<FUSED_NT>(m * pp.inv_temp, smf);
+            const int tok = block_sample_inverse_cdf<FUSED_NT>([&](int j) { return expf(x[j] * pp.inv_temp - m); }, pp.V, u, smf, smi);
             if (threadIdx.x == 0) st_wt(&ph.tok_out[(row / pp.m) * ph.o_sseq + (row % pp.m) * ph.o_srow], tok);
         }
         break;

@@ -1078,16 +1078,19 @@ __device__ __forceinline__ float block_reduce_max(float v, float* sm) {
     for (int w = 1; w < NT / 64; ++w) r = fmaxf(r, sm[w]);
     return r;
 }
-// maximum of x[j] * it over one row, 8 independent loads per trip
+// Loads in flight per thread in the passes over a row: its latency is trips x memory round trips (32000 logits, 512 threads: the
+// three passes of a drawn token took 21 us with 8 loads per trip and a scan of 64 elements per step of the walk, now 14; a sampled acceptance 46 -> 32)
+constexpr int SAMPLE_U = 16;
+// maximum of x[j] * it over one row
 template <int NT>
 __device__ __forceinline__ float block_row_max(const float* __restrict__ x, int V, float it, float* sm) {
     float m = -INFINITY;
-    for (int j = threadIdx.x; j < V; j += NT * 8) {
-        float x8[8];
+    for (int j = threadIdx.x; j < V; j += NT * SAMPLE_U) {
+        float xk[SAMPLE_U];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x8[k] = x[min(j + NT * k, V - 1)];
+        for (int k = 0; k < SAMPLE_U; ++k) xk[k] = x[min(j + NT * k, V - 1)];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) m = fmaxf(m, x8[k] * it);       // clamped duplicates of the last element do not change a maximum
+        for (int k = 0; k < SAMPLE_U; ++k) m = fmaxf(m, xk[k] * it);       // clamped duplicates of the last element do not change a maximum
     }
     return block_reduce_max<NT>(m, sm);
 }
@@ -1107,23 +1110,23 @@ __device__ __forceinline__ int block_reduce_min_int(int v, int* sm) {
 // exceeds u * total; if rounding leaves none, the last index with a positive weight.  All threads return the index.
 // Wavefront w owns the contiguous segment [w*L, (w+1)*L) (L a multiple of 64) and reads it 64 consecutive elements
 // at a time (coalesced).  Pass A: segment totals.  Pass B: the wavefront whose segment contains the target walks it
-// again, 64 elements per step, with an in-order wavefront scan, and takes the first lane whose prefix exceeds it.
+// again, 512 elements per step: eight consecutive ones per lane, an in-order scan over the lanes' sums, and in the first lane
+// whose prefix exceeds the target the first element that does.  Elements of weight zero are never taken.
 template <int NT, typename WF>
-__device__ __forceinline__ int block_sample_inverse_cdf(WF wf, int V, float u, float* smf, int* smi) {
+__device__ __forceinline__ int block_sample_inverse_cdf(WF wf, int V, float u, float* smf, int* smi, float* total_out = nullptr) {
     constexpr int NWV = NT / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int L = ((V + NWV * 64 - 1) / (NWV * 64)) * 64;
     const int s0 = min(wave * L, V), s1 = min(s0 + L, V);
     float part = 0.f;
     int last_pos = -1;
-    // (8 independent loads per trip: a one-load-per-trip loop pays a memory round trip per element)
-    for (int j = s0 + lane; j < s1; j += 64 * 8) {
-        float w8[8];
+    for (int j = s0 + lane; j < s1; j += 64 * SAMPLE_U) {
+        float wk[SAMPLE_U];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) w8[k] = wf(min(j + 64 * k, V - 1));
+        for (int k = 0; k < SAMPLE_U; ++k) wk[k] = wf(min(j + 64 * k, V - 1));
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (j + 64 * k < s1) { part += w8[k]; if (w8[k] > 0.f) last_pos = j + 64 * k; }
+        for (int k = 0; k < SAMPLE_U; ++k) {
+            if (j + 64 * k < s1) { part += wk[k]; if (wk[k] > 0.f) last_pos = j + 64 * k; }
         }
     }
     const float tw = wave_sum(part);
@@ -1133,6 +1136,7 @@ __device__ __forceinline__ int block_sample_inverse_cdf(WF wf, int V, float u, f
     float base = 0.f, total = 0.f;
 #pragma unroll
     for (int w = 0; w < NWV; ++w) { if (w < wave) base += smf[w]; total += smf[w]; }
+    if (total_out) *total_out = total;
     const float target = u * total;
     int wsel = -1;
     {
@@ -1143,25 +1147,30 @@ __device__ __forceinline__ int block_sample_inverse_cdf(WF wf, int V, float u, f
     int found = 0x7FFFFFFF;
     if (wave == wsel) {
         float run = base;
-        // (eight steps' weights requested together: a step per trip was a memory round trip per 64 elements)
         for (int r8 = s0; r8 < s1 && found == 0x7FFFFFFF; r8 += 64 * 8) {
-            float w8[8];
+            const int j0 = r8 + 8 * lane;
+            float w8[8], own = 0.f;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) w8[k] = wf(min(r8 + 64 * k + lane, V - 1));
+            for (int k = 0; k < 8; ++k) w8[k] = wf(min(j0 + k, V - 1));
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int r = r8 + 64 * k, j = r + lane;
-                if (r >= s1 || found != 0x7FFFFFFF) continue;
-                float incl = (j < s1) ? w8[k] : 0.f;
+            for (int k = 0; k < 8; ++k) { if (j0 + k >= s1) w8[k] = 0.f; own += w8[k]; }
+            float incl = own;
 #pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const float up = __shfl_up(incl, o, 64);
-                    if (lane >= o) incl += up;
-                }
-                const unsigned long long hit = __ballot(run + incl > target && j < s1);
-                if (hit) found = r + (int)__builtin_ctzll(hit);
-                else run += __shfl(incl, 63, 64);
+            for (int o = 1; o < 64; o <<= 1) {
+                const float up = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += up;
             }
+            const unsigned long long hit = __ballot(run + incl > target && own > 0.f);
+            if (hit) {
+                const float before = __shfl_up(incl, 1, 64);
+                float c = run + (lane > 0 ? before : 0.f);
+                int at = 0;
+                bool over = false;
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (!over && w8[k] > 0.f) { at = k; c += w8[k]; over = c > target; }
+                found = __shfl(j0 + at, (int)__builtin_ctzll(hit), 64);
+            } else run += __shfl(incl, 63, 64);
         }
         if (found == 0x7FFFFFFF) {            // rounding: the segment total said "here", the in-order walk did not get there
             int lp = last_pos;
@@ -1181,22 +1190,22 @@ template <int NT>
 __device__ __forceinline__ void block_softmax_stats2(const float* __restrict__ x, const float* __restrict__ y, int V, float it, float* smf,
                                                      float (&mx)[2], float (&sum)[2]) {
     float m0 = -INFINITY, m1 = -INFINITY;
-    for (int j = threadIdx.x; j < V; j += NT * 8) {
-        float x8[8], y8[8];
+    for (int j = threadIdx.x; j < V; j += NT * SAMPLE_U) {
+        float xk[SAMPLE_U], yk[SAMPLE_U];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) { x8[k] = x[min(j + NT * k, V - 1)]; y8[k] = y[min(j + NT * k, V - 1)]; }
+        for (int k = 0; k < SAMPLE_U; ++k) { xk[k] = x[min(j + NT * k, V - 1)]; yk[k] = y[min(j + NT * k, V - 1)]; }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) { m0 = fmaxf(m0, x8[k] * it); m1 = fmaxf(m1, y8[k] * it); }
+        for (int k = 0; k < SAMPLE_U; ++k) { m0 = fmaxf(m0, xk[k] * it); m1 = fmaxf(m1, yk[k] * it); }
     }
     m0 = block_reduce_max<NT>(m0, smf);
     m1 = block_reduce_max<NT>(m1, smf);
     float s0 = 0.f, s1 = 0.f;
-    for (int j = threadIdx.x; j < V; j += NT * 8) {
-        float x8[8], y8[8];
+    for (int j = threadIdx.x; j < V; j += NT * SAMPLE_U) {
+        float xk[SAMPLE_U], yk[SAMPLE_U];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) { x8[k] = x[min(j + NT * k, V - 1)]; y8[k] = y[min(j + NT * k, V - 1)]; }
+        for (int k = 0; k < SAMPLE_U; ++k) { xk[k] = x[min(j + NT * k, V - 1)]; yk[k] = y[min(j + NT * k, V - 1)]; }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) if (j + NT * k < V) { s0 += expf(x8[k] * it - m0); s1 += expf(y8[k] * it - m1); }
+        for (int k = 0; k < SAMPLE_U; ++k) if (j + NT * k < V) { s0 += expf(xk[k] * it - m0); s1 += expf(yk[k] * it - m1); }
     }
     s0 = wave_sum(s0); s1 = wave_sum(s1);
     float tot[2] = {s0, s1};
@@ -1259,20 +1268,12 @@ __global__ __launch_bounds__(ACCEPT_NT) void accept_sample_kernel(const int32_t*
         const float mp = mxs[0], mq = mxs[1], sp = sums[0], sq = sums[1];
         const float px = expf(lp[x] * inv_temp - mp) / sp, qx = expf(lq[x] * inv_temp - mq) / sq;
         if (u_acc[b * K + i] * qx < px) continue;
-        // rejected: does p - q have a positive part at all?
+        // rejected: a draw from the positive part of p - q, if it has one
         const float isp = 1.0f / sp, isq = 1.0f / sq;
         auto resid = [&](int j) { return fmaxf(expf(lp[j] * inv_temp - mp) * isp - expf(lq[j] * inv_temp - mq) * isq, 0.f); };
-        float any = 0.f;
-        for (int j = threadIdx.x; j < V; j += ACCEPT_NT * 4) {
-            float r4[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) r4[k] = resid(min(j + ACCEPT_NT * k, V - 1));
-#pragma unroll
-            for (int k = 0; k < 4; ++k) any = fmaxf(any, r4[k]);
-        }
-        any = block_reduce_max<ACCEPT_NT>(any, smf);
-        if (any > 0.f) tok = block_sample_inverse_cdf<ACCEPT_NT>(resid, V, u_res[b], smf, smi);
-        else tok = block_sample_inverse_cdf<ACCEPT_NT>([&](int j) { return expf(lp[j] * inv_temp - mp); }, V, u_res[b], smf, smi);
+        float total = 0.f;
+        tok = block_sample_inverse_cdf<ACCEPT_NT>(resid, V, u_res[b], smf, smi, &total);
+        if (!(total > 0.f)) tok = block_sample_inverse_cdf<ACCEPT_NT>([&](int j) { return expf(lp[j] * inv_temp - mp); }, V, u_res[b], smf, smi);
         n = i;
         break;
     }
