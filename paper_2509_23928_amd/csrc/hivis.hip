@@ -1089,6 +1089,30 @@ bool tall_fused(const hivis_ctx* c, int M, int kblks, int ntiles, TallPlan* pl) 
     return pl->us <= tall_plan(c, M, kblks, ntiles, true).us + ROW_KERNEL_US;
 }
 
+// Room for the K slices of every pass the prefill buffers can hold, at create: growing it inside a request cost its first pass up to
+// 5 ms.  (gemm_wide_kernel: slices x columns <= 3 x CUs x 128, at most 64 rows.)  At most 128 MB, what 1000 rows of 4096 columns
+// in eight slices need: allocating more takes a context longer than it saves, and wider passes grow it.  No room is not an error here.
+void splitk_reserve(hivis_ctx* c) {
+    const hivis_config& g = c->cfg;
+    const int d = g.d, qd = g.n_q_heads * g.head_dim, nqkv = qd + 2 * g.n_kv_heads * g.head_dim, F = g.ffn;
+    size_t need = (size_t)MAX_ROWS * 3 * c->num_cu * 128;
+    const size_t most = (size_t)32 << 20;
+    for (int M = 128; M <= c->pf_rows && need < most; M += 64) {
+        const int K[4] = {d, qd, d, F}, N[4] = {nqkv, d, 2 * F, d};
+        for (int i = 0; i < 4; ++i) {
+            TallPlan pl;
+            if (i % 2 == 0 && tall_fused(c, M, K[i] / 32, N[i] / 16, &pl)) continue;
+            pl = tall_plan(c, M, K[i] / 32, N[i] / 16, true);
+            if (pl.ksplit > 1) need = std::max(need, (size_t)pl.ksplit * M * N[i]);
+        }
+    }
+    need = std::min(need, std::max(most, (size_t)MAX_ROWS * 3 * c->num_cu * 128));
+    void* q = nullptr;
+    if (hipMalloc(&q, need * sizeof(float)) != hipSuccess) { (void)hipGetLastError(); return; }
+    c->allocs.push_back(q);
+    c->splitk_ws = (float*)q; c->splitk_floats = need;
+}
+
 // M = nseq * m rows: q (rotated) to q_out [M][q_dim], k and v of sequence seq0 + s to its cache rows base[seq0 + s] + offset ..
 template <typename WT>
 int rows_qkv(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const uint4* frag, const int* base, int offset, int seq0, int nseq, int m,
@@ -1773,6 +1797,7 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
         if ((rc = dev_alloc(c, &c->pf_gu, (size_t)R * std::max(2 * F, qd + 2 * kd)))) return rc;      // (more rows: finished in the GEMM, or K slices)
         if ((rc = dev_alloc(c, &c->pf_frag, (size_t)PR * std::max(2 * d, qd) / 4))) return rc;      // 4 bytes per value, in 16-byte units
         if ((rc = dev_alloc(c, &c->pf_frag2, (size_t)PR * F / 4))) return rc;
+        splitk_reserve(c);
     }
     if ((rc = dev_alloc(c, &c->logits_v, (size_t)R * V))) return rc;
     if ((rc = dev_alloc(c, &c->logits_d, (size_t)g.k_max * B * V))) return rc;
