@@ -1,6 +1,7 @@
 // Host side of the HiViS draft-verify library: context, state machine, launch sequences.
 // The C ABI is declared and documented in include/hivis.h.
 #include "hivis.h"
+#include "hivis_sizes.h"
 #include "hivis_kernels.h"
 #include "hivis_gemm.h"
 #include "hivis_fused.h"
@@ -30,9 +31,6 @@ static __device__ __align__(256) unsigned char scratch[HIVIS_SCRATCH_BYTES];
 namespace {
 
 enum State { ST_CREATED = 0, ST_READY, ST_DRAFTED, ST_VERIFIED, ST_TREE_DRAFTED, ST_TREE_VERIFIED };
-
-constexpr int MAX_ROWS = 64;        // rows per pass that the activation buffers hold (tree verify: root + 63 candidates)
-constexpr int CHAIN_MAX_ROWS = 32;  // chain verify rows B*(K+1); prefill chunk; rows per launch of the skinny GEMM
 
 // Rows of a draft tree (null pointers: ordinary causal rows)
 struct TreeRows { const int* pos_delta = nullptr; const unsigned long long* mask = nullptr; };
@@ -93,6 +91,7 @@ struct hivis_ctx {
     void* vis = nullptr;        // staging for vis_embeds [B][max_vis][d]
     // whole-prompt prefill buffers (bf16 models): all v+l rows of one or several sequences per layer
     int pf_rows = 0;
+    hivis::PrefillSizes pf_sizes{};
     float *pf_x = nullptr, *pf_xt = nullptr, *pf_a = nullptr, *pf_qkv = nullptr, *pf_att = nullptr, *pf_proj = nullptr, *pf_gu = nullptr;
     uint4 *pf_frag = nullptr, *pf_frag2 = nullptr;      // activation fragments: of d / q_dim wide rows, and of the MLP's inner rows
     std::vector<int32_t> h_ids;
@@ -258,7 +257,7 @@ int upload_layer(hivis_ctx* c, const hivis_layer_weights& w, void* staging, Laye
 // column chunks per row for the row-wise kernels: few rows -> split every row over several workgroups
 static inline int row_chunks(int rows) { return rows >= 256 ? 1 : std::max(1, std::min(8, 256 / std::max(rows, 1))); }
 
-void launch_pack(hivis_ctx* c, const float* A, int lda, int M, int kblks);
+int launch_pack(hivis_ctx* c, const float* A, int lda, int M, int K, uint4** out);
 int wide_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, int ldy, hivis::Parts* defer = nullptr);
 template <typename WT>
 int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* h, hivis::Parts pending, const int* base,
@@ -276,8 +275,9 @@ template <typename WT>
 int gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, int N, float* Y, int ldy, int epi) {
     if (M < 1 || M > MAX_ROWS) return fail(c, HIVIS_EINVAL, "gemm rows %d out of range", M);
     if (sizeof(WT) == 2 && M >= c->wide_min && c->pf_frag && c->pf_rows >= MAX_ROWS && ldy == N && epi == EPI_STORE && !c->no_wide_gemm) {
-        launch_pack(c, A, lda, M, K / 32);
-        return wide_gemm(c, c->pf_frag, M, K, Wp, N, Y, ldy);
+        uint4* frag = nullptr;
+        if (int rc = launch_pack(c, A, lda, M, K, &frag)) return rc;
+        return wide_gemm(c, frag, M, K, Wp, N, Y, ldy);
     }
     if (M > CHAIN_MAX_ROWS) {            // wider passes (tree verify)
         // fp32 models: one launch per 32 rows
@@ -995,9 +995,14 @@ int splitk_space(hivis_ctx* c, size_t floats) {
     c->splitk_floats = floats;
     return HIVIS_OK;
 }
-void launch_pack(hivis_ctx* c, const float* A, int lda, int M, int kblks) {
-    const size_t chunks = (size_t)((M + 15) / 16) * kblks * 64;
-    hipLaunchKernelGGL(pack_afrag_kernel, dim3((unsigned)std::min<size_t>((chunks + 255) / 256, 65535)), dim3(256), 0, c->stream, A, lda, M, kblks, c->pf_frag);
+// rows of fp32 -> fragments, in the buffer that holds them (*out)
+int launch_pack(hivis_ctx* c, const float* A, int lda, int M, int K, uint4** out) {
+    const int which = frag_buffer(c->pf_sizes, M, K);
+    if (!which) return fail(c, HIVIS_EINVAL, "no buffer holds the fragments of %d rows of %d values", M, K);
+    *out = which == 1 ? c->pf_frag : c->pf_frag2;
+    const size_t chunks = frag_values(M, K) / 8;
+    hipLaunchKernelGGL(pack_afrag_kernel, dim3((unsigned)std::min<size_t>((chunks + 255) / 256, 65535)), dim3(256), 0, c->stream, A, lda, M, K / 32, *out);
+    return HIVIS_OK;
 }
 
 // Column tiles per wavefront and K slices of a tall GEMM: the pair with the least estimated time.  A workgroup (one per CU)
@@ -1160,7 +1165,8 @@ int rows_norm(hivis_ctx* c, float* h, const Parts& delta, int M, const void* gai
         if (delta.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, delta, d, d, c->pf_proj, d);
         const float* one = delta.n > 1 ? c->pf_proj : delta.p;
         hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, c->stream, h, d, one, d, (const WT*)gain, c->pf_a, d, d, c->cfg.rms_eps);
-        launch_pack(c, c->pf_a, d, M, d / 32);
+        uint4* frag = nullptr;              // (d wide rows: always pf_frag)
+        if (int rc = launch_pack(c, c->pf_a, d, M, d, &frag)) return rc;
     }
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
@@ -1180,8 +1186,9 @@ int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* 
     // then keep whatever the buffer held: an MFMA output row depends on its own activation row only, and those rows are never stored)
     bool att_frag = false;
     if (int rc = attention_rows_mfma<WT>(c, c->qkv, qd, kv, base, offset, seq0, nseq, m, c->att, qd, tr.mask, c->pf_frag, &att_frag)) return rc;
-    if (!att_frag) launch_pack(c, c->att, qd, M, qd / 32);
-    if (int rc = rows_gemm(c, c->pf_frag, M, qd, L.wo, d, c->proj, &po)) return rc;
+    uint4* frag = c->pf_frag;
+    if (!att_frag) { if (int rc = launch_pack(c, c->att, qd, M, qd, &frag)) return rc; }
+    if (int rc = rows_gemm(c, frag, M, qd, L.wo, d, c->proj, &po)) return rc;
     if (int rc = rows_norm<WT>(c, h, po, M, L.norm2)) return rc;
     if (int rc = rows_gateup(c, L, c->pf_frag, M, c->gu, c->pf_frag2)) return rc;
     return rows_gemm(c, c->pf_frag2, M, F, L.wd, d, c->proj, out_pending);
@@ -1198,9 +1205,10 @@ int rows_attn_mlp(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const float*
     bool att_frag = false;
     if (c->fused) { if (int rc = attention_rows_mfma<WT>(c, q, qd, kv, c->zeros, offset, seq0, nseq, n, c->pf_att, qd, nullptr, c->pf_frag, &att_frag, qrows)) return rc; }
     else if (int rc = attention<WT>(c, q, qd, kv, c->zeros, offset, seq0, nseq, n, offset + n, c->pf_att, qd, nullptr, qrows)) return rc;
-    if (!att_frag) launch_pack(c, c->pf_att, qd, M, qd / 32);
+    uint4* frag = c->pf_frag;
+    if (!att_frag) { if (int rc = launch_pack(c, c->pf_att, qd, M, qd, &frag)) return rc; }
     Parts po{};
-    if (int rc = rows_gemm(c, c->pf_frag, M, qd, L.wo, d, c->pf_proj, &po)) return rc;
+    if (int rc = rows_gemm(c, frag, M, qd, L.wo, d, c->pf_proj, &po)) return rc;
     if (int rc = rows_norm<WT>(c, h, po, M, L.norm2)) return rc;
     if (int rc = rows_gateup(c, L, c->pf_frag, M, c->pf_gu, c->pf_frag2)) return rc;
     return rows_gemm(c, c->pf_frag2, M, F, L.wd, d, c->pf_proj, out_pending);
@@ -1692,9 +1700,10 @@ int build_embed_fc_table(hivis_ctx* c, const hivis_weights* w) {
         for (int r0 = 0; r0 < V && !rc; r0 += R) {
             const int n = std::min(R, V - r0);
             hipLaunchKernelGGL((rows_to_f32_kernel<WT>), dim3(1024), dim3(256), 0, c->stream, (const WT*)c->embed + (size_t)r0 * d, (size_t)n * d, c->pf_x);
-            launch_pack(c, c->pf_x, d, n, d / 32);
+            uint4* frag = nullptr;
+            if ((rc = launch_pack(c, c->pf_x, d, n, d, &frag))) break;
             TallOut o{}; o.Y = table + (size_t)r0 * d; o.ldy = d;
-            rc = launch_tall<TALL_STORE>(c, tall_plan(c, n, d / 32, d / 16, false), c->pf_frag, n, d, w2p, d, o);
+            rc = launch_tall<TALL_STORE>(c, tall_plan(c, n, d / 32, d / 16, false), frag, n, d, w2p, d, o);
         }
         if (rc) break;
         if (hipStreamSynchronize(c->stream) != hipSuccess) { rc = fail(c, HIVIS_EHIP, "building the embedding table of the fusion FC failed"); break; }
@@ -1785,9 +1794,8 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     if ((rc = dev_alloc(c, &c->feat, (size_t)B * g.max_text * d))) return rc;
     if (sizeof(WT) == 2) {
         if ((rc = tall_setup<TALL_STORE>(c)) || (rc = tall_setup<TALL_SILU>(c)) || (rc = tall_setup<TALL_QKV>(c))) return rc;
-        // rows of the prefill buffers: the longest prompt, or as many sequences at a time as fit 4096 rows
-        const int one = g.max_vis + g.max_text;
-        const int PR = (std::max(one, std::min(B * one, 4096)) + 15) & ~15;        // whole row tiles
+        c->pf_sizes = prefill_sizes(d, qd, F, B, g.max_vis, g.max_text);
+        const int PR = c->pf_sizes.rows;
         c->pf_rows = PR;
         if ((rc = dev_alloc(c, &c->pf_x, (size_t)PR * d))) return rc;
         if ((rc = dev_alloc(c, &c->pf_xt, (size_t)std::min(PR, B * g.max_text) * d))) return rc;
@@ -1795,8 +1803,8 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
         if ((rc = dev_alloc(c, &c->pf_qkv, std::max((size_t)PR * qd, (size_t)R * (qd + 2 * kd))))) return rc;
         if ((rc = dev_alloc(c, &c->pf_proj, (size_t)PR * d))) return rc;
         if ((rc = dev_alloc(c, &c->pf_gu, (size_t)R * std::max(2 * F, qd + 2 * kd)))) return rc;      // (more rows: finished in the GEMM, or K slices)
-        if ((rc = dev_alloc(c, &c->pf_frag, (size_t)PR * std::max(2 * d, qd) / 4))) return rc;      // 4 bytes per value, in 16-byte units
-        if ((rc = dev_alloc(c, &c->pf_frag2, (size_t)PR * F / 4))) return rc;
+        if ((rc = dev_alloc(c, &c->pf_frag, c->pf_sizes.frag / 4))) return rc;      // 4 bytes per value, in 16-byte units
+        if ((rc = dev_alloc(c, &c->pf_frag2, c->pf_sizes.frag2 / 4))) return rc;
         splitk_reserve(c);
     }
     if ((rc = dev_alloc(c, &c->logits_v, (size_t)R * V))) return rc;
