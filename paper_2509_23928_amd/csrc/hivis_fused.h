@@ -626,8 +626,8 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
                     float x1 = v, x2 = tile[idx + RPL] * sc;
                     if (ph.bias) { x1 += ph.bias[col]; x2 += ph.bias[col + 1]; }
                     if (col < qd + kd) {
-                        const float c = epi_a[sl], s = epi_b[sl];
-                        const float y1 = x1 * c - x2 * s, y2 = x2 * c + x1 * s;
+                        float y1, y2;
+                        rotate_pair(x1, x2, epi_a[sl], epi_b[sl], y1, y2);
                         if (col < qd) {
                             st_wt_pair(&ph.Y[(size_t)row * ph.ldy + col], y1, y2);
                         } else {

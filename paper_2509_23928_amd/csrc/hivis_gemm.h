@@ -188,11 +188,10 @@ __device__ __forceinline__ void tall_write(const TallOut& o, const v4u_t* area, 
                     f32x4_t y = x[u] + bias;
                     if (isq || isk) {
                         // columns 2i, 2i+1 of a head are the rotary pair (i, i + HD/2); two pairs
-                        const f32x4_t z = y;
-                        y[0] = (float)((double)z[0] * (double)t[u][0] - (double)z[1] * (double)t[u][1]);
-                        y[1] = (float)((double)z[1] * (double)t[u][0] + (double)z[0] * (double)t[u][1]);
-                        y[2] = (float)((double)z[2] * (double)t[u][2] - (double)z[3] * (double)t[u][3]);
-                        y[3] = (float)((double)z[3] * (double)t[u][2] + (double)z[2] * (double)t[u][3]);
+                        float z[4];
+                        rotate_pair(y[0], y[1], t[u][0], t[u][1], z[0], z[1]);
+                        rotate_pair(y[2], y[3], t[u][2], t[u][3], z[2], z[3]);
+                        y = f32x4_t{z[0], z[1], z[2], z[3]};
                     }
                     if (isq) *reinterpret_cast<f32x4_t*>(o.Y + (size_t)(row0 + rw[u]) * o.ldy + col) = y;
                     else {

@@ -11,6 +11,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "hivis_rotary.h"
 
 namespace hivis {
 
@@ -603,8 +604,8 @@ __global__ void rope_append_kernel(float* __restrict__ qkv, int Hq, int Hkv, int
         float* x = r + (size_t)head * HD;          // the pair (i, i + hd/2) sits in columns 2i, 2i+1 (PACK_QKV order)
         const float b1 = bias ? bias[(size_t)head * HD + 2 * i] : 0.f, b2 = bias ? bias[(size_t)head * HD + 2 * i + 1] : 0.f;
         const float x1 = x[2 * i] + b1, x2 = x[2 * i + 1] + b2;
-        const float y1 = (float)((double)x1 * c - (double)x2 * s);
-        const float y2 = (float)((double)x2 * c + (double)x1 * s);
+        float y1, y2;
+        rotate_pair(x1, x2, c, s, y1, y2);
         if (head < Hq) {
             x[2 * i] = y1; x[2 * i + 1] = y2;
         } else {

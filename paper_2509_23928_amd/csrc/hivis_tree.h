@@ -501,8 +501,7 @@ __global__ void wide_rope_append_kernel(Parts qkv, float* __restrict__ q_out, in
                 sincos((double)pos * inv_freq, &s, &c);
             }
             const float x1 = e ? x.z : x.x, x2 = e ? x.w : x.y;
-            y[2 * e] = (float)((double)x1 * c - (double)x2 * s);
-            y[2 * e + 1] = (float)((double)x2 * c + (double)x1 * s);
+            rotate_pair(x1, x2, c, s, y[2 * e], y[2 * e + 1]);
         }
         if (head < Hq) {
             *reinterpret_cast<float4*>(q_out + (size_t)row * ldq + (size_t)head * HD + 2 * i) = make_float4(y[0], y[1], y[2], y[3]);
