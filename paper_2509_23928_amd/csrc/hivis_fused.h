@@ -278,6 +278,9 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     // that many rows only (with eight, their second set of row registers spills)
     constexpr int U = KBW, QM = (EPI == FEPI_QKV_TAB) ? 2 : (EPI == FEPI_QKV_TAB4) ? 4 : FUSED_QM, NT = FUSED_NT;
     static_assert((G % 2) == 0, "tiles are processed in pairs");
+    // bf16w: two accumulators for the high parts where a group's tiles are few (eight wavefronts' sums then round as sixteen K
+    // slices' do, which is what passes of these widths had; the wide products had four slices, and their registers are taken)
+    constexpr int NHI = G == FusedCfg<WT>::G ? 1 : 2;
     constexpr int TILE = G * 64 * RPL;
     constexpr int SLOTS = TILE / NT;         // epilogue slots per thread (all of the same row and column-in-tile)
     static_assert(TILE % NT == 0, "whole epilogue slots per thread");
@@ -463,9 +466,9 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     for (int tg = t_begin; tg < t_end; tg += G) {
         const int ng = min(G, t_end - tg);
         const bool first = (tg == t_begin);
-        f32x4_t acc[G];
+        typename AccT<WT, NHI>::type acc[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) acc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < G; ++g) acc_zero(acc[g]);
         afrag_t af[KBW];
         if constexpr (SINGLE) {
             // ---- every workgroup owns at most one tile.  The K passes go in pairs, and everything the NEXT pair needs
@@ -478,12 +481,10 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             for (int pass = 0; pass < npass; pass += 2) {
                 HIVIS_STAGE_FROM(pass, araw, graw, true, )
                 if (pass == 0) { HIVIS_MARK(1) }
-#pragma unroll
-                for (int j = 0; j < U; ++j) mfma_block(acc[0], af[j], head[j]);
+                mfma_unit(acc[0], af, head);
                 if (pass + 1 < npass) {
                     HIVIS_STAGE_FROM(pass + 1, araw2, graw2, true, )
-#pragma unroll
-                    for (int j = 0; j < U; ++j) mfma_block(acc[0], af[j], wb1[j]);
+                    mfma_unit(acc[0], af, wb1);
                 }
                 if (pass + 2 < npass) {
                     HIVIS_LOAD_RAW_TO(pass + 2, araw, graw)
@@ -514,13 +515,11 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
                 for (int g0 = 0; g0 < G; g0 += 2) {
                     if (g0 < ng) {
                         if (g0 + 1 < ng && !(g0 == 0 && have_wb1)) issue_unit(wb1, W, kblks, tg + g0 + 1, kb0, nkb, lane);
-#pragma unroll
-                        for (int j = 0; j < U; ++j) mfma_block(acc[g0], af[j], head[j]);
+                        mfma_unit(acc[g0], af, head);
                         if (g0 + 2 < ng) issue_unit(head, W, kblks, tg + g0 + 2, kb0, nkb, lane);
                         else if (nvalid) issue_unit(head, W, kblks, ntile, nkb0, nnkb, lane);
                         if (g0 + 1 < ng) {
-#pragma unroll
-                            for (int j = 0; j < U; ++j) mfma_block(acc[g0 + 1], af[j], wb1[j]);
+                            mfma_unit(acc[g0 + 1], af, wb1);
                         }
                     }
                 }
@@ -554,6 +553,9 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             if constexpr (RPL == 2) {
                 dst[0] = acc[g][0] + acc[g][2];
                 dst[1] = acc[g][1] + acc[g][3];
+            } else if constexpr (std::is_same<WT, bf16w_t>::value) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dst[e] = (NHI == 2 ? acc[g].hi[0][e] + acc[g].hi[NHI - 1][e] : acc[g].hi[0][e]) + acc[g].lo[e];
             } else {
                 dst[0] = acc[g][0]; dst[1] = acc[g][1]; dst[2] = acc[g][2]; dst[3] = acc[g][3];
             }

@@ -9,9 +9,8 @@ namespace hivis {
 // row tile holds 16 rows; for each block of 32 k-values it has one 1 KiB fragment block of high parts followed by one of
 // low parts:
 //   frag[((row / 16) * kblks + k / 32) * 2 + part][lane] (16 bytes), lane = row % 16 + 16 * ((k / 8) % 4), 8 k-values each
-// which is the operand layout of the 16x16x32 MFMA and the mirror image of the weights' streaming layout.  Both parts are
-// multiplied into the SAME accumulators, so a wavefront's 128 accumulator registers cover 64 x 128 real outputs and one
-// weight fragment serves two MFMAs per row tile.
+// which is the operand layout of the 16x16x32 MFMA and the mirror image of the weights' streaming layout.  One weight fragment
+// serves two MFMAs per row tile.
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ size_t afrag_at(int kblks, int row, int k) {
     return (((size_t)(row >> 4) * kblks + (k >> 5)) * 2) * 64 + (row & 15) + 16 * ((k >> 3) & 3);
@@ -98,6 +97,9 @@ __device__ __forceinline__ void block_to_lds(const v4u_t* src, v4u_t* lds) {
 // Blocks go from memory to LDS directly (they are in fragment order already) into a ring of four K blocks.  A wavefront
 // owns 64 rows x 16 CW columns: 4 x CW accumulator tiles; the weights are the MFMA's A operand, so that a lane ends up with
 // four consecutive columns of one row.
+// Both parts add into the SAME accumulators (there are no registers for two sets).  That rounds twice as often at the high parts'
+// magnitude, but each group's sum has half the K blocks: together the error of the sums alone is that of one sum over all of K with the
+// low parts beside it (4.0e-7 of the result for both at K = 4096, 6.7e-7 at K = 11008; the 16 mantissa bits of the operands leave 2.5e-6).
 // Matrix bound: with random data the MFMAs alone run at 2.0 PFLOP/s on this card (2.46 on zeros, it is power that
 // limits them), a library product of 8192^3 at 1.10.  640 rows, K = 4096, high and low parts counted: 22016 columns 249 ->
 // 172 us (1.35 PFLOP/s), 12288 columns 127 -> 94 us (1.37); 3008 x 22016: 1090 -> 813 us (1.33).  The version with the requests
@@ -371,11 +373,15 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const v4u_t* __restri
                       : Wp + ((size_t)min(ct_wg + (b - NA), ntiles - 1) * kblks + kb0) * 64) + lane;
         inc[i] = isa ? 128 : 64;
     }
-    f32x4_t acc[RTW][CTW];
+    // The low parts have accumulators of their own, added at the end: rounded at the high parts' magnitude instead, the K sum's
+    // error was 1.4 times as large (61 rows, K = 4096 in 3 slices: 3.2e-7 of the result, now 2.2e-7).
+    f32x4_t acc[2][RTW][CTW];
 #pragma unroll
-    for (int r = 0; r < RTW; ++r)
+    for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int c = 0; c < CTW; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < RTW; ++r)
+#pragma unroll
+            for (int c = 0; c < CTW; ++c) acc[p][r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     v4u_t st[NSET][PER_WAVE];
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) st[0][i] = src[i][0];
@@ -409,7 +415,7 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const v4u_t* __restri
                     for (int r = 0; r < RTW; ++r)
 #pragma unroll
                         for (int c = 0; c < CTW; ++c)
-                            acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[c]), __builtin_bit_cast(bf16x8_t, a[p][r]), acc[r][c], 0, 0, 0);
+                            acc[p][r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[c]), __builtin_bit_cast(bf16x8_t, a[p][r]), acc[p][r][c], 0, 0, 0);
                 if (kb + 1 < nkb) {
 #pragma unroll
                     for (int i = 0; i < PER_WAVE; ++i) nxt[(size_t)(wave + 4 * i) * 64 + lane] = st[(u + 1) % NSET][i];
@@ -429,7 +435,7 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const v4u_t* __restri
 #pragma unroll
         for (int c = 0; c < CTW; ++c) {
             const int ct = ct_wg + wc * CTW + c;
-            if (ct < ntiles) *reinterpret_cast<f32x4_t*>(Y + (size_t)row * ldy + ct * 16 + 4 * (lane >> 4)) = acc[r][c];
+            if (ct < ntiles) *reinterpret_cast<f32x4_t*>(Y + (size_t)row * ldy + ct * 16 + 4 * (lane >> 4)) = acc[0][r][c] + acc[1][r][c];
         }
     }
 }

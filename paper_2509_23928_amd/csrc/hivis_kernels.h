@@ -39,8 +39,8 @@ typedef _Float16 f16_t;                                   // IEEE half: KV-cache
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return bf16_to_f32(x); }
 __device__ __forceinline__ float to_f32(f16_t x) { return (float)x; }
-// bf16 storage in the phase kernels of passes of 9..16 rows: the high and the low parts of 16 rows are two MFMA operands
-// that add into the same accumulators (bf16_t: both parts of 8 rows are the 16 rows of one operand)
+// bf16 storage in the phase kernels of passes of 9..16 rows: the high and the low parts of 16 rows are two MFMA operands with
+// accumulators of their own (bf16_t: both parts of 8 rows are the 16 rows of one operand)
 struct bf16w_t { uint16_t bits; };
 __device__ __forceinline__ float to_f32(bf16w_t x) { return bf16_to_f32(x.bits); }
 __device__ __forceinline__ void from_f32(float& dst, float x) { dst = x; }
@@ -322,9 +322,31 @@ __device__ __forceinline__ void mfma_block(f32x4_t& d, const float4& a, const ui
     d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(w.w), d, 0, 0, 0);
 }
 
-__device__ __forceinline__ void mfma_block(f32x4_t& d, const HiLoFrag& a, const uint4& w) {
-    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.hi, __builtin_bit_cast(bf16x8_t, w), d, 0, 0, 0);
-    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.lo, __builtin_bit_cast(bf16x8_t, w), d, 0, 0, 0);
+// Sums of a tile over K blocks.  bf16w: the low parts' products in an accumulator of their own (rounded at their own magnitude),
+// and the high parts' in NHI, K blocks in turn.
+template <int NHI> struct HiLoAcc { f32x4_t hi[NHI], lo; };
+template <typename WT, int NHI> struct AccT { typedef f32x4_t type; };
+template <int NHI> struct AccT<bf16w_t, NHI> { typedef HiLoAcc<NHI> type; };
+__device__ __forceinline__ void acc_zero(f32x4_t& d) { d = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+template <int NHI>
+__device__ __forceinline__ void acc_zero(HiLoAcc<NHI>& d) {
+#pragma unroll
+    for (int i = 0; i < NHI; ++i) acc_zero(d.hi[i]);
+    acc_zero(d.lo);
+}
+// products of U consecutive K blocks
+template <typename AF, int U>
+__device__ __forceinline__ void mfma_unit(f32x4_t& d, const AF (&a)[U], const uint4 (&w)[U]) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) mfma_block(d, a[j], w[j]);
+}
+template <int NHI, int U>
+__device__ __forceinline__ void mfma_unit(HiLoAcc<NHI>& d, const HiLoFrag (&a)[U], const uint4 (&w)[U]) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        d.hi[j % NHI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j].hi, __builtin_bit_cast(bf16x8_t, w[j]), d.hi[j % NHI], 0, 0, 0);
+        d.lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j].lo, __builtin_bit_cast(bf16x8_t, w[j]), d.lo, 0, 0, 0);
+    }
 }
 
 // Epilogue modes of the skinny GEMM
