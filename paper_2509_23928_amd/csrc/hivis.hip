@@ -528,8 +528,13 @@ int drafter_forward(hivis_ctx* c, const float* cat, int seq0, int nseq, int m, i
 // ---- persistent-kernel path --------------------------------------------------------------------
 enum { PROG_VERIFY = 0, PROG_DRAFT = 1, PROG_ROLL = 2, PROG_DRAFT_SAMPLE = 3 };
 
-// Rows a phase program takes: one MFMA tile; bf16 models, one launch per phase: up to 16, through the bf16w kernels (a
-// 12-row verify pass of the 7B widths as a program: see the table at gemm_phase's bf16w configuration).
+// Rows a phase program takes: one MFMA tile; bf16 models, one launch per phase: up to 16, through the bf16w kernels.  Measured with
+// two target layers against the stand-alone kernels (9 and 10 rows) and K slices (from 11 on), us per call, before -> now:
+//                                    verify 9 rows   12 rows      16 rows      re-feed 9 rows  16 rows      draft round, 9 sequences, K = 2
+//   d 4096, ffn 11008, vocab  32000  397 -> 314      397 -> 330   419 -> 347   214 -> 156      221 -> 176   325 -> 273
+//   d 5120, ffn 13824, vocab  32000  492 -> 405      484 -> 415   499 -> 426   278 -> 206      278 -> 214   407 -> 337
+//   d 3584, ffn 18944, vocab 152064  760 -> 497      730 -> 520   795 -> 547   227 -> 178      231 -> 202   757 -> 577
+//   d 2048, ffn  5632, vocab  32000  224 -> 173      249 -> 184   266 -> 191   121 ->  98      152 -> 105   168 -> 152
 template <typename WT>
 bool fused_rows_ok(const hivis_ctx* c, int M) { return M <= (sizeof(WT) == 2 && !c->persistent ? WTraits<bf16w_t>::ROWS : WTraits<WT>::ROWS); }
 
