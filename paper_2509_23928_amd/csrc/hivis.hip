@@ -119,7 +119,10 @@ struct hivis_ctx {
     float* tree_pool[17] = {};                            // buffers of tree_rows_program by row count (allocated at first use)
     float *tcand_v = nullptr, *tseg = nullptr; int32_t* tcand_i = nullptr; int tnseg = 0;   // per-segment top-k candidates and (max, sum) partials   // hidden rows, their logits, level inputs, re-feed inputs
     void** kv_ptrs = nullptr; void* kv_staging = nullptr;
-    float* splitk_ws = nullptr; size_t splitk_floats = 0; bool no_wide_gemm = false; int wide_min = 11;   // measured: 10-row passes faster on the skinny kernels, 12-row passes on the split-K layer   // K-slice partials of the wide GEMM; HIVIS_WIDE_GEMM=0 disables it
+    float* splitk_ws = nullptr; size_t splitk_floats = 0;      // K-slice partials (splitk_space)
+    // passes that no phase program takes: split-K layers from wide_min rows on (with stand-alone kernels on both sides 10 rows were faster
+    // on the skinny ones, 12 on the split-K layer); HIVIS_WIDE_GEMM=0: never
+    bool no_wide_gemm = false; int wide_min = 11;
     int32_t* h_tree_result = nullptr;                     // pinned [1 + TREE_MAX_DEPTH + 1]
 
     // timing
@@ -993,12 +996,28 @@ int fused_setup(hivis_ctx* c) {
 
 
 // ---- GEMMs on activation fragments (bf16 models) --------------------------------------------------------------
-// K-slice partials of a GEMM (kept and grown on demand)
-int splitk_space(hivis_ctx* c, size_t floats) {
-    if (floats <= c->splitk_floats) return HIVIS_OK;
-    if (int rc = dev_alloc(c, &c->splitk_ws, floats)) return rc;
-    c->splitk_floats = floats;
-    return HIVIS_OK;
+// Room for K-slice partials: up to SPLITK_RESERVE floats from create on (allocating more takes a context longer than it saves);
+// when a pass needs more, they are replaced once by all that any pass of this context can need.  (Growing step by step cost each
+// longer prompt up to 5 ms and left the smaller buffers behind.)  The partials of one product are consumed before the next one
+// starts, so nothing refers to the old buffer.  False: no device memory, and the caller does without slices.
+// HIVIS_SPLITK_RESERVE=n: MB instead of 128, 0 for none.
+constexpr size_t SPLITK_RESERVE = (size_t)32 << 20;
+bool splitk_alloc(hivis_ctx* c, size_t floats) {
+    void* q = nullptr;
+    if (hipMalloc(&q, floats * sizeof(float)) != hipSuccess) { (void)hipGetLastError(); return false; }
+    c->splitk_ws = (float*)q; c->splitk_floats = floats;
+    return true;
+}
+size_t splitk_most(const hivis_ctx* c) {
+    const hivis_config& g = c->cfg;
+    return hivis::splitk_floats(c->num_cu, g.d, g.n_q_heads * g.head_dim, g.n_kv_heads * g.head_dim, g.ffn, c->pf_rows);
+}
+bool splitk_space(hivis_ctx* c, size_t floats) {
+    if (floats <= c->splitk_floats) return true;
+    if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
+    (void)hipFree(c->splitk_ws);
+    c->splitk_ws = nullptr; c->splitk_floats = 0;
+    return splitk_alloc(c, std::max(floats, splitk_most(c))) || splitk_alloc(c, floats);
 }
 // rows of fp32 -> fragments, in the buffer that holds them (*out)
 int launch_pack(hivis_ctx* c, const float* A, int lda, int M, int K, uint4** out) {
@@ -1010,32 +1029,17 @@ int launch_pack(hivis_ctx* c, const float* A, int lda, int M, int K, uint4** out
     return HIVIS_OK;
 }
 
-// Column tiles per wavefront and K slices of a tall GEMM: the pair with the least estimated time.  A workgroup (one per CU)
-// takes 0.066 us per K block and column tile when it runs alone and about 1.3 times that when all CUs work (the card's
-// power limit), plus 7 us to start and finish; slices cost their partial sums, written once and read once.  (Measured at 640 rows,
-// K = 4096: 22016 columns 430 tiles 181 us / 495 tiles 172 us / 575 tiles, a third round, 205 us; 4096 columns as 80 tiles 75 us,
-// as 3 x 80 tiles 39 us.)
-struct TallPlan { int cw, ksplit; double us; };
-TallPlan tall_plan(const hivis_ctx* c, int M, int kblks, int ntiles, bool may_split) {
-    TallPlan best{8, 1, 1e30};
-    const int nrow = (M + TALL_ROWS - 1) / TALL_ROWS;
-    for (int cw = 8; cw >= 6; --cw)
-        for (int S = 1; S <= (may_split ? 8 : 1); ++S) {
-            const int kper = (kblks + S - 1) / S;
-            if (S > 1 && ((S - 1) * kper >= kblks || kper < 8)) continue;        // no empty slice, no tiny ones
-            const double tiles = (double)nrow * ((ntiles + 2 * cw - 1) / (2 * cw)) * S;
-            const double rounds = std::ceil(tiles / c->num_cu), fill = tiles / (rounds * c->num_cu);
-            double us = rounds * (kper * 0.066 * cw * (0.8 + 0.5 * fill) + 7.0);
-            if (S > 1) us += 2.0 * S * M * ntiles * 16 * 4.0 / 4.0e6;
-            if (us < best.us - 1e-9) best = {cw, S, us};
-        }
-    return best;
+// the plan of a GEMM whose K range may be cut into slices, with room for them
+TallPlan sliced_plan(hivis_ctx* c, int M, int K, int N) {
+    TallPlan pl = tall_plan(c->num_cu, M, K / 32, N / 16, true);
+    if (pl.ksplit > 1 && !splitk_space(c, (size_t)pl.ksplit * M * N)) pl = tall_plan(c->num_cu, M, K / 32, N / 16, false);
+    return pl;
 }
 
 template <int EPI>
 int launch_tall(hivis_ctx* c, const TallPlan& pl, const uint4* frag, int M, int K, const uint4* Wp, int N, TallOut o) {
     const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;
-    if (pl.ksplit > 1) { if (int rc = splitk_space(c, (size_t)pl.ksplit * M * o.ldy)) return rc; o.part = c->splitk_ws; }
+    if (pl.ksplit > 1) o.part = c->splitk_ws;
     const int tiles = ((M + TALL_ROWS - 1) / TALL_ROWS) * ((ntiles + 2 * pl.cw - 1) / (2 * pl.cw)) * pl.ksplit;
 #define HIVIS_TALL(CW_)                                                                                                                    \
     hipLaunchKernelGGL((gemm_tall_kernel<CW_, EPI>), dim3(8 * ((tiles + 7) / 8)), dim3(TALL_THREADS), tall_lds_bytes<CW_>(), c->stream,    \
@@ -1061,11 +1065,8 @@ int tall_setup(hivis_ctx* c) {
 int wide_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer) {
     const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;
     const int ncol = (ntiles + 7) / 8;                                  // 8 column tiles per workgroup
-    // about 3 workgroups per CU and at most 16 slices (swept at 61 rows: 256/384/512/768/1024 workgroups, 8/16 slices;
-    // 256-column tiles with half the slices were no faster, at 61 rows and at 32)
-    int S = std::max(1, std::min(16, 3 * c->num_cu / ncol));
-    while (S > 1 && ((S - 1) * ((kblks + S - 1) / S) >= kblks || (kblks + S - 1) / S < 4)) --S;     // no empty slice, >= 4 K blocks each
-    if (S > 1) { if (int rc = splitk_space(c, (size_t)S * M * ldy)) return rc; }
+    int S = wide_slices(c->num_cu, kblks, ntiles);
+    if (S > 1 && !splitk_space(c, (size_t)S * M * ldy)) S = 1;
     float* part = S > 1 ? c->splitk_ws : nullptr;
     if (row_tiles <= 2)      // at most 32 rows: 2 row tiles per workgroup, half the fragment traffic and MFMA work
         hipLaunchKernelGGL((gemm_wide_kernel<1>), dim3(ncol * S), dim3(256), 2 * 12 * 1024, c->stream,
@@ -1083,44 +1084,19 @@ int wide_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, in
 // Any number of rows; the result is *out: K slices, or the one result in Y (row stride N).
 int rows_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, Parts* out) {
     if (M <= MAX_ROWS) return wide_gemm(c, frag, M, K, Wp, N, Y, N, out);
-    const TallPlan pl = tall_plan(c, M, K / 32, N / 16, true);
+    const TallPlan pl = sliced_plan(c, M, K, N);
     TallOut o{}; o.Y = Y; o.ldy = N;
     if (int rc = launch_tall<TALL_STORE>(c, pl, frag, M, K, Wp, N, o)) return rc;
     *out = Parts{pl.ksplit > 1 ? c->splitk_ws : Y, pl.ksplit, (size_t)M * N};
     return HIVIS_OK;
 }
 
-// The q|k|v and the gate|up product end in the GEMM itself (TALL_QKV / TALL_SILU) unless K slices win back more than the row
-// kernel costs (ROW_KERNEL_US: its launch and ramp; its traffic is in the slices' estimate).  At most 64 rows: slices.
-constexpr double ROW_KERNEL_US = 8.0;
-bool tall_fused(const hivis_ctx* c, int M, int kblks, int ntiles, TallPlan* pl) {
+// whether a product of M > 64 rows ends in the GEMM itself (TALL_QKV / TALL_SILU), and its plan then
+bool ends_in_gemm(hivis_ctx* c, int M, int K, int N, TallPlan* pl) {
     if (M <= MAX_ROWS) return false;
-    *pl = tall_plan(c, M, kblks, ntiles, false);
-    return pl->us <= tall_plan(c, M, kblks, ntiles, true).us + ROW_KERNEL_US;
-}
-
-// Room for the K slices of every pass the prefill buffers can hold, at create: growing it inside a request cost its first pass up to
-// 5 ms.  (gemm_wide_kernel: slices x columns <= 3 x CUs x 128, at most 64 rows.)  At most 128 MB, what 1000 rows of 4096 columns
-// in eight slices need: allocating more takes a context longer than it saves, and wider passes grow it.  No room is not an error here.
-void splitk_reserve(hivis_ctx* c) {
-    const hivis_config& g = c->cfg;
-    const int d = g.d, qd = g.n_q_heads * g.head_dim, nqkv = qd + 2 * g.n_kv_heads * g.head_dim, F = g.ffn;
-    size_t need = (size_t)MAX_ROWS * 3 * c->num_cu * 128;
-    const size_t most = (size_t)32 << 20;
-    for (int M = 128; M <= c->pf_rows && need < most; M += 64) {
-        const int K[4] = {d, qd, d, F}, N[4] = {nqkv, d, 2 * F, d};
-        for (int i = 0; i < 4; ++i) {
-            TallPlan pl;
-            if (i % 2 == 0 && tall_fused(c, M, K[i] / 32, N[i] / 16, &pl)) continue;
-            pl = tall_plan(c, M, K[i] / 32, N[i] / 16, true);
-            if (pl.ksplit > 1) need = std::max(need, (size_t)pl.ksplit * M * N[i]);
-        }
-    }
-    need = std::min(need, std::max(most, (size_t)MAX_ROWS * 3 * c->num_cu * 128));
-    void* q = nullptr;
-    if (hipMalloc(&q, need * sizeof(float)) != hipSuccess) { (void)hipGetLastError(); return; }
-    c->allocs.push_back(q);
-    c->splitk_ws = (float*)q; c->splitk_floats = need;
+    *pl = tall_plan(c->num_cu, M, K / 32, N / 16, false);
+    const TallPlan sliced = sliced_plan(c, M, K, N);
+    return sliced.ksplit == 1 || tall_fused(*pl, sliced);
 }
 
 // M = nseq * m rows: q (rotated) to q_out [M][q_dim], k and v of sequence seq0 + s to its cache rows base[seq0 + s] + offset ..
@@ -1131,7 +1107,7 @@ int rows_qkv(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const uint4* frag
     const hivis_config& g = c->cfg;
     const int M = nseq * m, d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, nqkv = qd + 2 * kd, npos = g.max_vis + g.max_text;
     TallPlan pl;
-    if (base == c->zeros && offset == 0 && !tr.pos_delta && tall_fused(c, M, d / 32, nqkv / 16, &pl)) {
+    if (base == c->zeros && offset == 0 && !tr.pos_delta && ends_in_gemm(c, M, d, nqkv, &pl)) {
         TallOut o{};
         o.Y = q_out; o.ldy = qd; o.bias = L.bqkv; o.rope = c->rope_tab; o.npos = npos; o.seq0 = seq0; o.m = m;
         o.qd = qd; o.kd = kd; o.HD = g.head_dim; o.Hkv = g.n_kv_heads; o.maxL = kv.maxL; o.kc = (f16_t*)kv.k; o.vc = (f16_t*)kv.v;
@@ -1149,7 +1125,7 @@ int rows_qkv(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const uint4* frag
 int rows_gateup(hivis_ctx* c, const LayerDev& L, const uint4* frag, int M, float* scratch, uint4* frag_out) {
     const int d = c->cfg.d, F = c->cfg.ffn;
     TallPlan pl;
-    if (tall_fused(c, M, d / 32, 2 * F / 16, &pl)) {
+    if (ends_in_gemm(c, M, d, 2 * F, &pl)) {
         TallOut o{}; o.frag = frag_out; o.kblks_out = F / 32;
         return launch_tall<TALL_SILU>(c, pl, frag, M, d, L.wgu, 2 * F, o);
     }
@@ -1708,7 +1684,7 @@ int build_embed_fc_table(hivis_ctx* c, const hivis_weights* w) {
             uint4* frag = nullptr;
             if ((rc = launch_pack(c, c->pf_x, d, n, d, &frag))) break;
             TallOut o{}; o.Y = table + (size_t)r0 * d; o.ldy = d;
-            rc = launch_tall<TALL_STORE>(c, tall_plan(c, n, d / 32, d / 16, false), frag, n, d, w2p, d, o);
+            rc = launch_tall<TALL_STORE>(c, tall_plan(c->num_cu, n, d / 32, d / 16, false), frag, n, d, w2p, d, o);
         }
         if (rc) break;
         if (hipStreamSynchronize(c->stream) != hipSuccess) { rc = fail(c, HIVIS_EHIP, "building the embedding table of the fusion FC failed"); break; }
@@ -1810,7 +1786,9 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
         if ((rc = dev_alloc(c, &c->pf_gu, (size_t)R * std::max(2 * F, qd + 2 * kd)))) return rc;      // (more rows: finished in the GEMM, or K slices)
         if ((rc = dev_alloc(c, &c->pf_frag, c->pf_sizes.frag / 4))) return rc;      // 4 bytes per value, in 16-byte units
         if ((rc = dev_alloc(c, &c->pf_frag2, c->pf_sizes.frag2 / 4))) return rc;
-        splitk_reserve(c);
+        const char* re = getenv("HIVIS_SPLITK_RESERVE");
+        const size_t reserve = re && atoi(re) >= 0 ? (size_t)atoi(re) << 18 : SPLITK_RESERVE;
+        if (reserve) (void)splitk_alloc(c, std::min(reserve, splitk_most(c)));      // (no room is not an error here)
     }
     if ((rc = dev_alloc(c, &c->logits_v, (size_t)R * V))) return rc;
     if ((rc = dev_alloc(c, &c->logits_d, (size_t)g.k_max * B * V))) return rc;
@@ -1911,6 +1889,7 @@ int hivis_destroy(hivis_ctx* c) {
     if (!c) return HIVIS_OK;
     (void)hipStreamSynchronize(c->stream);
     for (void* p : c->allocs) (void)hipFree(p);
+    (void)hipFree(c->splitk_ws);
     for (auto& kv : c->programs) delete kv.second.host;
     for (hipEvent_t e : c->pev) (void)hipEventDestroy(e);
     if (c->h_result) (void)hipHostFree(c->h_result);

@@ -1,6 +1,7 @@
 // Dense MFMA GEMM of the prefill (hundreds to thousands of activation rows, bf16 weights) and its operand layout.
 #pragma once
 #include "hivis_kernels.h"
+#include "hivis_sizes.h"
 
 namespace hivis {
 
@@ -106,7 +107,7 @@ __device__ __forceinline__ void block_to_lds(const v4u_t* src, v4u_t* lds) {
 // at the head of the multiplication phase took 203 and 107 us; groups owning row halves instead of K blocks (256-row
 // tiles) were no faster at 3008 rows and left too few tiles at 640.
 // ------------------------------------------------------------------------------------------
-constexpr int TALL_THREADS = 512, TALL_ROWS = 128;
+constexpr int TALL_THREADS = 512;
 // (a ring of four K blocks; at the end one area of 64 rows x 64 columns per wavefront)
 template <int CW> constexpr int tall_lds_bytes() { return 4 * (16 + 2 * CW) > 128 ? 4 * (16 + 2 * CW) * 1024 : 128 * 1024; }
 

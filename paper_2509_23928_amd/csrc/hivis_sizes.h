@@ -1,7 +1,8 @@
-// Sizes of the whole-prompt prefill buffers (bf16 models) and which of them holds what.  Host arithmetic only, no HIP: the
-// library sizes and checks with it, and a test compiles it alone.
+// Sizes of the whole-prompt prefill buffers (bf16 models), which of them holds what, and the plans of the GEMMs that fill them.
+// Host arithmetic only, no HIP: the library sizes and checks with it, and a test compiles it alone.
 #pragma once
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 
 namespace hivis {
@@ -30,6 +31,60 @@ inline PrefillSizes prefill_sizes(int d, int qd, int F, int batch, int max_vis, 
 inline int frag_buffer(const PrefillSizes& s, int M, int K) {
     const size_t n = frag_values(M, K);
     return n <= s.frag ? 1 : n <= s.frag2 ? 2 : 0;
+}
+
+// Column tiles per wavefront and K slices of a tall GEMM: the pair with the least estimated time.  A workgroup (one per CU)
+// takes 0.066 us per K block and column tile when it runs alone and about 1.3 times that when all CUs work (the card's
+// power limit), plus 7 us to start and finish; slices cost their partial sums, written once and read once.  (Measured at 640 rows,
+// K = 4096: 22016 columns 430 tiles 181 us / 495 tiles 172 us / 575 tiles, a third round, 205 us; 4096 columns as 80 tiles 75 us,
+// as 3 x 80 tiles 39 us.)
+constexpr int TALL_ROWS = 128;
+struct TallPlan { int cw, ksplit; double us; };
+inline TallPlan tall_plan(int num_cu, int M, int kblks, int ntiles, bool may_split) {
+    TallPlan best{8, 1, 1e30};
+    const int nrow = (M + TALL_ROWS - 1) / TALL_ROWS;
+    for (int cw = 8; cw >= 6; --cw)
+        for (int S = 1; S <= (may_split ? 8 : 1); ++S) {
+            const int kper = (kblks + S - 1) / S;
+            if (S > 1 && ((S - 1) * kper >= kblks || kper < 8)) continue;        // no empty slice, no tiny ones
+            const double tiles = (double)nrow * ((ntiles + 2 * cw - 1) / (2 * cw)) * S;
+            const double rounds = std::ceil(tiles / num_cu), fill = tiles / (rounds * num_cu);
+            double us = rounds * (kper * 0.066 * cw * (0.8 + 0.5 * fill) + 7.0);
+            if (S > 1) us += 2.0 * S * M * ntiles * 16 * 4.0 / 4.0e6;
+            if (us < best.us - 1e-9) best = {cw, S, us};
+        }
+    return best;
+}
+
+// The q|k|v and the gate|up product end in the GEMM itself unless K slices win back more than the row kernel costs
+// (ROW_KERNEL_US: its launch and ramp; its traffic is in the slices' estimate).  At most 64 rows: slices.
+constexpr double ROW_KERNEL_US = 8.0;
+inline bool tall_fused(const TallPlan& whole, const TallPlan& sliced) { return whole.us <= sliced.us + ROW_KERNEL_US; }
+
+// K slices of a GEMM of at most 64 rows: about 3 workgroups of 8 column tiles per CU and at most 16 slices (swept at 61 rows:
+// 256/384/512/768/1024 workgroups, 8/16 slices; 256-column tiles with half the slices were no faster, at 61 rows and at 32)
+inline int wide_slices(int num_cu, int kblks, int ntiles) {
+    int S = std::max(1, std::min(16, 3 * num_cu / ((ntiles + 7) / 8)));
+    while (S > 1 && ((S - 1) * ((kblks + S - 1) / S) >= kblks || (kblks + S - 1) / S < 4)) --S;     // no empty slice, >= 4 K blocks each
+    return S;
+}
+
+// Floats that hold the K slices of every product of a context: the most that a pass of up to 64 rows needs (slices x column
+// blocks <= 3 per CU), and that a prefill of up to `rows` rows needs.  A plan depends on the row count through whole row blocks, and
+// inside a block the more rows, the fewer slices: the slices of a block's first row count, times its last, bound all of it.
+inline size_t splitk_floats(int num_cu, int d, int qd, int kd, int F, int rows) {
+    size_t need = (size_t)MAX_ROWS * 3 * num_cu * 128;
+    const int K[6] = {d, qd, d, F, d, 2 * d}, N[6] = {qd + 2 * kd, d, 2 * F, d, d, d};      // q|k|v, O, gate|up, down, fusion FC
+    for (int r0 = MAX_ROWS + 1; r0 <= rows; r0 = (r0 - 1) / TALL_ROWS * TALL_ROWS + TALL_ROWS + 1) {
+        const int r1 = std::min(rows, (r0 - 1) / TALL_ROWS * TALL_ROWS + TALL_ROWS);
+        for (int i = 0; i < 6; ++i) {
+            const TallPlan sliced = tall_plan(num_cu, r0, K[i] / 32, N[i] / 16, true);
+            if (sliced.ksplit == 1) continue;
+            if ((i == 0 || i == 2) && tall_fused(tall_plan(num_cu, r0, K[i] / 32, N[i] / 16, false), sliced)) continue;
+            need = std::max(need, (size_t)sliced.ksplit * r1 * N[i]);
+        }
+    }
+    return need;
 }
 
 }  // namespace hivis

@@ -1,5 +1,6 @@
-"""The prefill buffers are also the operand buffers of the 11..64-row passes: whatever a pass packs has to fit the buffer it
-is sent to, down to the smallest context that takes such a pass (64 rows of room)."""
+"""Host arithmetic of the buffers of bf16 models.  The prefill buffers are also the operand buffers of the 11..64-row passes:
+whatever a pass packs has to fit the buffer it is sent to, down to the smallest context that takes such a pass (64 rows of room).
+And the room for K slices covers every row count, so that it grows at most once."""
 import itertools
 
 import pytest
@@ -17,6 +18,27 @@ extern "C" long over(int d, int qd, int F, int B, int vis, int text, int M, int 
     if (!which) return -1;
     const size_t room = which == 1 ? s.frag : s.frag2, need = frag_values(M, K);
     return need <= room ? 0 : (long)((need - room + K - 1) / K);
+}
+// most floats of K slices over all row counts of a prefill pass, as the passes choose them, beyond what splitk_floats says
+extern "C" long slices_over(int cu, int d, int qd, int kd, int F, int rows) {
+    const size_t room = splitk_floats(cu, d, qd, kd, F, rows);
+    const int K[6] = {d, qd, d, F, d, 2 * d}, N[6] = {qd + 2 * kd, d, 2 * F, d, d, d};
+    long over = 0;
+    for (int M = 65; M <= rows; ++M)
+        for (int i = 0; i < 6; ++i) {
+            const TallPlan sliced = tall_plan(cu, M, K[i] / 32, N[i] / 16, true), whole = tall_plan(cu, M, K[i] / 32, N[i] / 16, false);
+            if (sliced.ksplit == 1 || ((i == 0 || i == 2) && tall_fused(whole, sliced))) continue;
+            over = std::max(over, (long)sliced.ksplit * M * N[i] - (long)room);
+        }
+    return over;
+}
+extern "C" long wide_over(int cu, int K, int N) {
+    long over = 0;
+    for (int M = 1; M <= 64; ++M) {
+        const int S = wide_slices(cu, K / 32, N / 16);
+        if (S > 1) over = std::max(over, (long)S * M * N - (long)splitk_floats(cu, 64, 64, 64, 64, 64));
+    }
+    return over;
 }
 """
 
@@ -49,3 +71,14 @@ def test_packed_rows_fit(lib, widths):
 
 def test_refuses_what_fits_nowhere(lib):
     assert lib.over(256, 256, 1024, 1, 32, 32, 65, 1024) == -1
+
+
+@pytest.mark.parametrize("widths", WIDTHS, ids=str)
+@pytest.mark.parametrize("cu", [256, 64])
+def test_room_for_every_slice(lib, widths, cu):
+    d, qd, F = widths
+    for kd in {64, qd}:
+        for rows in (64, 129, 640, 3008, 4096):
+            assert lib.slices_over(cu, d, qd, kd, F, rows) <= 0, (kd, rows)
+    for K, N in itertools.product({d, 2 * d, qd, F}, {d, 2 * F, 3 * qd, 32000, 152064, 528}):
+        assert lib.wide_over(cu, K, N) <= 0, (K, N)

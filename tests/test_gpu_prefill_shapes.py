@@ -68,3 +68,25 @@ def test_widths(kw):
                          ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
 def test_shared_attention(kw):
     check_prefill(cfg_of(**kw))
+
+
+def test_room_for_slices_grows_once(monkeypatch):
+    """Without a reserve the first product that is cut into K slices allocates the room, for every row count of the context: the
+    prompts after it, more and fewer rows, find it there."""
+    import torch
+    from paper_2509_23928_amd import Hivis
+    monkeypatch.setenv("HIVIS_SPLITK_RESERVE", "0")
+    cfg = cfg_of(n_vis=700, n_text=33, d=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, ffn=2720, gen_cycles=4)
+    w = synth.make_weights(cfg, seed=2)
+    vis, ids = synth.make_prompt(cfg, seed=2)
+    hv = Hivis(cfg, w)
+    free = []
+    for v, l in ((90, 33), (700, 33), (0, 20), (700, 11), (401, 9)):
+        first = hv.prefill(vis[:, :v], ids[:, :l])
+        free.append(torch.cuda.mem_get_info()[0])
+        o = HivisOracle(cfg, w)
+        x, ref = o.prefill(vis[0, :v], ids[0, :l])
+        assert rel(hv.get_logits(2)[0], ref) <= REL and int(first[0]) == x
+        assert rel(hv.get_hidden(1)[0], o.f_next) <= REL
+    hv.close()
+    assert len(set(free)) == 1, free
