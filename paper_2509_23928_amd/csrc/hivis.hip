@@ -92,6 +92,7 @@ struct hivis_ctx {
     // whole-prompt prefill buffers (bf16 models): all v+l rows of one or several sequences per layer
     int pf_rows = 0;
     hivis::PrefillSizes pf_sizes{};
+    int tall_cw = 0;
     float *pf_x = nullptr, *pf_xt = nullptr, *pf_a = nullptr, *pf_qkv = nullptr, *pf_att = nullptr, *pf_proj = nullptr, *pf_gu = nullptr;
     uint4 *pf_frag = nullptr, *pf_frag2 = nullptr;      // activation fragments: of d / q_dim wide rows, and of the MLP's inner rows
     std::vector<int32_t> h_ids;
@@ -1031,8 +1032,8 @@ int launch_pack(hivis_ctx* c, const float* A, int lda, int M, int K, uint4** out
 
 // the plan of a GEMM whose K range may be cut into slices, with room for them
 TallPlan sliced_plan(hivis_ctx* c, int M, int K, int N) {
-    TallPlan pl = tall_plan(c->num_cu, M, K / 32, N / 16, true);
-    if (pl.ksplit > 1 && !splitk_space(c, (size_t)pl.ksplit * M * N)) pl = tall_plan(c->num_cu, M, K / 32, N / 16, false);
+    TallPlan pl = tall_plan(c->num_cu, M, K / 32, N / 16, true, c->tall_cw);
+    if (pl.ksplit > 1 && !splitk_space(c, (size_t)pl.ksplit * M * N)) pl = tall_plan(c->num_cu, M, K / 32, N / 16, false, c->tall_cw);
     return pl;
 }
 
@@ -1094,7 +1095,7 @@ int rows_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, in
 // whether a product of M > 64 rows ends in the GEMM itself (TALL_QKV / TALL_SILU), and its plan then
 bool ends_in_gemm(hivis_ctx* c, int M, int K, int N, TallPlan* pl) {
     if (M <= MAX_ROWS) return false;
-    *pl = tall_plan(c->num_cu, M, K / 32, N / 16, false);
+    *pl = tall_plan(c->num_cu, M, K / 32, N / 16, false, c->tall_cw);
     const TallPlan sliced = sliced_plan(c, M, K, N);
     return sliced.ksplit == 1 || tall_fused(*pl, sliced);
 }
@@ -1786,6 +1787,8 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
         if ((rc = dev_alloc(c, &c->pf_gu, (size_t)R * std::max(2 * F, qd + 2 * kd)))) return rc;      // (more rows: finished in the GEMM, or K slices)
         if ((rc = dev_alloc(c, &c->pf_frag, c->pf_sizes.frag / 4))) return rc;      // 4 bytes per value, in 16-byte units
         if ((rc = dev_alloc(c, &c->pf_frag2, c->pf_sizes.frag2 / 4))) return rc;
+        // HIVIS_TALL_CW=6, 7 or 8: prefill GEMMs in tiles of 192, 224 or 256 columns only
+        if (const char* ce = getenv("HIVIS_TALL_CW")) { const int cw = atoi(ce); if (cw >= 6 && cw <= 8) c->tall_cw = cw; }
         const char* re = getenv("HIVIS_SPLITK_RESERVE");
         const size_t reserve = re && atoi(re) >= 0 ? (size_t)atoi(re) << 18 : SPLITK_RESERVE;
         if (reserve) (void)splitk_alloc(c, std::min(reserve, splitk_most(c)));      // (no room is not an error here)

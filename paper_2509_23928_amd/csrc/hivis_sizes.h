@@ -37,13 +37,13 @@ inline int frag_buffer(const PrefillSizes& s, int M, int K) {
 // takes 0.066 us per K block and column tile when it runs alone and about 1.3 times that when all CUs work (the card's
 // power limit), plus 7 us to start and finish; slices cost their partial sums, written once and read once.  (Measured at 640 rows,
 // K = 4096: 22016 columns 430 tiles 181 us / 495 tiles 172 us / 575 tiles, a third round, 205 us; 4096 columns as 80 tiles 75 us,
-// as 3 x 80 tiles 39 us.)
+// as 3 x 80 tiles 39 us.)  only: 6..8, that many column tiles (0: any).
 constexpr int TALL_ROWS = 128;
 struct TallPlan { int cw, ksplit; double us; };
-inline TallPlan tall_plan(int num_cu, int M, int kblks, int ntiles, bool may_split) {
+inline TallPlan tall_plan(int num_cu, int M, int kblks, int ntiles, bool may_split, int only = 0) {
     TallPlan best{8, 1, 1e30};
     const int nrow = (M + TALL_ROWS - 1) / TALL_ROWS;
-    for (int cw = 8; cw >= 6; --cw)
+    for (int cw = only ? only : 8; cw >= (only ? only : 6); --cw)
         for (int S = 1; S <= (may_split ? 8 : 1); ++S) {
             const int kper = (kblks + S - 1) / S;
             if (S > 1 && ((S - 1) * kper >= kblks || kper < 8)) continue;        // no empty slice, no tiny ones
