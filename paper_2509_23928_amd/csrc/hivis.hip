@@ -117,7 +117,7 @@ struct hivis_ctx {
     int vrows = 0;                                        // rows of the last verify pass (chain: B*(K+1); tree: N+1)
     float *tH = nullptr, *tlogits = nullptr, *tcat = nullptr, *troll = nullptr;
     int32_t* ttok_rows = nullptr;                         // tokens of a level's rows
-    float* tree_pool[17] = {};                            // buffers of tree_rows_program by row count (allocated at first use)
+    float* tree_pool = nullptr;                           // buffers of tree_rows_program
     float *tcand_v = nullptr, *tseg = nullptr; int32_t* tcand_i = nullptr; int tnseg = 0;   // per-segment top-k candidates and (max, sum) partials   // hidden rows, their logits, level inputs, re-feed inputs
     void** kv_ptrs = nullptr; void* kv_staging = nullptr;
     float* splitk_ws = nullptr; size_t splitk_floats = 0;      // K-slice partials (splitk_space)
@@ -731,7 +731,7 @@ int get_program(hivis_ctx* c, int kind, int K, hivis_ctx::Program* out) {
     build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect);           // sizes only
     Pool pool;
     if (int rc = dev_alloc(c, &pool.base, count.used)) return rc;
-    HIP_TRY(c, hipMemset(pool.base, 0, count.used * sizeof(float)));
+    HIP_TRY(c, hipMemsetAsync(pool.base, 0, count.used * sizeof(float), c->stream));      // (on the stream of the passes that count on it)
     P.clear();
     build_phases<WT>(c, kind, K, pool, P, c->persistent, c->attn_elect);
     hivis_ctx::Program pg;
@@ -1450,6 +1450,59 @@ int do_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool sample) {
 
 
 // ---- draft tree (batch 1) ---------------------------------------------------------------------------
+PassParams tree_pass(const hivis_ctx* c, int m) {
+    const hivis_config& g = c->cfg;
+    PassParams pp{};
+    pp.M = m; pp.nseq = 1; pp.m = m; pp.d = g.d; pp.Hq = g.n_q_heads; pp.Hkv = g.n_kv_heads; pp.hd = g.head_dim; pp.F = g.ffn; pp.V = g.vocab;
+    pp.eps = g.rms_eps; pp.theta = g.rope_theta; pp.inv_temp = c->inv_temp; pp.bar = c->bar; pp.bad = c->bad; pp.spin_limit = 1u << 22;
+    return pp;
+}
+
+// m <= 16 rows of a draft tree (or of its re-feed) through the fusion FC + rho_idx and the drafter's layer as a phase list, one launch per
+// phase: inputs cat [m][2d] = hidden row | embedding and the rows' tokens (tok); layer output to out [m][d]; lm_out (optional): its
+// logits.  The lists of all row counts lie in one pool, tree_pool: the passes of a call follow each other on the stream.  The
+// attention's arrival counters (zero between launches) are its first words for every row count, so no list's rows overwrite them.
+template <typename WT>
+void tree_rows_phases(hivis_ctx* c, int m, const float* cat, const int32_t* tok, int rho_idx, int offset, TreeRows tr, float* out, float* lm_out,
+                      Pool& pool, std::vector<Phase>& P) {
+    const hivis_config& g = c->cfg;
+    const int d = g.d, V = g.vocab;
+    int* counters = (int*)pool.take(2 * g.n_q_heads);          // at most two row blocks of 8 per head
+    float* u = pool.take((size_t)m * d);
+    Phase fu{}; fu.type = PH_GEMM; fu.pro = PRO_PLAIN; fu.epi = FEPI_ADDVEC; fu.K = 2 * d; fu.N = d; fu.W = c->fuse_w; fu.A = cat; fu.lda = 2 * d;
+    fu.Y = u; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = rho_idx;
+    if (c->emb_w2) { fu.add_rows = c->emb_w2; fu.K = d; fu.W = c->fuse_w1; fu.tok = tok; fu.tok_sseq = 0; fu.tok_srow = 1; }      // embedding half from the table
+    P.push_back(fu);
+    const size_t l0 = P.size();
+    int ld = d;
+    layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, offset, 1, m, out, d, &ld, false, c->attn_elect);
+    for (size_t i = l0; i < P.size(); ++i) {
+        P[i].pos_delta = tr.pos_delta; P[i].att.tmask = tr.mask;
+        if (P[i].type == PH_ATTN && c->attn_elect) P[i].cnt = counters;
+    }
+    float* pm = pool.take((size_t)m * c->fused_grid); int* pi = (int*)pool.take((size_t)m * c->fused_grid);
+    if (lm_out) {
+        Phase lm{}; lm.type = PH_GEMM; lm.pro = PRO_PLAIN; lm.epi = FEPI_LOGITS; lm.K = d; lm.N = V; lm.W = c->lm_head; lm.A = out; lm.lda = d;
+        lm.Y = lm_out; lm.ldy = V; lm.pm = pm; lm.pi = pi;
+        P.push_back(lm);
+    }
+}
+// the phase attention of fp32 models takes no ancestor mask: those keep the stand-alone kernels
+template <typename WT>
+bool tree_program_ok(const hivis_ctx* c, int m) { return sizeof(WT) == 2 && c->fused && !c->persistent && m <= WTraits<bf16w_t>::ROWS; }
+
+template <typename WT>
+int tree_rows_program(hivis_ctx* c, int m, const float* cat, const int32_t* tok, int rho_idx, int offset, TreeRows tr, float* out, float* lm_out) {
+    std::vector<Phase> P;
+    Pool pool; pool.base = c->tree_pool;
+    tree_rows_phases<WT>(c, m, cat, tok, rho_idx, offset, tr, out, lm_out, pool, P);
+    const PassParams pp = tree_pass(c, m);
+    if constexpr (std::is_same<WT, bf16_t>::value) {
+        if (m > WTraits<WT>::ROWS || tr.pos_delta) return launch_phases<bf16w_t>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
+    }
+    return launch_phases<WT>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
+}
+
 // Device arrays of the tree, sized for the library's limits, allocated on the first tree call.
 template <typename WT>
 int tree_setup(hivis_ctx* c) {
@@ -1494,63 +1547,21 @@ int tree_setup(hivis_ctx* c) {
     HIP_TRY(c, hipMemsetAsync(t.ttok, 0, R * sizeof(*t.ttok), c->stream)); HIP_TRY(c, hipMemsetAsync(t.path, 0, (D + 1) * sizeof(*t.path), c->stream));
     HIP_TRY(c, hipMemsetAsync(t.next_tok, 0, (D + 1) * sizeof(*t.next_tok), c->stream)); HIP_TRY(c, hipMemsetAsync(t.result, 0, (D + 2) * sizeof(*t.result), c->stream));
     HIP_TRY(c, hipMemsetAsync(t.dmask, 0, R * sizeof(*t.dmask), c->stream)); HIP_TRY(c, hipMemsetAsync(t.dpos, 0, R * sizeof(*t.dpos), c->stream));
-    HIP_TRY(c, hipMemsetAsync(t.vmask, 0, R * sizeof(*t.vmask), c->stream));
+    HIP_TRY(c, hipMemsetAsync(t.vmask, 0, R * sizeof(*t.vmask), c->stream)); HIP_TRY(c, hipMemsetAsync(c->ttok_rows, 0, TREE_MAX_TOPK * sizeof(int32_t), c->stream));
+    if (tree_program_ok<WT>(c, 1)) {
+        size_t most = 0;
+        for (int m = 1; tree_program_ok<WT>(c, m); ++m) {
+            std::vector<Phase> P;
+            Pool count;
+            tree_rows_phases<WT>(c, m, nullptr, nullptr, 0, 0, TreeRows(), nullptr, nullptr, count, P);
+            most = std::max(most, count.used);
+        }
+        if ((rc = dev_alloc(c, &c->tree_pool, most))) return rc;
+        HIP_TRY(c, hipMemsetAsync(c->tree_pool, 0, most * sizeof(float), c->stream));          // (the arrival counters start at zero)
+    }
     c->tree_ready = true;
     return HIVIS_OK;
 }
-
-PassParams tree_pass(const hivis_ctx* c, int m) {
-    const hivis_config& g = c->cfg;
-    PassParams pp{};
-    pp.M = m; pp.nseq = 1; pp.m = m; pp.d = g.d; pp.Hq = g.n_q_heads; pp.Hkv = g.n_kv_heads; pp.hd = g.head_dim; pp.F = g.ffn; pp.V = g.vocab;
-    pp.eps = g.rms_eps; pp.theta = g.rope_theta; pp.inv_temp = c->inv_temp; pp.bar = c->bar; pp.bad = c->bad; pp.spin_limit = 1u << 22;
-    return pp;
-}
-
-// m <= 16 rows of a draft tree (or of its re-feed) through the fusion FC + rho_idx and the drafter's layer as a phase list, one launch per
-// phase: inputs cat [m][2d] = hidden row | embedding and the rows' tokens (tok); layer output to out [m][d]; lm_out (optional): its
-// logits.  The list's buffers are one pool per row count, kept: the passes of a call follow each other on the stream.
-template <typename WT>
-int tree_rows_program(hivis_ctx* c, int m, const float* cat, const int32_t* tok, int rho_idx, int offset, TreeRows tr, float* out, float* lm_out) {
-    const hivis_config& g = c->cfg;
-    const int d = g.d, V = g.vocab;
-    auto build = [&](Pool& pool, std::vector<Phase>& P) {
-        float* u = pool.take((size_t)m * d);
-        Phase fu{}; fu.type = PH_GEMM; fu.pro = PRO_PLAIN; fu.epi = FEPI_ADDVEC; fu.K = 2 * d; fu.N = d; fu.W = c->fuse_w; fu.A = cat; fu.lda = 2 * d;
-        fu.Y = u; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = rho_idx;
-        if (c->emb_w2) { fu.add_rows = c->emb_w2; fu.K = d; fu.W = c->fuse_w1; fu.tok = tok; fu.tok_sseq = 0; fu.tok_srow = 1; }      // embedding half from the table
-        P.push_back(fu);
-        const size_t l0 = P.size();
-        int ld = d;
-        layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, offset, 1, m, out, d, &ld, false, c->attn_elect);
-        for (size_t i = l0; i < P.size(); ++i) { P[i].pos_delta = tr.pos_delta; P[i].att.tmask = tr.mask; }
-        float* pm = pool.take((size_t)m * c->fused_grid); int* pi = (int*)pool.take((size_t)m * c->fused_grid);
-        if (lm_out) {
-            Phase lm{}; lm.type = PH_GEMM; lm.pro = PRO_PLAIN; lm.epi = FEPI_LOGITS; lm.K = d; lm.N = V; lm.W = c->lm_head; lm.A = out; lm.lda = d;
-            lm.Y = lm_out; lm.ldy = V; lm.pm = pm; lm.pi = pi;
-            P.push_back(lm);
-        }
-    };
-    float*& base = c->tree_pool[m];
-    if (!base) {
-        std::vector<Phase> sizes;
-        Pool count;
-        build(count, sizes);
-        if (int rc = dev_alloc(c, &base, count.used)) return rc;
-        HIP_TRY(c, hipMemset(base, 0, count.used * sizeof(float)));            // (the arrival counters start at zero)
-    }
-    std::vector<Phase> P;
-    Pool pool; pool.base = base;
-    build(pool, P);
-    const PassParams pp = tree_pass(c, m);
-    if constexpr (std::is_same<WT, bf16_t>::value) {
-        if (m > WTraits<WT>::ROWS || tr.pos_delta) return launch_phases<bf16w_t>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
-    }
-    return launch_phases<WT>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
-}
-// the phase attention of fp32 models takes no ancestor mask: those keep the stand-alone kernels
-template <typename WT>
-bool tree_program_ok(const hivis_ctx* c, int m) { return sizeof(WT) == 2 && c->fused && !c->persistent && m <= WTraits<bf16w_t>::ROWS; }
 
 // Pool of k + (depth-1) k^2 nodes, level by level; then the N best-scored candidates and their verify rows.
 template <typename WT>

@@ -254,6 +254,18 @@ def test_tree_without_phase_programs(monkeypatch):
     print("stand-alone tree max error / tolerance:", t.max_err, "accepted:", t.n_hist)
 
 
+def test_tree_calls_allocate_once():
+    """What a tree call keeps on the device is there from the first one on, whatever the sizes of the later ones."""
+    import torch
+    cfg = small_bf16()
+    t = TreeSideBySide(cfg, 7)
+    t.cycle(2, 2, 4)
+    free = torch.cuda.mem_get_info()[0]
+    for k, depth in [(3, 3), (16, 2), (8, 5), (10, 6), (4, 16), (9, 4), (5, 9), (12, 4), (7, 7), (15, 3), (11, 5)]:
+        t.cycle(k, depth, min(12, k + (depth - 1) * k * k))
+    assert torch.cuda.mem_get_info()[0] == free
+
+
 def test_tree_error_codes():
     from paper_2509_23928_amd import Hivis, HivisError, HIVIS_EINVAL, HIVIS_ESTATE, HIVIS_ECAP
     cfg = c1(n_vis=8, n_text=9)
