@@ -380,11 +380,8 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
             const int items = nseq * g.n_q_heads * sh.n_rblk;
             const size_t lds = attn_shared_lds_bytes(g.head_dim);
 #define HIVIS_SHARED(HD_, NW_)                                                                                                             \
-    do {                                                                                                                                   \
-        if (lds > 64 * 1024) HIP_TRY(c, hipFuncSetAttribute((const void*)attn_rows_shared_kernel<HD_, NW_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-        hipLaunchKernelGGL((attn_rows_shared_kernel<HD_, NW_>), dim3(items), dim3(64 * NW_), lds, c->stream, q, (const f16_t*)kv.k,        \
-                           (const f16_t*)kv.v, base, sh, ldo, frag_out);                                                                   \
-    } while (0)
+    hipLaunchKernelGGL((attn_rows_shared_kernel<HD_, NW_>), dim3(items), dim3(64 * NW_), lds, c->stream, q, (const f16_t*)kv.k,            \
+                       (const f16_t*)kv.v, base, sh, ldo, frag_out)
             if (g.head_dim == 128) { if (large) HIVIS_SHARED(128, 8); else HIVIS_SHARED(128, 4); }
             else { if (large) HIVIS_SHARED(64, 8); else HIVIS_SHARED(64, 4); }
 #undef HIVIS_SHARED
@@ -810,7 +807,8 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                 HIVIS_LAUNCH(PH_GEMM, FEPI_QKV);
                 break;
             case FEPI_SILU: HIVIS_LAUNCH(PH_GEMM, FEPI_SILU); break;
-            default: HIVIS_LAUNCH(PH_GEMM, FEPI_LOGITS); break;
+            case FEPI_LOGITS: HIVIS_LAUNCH(PH_GEMM, FEPI_LOGITS); break;
+            default: return fail(c, HIVIS_EINVAL, "phase %d: no kernel for epilogue %d", p, ph.epi);
             }
             break;
         case PH_ATTN: HIVIS_LAUNCH(PH_ATTN, 0); break;
@@ -818,7 +816,8 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         case PH_PREP: HIVIS_LAUNCH(PH_PREP, 0); break;
         case PH_NORM_ROWS: HIVIS_LAUNCH(PH_NORM_ROWS, 0); break;
         case PH_SAMPLE: HIVIS_LAUNCH(PH_SAMPLE, 0); break;
-        default: HIVIS_LAUNCH(PH_ARGMAX, 0); break;
+        case PH_ARGMAX: HIVIS_LAUNCH(PH_ARGMAX, 0); break;
+        default: return fail(c, HIVIS_EINVAL, "phase %d: unknown type %d", p, ph.type);
         }
 #undef HIVIS_LAUNCH
     }
@@ -1052,12 +1051,16 @@ int launch_tall(hivis_ctx* c, const TallPlan& pl, const uint4* frag, int M, int 
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
-// these kernels use more LDS than a launch gets without asking
-template <int EPI>
-int tall_setup(hivis_ctx* c) {
-    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<8, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<8>()));
-    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<7, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<7>()));
-    HIP_TRY(c, hipFuncSetAttribute((const void*)gemm_tall_kernel<6, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, tall_lds_bytes<6>()));
+// the whole-prompt kernels that use more LDS than a launch gets without asking
+int prefill_lds_setup(hivis_ctx* c) {
+    struct { const void* k; size_t bytes; } ks[] = {
+#define HIVIS_TALL_LDS(EPI_) {(const void*)gemm_tall_kernel<8, EPI_>, (size_t)tall_lds_bytes<8>()}, {(const void*)gemm_tall_kernel<7, EPI_>, (size_t)tall_lds_bytes<7>()}, \
+                             {(const void*)gemm_tall_kernel<6, EPI_>, (size_t)tall_lds_bytes<6>()}
+        HIVIS_TALL_LDS(TALL_STORE), HIVIS_TALL_LDS(TALL_SILU), HIVIS_TALL_LDS(TALL_QKV),
+#undef HIVIS_TALL_LDS
+        {(const void*)attn_rows_shared_kernel<128, 8>, attn_shared_lds_bytes(128)}, {(const void*)attn_rows_shared_kernel<128, 4>, attn_shared_lds_bytes(128)},
+        {(const void*)attn_rows_shared_kernel<64, 8>, attn_shared_lds_bytes(64)}, {(const void*)attn_rows_shared_kernel<64, 4>, attn_shared_lds_bytes(64)}};
+    for (const auto& k : ks) HIP_TRY(c, hipFuncSetAttribute(k.k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.bytes));
     return HIVIS_OK;
 }
 
@@ -1295,19 +1298,21 @@ int do_prefill(hivis_ctx* c, const void* vis_embeds, int v, const int32_t* text_
     if (c->bar) hipLaunchKernelGGL(set_ints_kernel, dim3(1), dim3(64), 0, c->stream, (int*)c->bar, 2, 0);
 
     const int total = v + l;
-    const bool tall = sizeof(WT) == 2;                       // bf16 models: whole prompts; else chunks of the decode passes' size
-    const int per = tall ? std::max(1, std::min(B, c->pf_rows / total)) : 1;
-    if constexpr (sizeof(WT) == 2)
+    // bf16 models: whole prompts, as many sequences at a time as the buffers hold; fp32: chunks of the decode passes' size
+    [[maybe_unused]] const int per = std::max(1, std::min(B, c->pf_rows / total));
+    if constexpr (sizeof(WT) == 2) {
         for (int b = 0; b < B; b += per)
             if (int rc = prefill_target_tall<WT>(c, b, std::min(per, B - b), v, l)) return rc;
-    for (int b = 0; b < B && !tall; ++b) {
-        for (int p0 = 0; p0 < total; p0 += CHAIN_MAX_ROWS) {
-            const int m = std::min(CHAIN_MAX_ROWS, total - p0);
-            hipLaunchKernelGGL((prefill_rows_kernel<WT>), dim3(m), dim3(256), 0, c->stream, (const WT*)c->vis + (size_t)b * g.max_vis * d, (size_t)0, v,
-                               (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), 0, p0, c->x, d);
-            const int first_out = std::max(0, v - p0);       // rows of this chunk before the first text row produce no feature
-            float* out = c->feat + ((size_t)b * g.max_text + std::max(0, p0 - v)) * d;
-            if (int rc = target_forward<WT>(c, b, 1, m, c->zeros, p0, p0 + m, out, d, std::min(first_out, m))) return rc;
+    } else {
+        for (int b = 0; b < B; ++b) {
+            for (int p0 = 0; p0 < total; p0 += CHAIN_MAX_ROWS) {
+                const int m = std::min(CHAIN_MAX_ROWS, total - p0);
+                hipLaunchKernelGGL((prefill_rows_kernel<WT>), dim3(m), dim3(256), 0, c->stream, (const WT*)c->vis + (size_t)b * g.max_vis * d, (size_t)0, v,
+                                   (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), 0, p0, c->x, d);
+                const int first_out = std::max(0, v - p0);       // rows of this chunk before the first text row produce no feature
+                float* out = c->feat + ((size_t)b * g.max_text + std::max(0, p0 - v)) * d;
+                if (int rc = target_forward<WT>(c, b, 1, m, c->zeros, p0, p0 + m, out, d, std::min(first_out, m))) return rc;
+            }
         }
     }
     hipLaunchKernelGGL(set_ints_kernel, dim3(1), dim3(64), 0, c->stream, c->tlen, B, total);
@@ -1316,17 +1321,19 @@ int do_prefill(hivis_ctx* c, const void* vis_embeds, int v, const int32_t* text_
     if (sample) hipLaunchKernelGGL(sample_rows_kernel, dim3(B), dim3(SAMPLE_NT), 0, c->stream, (const float*)c->logits_p, g.vocab, c->inv_temp, (const float*)c->u_res, 1, c->text + l, c->text_stride);
     else launch_argmax(c, c->logits_p, B, c->text + l, 1, c->text_stride);
     // drafter prefill over the l text positions: rows [f^j ; Embed(x_{j+1})] + rho_0
-    if constexpr (sizeof(WT) == 2)
+    if constexpr (sizeof(WT) == 2) {
         for (int b = 0; b < B; b += per)
             if (int rc = prefill_drafter_tall<WT>(c, b, std::min(per, B - b), l)) return rc;
-    for (int b = 0; b < B && !tall; ++b) {
-        for (int j0 = 0; j0 < l; j0 += CHAIN_MAX_ROWS) {
-            const int m = std::min(CHAIN_MAX_ROWS, l - j0);
-            hipLaunchKernelGGL((fuse_rows_kernel<WT>), dim3(m), dim3(256), 0, c->stream, (const float*)(c->feat + (size_t)b * g.max_text * d),
-                               (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), j0, c->catT, d);
-            if (int rc = drafter_forward<WT>(c, c->catT, b, 1, m, 0, j0, j0 + m, c->dout, d)) return rc;
-            if (j0 + m == l)   // f'_1: drafter output at the last true-feature row
-                hipLaunchKernelGGL(copy_rows_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)(c->dout + (size_t)(m - 1) * d), d, c->catD + (size_t)b * 2 * d, 2 * d, d);
+    } else {
+        for (int b = 0; b < B; ++b) {
+            for (int j0 = 0; j0 < l; j0 += CHAIN_MAX_ROWS) {
+                const int m = std::min(CHAIN_MAX_ROWS, l - j0);
+                hipLaunchKernelGGL((fuse_rows_kernel<WT>), dim3(m), dim3(256), 0, c->stream, (const float*)(c->feat + (size_t)b * g.max_text * d),
+                                   (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b * c->text_stride), j0, c->catT, d);
+                if (int rc = drafter_forward<WT>(c, c->catT, b, 1, m, 0, j0, j0 + m, c->dout, d)) return rc;
+                if (j0 + m == l)   // f'_1: drafter output at the last true-feature row
+                    hipLaunchKernelGGL(copy_rows_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)(c->dout + (size_t)(m - 1) * d), d, c->catD + (size_t)b * 2 * d, 2 * d, d);
+            }
         }
     }
     hipLaunchKernelGGL(set_ints_kernel, dim3(1), dim3(64), 0, c->stream, c->dlen, B, l);
@@ -1786,7 +1793,7 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     if ((rc = dev_alloc(c, &c->dout, (size_t)R * d))) return rc;
     if ((rc = dev_alloc(c, &c->feat, (size_t)B * g.max_text * d))) return rc;
     if (sizeof(WT) == 2) {
-        if ((rc = tall_setup<TALL_STORE>(c)) || (rc = tall_setup<TALL_SILU>(c)) || (rc = tall_setup<TALL_QKV>(c))) return rc;
+        if ((rc = prefill_lds_setup(c))) return rc;
         c->pf_sizes = prefill_sizes(d, qd, F, B, g.max_vis, g.max_text);
         const int PR = c->pf_sizes.rows;
         c->pf_rows = PR;

@@ -25,7 +25,7 @@ namespace hivis {
 enum { PH_GEMM = 0, PH_ATTN = 1, PH_ATTN_MERGE = 2, PH_PREP = 3, PH_NORM_ROWS = 4, PH_ARGMAX = 5, PH_SAMPLE = 6 };
 enum { PRO_PLAIN = 0, PRO_RMS = 1 };
 constexpr int FUSED_RMAX = 8;      // (head,row) pairs per attention work item in the persistent kernel
-enum { FEPI_STORE = 0, FEPI_ADD_TO = 1, FEPI_ADDVEC = 2, FEPI_QKV = 3, FEPI_SILU = 4, FEPI_LOGITS = 5,
+enum { FEPI_ADD_TO = 1, FEPI_ADDVEC = 2, FEPI_QKV = 3, FEPI_SILU = 4, FEPI_LOGITS = 5,
        FEPI_QKV_TAB = 6,     // kernel variants only (never a Phase.epi): QKV whose rows are A + add_rows[token], see Phase.wb;
        FEPI_QKV_TAB4 = 7 };  // two staged rows (at most two sequences) / four staged rows (three or four sequences)
 
@@ -602,7 +602,6 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             const float sc = gain ? inv_rms[row] : 1.0f;
             const float v = tile[idx] * sc;
             switch (epi) {
-            case FEPI_STORE: st_wt(&ph.Y[(size_t)row * ph.ldy + col], v); break;
             case FEPI_ADD_TO: st_wt(&ph.Y[(size_t)row * ph.ldy + col], epi_a[sl] + v); break;
             case FEPI_ADDVEC: st_wt(&ph.Y[(size_t)row * ph.ldy + col], v + to_f32(((const WT*)ph.vec)[(size_t)ph.vec_idx * N + col]) + epi_a[sl]); break;
             case FEPI_LOGITS:
@@ -1472,7 +1471,9 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
     typedef typename KVType<WT>::type KT;
     const int type = (TYPE >= 0) ? TYPE : ph.type;
     switch (type) {
-    case PH_GEMM: gemm_phase<WT, EPI, SINGLE>(ph, pp, lds, head, head_valid, wb1, wb1_valid, p); break;
+    case PH_GEMM:
+        if constexpr (TYPE < 0 || TYPE == PH_GEMM) gemm_phase<WT, EPI, SINGLE>(ph, pp, lds, head, head_valid, wb1, wb1_valid, p);
+        break;
     case PH_ATTN: {
         // (item, split) of a workgroup.  Default: split-minor.  flags & 2: every split of an item on ONE XCD (workgroup w
         // runs on XCD w % 8): XCD x works on the items x, x + 8, ..., so an item's partials meet in one L2.
