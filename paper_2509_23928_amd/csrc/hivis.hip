@@ -97,7 +97,7 @@ struct hivis_ctx {
     uint4 *pf_frag = nullptr, *pf_frag2 = nullptr;      // activation fragments: of d / q_dim wide rows, and of the MLP's inner rows
     std::vector<int32_t> h_ids;
 
-    // persistent-kernel path (passes of at most one MFMA tile of rows)
+    // phase programs (fused_rows_ok: how many rows they take)
     bool fused = false;
     int fused_grid = 0; size_t fused_lds = 0, fused_lds_w = 0;      // LDS of a phase launch; of the bf16w kernels
     float* rope_tab = nullptr; float* pm = nullptr; int* pi = nullptr; unsigned* bar = nullptr;
@@ -284,7 +284,7 @@ int gemm(hivis_ctx* c, const float* A, int lda, int M, int K, const uint4* Wp, i
         return wide_gemm(c, frag, M, K, Wp, N, Y, ldy);
     }
     if (M > CHAIN_MAX_ROWS) {            // wider passes (tree verify)
-        // fp32 models: one launch per 32 rows
+        // fp32 models, and bf16 ones with HIVIS_WIDE_GEMM=0 or less than 64 rows of room: one launch per 32 rows
         for (int r0 = 0; r0 < M; r0 += CHAIN_MAX_ROWS)
             if (int rc = gemm<WT>(c, A + (size_t)r0 * lda, lda, std::min(CHAIN_MAX_ROWS, M - r0), K, Wp, N, Y + (size_t)r0 * ldy, ldy, epi)) return rc;
         return HIVIS_OK;
@@ -1064,7 +1064,8 @@ int prefill_lds_setup(hivis_ctx* c) {
     return HIVIS_OK;
 }
 
-// Up to 64 rows in ONE pass over the weights (gemm_wide_kernel).  defer != nullptr: the slice partials are not reduced here;
+// Up to 64 rows in ONE pass over the weights (gemm_wide_kernel): the 11..64-row passes that no phase program takes, and a prefill's
+// products of up to 64 rows.  defer != nullptr: the slice partials are not reduced here;
 // *defer describes them for the consuming row kernel.
 int wide_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer) {
     const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;

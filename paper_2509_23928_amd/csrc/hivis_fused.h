@@ -8,7 +8,9 @@
 //   SiLU*up     -> epilogue of the fused gate|up GEMM (gate and up columns share a tile)
 //   residual    -> epilogue of the O and down GEMMs (each output element has exactly one writer)
 //   argmax      -> epilogue of the LM-head GEMM (per-workgroup candidates) + a tiny reduction phase
-// Used for passes of at most one MFMA tile of rows (8 rows for bf16 weights, 16 for fp32).
+// Used for passes of at most one MFMA tile of rows: 16 for fp32 weights, 8 for bf16 with the high and low activation parts in
+// one operand; bf16 passes of 9..16 rows and the levels of a draft tree take the 16-row form of the GEMM phases (bf16w_t: two
+// operands), one launch per phase.
 //
 // Memory discipline between phases (the L2 is per XCD and not coherent across XCDs): every buffer that one
 // phase writes and a later phase reads is written AT MOST ONCE per launch, with write-through stores, and is
@@ -252,7 +254,7 @@ template <typename WT> __device__ __forceinline__ int rope_offset(const Phase& p
     return ph.offset + row % pp.m;
 }
 
-// GEMM phase of the persistent kernel (rows <= one MFMA tile).  Work split as in gemm_skinny_kernel: the
+// GEMM phase (rows <= one MFMA tile).  Work split as in gemm_skinny_kernel: the
 // workgroup owns a contiguous range of 16-column tiles and covers all of K; in K pass p wavefront w owns
 // blocks [(p*NW + w)*KBW, +KBW) of every tile.
 //  * Activations: per pass the workgroup's threads load the pass's K range of all rows once (coalesced float4), apply

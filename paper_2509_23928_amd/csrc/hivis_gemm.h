@@ -338,7 +338,7 @@ __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t*
 }
 
 // ------------------------------------------------------------------------------------------
-// Wide GEMM (9..64 activation rows: the weights are streamed once).  A workgroup of 2 x 2 wavefronts computes 2 RTW row
+// Wide GEMM (up to 64 activation rows: the weights are streamed once).  A workgroup of 2 x 2 wavefronts computes 2 RTW row
 // tiles (32 or 64 rows) x 128 columns of one K slice: slice s writes its partial sums to part[s][M][ldy] and the
 // consuming row kernel adds them.  Per K block the workgroup copies its blocks from memory to LDS through registers,
 // NSET K blocks ahead (the bytes in flight per workgroup set the bandwidth); two LDS stages, one LDS-only barrier per block.

@@ -345,9 +345,9 @@ __global__ void tree_finish_kernel(const float* __restrict__ dout, const int32_t
 }
 
 // ------------------------------------------------------------------------------------------
-// Row-wise kernels of the 33..64-row passes (bf16 models).  They read a GEMM result as the sum of its K-slice partials
-// (value = sum over s < nparts of p[s * pstride + index], fixed order) and, where the consumer is the next split-K GEMM,
-// write its A operand directly as activation fragments (layout: hivis_gemm.h), so neither the reduction nor the fragment
+// Row-wise kernels around the fragment GEMMs (bf16 models: 11..64-row passes that no phase program takes, and the prefill).
+// They read a GEMM result as the sum of its K-slice partials (value = sum over s < nparts of p[s * pstride + index], fixed
+// order) and, where the consumer is the next GEMM on fragments, write its A operand directly as activation fragments (layout: hivis_gemm.h), so neither the reduction nor the fragment
 // packing is a launch of its own.
 // ------------------------------------------------------------------------------------------
 // h[row] += delta (sum of partials, optional); fragments of h[row] * gain / sqrt(mean(h^2) + eps).  One workgroup of 1024
