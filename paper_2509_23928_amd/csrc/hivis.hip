@@ -1136,7 +1136,7 @@ int rows_gateup(hivis_ctx* c, const LayerDev& L, const uint4* frag, int M, float
     }
     Parts p{};
     if (int rc = rows_gemm(c, frag, M, d, L.wgu, 2 * F, scratch, &p)) return rc;
-    hipLaunchKernelGGL(wide_silu_frag_kernel, dim3((M + 15) / 16, std::min(64, (F / 8 + 15) / 16)), dim3(256), 0, c->stream, p, M, F, frag_out);
+    hipLaunchKernelGGL(wide_silu_frag_kernel, dim3((M + 15) / 16, (F / 8 + 15) / 16), dim3(256), 0, c->stream, p, M, F, frag_out);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
