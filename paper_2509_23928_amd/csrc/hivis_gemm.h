@@ -9,12 +9,17 @@ namespace hivis {
 // Activation fragments.  Every fp32 activation is split into a bf16 high and a bf16 low part (about 16 mantissa bits).  A
 // row tile holds 16 rows; for each block of 32 k-values it has one 1 KiB fragment block of high parts followed by one of
 // low parts:
-//   frag[((row / 16) * kblks + k / 32) * 2 + part][lane] (16 bytes), lane = row % 16 + 16 * ((k / 8) % 4), 8 k-values each
-// which is the operand layout of the 16x16x32 MFMA and the mirror image of the weights' streaming layout.  One weight fragment
-// serves two MFMAs per row tile.
+//   frag[((row / 16) * kblks + k / 32) * 2 + part][piece(row % 16, (k / 8) % 4)] (16 bytes, 8 k-values each)
+// One weight fragment serves two MFMAs per row tile.
+// A row's four pieces of a block are 64 contiguous bytes: the kernels that write fragments work on a row (RMSNorm) or on some
+// columns of a few rows, and what they wait for is the number of 64-byte segments their stores touch.  In the MFMA's own lane order
+// (row + 16 g, a row's pieces 256 bytes apart) the 61-row verify of the 7B widths took 5.38 ms, now 5.31, the 32-row verify of
+// the 13B batch 8.30, now 8.17.  The lane that needs piece (row, g) picks it when it reads LDS; the order of the four pieces
+// changes with row / 4, so that the 16 lanes of one g then hit all banks.
 // ------------------------------------------------------------------------------------------
+__device__ __forceinline__ int afrag_piece(int row, int g) { return 4 * row + (g ^ (row >> 2)); }       // row < 16, g < 4
 __device__ __forceinline__ size_t afrag_at(int kblks, int row, int k) {
-    return (((size_t)(row >> 4) * kblks + (k >> 5)) * 2) * 64 + (row & 15) + 16 * ((k >> 3) & 3);
+    return (((size_t)(row >> 4) * kblks + (k >> 5)) * 2) * 64 + afrag_piece(row & 15, (k >> 3) & 3);
 }
 // 8 consecutive values x[0..8) of row `row` at k (a multiple of 8) -> the high and the low chunk
 __device__ __forceinline__ void store_afrag8(uint4* __restrict__ frag, int kblks, int row, int k, const float (&x)[8], bool zero) {
@@ -42,8 +47,8 @@ __device__ __forceinline__ void store_afrag4(uint4* __restrict__ frag, int kblks
 __global__ void pack_afrag_kernel(const float* __restrict__ A, int lda, int M, int kblks, uint4* __restrict__ out) {
     const size_t total = (size_t)((M + 15) / 16) * 16 * kblks * 4;        // one thread per chunk of 8 values
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-        // 16 rows x 4 chunks of one K block are one 1 KiB block: consecutive threads write consecutive 16-byte pieces
-        const int i = (int)(idx & 15), g = (int)((idx >> 4) & 3);
+        // 16 rows x 4 chunks of one K block are one 1 KiB block: four consecutive threads write 64 contiguous bytes of it
+        const int g = (int)(idx & 3), i = (int)((idx >> 2) & 15);
         const size_t blk = idx >> 6;
         const int kb = (int)(blk % (size_t)kblks), row = (int)(blk / (size_t)kblks) * 16 + i, k = kb * 32 + g * 8;
         const float4* p = reinterpret_cast<const float4*>(A + (size_t)min(row, M - 1) * lda + k);
@@ -137,14 +142,14 @@ struct TallOut {
 };
 
 // A wavefront's finished 64 rows x NT column tiles, in its own LDS area as [64][4 NT] pieces of four columns (piece p of row
-// r at p ^ (r & 15) of 16, so that neither side conflicts), to memory: consecutive lanes take consecutive pieces of a row,
-// or for fragments the 16 rows of a chunk, so that stores cover whole 128-byte lines (straight from the accumulators a
-// store touched 16 rows, 32 bytes of each in the cache: q|k|v of 640 rows 115 us against 94 us for plain rows).
+// r at p ^ (r & 15) of 16, so that neither side conflicts), to memory: consecutive lanes take consecutive pieces of a row (for
+// fragments its NT column tiles: up to 64 contiguous bytes), so that stores cover whole segments (straight from the
+// accumulators a store touched 16 rows, 32 bytes of each in the cache: q|k|v of 640 rows 115 us against 94 us for plain rows).
 template <int NT, int EPI>
 __device__ __forceinline__ void tall_write(const TallOut& o, const v4u_t* area, int row0, int ct0, int M, int ntiles, float* Y, int lane) {
     if constexpr (EPI == TALL_SILU) {
         for (int it = lane; it < 64 * NT; it += 64) {
-            const int r = (it & 15) + 16 * (it / (16 * NT)), t = (it >> 4) % NT, row = row0 + r;
+            const int r = it / NT, t = it % NT, row = row0 + r;
             f32x4_t p[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) p[e] = __builtin_bit_cast(f32x4_t, area[r * 16 + ((4 * t + e) ^ (r & 15))]);
@@ -221,6 +226,7 @@ __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t*
     extern __shared__ __align__(16) v4u_t tall_lds[];     // [4 K blocks][NBLK][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = wave >> 2, w4 = wave & 3;
+    const int piece = afrag_piece(lane & 15, lane >> 4);
     // Tiles are numbered so that neighbours share operands (up to 8 row blocks of one column block, then the next column
     // block; K slices outermost) and every XCD (workgroup L runs on XCD L % 8) takes one contiguous range of them: its L2
     // sees a compact patch of row and column blocks.
@@ -276,8 +282,9 @@ __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t*
         // waited for here, one phase before the other group reads it.
         if (s < mine) {
             const v4u_t* at = tall_lds + (size_t)((2 * s + grp) & 3) * NBLK * 64 + lane;
+            const v4u_t* aa = tall_lds + (size_t)((2 * s + grp) & 3) * NBLK * 64 + piece;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) { fa[0][r] = at[(size_t)(2 * (wr * 4 + r)) * 64]; fa[1][r] = at[(size_t)(2 * (wr * 4 + r) + 1) * 64]; }
+            for (int r = 0; r < 4; ++r) { fa[0][r] = aa[(size_t)(2 * (wr * 4 + r)) * 64]; fa[1][r] = aa[(size_t)(2 * (wr * 4 + r) + 1) * 64]; }
 #pragma unroll
             for (int c = 0; c < CW; ++c) fb[c] = at[(size_t)(NA + wc * CW + c) * 64];
         }
@@ -354,6 +361,7 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const v4u_t* __restri
     extern __shared__ __align__(16) v4u_t tall_lds[];      // [2 stages][NBLK][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wr = wave >> 1, wc = wave & 1;
+    const int piece = afrag_piece(lane & 15, lane >> 4);
     // the K slices of a column block on different XCDs, neighbouring column blocks on one
     const int ncol = (ntiles + NB - 1) / NB;
     const int split = blockIdx.x % ksplit, cblk = blockIdx.x / ksplit;
@@ -407,7 +415,7 @@ __global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const v4u_t* __restri
                 v4u_t* nxt = tall_lds + (size_t)((kb + 1) & 1) * NBLK * 64;
                 v4u_t a[2][RTW], b[CTW];
 #pragma unroll
-                for (int r = 0; r < RTW; ++r) { a[0][r] = cur[(size_t)(2 * (wr * RTW + r)) * 64 + lane]; a[1][r] = cur[(size_t)(2 * (wr * RTW + r) + 1) * 64 + lane]; }
+                for (int r = 0; r < RTW; ++r) { a[0][r] = cur[(size_t)(2 * (wr * RTW + r)) * 64 + piece]; a[1][r] = cur[(size_t)(2 * (wr * RTW + r) + 1) * 64 + piece]; }
 #pragma unroll
                 for (int c = 0; c < CTW; ++c) b[c] = cur[(size_t)(NA + wc * CTW + c) * 64 + lane];
 #pragma unroll

@@ -451,16 +451,17 @@ __global__ void add_parts_kernel(const float* __restrict__ h, Parts ps, int d, f
 }
 
 // act = silu(gate) * up from the interleaved gate|up result (sum of partials), written as fragments of the down projection.
-// grid (row tiles of 16 rows, column chunks), 256 threads; F % 8 == 0.  One trip per thread: with at most 64 chunks (4 row tiles of
-// a 61-row pass x 64 workgroups, a third of them with two trips) the 7B verify pass took 5.45 ms, now 5.38.  Sixteen consecutive threads serve the sixteen rows
-// of the tile for one group of 8 activations: together they write whole 256-byte pieces of the fragment blocks (a thread
-// per (row, group) in row-major order scattered 16-byte stores over the buffer: 137 us for a 3008-row prefill layer).
+// grid (row tiles of 16 rows, column chunks), 256 threads; F % 8 == 0.  Four consecutive threads serve four groups of 8
+// activations of one row, 64 threads the 16 rows of a tile: together they read 256 contiguous bytes of a row at a time and write
+// whole fragment blocks (a thread per (row, group) in row-major order scattered 16-byte stores over the buffer: 137 us for a
+// 3008-row prefill layer).  One trip per thread: with at most 64 chunks (4 row tiles of a 61-row pass x 64 workgroups, a third of
+// them with two trips) the 7B verify pass took 5.45 ms, now 5.38.
 __global__ void wide_silu_frag_kernel(Parts gu, int M, int F, uint4* __restrict__ frag) {
-    const int row = blockIdx.x * 16 + (threadIdx.x & 15), kblks = F / 32;
+    const int row = blockIdx.x * 16 + ((threadIdx.x >> 2) & 15), kblks = F / 32;
     const bool live = row < M;
     const int rr = min(row, M - 1);
     const int per = blockDim.x >> 4;
-    for (int gi = blockIdx.y * per + (threadIdx.x >> 4); gi < F / 8; gi += gridDim.y * per) {
+    for (int gi = blockIdx.y * per + (threadIdx.x & 3) + 4 * (threadIdx.x >> 6); gi < F / 8; gi += gridDim.y * per) {
         const size_t o = (size_t)rr * 2 * F + (size_t)gi * 16;
         const float4 g0 = parts_load4(gu, o), g1 = parts_load4(gu, o + 4), u0 = parts_load4(gu, o + 8), u1 = parts_load4(gu, o + 12);
         const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w}, u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
