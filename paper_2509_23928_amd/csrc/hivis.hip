@@ -341,13 +341,20 @@ int attention(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int*
     sh.nsplit = nsplit;
     const size_t need = (size_t)items * nsplit * 4 * ATT_RMAX * (g.head_dim + 2);
     if (need > c->attn_ws_floats) return fail(c, HIVIS_EINVAL, "attention workspace too small (%zu > %zu)", need, c->attn_ws_floats);
-    if (g.head_dim == 128) {
-        hipLaunchKernelGGL((attn_partial_kernel<KT, 128>), dim3(items, nsplit), dim3(256), 0, c->stream, q, (const KT*)kv.k, (const KT*)kv.v, base, sh, c->attn_ws);
-        hipLaunchKernelGGL((attn_merge_kernel<128>), dim3(items), dim3(256), 0, c->stream, c->attn_ws, base, sh, out, ldo);
-    } else {
-        hipLaunchKernelGGL((attn_partial_kernel<KT, 64>), dim3(items, nsplit), dim3(256), 0, c->stream, q, (const KT*)kv.k, (const KT*)kv.v, base, sh, c->attn_ws);
-        hipLaunchKernelGGL((attn_merge_kernel<64>), dim3(items), dim3(256), 0, c->stream, c->attn_ws, base, sh, out, ldo);
-    }
+    const int rows = sh.mi * sh.gh;              // an item's (head,row) pairs at most
+#define HIVIS_ATTN_PARTIAL(HD_, RC_) hipLaunchKernelGGL((attn_partial_kernel<KT, HD_, RC_>), dim3(items, nsplit), dim3(256), 0, c->stream, q, (const KT*)kv.k, (const KT*)kv.v, base, sh, c->attn_ws)
+#define HIVIS_ATTN_STANDALONE(HD_)                                                                                                       \
+    do {                                                                                                                                 \
+        if (rows <= 1) HIVIS_ATTN_PARTIAL(HD_, 1);                                                                                       \
+        else if (rows <= 2) HIVIS_ATTN_PARTIAL(HD_, 2);                                                                                  \
+        else if (rows <= 4) HIVIS_ATTN_PARTIAL(HD_, 4);                                                                                  \
+        else if (rows <= 8) HIVIS_ATTN_PARTIAL(HD_, 8);                                                                                  \
+        else HIVIS_ATTN_PARTIAL(HD_, ATT_RMAX);                                                                                          \
+        hipLaunchKernelGGL((attn_merge_kernel<HD_>), dim3(items), dim3(256), 0, c->stream, c->attn_ws, base, sh, out, ldo);              \
+    } while (0)
+    if (g.head_dim == 128) HIVIS_ATTN_STANDALONE(128); else HIVIS_ATTN_STANDALONE(64);
+#undef HIVIS_ATTN_STANDALONE
+#undef HIVIS_ATTN_PARTIAL
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }

@@ -721,7 +721,7 @@ __host__ __device__ constexpr size_t attn_lds_floats(int hd, int nwaves, int rma
 // One (item, split) by the calling workgroup of sh.nwaves wavefronts.  Partial results go to
 // ws[(item * nslots + slot)][ATT_RMAX][HD + 2] with slot = wave * nsplit + split; slots beyond the
 // number of key tiles have no work and write nothing.
-template <typename ST, int HD, int RM>
+template <typename ST, int HD, int RM, int RC>
 __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, const ST* __restrict__ kc,
                                                   const ST* __restrict__ vc, const int* __restrict__ base,
                                                   const AttnShape& sh, int item_id, int split, float* __restrict__ lds,
@@ -751,9 +751,11 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
     const float scale = rsqrtf((float)HD);
     float* pw = pw_all + (size_t)wave * RM * 64;
 
-    // All RM rows take part in everything below (the ones past R as zeros, never stored): a test of r < R at each of the
-    // unrolled rows put a wait behind every LDS read (a 32-row chunk of the 256-wide model: 55 us, now 20).
-    for (int idx = threadIdx.x; idx < RM * HD; idx += nthreads) {
+    // All RC rows take part in everything below (the ones past R as zeros, never stored): a test of r < R at each of the
+    // unrolled rows put a wait behind every LDS read (a 32-row chunk of the 256-wide model: 55 us, now 20).  RC is the rows an
+    // item holds, rounded up to 1, 2, 4, 8 or 16: with sixteen for any count the prefill of one token took 242 us, of five 253; now
+    // 217 and 236 (224 and 247 with the tests).
+    for (int idx = threadIdx.x; idx < RC * HD; idx += nthreads) {
         const int r = min(idx / HD, R - 1), c = idx % HD;
         const int hh = kvh * group + h0 + r / ni, i = i0 + r % ni;
         qs[idx] = idx / HD < R ? q[(size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + c] * scale : 0.f;
@@ -763,9 +765,9 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
     const ST* kbase = kc + ((size_t)seq * sh.Hkv + kvh) * sh.maxL * HD * KW;
     const ST* vbase = vc + ((size_t)seq * sh.Hkv + kvh) * sh.maxL * HD * KW;
 
-    float mrun[RM], lrun[RM], acc[RM][DPL];
+    float mrun[RC], lrun[RC], acc[RC][DPL];
 #pragma unroll
-    for (int r = 0; r < RM; ++r) {
+    for (int r = 0; r < RC; ++r) {
         mrun[r] = -INFINITY; lrun[r] = 0.f;
 #pragma unroll
         for (int e = 0; e < DPL; ++e) acc[r][e] = 0.f;
@@ -774,9 +776,9 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
     for (int ti = slot; ti < ntiles; ti += nslots) {
         const int j = ti * 64 + lane;
         const bool valid = j < nkeys;
-        float s[RM];
+        float s[RC];
 #pragma unroll
-        for (int r = 0; r < RM; ++r) s[r] = 0.f;
+        for (int r = 0; r < RC; ++r) s[r] = 0.f;
         if (valid) {
             const uint4* kp = reinterpret_cast<const uint4*>(kbase + (size_t)j * HD * KW);
 #pragma unroll 4
@@ -791,7 +793,7 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
                     for (int e = 0; e < CH; ++e) kf[e] += kl[e];
                 }
 #pragma unroll
-                for (int r = 0; r < RM; ++r) {
+                for (int r = 0; r < RC; ++r) {
                     const float* qr = qs + r * HD + c * CH;
 #pragma unroll
                     for (int e = 0; e < CH; ++e) s[r] += qr[e] * kf[e];
@@ -799,7 +801,7 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
             }
         }
 #pragma unroll
-        for (int r = 0; r < RM; ++r) {
+        for (int r = 0; r < RC; ++r) {
             {
                 const int qpos = pos0 + i0 + r % ni;
                 const bool tree = sh.tmask != nullptr;
@@ -834,7 +836,7 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
                 for (int e = 0; e < DPL; ++e) vf[u][e] = kv_get(vrow, HD, lane * DPL + e);
             }
 #pragma unroll
-            for (int r = 0; r < RM; ++r) {
+            for (int r = 0; r < RC; ++r) {
                 const float4 p0 = *reinterpret_cast<const float4*>(pw + r * 64 + j0), p1 = *reinterpret_cast<const float4*>(pw + r * 64 + j0 + 4);
                 const float p8[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
 #pragma unroll
@@ -850,7 +852,7 @@ __device__ __forceinline__ void attn_item_partial(const float* __restrict__ q, c
     if (slot >= ntiles) return;
     float* out = ws + ((size_t)item_id * nslots + slot) * RM * (HD + 2);
 #pragma unroll
-    for (int r = 0; r < RM; ++r) {
+    for (int r = 0; r < RC; ++r) {
         if (r < R) {
             const float lsum = wave_sum(lrun[r]);
 #pragma unroll
@@ -894,12 +896,12 @@ __device__ __forceinline__ void attn_item_merge(const float* __restrict__ ws, co
     }
 }
 
-template <typename ST, int HD>
+template <typename ST, int HD, int RC>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const float* __restrict__ q, const ST* __restrict__ kc,
                                                             const ST* __restrict__ vc, const int* __restrict__ base,
                                                             AttnShape sh, float* __restrict__ ws) {
     __shared__ __align__(16) float lds[attn_lds_floats(HD, 4)];
-    attn_item_partial<ST, HD, ATT_RMAX>(q, kc, vc, base, sh, blockIdx.x, blockIdx.y, lds, ws);
+    attn_item_partial<ST, HD, ATT_RMAX, RC>(q, kc, vc, base, sh, blockIdx.x, blockIdx.y, lds, ws);
 }
 
 template <int HD>
