@@ -807,6 +807,12 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             case FEPI_ADD_TO: HIVIS_LAUNCH(PH_GEMM, FEPI_ADD_TO); break;
             case FEPI_ADDVEC: HIVIS_LAUNCH(PH_GEMM, FEPI_ADDVEC); break;
             case FEPI_QKV:
+                if constexpr (std::is_same<WT, bf16_t>::value) {        // rows of a draft tree: the 16-row form knows their positions
+                    if (ph.pos_delta) {
+                        hipExtLaunchKernelGGL((phase_kernel<bf16w_t, PH_GEMM, FEPI_QKV, false>), dim3(grid), dim3(FUSED_NT), c->fused_lds_w, c->stream, kev0, kev1, 0, ph, ppl);
+                        break;
+                    }
+                }
                 if constexpr (!std::is_same<WT, bf16w_t>::value) {      // (table rows are added for at most four sequences)
                     if (ph.add_rows && pp.M <= 2) { HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB); break; }
                     if (ph.add_rows) { HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB4); break; }
@@ -1477,6 +1483,8 @@ PassParams tree_pass(const hivis_ctx* c, int m) {
 // phase: inputs cat [m][2d] = hidden row | embedding and the rows' tokens (tok); layer output to out [m][d]; lm_out (optional): its
 // logits.  The lists of all row counts lie in one pool, tree_pool: the passes of a call follow each other on the stream.  The
 // attention's arrival counters (zero between launches) are its first words for every row count, so no list's rows overwrite them.
+// Up to 8 rows: the 8-row kernels, except for q|k|v, where the 16-row one alone takes tree positions (drafts of the 7B widths with k = 8: 699 ->
+// 682 us, of a 2048-wide model with k = 2: 152 -> 141; there the 16-row kernels were slower than the stand-alone ones, 150).
 template <typename WT>
 void tree_rows_phases(hivis_ctx* c, int m, const float* cat, const int32_t* tok, int rho_idx, int offset, TreeRows tr, float* out, float* lm_out,
                       Pool& pool, std::vector<Phase>& P) {
@@ -1513,7 +1521,7 @@ int tree_rows_program(hivis_ctx* c, int m, const float* cat, const int32_t* tok,
     tree_rows_phases<WT>(c, m, cat, tok, rho_idx, offset, tr, out, lm_out, pool, P);
     const PassParams pp = tree_pass(c, m);
     if constexpr (std::is_same<WT, bf16_t>::value) {
-        if (m > WTraits<WT>::ROWS || tr.pos_delta) return launch_phases<bf16w_t>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
+        if (m > WTraits<WT>::ROWS) return launch_phases<bf16w_t>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
     }
     return launch_phases<WT>(c, P.data(), (int)P.size(), PROG_DRAFT, offset + m, pp, false);
 }
