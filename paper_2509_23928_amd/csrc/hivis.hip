@@ -1113,8 +1113,8 @@ int rows_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, in
 bool ends_in_gemm(hivis_ctx* c, int M, int K, int N, TallPlan* pl) {
     if (M <= MAX_ROWS) return false;
     *pl = tall_plan(c->num_cu, M, K / 32, N / 16, false, c->tall_cw);
-    const TallPlan sliced = sliced_plan(c, M, K, N);
-    return sliced.ksplit == 1 || tall_fused(*pl, sliced);
+    // (room for the slices is asked for only where they are wanted: those of gate|up are the largest)
+    return tall_fused(*pl, tall_plan(c->num_cu, M, K / 32, N / 16, true, c->tall_cw)) || sliced_plan(c, M, K, N).ksplit == 1;
 }
 
 // M = nseq * m rows: q (rotated) to q_out [M][q_dim], k and v of sequence seq0 + s to its cache rows base[seq0 + s] + offset ..
