@@ -1018,6 +1018,7 @@ constexpr size_t SPLITK_RESERVE = (size_t)32 << 20;
 bool splitk_alloc(hivis_ctx* c, size_t floats) {
     void* q = nullptr;
     if (hipMalloc(&q, floats * sizeof(float)) != hipSuccess) { (void)hipGetLastError(); return false; }
+    c->allocs.push_back(q);
     c->splitk_ws = (float*)q; c->splitk_floats = floats;
     return true;
 }
@@ -1028,8 +1029,11 @@ size_t splitk_most(const hivis_ctx* c) {
 bool splitk_space(hivis_ctx* c, size_t floats) {
     if (floats <= c->splitk_floats) return true;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
-    (void)hipFree(c->splitk_ws);
-    c->splitk_ws = nullptr; c->splitk_floats = 0;
+    if (c->splitk_ws) {
+        c->allocs.erase(std::find(c->allocs.begin(), c->allocs.end(), (void*)c->splitk_ws));
+        (void)hipFree(c->splitk_ws);
+        c->splitk_ws = nullptr; c->splitk_floats = 0;
+    }
     return splitk_alloc(c, std::max(floats, splitk_most(c))) || splitk_alloc(c, floats);
 }
 // rows of fp32 -> fragments, in the buffer that holds them (*out)
@@ -1926,7 +1930,6 @@ int hivis_destroy(hivis_ctx* c) {
     if (!c) return HIVIS_OK;
     (void)hipStreamSynchronize(c->stream);
     for (void* p : c->allocs) (void)hipFree(p);
-    (void)hipFree(c->splitk_ws);
     for (auto& kv : c->programs) delete kv.second.host;
     for (hipEvent_t e : c->pev) (void)hipEventDestroy(e);
     if (c->h_result) (void)hipHostFree(c->h_result);
