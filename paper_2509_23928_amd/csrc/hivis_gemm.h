@@ -108,7 +108,8 @@ __device__ __forceinline__ void block_to_lds(const v4u_t* src, v4u_t* lds) {
 // low parts beside it (4.0e-7 of the result for both at K = 4096, 6.7e-7 at K = 11008; the 16 mantissa bits of the operands leave 2.5e-6).
 // Matrix bound: with random data the MFMAs alone run at 2.0 PFLOP/s on this card (2.46 on zeros, it is power that
 // limits them), a library product of 8192^3 at 1.10.  640 rows, K = 4096, high and low parts counted: 22016 columns 249 ->
-// 172 us (1.35 PFLOP/s), 12288 columns 127 -> 94 us (1.37); 3008 x 22016: 1090 -> 813 us (1.33).  The version with the requests
+// 172 us (1.35 PFLOP/s), 12288 columns 127 -> 94 us (1.37); 3008 x 22016: 1090 -> 813 us (1.33): launches of one size back to back, inside
+// traced requests 182, 106 and 854 us.  The version with the requests
 // at the head of the multiplication phase took 203 and 107 us; groups owning row halves instead of K blocks (256-row
 // tiles) were no faster at 3008 rows and left too few tiles at 640.
 // ------------------------------------------------------------------------------------------
