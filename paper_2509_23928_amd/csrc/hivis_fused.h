@@ -160,14 +160,21 @@ template <int NW, int KBW> __device__ __forceinline__ int unit_nkb(int kblks, in
     return max(0, min(bw, kblks - p * NW * KBW - wave * bw));
 }
 
-// Loads of one unit: the wavefront's K blocks [kb0, kb0+nkb) of tile `tile`.
-template <int U>
+// Loads of one unit: the wavefront's K blocks [kb0, kb0+nkb) of tile `tile`.  Buffer loads: blocks beyond nkb lie outside the
+// descriptor's range and come back as zeros without a memory access, so a ragged unit needs no branches.  (With a branch per block
+// the compiler placed a copy, and before it a wait for everything in flight, behind the second load of a unit: every wavefront
+// waited a memory round trip before it requested the other fourteen.)  bf16: with the non-temporal hint, because a weight
+// is read by one workgroup, once per pass: a plain stream of 180 MB takes 27.2 us with it and 30.4 without, of 34 MB 6.4 and 7.0.
+// fp32 models (a few MB) are re-read from the L2: without.
+// Both together, C2 verify pass: gate|up 35.2 -> 32.0 us, q|k|v 22.6 -> 20.4, LM head 54.5 -> 49.3; with the hint alone 32.2, 21.5, 50.4.
+template <typename WT, int U>
 __device__ __forceinline__ void issue_unit(uint4 (&wb)[U], const uint4* __restrict__ W, int kblks, int tile, int kb0,
                                            int nkb, int lane) {
-    const uint4* p = W + ((size_t)tile * kblks + kb0) * 64 + lane;
+    typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+    constexpr int HINT = std::is_same<WT, float>::value ? 0 : 2;         // 2: non-temporal
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)(W + ((size_t)tile * kblks + kb0) * 64), 0, nkb * 1024, 0x00020000);
 #pragma unroll
-    for (int j = 0; j < U; ++j)
-        if (j < nkb) wb[j] = p[(size_t)j * 64]; else wb[j] = make_uint4(0, 0, 0, 0);
+    for (int j = 0; j < U; ++j) { const u4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + j * 1024, 0, HINT); wb[j] = __builtin_bit_cast(uint4, v); }
 }
 
 // tile row (MFMA A row) that holds activation row `row`: bf16 keeps hi at 4*(row/2) + row%2 and lo two rows below
@@ -338,13 +345,13 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     // of the next pass.
 #define HIVIS_FIRST_UNITS(W_, kblks_, tile_, ntl_, npass_)                                                         \
     {                                                                                                              \
-        issue_unit(head, W_, kblks_, tile_, unit_kb0<NW, KBW>(kblks_, 0, wave), unit_nkb<NW, KBW>(kblks_, 0, wave), lane); \
+        issue_unit<WT>(head, W_, kblks_, tile_, unit_kb0<NW, KBW>(kblks_, 0, wave), unit_nkb<NW, KBW>(kblks_, 0, wave), lane); \
         head_valid = true;                                                                                         \
         /* one call site for the second unit (two alternative ones make the compiler drain the first unit's loads) */ \
         const bool next_tile_ = (ntl_) >= 2;                                                                       \
         wb1_valid = next_tile_ || (SINGLE && (npass_) >= 2);                                                       \
         const int p1_ = next_tile_ ? 0 : 1;                                                                        \
-        if (wb1_valid) issue_unit(wb1, W_, kblks_, (tile_) + (next_tile_ ? 1 : 0), unit_kb0<NW, KBW>(kblks_, p1_, wave), unit_nkb<NW, KBW>(kblks_, p1_, wave), lane); \
+        if (wb1_valid) issue_unit<WT>(wb1, W_, kblks_, (tile_) + (next_tile_ ? 1 : 0), unit_kb0<NW, KBW>(kblks_, p1_, wave), unit_nkb<NW, KBW>(kblks_, p1_, wave), lane); \
     }
 
     if (ntl <= 0) {
@@ -479,7 +486,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             //      matters is how much is in flight per wait: two units here.  With one unit requested per pass every
             //      pass paid a memory round trip for 8 KiB per wavefront and the kernel was latency-bound.
             if (npass > 1) HIVIS_LOAD_RAW_TO(1, araw2, graw2)
-            if (!wb1_first && npass > 1) issue_unit(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, 1, wave), unit_nkb<NW, KBW>(kblks, 1, wave), lane);
+            if (!wb1_first && npass > 1) issue_unit<WT>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, 1, wave), unit_nkb<NW, KBW>(kblks, 1, wave), lane);
             for (int pass = 0; pass < npass; pass += 2) {
                 HIVIS_STAGE_FROM(pass, araw, graw, true, )
                 if (pass == 0) { HIVIS_MARK(1) }
@@ -490,11 +497,11 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
                 }
                 if (pass + 2 < npass) {
                     HIVIS_LOAD_RAW_TO(pass + 2, araw, graw)
-                    issue_unit(head, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 2, wave), unit_nkb<NW, KBW>(kblks, pass + 2, wave), lane);
+                    issue_unit<WT>(head, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 2, wave), unit_nkb<NW, KBW>(kblks, pass + 2, wave), lane);
                 }
                 if (pass + 3 < npass) {
                     HIVIS_LOAD_RAW_TO(pass + 3, araw2, graw2)
-                    issue_unit(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 3, wave), unit_nkb<NW, KBW>(kblks, pass + 3, wave), lane);
+                    issue_unit<WT>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 3, wave), unit_nkb<NW, KBW>(kblks, pass + 3, wave), lane);
                 }
             }
         } else {
@@ -516,17 +523,17 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
 #pragma unroll
                 for (int g0 = 0; g0 < G; g0 += 2) {
                     if (g0 < ng) {
-                        if (g0 + 1 < ng && !(g0 == 0 && have_wb1)) issue_unit(wb1, W, kblks, tg + g0 + 1, kb0, nkb, lane);
+                        if (g0 + 1 < ng && !(g0 == 0 && have_wb1)) issue_unit<WT>(wb1, W, kblks, tg + g0 + 1, kb0, nkb, lane);
                         mfma_unit(acc[g0], af, head);
-                        if (g0 + 2 < ng) issue_unit(head, W, kblks, tg + g0 + 2, kb0, nkb, lane);
-                        else if (nvalid) issue_unit(head, W, kblks, ntile, nkb0, nnkb, lane);
+                        if (g0 + 2 < ng) issue_unit<WT>(head, W, kblks, tg + g0 + 2, kb0, nkb, lane);
+                        else if (nvalid) issue_unit<WT>(head, W, kblks, ntile, nkb0, nnkb, lane);
                         if (g0 + 1 < ng) {
                             mfma_unit(acc[g0 + 1], af, wb1);
                         }
                     }
                 }
                 // second unit of the next (tile group, pass): its registers are free now
-                if (nvalid && ntiles2 >= 2) { issue_unit(wb1, W, kblks, ntile + 1, nkb0, nnkb, lane); wb1_valid = true; }
+                if (nvalid && ntiles2 >= 2) { issue_unit<WT>(wb1, W, kblks, ntile + 1, nkb0, nnkb, lane); wb1_valid = true; }
                 if (first && pass == 0) { HIVIS_MARK(2) }
             }
         }
