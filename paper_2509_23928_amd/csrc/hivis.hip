@@ -5,6 +5,7 @@
 #include "hivis_kernels.h"
 #include "hivis_gemm.h"
 #include "hivis_fused.h"
+#include "hivis_stream.h"
 #include "hivis_tree.h"
 
 #include <hip/hip_ext.h>
@@ -76,6 +77,11 @@ struct hivis_ctx {
     float *catT = nullptr;      // [MAX_ROWS][2d]: verify features g | embeddings of the following tokens
     float *catD = nullptr;      // [B][2d]: drafter hidden f' | embedding of the drafted token
     float *u = nullptr, *dout = nullptr;
+    // phase programs on row fragments (bf16 models with the fusion FC's table, one launch per phase)
+    bool stream_rows = false;
+    uint4* catDf = nullptr;              // the rows of catD as row fragments (of batch rows)
+    uint4* vfrag = nullptr;              // features of a verify program's rows
+    uint4* tcatf = nullptr;              // hidden rows of a tree level, or of a tree's re-feed
     float *feat = nullptr;      // [B][max_text][d] true features of prompt text rows (prefill only)
     float *attn_ws = nullptr; size_t attn_ws_floats = 0;
     int* rows_cnt = nullptr; int rows_cnt_n = 0;      // arrival counters of the key-split attention launched outside a phase program (zero between launches)
@@ -617,11 +623,50 @@ float* layer_phases(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const Layer
     return h2;
 }
 
+// Residual rows of a pass on row fragments: fp32 rows h [M][d]; F: the rows times the next norm's gain, ssq: their sums of squares in
+// nssq parts per row.  (F null: the first phase adds table rows to fp32 rows itself.)
+struct StreamRows { float* h; uint4* F; float* ssq; int nssq; };
+
+// layer_phases on row fragments.  out: where the layer's rows go (h, F, ssq: null for what nobody reads); out_gain: gain for out.F.
+template <typename WT>
+void layer_stream(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const LayerDev& L, const KVDev& kv, StreamRows in, const int* base, int offset, int nseq, int m,
+                  StreamRows out, const void* out_gain, bool elect) {
+    const hivis_config& g = c->cfg;
+    const int M = nseq * m;
+    const int d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, F = g.ffn, nqkv = qd + 2 * kd;
+    float* qrows = pool.take((size_t)M * qd);
+    uint4* attF = (uint4*)pool.take((size_t)M * qd);
+    float* h1 = pool.take((size_t)M * d);
+    uint4* h1F = (uint4*)pool.take((size_t)M * d);
+    float* h1s = pool.take((size_t)M * ssq_stride(d / 16));
+    uint4* actF = (uint4*)pool.take((size_t)M * F);
+    Phase q{}; q.type = PH_GEMM; q.pro = PRO_RMS; q.epi = FEPI_QKV; q.K = d; q.N = nqkv; q.W = L.wqkv; q.A = in.h; q.lda = d;
+    q.gain = L.norm1; q.Y = qrows; q.ldy = qd; q.kc = kv.k; q.vc = kv.v; q.maxL = kv.maxL; q.base = base; q.offset = offset; q.rope = c->rope_tab; q.bias = L.bqkv;
+    q.Af = in.F; q.ssq = in.ssq; q.nssq = in.nssq;
+    P.push_back(q);
+    Phase a{}; a.type = PH_ATTN; a.A = qrows; a.lda = qd; a.kc = kv.k; a.vc = kv.v; a.maxL = kv.maxL; a.base = base; a.offset = offset;
+    a.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, qd, &a.att_items);
+    a.ws = pool.take((size_t)a.att_items * a.att.nsplit * FUSED_RMAX * (g.head_dim + 2));
+    a.F = attF; a.ldy = qd;
+    if (elect) a.cnt = (int*)pool.take((size_t)a.att_items);       // zero from the pool's memset; the merging workgroup re-zeroes it
+    P.push_back(a);
+    if (!elect) { Phase mg = a; mg.type = PH_ATTN_MERGE; P.push_back(mg); }
+    Phase o{}; o.type = PH_GEMM; o.pro = PRO_PLAIN; o.epi = FEPI_ADD_TO; o.K = qd; o.N = d; o.W = L.wo; o.Af = attF;
+    o.Y = h1; o.ldy = d; o.R = in.h; o.ldr = d; o.F = h1F; o.fgain = L.norm2; o.ssq_out = h1s;
+    P.push_back(o);
+    Phase gu{}; gu.type = PH_GEMM; gu.pro = PRO_RMS; gu.epi = FEPI_SILU; gu.K = d; gu.N = 2 * F; gu.W = L.wgu; gu.Af = h1F; gu.ssq = h1s; gu.nssq = d / 16;
+    gu.F = actF;
+    P.push_back(gu);
+    Phase dn{}; dn.type = PH_GEMM; dn.pro = PRO_PLAIN; dn.epi = FEPI_ADD_TO; dn.K = F; dn.N = d; dn.W = L.wd; dn.Af = actF;
+    dn.Y = out.h; dn.ldy = d; dn.R = h1; dn.ldr = d; dn.F = out.F; dn.fgain = out_gain; dn.ssq_out = out.ssq;
+    P.push_back(dn);
+}
+
 // greedy candidates per row of an LM-head phase: its workgroups (a single-launch program always runs the whole grid)
 int lm_candidates(const hivis_ctx* c, int N, bool persistent) { return persistent ? c->fused_grid : std::min(c->fused_grid, N / 16); }
 
 template <typename WT>
-void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>& P, bool persistent, bool elect) {
+void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>& P, bool persistent, bool elect, bool stream) {
     const hivis_config& g = c->cfg;
     const int B = g.batch, d = g.d, V = g.vocab, G = c->fused_grid;
     int ld = d;
@@ -630,7 +675,87 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
     // LM-head phase (the workgroup that arrives last reduces the candidates).  The single-launch program keeps both phases.
     const bool fold = !persistent;
     const bool lm_elect = elect && !persistent;
-    if (kind == PROG_VERIFY) {
+    auto rows_of = [&](int M, bool sums) {
+        StreamRows r{};
+        r.h = pool.take((size_t)M * d); r.F = (uint4*)pool.take((size_t)M * d);
+        if (sums) { r.ssq = pool.take((size_t)M * ssq_stride(d / 16)); r.nssq = d / 16; }
+        return r;
+    };
+    if (stream && kind == PROG_VERIFY) {
+        const int m = K + 1, M = B * m;
+        StreamRows x = rows_of(M, false);
+        x.ssq = pool.take((size_t)M * ssq_stride(1)); x.nssq = 1;
+        Phase pr{}; pr.type = PH_PREP; pr.ids = c->row_tok; pr.id_sseq = m; pr.id_srow = 1; pr.gain = c->embed; pr.Y = x.h; pr.ldy = d;
+        pr.F = x.F; pr.fgain = c->layers[0].norm1; pr.ssq_out = x.ssq;
+        P.push_back(pr);
+        for (int l = 0; l < g.n_layers; ++l) {
+            const bool end = l + 1 == g.n_layers;
+            StreamRows y = end ? StreamRows{pool.take((size_t)M * d), nullptr, nullptr, 0} : rows_of(M, true);
+            layer_stream<WT>(c, P, pool, c->layers[l], c->tkv[l], x, c->tlen, 0, B, m, y, end ? nullptr : c->layers[l + 1].norm1, elect);
+            x = y;
+        }
+        Phase nr{}; nr.type = PH_NORM_ROWS; nr.A = x.h; nr.lda = d; nr.gain = c->final_norm; nr.Y = c->catT; nr.ldy = 2 * d; nr.F = c->vfrag;
+        P.push_back(nr);
+        Phase lm{}; lm.type = PH_GEMM; lm.pro = PRO_PLAIN; lm.epi = FEPI_LOGITS; lm.K = d; lm.N = V; lm.W = c->lm_head; lm.Af = c->vfrag;
+        lm.Y = c->logits_v; lm.ldy = V; lm.pm = pool.take((size_t)M * G); lm.pi = (int*)pool.take((size_t)M * G);
+        lm.tok_out = c->ttok; lm.o_sseq = g.k_max + 1; lm.o_srow = 1;
+        if (lm_elect) lm.cnt = (int*)pool.take(1);
+        P.push_back(lm);
+        if (!lm_elect) {
+            Phase am{}; am.type = PH_ARGMAX; am.tok_out = c->ttok; am.o_sseq = g.k_max + 1; am.o_srow = 1; am.pm = lm.pm; am.pi = lm.pi; am.N = lm_candidates(c, lm.N, false);
+            P.push_back(am);
+        }
+    } else if (stream && kind != PROG_ROLL) {
+        const uint4* f = c->catDf;            // the drafter's hidden rows
+        for (int i = 1; i <= K; ++i) {
+            Phase lm{}; lm.type = PH_GEMM; lm.pro = PRO_PLAIN; lm.epi = FEPI_LOGITS; lm.K = d; lm.N = V; lm.W = c->lm_head; lm.Af = f;
+            lm.Y = c->logits_d + (size_t)(i - 1) * B * V; lm.ldy = V; lm.pm = pool.take((size_t)B * G); lm.pi = (int*)pool.take((size_t)B * G);
+            lm.tok_out = c->drafts + (i - 1); lm.o_sseq = g.k_max; lm.o_srow = 0;
+            // greedy token of step i: reduced by the phase that follows (as below), by the LM head's last workgroup, or by a phase of its own
+            const bool later = kind == PROG_DRAFT && i < K, ext = later && c->lm_ext && B <= 4;
+            const bool in_lm = !later && lm_elect && kind == PROG_DRAFT;
+            float* u_part = ext ? pool.take((size_t)B * d) : nullptr;
+            if (ext) { lm.N = V + d; lm.Y2 = u_part; lm.ldy2 = d; lm.vec = c->rho; lm.vec_idx = std::min(i, g.n_resid - 1); }
+            if (in_lm) lm.cnt = (int*)pool.take(1);
+            P.push_back(lm);
+            const int ncand = lm_candidates(c, lm.N, false);
+            if (!in_lm && !later) {
+                Phase am{}; am.type = PH_ARGMAX; am.tok_out = lm.tok_out; am.o_sseq = g.k_max; am.o_srow = 0; am.pm = lm.pm; am.pi = lm.pi; am.N = ncand;
+                if (kind == PROG_DRAFT_SAMPLE) { am.type = PH_SAMPLE; am.A = lm.Y; am.lda = V; am.u = c->u_draft; am.u_sseq = g.k_max; am.u_idx = i - 1; }
+                P.push_back(am);
+            }
+            if (i == K) break;
+            StreamRows u{};
+            if (ext) u.h = pool.take((size_t)B * d);
+            else {
+                u = rows_of(B, true);
+                Phase fu{}; fu.type = PH_GEMM; fu.pro = PRO_PLAIN; fu.epi = FEPI_ADDVEC; fu.K = d; fu.N = d; fu.W = c->fuse_w1; fu.Af = f;
+                fu.Y = u.h; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = std::min(i, g.n_resid - 1); fu.add_rows = c->emb_w2;
+                fu.F = u.F; fu.fgain = c->draft.norm1; fu.ssq_out = u.ssq;
+                if (later) { fu.pm = lm.pm; fu.pi = lm.pi; fu.ncand = ncand; fu.tok_out = lm.tok_out; fu.o_sseq = g.k_max; fu.o_srow = 0; }
+                else { fu.tok = c->drafts + (i - 1); fu.tok_sseq = g.k_max; fu.tok_srow = 0; }
+                P.push_back(fu);
+            }
+            const size_t qi = P.size();
+            uint4* fn = (uint4*)pool.take((size_t)B * d);
+            layer_stream<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, i - 1, B, 1, StreamRows{nullptr, fn, nullptr, 0}, nullptr, elect);
+            if (ext) {      // the layer's first phase (QKV): rows = u_part + table[token], tokens from this step's candidates, u written back
+                Phase& q = P[qi];
+                q.A = u_part; q.lda = d; q.add_rows = c->emb_w2; q.wb = u.h; q.tok = nullptr; q.pm = lm.pm; q.pi = lm.pi; q.ncand = ncand;
+                q.tok_out = lm.tok_out; q.o_sseq = g.k_max; q.o_srow = 0;
+            }
+            f = fn;
+        }
+    } else if (stream) {
+        // the re-fed rows are the verify pass's features, whose fragments it left
+        const int m = K + 1, M = B * m;
+        StreamRows u = rows_of(M, true);
+        Phase fu{}; fu.type = PH_GEMM; fu.pro = PRO_PLAIN; fu.epi = FEPI_ADDVEC; fu.K = d; fu.N = d; fu.W = c->fuse_w1; fu.Af = c->vfrag;
+        fu.Y = u.h; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = 0; fu.add_rows = c->emb_w2; fu.tok = c->next_tok; fu.tok_sseq = g.k_max + 1; fu.tok_srow = 1;
+        fu.F = u.F; fu.fgain = c->draft.norm1; fu.ssq_out = u.ssq;
+        P.push_back(fu);
+        layer_stream<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, 0, B, m, StreamRows{c->dout, nullptr, nullptr, 0}, nullptr, elect);
+    } else if (kind == PROG_VERIFY) {
         const int m = K + 1, M = B * m;
         float* x = pool.take((size_t)M * d);
         Phase pr{}; pr.type = PH_PREP; pr.ids = c->row_tok; pr.id_sseq = m; pr.id_srow = 1; pr.gain = c->embed; pr.Y = x; pr.ldy = d;
@@ -732,12 +857,12 @@ int get_program(hivis_ctx* c, int kind, int K, hivis_ctx::Program* out) {
     if (it != c->programs.end()) { *out = it->second; return HIVIS_OK; }
     std::vector<Phase> P;
     Pool count;
-    build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect);           // sizes only
+    build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect, c->stream_rows);           // sizes only
     Pool pool;
     if (int rc = dev_alloc(c, &pool.base, count.used)) return rc;
     HIP_TRY(c, hipMemsetAsync(pool.base, 0, count.used * sizeof(float), c->stream));      // (on the stream of the passes that count on it)
     P.clear();
-    build_phases<WT>(c, kind, K, pool, P, c->persistent, c->attn_elect);
+    build_phases<WT>(c, kind, K, pool, P, c->persistent, c->attn_elect, c->stream_rows);
     hivis_ctx::Program pg;
     pg.n = (int)P.size();
     if (int rc = dev_alloc(c, &pg.dev, P.size())) return rc;
@@ -801,6 +926,39 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             c->kev_used += 2;
             c->kbytes = (double)ph.K * ph.N * c->esize;
         }
+        if constexpr (!std::is_same<WT, float>::value) {
+            if (ph.type == PH_GEMM && ph.Af) {
+                // tiles of a workgroup in groups of at most 8, as even as they come (a kernel of fewer tiles takes more groups)
+                const int most = (ph.N / 16 + grid - 1) / grid, group = (most + (most + 7) / 8 - 1) / ((most + 7) / 8);
+                const bool sh = ph.K <= STREAM_SHORT_K;
+#define HIVIS_STREAM_(EP, G_, SH_) hipExtLaunchKernelGGL((stream_kernel<WT, EP, G_, SH_>), dim3(grid), dim3(FUSED_NT), stream_lds_floats(G_, WTraits<WT>::RPL) * sizeof(float), c->stream, kev0, kev1, 0, ph, ppl)
+#define HIVIS_STREAM(EP, G_) HIVIS_STREAM_(EP, G_, false)
+#define HIVIS_STREAM2(EP, G_) do { if (sh) HIVIS_STREAM_(EP, G_, true); else HIVIS_STREAM_(EP, G_, false); } while (0)
+                switch (ph.epi) {
+                case FEPI_ADD_TO: if (group <= 1) HIVIS_STREAM2(FEPI_ADD_TO, 1); else HIVIS_STREAM(FEPI_ADD_TO, 2); break;
+                case FEPI_ADDVEC: if (group <= 1) HIVIS_STREAM2(FEPI_ADDVEC, 1); else HIVIS_STREAM(FEPI_ADDVEC, 2); break;
+                case FEPI_QKV: if (group <= 1) HIVIS_STREAM2(FEPI_QKV, 1); else if (group <= 2) HIVIS_STREAM2(FEPI_QKV, 2); else if (group <= 3) HIVIS_STREAM(FEPI_QKV, 3); else HIVIS_STREAM(FEPI_QKV, 4); break;
+                case FEPI_SILU:
+                    if (group <= 2) HIVIS_STREAM2(FEPI_SILU, 2); else if (group <= 3) HIVIS_STREAM2(FEPI_SILU, 3); else if (group <= 4) HIVIS_STREAM(FEPI_SILU, 4);
+                    else if (group <= 6) HIVIS_STREAM(FEPI_SILU, 6); else HIVIS_STREAM(FEPI_SILU, 8);
+                    break;
+                case FEPI_LOGITS: if (group <= 2) HIVIS_STREAM(FEPI_LOGITS, 2); else if (group <= 4) HIVIS_STREAM(FEPI_LOGITS, 4); else if (group <= 6) HIVIS_STREAM2(FEPI_LOGITS, 6); else HIVIS_STREAM2(FEPI_LOGITS, 8); break;
+                default: return fail(c, HIVIS_EINVAL, "phase %d: no kernel for epilogue %d", p, ph.epi);
+                }
+#undef HIVIS_STREAM2
+#undef HIVIS_STREAM
+#undef HIVIS_STREAM_
+                continue;
+            }
+            if (ph.type == PH_NORM_ROWS && ph.F) {
+                hipExtLaunchKernelGGL(stream_norm_kernel, dim3(pp.M), dim3(FUSED_NT), 0, c->stream, kev0, kev1, 0, ph, ppl);
+                continue;
+            }
+            if (ph.type == PH_PREP && ph.F) {
+                hipExtLaunchKernelGGL(stream_prep_kernel, dim3(pp.M), dim3(FUSED_NT), 0, c->stream, kev0, kev1, 0, ph, ppl);
+                continue;
+            }
+        }
         switch (ph.type) {
         case PH_GEMM:
             switch (ph.epi) {
@@ -855,9 +1013,9 @@ int run_program(hivis_ctx* c, int kind, int K, int nseq, int m) {
     pp.prof2 = do_prof ? c->prof + 4096 * 3 : nullptr;
     if (!c->persistent) {
         if constexpr (std::is_same<WT, bf16_t>::value) {
-            if (pp.M > WTraits<WT>::ROWS) return launch_phases<bf16w_t>(c, pg.host->data(), pg.n, kind, K, pp, false);
-        }
-        if (int rc = launch_phases<WT>(c, pg.host->data(), pg.n, kind, K, pp, do_prof)) return rc;
+            if (pp.M > WTraits<WT>::ROWS) { if (int rc = launch_phases<bf16w_t>(c, pg.host->data(), pg.n, kind, K, pp, do_prof)) return rc; }
+            else if (int rc = launch_phases<WT>(c, pg.host->data(), pg.n, kind, K, pp, do_prof)) return rc;
+        } else if (int rc = launch_phases<WT>(c, pg.host->data(), pg.n, kind, K, pp, do_prof)) return rc;
         if (do_prof) {
             // developer aid: timestamps (100 MHz) that workgroup 0 of each launch wrote, for one layer in the middle
             std::vector<unsigned long long> t2((size_t)pg.n * 8);
@@ -936,15 +1094,22 @@ int draft_noalloc(hivis_ctx* c, int K) {
     const hivis_config& g = c->cfg;
     std::vector<Phase>& P = c->na_phases;
     if (draft_phase_capacity(K) > P.capacity()) return fail(c, HIVIS_ECAP, "phase list of K=%d exceeds the storage reserved at create", K);
-    P.clear();
-    Pool count;
-    build_phases<WT>(c, PROG_DRAFT, K, count, P, false, false);            // sizes only
-    const size_t need = count.used * sizeof(float);
+    // (a round whose buffers fit only as fp32 rows runs on those)
+    bool stream = c->stream_rows;
+    size_t need = 0;
+    for (;;) {
+        P.clear();
+        Pool count;
+        build_phases<WT>(c, PROG_DRAFT, K, count, P, false, false, stream);            // sizes only
+        need = count.used * sizeof(float);
+        if (need <= (size_t)HIVIS_SCRATCH_BYTES || !stream) break;
+        stream = false;
+    }
     if (need > (size_t)HIVIS_SCRATCH_BYTES)
         return fail(c, HIVIS_ECAP, "draft round of K=%d needs %zu bytes of scratch, the static array holds %u", K, need, (unsigned)HIVIS_SCRATCH_BYTES);
     P.clear();
     Pool pool; pool.base = (float*)c->scratch_dev;                  // the looked-up device address, not the array's name
-    build_phases<WT>(c, PROG_DRAFT, K, pool, P, false, false);
+    build_phases<WT>(c, PROG_DRAFT, K, pool, P, false, false, stream);
     PassParams pp{};
     pp.phases = nullptr; pp.nphases = (int)P.size();
     pp.M = g.batch; pp.nseq = g.batch; pp.m = 1;
@@ -987,6 +1152,11 @@ int fused_setup(hivis_ctx* c) {
                             (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_QKV, false>, (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_SILU, false>,
                             (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_LOGITS, false>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->fused_lds_w));
+    }
+    if constexpr (std::is_same<WT, bf16_t>::value) {
+        // (the only stream kernels beyond 64 KB of LDS)
+        const void* ks[] = {(const void*)stream_kernel<bf16w_t, FEPI_SILU, 8, false>, (const void*)stream_kernel<bf16w_t, FEPI_LOGITS, 8, false>, (const void*)stream_kernel<bf16w_t, FEPI_LOGITS, 8, true>};
+        for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(stream_lds_floats(8, WTraits<bf16w_t>::RPL) * sizeof(float))));
     }
     { const char* pe = getenv("HIVIS_PERSISTENT"); c->persistent = pe && pe[0] == '1'; }
     { const char* we = getenv("HIVIS_WIDE_GEMM"); c->no_wide_gemm = we && we[0] == '0'; }
@@ -1259,7 +1429,8 @@ int prefill_drafter_tall(hivis_ctx* c, int b0, int nseq, int l) {
     if (int rc = rows_qkv<WT>(c, c->draft, c->dkv, c->pf_frag, c->zeros, 0, b0, nseq, l, TreeRows(), c->pf_gu, c->pf_qkv)) return rc;
     hipLaunchKernelGGL(tail_rows_kernel, dim3(1, nseq), dim3(256), 0, c->stream, (const float*)c->pf_x, l, l - 1, c->pf_xt, d);
     if (int rc = rows_attn_mlp<WT>(c, c->draft, c->dkv, c->pf_qkv + (size_t)(l - 1) * qd, l, l - 1, b0, nseq, 1, c->pf_xt, &p)) return rc;
-    hipLaunchKernelGGL(add_parts_kernel, dim3(nseq, row_chunks(nseq)), dim3(256), 0, c->stream, (const float*)c->pf_xt, p, d, c->catD + (size_t)b0 * 2 * d, 2 * d);
+    hipLaunchKernelGGL(add_parts_kernel, dim3(nseq, row_chunks(nseq)), dim3(256), 0, c->stream, (const float*)c->pf_xt, p, d, c->catD + (size_t)b0 * 2 * d, 2 * d,
+                       c->catDf, b0, g.batch);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
@@ -1443,7 +1614,7 @@ int do_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool sample) {
         for (int b = 0; b < B; ++b) max_keys = std::max(max_keys, c->h_dlen[b]);
         if (int rc = drafter_forward<WT>(c, c->catT, 0, B, K + 1, 0, 0, max_keys + K + 1, c->dout, d)) return rc;
     }
-    hipLaunchKernelGGL(select_row_kernel, dim3(B), dim3(256), 0, c->stream, (const float*)c->dout, K + 1, (const int32_t*)c->nacc, c->catD, 2 * d, c->dlen, d);
+    hipLaunchKernelGGL(select_row_kernel, dim3(B), dim3(256), 0, c->stream, (const float*)c->dout, K + 1, (const int32_t*)c->nacc, c->catD, 2 * d, c->dlen, d, c->catDf);
     HIP_TRY(c, hipGetLastError());
     pt.stop();
     const size_t nres = (size_t)B + (size_t)B * (g.k_max + 1);
@@ -1495,6 +1666,26 @@ void tree_rows_phases(hivis_ctx* c, int m, const float* cat, const int32_t* tok,
     const hivis_config& g = c->cfg;
     const int d = g.d, V = g.vocab;
     int* counters = (int*)pool.take(2 * g.n_q_heads);          // at most two row blocks of 8 per head
+    if (c->stream_rows) {
+        StreamRows u{pool.take((size_t)m * d), (uint4*)pool.take((size_t)m * d), pool.take((size_t)m * ssq_stride(d / 16)), d / 16};
+        Phase fu{}; fu.type = PH_GEMM; fu.pro = PRO_PLAIN; fu.epi = FEPI_ADDVEC; fu.K = d; fu.N = d; fu.W = c->fuse_w1; fu.Af = c->tcatf;
+        fu.Y = u.h; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = rho_idx; fu.add_rows = c->emb_w2; fu.tok = tok; fu.tok_sseq = 0; fu.tok_srow = 1;
+        fu.F = u.F; fu.fgain = c->draft.norm1; fu.ssq_out = u.ssq;
+        P.push_back(fu);
+        const size_t l0 = P.size();
+        uint4* outF = lm_out ? (uint4*)pool.take((size_t)m * d) : nullptr;
+        layer_stream<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, offset, 1, m, StreamRows{out, outF, nullptr, 0}, nullptr, c->attn_elect);
+        for (size_t i = l0; i < P.size(); ++i) {
+            P[i].pos_delta = tr.pos_delta; P[i].att.tmask = tr.mask;
+            if (P[i].type == PH_ATTN && c->attn_elect) P[i].cnt = counters;
+        }
+        if (lm_out) {
+            Phase lm{}; lm.type = PH_GEMM; lm.pro = PRO_PLAIN; lm.epi = FEPI_LOGITS; lm.K = d; lm.N = V; lm.W = c->lm_head; lm.Af = outF;
+            lm.Y = lm_out; lm.ldy = V; lm.pm = pool.take((size_t)m * c->fused_grid); lm.pi = (int*)pool.take((size_t)m * c->fused_grid);
+            P.push_back(lm);
+        }
+        return;
+    }
     float* u = pool.take((size_t)m * d);
     Phase fu{}; fu.type = PH_GEMM; fu.pro = PRO_PLAIN; fu.epi = FEPI_ADDVEC; fu.K = 2 * d; fu.N = d; fu.W = c->fuse_w; fu.A = cat; fu.lda = 2 * d;
     fu.Y = u; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = rho_idx;
@@ -1553,6 +1744,7 @@ int tree_setup(hivis_ctx* c) {
     if ((rc = dev_alloc(c, &c->tcat, (size_t)TREE_MAX_TOPK * 2 * d))) return rc;
     if ((rc = dev_alloc(c, &c->ttok_rows, TREE_MAX_TOPK))) return rc;
     if ((rc = dev_alloc(c, &c->troll, (size_t)(D + 1) * 2 * d))) return rc;
+    { float* f; if ((rc = dev_alloc(c, &f, (size_t)WTraits<bf16w_t>::ROWS * d))) return rc; c->tcatf = (uint4*)f; }
     c->tnseg = (V + TOPK_SEG - 1) / TOPK_SEG;
     if ((rc = dev_alloc(c, &c->tcand_v, (size_t)TREE_MAX_TOPK * c->tnseg * TREE_MAX_TOPK))) return rc;
     if ((rc = dev_alloc(c, &c->tcand_i, (size_t)TREE_MAX_TOPK * c->tnseg * TREE_MAX_TOPK))) return rc;
@@ -1580,7 +1772,8 @@ int tree_setup(hivis_ctx* c) {
         for (int m = 1; tree_program_ok<WT>(c, m); ++m) {
             std::vector<Phase> P;
             Pool count;
-            tree_rows_phases<WT>(c, m, nullptr, nullptr, 0, 0, TreeRows(), nullptr, nullptr, count, P);
+            float some = 0.f;            // (any address: the list with an LM head is the longer one)
+            tree_rows_phases<WT>(c, m, nullptr, nullptr, 0, 0, TreeRows(), nullptr, &some, count, P);
             most = std::max(most, count.used);
         }
         if ((rc = dev_alloc(c, &c->tree_pool, most))) return rc;
@@ -1613,7 +1806,7 @@ int do_tree_draft(hivis_ctx* c, int k, int depth, int N) {
         const int32_t* E = t.expand + n_prev;
         const bool program = tree_program_ok<WT>(c, k);
         hipLaunchKernelGGL((tree_expand_kernel<WT>), dim3(k), dim3(256), 0, c->stream, lo, n, k, n_prev, j, t, (const float*)c->tH,
-                           program && c->emb_w2 ? (const WT*)nullptr : (const WT*)c->embed, c->tcat, c->ttok_rows, d);
+                           program && c->emb_w2 ? (const WT*)nullptr : (const WT*)c->embed, c->tcat, c->ttok_rows, d, program && c->stream_rows ? c->tcatf : (uint4*)nullptr);
         TreeRows tr; tr.pos_delta = t.dpos + n_prev; tr.mask = t.dmask + n_prev;
         float* hid = c->tH + (size_t)row0 * d; float* lg = c->tlogits + (size_t)row0 * V;
         if (program) {
@@ -1670,10 +1863,10 @@ int do_tree_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool samp
     // drafter: every tree row is dropped (its length never advanced); depth+1 rows rebuilt from the true features
     const bool program = tree_program_ok<WT>(c, depth + 1);
     hipLaunchKernelGGL((tree_roll_cat_kernel<WT>), dim3(depth + 1), dim3(256), 0, c->stream, (const float*)c->catT, 2 * d, (const int32_t*)t.path,
-                       (const int32_t*)t.next_tok, program && c->emb_w2 ? (const WT*)nullptr : (const WT*)c->embed, c->troll, d);
+                       (const int32_t*)t.next_tok, program && c->emb_w2 ? (const WT*)nullptr : (const WT*)c->embed, c->troll, d, program && c->stream_rows ? c->tcatf : (uint4*)nullptr);
     if (program) { if (int rc = tree_rows_program<WT>(c, depth + 1, c->troll, t.next_tok, 0, 0, TreeRows(), c->dout, nullptr)) return rc; }
     else if (int rc = drafter_forward<WT>(c, c->troll, 0, 1, depth + 1, 0, 0, c->h_dlen[0] + depth + 1, c->dout, d)) return rc;
-    hipLaunchKernelGGL(tree_finish_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)c->dout, (const int32_t*)t.result, c->catD, c->dlen, c->tlen, d);
+    hipLaunchKernelGGL(tree_finish_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)c->dout, (const int32_t*)t.result, c->catD, c->dlen, c->tlen, d, c->catDf);
     HIP_TRY(c, hipGetLastError());
     pt.stop();
     HIP_TRY(c, hipMemcpyAsync(c->h_tree_result, t.result, (depth + 2) * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
@@ -1875,6 +2068,13 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     if ((rc = build_embed_fc_table<WT>(c, w))) return rc;
+    if (sizeof(WT) == 2 && c->fused && !c->persistent && c->emb_w2 && d <= STREAM_MAX_D) {
+        const int R16 = WTraits<bf16w_t>::ROWS;
+        float *f, *v;
+        if ((rc = dev_alloc(c, &f, (size_t)B * d)) || (rc = dev_alloc(c, &v, (size_t)R16 * d))) return rc;
+        c->catDf = (uint4*)f; c->vfrag = (uint4*)v;
+        c->stream_rows = true;
+    }
     return HIVIS_OK;
 }
 

@@ -72,6 +72,11 @@ struct Phase {
     const float* u; int u_sseq, u_idx;             // SAMPLE: uniform number of row (seq, i) = u[seq*u_sseq + u_idx]; logits rows in A (stride lda)
     const uint4* next_W; int next_K, next_N;       // GEMM: weights of the next GEMM phase of the program (prefetch), or null
     uint4* frag;                                   // ATTN with one key split, optional: the rows go out as A fragments of the next GEMM (K = ldy) instead of to Y
+    // phases on row fragments (stream_kernel, see hivis_stream.h): Af the activation rows; ssq their sums of squares in nssq parts per
+    // row (nssq 0: no norm); F, fgain, ssq_out: the results as row fragments, times a gain (optional), and the sums of squares per
+    // 16 columns.  ATTN: F instead of Y.
+    const uint4* Af; const float* ssq; int nssq;
+    uint4* F; const void* fgain; float* ssq_out;
 };
 
 struct PassParams {
@@ -165,16 +170,23 @@ template <int NW, int KBW> __device__ __forceinline__ int unit_nkb(int kblks, in
 // the compiler placed a copy, and before it a wait for everything in flight, behind the second load of a unit: every wavefront
 // waited a memory round trip before it requested the other fourteen.)  bf16: with the non-temporal hint, because a weight
 // is read by one workgroup, once per pass: a plain stream of 180 MB takes 27.2 us with it and 30.4 without, of 34 MB 6.4 and 7.0.
-// fp32 models (a few MB) are re-read from the L2: without.
 // Both together, C2 verify pass: gate|up 35.2 -> 32.0 us, q|k|v 22.6 -> 20.4, LM head 54.5 -> 49.3; with the hint alone 32.2, 21.5, 50.4.
+// fp32 models (a few MB, re-read from the L2, a block or two per wavefront) keep plain loads, a branch each: with the hint 2 % slower, with
+// buffer loads 1 %.
 template <typename WT, int U>
 __device__ __forceinline__ void issue_unit(uint4 (&wb)[U], const uint4* __restrict__ W, int kblks, int tile, int kb0,
                                            int nkb, int lane) {
-    typedef unsigned u4_t __attribute__((ext_vector_type(4)));
-    constexpr int HINT = std::is_same<WT, float>::value ? 0 : 2;         // 2: non-temporal
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)(W + ((size_t)tile * kblks + kb0) * 64), 0, nkb * 1024, 0x00020000);
+    const uint4* p = W + ((size_t)tile * kblks + kb0) * 64;
+    if constexpr (std::is_same<WT, float>::value) {
 #pragma unroll
-    for (int j = 0; j < U; ++j) { const u4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + j * 1024, 0, HINT); wb[j] = __builtin_bit_cast(uint4, v); }
+        for (int j = 0; j < U; ++j)
+            if (j < nkb) wb[j] = p[(size_t)j * 64 + lane]; else wb[j] = make_uint4(0, 0, 0, 0);
+    } else {
+        typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, nkb * 1024, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < U; ++j) { const u4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + j * 1024, 0, 2); wb[j] = __builtin_bit_cast(uint4, v); }      // 2: non-temporal
+    }
 }
 
 // tile row (MFMA A row) that holds activation row `row`: bf16 keeps hi at 4*(row/2) + row%2 and lo two rows below
@@ -711,26 +723,34 @@ __host__ __device__ constexpr size_t fused_attn_lds_floats(int hd, int nw, int r
 // that loads split after split spent 8-10 us here), which is why the split count is bounded at compile time.
 // wl: LDS scratch of 3 * ATTN_MAX_SPLITS * RM floats that nothing else uses until the routine returns.
 constexpr int ATTN_MAX_SPLITS = 16;
+// Destination of attention rows: fp32 rows, or row fragments of the O projection (rows = rows of the pass)
+struct AttnOut { float* y; int ldo; uint4* frag; int rows; };
+__device__ __forceinline__ void attn_store_pair(const AttnOut& o, int row, int col, float a, float b) {
+    if (o.frag) st_row_pair(o.frag, o.rows, row, col, a, b);
+    else st_wt_pair(&o.y[(size_t)row * o.ldo + col], a, b);
+}
+__device__ __forceinline__ float2 ld_agent2(const float* p) {
+    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
 template <int HD, int RM, int MAXS>
 __device__ __forceinline__ void attn_merge_splits_n(const float* __restrict__ pbase, int nsplit, int R, int ni, int head0, int i0, int sl,
-                                                    const AttnShape& sh, float* __restrict__ wl, float* __restrict__ att_out, int ldo) {
-    constexpr int PER = (RM * HD + FUSED_NT - 1) / FUSED_NT;       // output elements per thread
+                                                    const AttnShape& sh, float* __restrict__ wl, const AttnOut& out) {
+    constexpr int PER = (RM * HD / 2 + FUSED_NT - 1) / FUSED_NT;       // pairs of output elements per thread
     static_assert(MAXS * RM <= FUSED_NT, "one thread per (split, row) pair of statistics");
     float* wm = wl; float* wsum = wl + MAXS * RM; float* ww = wl + 2 * MAXS * RM;
-    float v[PER][MAXS];
+    float2 v[PER][MAXS];
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         const int idx = threadIdx.x + e * FUSED_NT;
-        const int r = min(idx / HD, R - 1), c = idx % HD;
+        const int r = min(idx / (HD / 2), R - 1), c = 2 * (idx % (HD / 2));
 #pragma unroll
-        for (int sp = 0; sp < MAXS; ++sp) v[e][sp] = ld_agent(&pbase[((size_t)min(sp, nsplit - 1) * RM + r) * (HD + 2) + c]);
+        for (int sp = 0; sp < MAXS; ++sp) v[e][sp] = ld_agent2(&pbase[((size_t)min(sp, nsplit - 1) * RM + r) * (HD + 2) + c]);
     }
     if ((int)threadIdx.x < MAXS * RM) {
         const int sp = threadIdx.x / RM, r = threadIdx.x % RM;
-        const float* p = pbase + ((size_t)min(sp, nsplit - 1) * RM + min(r, R - 1)) * (HD + 2);
-        const float ms = ld_agent(&p[HD]), ls = ld_agent(&p[HD + 1]);
+        const float2 st = ld_agent2(pbase + ((size_t)min(sp, nsplit - 1) * RM + min(r, R - 1)) * (HD + 2) + HD);
         const bool live = sp < nsplit && r < R;
-        wm[threadIdx.x] = live ? ms : -INFINITY; wsum[threadIdx.x] = live ? ls : 0.f;
+        wm[threadIdx.x] = live ? st.x : -INFINITY; wsum[threadIdx.x] = live ? st.y : 0.f;
     }
     lds_barrier();
     if ((int)threadIdx.x < MAXS * RM) {
@@ -751,13 +771,13 @@ __device__ __forceinline__ void attn_merge_splits_n(const float* __restrict__ pb
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         const int idx = threadIdx.x + e * FUSED_NT;
-        const int r = idx / HD, c = idx % HD;
+        const int r = idx / (HD / 2), c = 2 * (idx % (HD / 2));
         if (r < R) {
-            float o = 0.f;
+            float o0 = 0.f, o1 = 0.f;
 #pragma unroll
-            for (int sp = 0; sp < MAXS; ++sp) o += ww[sp * RM + r] * v[e][sp];
+            for (int sp = 0; sp < MAXS; ++sp) { const float w = ww[sp * RM + r]; o0 += w * v[e][sp].x; o1 += w * v[e][sp].y; }
             const int hh = head0 + r / ni, i = i0 + r % ni;
-            st_wt(&att_out[(size_t)(sl * sh.m + i) * ldo + (size_t)hh * HD + c], o);
+            attn_store_pair(out, sl * sh.m + i, hh * HD + c, o0, o1);
         }
     }
     lds_barrier();
@@ -765,10 +785,10 @@ __device__ __forceinline__ void attn_merge_splits_n(const float* __restrict__ pb
 // (the loads are unrolled to a compile-time bound: the smallest of 4 / 8 / 16 that holds the split count)
 template <int HD, int RM>
 __device__ __forceinline__ void attn_merge_splits(const float* __restrict__ pbase, int nsplit, int R, int ni, int head0, int i0, int sl,
-                                                  const AttnShape& sh, float* __restrict__ wl, float* __restrict__ att_out, int ldo) {
-    if (nsplit <= 4) attn_merge_splits_n<HD, RM, 4>(pbase, nsplit, R, ni, head0, i0, sl, sh, wl, att_out, ldo);
-    else if (nsplit <= 8) attn_merge_splits_n<HD, RM, 8>(pbase, nsplit, R, ni, head0, i0, sl, sh, wl, att_out, ldo);
-    else attn_merge_splits_n<HD, RM, ATTN_MAX_SPLITS>(pbase, nsplit, R, ni, head0, i0, sl, sh, wl, att_out, ldo);
+                                                  const AttnShape& sh, float* __restrict__ wl, const AttnOut& out) {
+    if (nsplit <= 4) attn_merge_splits_n<HD, RM, 4>(pbase, nsplit, R, ni, head0, i0, sl, sh, wl, out);
+    else if (nsplit <= 8) attn_merge_splits_n<HD, RM, 8>(pbase, nsplit, R, ni, head0, i0, sl, sh, wl, out);
+    else attn_merge_splits_n<HD, RM, ATTN_MAX_SPLITS>(pbase, nsplit, R, ni, head0, i0, sl, sh, wl, out);
 }
 // Tail shared by the attention variants: the NW per-wavefront partials in mrg ([NW][RM][HD + 2]: weighted value
 // sums, running maximum, sum of weights) are merged in wavefront order; with one key split the attention rows are
@@ -777,7 +797,7 @@ __device__ __forceinline__ void attn_merge_splits(const float* __restrict__ pbas
 template <int HD, int RM>
 __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, int* __restrict__ flag, const AttnShape& sh, int item_id, int split,
                                                int R, int ni, int head0, int i0, int sl, float* __restrict__ ws, int* __restrict__ cnt,
-                                               float* __restrict__ att_out, int ldo, unsigned long long* marks, uint4* __restrict__ frag_out = nullptr) {
+                                               const AttnOut& dst, unsigned long long* marks, uint4* __restrict__ frag_out = nullptr) {
     constexpr int NW = FUSED_NW;
     lds_barrier();
     HIVIS_AMARK(4)
@@ -806,29 +826,30 @@ __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, in
 #pragma unroll
             for (int e = 0; e < 8; ++e) y[e] = num[e] / den;
             const int hh = head0 + r / ni, i = i0 + r % ni;
-            store_afrag8(frag_out, ldo / 32, sl * sh.m + i, hh * HD + c0, y, false);
+            store_afrag8(frag_out, dst.ldo / 32, sl * sh.m + i, hh * HD + c0, y, false);
         }
         lds_barrier();
         return;
     }
     if (sh.nsplit == 1) {
         // the whole key range was handled here: merge the NW partials and write the attention rows directly
-        for (int idx = threadIdx.x; idx < R * HD; idx += FUSED_NT) {
-            const int r = idx / HD, c = idx % HD;
+        for (int idx = threadIdx.x; idx < R * (HD / 2); idx += FUSED_NT) {
+            const int r = idx / (HD / 2), c = 2 * (idx % (HD / 2));
             float mx = -INFINITY;
 #pragma unroll
             for (int w = 0; w < NW; ++w) mx = fmaxf(mx, mrg[(w * RM + r) * (HD + 2) + HD]);
-            float num = 0.f, den = 0.f;
+            float n0 = 0.f, n1 = 0.f, den = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
-                const float mw = mrg[(w * RM + r) * (HD + 2) + HD];
+                const float* src = mrg + (w * RM + r) * (HD + 2);
+                const float mw = src[HD];
                 if (mw != -INFINITY) {
                     const float e = __expf(mw - mx);
-                    num += mrg[(w * RM + r) * (HD + 2) + c] * e; den += mrg[(w * RM + r) * (HD + 2) + HD + 1] * e;
+                    n0 += src[c] * e; n1 += src[c + 1] * e; den += src[HD + 1] * e;
                 }
             }
             const int hh = head0 + r / ni, i = i0 + r % ni;
-            st_wt(&att_out[(size_t)(sl * sh.m + i) * ldo + (size_t)hh * HD + c], num / den);
+            attn_store_pair(dst, sl * sh.m + i, hh * HD + c, n0 / den, n1 / den);
         }
         lds_barrier();
         return;
@@ -873,7 +894,7 @@ __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, in
         if (!(sh.flags & 1)) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const float* pbase = ws + (size_t)item_id * sh.nsplit * RM * (HD + 2);
         // (the wavefront partials in mrg are dead since the barrier before the arrival: their space is the scratch)
-        attn_merge_splits<HD, RM>(pbase, sh.nsplit, R, ni, head0, i0, sl, sh, const_cast<float*>(mrg), att_out, ldo);
+        attn_merge_splits<HD, RM>(pbase, sh.nsplit, R, ni, head0, i0, sl, sh, const_cast<float*>(mrg), dst);
         if (threadIdx.x == 0) st_wt(&cnt[item_id], 0);
     }
     lds_barrier();
@@ -910,7 +931,7 @@ template <int HD, int RM>
 __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
                                              const int* __restrict__ base, const AttnShape& sh, int item_id, int split,
                                              float* __restrict__ lds, float* __restrict__ ws, int* __restrict__ cnt,
-                                             float* __restrict__ att_out, int ldo, unsigned long long* marks = nullptr,
+                                             const AttnOut& dst, unsigned long long* marks = nullptr,
                                              uint4* __restrict__ frag_out = nullptr) {
     HIVIS_AMARK(0)
     static_assert(RM <= 16 && HD % 32 == 0, "rows are the 16-wide MFMA dimension");
@@ -1089,7 +1110,7 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
         }
         if (g == 0) { mr[HD] = mrun; mr[HD + 1] = lsum; }
     }
-    attn_wg_finish<HD, RM>(mrg, flag, sh, item_id, split, R, ni, kvh * group + h0, i0, sl, ws, cnt, att_out, ldo, marks, frag_out);
+    attn_wg_finish<HD, RM>(mrg, flag, sh, item_id, split, R, ni, kvh * group + h0, i0, sl, ws, cnt, dst, marks, frag_out);
 }
 
 // The MFMA attention as a kernel of its own, with all 16 MFMA columns holding real (head,row) pairs: passes with many
@@ -1107,7 +1128,7 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_kernel(const float* __rest
     int item = blockIdx.x;
     const int nr = sh.n_rblk, ngrp = (int)gridDim.x / nr;
     if (nr > 1 && (ngrp & 7) == 0 && ngrp * nr == (int)gridDim.x) { const int x = item & 7, slot = item >> 3; item = (x + 8 * (slot / nr)) * nr + slot % nr; }
-    attn_wg_mfma<HD, ATTN_ROWS_RM>(q, kc, vc, base, sh, item, 0, attn_rows_lds, nullptr, nullptr, out, ldo, nullptr, frag_out);
+    attn_wg_mfma<HD, ATTN_ROWS_RM>(q, kc, vc, base, sh, item, 0, attn_rows_lds, nullptr, nullptr, AttnOut{out, ldo, nullptr, 0}, nullptr, frag_out);
 }
 
 // Attention of long row ranges (prefill): the published flash-attention work split.  A workgroup of NW wavefronts owns
@@ -1299,7 +1320,7 @@ template <typename KT, int HD, int RM, int RC>
 __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, const KT* __restrict__ kc, const KT* __restrict__ vc,
                                                 const int* __restrict__ base, const AttnShape& sh, int item_id, int split,
                                                 float* __restrict__ lds, float* __restrict__ ws, int* __restrict__ cnt,
-                                                float* __restrict__ att_out, int ldo, unsigned long long* marks = nullptr) {
+                                                const AttnOut& dst, unsigned long long* marks = nullptr) {
     HIVIS_AMARK(0)
     constexpr int NW = FUSED_NW;
     constexpr int ROWB = HD * (int)sizeof(KT);     // bytes of one cached row
@@ -1452,14 +1473,14 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
             if (lane == 0) { mrg[(wave * RM + r) * (HD + 2) + HD] = mrun[r]; mrg[(wave * RM + r) * (HD + 2) + HD + 1] = lsum; }
         }
     }
-    attn_wg_finish<HD, RM>(mrg, reinterpret_cast<int*>(pw_all), sh, item_id, split, R, ni, kvh * group + h0, i0, sl, ws, cnt, att_out, ldo, marks);
+    attn_wg_finish<HD, RM>(mrg, reinterpret_cast<int*>(pw_all), sh, item_id, split, R, ni, kvh * group + h0, i0, sl, ws, cnt, dst, marks);
 #undef HIVIS_ATTN_LOADS
 }
 
 // Merge of the nsplit workgroup partials of one item, in split order; writes the attention output rows.
 template <int HD, int RM>
 __device__ __forceinline__ void attn_wg_merge(const float* __restrict__ ws, const AttnShape& sh, int item_id,
-                                              float* __restrict__ lds, float* __restrict__ out, int ldo) {
+                                              float* __restrict__ lds, const AttnOut& out) {
     int item = item_id;
     const int rblk = item % sh.n_rblk; item /= sh.n_rblk;
     const int hblk = item % sh.n_hblk; item /= sh.n_hblk;
@@ -1470,7 +1491,7 @@ __device__ __forceinline__ void attn_wg_merge(const float* __restrict__ ws, cons
     const int i0 = rblk * sh.mi, ni = min(sh.mi, sh.m - i0);
     const int R = nh * ni;
     const float* base = ws + (size_t)item_id * sh.nsplit * RM * (HD + 2);
-    attn_merge_splits<HD, RM>(base, sh.nsplit, R, ni, kvh * group + h0, i0, sl, sh, lds, out, ldo);
+    attn_merge_splits<HD, RM>(base, sh.nsplit, R, ni, kvh * group + h0, i0, sl, sh, lds, out);
 }
 
 // One phase, executed by the calling grid (every workgroup calls this with the same arguments).
@@ -1484,6 +1505,7 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
         if constexpr (TYPE < 0 || TYPE == PH_GEMM) gemm_phase<WT, EPI, SINGLE>(ph, pp, lds, head, head_valid, wb1, wb1_valid, p);
         break;
     case PH_ATTN: {
+        const AttnOut dst = {ph.Y, ph.ldy, ph.F, pp.M};
         // (item, split) of a workgroup.  Default: split-minor.  flags & 2: every split of an item on ONE XCD (workgroup w
         // runs on XCD w % 8): XCD x works on the items x, x + 8, ..., so an item's partials meet in one L2.
         const int nsp = ph.att.nsplit;
@@ -1494,12 +1516,12 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
             if (xcd_map) { const int j = w >> 3; item = (w & 7) + 8 * (j / nsp); split = j % nsp; if (item >= ph.att_items) continue; }
             else { item = w / nsp; split = w % nsp; }
             if constexpr (std::is_same<KT, f16_t>::value) {
-                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2, ph.frag);
-                else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2, ph.frag);
+                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
+                else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
             } else {
                 // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
                 const bool one = ph.att.gh * ph.att.mi == 1;
-#define HIVIS_ATTN_F32(HD_, RC_) attn_wg_partial<KT, HD_, FUSED_RMAX, RC_>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, ph.Y, ph.ldy, pp.prof2)
+#define HIVIS_ATTN_F32(HD_, RC_) attn_wg_partial<KT, HD_, FUSED_RMAX, RC_>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2)
                 if (pp.hd == 128) { if (one) HIVIS_ATTN_F32(128, 1); else HIVIS_ATTN_F32(128, FUSED_RMAX); }
                 else if (one) HIVIS_ATTN_F32(64, 1);
                 else HIVIS_ATTN_F32(64, FUSED_RMAX);
@@ -1510,8 +1532,8 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
     case PH_ATTN_MERGE:
         if (pp.prof2 && blockIdx.x == 0 && threadIdx.x == 0) pp.prof2[0] = wall_clock64();
         for (int item = blockIdx.x; item < ph.att_items; item += gridDim.x) {
-            if (pp.hd == 128) attn_wg_merge<128, FUSED_RMAX>(ph.ws, ph.att, item, lds, ph.Y, ph.ldy);
-            else attn_wg_merge<64, FUSED_RMAX>(ph.ws, ph.att, item, lds, ph.Y, ph.ldy);
+            if (pp.hd == 128) attn_wg_merge<128, FUSED_RMAX>(ph.ws, ph.att, item, lds, AttnOut{ph.Y, ph.ldy, ph.F, pp.M});
+            else attn_wg_merge<64, FUSED_RMAX>(ph.ws, ph.att, item, lds, AttnOut{ph.Y, ph.ldy, ph.F, pp.M});
         }
         break;
     case PH_PREP: {

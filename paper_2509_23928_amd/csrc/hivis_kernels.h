@@ -106,6 +106,15 @@ __device__ __forceinline__ void st_wt_kv_pair(_Float16* row, int HD, int c, floa
     st_wt(reinterpret_cast<uint32_t*>(row + HD + c), __builtin_bit_cast(uint32_t, lo));
 }
 
+// two adjacent values k, k + 1 (k even) of row `row` of M as row fragments (layout: hivis_stream.h)
+__device__ __forceinline__ void st_row_pair(uint4* __restrict__ frag, int M, int row, int k, float a, float b) {
+    uint32_t hi, lo;
+    f32_to_bf16x2_hilo(a, b, hi, lo);
+    uint32_t* p = reinterpret_cast<uint32_t*>(frag + ((size_t)(k >> 5) * M + row) * 8 + ((k >> 3) & 3)) + ((k >> 1) & 3);
+    st_wt(p, hi);
+    st_wt(p + 16, lo);
+}
+
 // KV-cache storage that goes with a weight type.  fp32 models keep K and V in fp32.  bf16 models keep every cached
 // value as TWO IEEE halves, hi = half(x) and lo = half(x - hi) (about 22 mantissa bits), in one row of 2*HD halves:
 // [hi 0..HD) | lo 0..HD)].  Both halves are MFMA operands as they are.  One half alone is not enough at depth: the
@@ -1325,11 +1334,16 @@ __global__ __launch_bounds__(ACCEPT_NT) void accept_sample_kernel(const int32_t*
 }
 
 // After the re-feed: the drafter's pending hidden state is its output at row n_b; its cache keeps n_b+1 rows.
+// (frag, optional: the row as row fragments as well, row b of gridDim.x)
 __global__ void select_row_kernel(const float* __restrict__ dout, int m, const int32_t* __restrict__ nacc,
-                                  float* __restrict__ fnext, int ldf, int* __restrict__ dlen, int d) {
+                                  float* __restrict__ fnext, int ldf, int* __restrict__ dlen, int d, uint4* __restrict__ frag) {
     const int b = blockIdx.x;
     const int n = nacc[b];
-    for (int c = threadIdx.x; c < d; c += blockDim.x) fnext[(size_t)b * ldf + c] = dout[((size_t)b * m + n) * d + c];
+    for (int c = 2 * threadIdx.x; c < d; c += 2 * blockDim.x) {
+        const float2 x = *reinterpret_cast<const float2*>(dout + ((size_t)b * m + n) * d + c);
+        *reinterpret_cast<float2*>(fnext + (size_t)b * ldf + c) = x;
+        if (frag) st_row_pair(frag, gridDim.x, b, c, x.x, x.y);
+    }
     if (threadIdx.x == 0) dlen[b] += n + 1;
 }
 

@@ -185,10 +185,12 @@ __global__ __launch_bounds__(CHILD_NT) void tree_children_kernel(const float* __
 // The k best-scored of the n nodes [lo, lo + n) of one level become the drafter's tree rows n_prev .. n_prev + k - 1
 // (rank order), and row rank's fusion input [hidden row the node was drawn from ; Embed(node token)] is written to cat, its token
 // to tok.  One workgroup per rank, n <= 256: each ranks all nodes (a launch of its own for that cost more than the k-fold
-// counting).  table == nullptr: the embedding half is not needed (it comes from the fusion FC's table).
+// counting).  table == nullptr: the embedding half is not needed (it comes from the fusion FC's table).  frag != nullptr: the hidden
+// rows go there as row fragments (of k rows) instead of to cat.
 template <typename WT>
 __global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, int n_prev, int level, TreeDev t, const float* __restrict__ H,
-                                                          const WT* __restrict__ table, float* __restrict__ cat, int32_t* __restrict__ tok, int d) {
+                                                          const WT* __restrict__ table, float* __restrict__ cat, int32_t* __restrict__ tok, int d,
+                                                          uint4* __restrict__ frag) {
     __shared__ float s[256];
     __shared__ int pick[2];                  // hidden row, token
     const int i = threadIdx.x, want = blockIdx.x;
@@ -211,6 +213,10 @@ __global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, 
     }
     __syncthreads();
     const float4* h = reinterpret_cast<const float4*>(H + (size_t)pick[0] * d);
+    if (frag) {
+        for (int c = i; c < d / 4; c += 256) { const float4 x = h[c]; st_row_pair(frag, k, want, 4 * c, x.x, x.y); st_row_pair(frag, k, want, 4 * c + 2, x.z, x.w); }
+        return;
+    }
     float* o = cat + (size_t)want * 2 * d;
     for (int c = i; c < d / 4; c += 256) reinterpret_cast<float4*>(o)[c] = h[c];
     if (table) {
@@ -321,13 +327,20 @@ __global__ void tree_kv_gather_kernel(KT* const* __restrict__ kv, int maxL, int 
 }
 
 // Re-feed rows after acceptance: [true feature of path row e ; Embed(token after it)], e = 0..depth (rows beyond the
-// accepted length repeat the last one and are dead).  g: verify features, row stride ldg.  table == nullptr as above.
+// accepted length repeat the last one and are dead).  g: verify features, row stride ldg.  table, frag as above (gridDim.x rows).
 template <typename WT>
 __global__ void tree_roll_cat_kernel(const float* __restrict__ g, int ldg, const int32_t* __restrict__ path,
                                      const int32_t* __restrict__ next_tok, const WT* __restrict__ table,
-                                     float* __restrict__ cat, int d) {
+                                     float* __restrict__ cat, int d, uint4* __restrict__ frag) {
     const int e = blockIdx.x;
     const float4* f = reinterpret_cast<const float4*>(g + (size_t)path[e] * ldg);
+    if (frag) {
+        for (int c = threadIdx.x; c < d / 4; c += blockDim.x) {
+            const float4 x = f[c];
+            st_row_pair(frag, gridDim.x, e, 4 * c, x.x, x.y); st_row_pair(frag, gridDim.x, e, 4 * c + 2, x.z, x.w);
+        }
+        return;
+    }
     float* o = cat + (size_t)e * 2 * d;
     for (int c = threadIdx.x; c < d / 4; c += blockDim.x) reinterpret_cast<float4*>(o)[c] = f[c];
     if (table) {
@@ -338,9 +351,13 @@ __global__ void tree_roll_cat_kernel(const float* __restrict__ g, int ldg, const
 
 // After the re-feed: pending hidden state = drafter output at row n; both caches keep n + 1 more rows.
 __global__ void tree_finish_kernel(const float* __restrict__ dout, const int32_t* __restrict__ result, float* __restrict__ fnext,
-                                   int* __restrict__ dlen, int* __restrict__ tlen, int d) {
+                                   int* __restrict__ dlen, int* __restrict__ tlen, int d, uint4* __restrict__ frag) {
     const int n = result[0];
-    for (int c = threadIdx.x; c < d; c += blockDim.x) fnext[c] = dout[(size_t)n * d + c];
+    for (int c = 2 * threadIdx.x; c < d; c += 2 * blockDim.x) {
+        const float2 x = *reinterpret_cast<const float2*>(dout + (size_t)n * d + c);
+        *reinterpret_cast<float2*>(fnext + c) = x;
+        if (frag) st_row_pair(frag, 1, 0, c, x.x, x.y);
+    }
     if (threadIdx.x == 0) { dlen[0] += n + 1; tlen[0] += n + 1; }
 }
 
@@ -441,12 +458,14 @@ __global__ void fuse_frag_kernel(const float* __restrict__ feat, int fstride, in
         for (int k = threadIdx.x; k < d; k += blockDim.x) h[(size_t)row * d + k] = to_f32(rho[k]) + (tab ? tab[(size_t)tok * d + k] : 0.f);
 }
 
-// out row = h row + sum of the partials (d a multiple of 4)
-__global__ void add_parts_kernel(const float* __restrict__ h, Parts ps, int d, float* __restrict__ out, int ldo) {
+// out row = h row + sum of the partials (d a multiple of 4); frag (optional): the row as row fragments as well, row row0 + r of `rows`
+__global__ void add_parts_kernel(const float* __restrict__ h, Parts ps, int d, float* __restrict__ out, int ldo, uint4* __restrict__ frag, int row0, int rows) {
     const int row = blockIdx.x;
     for (int c4 = blockIdx.y * blockDim.x + threadIdx.x; c4 < d / 4; c4 += gridDim.y * blockDim.x) {
         const float4 a = *reinterpret_cast<const float4*>(h + (size_t)row * d + 4 * c4), b = parts_load4(ps, (size_t)row * d + 4 * c4);
-        *reinterpret_cast<float4*>(out + (size_t)row * ldo + 4 * c4) = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+        const float4 y = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+        *reinterpret_cast<float4*>(out + (size_t)row * ldo + 4 * c4) = y;
+        if (frag) { st_row_pair(frag, rows, row0 + row, 4 * c4, y.x, y.y); st_row_pair(frag, rows, row0 + row, 4 * c4 + 2, y.z, y.w); }
     }
 }
 
