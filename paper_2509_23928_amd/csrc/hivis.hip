@@ -562,7 +562,9 @@ AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, 
     sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
     sh.seq0 = 0; sh.offset = offset; sh.maxL = maxL; sh.ldq = ldq; sh.nwaves = FUSED_NW;
     const int items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
-    sh.nsplit = std::min(ATTN_MAX_SPLITS, std::max(1, c->fused_grid / items));
+    // (with the splits of an item on one XCD the grid holds whole rounds of eight items: more workgroups than CUs would take two turns,
+    // 14.4 -> 23.5 us for 28 items in nine splits)
+    sh.nsplit = std::min(ATTN_MAX_SPLITS, std::max(1, c->fused_grid / ((c->attn_flags & 2) ? (items + 7) / 8 * 8 : items)));
     *items_out = items;
     return sh;
 }
@@ -931,6 +933,18 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                 // tiles of a workgroup in groups of at most 8, as even as they come (a kernel of fewer tiles takes more groups)
                 const int most = (ph.N / 16 + grid - 1) / grid, group = (most + (most + 7) / 8 - 1) / ((most + 7) / 8);
                 const bool sh = ph.K <= STREAM_SHORT_K;
+                if constexpr (std::is_same<WT, bf16w_t>::value) {
+                    // 9..16 rows and at most half as many tiles as CUs: a second workgroup per tile, each with half the rows in the 8-row form
+                    // (half the fragments through a CU's address pipeline; the tile's weights come from the L2 once).  2048 columns, 12 rows:
+                    // down (K = 5632) 14.1 -> 10.8 us, O 6.6 -> 6.0.
+                    if ((ph.epi == FEPI_ADD_TO || ph.epi == FEPI_ADDVEC) && 2 * grid <= c->fused_grid && grid == ph.N / 16) {
+#define HIVIS_HALVES(EP, SH_) hipExtLaunchKernelGGL((stream_kernel<bf16_t, EP, 1, SH_>), dim3(2 * grid), dim3(FUSED_NT), stream_lds_floats(1, WTraits<bf16_t>::RPL) * sizeof(float), c->stream, kev0, kev1, 0, ph, ppl)
+                        if (ph.epi == FEPI_ADD_TO) { if (sh) HIVIS_HALVES(FEPI_ADD_TO, true); else HIVIS_HALVES(FEPI_ADD_TO, false); }
+                        else { if (sh) HIVIS_HALVES(FEPI_ADDVEC, true); else HIVIS_HALVES(FEPI_ADDVEC, false); }
+#undef HIVIS_HALVES
+                        continue;
+                    }
+                }
 #define HIVIS_STREAM_(EP, G_, SH_) hipExtLaunchKernelGGL((stream_kernel<WT, EP, G_, SH_>), dim3(grid), dim3(FUSED_NT), stream_lds_floats(G_, WTraits<WT>::RPL) * sizeof(float), c->stream, kev0, kev1, 0, ph, ppl)
 #define HIVIS_STREAM(EP, G_) HIVIS_STREAM_(EP, G_, false)
 #define HIVIS_STREAM2(EP, G_) do { if (sh) HIVIS_STREAM_(EP, G_, true); else HIVIS_STREAM_(EP, G_, false); } while (0)
@@ -1614,14 +1628,13 @@ int do_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool sample) {
         for (int b = 0; b < B; ++b) max_keys = std::max(max_keys, c->h_dlen[b]);
         if (int rc = drafter_forward<WT>(c, c->catT, 0, B, K + 1, 0, 0, max_keys + K + 1, c->dout, d)) return rc;
     }
-    hipLaunchKernelGGL(select_row_kernel, dim3(B), dim3(256), 0, c->stream, (const float*)c->dout, K + 1, (const int32_t*)c->nacc, c->catD, 2 * d, c->dlen, d, c->catDf);
+    const size_t nres = (size_t)B + (size_t)B * (g.k_max + 1);
+    hipLaunchKernelGGL(select_row_kernel, dim3(B), dim3(256), 0, c->stream, (const float*)c->dout, K + 1, (const int32_t*)c->nacc, c->catD, 2 * d, c->dlen, d, c->catDf,
+                       c->h_result, (int)nres, (const int*)c->bad);
     HIP_TRY(c, hipGetLastError());
     pt.stop();
-    const size_t nres = (size_t)B + (size_t)B * (g.k_max + 1);
-    HIP_TRY(c, hipMemcpyAsync(c->h_result, c->nacc, nres * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     c->h_result[nres] = 0;
     if (c->fused && c->persistent) HIP_TRY(c, hipMemcpyAsync(c->h_result + nres, c->bar + 1, sizeof(unsigned), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->h_result + nres + 1, c->bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     // Either flag means the device state (lengths, text) has already moved on from something invalid while the host
     // mirrors have not: the context is put back to "created", which only a new hivis_prefill leaves.
@@ -1866,11 +1879,10 @@ int do_tree_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool samp
                        (const int32_t*)t.next_tok, program && c->emb_w2 ? (const WT*)nullptr : (const WT*)c->embed, c->troll, d, program && c->stream_rows ? c->tcatf : (uint4*)nullptr);
     if (program) { if (int rc = tree_rows_program<WT>(c, depth + 1, c->troll, t.next_tok, 0, 0, TreeRows(), c->dout, nullptr)) return rc; }
     else if (int rc = drafter_forward<WT>(c, c->troll, 0, 1, depth + 1, 0, 0, c->h_dlen[0] + depth + 1, c->dout, d)) return rc;
-    hipLaunchKernelGGL(tree_finish_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)c->dout, (const int32_t*)t.result, c->catD, c->dlen, c->tlen, d, c->catDf);
+    hipLaunchKernelGGL(tree_finish_kernel, dim3(1), dim3(256), 0, c->stream, (const float*)c->dout, (const int32_t*)t.result, c->catD, c->dlen, c->tlen, d, c->catDf,
+                       c->h_tree_result, depth + 2, (const int*)c->bad, TREE_MAX_DEPTH + 2);
     HIP_TRY(c, hipGetLastError());
     pt.stop();
-    HIP_TRY(c, hipMemcpyAsync(c->h_tree_result, t.result, (depth + 2) * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->h_tree_result + TREE_MAX_DEPTH + 2, c->bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     resolve_phase_events(c);
     if (c->h_tree_result[TREE_MAX_DEPTH + 2]) { c->state = ST_CREATED; return fail(c, HIVIS_EINVAL, "a pass produced logits without a finite maximum (NaN or Inf in the inputs or weights); prefill again"); }

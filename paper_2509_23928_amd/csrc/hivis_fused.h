@@ -93,6 +93,10 @@ struct PassParams {
     unsigned long long* prof;       // optional [nphases][3] timestamps of workgroup 0 (phase start, phase end, barrier end), 100 MHz
 };
 
+// sequence of a row, and the row within it (a division by a run-time value takes some forty dependent instructions: not for one sequence)
+__device__ __forceinline__ int seq_of(const PassParams& pp, int row) { return pp.nseq == 1 ? 0 : row / pp.m; }
+__device__ __forceinline__ int row_in_seq(const PassParams& pp, int row) { return pp.nseq == 1 ? row : row % pp.m; }
+
 // Grid-wide barrier.  Every thread first waits until its own write-through stores have been acknowledged (a GEMM
 // phase has done so itself before requesting the next phase's weights: stores_drained), then one thread arrives and spins; bounded: on timeout the abort flag is raised and every workgroup leaves.  No
 // cache write-back or invalidation is needed (see the memory discipline above).  Returns false
@@ -270,7 +274,7 @@ __device__ __forceinline__ void lm_head_elect(const Phase& ph, const PassParams&
 // rotary position of a row relative to its sequence's cache length (bf16w: passes over the rows of a draft tree as well)
 template <typename WT> __device__ __forceinline__ int rope_offset(const Phase& ph, const PassParams& pp, int row) {
     if constexpr (std::is_same<WT, bf16w_t>::value) { if (ph.pos_delta) return ph.pos_delta[row]; }
-    return ph.offset + row % pp.m;
+    return ph.offset + row_in_seq(pp, row);
 }
 
 // GEMM phase (rows <= one MFMA tile).  Work split as in gemm_skinny_kernel: the
@@ -326,8 +330,8 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     // evenly, the workgroups with one tile more must be spread over all XCDs (each has its own L2 and memory path):
     // XCD x takes the contiguous share [x * grid/8, (x+1) * grid/8) of the virtual workgroup order.
     const int vb = (gridDim.x % 8 == 0) ? (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) : (int)blockIdx.x;
-    const int t_begin = __builtin_amdgcn_readfirstlane((int)(((long long)vb * ntiles) / gridDim.x));
-    const int t_end = __builtin_amdgcn_readfirstlane((int)(((long long)(vb + 1) * ntiles) / gridDim.x));
+    const int t_begin = __builtin_amdgcn_readfirstlane((int)((unsigned)vb * (unsigned)ntiles / gridDim.x));
+    const int t_end = __builtin_amdgcn_readfirstlane((int)((unsigned)(vb + 1) * (unsigned)ntiles / gridDim.x));
     const int ntl = t_end - t_begin;
     const int npass = (kblks + NW * KBW - 1) / (NW * KBW);
     const WT* gain = (ph.pro == PRO_RMS) ? (const WT*)ph.gain : nullptr;
@@ -348,8 +352,8 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
 
     // first units of the next GEMM phase for this wavefront (persistent mode only: requested at the end of this phase)
     const int n_kblks = ph.next_K / KB, n_ntiles = ph.next_N / 16;
-    const int n_tile = __builtin_amdgcn_readfirstlane(ph.next_W ? (int)(((long long)vb * n_ntiles) / gridDim.x) : 0);
-    const int n_tend = __builtin_amdgcn_readfirstlane(ph.next_W ? (int)(((long long)(vb + 1) * n_ntiles) / gridDim.x) : 0);
+    const int n_tile = __builtin_amdgcn_readfirstlane(ph.next_W ? (int)((unsigned)vb * (unsigned)n_ntiles / gridDim.x) : 0);
+    const int n_tend = __builtin_amdgcn_readfirstlane(ph.next_W ? (int)((unsigned)(vb + 1) * (unsigned)n_ntiles / gridDim.x) : 0);
     const bool n_has = ph.next_W && n_tile < n_tend;
     const int n_npass = (n_kblks + NW * KBW - 1) / (NW * KBW);
     // The unit order of a phase is tile-inner, pass-outer within a tile group.  `head` holds the first unit and
@@ -561,7 +565,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             else if (epi == FEPI_ADDVEC && ph.add_rows != nullptr) epi_a[sl] = ph.add_rows[(size_t)clamp_token(tok_e, pp.V) * N + col];
             else if (epi == FEPI_QKV) {
                 const int p2 = (col % pp.hd) >> 1;
-                const int seq_ = row / pp.m;
+                const int seq_ = seq_of(pp, row);
                 const int pos_ = min((ph.att.nbase > 0 ? ph.att.base_val[seq_] : ph.base[seq_]) + rope_offset<WT>(ph, pp, row), ph.maxL - 1);
                 const float2 cs_ = *reinterpret_cast<const float2*>(ph.rope + ((size_t)pos_ * (pp.hd / 2) + p2) * 2);
                 epi_a[sl] = cs_.x; epi_b[sl] = cs_.y;
@@ -642,8 +646,8 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             case FEPI_QKV: {
                 // every even column handles the pair (col, col+1): a rotary pair of q or k, or two v elements
                 const int qd = pp.Hq * pp.hd, kd = pp.Hkv * pp.hd, hd = pp.hd;
-                const int seq = row / pp.m;
-                const int pos = min((ph.att.nbase > 0 ? ph.att.base_val[seq] : ph.base[seq]) + ph.offset + row % pp.m, ph.maxL - 1);
+                const int seq = seq_of(pp, row);
+                const int pos = min((ph.att.nbase > 0 ? ph.att.base_val[seq] : ph.base[seq]) + ph.offset + row_in_seq(pp, row), ph.maxL - 1);
                 if ((cl & 1) == 0) {
                     float x1 = v, x2 = tile[idx + RPL] * sc;
                     if (ph.bias) { x1 += ph.bias[col]; x2 += ph.bias[col + 1]; }
@@ -723,6 +727,22 @@ __host__ __device__ constexpr size_t fused_attn_lds_floats(int hd, int nw, int r
 // that loads split after split spent 8-10 us here), which is why the split count is bounded at compile time.
 // wl: LDS scratch of 3 * ATTN_MAX_SPLITS * RM floats that nothing else uses until the routine returns.
 constexpr int ATTN_MAX_SPLITS = 16;
+// An attention item's row block, head block, key head and sequence; quotients by run-time values only where they are needed (some forty
+// dependent instructions each: the attention kernels spent their first microsecond on them)
+struct AttnItem { int rblk, hblk, kvh, sl, group; };
+__device__ __forceinline__ int div_pow2(int a, int b) { return (b & (b - 1)) == 0 ? a >> (31 - __clz(b)) : a / b; }
+__device__ __forceinline__ AttnItem attn_item(const AttnShape& sh, int item) {
+    AttnItem it = {0, 0, item, 0, 1};
+    if (sh.n_rblk > 1) { const int q = item / sh.n_rblk; it.rblk = item - q * sh.n_rblk; item = q; }
+    if (sh.n_hblk > 1) { const int q = item / sh.n_hblk; it.hblk = item - q * sh.n_hblk; item = q; }
+    it.kvh = item;
+    if (item >= sh.Hkv) { it.sl = item / sh.Hkv; it.kvh = item - it.sl * sh.Hkv; }
+    if (sh.Hq != sh.Hkv) it.group = sh.Hq / sh.Hkv;
+    return it;
+}
+// head and row of pair r of an item with ni rows, R pairs
+__device__ __forceinline__ void attn_pair(int r, int ni, int R, int& h, int& i) { h = 0; i = r; if (ni < R) { h = r / ni; i = r - h * ni; } }
+
 // Destination of attention rows: fp32 rows, or row fragments of the O projection (rows = rows of the pass)
 struct AttnOut { float* y; int ldo; uint4* frag; int rows; };
 __device__ __forceinline__ void attn_store_pair(const AttnOut& o, int row, int col, float a, float b) {
@@ -731,6 +751,9 @@ __device__ __forceinline__ void attn_store_pair(const AttnOut& o, int row, int c
 }
 __device__ __forceinline__ float2 ld_agent2(const float* p) {
     return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void st_wt2(float* p, float a, float b) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, make_float2(a, b)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <int HD, int RM, int MAXS>
 __device__ __forceinline__ void attn_merge_splits_n(const float* __restrict__ pbase, int nsplit, int R, int ni, int head0, int i0, int sl,
@@ -776,8 +799,9 @@ __device__ __forceinline__ void attn_merge_splits_n(const float* __restrict__ pb
             float o0 = 0.f, o1 = 0.f;
 #pragma unroll
             for (int sp = 0; sp < MAXS; ++sp) { const float w = ww[sp * RM + r]; o0 += w * v[e][sp].x; o1 += w * v[e][sp].y; }
-            const int hh = head0 + r / ni, i = i0 + r % ni;
-            attn_store_pair(out, sl * sh.m + i, hh * HD + c, o0, o1);
+            int h, i;
+            attn_pair(r, ni, R, h, i);
+            attn_store_pair(out, sl * sh.m + i0 + i, (head0 + h) * HD + c, o0, o1);
         }
     }
     lds_barrier();
@@ -848,31 +872,32 @@ __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, in
                     n0 += src[c] * e; n1 += src[c + 1] * e; den += src[HD + 1] * e;
                 }
             }
-            const int hh = head0 + r / ni, i = i0 + r % ni;
-            attn_store_pair(dst, sl * sh.m + i, hh * HD + c, n0 / den, n1 / den);
+            int h, i;
+            attn_pair(r, ni, R, h, i);
+            attn_store_pair(dst, sl * sh.m + i0 + i, (head0 + h) * HD + c, n0 / den, n1 / den);
         }
         lds_barrier();
         return;
     }
     // ---- merge the NW partials (fixed order) and write ONE partial of this workgroup
     float* out = ws + ((size_t)item_id * sh.nsplit + split) * RM * (HD + 2);
-    for (int idx = threadIdx.x; idx < R * (HD + 2); idx += FUSED_NT) {
-        const int r = idx / (HD + 2), c = idx % (HD + 2);
+    for (int idx = threadIdx.x; idx < R * (HD / 2); idx += FUSED_NT) {
+        const int r = idx / (HD / 2), c = 2 * (idx % (HD / 2));
         float mx = -INFINITY;
 #pragma unroll
         for (int w = 0; w < NW; ++w) mx = fmaxf(mx, mrg[(w * RM + r) * (HD + 2) + HD]);
-        float v;
-        if (c == HD) v = mx;
-        else {
-            v = 0.f;
-            const int cc = (c == HD + 1) ? HD + 1 : c;
+        float n0 = 0.f, n1 = 0.f, den = 0.f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float mw = mrg[(w * RM + r) * (HD + 2) + HD];
-                if (mw != -INFINITY) v += mrg[(w * RM + r) * (HD + 2) + cc] * __expf(mw - mx);
+        for (int w = 0; w < NW; ++w) {
+            const float* src = mrg + (w * RM + r) * (HD + 2);
+            const float mw = src[HD];
+            if (mw != -INFINITY) {
+                const float e = __expf(mw - mx);
+                n0 += src[c] * e; n1 += src[c + 1] * e; den += src[HD + 1] * e;
             }
         }
-        st_wt(&out[r * (HD + 2) + c], v);
+        st_wt2(&out[r * (HD + 2) + c], n0, n1);
+        if (c == 0) st_wt2(&out[r * (HD + 2) + HD], mx, den);
     }
     HIVIS_AMARK(5)
     if (cnt == nullptr) { lds_barrier(); return; }        // the partials are merged by a separate phase
@@ -954,19 +979,15 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
     float* mrg = lds;                                               // [NW][RM][HD + 2] per-wavefront partials: same space, after the loop
     int* flag = reinterpret_cast<int*>(lds + fused_attn_mfma_lds_floats(HD, NW, RM) - 16);
 
-    int item = item_id;
-    const int rblk = item % sh.n_rblk; item /= sh.n_rblk;
-    const int hblk = item % sh.n_hblk; item /= sh.n_hblk;
-    const int kvh = item % sh.Hkv;
-    const int sl = item / sh.Hkv;
+    const AttnItem it = attn_item(sh, item_id);
+    const int rblk = it.rblk, hblk = it.hblk, kvh = it.kvh, sl = it.sl, group = it.group;
     const int seq = sh.seq0 + sl;
-    const int group = sh.Hq / sh.Hkv;
     const int h0 = hblk * sh.gh, nh = min(sh.gh, group - h0);
     const int i0 = rblk * sh.mi, ni = min(sh.mi, sh.m - i0);
     const int R = nh * ni;
     const int pos0 = (sh.nbase > 0 ? sh.base_val[sl] : base[seq]) + sh.offset;
     const int nkeys = min(pos0 + i0 + ni, sh.maxL);
-    const int cs = ((nkeys + sh.nsplit - 1) / sh.nsplit + 15) & ~15;        // keys per split, multiple of 16
+    const int cs = (div_pow2(nkeys + sh.nsplit - 1, sh.nsplit) + 15) & ~15;        // keys per split, multiple of 16
     const int k0 = split * cs, k1 = min(nkeys, k0 + cs);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront index as a scalar: branches on it are uniform
     const int n16 = lane & 15, g = lane >> 4;
@@ -993,12 +1014,12 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
     if (k0 + 16 * wave < k1) HIVIS_ATTN_LOADS(k0 + 16 * wave)
     HIVIS_AMARK(1)
 
+    int ph_, pi_;                                          // this lane's (head, row) pair
+    attn_pair(min(n16, R - 1), ni, R, ph_, pi_);
     // B operand of the score product: q[row lane%16][32 ks + 8 (lane/16) .. +8] * scale as hi + lo halves; rows >= R are zero
     f16x8_t qh[KS], ql[KS];
     {
-        const int rq = min(n16, R - 1);
-        const int hh = kvh * group + h0 + rq / ni, i = i0 + rq % ni;
-        const float* qrow = q + (size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + g * 8;
+        const float* qrow = q + (size_t)attn_qrow(sh, sl, i0 + pi_) * sh.ldq + (size_t)(kvh * group + h0 + ph_) * HD + g * 8;
         const float scale = (n16 < R) ? rsqrtf((float)HD) : 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -1012,9 +1033,9 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
             }
         }
     }
-    const int qpos = (n16 < R) ? pos0 + i0 + n16 % ni : 0x7FFFFFFF;     // causal limit of this lane's row
+    const int qpos = (n16 < R) ? pos0 + i0 + pi_ : 0x7FFFFFFF;     // causal limit of this lane's row
     const bool tree = sh.tmask != nullptr;                              // rows of a draft tree: ancestor mask instead
-    const unsigned long long tmk = (tree && n16 < R) ? sh.tmask[sl * sh.m + i0 + n16 % ni] : ~0ull;
+    const unsigned long long tmk = (tree && n16 < R) ? sh.tmask[sl * sh.m + i0 + pi_] : ~0ull;
     const int tb = pos0 - sh.offset;
     HIVIS_AMARK(2)
 
@@ -1335,19 +1356,15 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
     float* pw_all = qs + RM * HD;                  // [NW][RM][16] probabilities of the wavefront's 16 keys
     float* mrg = pw_all + NW * RM * 16;            // [NW][RM][HD + 2] per-wavefront partials
 
-    int item = item_id;
-    const int rblk = item % sh.n_rblk; item /= sh.n_rblk;
-    const int hblk = item % sh.n_hblk; item /= sh.n_hblk;
-    const int kvh = item % sh.Hkv;
-    const int sl = item / sh.Hkv;
+    const AttnItem it = attn_item(sh, item_id);
+    const int rblk = it.rblk, hblk = it.hblk, kvh = it.kvh, sl = it.sl, group = it.group;
     const int seq = sh.seq0 + sl;
-    const int group = sh.Hq / sh.Hkv;
     const int h0 = hblk * sh.gh, nh = min(sh.gh, group - h0);
     const int i0 = rblk * sh.mi, ni = min(sh.mi, sh.m - i0);
     const int R = nh * ni;
     const int pos0 = (sh.nbase > 0 ? sh.base_val[sl] : base[seq]) + sh.offset;
     const int nkeys = min(pos0 + i0 + ni, sh.maxL);
-    const int cs = ((nkeys + sh.nsplit - 1) / sh.nsplit + 15) & ~15;        // keys per split, multiple of 16
+    const int cs = (div_pow2(nkeys + sh.nsplit - 1, sh.nsplit) + 15) & ~15;        // keys per split, multiple of 16
     const int k0 = split * cs, k1 = min(nkeys, k0 + cs);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wavefront index as a scalar: branches on it are uniform
     const float scale = rsqrtf((float)HD);
@@ -1376,8 +1393,9 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
 
     for (int idx = threadIdx.x; idx < R * HD; idx += FUSED_NT) {
         const int r = idx / HD, c = idx % HD;
-        const int hh = kvh * group + h0 + r / ni, i = i0 + r % ni;
-        qs[idx] = q[(size_t)attn_qrow(sh, sl, i) * sh.ldq + (size_t)hh * HD + c] * scale;
+        int h, i;
+        attn_pair(r, ni, R, h, i);
+        qs[idx] = q[(size_t)attn_qrow(sh, sl, i0 + i) * sh.ldq + (size_t)(kvh * group + h0 + h) * HD + c] * scale;
     }
     lds_barrier();
     HIVIS_AMARK(2)
@@ -1419,7 +1437,9 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
         for (int r = 0; r < RC; ++r) {
             if (RC == 1 || r < R) {
                 float sv = quad_sum(s[r]);                // the 4 lanes of a key hold its 4 quarter dot products
-                const int qpos = pos0 + i0 + r % ni;
+                int h, i;
+                attn_pair(r, ni, R, h, i);
+                const int qpos = pos0 + i0 + i;
                 if (key >= k1 || key > qpos) sv = -INFINITY;
                 const float tmax = wave_max(sv);
                 const float mnew = fmaxf(mrun[r], tmax);
@@ -1481,12 +1501,8 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
 template <int HD, int RM>
 __device__ __forceinline__ void attn_wg_merge(const float* __restrict__ ws, const AttnShape& sh, int item_id,
                                               float* __restrict__ lds, const AttnOut& out) {
-    int item = item_id;
-    const int rblk = item % sh.n_rblk; item /= sh.n_rblk;
-    const int hblk = item % sh.n_hblk; item /= sh.n_hblk;
-    const int kvh = item % sh.Hkv;
-    const int sl = item / sh.Hkv;
-    const int group = sh.Hq / sh.Hkv;
+    const AttnItem it = attn_item(sh, item_id);
+    const int rblk = it.rblk, hblk = it.hblk, kvh = it.kvh, sl = it.sl, group = it.group;
     const int h0 = hblk * sh.gh, nh = min(sh.gh, group - h0);
     const int i0 = rblk * sh.mi, ni = min(sh.mi, sh.m - i0);
     const int R = nh * ni;
@@ -1513,8 +1529,8 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
         const int total = xcd_map ? 8 * ((ph.att_items + 7) / 8) * nsp : ph.att_items * nsp;
         for (int w = blockIdx.x; w < total; w += gridDim.x) {
             int item, split;
-            if (xcd_map) { const int j = w >> 3; item = (w & 7) + 8 * (j / nsp); split = j % nsp; if (item >= ph.att_items) continue; }
-            else { item = w / nsp; split = w % nsp; }
+            if (xcd_map) { const int j = w >> 3, q = div_pow2(j, nsp); item = (w & 7) + 8 * q; split = j - q * nsp; if (item >= ph.att_items) continue; }
+            else { item = div_pow2(w, nsp); split = w - item * nsp; }
             if constexpr (std::is_same<KT, f16_t>::value) {
                 if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
                 else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);

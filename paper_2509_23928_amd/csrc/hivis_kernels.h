@@ -110,9 +110,9 @@ __device__ __forceinline__ void st_wt_kv_pair(_Float16* row, int HD, int c, floa
 __device__ __forceinline__ void st_row_pair(uint4* __restrict__ frag, int M, int row, int k, float a, float b) {
     uint32_t hi, lo;
     f32_to_bf16x2_hilo(a, b, hi, lo);
-    uint32_t* p = reinterpret_cast<uint32_t*>(frag + ((size_t)(k >> 5) * M + row) * 8 + ((k >> 3) & 3)) + ((k >> 1) & 3);
+    uint32_t* p = reinterpret_cast<uint32_t*>(frag + ((size_t)(k >> 5) * 2 * M + row) * 4 + ((k >> 3) & 3)) + ((k >> 1) & 3);
     st_wt(p, hi);
-    st_wt(p + 16, lo);
+    st_wt(p + 16 * M, lo);
 }
 
 // KV-cache storage that goes with a weight type.  fp32 models keep K and V in fp32.  bf16 models keep every cached
@@ -1334,11 +1334,17 @@ __global__ __launch_bounds__(ACCEPT_NT) void accept_sample_kernel(const int32_t*
 }
 
 // After the re-feed: the drafter's pending hidden state is its output at row n_b; its cache keeps n_b+1 rows.
-// (frag, optional: the row as row fragments as well, row b of gridDim.x)
+// (frag, optional: the row as row fragments as well, row b of gridDim.x)  The call's results, nres words from nacc on, and the
+// bad-logits flag go straight to the host's pinned mirror: a copy command each took longer than this kernel.
 __global__ void select_row_kernel(const float* __restrict__ dout, int m, const int32_t* __restrict__ nacc,
-                                  float* __restrict__ fnext, int ldf, int* __restrict__ dlen, int d, uint4* __restrict__ frag) {
+                                  float* __restrict__ fnext, int ldf, int* __restrict__ dlen, int d, uint4* __restrict__ frag,
+                                  int32_t* __restrict__ host, int nres, const int* __restrict__ bad) {
     const int b = blockIdx.x;
     const int n = nacc[b];
+    if (b == 0) {
+        for (int i = threadIdx.x; i < nres; i += blockDim.x) __hip_atomic_store(&host[i], nacc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (threadIdx.x == 0) __hip_atomic_store(&host[nres + 1], bad[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     for (int c = 2 * threadIdx.x; c < d; c += 2 * blockDim.x) {
         const float2 x = *reinterpret_cast<const float2*>(dout + ((size_t)b * m + n) * d + c);
         *reinterpret_cast<float2*>(fnext + (size_t)b * ldf + c) = x;

@@ -7,12 +7,15 @@
 // moved it through LDS before its first product: two further dependent steps at the start of each launch, a thousand vector
 // instructions per wavefront, and registers that the weights in flight need.)  HBM bound.  Kernel traces, before -> now: 7B widths, 6 rows:
 // q|k|v 20.4 -> 20.0 us, O 11.3 -> 9.3, gate|up 32.0 -> 31.1, down 20.1 -> 18.8, attention (which now writes fragments) 13.4 -> 11.9; LM head 49.3 ->
-// 46.2; 2048 wide, 12 rows: q|k|v 10.2 -> 8.3, O 9.5 -> 7.4, gate|up 14.4 -> 11.3, down 18.0 -> 16.2.  A plain stream of the same bytes takes 16.4, 6.4,
+// 46.2; 2048 wide, 12 rows: q|k|v 10.2 -> 7.8, O 9.5 -> 6.0, gate|up 14.4 -> 11.0, down 18.0 -> 10.8.  A plain stream of the same bytes takes 16.4, 6.4,
 // 27.2, 14.7 and 38.5 us.
 //
-// Row fragments of M rows of K values: K block kb (32 values), row r, part p (0 high, 1 low), piece g (8 values)
-//   frag[((kb * M + r) * 2 + p) * 4 + g]        16 bytes each
-// so that a K block is M * 128 contiguous bytes, whatever M is.
+// Row fragments of M rows of K values: K block kb (32 values), part p (0 high, 1 low), row r, piece g (8 values)
+//   frag[((kb * 2 + p) * M + r) * 4 + g]        16 bytes each
+// so that a K block is M * 128 contiguous bytes, whatever M is, and a part of it M * 64 (with a row's parts side by side every load of the
+// 16-row form touched half of twice as many cache lines: 12 rows, 2048 wide, down 16.2 -> 14.1 us, O 7.4 -> 6.6).
+// Not for more than 16 rows: every workgroup reads all fragments, 717 MB through the L2s for the down projection of 61 rows, 53 us where the
+// K-sliced GEMM and its row kernel take 32.
 #pragma once
 #include "hivis_fused.h"
 
@@ -28,14 +31,15 @@ constexpr int OUT_OF_RANGE = 0x40000000;       // byte offset of a lane that loa
 constexpr int STREAM_MAX_D = 8192;             // row widths served (registers for a row's sums of squares, and for a row)
 
 // the lane's operand row: 8-row form: row 2 (i / 4) + i % 2, high part for i & 2 == 0; 16-row form: row i, both parts
-template <typename WT> __device__ __forceinline__ int frag_lane_offset(int lane, int M);
-template <> __device__ __forceinline__ int frag_lane_offset<bf16_t>(int lane, int M) {
+// (of the n rows from r0 on, in fragments of M rows)
+template <typename WT> __device__ __forceinline__ int frag_lane_offset(int lane, int M, int r0, int n);
+template <> __device__ __forceinline__ int frag_lane_offset<bf16_t>(int lane, int M, int r0, int n) {
     const int i = lane & 15, row = 2 * (i >> 2) + (i & 1);
-    return row < M ? (row * 8 + ((i >> 1) & 1) * 4 + (lane >> 4)) * 16 : OUT_OF_RANGE;
+    return row < n ? ((((i >> 1) & 1) * M + r0 + row) * 4 + (lane >> 4)) * 16 : OUT_OF_RANGE;
 }
-template <> __device__ __forceinline__ int frag_lane_offset<bf16w_t>(int lane, int M) {
+template <> __device__ __forceinline__ int frag_lane_offset<bf16w_t>(int lane, int, int r0, int n) {
     const int row = lane & 15;
-    return row < M ? (row * 8 + (lane >> 4)) * 16 : OUT_OF_RANGE;
+    return row < n ? ((r0 + row) * 4 + (lane >> 4)) * 16 : OUT_OF_RANGE;
 }
 // fragments of K blocks [kb0, kb0 + nkb)
 template <int U>
@@ -50,7 +54,7 @@ __device__ __forceinline__ void issue_rows(HiLoFrag (&a)[U], const uint4* __rest
 #pragma unroll
     for (int j = 0; j < U; ++j) {
         a[j].hi = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off + j * M * 128, 0, 0));
-        a[j].lo = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off + j * M * 128 + 64, 0, 0));
+        a[j].lo = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off + (2 * j + 1) * M * 64, 0, 0));
     }
 }
 
@@ -103,13 +107,19 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
     float* red = lds;                                   // [NW][G][64][RPL]
     float* inv_rms = lds + (size_t)NW * G * 64 * RPL;   // [16]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int M = pp.M, K = ph.K, N = ph.N, kblks = K / 32, ntiles = N / 16;
-    const int vb = (gridDim.x % 8 == 0) ? (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) : (int)blockIdx.x;
-    const int t_begin = __builtin_amdgcn_readfirstlane((int)((unsigned)vb * (unsigned)ntiles / gridDim.x));
-    const int t_end = __builtin_amdgcn_readfirstlane((int)((unsigned)(vb + 1) * (unsigned)ntiles / gridDim.x));
+    const int K = ph.K, N = ph.N, kblks = K / 32, ntiles = N / 16;
+    int vb = (gridDim.x % 8 == 0) ? (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) : (int)blockIdx.x, nwg = gridDim.x;
+    // Two workgroups per tile (the 8-row form given more rows, see launch_phases): rows [r0, r0 + M) of Mt, neighbours on one XCD
+    const int Mt = pp.M;
+    int r0 = 0, M = Mt;
+    if constexpr (std::is_same<WT, bf16_t>::value && G == 1 && !PAIRS) {
+        if (Mt > ROWS) { M = (Mt + 1) / 2; if (vb & 1) { r0 = M; M = Mt - M; } vb >>= 1; nwg >>= 1; }
+    }
+    const int t_begin = __builtin_amdgcn_readfirstlane((int)((unsigned)vb * (unsigned)ntiles / (unsigned)nwg));
+    const int t_end = __builtin_amdgcn_readfirstlane((int)((unsigned)(vb + 1) * (unsigned)ntiles / (unsigned)nwg));
     const int npass = (kblks + NW * U * PU - 1) / (NW * U * PU) * PU;
     const StreamUnits un = {kblks, (kblks + NW * npass - 1) / (NW * npass)};
-    const int lane_off = frag_lane_offset<WT>(lane, M);
+    const int lane_off = frag_lane_offset<WT>(lane, Mt, r0, M);
 
     // the slot of this thread: tile of the group, row, column(s)
     int s_g[SLOTS], s_row[SLOTS], s_c[SLOTS];
@@ -119,11 +129,12 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
         s_c[sl] = idx % CPT; s_row[sl] = (idx / CPT) % ROWS; s_g[sl] = idx / (CPT * ROWS);
     }
     // the token of the thread's row (the same for all its slots): given, or the greedy one of the LM-head phase before this one, reduced
-    // here by the 16 lanes of the row (lowest index wins ties); workgroup 0 also stores it
+    // here by the 16 lanes of the row (lowest index wins ties); the workgroups of tile 0 also store it
     int tok = 0;
+    static_assert((EPI != FEPI_ADDVEC && EPI != FEPI_LOGITS) || NT % (CPT * ROWS) == 0, "a thread serves one row");
     if constexpr (EPI == FEPI_ADDVEC) {
-        const int r = min(s_row[0], M - 1);
-        if (ph.tok) tok = __hip_atomic_load(&ph.tok[(r / pp.m) * ph.tok_sseq + (r % pp.m) * ph.tok_srow], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int r = r0 + min(s_row[0], M - 1);
+        if (ph.tok) tok = __hip_atomic_load(&ph.tok[seq_of(pp, r) * ph.tok_sseq + row_in_seq(pp, r) * ph.tok_srow], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else {
             float bv = -INFINITY; int bi = 0x7FFFFFFF;
 #pragma unroll 4
@@ -138,7 +149,7 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
                 if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
             }
             tok = bi;
-            if (blockIdx.x == 0 && s_c[0] == 0 && s_g[0] == 0 && s_row[0] < M) {
+            if (vb == 0 && s_c[0] == 0 && s_g[0] == 0 && s_row[0] < M) {
                 if (pp.bad && (unsigned)bi >= (unsigned)pp.V) st_wt(pp.bad, 1);
                 st_wt(&ph.tok_out[(r / pp.m) * ph.o_sseq + (r % pp.m) * ph.o_srow], clamp_token(bi, pp.V));
             }
@@ -149,7 +160,7 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
     auto epi_request = [&](int tg_) {
 #pragma unroll
         for (int sl = 0; sl < SLOTS; ++sl) {
-            const int row = min(s_row[sl], M - 1);
+            const int row = r0 + min(s_row[sl], M - 1);
             if constexpr (EPI == FEPI_ADD_TO || EPI == FEPI_ADDVEC) {
                 const int col = min((tg_ + s_g[sl]) * 16 + s_c[sl], N - 1);
                 e_b[sl] = buffer_bf16(buffer_of(ph.fgain, ph.fgain ? N * 2 : 0), col * 2);
@@ -157,8 +168,8 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
                 else e_c[sl] = bf16_to_f32(((const bf16_t*)ph.vec)[(size_t)ph.vec_idx * N + col]);
             } else if constexpr (EPI == FEPI_QKV) {
                 const int col = min((tg_ + s_g[sl]) * 16 + 2 * s_c[sl], N - 2);
-                const int seq = row / pp.m;
-                const int delta = ph.pos_delta ? ph.pos_delta[row] : ph.offset + row % pp.m;
+                const int seq = seq_of(pp, row);
+                const int delta = ph.pos_delta ? ph.pos_delta[row] : ph.offset + row_in_seq(pp, row);
                 const int pos = min((ph.att.nbase > 0 ? ph.att.base_val[seq] : ph.base[seq]) + delta, ph.maxL - 1);
                 const float2 cs = *reinterpret_cast<const float2*>(ph.rope + ((size_t)pos * (pp.hd / 2) + ((col % pp.hd) >> 1)) * 2);
                 e_a[sl] = cs.x; e_b[sl] = cs.y;
@@ -184,7 +195,7 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
     typename AFrag<WT>::type a[AB][U];
     uint4 w[D][U];
     // (a pass nobody needs, a tile beyond the range: no blocks)
-#define HIVIS_ROWS(buf_, pass_, on_) issue_rows(a[buf_], ph.Af, M, lane_off, un.first(pass_, wave), (on_) ? un.count(pass_, wave) : 0)
+#define HIVIS_ROWS(buf_, pass_, on_) issue_rows(a[buf_], ph.Af, Mt, lane_off, un.first(pass_, wave), (on_) ? un.count(pass_, wave) : 0)
 #define HIVIS_UNIT(buf_, tile_, pass_) issue_unit<WT>(w[buf_], ph.W, kblks, tile_, un.first(pass_, wave), (tile_) < t_end ? un.count(pass_, wave) : 0, lane)
     __builtin_amdgcn_sched_barrier(0);
     HIVIS_MARK(1)
@@ -238,13 +249,14 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
         if (tg > t_begin) lds_barrier();                   // (the last group's have been read)
 #pragma unroll
         for (int g = 0; g < G; ++g) {
+            const auto& x = acc[g];
             float* dst = red + ((size_t)(wave * G + g) * 64 + lane) * RPL;
             if constexpr (RPL == 2) {
-                *reinterpret_cast<float2*>(dst) = make_float2(acc[g][0] + acc[g][2], acc[g][1] + acc[g][3]);
+                *reinterpret_cast<float2*>(dst) = make_float2(x[0] + x[2], x[1] + x[3]);
             } else {
                 float y[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = (CF::NHI == 2 ? acc[g].hi[0][e] + acc[g].hi[CF::NHI - 1][e] : acc[g].hi[0][e]) + acc[g].lo[e];
+                for (int e = 0; e < 4; ++e) y[e] = (CF::NHI == 2 ? x.hi[0][e] + x.hi[CF::NHI - 1][e] : x.hi[0][e]) + x.lo[e];
                 *reinterpret_cast<float4*>(dst) = make_float4(y[0], y[1], y[2], y[3]);
             }
         }
@@ -264,16 +276,17 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
             if (g >= ng || row >= M) continue;             // (uniform over the slots of one tile and row)
             if constexpr (EPI == FEPI_ADD_TO || EPI == FEPI_ADDVEC) {
                 const int c = s_c[sl], col = tile * 16 + c;
+                const int rw = r0 + row;
                 const float v = sum(g, row, c);
                 const float y = EPI == FEPI_ADD_TO ? e_a[sl] + v : v + e_c[sl] + e_a[sl];
-                if (ph.Y) st_wt(&ph.Y[(size_t)row * ph.ldy + col], y);
+                if (ph.Y) st_wt(&ph.Y[(size_t)rw * ph.ldy + col], y);
                 if (ph.F) {
                     const float z = ph.fgain ? y * e_b[sl] : y, z1 = dpp_move<DPP_QUAD_XOR1, 0xF>(z, z);
-                    if ((c & 1) == 0) st_row_pair(ph.F, M, row, col, z, z1);
+                    if ((c & 1) == 0) st_row_pair(ph.F, Mt, rw, col, z, z1);
                 }
                 if (ph.ssq_out) {
                     const float s = row16_sum(y * y);
-                    if (c == 0) st_wt(&ph.ssq_out[(size_t)row * ssq_stride(ntiles) + tile], s);
+                    if (c == 0) st_wt(&ph.ssq_out[(size_t)rw * ssq_stride(ntiles) + tile], s);
                 }
             } else if constexpr (EPI == FEPI_SILU) {
                 const int c = s_c[sl], col = tile * 8 + c;
@@ -282,8 +295,8 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
                 if ((c & 1) == 0) st_row_pair(ph.F, M, row, col, y, y1);
             } else if constexpr (EPI == FEPI_QKV) {
                 // a rotary pair of q or k, or two elements of v
-                const int col = tile * 16 + 2 * s_c[sl], qd = pp.Hq * pp.hd, kd = pp.Hkv * pp.hd, hd = pp.hd, seq = row / pp.m;
-                const int slot = min((ph.att.nbase > 0 ? ph.att.base_val[seq] : ph.base[seq]) + ph.offset + row % pp.m, ph.maxL - 1);
+                const int col = tile * 16 + 2 * s_c[sl], qd = pp.Hq * pp.hd, kd = pp.Hkv * pp.hd, hd = pp.hd, seq = seq_of(pp, row);
+                const int slot = min((ph.att.nbase > 0 ? ph.att.base_val[seq] : ph.base[seq]) + ph.offset + row_in_seq(pp, row), ph.maxL - 1);
                 float x1 = sum(g, row, 2 * s_c[sl]), x2 = sum(g, row, 2 * s_c[sl] + 1);
                 if (ph.bias) { x1 += ph.bias[col]; x2 += ph.bias[col + 1]; }
                 if (col < qd + kd) {

@@ -351,8 +351,12 @@ __global__ void tree_roll_cat_kernel(const float* __restrict__ g, int ldg, const
 
 // After the re-feed: pending hidden state = drafter output at row n; both caches keep n + 1 more rows.
 __global__ void tree_finish_kernel(const float* __restrict__ dout, const int32_t* __restrict__ result, float* __restrict__ fnext,
-                                   int* __restrict__ dlen, int* __restrict__ tlen, int d, uint4* __restrict__ frag) {
+                                   int* __restrict__ dlen, int* __restrict__ tlen, int d, uint4* __restrict__ frag,
+                                   int32_t* __restrict__ host, int nres, const int* __restrict__ bad, int bad_at) {
     const int n = result[0];
+    // (results and flag straight to the host's pinned mirror, as in select_row_kernel)
+    if ((int)threadIdx.x < nres) __hip_atomic_store(&host[threadIdx.x], result[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 255) __hip_atomic_store(&host[bad_at], bad[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     for (int c = 2 * threadIdx.x; c < d; c += 2 * blockDim.x) {
         const float2 x = *reinterpret_cast<const float2*>(dout + (size_t)n * d + c);
         *reinterpret_cast<float2*>(fnext + c) = x;
