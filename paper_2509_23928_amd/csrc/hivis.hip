@@ -62,7 +62,7 @@ struct hivis_ctx {
     uint4* lm_head = nullptr; uint4* fuse_w = nullptr;
     uint4* fuse_w1 = nullptr;            // rows [0, d) of the fusion FC, packed on their own (K = d), and
     bool lm_ext = false;                 // the packed LM head is followed by w1's tiles in one buffer (lm_head .. lm_head + (V + d) d)
-    float* emb_w2 = nullptr;             // [V][d] fp32: Embed(token) . w2, the embedding half of the fusion FC per token (bf16 models)
+    float* emb_w2 = nullptr;             // [V][d] fp32: Embed(token) . w2, the embedding half of the fusion FC per token
     std::vector<LayerDev> layers; LayerDev draft;
     std::vector<KVDev> tkv; KVDev dkv;
 
@@ -557,7 +557,10 @@ AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, 
     AttnShape sh{};
     sh.Hq = g.n_q_heads; sh.Hkv = g.n_kv_heads; sh.m = m;
     const int group = g.n_q_heads / g.n_kv_heads;
-    if (m >= FUSED_RMAX) { sh.mi = FUSED_RMAX; sh.gh = 1; }
+    // (fp32 caches: the vector ALU works on an item's rows one after the other, so each row is an item of its own while there are CUs for them:
+    // verify of 5 rows x 4 heads 10.9 -> 6.2 us; the matrix cores of the bf16 models take all rows of an item at once)
+    if (g.dtype == HIVIS_F32 && nseq * g.n_q_heads * m <= c->fused_grid) { sh.mi = 1; sh.gh = 1; }
+    else if (m >= FUSED_RMAX) { sh.mi = FUSED_RMAX; sh.gh = 1; }
     else { sh.mi = m; sh.gh = std::max(1, std::min(group, FUSED_RMAX / m)); }
     sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
     sh.seq0 = 0; sh.offset = offset; sh.maxL = maxL; sh.ldq = ldq; sh.nwaves = FUSED_NW;
@@ -668,7 +671,7 @@ void layer_stream(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const LayerDe
 int lm_candidates(const hivis_ctx* c, int N, bool persistent) { return persistent ? c->fused_grid : std::min(c->fused_grid, N / 16); }
 
 template <typename WT>
-void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>& P, bool persistent, bool elect, bool stream) {
+void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>& P, bool persistent, bool elect, bool stream, bool lm_ext) {
     const hivis_config& g = c->cfg;
     const int B = g.batch, d = g.d, V = g.vocab, G = c->fused_grid;
     int ld = d;
@@ -714,7 +717,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
             lm.Y = c->logits_d + (size_t)(i - 1) * B * V; lm.ldy = V; lm.pm = pool.take((size_t)B * G); lm.pi = (int*)pool.take((size_t)B * G);
             lm.tok_out = c->drafts + (i - 1); lm.o_sseq = g.k_max; lm.o_srow = 0;
             // greedy token of step i: reduced by the phase that follows (as below), by the LM head's last workgroup, or by a phase of its own
-            const bool later = kind == PROG_DRAFT && i < K, ext = later && c->lm_ext && B <= 4;
+            const bool later = kind == PROG_DRAFT && i < K, ext = later && lm_ext && B <= 4;
             const bool in_lm = !later && lm_elect && kind == PROG_DRAFT;
             float* u_part = ext ? pool.take((size_t)B * d) : nullptr;
             if (ext) { lm.N = V + d; lm.Y2 = u_part; lm.ldy2 = d; lm.vec = c->rho; lm.vec_idx = std::min(i, g.n_resid - 1); }
@@ -787,7 +790,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
             const bool in_fc = fold && kind == PROG_DRAFT && i < K;
             // ... and with the extended LM head there is no FC phase: this LM-head launch also computes f' w1 + rho for the
             // next step (d extra columns), and the next step's QKV phase reduces the token and adds the table row of it
-            const bool ext = in_fc && c->lm_ext && B <= 4;       // (the QKV variants that add the table rows stage two or four rows)
+            const bool ext = in_fc && lm_ext && B <= 4;       // (the QKV variants that add the table rows stage two or four rows)
             float* u_part = ext ? pool.take((size_t)B * d) : nullptr;
             if (ext) { lm.N = V + d; lm.Y2 = u_part; lm.ldy2 = d; lm.vec = c->rho; lm.vec_idx = std::min(i, g.n_resid - 1); }
             const bool in_lm = !in_fc && lm_elect && kind == PROG_DRAFT;
@@ -859,12 +862,12 @@ int get_program(hivis_ctx* c, int kind, int K, hivis_ctx::Program* out) {
     if (it != c->programs.end()) { *out = it->second; return HIVIS_OK; }
     std::vector<Phase> P;
     Pool count;
-    build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect, c->stream_rows);           // sizes only
+    build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect, c->stream_rows, c->lm_ext);           // sizes only
     Pool pool;
     if (int rc = dev_alloc(c, &pool.base, count.used)) return rc;
     HIP_TRY(c, hipMemsetAsync(pool.base, 0, count.used * sizeof(float), c->stream));      // (on the stream of the passes that count on it)
     P.clear();
-    build_phases<WT>(c, kind, K, pool, P, c->persistent, c->attn_elect, c->stream_rows);
+    build_phases<WT>(c, kind, K, pool, P, c->persistent, c->attn_elect, c->stream_rows, c->lm_ext);
     hivis_ctx::Program pg;
     pg.n = (int)P.size();
     if (int rc = dev_alloc(c, &pg.dev, P.size())) return rc;
@@ -884,6 +887,11 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
     // merge launch) for short ones; the program was sized for the largest split count
     int max_keys = 0;
     for (int b = 0; b < g.batch; ++b) max_keys = std::max(max_keys, (kind == PROG_VERIFY ? c->h_tlen[b] : c->h_dlen[b]) + K + 1);
+    // Cached rows of all target layers that the memory-side cache (256 MB) does not hold from pass to pass are read with the non-temporal
+    // hint, where one workgroup reads each: 3010 keys x 4 layers (394 MB) 23.8 -> 23.0 us per layer.  Rows that it does hold are not: the
+    // weights, read with the hint, leave them there (650 keys x 8 layers, 170 MB: 11.6 us, 12.8 with the hint; the drafter's layer 7.2 and 8.4).
+    const bool once = !std::is_same<WT, float>::value && kind == PROG_VERIFY &&
+                      (double)g.n_layers * g.batch * g.n_kv_heads * max_keys * g.head_dim * 8.0 > 256.0e6;
     for (int p = 0; p < n; ++p) {
         Phase ph = phases[p];
         ph.next_W = nullptr;                       // nothing is prefetched across a kernel boundary (pulling the next launch's
@@ -917,7 +925,9 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
 #define HIVIS_LAUNCH(TY, EP) do { typedef typename std::conditional<TY == PH_GEMM, WT, RT>::type KT_; \
                               if (single) hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, true>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); \
                               else hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, false>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); } while (0)
-        const bool single = ph.type == PH_GEMM && ph.epi != FEPI_LOGITS && ph.epi != FEPI_SILU && ph.epi != FEPI_QKV && ph.N / 16 <= grid;   // one tile per workgroup at most
+        // one tile per workgroup at most.  (q|k|v, gate|up and LM head: fp32 models only, whose matrices are that small; 256 wide: 7.7 -> 7.0, 7.2 -> 6.0 and 9.0 -> 7.8 us)
+        const bool single = ph.type == PH_GEMM && ph.N / 16 <= grid &&
+                            (std::is_same<WT, float>::value || (ph.epi != FEPI_LOGITS && ph.epi != FEPI_SILU && ph.epi != FEPI_QKV));
         const bool kmatch = kind == PROG_VERIFY && ph.type == PH_GEMM && ph.epi == c->ktime_epi;
         const int64_t kseq = kmatch ? c->ktime_seen++ : 0;
         const bool ktimed = kmatch && (kseq % c->ktime_stride) == 0;
@@ -996,7 +1006,9 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             default: return fail(c, HIVIS_EINVAL, "phase %d: no kernel for epilogue %d", p, ph.epi);
             }
             break;
-        case PH_ATTN: HIVIS_LAUNCH(PH_ATTN, 0); break;
+        case PH_ATTN:
+            if (once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1) HIVIS_LAUNCH(PH_ATTN, ATTN_ONCE); else HIVIS_LAUNCH(PH_ATTN, 0);
+            break;
         case PH_ATTN_MERGE: HIVIS_LAUNCH(PH_ATTN_MERGE, 0); break;
         case PH_PREP: HIVIS_LAUNCH(PH_PREP, 0); break;
         case PH_NORM_ROWS: HIVIS_LAUNCH(PH_NORM_ROWS, 0); break;
@@ -1108,22 +1120,23 @@ int draft_noalloc(hivis_ctx* c, int K) {
     const hivis_config& g = c->cfg;
     std::vector<Phase>& P = c->na_phases;
     if (draft_phase_capacity(K) > P.capacity()) return fail(c, HIVIS_ECAP, "phase list of K=%d exceeds the storage reserved at create", K);
-    // (a round whose buffers fit only as fp32 rows runs on those)
-    bool stream = c->stream_rows;
-    size_t need = 0;
-    for (;;) {
+    // Accepted is what fits as the plain list: fp32 rows between the phases, and for fp32 models a launch of the fusion FC per step.  Row
+    // fragments, and the FC on the LM-head launch of fp32 models, where they fit as well.
+    auto size = [&](bool stream, bool ext) {
         P.clear();
         Pool count;
-        build_phases<WT>(c, PROG_DRAFT, K, count, P, false, false, stream);            // sizes only
-        need = count.used * sizeof(float);
-        if (need <= (size_t)HIVIS_SCRATCH_BYTES || !stream) break;
-        stream = false;
-    }
+        build_phases<WT>(c, PROG_DRAFT, K, count, P, false, false, stream, ext);            // sizes only
+        return count.used * sizeof(float);
+    };
+    const bool bf16 = sizeof(WT) == 2;
+    const size_t need = size(false, bf16 && c->lm_ext);
+    const bool ext = c->lm_ext && (bf16 || size(false, true) <= (size_t)HIVIS_SCRATCH_BYTES);
+    const bool stream = c->stream_rows && size(true, ext) <= (size_t)HIVIS_SCRATCH_BYTES;
     if (need > (size_t)HIVIS_SCRATCH_BYTES)
         return fail(c, HIVIS_ECAP, "draft round of K=%d needs %zu bytes of scratch, the static array holds %u", K, need, (unsigned)HIVIS_SCRATCH_BYTES);
     P.clear();
     Pool pool; pool.base = (float*)c->scratch_dev;                  // the looked-up device address, not the array's name
-    build_phases<WT>(c, PROG_DRAFT, K, pool, P, false, false, stream);
+    build_phases<WT>(c, PROG_DRAFT, K, pool, P, false, false, stream, ext);
     PassParams pp{};
     pp.phases = nullptr; pp.nphases = (int)P.size();
     pp.M = g.batch; pp.nseq = g.batch; pp.m = 1;
@@ -1153,9 +1166,15 @@ int fused_setup(hivis_ctx* c) {
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_SILU, false>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, false>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADD_TO, true>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADDVEC, true>,
-                            (const void*)phase_kernel<WT, PH_ATTN, 0, false>, (const void*)phase_kernel<WT, PH_ATTN_MERGE, 0, false>,
+                            (const void*)phase_kernel<WT, PH_ATTN, 0, false>, (const void*)phase_kernel<WT, PH_ATTN, ATTN_ONCE, false>, (const void*)phase_kernel<WT, PH_ATTN_MERGE, 0, false>,
                             (const void*)phase_kernel<WT, PH_PREP, 0, false>, (const void*)phase_kernel<WT, PH_NORM_ROWS, 0, false>,
                             (const void*)phase_kernel<WT, PH_ARGMAX, 0, false>, (const void*)phase_kernel<WT, PH_SAMPLE, 0, false>};
+        for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
+    }
+    if constexpr (std::is_same<WT, float>::value) {
+        const void* ks[] = {(const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV, true>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB, true>,
+                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB4, true>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_SILU, true>,
+                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, true>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
     }
     if constexpr (std::is_same<WT, bf16_t>::value) {
@@ -1895,16 +1914,15 @@ int do_tree_accept(hivis_ctx* c, int32_t* n_accepted, int32_t* tokens, bool samp
 }
 
 // The fusion FC is linear in its two halves: [f ; Embed(x)] [w1 ; w2] = f w1 + Embed(x) w2 (section 3.2), and the second
-// term depends on the token alone.  For bf16 models the table T[x] = Embed(x) w2 ([V][d], fp32: bf16 x bf16 products summed
-// in fp32) is computed here once, with the prefill's GEMM over ranges of embedding rows, and the phase programs' FC then
+// term depends on the token alone.  The table T[x] = Embed(x) w2 ([V][d], fp32: products summed
+// in fp32) is computed here once, with the prefill's GEMM over ranges of embedding rows (fp32 models: 32 rows at a time), and the phase programs' FC then
 // streams w1 only (d x d instead of 2d x d per step) and adds T[x] in its epilogue.  HIVIS_EMB_TABLE=0 keeps the full FC.
 template <typename WT>
 int build_embed_fc_table(hivis_ctx* c, const hivis_weights* w) {
-    if constexpr (sizeof(WT) != 2) return HIVIS_OK;
     const hivis_config& g = c->cfg;
     const int d = g.d, V = g.vocab;
     { const char* e = getenv("HIVIS_EMB_TABLE"); if (e && e[0] == '0') return HIVIS_OK; }
-    if (!c->fused || c->persistent || !c->pf_frag || c->pf_rows < 8) return HIVIS_OK;
+    if (!c->fused || c->persistent || (sizeof(WT) == 2 && (!c->pf_frag || c->pf_rows < 8))) return HIVIS_OK;
     void* staging = nullptr;
     HIP_TRY(c, hipMalloc(&staging, (size_t)d * d * sizeof(WT) + 4096));
     uint4* w2p = nullptr;
@@ -1921,8 +1939,12 @@ int build_embed_fc_table(hivis_ctx* c, const hivis_weights* w) {
             c->allocs.push_back(q);
             table = (float*)q;
         }
+        if constexpr (sizeof(WT) != 2) {
+            for (int r0 = 0; r0 < V && !rc; r0 += CHAIN_MAX_ROWS)
+                rc = gemm<WT>(c, (const WT*)c->embed + (size_t)r0 * d, d, std::min(CHAIN_MAX_ROWS, V - r0), d, w2p, d, table + (size_t)r0 * d, d, EPI_STORE);
+        }
         const int R = c->pf_rows;                                  // rows per GEMM: what the prefill buffers hold
-        for (int r0 = 0; r0 < V && !rc; r0 += R) {
+        for (int r0 = 0; sizeof(WT) == 2 && r0 < V && !rc; r0 += R) {
             const int n = std::min(R, V - r0);
             hipLaunchKernelGGL((rows_to_f32_kernel<WT>), dim3(1024), dim3(256), 0, c->stream, (const WT*)c->embed + (size_t)r0 * d, (size_t)n * d, c->pf_x);
             uint4* frag = nullptr;

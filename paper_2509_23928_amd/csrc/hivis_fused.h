@@ -26,6 +26,8 @@ namespace hivis {
 
 enum { PH_GEMM = 0, PH_ATTN = 1, PH_ATTN_MERGE = 2, PH_PREP = 3, PH_NORM_ROWS = 4, PH_ARGMAX = 5, PH_SAMPLE = 6 };
 enum { PRO_PLAIN = 0, PRO_RMS = 1 };
+// kernel variant of PH_ATTN (in the place of an epilogue): the cached rows with the non-temporal hint (rule: launch_phases)
+enum { ATTN_ONCE = 1 };
 constexpr int FUSED_RMAX = 8;      // (head,row) pairs per attention work item in the persistent kernel
 enum { FEPI_ADD_TO = 1, FEPI_ADDVEC = 2, FEPI_QKV = 3, FEPI_SILU = 4, FEPI_LOGITS = 5,
        FEPI_QKV_TAB = 6,     // kernel variants only (never a Phase.epi): QKV whose rows are A + add_rows[token], see Phase.wb;
@@ -952,7 +954,7 @@ __host__ __device__ constexpr size_t fused_attn_mfma_lds_floats(int hd, int nw, 
     return (tiles > mrg ? tiles : mrg) + 16;
 }
 
-template <int HD, int RM>
+template <int HD, int RM, bool ONCE = false>
 __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
                                              const int* __restrict__ base, const AttnShape& sh, int item_id, int split,
                                              float* __restrict__ lds, float* __restrict__ ws, int* __restrict__ cnt,
@@ -1007,8 +1009,13 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
     {                                                                                                              \
         _Pragma("unroll") for (int t = 0; t < VT; ++t) {                                                           \
             const size_t off_ = (size_t)min((kb_) + t * KPI + vks, nkeys - 1) * ROWB + vdc * 16;                   \
-            knext[t] = *reinterpret_cast<const u32x4_t*>(kbase + off_);                                            \
-            vnext[t] = *reinterpret_cast<const u32x4_t*>(vbase + off_);                                            \
+            if constexpr (ONCE) {                                                                                  \
+                knext[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(kbase + off_));             \
+                vnext[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(vbase + off_));             \
+            } else {                                                                                               \
+                knext[t] = *reinterpret_cast<const u32x4_t*>(kbase + off_);                                        \
+                vnext[t] = *reinterpret_cast<const u32x4_t*>(vbase + off_);                                        \
+            }                                                                                                      \
         }                                                                                                          \
     }
     if (k0 + 16 * wave < k1) HIVIS_ATTN_LOADS(k0 + 16 * wave)
@@ -1532,8 +1539,8 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
             if (xcd_map) { const int j = w >> 3, q = div_pow2(j, nsp); item = (w & 7) + 8 * q; split = j - q * nsp; if (item >= ph.att_items) continue; }
             else { item = div_pow2(w, nsp); split = w - item * nsp; }
             if constexpr (std::is_same<KT, f16_t>::value) {
-                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
-                else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
+                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX, TYPE == PH_ATTN && EPI == ATTN_ONCE>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
+                else attn_wg_mfma<64, FUSED_RMAX, TYPE == PH_ATTN && EPI == ATTN_ONCE>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
             } else {
                 // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
                 const bool one = ph.att.gh * ph.att.mi == 1;
