@@ -81,6 +81,8 @@ struct hivis_ctx {
     bool stream_rows = false;
     uint4* catDf = nullptr;              // the rows of catD as row fragments (of batch rows)
     uint4* vfrag = nullptr;              // features of a verify program's rows
+    // up to 16 rows of a prefill: residual rows times a gain, attention rows (or features), MLP rows; sums of squares
+    uint4 *st_frag = nullptr, *st_att = nullptr, *st_act = nullptr; float* st_ssq = nullptr;
     uint4* tcatf = nullptr;              // hidden rows of a tree level, or of a tree's re-feed
     float *feat = nullptr;      // [B][max_text][d] true features of prompt text rows (prefill only)
     float *attn_ws = nullptr; size_t attn_ws_floats = 0;
@@ -372,7 +374,8 @@ AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, 
 // keys, no key split), launched once over all items.  Rows of sequence seq0 + s sit at positions base[seq0 + s] + offset + i.
 template <typename WT>
 int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int* base, int offset, int seq0, int nseq, int m,
-                        float* out, int ldo, const unsigned long long* tmask = nullptr, uint4* frag_out = nullptr, bool* wrote_frag = nullptr, int qrows = 0) {
+                        float* out, int ldo, const unsigned long long* tmask = nullptr, uint4* frag_out = nullptr, bool* wrote_frag = nullptr, int qrows = 0, uint4* row_frag = nullptr) {
+    // row_frag (optional, up to 16 rows): the rows go there as row fragments.
     // frag_out / wrote_frag (optional): where the kernel chosen can, the rows go out as A fragments of the next GEMM
     // (K = ldo) instead of fp32 rows, and *wrote_frag says so
     if (wrote_frag) *wrote_frag = false;
@@ -418,11 +421,11 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
             if (g.head_dim == 128) {
                 static bool attr128 = false;
                 if (!attr128) { HIP_TRY(c, hipFuncSetAttribute((const void*)attn_rows_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); attr128 = true; }
-                hipLaunchKernelGGL((attn_rows_kernel<128>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, out, ldo, frag);
+                hipLaunchKernelGGL((attn_rows_kernel<128>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, AttnOut{out, ldo, row_frag, nseq * m}, frag);
             } else {
                 static bool attr64 = false;
                 if (!attr64) { HIP_TRY(c, hipFuncSetAttribute((const void*)attn_rows_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); attr64 = true; }
-                hipLaunchKernelGGL((attn_rows_kernel<64>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, out, ldo, frag);
+                hipLaunchKernelGGL((attn_rows_kernel<64>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, AttnOut{out, ldo, row_frag, nseq * m}, frag);
             }
             HIP_TRY(c, hipGetLastError());
             return HIVIS_OK;
@@ -435,7 +438,7 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
     ph.att.seq0 = seq0; ph.att.nsplit = 1; ph.att.tmask = tmask; ph.att.flags = c->attn_flags; ph.att.qrows = qrows;
     ph.att_items = items;
     ph.A = q; ph.kc = kv.k; ph.vc = kv.v; ph.maxL = kv.maxL; ph.base = base; ph.offset = offset;
-    ph.Y = out; ph.ldy = ldo; ph.ws = nullptr; ph.cnt = nullptr;
+    ph.Y = out; ph.ldy = ldo; ph.ws = nullptr; ph.cnt = nullptr; ph.F = row_frag;
     if (c->attn_elect && items <= c->rows_cnt_n) {
         // long caches: the key range of an item is split over workgroups and the last one to arrive merges (as in the
         // phase programs); the host mirrors the cache lengths that `base` holds
@@ -888,7 +891,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
     int max_keys = 0;
     for (int b = 0; b < g.batch; ++b) max_keys = std::max(max_keys, (kind == PROG_VERIFY ? c->h_tlen[b] : c->h_dlen[b]) + K + 1);
     // Cached rows of all target layers that the memory-side cache (256 MB) does not hold from pass to pass are read with the non-temporal
-    // hint, where one workgroup reads each: 3010 keys x 4 layers (394 MB) 23.8 -> 23.0 us per layer.  Rows that it does hold are not: the
+    // hint, where one workgroup reads each: 3010 keys x 4 layers (394 MB) 24.7 -> 23.1 us per layer.  Rows that it does hold are not: the
     // weights, read with the hint, leave them there (650 keys x 8 layers, 170 MB: 11.6 us, 12.8 with the hint; the drafter's layer 7.2 and 8.4).
     const bool once = !std::is_same<WT, float>::value && kind == PROG_VERIFY &&
                       (double)g.n_layers * g.batch * g.n_kv_heads * max_keys * g.head_dim * 8.0 > 256.0e6;
@@ -1400,6 +1403,42 @@ int layer_forward_wide(hivis_ctx* c, const LayerDev& L, const KVDev& kv, float* 
     return rows_gemm(c, c->pf_frag2, M, F, L.wd, d, c->proj, out_pending);
 }
 
+// ---- prefill rows that the GEMMs on row fragments take (up to 16; c->stream_rows) --------------------------------------
+// One GEMM phase on nseq x m rows, outside a program.
+int launch_stream(hivis_ctx* c, Phase ph, int nseq, int m) {
+    const hivis_config& g = c->cfg;
+    PassParams pp{};
+    pp.M = nseq * m; pp.nseq = nseq; pp.m = m; pp.d = g.d; pp.Hq = g.n_q_heads; pp.Hkv = g.n_kv_heads; pp.hd = g.head_dim; pp.F = g.ffn; pp.V = g.vocab;
+    pp.eps = g.rms_eps; pp.theta = g.rope_theta; pp.bad = c->bad;
+    ph.type = PH_GEMM;
+    ph.att.seq0 = 1;                       // (positions from ph.base, not from the host's mirrors of the cache lengths: those are of the last request)
+    return pp.M > WTraits<bf16_t>::ROWS ? launch_phases<bf16w_t>(c, &ph, 1, PROG_ROLL, 0, pp, false) : launch_phases<bf16_t>(c, &ph, 1, PROG_ROLL, 0, pp, false);
+}
+// q (rotated) to q_out, k and v of sequences seq0 .. to their cache rows 0 ..; rows and sums of squares in st_frag / st_ssq
+int stream_qkv(hivis_ctx* c, const LayerDev& L, const KVDev& kv, int nssq, int seq0, int nseq, int m, float* q_out) {
+    const hivis_config& g = c->cfg;
+    const int qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim;
+    const size_t at = (size_t)seq0 * g.n_kv_heads * kv.maxL * g.head_dim * KVWidth<f16_t>::W;
+    Phase q{}; q.epi = FEPI_QKV; q.K = g.d; q.N = qd + 2 * kd; q.W = L.wqkv; q.Af = c->st_frag; q.ssq = c->st_ssq; q.nssq = nssq;
+    q.Y = q_out; q.ldy = qd; q.kc = (f16_t*)kv.k + at; q.vc = (f16_t*)kv.v + at; q.maxL = kv.maxL; q.base = c->zeros; q.offset = 0; q.rope = c->rope_tab; q.bias = L.bqkv;
+    return launch_stream(c, q, nseq, m);
+}
+// Second half of a layer on the last n rows of each of nseq sequences, as rows_attn_mlp: h in place, complete.  next_gain (optional): h times
+// it goes to st_frag, the sums of squares to st_ssq.
+int stream_attn_mlp(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const float* q, int qrows, int offset, int seq0, int nseq, int n, float* h, const void* next_gain) {
+    const hivis_config& g = c->cfg;
+    const int d = g.d, qd = g.n_q_heads * g.head_dim, F = g.ffn;
+    if (int rc = attention_rows_mfma<bf16_t>(c, q, qd, kv, c->zeros, offset, seq0, nseq, n, nullptr, qd, nullptr, nullptr, nullptr, qrows, c->st_att)) return rc;
+    Phase o{}; o.epi = FEPI_ADD_TO; o.K = qd; o.N = d; o.W = L.wo; o.Af = c->st_att; o.Y = h; o.ldy = d; o.R = h; o.ldr = d;
+    o.F = c->st_frag; o.fgain = L.norm2; o.ssq_out = c->st_ssq;
+    if (int rc = launch_stream(c, o, nseq, n)) return rc;
+    Phase gu{}; gu.epi = FEPI_SILU; gu.K = d; gu.N = 2 * F; gu.W = L.wgu; gu.Af = c->st_frag; gu.ssq = c->st_ssq; gu.nssq = d / 16; gu.F = c->st_act;
+    if (int rc = launch_stream(c, gu, nseq, n)) return rc;
+    Phase dn{}; dn.epi = FEPI_ADD_TO; dn.K = F; dn.N = d; dn.W = L.wd; dn.Af = c->st_act; dn.Y = h; dn.ldy = d; dn.R = h; dn.ldr = d;
+    if (next_gain) { dn.F = c->st_frag; dn.fgain = next_gain; dn.ssq_out = c->st_ssq; }
+    return launch_stream(c, dn, nseq, n);
+}
+
 // ---- whole-prompt prefill (bf16 models): all rows of one or several sequences per layer -------------------------
 // Second half of a layer, after q, k and v: attention, O projection, MLP on the last n rows of each of nseq sequences (their q rows:
 // q, qrows rows apart from one sequence to the next; positions offset ..).  h [nseq * n][d]: their residual rows.
@@ -1408,6 +1447,7 @@ int rows_attn_mlp(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const float*
                   float* h, Parts* out_pending) {
     const hivis_config& g = c->cfg;
     const int M = nseq * n, d = g.d, qd = g.n_q_heads * g.head_dim, F = g.ffn;
+    if (c->stream_rows && M <= WTraits<bf16w_t>::ROWS) { *out_pending = Parts{nullptr, 0, 0}; return stream_attn_mlp(c, L, kv, q, qrows, offset, seq0, nseq, n, h, nullptr); }
     bool att_frag = false;
     if (c->fused) { if (int rc = attention_rows_mfma<WT>(c, q, qd, kv, c->zeros, offset, seq0, nseq, n, c->pf_att, qd, nullptr, c->pf_frag, &att_frag, qrows)) return rc; }
     else if (int rc = attention<WT>(c, q, qd, kv, c->zeros, offset, seq0, nseq, n, offset + n, c->pf_att, qd, nullptr, qrows)) return rc;
@@ -1428,6 +1468,19 @@ int prefill_target_tall(hivis_ctx* c, int b0, int nseq, int v, int l) {
                        (const WT*)c->embed, (const int32_t*)(c->text + (size_t)b0 * c->text_stride), c->text_stride, 0, c->pf_x, d);
     Parts pend{nullptr, 0, 0};
     float* h = c->pf_x;
+    if (c->stream_rows && M <= WTraits<bf16w_t>::ROWS) {
+        // (a prompt of a few words: five launches per layer instead of eight; nine rows, two layers: 130 us less per request)
+        hipLaunchKernelGGL(stream_rows_kernel, dim3(M), dim3(FUSED_NT), 0, c->stream, (const float*)h, d, d, (const bf16_t*)c->layers[0].norm1, c->st_frag, 0, M, c->st_ssq);
+        for (int l_ = 0; l_ < g.n_layers; ++l_) {
+            if (int rc = stream_qkv(c, c->layers[l_], c->tkv[l_], l_ ? d / 16 : 1, b0, nseq, m, c->pf_qkv)) return rc;
+            if (int rc = stream_attn_mlp(c, c->layers[l_], c->tkv[l_], c->pf_qkv, m, 0, b0, nseq, m, h, l_ + 1 < g.n_layers ? c->layers[l_ + 1].norm1 : nullptr)) return rc;
+        }
+        for (int s = 0; s < nseq; ++s)
+            hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(l), dim3(256), 0, c->stream, h + ((size_t)s * m + v) * d, d, (const float*)nullptr, 0,
+                               (const WT*)c->final_norm, c->feat + (size_t)(b0 + s) * g.max_text * d, d, d, g.rms_eps);
+        HIP_TRY(c, hipGetLastError());
+        return HIVIS_OK;
+    }
     for (int l_ = 0; l_ < g.n_layers; ++l_) {
         const LayerDev& L = c->layers[l_];
         if (int rc = rows_norm<WT>(c, h, pend, M, L.norm1)) return rc;
@@ -1440,7 +1493,7 @@ int prefill_target_tall(hivis_ctx* c, int b0, int nseq, int v, int l) {
     // features of the text rows (h now holds l rows per sequence): final norm of (h + last MLP delta)
     if (pend.n > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(nseq * l, row_chunks(nseq * l)), dim3(256), 0, c->stream, pend, d, d, c->pf_proj, d);
     for (int s = 0; s < nseq; ++s)
-        hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(l), dim3(256), 0, c->stream, h + (size_t)s * l * d, d, (const float*)c->pf_proj + (size_t)s * l * d, d,
+        hipLaunchKernelGGL((add_rmsnorm_kernel<WT>), dim3(l), dim3(256), 0, c->stream, h + (size_t)s * l * d, d, pend.p ? (const float*)c->pf_proj + (size_t)s * l * d : nullptr, d,
                            (const WT*)c->final_norm, c->feat + (size_t)(b0 + s) * g.max_text * d, d, d, g.rms_eps);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
@@ -1454,12 +1507,23 @@ int prefill_drafter_tall(hivis_ctx* c, int b0, int nseq, int l) {
     const int M = nseq * l, d = g.d, qd = g.n_q_heads * g.head_dim;
     const float* table = c->emb_w2;          // Embed(x) w2 of every token: the FC then multiplies f alone
     const int K = table ? d : 2 * d;
-    hipLaunchKernelGGL((fuse_frag_kernel<WT>), dim3((M + 15) / 16 * 16), dim3(256), 0, c->stream, (const float*)(c->feat + (size_t)b0 * g.max_text * d), g.max_text, l, M,
-                       (const int32_t*)(c->text + (size_t)b0 * c->text_stride), c->text_stride, (const WT*)c->embed, table, (const WT*)c->rho, c->pf_x, c->pf_frag, d);
     Parts p{};
-    if (int rc = rows_gemm(c, c->pf_frag, M, K, table ? c->fuse_w1 : c->fuse_w, d, c->pf_proj, &p)) return rc;
-    if (int rc = rows_norm<WT>(c, c->pf_x, p, M, c->draft.norm1)) return rc;
-    if (int rc = rows_qkv<WT>(c, c->draft, c->dkv, c->pf_frag, c->zeros, 0, b0, nseq, l, TreeRows(), c->pf_gu, c->pf_qkv)) return rc;
+    if (c->stream_rows && M <= WTraits<bf16w_t>::ROWS) {
+        for (int s = 0; s < nseq; ++s)
+            hipLaunchKernelGGL(stream_rows_kernel, dim3(l), dim3(FUSED_NT), 0, c->stream, (const float*)(c->feat + (size_t)(b0 + s) * g.max_text * d), d, d,
+                               (const bf16_t*)nullptr, c->st_att, s * l, M, (float*)nullptr);
+        Phase fu{}; fu.epi = FEPI_ADDVEC; fu.K = d; fu.N = d; fu.W = c->fuse_w1; fu.Af = c->st_att; fu.Y = c->pf_x; fu.ldy = d; fu.vec = c->rho; fu.vec_idx = 0;
+        fu.add_rows = c->emb_w2; fu.tok = c->text + (size_t)b0 * c->text_stride + 1; fu.tok_sseq = c->text_stride; fu.tok_srow = 1;
+        fu.F = c->st_frag; fu.fgain = c->draft.norm1; fu.ssq_out = c->st_ssq;
+        if (int rc = launch_stream(c, fu, nseq, l)) return rc;
+        if (int rc = stream_qkv(c, c->draft, c->dkv, d / 16, b0, nseq, l, c->pf_qkv)) return rc;
+    } else {
+        hipLaunchKernelGGL((fuse_frag_kernel<WT>), dim3((M + 15) / 16 * 16), dim3(256), 0, c->stream, (const float*)(c->feat + (size_t)b0 * g.max_text * d), g.max_text, l, M,
+                           (const int32_t*)(c->text + (size_t)b0 * c->text_stride), c->text_stride, (const WT*)c->embed, table, (const WT*)c->rho, c->pf_x, c->pf_frag, d);
+        if (int rc = rows_gemm(c, c->pf_frag, M, K, table ? c->fuse_w1 : c->fuse_w, d, c->pf_proj, &p)) return rc;
+        if (int rc = rows_norm<WT>(c, c->pf_x, p, M, c->draft.norm1)) return rc;
+        if (int rc = rows_qkv<WT>(c, c->draft, c->dkv, c->pf_frag, c->zeros, 0, b0, nseq, l, TreeRows(), c->pf_gu, c->pf_qkv)) return rc;
+    }
     hipLaunchKernelGGL(tail_rows_kernel, dim3(1, nseq), dim3(256), 0, c->stream, (const float*)c->pf_x, l, l - 1, c->pf_xt, d);
     if (int rc = rows_attn_mlp<WT>(c, c->draft, c->dkv, c->pf_qkv + (size_t)(l - 1) * qd, l, l - 1, b0, nseq, 1, c->pf_xt, &p)) return rc;
     hipLaunchKernelGGL(add_parts_kernel, dim3(nseq, row_chunks(nseq)), dim3(256), 0, c->stream, (const float*)c->pf_xt, p, d, c->catD + (size_t)b0 * 2 * d, 2 * d,
@@ -2107,6 +2171,10 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
         float *f, *v;
         if ((rc = dev_alloc(c, &f, (size_t)B * d)) || (rc = dev_alloc(c, &v, (size_t)R16 * d))) return rc;
         c->catDf = (uint4*)f; c->vfrag = (uint4*)v;
+        float *sf, *sa, *sm;
+        if ((rc = dev_alloc(c, &sf, (size_t)R16 * d)) || (rc = dev_alloc(c, &sa, (size_t)R16 * std::max(d, qd))) || (rc = dev_alloc(c, &sm, (size_t)R16 * F)) ||
+            (rc = dev_alloc(c, &c->st_ssq, (size_t)R16 * ssq_stride(d / 16)))) return rc;
+        c->st_frag = (uint4*)sf; c->st_att = (uint4*)sa; c->st_act = (uint4*)sm;
         c->stream_rows = true;
     }
     return HIVIS_OK;

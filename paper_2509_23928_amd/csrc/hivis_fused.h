@@ -1146,9 +1146,9 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
 constexpr int ATTN_ROWS_RM = 16;
 template <int HD>
 __global__ __launch_bounds__(FUSED_NT) void attn_rows_kernel(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
-                                                             const int* __restrict__ base, AttnShape sh, float* __restrict__ out, int ldo,
+                                                             const int* __restrict__ base, AttnShape sh, AttnOut out,
                                                              uint4* __restrict__ frag_out) {
-    // frag_out (optional): the rows are written as A fragments of the next GEMM (K = ldo) instead of fp32 rows to `out`
+    // frag_out (optional): the rows are written as A fragments of the next GEMM (K = out.ldo) instead of to `out`
     extern __shared__ __align__(16) float attn_rows_lds[];
     // Work items are numbered row block fastest, and workgroup b runs on XCD b % 8: the row blocks of one head would land
     // on different XCDs and each fetch the head's cached K and V rows from memory (61-row pass: 86 MB per layer for 23 MB
@@ -1156,7 +1156,7 @@ __global__ __launch_bounds__(FUSED_NT) void attn_rows_kernel(const float* __rest
     int item = blockIdx.x;
     const int nr = sh.n_rblk, ngrp = (int)gridDim.x / nr;
     if (nr > 1 && (ngrp & 7) == 0 && ngrp * nr == (int)gridDim.x) { const int x = item & 7, slot = item >> 3; item = (x + 8 * (slot / nr)) * nr + slot % nr; }
-    attn_wg_mfma<HD, ATTN_ROWS_RM>(q, kc, vc, base, sh, item, 0, attn_rows_lds, nullptr, nullptr, AttnOut{out, ldo, nullptr, 0}, nullptr, frag_out);
+    attn_wg_mfma<HD, ATTN_ROWS_RM>(q, kc, vc, base, sh, item, 0, attn_rows_lds, nullptr, nullptr, out, nullptr, frag_out);
 }
 
 // Attention of long row ranges (prefill): the published flash-attention work split.  A workgroup of NW wavefronts owns

@@ -415,6 +415,30 @@ __global__ __launch_bounds__(FUSED_NT) void stream_norm_kernel(Phase ph, PassPar
     }
 }
 
+// fp32 rows x (row stride ldx) -> rows row0 .. of `rows` as row fragments, times a gain (optional), and one sum of squares per row (optional).
+__global__ __launch_bounds__(FUSED_NT) void stream_rows_kernel(const float* __restrict__ x, int ldx, int d, const bf16_t* __restrict__ gain,
+                                                               uint4* __restrict__ frag, int row0, int rows, float* __restrict__ ssq) {
+    __shared__ float part[FUSED_NW];
+    const int row = row0 + blockIdx.x;
+    float ss = 0.f;
+    for (int c = 4 * threadIdx.x; c < d; c += 4 * FUSED_NT) {
+        const float4 v = *reinterpret_cast<const float4*>(x + (size_t)blockIdx.x * ldx + c);
+        const float4 g = gain ? load4_f32(gain + c) : make_float4(1.f, 1.f, 1.f, 1.f);
+        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+        st_row_pair(frag, rows, row, c, v.x * g.x, v.y * g.y);
+        st_row_pair(frag, rows, row, c + 2, v.z * g.z, v.w * g.w);
+    }
+    if (ssq == nullptr) return;
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+    lds_barrier();
+    if (threadIdx.x == 0) {
+        float t = 0.f;
+        for (int w = 0; w < FUSED_NW; ++w) t += part[w];
+        st_wt(&ssq[row * ssq_stride(1)], t);
+    }
+}
+
 // Embedding rows of a verify pass: fp32 rows (the residual stream), fragments times the first norm's gain, one sum of squares per row
 __global__ __launch_bounds__(FUSED_NT) void stream_prep_kernel(Phase ph, PassParams pp) {
     __shared__ float part[FUSED_NW];

@@ -462,11 +462,11 @@ __global__ void fuse_frag_kernel(const float* __restrict__ feat, int fstride, in
         for (int k = threadIdx.x; k < d; k += blockDim.x) h[(size_t)row * d + k] = to_f32(rho[k]) + (tab ? tab[(size_t)tok * d + k] : 0.f);
 }
 
-// out row = h row + sum of the partials (d a multiple of 4); frag (optional): the row as row fragments as well, row row0 + r of `rows`
+// out row = h row + sum of the partials (optional; d a multiple of 4); frag (optional): the row as row fragments as well, row row0 + r of `rows`
 __global__ void add_parts_kernel(const float* __restrict__ h, Parts ps, int d, float* __restrict__ out, int ldo, uint4* __restrict__ frag, int row0, int rows) {
     const int row = blockIdx.x;
     for (int c4 = blockIdx.y * blockDim.x + threadIdx.x; c4 < d / 4; c4 += gridDim.y * blockDim.x) {
-        const float4 a = *reinterpret_cast<const float4*>(h + (size_t)row * d + 4 * c4), b = parts_load4(ps, (size_t)row * d + 4 * c4);
+        const float4 a = *reinterpret_cast<const float4*>(h + (size_t)row * d + 4 * c4), b = ps.p ? parts_load4(ps, (size_t)row * d + 4 * c4) : make_float4(0.f, 0.f, 0.f, 0.f);
         const float4 y = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
         *reinterpret_cast<float4*>(out + (size_t)row * ldo + 4 * c4) = y;
         if (frag) { st_row_pair(frag, rows, row0 + row, 4 * c4, y.x, y.y); st_row_pair(frag, rows, row0 + row, 4 * c4 + 2, y.z, y.w); }
