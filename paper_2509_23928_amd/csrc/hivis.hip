@@ -943,8 +943,10 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         }
         if constexpr (!std::is_same<WT, float>::value) {
             if (ph.type == PH_GEMM && ph.Af) {
-                // tiles of a workgroup in groups of at most 8, as even as they come (a kernel of fewer tiles takes more groups)
-                const int most = (ph.N / 16 + grid - 1) / grid, group = (most + (most + 7) / 8 - 1) / ((most + 7) / 8);
+                // tiles of a workgroup in groups of at most 8, as even as they come (a kernel of fewer tiles takes more groups).  Nine for the 8-row
+                // LM head: with w1's columns (2256 tiles) 47.6 us in one group of nine, 49.7 in two of five
+                const int most = (ph.N / 16 + grid - 1) / grid, upto = std::is_same<WT, bf16_t>::value && ph.epi == FEPI_LOGITS && ph.K > STREAM_SHORT_K ? 9 : 8;
+                const int ngroups = (most + upto - 1) / upto, group = (most + ngroups - 1) / ngroups;
                 const bool sh = ph.K <= STREAM_SHORT_K;
                 if constexpr (std::is_same<WT, bf16w_t>::value) {
                     // 9..16 rows and at most half as many tiles as CUs: a second workgroup per tile, each with half the rows in the 8-row form
@@ -969,7 +971,12 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                     if (group <= 2) HIVIS_STREAM2(FEPI_SILU, 2); else if (group <= 3) HIVIS_STREAM2(FEPI_SILU, 3); else if (group <= 4) HIVIS_STREAM(FEPI_SILU, 4);
                     else if (group <= 6) HIVIS_STREAM(FEPI_SILU, 6); else HIVIS_STREAM(FEPI_SILU, 8);
                     break;
-                case FEPI_LOGITS: if (group <= 2) HIVIS_STREAM(FEPI_LOGITS, 2); else if (group <= 4) HIVIS_STREAM(FEPI_LOGITS, 4); else if (group <= 6) HIVIS_STREAM2(FEPI_LOGITS, 6); else HIVIS_STREAM2(FEPI_LOGITS, 8); break;
+                case FEPI_LOGITS: if (group <= 2) HIVIS_STREAM(FEPI_LOGITS, 2); else if (group <= 4) HIVIS_STREAM(FEPI_LOGITS, 4); else if (group <= 6) HIVIS_STREAM2(FEPI_LOGITS, 6);
+                    else {
+                        if constexpr (std::is_same<WT, bf16_t>::value) { if (group > 8) { HIVIS_STREAM(FEPI_LOGITS, 9); break; } }
+                        HIVIS_STREAM2(FEPI_LOGITS, 8);
+                    }
+                    break;
                 default: return fail(c, HIVIS_EINVAL, "phase %d: no kernel for epilogue %d", p, ph.epi);
                 }
 #undef HIVIS_STREAM2

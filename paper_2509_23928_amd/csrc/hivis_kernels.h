@@ -115,6 +115,16 @@ __device__ __forceinline__ void st_row_pair(uint4* __restrict__ frag, int M, int
     st_wt(p + 16 * M, lo);
 }
 
+// four of them, k a multiple of 4
+__device__ __forceinline__ void st_row_quad(uint4* __restrict__ frag, int M, int row, int k, float a, float b, float c, float d) {
+    uint2 hi, lo;
+    f32_to_bf16x2_hilo(a, b, hi.x, lo.x);
+    f32_to_bf16x2_hilo(c, d, hi.y, lo.y);
+    unsigned long long* p = reinterpret_cast<unsigned long long*>(frag + ((size_t)(k >> 5) * 2 * M + row) * 4 + ((k >> 3) & 3)) + ((k >> 2) & 1);
+    __hip_atomic_store(p, __builtin_bit_cast(unsigned long long, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 8 * M, __builtin_bit_cast(unsigned long long, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // KV-cache storage that goes with a weight type.  fp32 models keep K and V in fp32.  bf16 models keep every cached
 // value as TWO IEEE halves, hi = half(x) and lo = half(x - hi) (about 22 mantissa bits), in one row of 2*HD halves:
 // [hi 0..HD) | lo 0..HD)].  Both halves are MFMA operands as they are.  One half alone is not enough at depth: the

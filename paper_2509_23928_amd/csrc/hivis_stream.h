@@ -409,8 +409,7 @@ __global__ __launch_bounds__(FUSED_NT) void stream_norm_kernel(Phase ph, PassPar
             float* o = ph.Y + (size_t)row * ph.ldy + c;
 #pragma unroll
             for (int j = 0; j < 4; ++j) st_wt(o + j, y[j]);
-            st_row_pair(ph.F, pp.M, row, c, y[0], y[1]);
-            st_row_pair(ph.F, pp.M, row, c + 2, y[2], y[3]);
+            st_row_quad(ph.F, pp.M, row, c, y[0], y[1], y[2], y[3]);
         }
     }
 }
@@ -425,8 +424,7 @@ __global__ __launch_bounds__(FUSED_NT) void stream_rows_kernel(const float* __re
         const float4 v = *reinterpret_cast<const float4*>(x + (size_t)blockIdx.x * ldx + c);
         const float4 g = gain ? load4_f32(gain + c) : make_float4(1.f, 1.f, 1.f, 1.f);
         ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        st_row_pair(frag, rows, row, c, v.x * g.x, v.y * g.y);
-        st_row_pair(frag, rows, row, c + 2, v.z * g.z, v.w * g.w);
+        st_row_quad(frag, rows, row, c, v.x * g.x, v.y * g.y, v.z * g.z, v.w * g.w);
     }
     if (ssq == nullptr) return;
     ss = wave_sum(ss);
@@ -452,8 +450,7 @@ __global__ __launch_bounds__(FUSED_NT) void stream_prep_kernel(Phase ph, PassPar
         ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
         float* y = ph.Y + (size_t)row * ph.ldy + c;
         st_wt(y, x.x); st_wt(y + 1, x.y); st_wt(y + 2, x.z); st_wt(y + 3, x.w);
-        st_row_pair(ph.F, pp.M, row, c, x.x * gn.x, x.y * gn.y);
-        st_row_pair(ph.F, pp.M, row, c + 2, x.z * gn.z, x.w * gn.w);
+        st_row_quad(ph.F, pp.M, row, c, x.x * gn.x, x.y * gn.y, x.z * gn.z, x.w * gn.w);
     }
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;

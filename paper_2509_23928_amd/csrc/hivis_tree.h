@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, 
     __syncthreads();
     const float4* h = reinterpret_cast<const float4*>(H + (size_t)pick[0] * d);
     if (frag) {
-        for (int c = i; c < d / 4; c += 256) { const float4 x = h[c]; st_row_pair(frag, k, want, 4 * c, x.x, x.y); st_row_pair(frag, k, want, 4 * c + 2, x.z, x.w); }
+        for (int c = i; c < d / 4; c += 256) { const float4 x = h[c]; st_row_quad(frag, k, want, 4 * c, x.x, x.y, x.z, x.w); }
         return;
     }
     float* o = cat + (size_t)want * 2 * d;
@@ -337,7 +337,7 @@ __global__ void tree_roll_cat_kernel(const float* __restrict__ g, int ldg, const
     if (frag) {
         for (int c = threadIdx.x; c < d / 4; c += blockDim.x) {
             const float4 x = f[c];
-            st_row_pair(frag, gridDim.x, e, 4 * c, x.x, x.y); st_row_pair(frag, gridDim.x, e, 4 * c + 2, x.z, x.w);
+            st_row_quad(frag, gridDim.x, e, 4 * c, x.x, x.y, x.z, x.w);
         }
         return;
     }
@@ -469,7 +469,7 @@ __global__ void add_parts_kernel(const float* __restrict__ h, Parts ps, int d, f
         const float4 a = *reinterpret_cast<const float4*>(h + (size_t)row * d + 4 * c4), b = ps.p ? parts_load4(ps, (size_t)row * d + 4 * c4) : make_float4(0.f, 0.f, 0.f, 0.f);
         const float4 y = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
         *reinterpret_cast<float4*>(out + (size_t)row * ldo + 4 * c4) = y;
-        if (frag) { st_row_pair(frag, rows, row0 + row, 4 * c4, y.x, y.y); st_row_pair(frag, rows, row0 + row, 4 * c4 + 2, y.z, y.w); }
+        if (frag) { st_row_quad(frag, rows, row0 + row, 4 * c4, y.x, y.y, y.z, y.w); }
     }
 }
 
