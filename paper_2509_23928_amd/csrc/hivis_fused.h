@@ -11,6 +11,9 @@
 // Used for passes of at most one MFMA tile of rows: 16 for fp32 weights, 8 for bf16 with the high and low activation parts in
 // one operand; bf16 passes of 9..16 rows and the levels of a draft tree take the 16-row form of the GEMM phases (bf16w_t: two
 // operands), one launch per phase.
+// Where a bf16 program has one launch per phase, the fusion FC's table and rows of up to STREAM_MAX_D values, its producers store
+// row fragments and its GEMM phases run in stream_kernel (hivis_stream.h), which stages nothing; gemm_phase, which stages fp32 rows,
+// serves fp32 models, the q|k|v phase of a draft step (its rows are a sum with a table row that it picks first) and the rest.
 //
 // Memory discipline between phases (the L2 is per XCD and not coherent across XCDs): every buffer that one
 // phase writes and a later phase reads is written AT MOST ONCE per launch, with write-through stores, and is

@@ -49,8 +49,11 @@ __device__ __forceinline__ void from_f32(f16_t& dst, float x) {   // round to ne
     dst = (f16_t)fminf(fmaxf(x, -65504.f), 65504.f);
 }
 
-// 16 bytes of a weight matrix that one workgroup reads once (non-temporal: 1.09 GB at 6.9 TB/s instead of 6.15)
+// 16 bytes of a weight matrix that one workgroup reads once (non-temporal: 1.09 GB at 6.9 TB/s instead of 6.15; fp32 models are a few
+// MB and live in the L2: the hint made their decode passes 2 % slower)
+template <typename WT>
 __device__ __forceinline__ uint4 load_stream(const uint4* p) {
+    if constexpr (std::is_same<WT, float>::value) return *p;
     typedef unsigned u4_t __attribute__((ext_vector_type(4)));
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u4_t*>(p)));
 }
@@ -413,14 +416,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const float* __res
             const uint4* wp = Wp + ((size_t)tg * kblks + kb0) * 64 + lane;
 #pragma unroll
             for (int j = 0; j < KBW; ++j)
-                if (j < nkb) wb[0][j] = load_stream(wp + (size_t)j * 64); else wb[0][j] = make_uint4(0, 0, 0, 0);
+                if (j < nkb) wb[0][j] = load_stream<WT>(wp + (size_t)j * 64); else wb[0][j] = make_uint4(0, 0, 0, 0);
             if constexpr (UPFRONT) {
 #pragma unroll
                 for (int g = 1; g < G; ++g) {
                     const uint4* wn = wp + (size_t)min(g, ng - 1) * kblks * 64;      // tiles beyond the group: a clamped (unused) one
 #pragma unroll
                     for (int j = 0; j < KBW; ++j)
-                        if (j < nkb) wb[g][j] = load_stream(wn + (size_t)j * 64); else wb[g][j] = make_uint4(0, 0, 0, 0);
+                        if (j < nkb) wb[g][j] = load_stream<WT>(wn + (size_t)j * 64); else wb[g][j] = make_uint4(0, 0, 0, 0);
                 }
             }
             ARaw<WT> raw[T][KBW];
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const float* __res
                             const uint4* wn = wp + (size_t)(g + 1) * kblks * 64;
 #pragma unroll
                             for (int j = 0; j < KBW; ++j)
-                                if (j < nkb) wb[(g + 1) & 1][j] = load_stream(wn + (size_t)j * 64); else wb[(g + 1) & 1][j] = make_uint4(0, 0, 0, 0);
+                                if (j < nkb) wb[(g + 1) & 1][j] = load_stream<WT>(wn + (size_t)j * 64); else wb[(g + 1) & 1][j] = make_uint4(0, 0, 0, 0);
                         }
                     }
 #pragma unroll
@@ -963,7 +966,7 @@ __global__ __launch_bounds__(512) void calib_stream_kernel(const uint4* __restri
         const uint4* p = buf + t * 4096 + (size_t)wave * 512 + lane;
         uint4 v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = load_stream(p + (size_t)j * 64);
+        for (int j = 0; j < 8; ++j) v[j] = load_stream<bf16_t>(p + (size_t)j * 64);
 #pragma unroll
         for (int j = 0; j < 8; ++j) { acc.x ^= v[j].x; acc.y ^= v[j].y; acc.z ^= v[j].z; acc.w ^= v[j].w; }
     }
