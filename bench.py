@@ -273,7 +273,7 @@ def main():
     k_us = k_ms / max(k_launches, 1) * 1e3
     k_gbs = k_bytes / (k_us * 1e-6) / 1e9 if k_launches else 0.0
     out["roofline"] = {"bound": "hbm",
-                       "kernel": "phase_kernel<bf16, GEMM, gate|up>: fused RMSNorm + [d x 2F] weight stream + SiLU*up of the verify pass "
+                       "kernel": "stream_kernel<bf16, gate|up>: fused RMSNorm + [d x 2F] weight stream + SiLU*up of the verify pass "
                                  "(largest share of bytes and of time); HIP start/stop events attached to every 8th launch on the library's stream (hipExtLaunchKernel: the kernel's own begin/end timestamps, no marker packets in the queue)",
                        "achieved": k_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": k_gbs / HBM_PEAK_GBS,
                        "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(args.config), "algorithmic_bytes_per_launch": k_bytes,
