@@ -6,7 +6,7 @@
 // multiplies; 1/rms is applied to the sums.  (Staging fp32 rows instead, every workgroup of every launch converted every row and
 // moved it through LDS before its first product: two further dependent steps at the start of each launch, a thousand vector
 // instructions per wavefront, and registers that the weights in flight need.)  HBM bound.  Kernel traces, before -> now: 7B widths, 6 rows:
-// q|k|v 20.4 -> 20.0 us, O 11.3 -> 9.3, gate|up 32.0 -> 31.1, down 20.1 -> 18.8, attention (which now writes fragments) 13.4 -> 11.9; LM head 49.3 ->
+// q|k|v 20.4 -> 20.0 us, O 11.3 -> 9.3, gate|up 32.0 -> 31.1, down 20.1 -> 18.8, attention (which now writes fragments) 13.4 -> 11.6; LM head 49.3 ->
 // 46.2; 2048 wide, 12 rows: q|k|v 10.2 -> 7.8, O 9.5 -> 6.0, gate|up 14.4 -> 11.0, down 18.0 -> 10.8.  A plain stream of the same bytes takes 16.4, 6.4,
 // 27.2, 14.7 and 38.5 us.
 //
