@@ -402,8 +402,9 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     }
     float4 araw[QM]; gain4_t graw = gain4_t();
     float4 araw2[SINGLE ? QM : 1]; gain4_t graw2 = gain4_t();      // rows of the second pass of a pair (one tile per workgroup)
-    float4 braw[TAB ? QM : 1];                                     // QKV with add_rows: the table rows added to the activation rows
-#define HIVIS_LOAD_RAW_TO(ps, ARAW, GRAW)                                                                          \
+    float4 braw[TAB ? QM : 1];                                     // QKV with add_rows: the table rows added to the activation rows,
+    float4 braw2[TAB && SINGLE ? QM : 1];                          // and those of the second pass of a pair
+#define HIVIS_LOAD_RAW_TO(ps, ARAW, GRAW, BRAW)                                                                    \
     {                                                                                                              \
         const int k_ = min(unit_kb0<NW, KBW>(kblks, ps, wave) * KB + 4 * col4, K - 4);                             \
         if (gain) GRAW = *reinterpret_cast<const gain4_t*>(gain + k_);   /* converted where it is used: no wait here */ \
@@ -412,13 +413,13 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             const int row_ = min(row0 + q * RS, M - 1);                                                            \
             if (from_emb_) ARAW[q] = load4_f32(reinterpret_cast<const WT*>(ph.emb) + (size_t)clamp_token(tokr[q], pp.V) * (K / 2) + (k_ - K / 2)); \
             else ARAW[q] = *reinterpret_cast<const float4*>(A + (size_t)row_ * lda + k_);                          \
-            if (TAB) braw[q] = *reinterpret_cast<const float4*>(ph.add_rows + (size_t)clamp_token(tokr[q], pp.V) * K + k_); \
+            if (TAB) BRAW[q] = *reinterpret_cast<const float4*>(ph.add_rows + (size_t)clamp_token(tokr[q], pp.V) * K + k_); \
         }                                                                                                          \
     }
-#define HIVIS_LOAD_RAW(ps) HIVIS_LOAD_RAW_TO(ps, araw, graw)
-    // Stage this wavefront's slice of pass `ps` (whose rows are in ARAW) into its LDS slice as MFMA fragments, run
+#define HIVIS_LOAD_RAW(ps) HIVIS_LOAD_RAW_TO(ps, araw, graw, braw)
+    // Stage this wavefront's slice of pass `ps` (whose rows are in ARAW, and BRAW) into its LDS slice as MFMA fragments, run
     // NEXT (the request for the rows staged next, or nothing), and fetch the fragments af[0..KBW).
-#define HIVIS_STAGE_FROM(ps, ARAW, GRAW, do_ssq, NEXT)                                                             \
+#define HIVIS_STAGE_FROM(ps, ARAW, GRAW, BRAW, do_ssq, NEXT)                                                       \
     {                                                                                                              \
         const int nkb_ = unit_nkb<NW, KBW>(kblks, ps, wave);                                                       \
         _Pragma("unroll") for (int q = 0; q < QM; ++q) {                                                           \
@@ -426,7 +427,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             if (row_ < M && 4 * col4 < nkb_ * KB) {                                                                \
                 float x_[4] = {ARAW[q].x, ARAW[q].y, ARAW[q].z, ARAW[q].w};                                        \
                 if (TAB) {                                                                                         \
-                    x_[0] += braw[q].x; x_[1] += braw[q].y; x_[2] += braw[q].z; x_[3] += braw[q].w;                \
+                    x_[0] += BRAW[q].x; x_[1] += BRAW[q].y; x_[2] += BRAW[q].z; x_[3] += BRAW[q].w;                \
                     if (blockIdx.x == 0 && tg == t_begin) {                                                        \
                         float* wb_ = ph.wb + (size_t)row_ * K + unit_kb0<NW, KBW>(kblks, ps, wave) * KB + 4 * col4; \
                         st_wt(wb_, x_[0]); st_wt(wb_ + 1, x_[1]); st_wt(wb_ + 2, x_[2]); st_wt(wb_ + 3, x_[3]);    \
@@ -450,7 +451,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
         __builtin_amdgcn_wave_barrier();                                                                           \
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                                     \
     }
-#define HIVIS_STAGE(ps, nx, do_ssq) HIVIS_STAGE_FROM(ps, araw, graw, do_ssq, if ((nx) >= 0) HIVIS_LOAD_RAW(nx))
+#define HIVIS_STAGE(ps, nx, do_ssq) HIVIS_STAGE_FROM(ps, araw, graw, braw, do_ssq, if ((nx) >= 0) HIVIS_LOAD_RAW(nx))
     // Tokens = greedy tokens of the LM-head phase before this one (fusion FC with ph.tok == null): every wavefront
     // reduces that phase's candidates itself (lowest index wins ties); workgroup 0 also stores them.
     const bool cand_tokens = ((EPI == FEPI_ADDVEC && (ph.emb != nullptr || ph.add_rows != nullptr)) || TAB) && ph.tok == nullptr;
@@ -506,22 +507,22 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             //      compiler waits for "all loads" wherever one is used (conditional loads defeat its counting), so what
             //      matters is how much is in flight per wait: two units here.  With one unit requested per pass every
             //      pass paid a memory round trip for 8 KiB per wavefront and the kernel was latency-bound.
-            if (npass > 1) HIVIS_LOAD_RAW_TO(1, araw2, graw2)
+            if (npass > 1) HIVIS_LOAD_RAW_TO(1, araw2, graw2, braw2)
             if (!wb1_first && npass > 1) issue_unit<WT>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, 1, wave), unit_nkb<NW, KBW>(kblks, 1, wave), lane);
             for (int pass = 0; pass < npass; pass += 2) {
-                HIVIS_STAGE_FROM(pass, araw, graw, true, )
+                HIVIS_STAGE_FROM(pass, araw, graw, braw, true, )
                 if (pass == 0) { HIVIS_MARK(1) }
                 mfma_unit(acc[0], af, head);
                 if (pass + 1 < npass) {
-                    HIVIS_STAGE_FROM(pass + 1, araw2, graw2, true, )
+                    HIVIS_STAGE_FROM(pass + 1, araw2, graw2, braw2, true, )
                     mfma_unit(acc[0], af, wb1);
                 }
                 if (pass + 2 < npass) {
-                    HIVIS_LOAD_RAW_TO(pass + 2, araw, graw)
+                    HIVIS_LOAD_RAW_TO(pass + 2, araw, graw, braw)
                     issue_unit<WT>(head, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 2, wave), unit_nkb<NW, KBW>(kblks, pass + 2, wave), lane);
                 }
                 if (pass + 3 < npass) {
-                    HIVIS_LOAD_RAW_TO(pass + 3, araw2, graw2)
+                    HIVIS_LOAD_RAW_TO(pass + 3, araw2, graw2, braw2)
                     issue_unit<WT>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 3, wave), unit_nkb<NW, KBW>(kblks, pass + 3, wave), lane);
                 }
             }
