@@ -367,7 +367,7 @@ int attention(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int*
     return HIVIS_OK;
 }
 
-AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, int ldq, int* items_out);
+AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, int ldq, bool alone, int* items_out);
 
 // Attention of nseq x m rows on the matrix cores, outside a phase program (prefill; passes with more rows than one MFMA
 // tile): the same workgroup routine as the verify pass (one item = one kv head x <= 8 (head,row) pairs, all visible
@@ -434,7 +434,7 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
     int items = 0;
     Phase ph{};
     ph.type = PH_ATTN;
-    ph.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, ldq, &items);
+    ph.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, ldq, false, &items);
     ph.att.seq0 = seq0; ph.att.nsplit = 1; ph.att.tmask = tmask; ph.att.flags = c->attn_flags; ph.att.qrows = qrows;
     ph.att_items = items;
     ph.A = q; ph.kc = kv.k; ph.vc = kv.v; ph.maxL = kv.maxL; ph.base = base; ph.offset = offset;
@@ -555,19 +555,16 @@ enum { PROG_VERIFY = 0, PROG_DRAFT = 1, PROG_ROLL = 2, PROG_DRAFT_SAMPLE = 3 };
 template <typename WT>
 bool fused_rows_ok(const hivis_ctx* c, int M) { return M <= (sizeof(WT) == 2 && !c->persistent ? WTraits<bf16w_t>::ROWS : WTraits<WT>::ROWS); }
 
-AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, int ldq, int* items_out) {
+// alone (fp32 caches only): each head and row an item of its own while there are CUs for them.  The vector ALU works on an item's rows one
+// after the other: verify of 5 rows x 4 heads 10.9 -> 6.2 us.  (The matrix cores of the bf16 models take all rows of an item at once.)
+AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, int ldq, bool alone, int* items_out) {
     const hivis_config& g = c->cfg;
     AttnShape sh{};
     sh.Hq = g.n_q_heads; sh.Hkv = g.n_kv_heads; sh.m = m;
-    const int group = g.n_q_heads / g.n_kv_heads;
-    // (fp32 caches: the vector ALU works on an item's rows one after the other, so each row is an item of its own while there are CUs for them:
-    // verify of 5 rows x 4 heads 10.9 -> 6.2 us; the matrix cores of the bf16 models take all rows of an item at once)
-    if (g.dtype == HIVIS_F32 && nseq * g.n_q_heads * m <= c->fused_grid) { sh.mi = 1; sh.gh = 1; }
-    else if (m >= FUSED_RMAX) { sh.mi = FUSED_RMAX; sh.gh = 1; }
-    else { sh.mi = m; sh.gh = std::max(1, std::min(group, FUSED_RMAX / m)); }
-    sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
+    const AttnCut cut = attn_cut(nseq, m, g.n_q_heads, g.n_kv_heads, alone && nseq * g.n_q_heads * m <= c->fused_grid);
+    sh.mi = cut.mi; sh.gh = cut.gh; sh.n_hblk = cut.n_hblk; sh.n_rblk = cut.n_rblk;
     sh.seq0 = 0; sh.offset = offset; sh.maxL = maxL; sh.ldq = ldq; sh.nwaves = FUSED_NW;
-    const int items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
+    const int items = cut.items;
     // (with the splits of an item on one XCD the grid holds whole rounds of eight items: more workgroups than CUs would take two turns,
     // 14.4 -> 23.5 us for 28 items in nine splits)
     sh.nsplit = std::min(ATTN_MAX_SPLITS, std::max(1, c->fused_grid / ((c->attn_flags & 2) ? (items + 7) / 8 * 8 : items)));
@@ -591,7 +588,7 @@ struct Pool {
 // of the layer output (row stride ldd).
 template <typename WT>
 float* layer_phases(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const LayerDev& L, const KVDev& kv, float* h, const int* base,
-                    int offset, int nseq, int m, float* dst, int ldd, int* ld_out, bool persistent, bool elect) {
+                    int offset, int nseq, int m, float* dst, int ldd, int* ld_out, bool persistent, bool elect, bool alone) {
     const hivis_config& g = c->cfg;
     const int M = nseq * m;
     const int d = g.d, qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim, F = g.ffn, nqkv = qd + 2 * kd;
@@ -605,8 +602,8 @@ float* layer_phases(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const Layer
     q.gain = L.norm1; q.Y = qkv; q.ldy = nqkv; q.kc = kv.k; q.vc = kv.v; q.maxL = kv.maxL; q.base = base; q.offset = offset; q.rope = c->rope_tab; q.bias = L.bqkv;
     P.push_back(q);
     Phase a{}; a.type = PH_ATTN; a.A = qkv; a.lda = nqkv; a.kc = kv.k; a.vc = kv.v; a.maxL = kv.maxL; a.base = base; a.offset = offset;
-    a.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, nqkv, &a.att_items);
-    a.ws = pool.take((size_t)a.att_items * a.att.nsplit * FUSED_RMAX * (g.head_dim + 2));
+    a.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, nqkv, alone, &a.att_items);
+    a.ws = pool.take(attn_partials(c->fused_grid, a.att_items) * FUSED_RMAX * (g.head_dim + 2));
     if (persistent || elect) {
         a.cnt = (int*)pool.take((size_t)a.att_items);  // zero from the pool's memset; the merging workgroup re-zeroes it
         a.Y = att; a.ldy = qd;
@@ -653,8 +650,8 @@ void layer_stream(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const LayerDe
     q.Af = in.F; q.ssq = in.ssq; q.nssq = in.nssq;
     P.push_back(q);
     Phase a{}; a.type = PH_ATTN; a.A = qrows; a.lda = qd; a.kc = kv.k; a.vc = kv.v; a.maxL = kv.maxL; a.base = base; a.offset = offset;
-    a.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, qd, &a.att_items);
-    a.ws = pool.take((size_t)a.att_items * a.att.nsplit * FUSED_RMAX * (g.head_dim + 2));
+    a.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, qd, false, &a.att_items);
+    a.ws = pool.take(attn_partials(c->fused_grid, a.att_items) * FUSED_RMAX * (g.head_dim + 2));
     a.F = attF; a.ldy = qd;
     if (elect) a.cnt = (int*)pool.take((size_t)a.att_items);       // zero from the pool's memset; the merging workgroup re-zeroes it
     P.push_back(a);
@@ -674,7 +671,7 @@ void layer_stream(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const LayerDe
 int lm_candidates(const hivis_ctx* c, int N, bool persistent) { return persistent ? c->fused_grid : std::min(c->fused_grid, N / 16); }
 
 template <typename WT>
-void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>& P, bool persistent, bool elect, bool stream, bool lm_ext) {
+void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>& P, bool persistent, bool elect, bool stream, bool lm_ext, bool alone) {
     const hivis_config& g = c->cfg;
     const int B = g.batch, d = g.d, V = g.vocab, G = c->fused_grid;
     int ld = d;
@@ -769,7 +766,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
         Phase pr{}; pr.type = PH_PREP; pr.ids = c->row_tok; pr.id_sseq = m; pr.id_srow = 1; pr.gain = c->embed; pr.Y = x; pr.ldy = d;
         pr.base = c->tlen; pr.offset = 0;
         P.push_back(pr);
-        for (int l = 0; l < g.n_layers; ++l) x = layer_phases<WT>(c, P, pool, c->layers[l], c->tkv[l], x, c->tlen, 0, B, m, nullptr, 0, &ld, persistent, elect);
+        for (int l = 0; l < g.n_layers; ++l) x = layer_phases<WT>(c, P, pool, c->layers[l], c->tkv[l], x, c->tlen, 0, B, m, nullptr, 0, &ld, persistent, elect, alone);
         Phase nr{}; nr.type = PH_NORM_ROWS; nr.A = x; nr.lda = d; nr.gain = c->final_norm; nr.Y = c->catT; nr.ldy = 2 * d;
         P.push_back(nr);
         Phase lm{}; lm.type = PH_GEMM; lm.pro = PRO_PLAIN; lm.epi = FEPI_LOGITS; lm.K = d; lm.N = V; lm.W = c->lm_head; lm.A = c->catT; lm.lda = 2 * d;
@@ -824,7 +821,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
                 if (!ext) P.push_back(fu);
                 const size_t qi = P.size();
                 const int ncand = lm_candidates(c, lm.N, persistent);
-                layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, i - 1, B, 1, cat_next, 2 * d, &ld, persistent, elect);
+                layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, i - 1, B, 1, cat_next, 2 * d, &ld, persistent, elect, alone);
                 if (ext) {      // the layer's first phase (QKV): rows = u_part + table[token], tokens from this step's candidates, u written back
                     Phase& q = P[qi];
                     q.A = u_part; q.lda = d; q.add_rows = c->emb_w2; q.wb = u; q.tok = nullptr; q.pm = lm.pm; q.pi = lm.pi; q.ncand = ncand;
@@ -848,7 +845,7 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
             P.push_back(pr);
         }
         P.push_back(fu);
-        layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, 0, B, m, c->dout, d, &ld, persistent, elect);
+        layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, 0, B, m, c->dout, d, &ld, persistent, elect, alone);
     }
     // chain the GEMM phases for the cross-barrier weight prefetch
     for (size_t i = 0; i < P.size(); ++i) {
@@ -865,12 +862,13 @@ int get_program(hivis_ctx* c, int kind, int K, hivis_ctx::Program* out) {
     if (it != c->programs.end()) { *out = it->second; return HIVIS_OK; }
     std::vector<Phase> P;
     Pool count;
-    build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect, c->stream_rows, c->lm_ext);           // sizes only
+    const bool alone = std::is_same<WT, float>::value;
+    build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect, c->stream_rows, c->lm_ext, alone);           // sizes only
     Pool pool;
     if (int rc = dev_alloc(c, &pool.base, count.used)) return rc;
     HIP_TRY(c, hipMemsetAsync(pool.base, 0, count.used * sizeof(float), c->stream));      // (on the stream of the passes that count on it)
     P.clear();
-    build_phases<WT>(c, kind, K, pool, P, c->persistent, c->attn_elect, c->stream_rows, c->lm_ext);
+    build_phases<WT>(c, kind, K, pool, P, c->persistent, c->attn_elect, c->stream_rows, c->lm_ext, alone);
     hivis_ctx::Program pg;
     pg.n = (int)P.size();
     if (int rc = dev_alloc(c, &pg.dev, P.size())) return rc;
@@ -1130,23 +1128,25 @@ int draft_noalloc(hivis_ctx* c, int K) {
     const hivis_config& g = c->cfg;
     std::vector<Phase>& P = c->na_phases;
     if (draft_phase_capacity(K) > P.capacity()) return fail(c, HIVIS_ECAP, "phase list of K=%d exceeds the storage reserved at create", K);
-    // Accepted is what fits as the plain list: fp32 rows between the phases, and for fp32 models a launch of the fusion FC per step.  Row
-    // fragments, and the FC on the LM-head launch of fp32 models, where they fit as well.
-    auto size = [&](bool stream, bool ext) {
+    // Accepted is what fits as the plain list: fp32 rows between the phases, and for fp32 models a launch of the fusion FC per step and
+    // attention items that share their keys.  Row fragments, and for fp32 models items of one row and the FC on the LM-head launch,
+    // where they fit as well.
+    auto size = [&](bool stream, bool ext, bool alone) {
         P.clear();
         Pool count;
-        build_phases<WT>(c, PROG_DRAFT, K, count, P, false, false, stream, ext);            // sizes only
+        build_phases<WT>(c, PROG_DRAFT, K, count, P, false, false, stream, ext, alone);            // sizes only
         return count.used * sizeof(float);
     };
     const bool bf16 = sizeof(WT) == 2;
-    const size_t need = size(false, bf16 && c->lm_ext);
-    const bool ext = c->lm_ext && (bf16 || size(false, true) <= (size_t)HIVIS_SCRATCH_BYTES);
-    const bool stream = c->stream_rows && size(true, ext) <= (size_t)HIVIS_SCRATCH_BYTES;
+    const size_t need = size(false, bf16 && c->lm_ext, false);
+    const bool alone = !bf16 && size(false, false, true) <= (size_t)HIVIS_SCRATCH_BYTES;
+    const bool ext = c->lm_ext && (bf16 || size(false, true, alone) <= (size_t)HIVIS_SCRATCH_BYTES);
+    const bool stream = c->stream_rows && size(true, ext, alone) <= (size_t)HIVIS_SCRATCH_BYTES;
     if (need > (size_t)HIVIS_SCRATCH_BYTES)
         return fail(c, HIVIS_ECAP, "draft round of K=%d needs %zu bytes of scratch, the static array holds %u", K, need, (unsigned)HIVIS_SCRATCH_BYTES);
     P.clear();
     Pool pool; pool.base = (float*)c->scratch_dev;                  // the looked-up device address, not the array's name
-    build_phases<WT>(c, PROG_DRAFT, K, pool, P, false, false, stream, ext);
+    build_phases<WT>(c, PROG_DRAFT, K, pool, P, false, false, stream, ext, alone);
     PassParams pp{};
     pp.phases = nullptr; pp.nphases = (int)P.size();
     pp.M = g.batch; pp.nseq = g.batch; pp.m = 1;
@@ -1796,7 +1796,7 @@ void tree_rows_phases(hivis_ctx* c, int m, const float* cat, const int32_t* tok,
     P.push_back(fu);
     const size_t l0 = P.size();
     int ld = d;
-    layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, offset, 1, m, out, d, &ld, false, c->attn_elect);
+    layer_phases<WT>(c, P, pool, c->draft, c->dkv, u, c->dlen, offset, 1, m, out, d, &ld, false, c->attn_elect, false);
     for (size_t i = l0; i < P.size(); ++i) {
         P[i].pos_delta = tr.pos_delta; P[i].att.tmask = tr.mask;
         if (P[i].type == PH_ATTN && c->attn_elect) P[i].cnt = counters;

@@ -31,7 +31,6 @@ enum { PH_GEMM = 0, PH_ATTN = 1, PH_ATTN_MERGE = 2, PH_PREP = 3, PH_NORM_ROWS = 
 enum { PRO_PLAIN = 0, PRO_RMS = 1 };
 // kernel variant of PH_ATTN (in the place of an epilogue): the cached rows with the non-temporal hint (rule: launch_phases)
 enum { ATTN_ONCE = 1 };
-constexpr int FUSED_RMAX = 8;      // (head,row) pairs per attention work item in the persistent kernel
 enum { FEPI_ADD_TO = 1, FEPI_ADDVEC = 2, FEPI_QKV = 3, FEPI_SILU = 4, FEPI_LOGITS = 5,
        FEPI_QKV_TAB = 6,     // kernel variants only (never a Phase.epi): QKV whose rows are A + add_rows[token], see Phase.wb;
        FEPI_QKV_TAB4 = 7 };  // two staged rows (at most two sequences) / four staged rows (three or four sequences)
@@ -732,7 +731,6 @@ __host__ __device__ constexpr size_t fused_attn_lds_floats(int hd, int nw, int r
 // requested before anything waits (the partials come from memory, a round trip of more than a microsecond: a loop
 // that loads split after split spent 8-10 us here), which is why the split count is bounded at compile time.
 // wl: LDS scratch of 3 * ATTN_MAX_SPLITS * RM floats that nothing else uses until the routine returns.
-constexpr int ATTN_MAX_SPLITS = 16;
 // An attention item's row block, head block, key head and sequence; quotients by run-time values only where they are needed (some forty
 // dependent instructions each: the attention kernels spent their first microsecond on them)
 struct AttnItem { int rblk, hblk, kvh, sl, group; };

@@ -1,4 +1,5 @@
-// Sizes of the whole-prompt prefill buffers (bf16 models), which of them holds what, and the plans of the GEMMs that fill them.
+// Sizes of the whole-prompt prefill buffers (bf16 models), which of them holds what, the plans of the GEMMs that fill them, and the work
+// items of the phase programs' attention.
 // Host arithmetic only, no HIP: the library sizes and checks with it, and a test compiles it alone.
 #pragma once
 #include <algorithm>
@@ -86,5 +87,23 @@ inline size_t splitk_floats(int num_cu, int d, int qd, int kd, int F, int rows) 
     }
     return need;
 }
+
+// Attention of a phase program: work items of up to FUSED_RMAX (query head, row) pairs of one key head and sequence, each with its keys cut
+// into up to ATTN_MAX_SPLITS ranges.  alone: every head and row an item of its own.
+constexpr int FUSED_RMAX = 8;
+constexpr int ATTN_MAX_SPLITS = 16;
+struct AttnCut { int mi, gh, n_hblk, n_rblk, items; };      // rows and heads per item, blocks of each, items
+inline AttnCut attn_cut(int nseq, int m, int hq, int hkv, bool alone) {
+    AttnCut a{};
+    const int group = hq / hkv;
+    if (alone) { a.mi = 1; a.gh = 1; }
+    else if (m >= FUSED_RMAX) { a.mi = FUSED_RMAX; a.gh = 1; }
+    else { a.mi = m; a.gh = std::max(1, std::min(group, FUSED_RMAX / m)); }
+    a.n_hblk = (group + a.gh - 1) / a.gh; a.n_rblk = (m + a.mi - 1) / a.mi;
+    a.items = nseq * hkv * a.n_hblk * a.n_rblk;
+    return a;
+}
+// partials (each FUSED_RMAX rows of head_dim + 2 floats) that there is room for: what fills `grid` workgroups
+inline size_t attn_partials(int grid, int items) { return (size_t)items * std::min(ATTN_MAX_SPLITS, std::max(1, grid / items)); }
 
 }  // namespace hivis

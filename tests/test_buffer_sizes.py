@@ -1,6 +1,7 @@
 """Host arithmetic of the buffers of bf16 models.  The prefill buffers are also the operand buffers of the 11..64-row passes:
 whatever a pass packs has to fit the buffer it is sent to, down to the smallest context that takes such a pass (64 rows of room).
-And the room for K slices covers every row count, so that it grows at most once."""
+And the room for K slices covers every row count, so that it grows at most once.  Work items of the phase programs' attention."""
+import ctypes
 import itertools
 
 import pytest
@@ -40,6 +41,11 @@ extern "C" long wide_over(int cu, int K, int N) {
     }
     return over;
 }
+extern "C" void cut(int nseq, int m, int hq, int hkv, int alone, int* out) {
+    const AttnCut a = attn_cut(nseq, m, hq, hkv, alone);
+    out[0] = a.mi; out[1] = a.gh; out[2] = a.n_hblk; out[3] = a.n_rblk; out[4] = a.items;
+}
+extern "C" long partials(int grid, int items) { return attn_partials(grid, items); }
 """
 
 #           d, q_dim, F
@@ -82,3 +88,15 @@ def test_room_for_every_slice(lib, widths, cu):
             assert lib.slices_over(cu, d, qd, kd, F, rows) <= 0, (kd, rows)
     for K, N in itertools.product({d, 2 * d, qd, F}, {d, 2 * F, 3 * qd, 32000, 152064, 528}):
         assert lib.wide_over(cu, K, N) <= 0, (K, N)
+
+
+def test_attention_items(lib):
+    """Every (sequence, key head, query head, row) in one item of at most eight pairs; room for the partials of a grid of workgroups."""
+    for nseq, m, (hq, hkv), alone in itertools.product([1, 2, 4, 9], [1, 2, 5, 8, 9, 16], [(4, 4), (32, 4), (28, 4), (32, 8), (6, 3)], [0, 1]):
+        out = (ctypes.c_int * 5)()
+        lib.cut(nseq, m, hq, hkv, alone, out)
+        mi, gh, nh, nr, items = out
+        assert mi * gh <= (1 if alone else 8) and (nh - 1) * gh < hq // hkv <= nh * gh and (nr - 1) * mi < m <= nr * mi
+        assert items == nseq * hkv * nh * nr
+        for grid in (64, 256):
+            assert items <= lib.partials(grid, items) <= max(items, grid)
