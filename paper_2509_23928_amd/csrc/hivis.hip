@@ -555,8 +555,8 @@ enum { PROG_VERIFY = 0, PROG_DRAFT = 1, PROG_ROLL = 2, PROG_DRAFT_SAMPLE = 3 };
 template <typename WT>
 bool fused_rows_ok(const hivis_ctx* c, int M) { return M <= (sizeof(WT) == 2 && !c->persistent ? WTraits<bf16w_t>::ROWS : WTraits<WT>::ROWS); }
 
-// alone (fp32 caches only): each head and row an item of its own while there are CUs for them.  The vector ALU works on an item's rows one
-// after the other: verify of 5 rows x 4 heads 10.9 -> 6.2 us.  (The matrix cores of the bf16 models take all rows of an item at once.)
+// alone (fp32 caches only; the rule: attn_alone): each head and row an item of its own, if there are CUs for them.  (The matrix cores of the
+// bf16 models take all rows of an item at once.)
 AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, int ldq, bool alone, int* items_out) {
     const hivis_config& g = c->cfg;
     AttnShape sh{};
@@ -602,10 +602,12 @@ float* layer_phases(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const Layer
     q.gain = L.norm1; q.Y = qkv; q.ldy = nqkv; q.kc = kv.k; q.vc = kv.v; q.maxL = kv.maxL; q.base = base; q.offset = offset; q.rope = c->rope_tab; q.bias = L.bqkv;
     P.push_back(q);
     Phase a{}; a.type = PH_ATTN; a.A = qkv; a.lda = nqkv; a.kc = kv.k; a.vc = kv.v; a.maxL = kv.maxL; a.base = base; a.offset = offset;
-    a.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, nqkv, alone, &a.att_items);
-    a.ws = pool.take(attn_partials(c->fused_grid, a.att_items) * FUSED_RMAX * (g.head_dim + 2));
+    a.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, nqkv, false, &a.att_items);
+    int items = a.att_items;                           // (of the launch with the most, and the most partials)
+    if (alone) { (void)fused_attn_shape(c, nseq, m, offset, kv.maxL, nqkv, true, &items); a.att_alone = items > a.att_items; }
+    a.ws = pool.take(std::max(attn_partials(c->fused_grid, a.att_items), attn_partials(c->fused_grid, items)) * FUSED_RMAX * (g.head_dim + 2));
     if (persistent || elect) {
-        a.cnt = (int*)pool.take((size_t)a.att_items);  // zero from the pool's memset; the merging workgroup re-zeroes it
+        a.cnt = (int*)pool.take((size_t)items);        // zero from the pool's memset; the merging workgroup re-zeroes it
         a.Y = att; a.ldy = qd;
         P.push_back(a);
     } else {
@@ -862,7 +864,7 @@ int get_program(hivis_ctx* c, int kind, int K, hivis_ctx::Program* out) {
     if (it != c->programs.end()) { *out = it->second; return HIVIS_OK; }
     std::vector<Phase> P;
     Pool count;
-    const bool alone = std::is_same<WT, float>::value;
+    const bool alone = std::is_same<WT, float>::value && !c->persistent;
     build_phases<WT>(c, kind, K, count, P, c->persistent, c->attn_elect, c->stream_rows, c->lm_ext, alone);           // sizes only
     Pool pool;
     if (int rc = dev_alloc(c, &pool.base, count.used)) return rc;
@@ -898,7 +900,13 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         ph.next_W = nullptr;                       // nothing is prefetched across a kernel boundary (pulling the next launch's
                                                    // first units into L2 during the epilogue was measured: 3% slower)
         if (ph.type == PH_ATTN || ph.type == PH_ATTN_MERGE) {
-            ph.att.nsplit = std::max(1, std::min(ph.att.nsplit, (max_keys + c->keys_per_split - 1) / c->keys_per_split));
+            ph.att.nsplit = attn_splits(max_keys, ph.att.nsplit, c->keys_per_split);
+            if (ph.att_alone) {
+                int items = 0;
+                AttnShape one = fused_attn_shape(c, pp.nseq, pp.m, ph.offset, ph.maxL, ph.att.ldq, true, &items);
+                one.nsplit = attn_splits(max_keys, one.nsplit, c->keys_per_split);
+                if (attn_alone(pp.nseq, pp.m, g.n_q_heads, g.n_kv_heads, g.head_dim, max_keys, one.nsplit, ph.att.nsplit)) { ph.att = one; ph.att_items = items; }
+            }
             ph.att.flags = c->attn_flags;
         }
         if (ph.type == PH_ATTN || ph.type == PH_ATTN_MERGE || (ph.type == PH_GEMM && ph.epi == FEPI_QKV)) {

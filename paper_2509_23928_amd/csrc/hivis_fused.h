@@ -68,6 +68,7 @@ struct Phase {
     const int32_t* ids; int id_sseq, id_srow;      // PREP: token of row (seq, i) = ids[seq*id_sseq + i*id_srow] (ids may be null: no gather)
     int32_t* tok_out; int o_sseq, o_srow;          // ARGMAX: destination of the greedy token of row (seq, i)
     AttnShape att; int att_items;                  // ATTN / ATTN_MERGE
+    bool att_alone;                                // (host) there is room for items of one row each: the launch chooses by the cache's length
     const float* rope;                             // QKV epilogue: rotary table of the context, [position][hd/2][2] cos, sin
     const float* bias;                             // QKV epilogue: optional q/k/v projection biases [N] in packed column order
     float* ws;                                     // ATTN: per-workgroup partials of the key splits

@@ -103,6 +103,20 @@ inline AttnCut attn_cut(int nseq, int m, int hq, int hkv, bool alone) {
     a.items = nseq * hkv * a.n_hblk * a.n_rblk;
     return a;
 }
+// key splits of a launch over `keys` cached rows, of at most `most`
+inline int attn_splits(int keys, int most, int keys_per_split) { return std::max(1, std::min(most, (keys + keys_per_split - 1) / keys_per_split)); }
+// Whether the rows of an fp32 pass over `keys` cached rows of each of nseq sequences are items of their own.  The vector ALU works on an
+// item's rows one after the other, so that sharing an item costs a row about what 230 keys of 64 values cost.  Alone, rows leave fewer CUs
+// to split the keys over, and the items of a key head, dealt to all eight XCDs, fetch its cached rows up to eight times (a megabyte costs
+// what 8 keys do).  Measured over 14 head counts (4/4 to 64/4, 64 and 128 wide), 1..8 sequences, 1..16 rows and 100..3000 keys; us per verify pass
+// of four layers and 5 rows, shared -> alone: 4/4 heads of 64 over 100 keys 171 -> 150; 8/8 over 3000 keys 197 -> 184; 32/32 of 128 over 2000 keys
+// 301 -> 415, which the rule leaves shared.  Of 1296 such points it takes none that loses more than 0.3 us a layer, and 97 % of what the others gain.
+inline bool attn_alone(int nseq, int m, int hq, int hkv, int hd, int keys, int splits_alone, int splits_shared) {
+    const AttnCut s = attn_cut(nseq, m, hq, hkv, false);
+    const double alone = (keys + splits_alone - 1) / splits_alone, shared = (keys + splits_shared - 1) / splits_shared;
+    const double mb = 8.0e-6 * nseq * hkv * keys * hd * std::min(8, m * (hq / hkv));
+    return (alone - shared) * hd / 64 + 8 * mb <= 230 * s.mi * s.gh;
+}
 // partials (each FUSED_RMAX rows of head_dim + 2 floats) that there is room for: what fills `grid` workgroups
 inline size_t attn_partials(int grid, int items) { return (size_t)items * std::min(ATTN_MAX_SPLITS, std::max(1, grid / items)); }
 

@@ -45,6 +45,13 @@ extern "C" void cut(int nseq, int m, int hq, int hkv, int alone, int* out) {
     const AttnCut a = attn_cut(nseq, m, hq, hkv, alone);
     out[0] = a.mi; out[1] = a.gh; out[2] = a.n_hblk; out[3] = a.n_rblk; out[4] = a.items;
 }
+// whether a pass of an fp32 model on 256 CUs takes items of one row
+extern "C" int alone(int nseq, int m, int hq, int hkv, int hd, int keys) {
+    const AttnCut s = attn_cut(nseq, m, hq, hkv, false), a = attn_cut(nseq, m, hq, hkv, true);
+    if (a.items > 256) return 0;
+    auto splits = [&](int items) { return attn_splits(keys, std::min(ATTN_MAX_SPLITS, std::max(1, 256 / ((items + 7) / 8 * 8))), 192); };
+    return attn_alone(nseq, m, hq, hkv, hd, keys, splits(a.items), splits(s.items));
+}
 extern "C" long partials(int grid, int items) { return attn_partials(grid, items); }
 """
 
@@ -100,3 +107,13 @@ def test_attention_items(lib):
         assert items == nseq * hkv * nh * nr
         for grid in (64, 256):
             assert items <= lib.partials(grid, items) <= max(items, grid)
+
+
+@pytest.mark.parametrize("alone,shape", [
+    (1, (1, 5, 4, 4, 64, 100)), (1, (1, 5, 8, 8, 64, 3000)), (1, (1, 8, 32, 8, 128, 450)), (1, (1, 1, 32, 4, 128, 3000)), (1, (1, 16, 16, 16, 64, 700)),
+    (1, (1, 5, 32, 8, 64, 700)), (1, (1, 8, 28, 4, 128, 700)),
+    (0, (1, 5, 32, 32, 128, 2000)), (0, (1, 5, 28, 4, 128, 2000)), (0, (4, 4, 16, 16, 64, 700)), (0, (2, 1, 32, 8, 128, 3000)), (0, (1, 5, 32, 32, 64, 2000)),
+], ids=str)
+def test_rows_alone_where_they_were_faster(lib, alone, shape):
+    """sequences, rows, query and key heads, head_dim, cached rows: measured faster as items of one row, or slower"""
+    assert lib.alone(*shape) == alone

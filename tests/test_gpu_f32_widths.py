@@ -54,3 +54,34 @@ def test_cycles(batch, K, kw):
             o.accept(drafts[b], g, t, force=(m, emitted))
             assert rel(hidden[b], o.f_next) <= REL
     hv.close()
+
+
+@pytest.mark.parametrize("kw,lengths", [
+    (dict(n_q_heads=32, n_kv_heads=8, head_dim=128), [9, 2000]),             # verify and re-feed: items of one row each, then shared
+    (dict(n_q_heads=32, n_kv_heads=8, head_dim=128, batch=2), [12, 1700, 30]),      # draft steps as well
+], ids=["verify", "draft"])
+def test_items_of_short_and_long_caches(kw, lengths):
+    """One context (and its phase programs) on both sides of the rule that cuts the attention into items."""
+    from paper_2509_23928_amd import Hivis
+    K = 3
+    cfg = synth.HivisConfig(**{**dict(name="f32-items", n_layers=1, d=64, ffn=64, vocab=528, dtype="f32", n_vis=0, n_text=max(lengths), K=K, batch=1,
+                                      gen_tokens=0, gen_cycles=2), **kw})
+    w = synth.make_weights(cfg, seed=4)
+    vis, ids = synth.make_prompt(cfg, seed=4)
+    hv = Hivis(cfg, w)
+    for n in lengths * 2:
+        first = hv.prefill(vis, np.ascontiguousarray(ids[:, :n]))
+        hv.draft(K)
+        hv.verify()
+        drafts, dlog, vlog = hv.get_tokens()[0], hv.get_logits(1), hv.get_logits(0)
+        hv.accept()
+        hidden = hv.get_hidden(1)
+        for b in range(cfg.batch):
+            o = HivisOracle(cfg, w)
+            assert o.prefill(vis[b], ids[b, :n])[0] == int(first[b])
+            assert rel(dlog[:, b], o.draft(K, follow=drafts[b])[1]) <= REL
+            g, ref, t = o.verify(drafts[b])
+            assert rel(vlog[b], ref) <= REL
+            o.accept(drafts[b], g, t)
+            assert rel(hidden[b], o.f_next) <= REL
+    hv.close()
