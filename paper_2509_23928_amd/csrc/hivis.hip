@@ -977,7 +977,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                     if (group <= 2) HIVIS_STREAM2(FEPI_SILU, 2); else if (group <= 3) HIVIS_STREAM2(FEPI_SILU, 3); else if (group <= 4) HIVIS_STREAM(FEPI_SILU, 4);
                     else if (group <= 6) HIVIS_STREAM(FEPI_SILU, 6); else HIVIS_STREAM(FEPI_SILU, 8);
                     break;
-                case FEPI_LOGITS: if (group <= 2) HIVIS_STREAM(FEPI_LOGITS, 2); else if (group <= 4) HIVIS_STREAM(FEPI_LOGITS, 4); else if (group <= 6) HIVIS_STREAM2(FEPI_LOGITS, 6);
+                case FEPI_LOGITS: if (group <= 2) HIVIS_STREAM2(FEPI_LOGITS, 2); else if (group <= 4) HIVIS_STREAM2(FEPI_LOGITS, 4); else if (group <= 6) HIVIS_STREAM2(FEPI_LOGITS, 6);
                     else {
                         if constexpr (std::is_same<WT, bf16_t>::value) { if (group > 8) { HIVIS_STREAM(FEPI_LOGITS, 9); break; } }
                         HIVIS_STREAM2(FEPI_LOGITS, 8);

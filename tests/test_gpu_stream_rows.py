@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
     (1, 2, dict(d=2048, ffn=2080)), (2, 5, dict(d=2048, ffn=2080)), (1, 2, dict(d=2080, ffn=2048)), (2, 5, dict(d=2080, ffn=2048)),
     (1, 3, dict(ffn=5632, vocab=36880)), (2, 5, dict(ffn=5632, vocab=36880)),              # 3 tiles of gate|up, two groups of logits
     (1, 3, dict(ffn=8192, vocab=24592)), (3, 3, dict(ffn=14336, vocab=16400)),              # 4 and 7 tiles; 7 and 5 of logits
+    (1, 3, dict(vocab=8208)), (2, 5, dict(vocab=8208)),                                     # 3 tiles of logits
     (1, 4, dict(ffn=18432, n_q_heads=48, n_kv_heads=8)), (2, 4, dict(ffn=10304, n_q_heads=96, n_kv_heads=48)),      # 9 and 6 tiles; 2 and 3 of q|k|v
     (1, 3, dict(d=4128, ffn=64, n_layers=1)), (2, 4, dict(d=4128, ffn=64, n_layers=1)), (1, 2, dict(d=8224, ffn=64, n_layers=1)),
 ], ids=lambda x: "-".join(f"{k}{v}" for k, v in x.items()) if isinstance(x, dict) else str(x))
