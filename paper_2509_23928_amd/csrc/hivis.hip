@@ -669,6 +669,13 @@ void layer_stream(hivis_ctx* c, std::vector<Phase>& P, Pool& pool, const LayerDe
     P.push_back(dn);
 }
 
+// bytes of the weights that a draft step reads: the drafter's layer, the LM head, the fusion FC's w1
+double draft_step_bytes(const hivis_ctx* c) {
+    const hivis_config& g = c->cfg;
+    const double qd = g.n_q_heads * g.head_dim, kd = g.n_kv_heads * g.head_dim;
+    return c->esize * (double)g.d * (2 * qd + 2 * kd + 3.0 * g.ffn + g.vocab + g.d);
+}
+
 // greedy candidates per row of an LM-head phase: its workgroups (a single-launch program always runs the whole grid)
 int lm_candidates(const hivis_ctx* c, int N, bool persistent) { return persistent ? c->fused_grid : std::min(c->fused_grid, N / 16); }
 
@@ -895,6 +902,11 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
     // weights, read with the hint, leave them there (650 keys x 8 layers, 170 MB: 11.6 us, 12.8 with the hint; the drafter's layer 7.2 and 8.4).
     const bool once = !std::is_same<WT, float>::value && kind == PROG_VERIFY &&
                       (double)g.n_layers * g.batch * g.n_kv_heads * max_keys * g.head_dim * 8.0 > 256.0e6;
+    // Weights of a draft round (or of a tree's levels), read once per step: without the hint where that cache holds all of a step's.  A round of
+    // 12 steps, one sequence, with the hint -> without: 1024 wide, 32000 columns (97 MB) 569 -> 530 us, 1536 wide (160 MB) 665 -> 622, 2048 wide
+    // (229 MB) 755 -> 713; but 2560 wide (336 MB) 974 -> 1040, 2048 wide with 50272 columns (348 MB) 963 -> 1044.  (With plain loads and
+    // staged rows 547, 655, 738, 1079 and 1052.)  Forms for rows of up to 2048 values, where that is: the others have the hint.
+    const bool keep = !std::is_same<WT, float>::value && (kind == PROG_DRAFT || kind == PROG_DRAFT_SAMPLE) && K > 1 && draft_step_bytes(c) <= 256.0e6;
     for (int p = 0; p < n; ++p) {
         Phase ph = phases[p];
         ph.next_W = nullptr;                       // nothing is prefetched across a kernel boundary (pulling the next launch's
@@ -934,6 +946,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
 #define HIVIS_LAUNCH(TY, EP) do { typedef typename std::conditional<TY == PH_GEMM, WT, RT>::type KT_; \
                               if (single) hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, true>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); \
                               else hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, false>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); } while (0)
+#define HIVIS_LAUNCH_KEEP(EP) hipExtLaunchKernelGGL((phase_kernel<bf16_t, PH_GEMM, EP, false, true>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl)
         // one tile per workgroup at most.  (q|k|v, gate|up and LM head: fp32 models only, whose matrices are that small; 256 wide: 7.7 -> 7.0, 7.2 -> 6.0 and 9.0 -> 7.8 us)
         const bool single = ph.type == PH_GEMM && ph.N / 16 <= grid &&
                             (std::is_same<WT, float>::value || (ph.epi != FEPI_LOGITS && ph.epi != FEPI_SILU && ph.epi != FEPI_QKV));
@@ -959,18 +972,21 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                     // (half the fragments through a CU's address pipeline; the tile's weights come from the L2 once).  2048 columns, 12 rows:
                     // down (K = 5632) 14.1 -> 10.8 us, O 6.6 -> 6.0.
                     if ((ph.epi == FEPI_ADD_TO || ph.epi == FEPI_ADDVEC) && 2 * grid <= c->fused_grid && grid == ph.N / 16) {
-#define HIVIS_HALVES(EP, SH_) hipExtLaunchKernelGGL((stream_kernel<bf16_t, EP, 1, SH_>), dim3(2 * grid), dim3(FUSED_NT), stream_lds_floats(1, WTraits<bf16_t>::RPL) * sizeof(float), c->stream, kev0, kev1, 0, ph, ppl)
+#define HIVIS_HALVES_(EP, SH_, KP_) hipExtLaunchKernelGGL((stream_kernel<bf16_t, EP, 1, SH_, KP_>), dim3(2 * grid), dim3(FUSED_NT), stream_lds_floats(1, WTraits<bf16_t>::RPL) * sizeof(float), c->stream, kev0, kev1, 0, ph, ppl)
+#define HIVIS_HALVES(EP, SH_) do { if (keep) HIVIS_HALVES_(EP, SH_, true); else HIVIS_HALVES_(EP, SH_, false); } while (0)
                         if (ph.epi == FEPI_ADD_TO) { if (sh) HIVIS_HALVES(FEPI_ADD_TO, true); else HIVIS_HALVES(FEPI_ADD_TO, false); }
                         else { if (sh) HIVIS_HALVES(FEPI_ADDVEC, true); else HIVIS_HALVES(FEPI_ADDVEC, false); }
 #undef HIVIS_HALVES
+#undef HIVIS_HALVES_
                         continue;
                     }
                 }
-#define HIVIS_STREAM_(EP, G_, SH_) hipExtLaunchKernelGGL((stream_kernel<WT, EP, G_, SH_>), dim3(grid), dim3(FUSED_NT), stream_lds_floats(G_, WTraits<WT>::RPL) * sizeof(float), c->stream, kev0, kev1, 0, ph, ppl)
-#define HIVIS_STREAM(EP, G_) HIVIS_STREAM_(EP, G_, false)
-#define HIVIS_STREAM2(EP, G_) do { if (sh) HIVIS_STREAM_(EP, G_, true); else HIVIS_STREAM_(EP, G_, false); } while (0)
+#define HIVIS_STREAM_(EP, G_, SH_, KP_) hipExtLaunchKernelGGL((stream_kernel<WT, EP, G_, SH_, KP_>), dim3(grid), dim3(FUSED_NT), stream_lds_floats(G_, WTraits<WT>::RPL) * sizeof(float), c->stream, kev0, kev1, 0, ph, ppl)
+#define HIVIS_STREAM(EP, G_) HIVIS_STREAM_(EP, G_, false, false)
+#define HIVIS_STREAM2(EP, G_) do { if (sh && keep) HIVIS_STREAM_(EP, G_, true, true); else if (sh) HIVIS_STREAM_(EP, G_, true, false); else HIVIS_STREAM_(EP, G_, false, false); } while (0)
+#define HIVIS_STREAM1(EP) do { if (!sh && keep) HIVIS_STREAM_(EP, 1, false, true); else HIVIS_STREAM2(EP, 1); } while (0)      // (rows of the MLP's inner width)
                 switch (ph.epi) {
-                case FEPI_ADD_TO: if (group <= 1) HIVIS_STREAM2(FEPI_ADD_TO, 1); else HIVIS_STREAM(FEPI_ADD_TO, 2); break;
+                case FEPI_ADD_TO: if (group <= 1) HIVIS_STREAM1(FEPI_ADD_TO); else HIVIS_STREAM(FEPI_ADD_TO, 2); break;
                 case FEPI_ADDVEC: if (group <= 1) HIVIS_STREAM2(FEPI_ADDVEC, 1); else HIVIS_STREAM(FEPI_ADDVEC, 2); break;
                 case FEPI_QKV: if (group <= 1) HIVIS_STREAM2(FEPI_QKV, 1); else if (group <= 2) HIVIS_STREAM2(FEPI_QKV, 2); else if (group <= 3) HIVIS_STREAM(FEPI_QKV, 3); else HIVIS_STREAM(FEPI_QKV, 4); break;
                 case FEPI_SILU:
@@ -985,6 +1001,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                     break;
                 default: return fail(c, HIVIS_EINVAL, "phase %d: no kernel for epilogue %d", p, ph.epi);
                 }
+#undef HIVIS_STREAM1
 #undef HIVIS_STREAM2
 #undef HIVIS_STREAM
 #undef HIVIS_STREAM_
@@ -1012,8 +1029,8 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                     }
                 }
                 if constexpr (!std::is_same<WT, bf16w_t>::value) {      // (table rows are added for at most four sequences)
-                    if (ph.add_rows && pp.M <= 2) { HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB); break; }
-                    if (ph.add_rows) { HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB4); break; }
+                    if (ph.add_rows && pp.M <= 2) { if (keep) HIVIS_LAUNCH_KEEP(FEPI_QKV_TAB); else HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB); break; }
+                    if (ph.add_rows) { if (keep) HIVIS_LAUNCH_KEEP(FEPI_QKV_TAB4); else HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB4); break; }
                 }
                 HIVIS_LAUNCH(PH_GEMM, FEPI_QKV);
                 break;
@@ -1032,6 +1049,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         case PH_ARGMAX: HIVIS_LAUNCH(PH_ARGMAX, 0); break;
         default: return fail(c, HIVIS_EINVAL, "phase %d: unknown type %d", p, ph.type);
         }
+#undef HIVIS_LAUNCH_KEEP
 #undef HIVIS_LAUNCH
     }
     HIP_TRY(c, hipGetLastError());
@@ -1196,6 +1214,8 @@ int fused_setup(hivis_ctx* c) {
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
     }
     if constexpr (std::is_same<WT, bf16_t>::value) {
+        const void* kk[] = {(const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB, false, true>, (const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB4, false, true>};
+        for (const void* k : kk) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
         typedef FusedCfg<bf16w_t> CW;
         c->fused_lds_w = fused_gemm_lds_floats(CW::NW, CW::G, WTraits<bf16w_t>::RPL, CW::KBW, FUSED_CHUNK<bf16w_t>) * sizeof(float);
         const void* ks[] = {(const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_ADD_TO, false>, (const void*)phase_kernel<bf16w_t, PH_GEMM, FEPI_ADD_TO, true>,
@@ -1206,7 +1226,8 @@ int fused_setup(hivis_ctx* c) {
     }
     if constexpr (std::is_same<WT, bf16_t>::value) {
         // (the only stream kernels beyond 64 KB of LDS)
-        const void* ks[] = {(const void*)stream_kernel<bf16w_t, FEPI_SILU, 8, false>, (const void*)stream_kernel<bf16w_t, FEPI_LOGITS, 8, false>, (const void*)stream_kernel<bf16w_t, FEPI_LOGITS, 8, true>};
+        const void* ks[] = {(const void*)stream_kernel<bf16w_t, FEPI_SILU, 8, false>, (const void*)stream_kernel<bf16w_t, FEPI_LOGITS, 8, false>, (const void*)stream_kernel<bf16w_t, FEPI_LOGITS, 8, true>,
+                            (const void*)stream_kernel<bf16w_t, FEPI_LOGITS, 8, true, true>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(stream_lds_floats(8, WTraits<bf16w_t>::RPL) * sizeof(float))));
     }
     { const char* pe = getenv("HIVIS_PERSISTENT"); c->persistent = pe && pe[0] == '1'; }

@@ -180,9 +180,10 @@ template <int NW, int KBW> __device__ __forceinline__ int unit_nkb(int kblks, in
 // waited a memory round trip before it requested the other fourteen.)  bf16: with the non-temporal hint, because a weight
 // is read by one workgroup, once per pass: a plain stream of 180 MB takes 27.2 us with it and 30.4 without, of 34 MB 6.4 and 7.0.
 // Both together, C2 verify pass: gate|up 35.2 -> 32.0 us, q|k|v 22.6 -> 20.4, LM head 54.5 -> 49.3; with the hint alone 32.2, 21.5, 50.4.
+// KEEP: without the hint, for weights that the memory-side cache holds from one pass to the next (rule: launch_phases).
 // fp32 models (a few MB, re-read from the L2, a block or two per wavefront) keep plain loads, a branch each: with the hint 2 % slower, with
 // buffer loads 1 %.
-template <typename WT, int U>
+template <typename WT, bool KEEP, int U>
 __device__ __forceinline__ void issue_unit(uint4 (&wb)[U], const uint4* __restrict__ W, int kblks, int tile, int kb0,
                                            int nkb, int lane) {
     const uint4* p = W + ((size_t)tile * kblks + kb0) * 64;
@@ -194,7 +195,7 @@ __device__ __forceinline__ void issue_unit(uint4 (&wb)[U], const uint4* __restri
         typedef unsigned u4_t __attribute__((ext_vector_type(4)));
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, nkb * 1024, 0x00020000);
 #pragma unroll
-        for (int j = 0; j < U; ++j) { const u4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + j * 1024, 0, 2); wb[j] = __builtin_bit_cast(uint4, v); }      // 2: non-temporal
+        for (int j = 0; j < U; ++j) { const u4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + j * 1024, 0, KEEP ? 0 : 2); wb[j] = __builtin_bit_cast(uint4, v); }      // 2: non-temporal
     }
 }
 
@@ -293,7 +294,7 @@ template <typename WT> __device__ __forceinline__ int rope_offset(const Phase& p
 //  * Weights: one unit (KBW KiB per wavefront) ahead, and the chain of prefetches does not stop at the end of
 //    a tile group, a pass or the phase: the last unit of a phase loads the first unit of the NEXT GEMM phase
 //    (`head`), so those loads are in flight while the workgroup waits at the grid barrier.
-template <typename WT, int EPI, bool SINGLE>
+template <typename WT, int EPI, bool SINGLE, bool KEEP>
 __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp, float* __restrict__ lds, uint4 (&head)[FusedCfg<WT>::KBW],
                            bool& head_valid, uint4 (&wb1)[FusedCfg<WT>::KBW], bool& wb1_valid, int pidx) {
 #define HIVIS_MARK(k) if (pp.prof2 && blockIdx.x == 0 && threadIdx.x == 0) pp.prof2[pidx * 8 + (k)] = wall_clock64();
@@ -366,13 +367,13 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
     // of the next pass.
 #define HIVIS_FIRST_UNITS(W_, kblks_, tile_, ntl_, npass_)                                                         \
     {                                                                                                              \
-        issue_unit<WT>(head, W_, kblks_, tile_, unit_kb0<NW, KBW>(kblks_, 0, wave), unit_nkb<NW, KBW>(kblks_, 0, wave), lane); \
+        issue_unit<WT, KEEP>(head, W_, kblks_, tile_, unit_kb0<NW, KBW>(kblks_, 0, wave), unit_nkb<NW, KBW>(kblks_, 0, wave), lane); \
         head_valid = true;                                                                                         \
         /* one call site for the second unit (two alternative ones make the compiler drain the first unit's loads) */ \
         const bool next_tile_ = (ntl_) >= 2;                                                                       \
         wb1_valid = next_tile_ || (SINGLE && (npass_) >= 2);                                                       \
         const int p1_ = next_tile_ ? 0 : 1;                                                                        \
-        if (wb1_valid) issue_unit<WT>(wb1, W_, kblks_, (tile_) + (next_tile_ ? 1 : 0), unit_kb0<NW, KBW>(kblks_, p1_, wave), unit_nkb<NW, KBW>(kblks_, p1_, wave), lane); \
+        if (wb1_valid) issue_unit<WT, KEEP>(wb1, W_, kblks_, (tile_) + (next_tile_ ? 1 : 0), unit_kb0<NW, KBW>(kblks_, p1_, wave), unit_nkb<NW, KBW>(kblks_, p1_, wave), lane); \
     }
 
     if (ntl <= 0) {
@@ -508,7 +509,7 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
             //      matters is how much is in flight per wait: two units here.  With one unit requested per pass every
             //      pass paid a memory round trip for 8 KiB per wavefront and the kernel was latency-bound.
             if (npass > 1) HIVIS_LOAD_RAW_TO(1, araw2, graw2, braw2)
-            if (!wb1_first && npass > 1) issue_unit<WT>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, 1, wave), unit_nkb<NW, KBW>(kblks, 1, wave), lane);
+            if (!wb1_first && npass > 1) issue_unit<WT, KEEP>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, 1, wave), unit_nkb<NW, KBW>(kblks, 1, wave), lane);
             for (int pass = 0; pass < npass; pass += 2) {
                 HIVIS_STAGE_FROM(pass, araw, graw, braw, true, )
                 if (pass == 0) { HIVIS_MARK(1) }
@@ -519,11 +520,11 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
                 }
                 if (pass + 2 < npass) {
                     HIVIS_LOAD_RAW_TO(pass + 2, araw, graw, braw)
-                    issue_unit<WT>(head, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 2, wave), unit_nkb<NW, KBW>(kblks, pass + 2, wave), lane);
+                    issue_unit<WT, KEEP>(head, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 2, wave), unit_nkb<NW, KBW>(kblks, pass + 2, wave), lane);
                 }
                 if (pass + 3 < npass) {
                     HIVIS_LOAD_RAW_TO(pass + 3, araw2, graw2, braw2)
-                    issue_unit<WT>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 3, wave), unit_nkb<NW, KBW>(kblks, pass + 3, wave), lane);
+                    issue_unit<WT, KEEP>(wb1, W, kblks, tg, unit_kb0<NW, KBW>(kblks, pass + 3, wave), unit_nkb<NW, KBW>(kblks, pass + 3, wave), lane);
                 }
             }
         } else {
@@ -545,17 +546,17 @@ __device__ __forceinline__ void gemm_phase(const Phase& ph, const PassParams& pp
 #pragma unroll
                 for (int g0 = 0; g0 < G; g0 += 2) {
                     if (g0 < ng) {
-                        if (g0 + 1 < ng && !(g0 == 0 && have_wb1)) issue_unit<WT>(wb1, W, kblks, tg + g0 + 1, kb0, nkb, lane);
+                        if (g0 + 1 < ng && !(g0 == 0 && have_wb1)) issue_unit<WT, KEEP>(wb1, W, kblks, tg + g0 + 1, kb0, nkb, lane);
                         mfma_unit(acc[g0], af, head);
-                        if (g0 + 2 < ng) issue_unit<WT>(head, W, kblks, tg + g0 + 2, kb0, nkb, lane);
-                        else if (nvalid) issue_unit<WT>(head, W, kblks, ntile, nkb0, nnkb, lane);
+                        if (g0 + 2 < ng) issue_unit<WT, KEEP>(head, W, kblks, tg + g0 + 2, kb0, nkb, lane);
+                        else if (nvalid) issue_unit<WT, KEEP>(head, W, kblks, ntile, nkb0, nnkb, lane);
                         if (g0 + 1 < ng) {
                             mfma_unit(acc[g0 + 1], af, wb1);
                         }
                     }
                 }
                 // second unit of the next (tile group, pass): its registers are free now
-                if (nvalid && ntiles2 >= 2) { issue_unit<WT>(wb1, W, kblks, ntile + 1, nkb0, nnkb, lane); wb1_valid = true; }
+                if (nvalid && ntiles2 >= 2) { issue_unit<WT, KEEP>(wb1, W, kblks, ntile + 1, nkb0, nnkb, lane); wb1_valid = true; }
                 if (first && pass == 0) { HIVIS_MARK(2) }
             }
         }
@@ -1521,14 +1522,14 @@ __device__ __forceinline__ void attn_wg_merge(const float* __restrict__ ws, cons
 }
 
 // One phase, executed by the calling grid (every workgroup calls this with the same arguments).
-template <typename WT, int TYPE, int EPI, bool SINGLE>
+template <typename WT, int TYPE, int EPI, bool SINGLE, bool KEEP = false>
 __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp, float* __restrict__ lds, uint4 (&head)[FusedCfg<WT>::KBW],
                                           bool& head_valid, uint4 (&wb1)[FusedCfg<WT>::KBW], bool& wb1_valid, int p) {
     typedef typename KVType<WT>::type KT;
     const int type = (TYPE >= 0) ? TYPE : ph.type;
     switch (type) {
     case PH_GEMM:
-        if constexpr (TYPE < 0 || TYPE == PH_GEMM) gemm_phase<WT, EPI, SINGLE>(ph, pp, lds, head, head_valid, wb1, wb1_valid, p);
+        if constexpr (TYPE < 0 || TYPE == PH_GEMM) gemm_phase<WT, EPI, SINGLE, KEEP>(ph, pp, lds, head, head_valid, wb1, wb1_valid, p);
         break;
     case PH_ATTN: {
         const AttnOut dst = {ph.Y, ph.ldy, ph.F, pp.M};
@@ -1662,7 +1663,7 @@ __device__ __forceinline__ void kernarg_warm() {
     asm volatile("" ::"s"(acc));
 }
 
-template <typename WT, int TYPE, int EPI, bool SINGLE>
+template <typename WT, int TYPE, int EPI, bool SINGLE, bool KEEP = false>
 __global__ __launch_bounds__(FUSED_NT) void phase_kernel(Phase ph, PassParams pp) {
     extern __shared__ __align__(16) float lds[];
     kernarg_warm<sizeof(Phase) + sizeof(PassParams)>();
@@ -1673,7 +1674,7 @@ __global__ __launch_bounds__(FUSED_NT) void phase_kernel(Phase ph, PassParams pp
         // HW_ID (wave, SIMD, CU, shader array, shader engine) and XCC_ID of the wavefront
         pp.prof3[blockIdx.x * 4 + 2] = (unsigned long long)__builtin_amdgcn_s_getreg((31 << 11) | 4) | ((unsigned long long)__builtin_amdgcn_s_getreg((3 << 11) | 20) << 32);
     }
-    run_phase<WT, TYPE, EPI, SINGLE>(ph, pp, lds, head, head_valid, wb1, wb1_valid, 0);
+    run_phase<WT, TYPE, EPI, SINGLE, KEEP>(ph, pp, lds, head, head_valid, wb1, wb1_valid, 0);
     if (pp.prof3) {
         lds_barrier();
         if (threadIdx.x == 0) pp.prof3[blockIdx.x * 4 + 1] = wall_clock64();

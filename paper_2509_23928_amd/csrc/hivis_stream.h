@@ -95,7 +95,7 @@ struct StreamUnits {
 
 // One GEMM phase: workgroup b owns a contiguous range of 16-column tiles (XCD by XCD, as in gemm_phase) and all of K, in groups of up
 // to G tiles.
-template <typename WT, int EPI, int G, bool SHORT>
+template <typename WT, int EPI, int G, bool SHORT, bool KEEP>
 __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& pp, float* __restrict__ lds) {
 #define HIVIS_MARK(k) if (pp.prof2 && blockIdx.x == 0 && threadIdx.x == 0) pp.prof2[k] = wall_clock64();
     typedef StreamCfg<WT, G, SHORT> CF;
@@ -197,7 +197,7 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
     uint4 w[D][U];
     // (a pass nobody needs, a tile beyond the range: no blocks)
 #define HIVIS_ROWS(buf_, pass_, on_) issue_rows(a[buf_], ph.Af, Mt, lane_off, un.first(pass_, wave), (on_) ? un.count(pass_, wave) : 0)
-#define HIVIS_UNIT(buf_, tile_, pass_) issue_unit<WT>(w[buf_], ph.W, kblks, tile_, un.first(pass_, wave), (tile_) < t_end ? un.count(pass_, wave) : 0, lane)
+#define HIVIS_UNIT(buf_, tile_, pass_) issue_unit<WT, KEEP>(w[buf_], ph.W, kblks, tile_, un.first(pass_, wave), (tile_) < t_end ? un.count(pass_, wave) : 0, lane)
     __builtin_amdgcn_sched_barrier(0);
     HIVIS_MARK(1)
 #pragma unroll
@@ -362,7 +362,8 @@ __device__ __forceinline__ void stream_gemm(const Phase& ph, const PassParams& p
 #undef HIVIS_MARK
 }
 
-template <typename WT, int EPI, int G, bool SHORT>
+// (KEEP: see issue_unit)
+template <typename WT, int EPI, int G, bool SHORT, bool KEEP = false>
 __global__ __launch_bounds__(FUSED_NT) void stream_kernel(Phase ph, PassParams pp) {
     extern __shared__ __align__(16) float lds[];
     kernarg_warm<sizeof(Phase) + sizeof(PassParams)>();
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(FUSED_NT) void stream_kernel(Phase ph, PassParams p
         pp.prof3[blockIdx.x * 4] = wall_clock64();
         pp.prof3[blockIdx.x * 4 + 2] = (unsigned long long)__builtin_amdgcn_s_getreg((31 << 11) | 4) | ((unsigned long long)__builtin_amdgcn_s_getreg((3 << 11) | 20) << 32);
     }
-    stream_gemm<WT, EPI, G, SHORT>(ph, pp, lds);
+    stream_gemm<WT, EPI, G, SHORT, KEEP>(ph, pp, lds);
     if (pp.prof3) {
         lds_barrier();
         if (threadIdx.x == 0) pp.prof3[blockIdx.x * 4 + 1] = wall_clock64();
