@@ -944,7 +944,8 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         typedef typename std::conditional<std::is_same<WT, bf16w_t>::value, bf16_t, WT>::type RT;
         const size_t lds = ph.type == PH_GEMM && std::is_same<WT, bf16w_t>::value ? c->fused_lds_w : c->fused_lds;
 #define HIVIS_LAUNCH(TY, EP) do { typedef typename std::conditional<TY == PH_GEMM, WT, RT>::type KT_; \
-                              if (single) hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, true>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); \
+                              constexpr bool may_ = TY == PH_GEMM && (std::is_same<WT, float>::value || EP == FEPI_ADD_TO || EP == FEPI_ADDVEC);     /* (the rule of `single`) */ \
+                              if (may_ && single) hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, may_>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); \
                               else hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, false>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); } while (0)
 #define HIVIS_LAUNCH_KEEP(EP) hipExtLaunchKernelGGL((phase_kernel<bf16_t, PH_GEMM, EP, false, true>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl)
         // one tile per workgroup at most.  (q|k|v, gate|up and LM head: fp32 models only, whose matrices are that small; 256 wide: 7.7 -> 7.0, 7.2 -> 6.0 and 9.0 -> 7.8 us)
@@ -1040,7 +1041,8 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             }
             break;
         case PH_ATTN:
-            if (once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1) HIVIS_LAUNCH(PH_ATTN, ATTN_ONCE); else HIVIS_LAUNCH(PH_ATTN, 0);
+            if constexpr (!std::is_same<WT, float>::value) { if (once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1) { HIVIS_LAUNCH(PH_ATTN, ATTN_ONCE); break; } }
+            HIVIS_LAUNCH(PH_ATTN, 0);
             break;
         case PH_ATTN_MERGE: HIVIS_LAUNCH(PH_ATTN_MERGE, 0); break;
         case PH_PREP: HIVIS_LAUNCH(PH_PREP, 0); break;
@@ -1202,7 +1204,7 @@ int fused_setup(hivis_ctx* c) {
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_SILU, false>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, false>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADD_TO, true>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADDVEC, true>,
-                            (const void*)phase_kernel<WT, PH_ATTN, 0, false>, (const void*)phase_kernel<WT, PH_ATTN, ATTN_ONCE, false>, (const void*)phase_kernel<WT, PH_ATTN_MERGE, 0, false>,
+                            (const void*)phase_kernel<WT, PH_ATTN, 0, false>, (const void*)phase_kernel<WT, PH_ATTN_MERGE, 0, false>,
                             (const void*)phase_kernel<WT, PH_PREP, 0, false>, (const void*)phase_kernel<WT, PH_NORM_ROWS, 0, false>,
                             (const void*)phase_kernel<WT, PH_ARGMAX, 0, false>, (const void*)phase_kernel<WT, PH_SAMPLE, 0, false>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
@@ -1214,7 +1216,8 @@ int fused_setup(hivis_ctx* c) {
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
     }
     if constexpr (std::is_same<WT, bf16_t>::value) {
-        const void* kk[] = {(const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB, false, true>, (const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB4, false, true>};
+        const void* kk[] = {(const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB, false, true>, (const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB4, false, true>,
+                            (const void*)phase_kernel<bf16_t, PH_ATTN, ATTN_ONCE, false>};
         for (const void* k : kk) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
         typedef FusedCfg<bf16w_t> CW;
         c->fused_lds_w = fused_gemm_lds_floats(CW::NW, CW::G, WTraits<bf16w_t>::RPL, CW::KBW, FUSED_CHUNK<bf16w_t>) * sizeof(float);
