@@ -32,6 +32,13 @@ TRAFFIC_BYTES_PER_LAUNCH = {"C2": 181.7e6}     # profiles/gateup_gemm_C2_hbm_cou
 PAPER_TAU = {"C2": 5.37, "C3": 5.06, "C4": 4.39, "C5": 5.15}    # Table 2, T=0 averages (tree drafting, A800): context only
 
 
+def gateup_kernel(cfg, K):
+    """The kernel that runs the gate|up GEMM of a verify pass of this workload (with the library's default switches)."""
+    if cfg.batch * (K + 1) > 16:
+        return "none timed (passes of more than 16 rows run no phase program)"
+    return "phase_kernel<float, gate|up>" if cfg.dtype == "f32" else "stream_kernel<bf16, gate|up>" if cfg.d <= 8192 else "phase_kernel<bf16, gate|up>"
+
+
 def run_step(hv, cfg, vis, ids, K, temperature=0.0, rng=None, tree=None):
     """prefill + cycles until cfg.gen_tokens tokens (or cfg.gen_cycles cycles).  Returns (tokens, cycles, accepted).
     temperature > 0: the sampling calls, with uniforms drawn on the device (hivis_rng_seed; not the headline configuration).
@@ -273,7 +280,7 @@ def main():
     k_us = k_ms / max(k_launches, 1) * 1e3
     k_gbs = k_bytes / (k_us * 1e-6) / 1e9 if k_launches else 0.0
     out["roofline"] = {"bound": "hbm",
-                       "kernel": "stream_kernel<bf16, gate|up>: fused RMSNorm + [d x 2F] weight stream + SiLU*up of the verify pass "
+                       "kernel": gateup_kernel(cfg, K) + ": fused RMSNorm + [d x 2F] weight stream + SiLU*up of the verify pass "
                                  "(largest share of bytes and of time); HIP start/stop events attached to every 8th launch on the library's stream (hipExtLaunchKernel: the kernel's own begin/end timestamps, no marker packets in the queue)",
                        "achieved": k_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": k_gbs / HBM_PEAK_GBS,
                        "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(args.config), "algorithmic_bytes_per_launch": k_bytes,
