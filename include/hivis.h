@@ -119,8 +119,8 @@ int hivis_prefill(hivis_ctx *ctx, const void *vis_embeds, int32_t v, const int32
 int hivis_draft(hivis_ctx *ctx, int32_t K);
 
 /* hivis_draft for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc): the same K drafter steps with the same kernels, one launch per step operation,
- * but every intermediate buffer of the round (rotary tables, fusion outputs, q/k/v rows, attention partials,
+ * harnesses that forbid hipMalloc): the same K drafter steps, one launch per step operation, with the same kernels
+ * where their buffers fit and with those that need less room where not, but every intermediate buffer of the round (rotary tables, fusion outputs, q/k/v rows, attention partials,
  * MLP activations, greedy candidates) lives in ONE static device array of HIVIS_NOALLOC_SCRATCH_BYTES that is part
  * of the library's code object; the call makes no hipMalloc / hipFree and creates no events (hivis_timing does not
  * cover it).  Inputs and outputs are those of hivis_draft: the context's pending hidden state and text-only cache

@@ -964,7 +964,8 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         if constexpr (!std::is_same<WT, float>::value) {
             if (ph.type == PH_GEMM && ph.Af) {
                 // tiles of a workgroup in groups of at most 8, as even as they come (a kernel of fewer tiles takes more groups).  Nine for the 8-row
-                // LM head: with w1's columns (2256 tiles) 47.6 us in one group of nine, 49.7 in two of five
+                // LM head: 4096 wide, 32000 columns and w1's (2256 tiles) 47.6 us in one group of nine, 49.7 in two of five.  (Measured at that width only;
+                // ten tiles, 5120 wide, are two groups of five.)
                 const int most = (ph.N / 16 + grid - 1) / grid, upto = std::is_same<WT, bf16_t>::value && ph.epi == FEPI_LOGITS && ph.K > STREAM_SHORT_K ? 9 : 8;
                 const int ngroups = (most + upto - 1) / upto, group = (most + ngroups - 1) / ngroups;
                 const bool sh = ph.K <= STREAM_SHORT_K;
@@ -1793,8 +1794,8 @@ PassParams tree_pass(const hivis_ctx* c, int m) {
 // phase: inputs cat [m][2d] = hidden row | embedding and the rows' tokens (tok); layer output to out [m][d]; lm_out (optional): its
 // logits.  The lists of all row counts lie in one pool, tree_pool: the passes of a call follow each other on the stream.  The
 // attention's arrival counters (zero between launches) are its first words for every row count, so no list's rows overwrite them.
-// Up to 8 rows: the 8-row kernels, except for q|k|v, where the 16-row one alone takes tree positions (drafts of the 7B widths with k = 8: 699 ->
-// 682 us, of a 2048-wide model with k = 2: 152 -> 141; there the 16-row kernels were slower than the stand-alone ones, 150).
+// Up to 8 rows: the 8-row kernels (drafts of the 7B widths with k = 8: 699 -> 682 us, of a 2048-wide model with k = 2: 152 -> 141; there the 16-row
+// kernels were slower than the stand-alone ones, 150); in the list without row fragments q|k|v takes the 16-row one, which alone knows tree positions.
 template <typename WT>
 void tree_rows_phases(hivis_ctx* c, int m, const float* cat, const int32_t* tok, int rho_idx, int offset, TreeRows tr, float* out, float* lm_out,
                       Pool& pool, std::vector<Phase>& P) {
@@ -2172,7 +2173,7 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
     if ((rc = dev_alloc(c, &c->u_acc, (size_t)B * g.k_max))) return rc;
     if ((rc = dev_alloc(c, &c->u_res, (size_t)B))) return rc;
     if ((rc = dev_alloc(c, &c->u_tree, (size_t)TREE_MAX_DEPTH + 1))) return rc;
-    // accepted counts and emitted tokens share one block, so one device-to-host copy into pinned memory returns both
+    // accepted counts and emitted tokens share one block: select_row_kernel stores it to the pinned mirror as it is
     if ((rc = dev_alloc(c, &c->nacc, (size_t)B + (size_t)B * (g.k_max + 1)))) return rc;
     c->out_tok = c->nacc + B;
     HIP_TRY(c, hipHostMalloc((void**)&c->h_result, ((size_t)B + (size_t)B * (g.k_max + 1) + 2) * sizeof(int32_t), hipHostMallocDefault));

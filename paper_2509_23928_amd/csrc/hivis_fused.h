@@ -78,8 +78,8 @@ struct Phase {
     const uint4* next_W; int next_K, next_N;       // GEMM: weights of the next GEMM phase of the program (prefetch), or null
     uint4* frag;                                   // ATTN with one key split, optional: the rows go out as A fragments of the next GEMM (K = ldy) instead of to Y
     // phases on row fragments (stream_kernel, see hivis_stream.h): Af the activation rows; ssq their sums of squares in nssq parts per
-    // row (nssq 0: no norm); F, fgain, ssq_out: the results as row fragments, times a gain (optional), and the sums of squares per
-    // 16 columns.  ATTN: F instead of Y.
+    // row (q|k|v and gate|up, whose epilogues apply 1/rms: at least one part; the others read none); F, fgain, ssq_out: the results as row
+    // fragments, times a gain (optional), and the sums of squares per 16 columns.  ATTN: F instead of Y.
     const uint4* Af; const float* ssq; int nssq;
     uint4* F; const void* fgain; float* ssq_out;
 };
