@@ -726,7 +726,11 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
             lm.Y = c->logits_d + (size_t)(i - 1) * B * V; lm.ldy = V; lm.pm = pool.take((size_t)B * G); lm.pi = (int*)pool.take((size_t)B * G);
             lm.tok_out = c->drafts + (i - 1); lm.o_sseq = g.k_max; lm.o_srow = 0;
             // greedy token of step i: reduced by the phase that follows (as below), by the LM head's last workgroup, or by a phase of its own
-            const bool later = kind == PROG_DRAFT && i < K, ext = later && lm_ext && B <= 4;
+            // The fusion FC on the LM-head launch, and a staged q|k|v that adds the table rows, for one or two sequences; for more, an FC phase and
+            // q|k|v on row fragments.  Rounds of 7 steps, FC phase -> on the LM head, one to four sequences: 2560 wide 594 -> 553, 597 -> 572, 602 ->
+            // 592, 605 -> 611 us; 4096 wide 889 -> 856, 891 -> 874, 897 -> 909, 905 -> 932; 5120 wide 1225 -> 1211, 1233 -> 1229, 1240 -> 1260, 1247 -> 1287;
+            // 2048 wide 440 -> 414, 444 -> 454, 447 -> 457, 449 -> 473.
+            const bool later = kind == PROG_DRAFT && i < K, ext = later && lm_ext && B <= 2;
             const bool in_lm = !later && lm_elect && kind == PROG_DRAFT;
             float* u_part = ext ? pool.take((size_t)B * d) : nullptr;
             if (ext) { lm.N = V + d; lm.Y2 = u_part; lm.ldy2 = d; lm.vec = c->rho; lm.vec_idx = std::min(i, g.n_resid - 1); }
@@ -1032,7 +1036,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                 }
                 if constexpr (!std::is_same<WT, bf16w_t>::value) {      // (table rows are added for at most four sequences)
                     if (ph.add_rows && pp.M <= 2) { if (keep) HIVIS_LAUNCH_KEEP(FEPI_QKV_TAB); else HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB); break; }
-                    if (ph.add_rows) { if (keep) HIVIS_LAUNCH_KEEP(FEPI_QKV_TAB4); else HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB4); break; }
+                    if (ph.add_rows) { HIVIS_LAUNCH(PH_GEMM, FEPI_QKV_TAB4); break; }
                 }
                 HIVIS_LAUNCH(PH_GEMM, FEPI_QKV);
                 break;
@@ -1217,8 +1221,7 @@ int fused_setup(hivis_ctx* c) {
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
     }
     if constexpr (std::is_same<WT, bf16_t>::value) {
-        const void* kk[] = {(const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB, false, true>, (const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB4, false, true>,
-                            (const void*)phase_kernel<bf16_t, PH_ATTN, ATTN_ONCE, false>};
+        const void* kk[] = {(const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB, false, true>, (const void*)phase_kernel<bf16_t, PH_ATTN, ATTN_ONCE, false>};
         for (const void* k : kk) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
         typedef FusedCfg<bf16w_t> CW;
         c->fused_lds_w = fused_gemm_lds_floats(CW::NW, CW::G, WTraits<bf16w_t>::RPL, CW::KBW, FUSED_CHUNK<bf16w_t>) * sizeof(float);
