@@ -803,7 +803,9 @@ void build_phases(hivis_ctx* c, int kind, int K, Pool& pool, std::vector<Phase>&
             const bool in_fc = fold && kind == PROG_DRAFT && i < K;
             // ... and with the extended LM head there is no FC phase: this LM-head launch also computes f' w1 + rho for the
             // next step (d extra columns), and the next step's QKV phase reduces the token and adds the table row of it
-            const bool ext = in_fc && lm_ext && B <= 4;       // (the QKV variants that add the table rows stage two or four rows)
+            // (the QKV variants that add the table rows stage two or four rows; fp32, rounds of 7 steps of one and four sequences: 256 wide 270 -> 232,
+            // 295 -> 265 us, 2048 wide 847 -> 809, 903 -> 882)
+            const bool ext = in_fc && lm_ext && B <= 4;
             float* u_part = ext ? pool.take((size_t)B * d) : nullptr;
             if (ext) { lm.N = V + d; lm.Y2 = u_part; lm.ldy2 = d; lm.vec = c->rho; lm.vec_idx = std::min(i, g.n_resid - 1); }
             const bool in_lm = !in_fc && lm_elect && kind == PROG_DRAFT;
@@ -952,7 +954,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
                               if (may_ && single) hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, may_>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); \
                               else hipExtLaunchKernelGGL((phase_kernel<KT_, TY, EP, false>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl); } while (0)
 #define HIVIS_LAUNCH_KEEP(EP) hipExtLaunchKernelGGL((phase_kernel<bf16_t, PH_GEMM, EP, false, true>), dim3(grid), dim3(FUSED_NT), lds, c->stream, kev0, kev1, 0, ph, ppl)
-        // one tile per workgroup at most.  (q|k|v, gate|up and LM head: fp32 models only, whose matrices are that small; 256 wide: 7.7 -> 7.0, 7.2 -> 6.0 and 9.0 -> 7.8 us)
+        // one tile per workgroup at most.  (q|k|v, gate|up and LM head: fp32 models only, whose matrices are that small; 256 wide: 7.7 -> 7.0, 7.2 -> 6.0 and 9.0 -> 7.8 us; q|k|v 1024 wide 8.7 -> 7.4, 2048 wide 11.0 -> 10.7)
         const bool single = ph.type == PH_GEMM && ph.N / 16 <= grid &&
                             (std::is_same<WT, float>::value || (ph.epi != FEPI_LOGITS && ph.epi != FEPI_SILU && ph.epi != FEPI_QKV));
         const bool kmatch = kind == PROG_VERIFY && ph.type == PH_GEMM && ph.epi == c->ktime_epi;
