@@ -911,8 +911,8 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
     // Weights of a draft round (or of a tree's levels), read once per step: without the hint where that cache holds all of a step's.  A round of
     // 12 steps, one sequence, with the hint -> without: 1024 wide, 32000 columns (97 MB) 569 -> 530 us, 1536 wide (160 MB) 665 -> 622, 2048 wide
     // (229 MB) 755 -> 713; but 2560 wide (336 MB) 974 -> 1040, 2048 wide with 50272 columns (348 MB) 963 -> 1044.  (With plain loads and
-    // staged rows 547, 655, 738, 1079 and 1052.)  Forms for rows of up to 2048 values, where that is: the others have the hint.
-    const bool keep = !std::is_same<WT, float>::value && (kind == PROG_DRAFT || kind == PROG_DRAFT_SAMPLE) && K > 1 && draft_step_bytes(c) <= 256.0e6;
+    // staged rows 547, 655, 738, 1079 and 1052.)  Rows of up to 2048 values, where that was measured.
+    const bool keep = !std::is_same<WT, float>::value && (kind == PROG_DRAFT || kind == PROG_DRAFT_SAMPLE) && K > 1 && g.d <= STREAM_SHORT_K && draft_step_bytes(c) <= 256.0e6;
     for (int p = 0; p < n; ++p) {
         Phase ph = phases[p];
         ph.next_W = nullptr;                       // nothing is prefetched across a kernel boundary (pulling the next launch's
