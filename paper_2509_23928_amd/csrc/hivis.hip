@@ -1326,6 +1326,11 @@ int prefill_lds_setup(hivis_ctx* c) {
                              {(const void*)gemm_tall_kernel<6, EPI_>, (size_t)tall_lds_bytes<6>()}
         HIVIS_TALL_LDS(TALL_STORE), HIVIS_TALL_LDS(TALL_SILU), HIVIS_TALL_LDS(TALL_QKV),
 #undef HIVIS_TALL_LDS
+#define HIVIS_WIDE_LDS(RT_, KW_, CT_) {(const void*)gemm_wide_kernel<RT_, KW_, CT_, WIDE_STORE>, (size_t)WideCfg<RT_, KW_, CT_>::LDS}, \
+                                      {(const void*)gemm_wide_kernel<RT_, KW_, CT_, WIDE_SILU>, (size_t)WideCfg<RT_, KW_, CT_>::LDS}
+        HIVIS_WIDE_LDS(2, 4, 2), HIVIS_WIDE_LDS(2, 4, 3), HIVIS_WIDE_LDS(2, 2, 2), HIVIS_WIDE_LDS(2, 4, 5), HIVIS_WIDE_LDS(2, 2, 3), HIVIS_WIDE_LDS(2, 2, 4), HIVIS_WIDE_LDS(2, 2, 5),
+        HIVIS_WIDE_LDS(4, 4, 2), HIVIS_WIDE_LDS(4, 4, 3), HIVIS_WIDE_LDS(4, 2, 2), HIVIS_WIDE_LDS(4, 4, 5), HIVIS_WIDE_LDS(4, 2, 3), HIVIS_WIDE_LDS(4, 2, 4),
+#undef HIVIS_WIDE_LDS
         {(const void*)attn_rows_shared_kernel<128, 8>, attn_shared_lds_bytes(128)}, {(const void*)attn_rows_shared_kernel<128, 4>, attn_shared_lds_bytes(128)},
         {(const void*)attn_rows_shared_kernel<64, 8>, attn_shared_lds_bytes(64)}, {(const void*)attn_rows_shared_kernel<64, 4>, attn_shared_lds_bytes(64)}};
     for (const auto& k : ks) HIP_TRY(c, hipFuncSetAttribute(k.k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.bytes));
@@ -1333,23 +1338,36 @@ int prefill_lds_setup(hivis_ctx* c) {
 }
 
 // Up to 64 rows in ONE pass over the weights (gemm_wide_kernel): the 11..64-row passes that no phase program takes, and a prefill's
-// products of up to 64 rows.  defer != nullptr: the slice partials are not reduced here;
-// *defer describes them for the consuming row kernel.
+// products of up to 64 rows.
+template <int EPI>
+int launch_wide(hivis_ctx* c, const WidePlan& pl, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, int ldy, uint4* frag_out, int kblks_out) {
+    const int ntiles = N / 16;
+    const dim3 grid(pl.ksplit, (ntiles + pl.tiles - 1) / pl.tiles);
+#define HIVIS_WIDE(RT_, KW_, CT_)                                                                                                              \
+    {                                                                                                                                          \
+        constexpr int lds_ = WideCfg<RT_, KW_, CT_>::LDS;                                                                                      \
+        hipLaunchKernelGGL((gemm_wide_kernel<RT_, KW_, CT_, EPI>), grid, dim3(WIDE_THREADS), lds_, c->stream, frag, (M + 15) / 16, K / 32, pl.kper, Wp, ntiles, M, \
+                           Y, ldy, pl.ksplit > 1 ? c->splitk_ws : nullptr, frag_out, kblks_out);                                               \
+    } break
+    if (M <= 32) switch (pl.form) {
+        case 0: HIVIS_WIDE(2, 4, 2); case 1: HIVIS_WIDE(2, 4, 3); case 2: HIVIS_WIDE(2, 2, 2); case 3: HIVIS_WIDE(2, 4, 5);
+        case 4: HIVIS_WIDE(2, 2, 3); case 5: HIVIS_WIDE(2, 2, 4); case 6: HIVIS_WIDE(2, 2, 5);
+    } else switch (pl.form) {
+        case 0: HIVIS_WIDE(4, 4, 2); case 1: HIVIS_WIDE(4, 4, 3); case 2: HIVIS_WIDE(4, 2, 2); case 3: HIVIS_WIDE(4, 4, 5);
+        case 4: HIVIS_WIDE(4, 2, 3); case 5: HIVIS_WIDE(4, 2, 4);
+    }
+#undef HIVIS_WIDE
+    HIP_TRY(c, hipGetLastError());
+    return HIVIS_OK;
+}
+// defer != nullptr: the slice partials are not reduced here; *defer describes them for the consuming row kernel.
 int wide_gemm(hivis_ctx* c, const uint4* frag, int M, int K, const uint4* Wp, int N, float* Y, int ldy, Parts* defer) {
-    const int kblks = K / 32, row_tiles = (M + 15) / 16, ntiles = N / 16;
-    const int ncol = (ntiles + 7) / 8;                                  // 8 column tiles per workgroup
-    int S = wide_slices(c->num_cu, kblks, ntiles);
-    if (S > 1 && !splitk_space(c, (size_t)S * M * ldy)) S = 1;
-    float* part = S > 1 ? c->splitk_ws : nullptr;
-    if (row_tiles <= 2)      // at most 32 rows: 2 row tiles per workgroup, half the fragment traffic and MFMA work
-        hipLaunchKernelGGL((gemm_wide_kernel<1>), dim3(ncol * S), dim3(256), 2 * 12 * 1024, c->stream,
-                           (const v4u_t*)frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
-    else
-        hipLaunchKernelGGL((gemm_wide_kernel<2>), dim3(ncol * S), dim3(256), 2 * 16 * 1024, c->stream,
-                           (const v4u_t*)frag, row_tiles, kblks, (const v4u_t*)Wp, ntiles, Y, ldy, M, S, part);
-    const Parts res{S > 1 ? part : Y, S, (size_t)M * ldy};
+    WidePlan pl = wide_plan(c->num_cu, M, K / 32, N / 16, true);
+    if (pl.ksplit > 1 && !splitk_space(c, (size_t)pl.ksplit * M * ldy)) pl = wide_plan(c->num_cu, M, K / 32, N / 16, false);
+    if (int rc = launch_wide<WIDE_STORE>(c, pl, frag, M, K, Wp, N, Y, ldy, nullptr, 0)) return rc;
+    const Parts res{pl.ksplit > 1 ? c->splitk_ws : Y, pl.ksplit, (size_t)M * ldy};
     if (defer) *defer = res;
-    else if (S > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, res, N, ldy, Y, ldy);
+    else if (pl.ksplit > 1) hipLaunchKernelGGL(splitk_reduce_kernel, dim3(M, row_chunks(M)), dim3(256), 0, c->stream, res, N, ldy, Y, ldy);
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
@@ -1397,6 +1415,11 @@ int rows_qkv(hivis_ctx* c, const LayerDev& L, const KVDev& kv, const uint4* frag
 // gate|up product and SiLU(gate) * up of M rows: fragments (in the layout of the down projection) to frag_out
 int rows_gateup(hivis_ctx* c, const LayerDev& L, const uint4* frag, int M, float* scratch, uint4* frag_out) {
     const int d = c->cfg.d, F = c->cfg.ffn;
+    if (M <= MAX_ROWS) {
+        const WidePlan whole = wide_plan(c->num_cu, M, d / 32, F / 8, false);
+        if (tall_fused(whole, wide_plan(c->num_cu, M, d / 32, F / 8, true)))
+            return launch_wide<WIDE_SILU>(c, whole, frag, M, d, L.wgu, 2 * F, nullptr, 0, frag_out, F / 32);
+    }
     TallPlan pl;
     if (ends_in_gemm(c, M, d, 2 * F, &pl)) {
         TallOut o{}; o.frag = frag_out; o.kblks_out = F / 32;

@@ -94,6 +94,11 @@ __device__ __forceinline__ void block_to_lds(const v4u_t* src, v4u_t* lds) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
 
+// The same from a buffer: lane l's 16 bytes, at byte `off` of the buffer, go to lds[l] (beyond the buffer: no access, LDS undefined)
+__device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t r, v4u_t* lds, int off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
+}
+
 // ------------------------------------------------------------------------------------------
 // Tall GEMM: 128 rows x 32 CW columns per workgroup of 8 wavefronts.  They are two groups of four, one wavefront of each
 // group per SIMD; the first group multiplies the even K blocks of the tile, the second the odd ones, and at the end they
@@ -346,106 +351,168 @@ __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t*
 }
 
 // ------------------------------------------------------------------------------------------
-// Wide GEMM (up to 64 activation rows: the weights are streamed once).  A workgroup of 2 x 2 wavefronts computes 2 RTW row
-// tiles (32 or 64 rows) x 128 columns of one K slice: slice s writes its partial sums to part[s][M][ldy] and the
-// consuming row kernel adds them.  Per K block the workgroup copies its blocks from memory to LDS through registers,
-// NSET K blocks ahead (the bytes in flight per workgroup set the bandwidth); two LDS stages, one LDS-only barrier per block.
+// Wide GEMM (up to 64 activation rows: the weights are streamed once).  A workgroup of 8 wavefronts computes all rows x (8 / KW) CT
+// column tiles over one K slice (kper K blocks, slice blockIdx.x); slice s writes its sums to part[s][M][ldy] and the consuming row kernel
+// adds them.  HBM bound, one workgroup per CU:
+//   * A weight block serves one wavefront only, so it goes from memory to that wavefront's registers, NBUF stages of four K blocks ahead
+//     (64..192 KB in flight per workgroup); the loop requests a block's successor right behind its products, nothing in it is
+//     conditional, and the compiler counts its waits.
+//   * The activations go from memory to a ring of R stages in LDS without registers, shared by all wavefronts; one barrier per stage.
+//   * A wavefront reads the fragments of every row (8 KB per K block at 64 rows) to multiply CT weight blocks with them, so KW
+//     wavefronts share a column group and take 4 / KW K blocks of a stage each: with one column tile per wavefront the reads from LDS were the
+//     limit (O, 61 rows: 13.9 us, now 11.2; down 27.2, now 21.6).  They add their sums through LDS at the end.
+// The columns of a workgroup decide how often the activations are read (once per column block), the slices how often the sums are written
+// and read again: wide_plan.  Against the form before (4 wavefronts, 128 columns, both operands through registers and LDS, up to 16 slices and
+// 768 workgroups, whose activations were as many bytes as its weights), us per launch back to back, before -> now; in brackets this kernel
+// without activations and products: 61 rows, 7B widths: q|k|v 28.4 -> 22.6 (22.9), O 12.6 -> 11.2 (9.5), gate|up 44.4 -> 34.5 in two slices,
+// 39.8 in one with SiLU and the fragments written (34.5), down 25.2 -> 21.6 (18.9), LM head 58.5 -> 49.3, in one slice (48.8).  31 rows, 3584 wide:
+// gate|up 54.6 -> 46.8 with SiLU, down 30.3 -> 24.5, LM head of 152064 columns 232 -> 186.  32 rows, 5120 wide: 32 -> 28, 14.2 -> 12.3, 56 -> 47, 29.3 ->
+// 24.9, 66 -> 52.5.  Starting the slices' K blocks at different places changed nothing or cost 2-10 us.
+// The low parts have accumulators of their own, added at the end: rounded at the high parts' magnitude instead, the K sum's
+// error was 1.4 times as large (61 rows, K = 4096 in 3 slices: 3.2e-7 of the result, now 2.2e-7).
+//   WIDE_STORE  fp32 rows (Y, row stride ldy; gridDim.x > 1: slices)
+//   WIDE_SILU   W = gate|up (8 + 8 columns per tile), one slice: silu(gate) * up leaves as activation fragments (frag, kblks_out K blocks);
+//               the row kernel that did it took 8 us and the slices' traffic
 // ------------------------------------------------------------------------------------------
-template <int RTW>
-__global__ __launch_bounds__(256, 2) void gemm_wide_kernel(const v4u_t* __restrict__ Af, int row_tiles, int kblks,
-                                                          const v4u_t* __restrict__ Wp, int ntiles, float* __restrict__ Y,
-                                                          int ldy, int M, int ksplit, float* __restrict__ part) {
-    constexpr int CTW = 4, NSET = 4;
-    constexpr int NA = 4 * RTW, NB = 2 * CTW, NBLK = NA + NB;     // (a row tile is a high and a low block)
-    constexpr int PER_WAVE = NBLK / 4;
-    static_assert(NBLK % 4 == 0, "blocks are dealt evenly to the 4 wavefronts");
-    extern __shared__ __align__(16) v4u_t tall_lds[];      // [2 stages][NBLK][64]
+constexpr int WIDE_THREADS = 512;
+enum { WIDE_STORE = 0, WIDE_SILU = 1 };
+template <int RT, int KW, int CT> struct WideCfg {
+    static constexpr int SK = WIDE_STAGE, J = SK / KW;                // K blocks of a stage; of it per wavefront
+    static constexpr int NBUF = J * CT <= 4 ? 4 : 2;                  // stages of weights in flight
+    static constexpr int R = RT == 4 && NBUF == 2 ? 3 : 4;            // stages of activations in LDS
+    static constexpr int STAGE = SK * RT * 2 * 64;                    // 16-byte pieces of a stage
+    // memory operations requested behind the activations of a stage by the time it is read, at the least: those of R - 2 further stages of
+    // activations, and the weights of as many stages as lie between the two points (R - 1) or were requested before the loop (NBUF)
+    static constexpr int BEHIND = (NBUF < R - 1 ? NBUF : R - 1) * J * CT + (R - 2) * RT;
+    static constexpr int EXCHANGE = (8 / KW) * CT * (KW - 1) * RT * 64;
+    static constexpr int LDS = 16 * (R * STAGE > EXCHANGE ? R * STAGE : EXCHANGE);
+    static_assert(BEHIND < 64 && LDS <= 160 * 1024 && SK * 2 == WIDE_THREADS / 64, "a wavefront per block of a row tile's stage");
+};
+
+template <int RT, int KW, int CT, int EPI>
+__global__ __launch_bounds__(WIDE_THREADS) void gemm_wide_kernel(const uint4* __restrict__ Af, int row_tiles, int kblks, int kper, const uint4* __restrict__ Wp,
+                                                                int ntiles, int M, float* __restrict__ Y, int ldy, float* __restrict__ part,
+                                                                uint4* __restrict__ frag, int kblks_out) {
+    typedef WideCfg<RT, KW, CT> CF;
+    constexpr int NBUF = CF::NBUF, R = CF::R, SK = CF::SK, J = CF::J;
+    extern __shared__ __align__(16) v4u_t tall_lds[];                 // [R][RT][K block, part][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
+    const int kg = wave % KW, cg = wave / KW;
     const int piece = afrag_piece(lane & 15, lane >> 4);
-    // the K slices of a column block on different XCDs, neighbouring column blocks on one
-    const int ncol = (ntiles + NB - 1) / NB;
-    const int split = blockIdx.x % ksplit, cblk = blockIdx.x / ksplit;
-    if (cblk >= ncol) return;
-    const int kper = (kblks + ksplit - 1) / ksplit, kb0 = split * kper;
-    const int nkb = min(kblks, kb0 + kper) - kb0;            // >= 1: the host picks ksplit so that no slice is empty
-    if (nkb <= 0) return;
-    if (ksplit > 1) Y = part + (size_t)split * M * ldy;
-    const int ct_wg = cblk * NB;
-    const v4u_t* src[PER_WAVE];
-    int inc[PER_WAVE];
+    // (blockIdx.x varies fastest: the K slices of a column block on different XCDs)
+    const int kb0 = blockIdx.x * kper, nkb = min(kblks - kb0, kper), nst = (nkb + SK - 1) / SK;       // >= 1: no slice is empty
+    const int ct0 = (blockIdx.y * (8 / KW) + cg) * CT;
+    if (gridDim.x > 1) Y = part + (size_t)blockIdx.x * M * ldy;
+
+    // Activations: wavefront w copies block w (K block w / 2, part w % 2) of every row tile of a stage.  Loads beyond the K slice, the row
+    // tiles or the column tiles do not access memory; weights then are zeros, but LDS keeps what it held (a row's Inf or NaN of another
+    // K block, say), so the blocks that fill up the last stage are cleared.  (Row tiles that do not exist: rows that are not stored.)
+    const __amdgpu_buffer_rsrc_t ra = buffer_of(Af, row_tiles * kblks * 2048);
+    int aoff[RT];
 #pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) {
-        const int b = wave + 4 * i;
-        const bool isa = b < NA;
-        // out-of-range tiles are replaced by in-range ones (clamped index); their results are never stored
-        src[i] = (isa ? Af + (((size_t)min(b >> 1, row_tiles - 1) * kblks + kb0) * 2 + (b & 1)) * 64
-                      : Wp + ((size_t)min(ct_wg + (b - NA), ntiles - 1) * kblks + kb0) * 64) + lane;
-        inc[i] = isa ? 128 : 64;
-    }
-    // The low parts have accumulators of their own, added at the end: rounded at the high parts' magnitude instead, the K sum's
-    // error was 1.4 times as large (61 rows, K = 4096 in 3 slices: 3.2e-7 of the result, now 2.2e-7).
-    f32x4_t acc[2][RTW][CTW];
+    for (int i = 0; i < RT; ++i) aoff[i] = i < row_tiles ? (i * kblks + kb0) * 2048 + wave * 1024 : OUT_OF_RANGE;
+    auto fetch_rows = [&](int s) {
+        v4u_t* const to = tall_lds + (s % R) * CF::STAGE + wave * 64;
+        const bool in = SK * s + (wave >> 1) < nkb;
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+            buffer_to_lds(ra, to + i * SK * 128, (in ? aoff[i] + s * (SK * 2048) : OUT_OF_RANGE) + lane * 16);
+        if (!in && s < nst) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) to[i * SK * 128 + lane] = v4u_t{0, 0, 0, 0};
+        }
+    };
+    __amdgpu_buffer_rsrc_t rw[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) rw[c] = buffer_of(Wp + ((size_t)min(ct0 + c, ntiles - 1) * kblks + kb0) * 64, ct0 + c < ntiles ? nkb * 1024 : 0);
+    bf16x8_t w[NBUF][J][CT];
+    // (the fences keep the weights' requests in the order of their use: a wait is for everything up to a request)
+    auto fetch_block = [&](bf16x8_t& d, int s, int j, int c) {
+        d = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rw[c], lane * 16 + s * (SK * 1024) + kg * (J * 1024) + j * 1024, 0, 2));      // 2: non-temporal
+        __builtin_amdgcn_sched_barrier(0x38F);                        // everything but vector memory may pass
+    };
+    f32x4_t acc[2][RT][CT];
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int r = 0; r < RTW; ++r)
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
-            for (int c = 0; c < CTW; ++c) acc[p][r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    v4u_t st[NSET][PER_WAVE];
+            for (int c = 0; c < CT; ++c) acc[p][r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) st[0][i] = src[i][0];
+    for (int s = 0; s < (NBUF > R - 1 ? NBUF : R - 1); ++s) {
+        if (s < R - 1) fetch_rows(s);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s < NBUF) {
 #pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) tall_lds[(size_t)(wave + 4 * i) * 64 + lane] = st[0][i];
+            for (int j = 0; j < J; ++j)
 #pragma unroll
-    for (int b = 1; b <= NSET; ++b) {
-        if (b < nkb) {
-#pragma unroll
-            for (int i = 0; i < PER_WAVE; ++i) st[b % NSET][i] = src[i][(size_t)b * inc[i]];
+                for (int c = 0; c < CT; ++c) fetch_block(w[s][j][c], s, j, c);
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    lds_barrier();
-    for (int kb0_ = 0; kb0_ < nkb; kb0_ += NSET) {
+    for (int s0 = 0;; s0 += NBUF) {
 #pragma unroll
-        for (int u = 0; u < NSET; ++u) {
-            // one K block: multiply block kb from its LDS stage, park block kb+1 (register set (u+1) % NSET) in the other
-            // stage, request block kb+1+NSET into that set
-            const int kb = kb0_ + u;
-            if (kb < nkb) {
-                const v4u_t* cur = tall_lds + (size_t)(kb & 1) * NBLK * 64;
-                v4u_t* nxt = tall_lds + (size_t)((kb + 1) & 1) * NBLK * 64;
-                v4u_t a[2][RTW], b[CTW];
+        for (int u = 0; u < NBUF; ++u) {
+            const int s = s0 + u;
+            // the activations of stage s have arrived (what was requested behind them may be in flight), and every wavefront has read stage s - 1
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(CF::BEHIND) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_rows(s + R - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const v4u_t* at = tall_lds + (s % R) * CF::STAGE + kg * (J * 128) + piece;
 #pragma unroll
-                for (int r = 0; r < RTW; ++r) { a[0][r] = cur[(size_t)(2 * (wr * RTW + r)) * 64 + piece]; a[1][r] = cur[(size_t)(2 * (wr * RTW + r) + 1) * 64 + piece]; }
+            for (int j = 0; j < J; ++j) {
+                bf16x8_t a[2][RT];
 #pragma unroll
-                for (int c = 0; c < CTW; ++c) b[c] = cur[(size_t)(NA + wc * CTW + c) * 64 + lane];
+                for (int r = 0; r < RT; ++r)
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
+                    for (int p = 0; p < 2; ++p) a[p][r] = __builtin_bit_cast(bf16x8_t, at[(r * SK * 2 + 2 * j + p) * 64]);
 #pragma unroll
-                    for (int r = 0; r < RTW; ++r)
+                for (int c = 0; c < CT; ++c) {
 #pragma unroll
-                        for (int c = 0; c < CTW; ++c)
-                            acc[p][r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[c]), __builtin_bit_cast(bf16x8_t, a[p][r]), acc[p][r][c], 0, 0, 0);
-                if (kb + 1 < nkb) {
+                    for (int p = 0; p < 2; ++p)
 #pragma unroll
-                    for (int i = 0; i < PER_WAVE; ++i) nxt[(size_t)(wave + 4 * i) * 64 + lane] = st[(u + 1) % NSET][i];
-                    if (kb + 1 + NSET < nkb) {
-#pragma unroll
-                        for (int i = 0; i < PER_WAVE; ++i) st[(u + 1) % NSET][i] = src[i][(size_t)(kb + 1 + NSET) * inc[i]];
-                    }
+                        for (int r = 0; r < RT; ++r) acc[p][r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][j][c], a[p][r], acc[p][r][c], 0, 0, 0);
+                    fetch_block(w[u][j][c], s + NBUF, j, c);
                 }
-                lds_barrier();
             }
+            if (s + 1 >= nst) goto summed;                            // (uniform; leaving is the only branch, so the waits inside stay exact)
         }
     }
+summed:
+    wait_vmem();                                                      // (the last requests: zeros to a ring that the exchange reuses)
+    // the wavefronts of a column group share its column tiles out: tile c is finished by wavefront c % KW of them
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    f32x4_t* const ex = reinterpret_cast<f32x4_t*>(tall_lds) + cg * CT * (KW - 1) * RT * 64 + lane;
 #pragma unroll
-    for (int r = 0; r < RTW; ++r) {
-        const int row = (wr * RTW + r) * 16 + (lane & 15);
-        if (row >= M) continue;
+    for (int c = 0; c < CT; ++c)
+        if (c % KW != kg) {
 #pragma unroll
-        for (int c = 0; c < CTW; ++c) {
-            const int ct = ct_wg + wc * CTW + c;
-            if (ct < ntiles) *reinterpret_cast<f32x4_t*>(Y + (size_t)row * ldy + ct * 16 + 4 * (lane >> 4)) = acc[0][r][c] + acc[1][r][c];
+            for (int r = 0; r < RT; ++r) ex[((c * (KW - 1) + kg - (kg > c % KW)) * RT + r) * 64] = acc[0][r][c] + acc[1][r][c];
+        }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        if (c % KW != kg || ct0 + c >= ntiles) continue;              // (uniform)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            f32x4_t v = acc[0][r][c] + acc[1][r][c];
+#pragma unroll
+            for (int k = 0; k < KW - 1; ++k) v += ex[((c * (KW - 1) + k) * RT + r) * 64];
+            // this lane: columns 4 (lane / 16) .. + 3 of the tile, one row
+            const int row = r * 16 + (lane & 15);
+            if constexpr (EPI == WIDE_SILU) {
+                f32x4_t up;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) up[e] = __shfl_xor(v[e], 32, 64);
+                if (lane < 32 && row < M) {
+                    float y[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = v[e] / (1.0f + expf(-v[e])) * up[e];
+                    store_afrag4(frag, kblks_out, row, 8 * (ct0 + c) + 4 * (lane >> 4), y[0], y[1], y[2], y[3]);
+                }
+            } else if (row < M) *reinterpret_cast<f32x4_t*>(Y + (size_t)row * ldy + (ct0 + c) * 16 + 4 * (lane >> 4)) = v;
         }
     }
 }

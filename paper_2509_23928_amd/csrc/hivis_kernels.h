@@ -66,6 +66,12 @@ __device__ __forceinline__ float4 load4_f32(const bf16_t* p) {
 __device__ __forceinline__ float4 load4_f32(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ float4 load4_f32(const bf16w_t* p) { return load4_f32(reinterpret_cast<const bf16_t*>(p)); }
 
+// Buffer descriptor of `bytes` bytes from p on: loads beyond them return zeros without a memory access
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+constexpr int OUT_OF_RANGE = 0x40000000;       // byte offset of a lane that loads nothing
+
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding global
 // load of the wavefront, which would drain the weight prefetch pipeline at each use.
 __device__ __forceinline__ void lds_barrier() {

@@ -58,16 +58,45 @@ inline TallPlan tall_plan(int num_cu, int M, int kblks, int ntiles, bool may_spl
 }
 
 // The q|k|v and the gate|up product end in the GEMM itself unless K slices win back more than the row kernel costs
-// (ROW_KERNEL_US: its launch and ramp; its traffic is in the slices' estimate).  At most 64 rows: slices.
+// (ROW_KERNEL_US: its launch and ramp; its traffic is in the slices' estimate).  At most 64 rows: gate|up likewise, q|k|v never.
 constexpr double ROW_KERNEL_US = 8.0;
-inline bool tall_fused(const TallPlan& whole, const TallPlan& sliced) { return whole.us <= sliced.us + ROW_KERNEL_US; }
+template <typename Plan> bool tall_fused(const Plan& whole, const Plan& sliced) { return whole.us <= sliced.us + ROW_KERNEL_US; }
 
-// K slices of a GEMM of at most 64 rows: about 3 workgroups of 8 column tiles per CU and at most 16 slices (swept at 61 rows:
-// 256/384/512/768/1024 workgroups, 8/16 slices; 256-column tiles with half the slices were no faster, at 61 rows and at 32)
+// GEMMs of at most 64 rows: column tiles of a workgroup ((8 / kw) * ct: kw wavefronts share ct column tiles, see gemm_wide_kernel) and K slices (of
+// kper K blocks each), the pair with the least estimated time.  One workgroup per CU; more of them than CUs only as one slice.  A workgroup
+// takes 0.0277 us per K block and row tile plus 0.0231 per K block and column tile when the CU is the limit; all of them together stream
+// 7.7 MB of weights per us and 24 of activations (read once per column block), the less of both the fewer CUs work; writing a
+// slice costs its bytes at 2 MB per us, reading it again in the consumer at 3.5.  Fitted to 286 launches (15 products of the 7B and 13B widths at 31, 32, 61 and 64
+// rows, all forms and slices): 4.7 % off on average; what it picks is at most 4 % slower than the best of them, but for the down projection of 18944 rows
+// at 64 rows (8 %).
+constexpr int WIDE_STAGE = 4;       // K blocks that a workgroup takes at a time
+struct WideForm { int kw, ct; };
+constexpr WideForm WIDE_FORMS[] = {{4, 2}, {4, 3}, {2, 2}, {4, 5}, {2, 3}, {2, 4}, {2, 5}};       // 4, 6, 8, 10, 12, 16, 20 column tiles
+constexpr int WIDE_NFORMS = sizeof(WIDE_FORMS) / sizeof(WIDE_FORMS[0]);
+constexpr int wide_forms(int M) { return M <= 32 ? WIDE_NFORMS : WIDE_NFORMS - 1; }                // (the widest: up to 32 rows, its sums fill the registers)
+// the most slices of a product: the room for them (splitk_floats) holds 3 * num_cu * 128 columns; none empty, none of less than 4 K blocks
 inline int wide_slices(int num_cu, int kblks, int ntiles) {
     int S = std::max(1, std::min(16, 3 * num_cu / ((ntiles + 7) / 8)));
-    while (S > 1 && ((S - 1) * ((kblks + S - 1) / S) >= kblks || (kblks + S - 1) / S < 4)) --S;     // no empty slice, >= 4 K blocks each
+    while (S > 1 && ((S - 1) * ((kblks + S - 1) / S) >= kblks || (kblks + S - 1) / S < 4)) --S;
     return S;
+}
+struct WidePlan { int form, tiles, ksplit, kper; double us; };
+inline WidePlan wide_plan(int num_cu, int M, int kblks, int ntiles, bool may_split) {
+    WidePlan best{0, 4, 1, kblks, 1e30};
+    const int rt = M <= 32 ? 2 : 4, most = may_split ? wide_slices(num_cu, kblks, ntiles) : 1;
+    for (int f = 0; f < wide_forms(M); ++f)
+        for (int S = 1; S <= most; ++S) {
+            const int tiles = 8 / WIDE_FORMS[f].kw * WIDE_FORMS[f].ct, kper = ((kblks + WIDE_STAGE - 1) / WIDE_STAGE + S - 1) / S * WIDE_STAGE;
+            const int wgs = (ntiles + tiles - 1) / tiles * S;
+            if (S > 1 && ((S - 1) * kper >= kblks || wgs > num_cu)) continue;
+            const int rounds = (wgs + num_cu - 1) / num_cu;
+            const double fill = (double)wgs / (rounds * num_cu), sums = 4.0e-6 * S * M * ntiles * 16;
+            const double cu = rounds * kper * (0.0277 * rt + 0.0231 * tiles);
+            const double all = (1.024e-3 * kblks * ntiles / 7.7 + 2.0e-3 * wgs * kper * rt / 24.0) / std::pow(fill, 0.31);
+            const double us = 2.6 + std::max(cu, all) + 3.0 * (rounds - 1) + sums * (1 / 2.0 + 1 / 3.5);
+            if (us < best.us - 1e-9) best = {f, tiles, S, kper, us};
+        }
+    return best;
 }
 
 // Floats that hold the K slices of every product of a context: the most that a pass of up to 64 rows needs (slices x column

@@ -21,13 +21,8 @@
 
 namespace hivis {
 
-// Buffer descriptor of `bytes` bytes from p on: loads beyond them return zeros without a memory access
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
 __device__ __forceinline__ float buffer_f32(__amdgpu_buffer_rsrc_t r, int byte) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, byte, 0, 0)); }
 __device__ __forceinline__ float buffer_bf16(__amdgpu_buffer_rsrc_t r, int byte) { return bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(r, byte, 0, 0)); }
-constexpr int OUT_OF_RANGE = 0x40000000;       // byte offset of a lane that loads nothing
 constexpr int STREAM_MAX_D = 8192;             // row widths served (registers for a row's sums of squares, and for a row)
 
 // the lane's operand row: 8-row form: row 2 (i / 4) + i % 2, high part for i & 2 == 0; 16-row form: row i, both parts
