@@ -111,10 +111,12 @@ __device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t r, v4u_t* l
 // Both parts add into the SAME accumulators (there are no registers for two sets).  That rounds twice as often at the high parts'
 // magnitude, but each group's sum has half the K blocks: together the error of the sums alone is that of one sum over all of K with the
 // low parts beside it (4.0e-7 of the result for both at K = 4096, 6.7e-7 at K = 11008; the 16 mantissa bits of the operands leave 2.5e-6).
-// Matrix bound: with random data the MFMAs alone run at 2.0 PFLOP/s on this card (2.46 on zeros, it is power that
-// limits them), a library product of 8192^3 at 1.10.  640 rows, K = 4096, high and low parts counted: 22016 columns 249 ->
-// 172 us (1.35 PFLOP/s), 12288 columns 127 -> 94 us (1.37); 3008 x 22016: 1090 -> 813 us (1.33): launches of one size back to back, inside
-// traced requests 182, 106 and 854 us.  The version with the requests
+// Bound by power: with random data the MFMAs alone run at 2.0 PFLOP/s on this card (2.46 on zeros), a library product of 8192^3 at 1.13,
+// and this kernel's loop takes 136 thousand cycles of a 224-column tile at K = 4096 (115 are MFMAs) whatever the data: 57 us at 2.39 GHz on
+// zeros, 77 at 1.76 on random data.  So what the MFMAs switch counts.  640 rows x 22016 columns, launches back to back, by their order: column
+// tiles outside, row tiles inside, the part outermost 164.4 us; the same with one operand kept from each to the next 161; both parts of
+// an accumulator in turn 158; and a row tile outside, so that each operand changes at every second product, 156.2 (1.48 PFLOP/s).
+// 640 rows, K = 4096, high and low parts counted, before the two groups: 22016 columns 249 us, 12288 columns 127; 3008 x 22016: 1090.  The version with the requests
 // at the head of the multiplication phase took 203 and 107 us; groups owning row halves instead of K blocks (256-row
 // tiles) were no faster at 3008 rows and left too few tiles at 640.
 // ------------------------------------------------------------------------------------------
@@ -303,13 +305,17 @@ __global__ __launch_bounds__(TALL_THREADS, 2) void gemm_tall_kernel(const v4u_t*
         // multiplication phase
         if (s < mine) {
             __builtin_amdgcn_s_setprio(1);
+            // both parts of an accumulator one after the other, and from one product to the next one operand stays (fixed by the fences)
 #pragma unroll
-            for (int p = 0; p < 2; ++p)
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int c = 0; c < CW; ++c)
+                for (int c_ = 0; c_ < CW; ++c_)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
+                    for (int p_ = 0; p_ < 2; ++p_) {
+                        const int c = (r & 1) ? CW - 1 - c_ : c_, p = ((r * CW + c_) & 1) ? 1 - p_ : p_;
                         acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[c]), __builtin_bit_cast(bf16x8_t, fa[p][r]), acc[r][c], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
             __builtin_amdgcn_s_setprio(0);
         }
         HIVIS_PHASE_END("lgkmcnt(0)");
