@@ -6,6 +6,7 @@
 #include "hivis_gemm.h"
 #include "hivis_fused.h"
 #include "hivis_stream.h"
+#include "hivis_tile.h"
 #include "hivis_tree.h"
 
 #include <hip/hip_ext.h>
@@ -1021,6 +1022,27 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             }
             if (ph.type == PH_PREP && ph.F) {
                 hipExtLaunchKernelGGL(stream_prep_kernel, dim3(pp.M), dim3(FUSED_NT), 0, c->stream, kev0, kev1, 0, ph, ppl);
+                continue;
+            }
+        }
+        if constexpr (std::is_same<WT, float>::value) {
+            // fp32, one tile per workgroup and one pass over K: the wavefronts share K evenly, in kernels for as many blocks as they then have.  (The
+            // fusion FC only with the table.)
+            const int kblks = ph.K / 16;
+            if (single && kblks <= TILE_MAX_BLOCKS && (ph.epi != FEPI_ADDVEC || ph.add_rows) && !(ph.epi == FEPI_QKV && (ph.pos_delta || (ph.add_rows && pp.M > 4)))) {
+                const int per = (kblks + FUSED_NW - 1) / FUSED_NW;
+#define HIVIS_TILE_(EP, U_) hipExtLaunchKernelGGL((tile_kernel<EP, U_>), dim3(grid), dim3(FUSED_NT), 0, c->stream, kev0, kev1, 0, ph, ppl)
+#define HIVIS_TILE(EP) do { if (per <= 2) HIVIS_TILE_(EP, 2); else if (per <= 4) HIVIS_TILE_(EP, 4); else if (per <= 6) HIVIS_TILE_(EP, 6); else HIVIS_TILE_(EP, 8); } while (0)
+                switch (ph.epi) {
+                case FEPI_ADD_TO: HIVIS_TILE(FEPI_ADD_TO); break;
+                case FEPI_ADDVEC: HIVIS_TILE(FEPI_ADDVEC); break;
+                case FEPI_QKV: if (ph.add_rows) HIVIS_TILE(FEPI_QKV_TAB); else HIVIS_TILE(FEPI_QKV); break;
+                case FEPI_SILU: HIVIS_TILE(FEPI_SILU); break;
+                case FEPI_LOGITS: HIVIS_TILE(FEPI_LOGITS); break;
+                default: return fail(c, HIVIS_EINVAL, "phase %d: no kernel for epilogue %d", p, ph.epi);
+                }
+#undef HIVIS_TILE
+#undef HIVIS_TILE_
                 continue;
             }
         }
