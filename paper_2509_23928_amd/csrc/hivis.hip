@@ -7,6 +7,7 @@
 #include "hivis_fused.h"
 #include "hivis_stream.h"
 #include "hivis_tile.h"
+#include "hivis_attn.h"
 #include "hivis_tree.h"
 
 #include <hip/hip_ext.h>
@@ -114,6 +115,7 @@ struct hivis_ctx {
     struct Program { hivis::Phase* dev = nullptr; int n = 0; std::vector<hivis::Phase>* host = nullptr; };
     int attn_shared_min = 128;           // rows per sequence from which a causal pass uses the shared-tile attention kernel (128 rows per workgroup)
     int keys_per_split = 192;            // attention: cached keys per workgroup (one or two 16-key tiles per wavefront) before the key range is split further
+    bool keys_forced = false;            // HIVIS_KEYS_PER_SPLIT: of half-precision caches as well (attn_block_splits otherwise)
     bool attn_elect = true;              // key splits merged by the workgroup that arrives last (false: by a merge launch)
     int attn_flags = 3;                  // AttnShape::flags of the phase programs
     bool persistent = false;             // HIVIS_PERSISTENT=1: one cooperative launch per pass instead of one launch per phase
@@ -370,9 +372,36 @@ int attention(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int*
 
 AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, int ldq, bool alone, int* items_out);
 
+int key_splits(const hivis_ctx* c, int keys, int most, bool half) { return half && !c->keys_forced ? attn_block_splits(keys, most) : attn_splits(keys, most, c->keys_per_split); }
+
+// One launch of attn_split_kernel.  rm: (head,row) pairs an item may hold, 8 or 16 (the partials' and the kernel's); once: cached rows with the
+// non-temporal hint.
+int launch_attn_split(hivis_ctx* c, const AttnShape& sh, int items, int rm, const float* q, const void* kc, const void* vc, const int* base, const AttnOut& out,
+                      uint4* frag_out, float* ws, int* cnt, bool once, unsigned long long* prof3 = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
+    const int hd = c->cfg.head_dim;
+    AttnArgs a{};
+    a.q = q; a.kc = (const f16_t*)kc; a.vc = (const f16_t*)vc; a.base = base; a.tmask = sh.tmask; a.ws = ws; a.cnt = cnt;
+    a.y = out.y; a.ldo = out.ldo; a.rows_out = out.frag; a.rows = out.rows; a.frag_out = frag_out;
+    a.ldq = sh.ldq; a.maxL = sh.maxL; a.offset = sh.offset; a.seq0 = sh.seq0; a.m = sh.m; a.qrows = sh.qrows; a.mi = sh.mi; a.gh = sh.gh; a.Hkv = sh.Hkv;
+    a.group = sh.Hq / sh.Hkv; a.n_rblk = sh.n_rblk; a.n_hblk = sh.n_hblk; a.items = items; a.nsplit = sh.nsplit; a.flags = sh.flags; a.nbase = sh.nbase;
+    a.by_rblk = FastDiv::by(sh.n_rblk); a.by_hblk = FastDiv::by(sh.n_hblk); a.by_hkv = FastDiv::by(sh.Hkv); a.by_split = FastDiv::by(sh.nsplit); a.by_mi = FastDiv::by(sh.mi);
+    for (int b = 0; b < sh.nbase; ++b) a.base_val[b] = sh.base_val[b];
+    a.prof3 = prof3;
+    const int heads = items / sh.n_rblk;
+    const dim3 grid = (sh.flags & 2) ? dim3(8, sh.nsplit, (heads + 7) / 8 * sh.n_rblk) : dim3(sh.nsplit, items);
+#define HIVIS_SPLIT(HD_, RM_, ONCE_)                                                                                                          \
+    do { constexpr int lds_ = AttnSplitCfg<HD_, RM_>::LDS;                                                                                    \
+         hipExtLaunchKernelGGL((attn_split_kernel<HD_, RM_, ONCE_>), grid, dim3(FUSED_NT), lds_, c->stream, ev0, ev1, 0, a); } while (0)
+    if (rm > FUSED_RMAX) { if (hd == 128) HIVIS_SPLIT(128, ATTN_ROWS_RM, false); else HIVIS_SPLIT(64, ATTN_ROWS_RM, false); }
+    else if (hd == 128) { if (once) HIVIS_SPLIT(128, FUSED_RMAX, true); else HIVIS_SPLIT(128, FUSED_RMAX, false); }
+    else { if (once) HIVIS_SPLIT(64, FUSED_RMAX, true); else HIVIS_SPLIT(64, FUSED_RMAX, false); }
+#undef HIVIS_SPLIT
+    HIP_TRY(c, hipGetLastError());
+    return HIVIS_OK;
+}
+
 // Attention of nseq x m rows on the matrix cores, outside a phase program (prefill; passes with more rows than one MFMA
-// tile): the same workgroup routine as the verify pass (one item = one kv head x <= 8 (head,row) pairs, all visible
-// keys, no key split), launched once over all items.  Rows of sequence seq0 + s sit at positions base[seq0 + s] + offset + i.
+// tile): long causal row ranges through the shared-tile kernel, others through the verify pass's kernel in one launch over all items.  Rows of sequence seq0 + s sit at positions base[seq0 + s] + offset + i.
 template <typename WT>
 int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int* base, int offset, int seq0, int nseq, int m,
                         float* out, int ldo, const unsigned long long* tmask = nullptr, uint4* frag_out = nullptr, bool* wrote_frag = nullptr, int qrows = 0, uint4* row_frag = nullptr) {
@@ -406,59 +435,38 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
             HIP_TRY(c, hipGetLastError());
             return HIVIS_OK;
         }
+        AttnShape sh{};
+        int items = 0, rm = FUSED_RMAX;
         if (m > FUSED_RMAX) {
-            // many rows per sequence: 16 (head,row) pairs per work item
-            AttnShape sh{};
+            // many rows per sequence: 16 (head,row) pairs per work item, which reads every cached key half as often
+            rm = ATTN_ROWS_RM;
             sh.Hq = g.n_q_heads; sh.Hkv = g.n_kv_heads; sh.m = m;
             const int group = g.n_q_heads / g.n_kv_heads;
-            if (m >= ATTN_ROWS_RM) { sh.mi = ATTN_ROWS_RM; sh.gh = 1; }
-            else { sh.mi = m; sh.gh = std::max(1, std::min(group, ATTN_ROWS_RM / m)); }
+            if (m >= rm) { sh.mi = rm; sh.gh = 1; }
+            else { sh.mi = m; sh.gh = std::max(1, std::min(group, rm / m)); }
             sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
-            sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.qrows = qrows; sh.nwaves = FUSED_NW; sh.nsplit = 1; sh.tmask = tmask;
-            const int items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
-            const size_t lds = fused_attn_mfma_lds_floats(g.head_dim, FUSED_NW, ATTN_ROWS_RM) * sizeof(float);
-            uint4* frag = (frag_out && wrote_frag && ldo % 32 == 0) ? frag_out : nullptr;
-            if (frag) *wrote_frag = true;
-            if (g.head_dim == 128) {
-                static bool attr128 = false;
-                if (!attr128) { HIP_TRY(c, hipFuncSetAttribute((const void*)attn_rows_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); attr128 = true; }
-                hipLaunchKernelGGL((attn_rows_kernel<128>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, AttnOut{out, ldo, row_frag, nseq * m}, frag);
-            } else {
-                static bool attr64 = false;
-                if (!attr64) { HIP_TRY(c, hipFuncSetAttribute((const void*)attn_rows_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); attr64 = true; }
-                hipLaunchKernelGGL((attn_rows_kernel<64>), dim3(items), dim3(FUSED_NT), lds, c->stream, q, (const f16_t*)kv.k, (const f16_t*)kv.v, base, sh, AttnOut{out, ldo, row_frag, nseq * m}, frag);
-            }
-            HIP_TRY(c, hipGetLastError());
-            return HIVIS_OK;
+            sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq;
+            items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
+        } else sh = fused_attn_shape(c, nseq, m, offset, kv.maxL, ldq, false, &items);
+        sh.seq0 = seq0; sh.tmask = tmask; sh.flags = c->attn_flags; sh.qrows = qrows; sh.nsplit = 1;
+        if (base == c->zeros && nseq <= 8) sh.nbase = nseq;             // (base_val: zeros)
+        float* ws = nullptr; int* cnt = nullptr;
+        if (c->attn_elect && items <= c->rows_cnt_n) {
+            // the key range of an item is split over workgroups and the last one to arrive merges (as in the phase programs); the host mirrors the
+            // cache lengths that `base` holds.  No more workgroups than CUs: with more, 160 items of 32 rows got slower (8.8 -> 9.6 ms per verify).
+            const std::vector<int>* hl = base == c->tlen ? &c->h_tlen : base == c->dlen ? &c->h_dlen : nullptr;
+            int max_keys = 0;
+            for (int s = 0; s < nseq; ++s) max_keys = std::max(max_keys, (hl ? (*hl)[seq0 + s] : 0) + offset + m);
+            const int wgs = (sh.flags & 2) ? (items / sh.n_rblk + 7) / 8 * 8 * sh.n_rblk : items;
+            int nsplit = key_splits(c, max_keys, std::min(ATTN_MAX_SPLITS, std::max(1, c->fused_grid / wgs)), true);
+            while (nsplit > 1 && (size_t)items * nsplit * rm * (g.head_dim + 2) > c->attn_ws_floats) --nsplit;
+            if (nsplit > 1) { sh.nsplit = nsplit; ws = c->attn_ws; cnt = c->rows_cnt; }
         }
+        uint4* frag = (frag_out && wrote_frag && ldo % 32 == 0) ? frag_out : nullptr;
+        if (frag) *wrote_frag = true;
+        return launch_attn_split(c, sh, items, rm, q, kv.k, kv.v, base, AttnOut{out, ldo, row_frag, nseq * m}, frag, ws, cnt, false);
     }
-    int items = 0;
-    Phase ph{};
-    ph.type = PH_ATTN;
-    ph.att = fused_attn_shape(c, nseq, m, offset, kv.maxL, ldq, false, &items);
-    ph.att.seq0 = seq0; ph.att.nsplit = 1; ph.att.tmask = tmask; ph.att.flags = c->attn_flags; ph.att.qrows = qrows;
-    ph.att_items = items;
-    ph.A = q; ph.kc = kv.k; ph.vc = kv.v; ph.maxL = kv.maxL; ph.base = base; ph.offset = offset;
-    ph.Y = out; ph.ldy = ldo; ph.ws = nullptr; ph.cnt = nullptr; ph.F = row_frag;
-    if (c->attn_elect && items <= c->rows_cnt_n) {
-        // long caches: the key range of an item is split over workgroups and the last one to arrive merges (as in the
-        // phase programs); the host mirrors the cache lengths that `base` holds
-        const std::vector<int>* hl = base == c->tlen ? &c->h_tlen : base == c->dlen ? &c->h_dlen : nullptr;
-        int max_keys = 0;
-        for (int s = 0; s < nseq; ++s) max_keys = std::max(max_keys, (hl ? (*hl)[seq0 + s] : 0) + offset + m);
-        int nsplit = std::min({ATTN_MAX_SPLITS, (max_keys + c->keys_per_split - 1) / c->keys_per_split, std::max(1, c->fused_grid / items)});    // no more workgroups than CUs: with more, C5's 160 items got slower (8.8 -> 9.6 ms per verify)
-        while (nsplit > 1 && (size_t)items * nsplit * FUSED_RMAX * (g.head_dim + 2) > c->attn_ws_floats) --nsplit;
-        if (nsplit > 1) { ph.att.nsplit = nsplit; ph.ws = c->attn_ws; ph.cnt = c->rows_cnt; }
-    }
-    if constexpr (std::is_same<typename KVType<WT>::type, f16_t>::value) {
-        if (ph.att.nsplit == 1 && frag_out && wrote_frag && ldo % 32 == 0) { ph.frag = frag_out; *wrote_frag = true; }
-    }
-    const int grid = ((ph.att.flags & 2) ? 8 * ((items + 7) / 8) : items) * ph.att.nsplit;
-    PassParams pp{};
-    pp.M = nseq * m; pp.nseq = nseq; pp.m = m; pp.d = g.d; pp.Hq = g.n_q_heads; pp.Hkv = g.n_kv_heads; pp.hd = g.head_dim; pp.F = g.ffn; pp.V = g.vocab;
-    hipLaunchKernelGGL((phase_kernel<WT, PH_ATTN, 0, false>), dim3(grid), dim3(FUSED_NT), c->fused_lds, c->stream, ph, pp);
-    HIP_TRY(c, hipGetLastError());
-    return HIVIS_OK;
+    return fail(c, HIVIS_EINVAL, "attention on the matrix cores needs half-precision caches");
 }
 
 // One decoder layer on M = nseq*m rows.  h: residual stream [M][d] (in place).  `pending` (may be null) is a delta
@@ -919,7 +927,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
         ph.next_W = nullptr;                       // nothing is prefetched across a kernel boundary (pulling the next launch's
                                                    // first units into L2 during the epilogue was measured: 3% slower)
         if (ph.type == PH_ATTN || ph.type == PH_ATTN_MERGE) {
-            ph.att.nsplit = attn_splits(max_keys, ph.att.nsplit, c->keys_per_split);
+            ph.att.nsplit = key_splits(c, max_keys, ph.att.nsplit, !std::is_same<WT, float>::value);
             if (ph.att_alone) {
                 int items = 0;
                 AttnShape one = fused_attn_shape(c, pp.nseq, pp.m, ph.offset, ph.maxL, ph.att.ldq, true, &items);
@@ -1070,8 +1078,9 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             }
             break;
         case PH_ATTN:
-            if constexpr (!std::is_same<WT, float>::value) { if (once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1) { HIVIS_LAUNCH(PH_ATTN, ATTN_ONCE); break; } }
-            HIVIS_LAUNCH(PH_ATTN, 0);
+            if constexpr (std::is_same<WT, float>::value) HIVIS_LAUNCH(PH_ATTN, 0);
+            else if (int rc = launch_attn_split(c, ph.att, ph.att_items, FUSED_RMAX, ph.A, ph.kc, ph.vc, ph.base, AttnOut{ph.Y, ph.ldy, ph.F, pp.M}, nullptr, ph.ws, ph.cnt,
+                                                once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1, ppl.prof3, kev0, kev1)) return rc;
             break;
         case PH_ATTN_MERGE: HIVIS_LAUNCH(PH_ATTN_MERGE, 0); break;
         case PH_PREP: HIVIS_LAUNCH(PH_PREP, 0); break;
@@ -1233,7 +1242,7 @@ int fused_setup(hivis_ctx* c) {
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_SILU, false>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, false>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADD_TO, true>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_ADDVEC, true>,
-                            (const void*)phase_kernel<WT, PH_ATTN, 0, false>, (const void*)phase_kernel<WT, PH_ATTN_MERGE, 0, false>,
+                            (const void*)phase_kernel<WT, PH_ATTN_MERGE, 0, false>,
                             (const void*)phase_kernel<WT, PH_PREP, 0, false>, (const void*)phase_kernel<WT, PH_NORM_ROWS, 0, false>,
                             (const void*)phase_kernel<WT, PH_ARGMAX, 0, false>, (const void*)phase_kernel<WT, PH_SAMPLE, 0, false>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
@@ -1241,11 +1250,11 @@ int fused_setup(hivis_ctx* c) {
     if constexpr (std::is_same<WT, float>::value) {
         const void* ks[] = {(const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV, true>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB, true>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB4, true>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_SILU, true>,
-                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, true>};
+                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, true>, (const void*)phase_kernel<WT, PH_ATTN, 0, false>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
     }
     if constexpr (std::is_same<WT, bf16_t>::value) {
-        const void* kk[] = {(const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB, false, true>, (const void*)phase_kernel<bf16_t, PH_ATTN, ATTN_ONCE, false>};
+        const void* kk[] = {(const void*)phase_kernel<bf16_t, PH_GEMM, FEPI_QKV_TAB, false, true>};
         for (const void* k : kk) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
         typedef FusedCfg<bf16w_t> CW;
         c->fused_lds_w = fused_gemm_lds_floats(CW::NW, CW::G, WTraits<bf16w_t>::RPL, CW::KBW, FUSED_CHUNK<bf16w_t>) * sizeof(float);
@@ -1265,7 +1274,7 @@ int fused_setup(hivis_ctx* c) {
     { const char* we = getenv("HIVIS_WIDE_GEMM"); c->no_wide_gemm = we && we[0] == '0'; }
     { const char* we = getenv("HIVIS_WIDE_MIN"); if (we && atoi(we) >= 1) c->wide_min = atoi(we); }
     { const char* ke = getenv("HIVIS_ATTN_SHARED_MIN"); if (ke && atoi(ke) >= 1) c->attn_shared_min = atoi(ke); }
-    { const char* ke = getenv("HIVIS_KEYS_PER_SPLIT"); if (ke && atoi(ke) >= 16) c->keys_per_split = atoi(ke); }
+    { const char* ke = getenv("HIVIS_KEYS_PER_SPLIT"); if (ke && atoi(ke) >= 16) { c->keys_per_split = atoi(ke); c->keys_forced = true; } }
     { const char* ee = getenv("HIVIS_ATTN_ELECT"); if (ee) c->attn_elect = ee[0] == '1'; }
     { const char* fe = getenv("HIVIS_ATTN_FLAGS"); if (fe) c->attn_flags = atoi(fe); }
     int nb = 0;
@@ -1353,6 +1362,10 @@ int prefill_lds_setup(hivis_ctx* c) {
         HIVIS_WIDE_LDS(2, 4, 2), HIVIS_WIDE_LDS(2, 4, 3), HIVIS_WIDE_LDS(2, 2, 2), HIVIS_WIDE_LDS(2, 4, 5), HIVIS_WIDE_LDS(2, 2, 3), HIVIS_WIDE_LDS(2, 2, 4), HIVIS_WIDE_LDS(2, 2, 5),
         HIVIS_WIDE_LDS(4, 4, 2), HIVIS_WIDE_LDS(4, 4, 3), HIVIS_WIDE_LDS(4, 2, 2), HIVIS_WIDE_LDS(4, 4, 5), HIVIS_WIDE_LDS(4, 2, 3), HIVIS_WIDE_LDS(4, 2, 4),
 #undef HIVIS_WIDE_LDS
+#define HIVIS_SPLIT_LDS(HD_, RM_, ONCE_) {(const void*)attn_split_kernel<HD_, RM_, ONCE_>, (size_t)AttnSplitCfg<HD_, RM_>::LDS}
+        HIVIS_SPLIT_LDS(128, ATTN_ROWS_RM, false), HIVIS_SPLIT_LDS(64, ATTN_ROWS_RM, false), HIVIS_SPLIT_LDS(128, FUSED_RMAX, true), HIVIS_SPLIT_LDS(128, FUSED_RMAX, false),
+        HIVIS_SPLIT_LDS(64, FUSED_RMAX, true), HIVIS_SPLIT_LDS(64, FUSED_RMAX, false),
+#undef HIVIS_SPLIT_LDS
         {(const void*)attn_rows_shared_kernel<128, 8>, attn_shared_lds_bytes(128)}, {(const void*)attn_rows_shared_kernel<128, 4>, attn_shared_lds_bytes(128)},
         {(const void*)attn_rows_shared_kernel<64, 8>, attn_shared_lds_bytes(64)}, {(const void*)attn_rows_shared_kernel<64, 4>, attn_shared_lds_bytes(64)}};
     for (const auto& k : ks) HIP_TRY(c, hipFuncSetAttribute(k.k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.bytes));
@@ -2250,7 +2263,7 @@ int do_create(hivis_ctx* c, const hivis_weights* w) {
         if (c->pf_rows && !c->fused) max_items = std::max(max_items, (size_t)g.n_q_heads * ((c->pf_rows + ATT_RMAX - 1) / ATT_RMAX + B));
         c->attn_ws_floats = (2 * (size_t)c->num_cu + max_items) * 4 * ATT_RMAX * (g.head_dim + 2);
         if ((rc = dev_alloc(c, &c->attn_ws, c->attn_ws_floats))) return rc;
-        c->rows_cnt_n = std::max(2, B) * g.n_q_heads;
+        c->rows_cnt_n = (std::max(2, B) + MAX_ROWS / ATTN_ROWS_RM) * g.n_q_heads;      // (items of up to 64 rows: a head and 16 of them, or up to 8 of one sequence)
         if ((rc = dev_alloc(c, &c->rows_cnt, (size_t)c->rows_cnt_n))) return rc;
         HIP_TRY(c, hipMemset(c->rows_cnt, 0, (size_t)c->rows_cnt_n * sizeof(int)));
     }

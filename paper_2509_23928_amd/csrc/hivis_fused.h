@@ -29,8 +29,6 @@ namespace hivis {
 
 enum { PH_GEMM = 0, PH_ATTN = 1, PH_ATTN_MERGE = 2, PH_PREP = 3, PH_NORM_ROWS = 4, PH_ARGMAX = 5, PH_SAMPLE = 6 };
 enum { PRO_PLAIN = 0, PRO_RMS = 1 };
-// kernel variant of PH_ATTN (in the place of an epilogue): the cached rows with the non-temporal hint (rule: launch_phases)
-enum { ATTN_ONCE = 1 };
 enum { FEPI_ADD_TO = 1, FEPI_ADDVEC = 2, FEPI_QKV = 3, FEPI_SILU = 4, FEPI_LOGITS = 5,
        FEPI_QKV_TAB = 6,     // kernel variants only (never a Phase.epi): QKV whose rows are A + add_rows[token], see Phase.wb;
        FEPI_QKV_TAB4 = 7 };  // two staged rows (at most two sequences) / four staged rows (three or four sequences)
@@ -76,7 +74,6 @@ struct Phase {
     float* pm; int* pi;                            // LOGITS writes, ARGMAX reads: greedy candidates [row][workgroup]
     const float* u; int u_sseq, u_idx;             // SAMPLE: uniform number of row (seq, i) = u[seq*u_sseq + u_idx]; logits rows in A (stride lda)
     const uint4* next_W; int next_K, next_N;       // GEMM: weights of the next GEMM phase of the program (prefetch), or null
-    uint4* frag;                                   // ATTN with one key split, optional: the rows go out as A fragments of the next GEMM (K = ldy) instead of to Y
     // phases on row fragments (stream_kernel, see hivis_stream.h): Af the activation rows; ssq their sums of squares in nssq parts per
     // row (q|k|v and gate|up, whose epilogues apply 1/rms: at least one part; the others read none); F, fgain, ssq_out: the results as row
     // fragments, times a gain (optional), and the sums of squares per 16 columns.  ATTN: F instead of Y.
@@ -749,10 +746,11 @@ __device__ __forceinline__ AttnItem attn_item(const AttnShape& sh, int item) {
 // head and row of pair r of an item with ni rows, R pairs
 __device__ __forceinline__ void attn_pair(int r, int ni, int R, int& h, int& i) { h = 0; i = r; if (ni < R) { h = r / ni; i = r - h * ni; } }
 
-// Destination of attention rows: fp32 rows, or row fragments of the O projection (rows = rows of the pass)
-struct AttnOut { float* y; int ldo; uint4* frag; int rows; };
+// Destination of attention rows: fp32 rows, row fragments of the O projection (rows = rows of the pass), or A fragments of it (K = ldo)
+struct AttnOut { float* y; int ldo; uint4* frag; int rows; uint4* afrag = nullptr; };
 __device__ __forceinline__ void attn_store_pair(const AttnOut& o, int row, int col, float a, float b) {
-    if (o.frag) st_row_pair(o.frag, o.rows, row, col, a, b);
+    if (o.afrag) store_afrag2(o.afrag, o.ldo / 32, row, col, a, b);
+    else if (o.frag) st_row_pair(o.frag, o.rows, row, col, a, b);
     else st_wt_pair(&o.y[(size_t)row * o.ldo + col], a, b);
 }
 __device__ __forceinline__ float2 ld_agent2(const float* p) {
@@ -827,40 +825,10 @@ __device__ __forceinline__ void attn_merge_splits(const float* __restrict__ pbas
 template <int HD, int RM>
 __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, int* __restrict__ flag, const AttnShape& sh, int item_id, int split,
                                                int R, int ni, int head0, int i0, int sl, float* __restrict__ ws, int* __restrict__ cnt,
-                                               const AttnOut& dst, unsigned long long* marks, uint4* __restrict__ frag_out = nullptr) {
+                                               const AttnOut& dst, unsigned long long* marks) {
     constexpr int NW = FUSED_NW;
     lds_barrier();
     HIVIS_AMARK(4)
-    if (sh.nsplit == 1 && frag_out != nullptr) {
-        // the attention rows go straight out as activation fragments of the O projection (K = ldo; layout: hivis_gemm.h):
-        // 8 consecutive dims of one row per thread and trip
-        for (int idx = threadIdx.x; idx < R * (HD / 8); idx += FUSED_NT) {
-            const int r = idx / (HD / 8), c0 = (idx % (HD / 8)) * 8;
-            float mx = -INFINITY;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) mx = fmaxf(mx, mrg[(w * RM + r) * (HD + 2) + HD]);
-            float num[8], den = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) num[e] = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float mw = mrg[(w * RM + r) * (HD + 2) + HD];
-                if (mw != -INFINITY) {
-                    const float ew = __expf(mw - mx);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) num[e] += mrg[(w * RM + r) * (HD + 2) + c0 + e] * ew;
-                    den += mrg[(w * RM + r) * (HD + 2) + HD + 1] * ew;
-                }
-            }
-            float y[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) y[e] = num[e] / den;
-            const int hh = head0 + r / ni, i = i0 + r % ni;
-            store_afrag8(frag_out, dst.ldo / 32, sl * sh.m + i, hh * HD + c0, y, false);
-        }
-        lds_barrier();
-        return;
-    }
     if (sh.nsplit == 1) {
         // the whole key range was handled here: merge the NW partials and write the attention rows directly
         for (int idx = threadIdx.x; idx < R * (HD / 2); idx += FUSED_NT) {
@@ -931,7 +899,7 @@ __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, in
     lds_barrier();
 }
 
-// ---- attention on the matrix cores (half-precision caches) ---------------------------------------------
+// ---- attention on the matrix cores (half-precision caches) in the single-launch program; launches of their own: attn_split_kernel -------
 // Same work split as attn_wg_partial, but both contractions run as MFMA with the (head,row) pairs as the 16-wide
 // N dimension, so the queries live in registers instead of LDS and a 16-key tile costs a few dozen MFMA instead of
 // ~500 scalar FMAs:
@@ -958,12 +926,11 @@ __host__ __device__ constexpr size_t fused_attn_mfma_lds_floats(int hd, int nw, 
     return (tiles > mrg ? tiles : mrg) + 16;
 }
 
-template <int HD, int RM, bool ONCE = false>
+template <int HD, int RM>
 __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
                                              const int* __restrict__ base, const AttnShape& sh, int item_id, int split,
                                              float* __restrict__ lds, float* __restrict__ ws, int* __restrict__ cnt,
-                                             const AttnOut& dst, unsigned long long* marks = nullptr,
-                                             uint4* __restrict__ frag_out = nullptr) {
+                                             const AttnOut& dst, unsigned long long* marks = nullptr) {
     HIVIS_AMARK(0)
     static_assert(RM <= 16 && HD % 32 == 0, "rows are the 16-wide MFMA dimension");
     constexpr int NW = FUSED_NW;
@@ -1013,13 +980,8 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
     {                                                                                                              \
         _Pragma("unroll") for (int t = 0; t < VT; ++t) {                                                           \
             const size_t off_ = (size_t)min((kb_) + t * KPI + vks, nkeys - 1) * ROWB + vdc * 16;                   \
-            if constexpr (ONCE) {                                                                                  \
-                knext[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(kbase + off_));             \
-                vnext[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(vbase + off_));             \
-            } else {                                                                                               \
-                knext[t] = *reinterpret_cast<const u32x4_t*>(kbase + off_);                                        \
-                vnext[t] = *reinterpret_cast<const u32x4_t*>(vbase + off_);                                        \
-            }                                                                                                      \
+            knext[t] = *reinterpret_cast<const u32x4_t*>(kbase + off_);                                            \
+            vnext[t] = *reinterpret_cast<const u32x4_t*>(vbase + off_);                                            \
         }                                                                                                          \
     }
     if (k0 + 16 * wave < k1) HIVIS_ATTN_LOADS(k0 + 16 * wave)
@@ -1142,26 +1104,11 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
         }
         if (g == 0) { mr[HD] = mrun; mr[HD + 1] = lsum; }
     }
-    attn_wg_finish<HD, RM>(mrg, flag, sh, item_id, split, R, ni, kvh * group + h0, i0, sl, ws, cnt, dst, marks, frag_out);
+    attn_wg_finish<HD, RM>(mrg, flag, sh, item_id, split, R, ni, kvh * group + h0, i0, sl, ws, cnt, dst, marks);
 }
 
-// The MFMA attention as a kernel of its own, with all 16 MFMA columns holding real (head,row) pairs: passes with many
-// rows per sequence (prefill, tree verify) read every cached key half as often as with 8 pairs per work item.
+// the most (head,row) pairs of an item where a sequence has more than FUSED_RMAX rows: all 16 MFMA columns hold real ones
 constexpr int ATTN_ROWS_RM = 16;
-template <int HD>
-__global__ __launch_bounds__(FUSED_NT) void attn_rows_kernel(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
-                                                             const int* __restrict__ base, AttnShape sh, AttnOut out,
-                                                             uint4* __restrict__ frag_out) {
-    // frag_out (optional): the rows are written as A fragments of the next GEMM (K = out.ldo) instead of to `out`
-    extern __shared__ __align__(16) float attn_rows_lds[];
-    // Work items are numbered row block fastest, and workgroup b runs on XCD b % 8: the row blocks of one head would land
-    // on different XCDs and each fetch the head's cached K and V rows from memory (61-row pass: 86 MB per layer for 23 MB
-    // of cache rows).  Where the heads divide by 8, XCD x takes the heads x, x + 8, ... with all their row blocks.
-    int item = blockIdx.x;
-    const int nr = sh.n_rblk, ngrp = (int)gridDim.x / nr;
-    if (nr > 1 && (ngrp & 7) == 0 && ngrp * nr == (int)gridDim.x) { const int x = item & 7, slot = item >> 3; item = (x + 8 * (slot / nr)) * nr + slot % nr; }
-    attn_wg_mfma<HD, ATTN_ROWS_RM>(q, kc, vc, base, sh, item, 0, attn_rows_lds, nullptr, nullptr, out, nullptr, frag_out);
-}
 
 // Attention of long row ranges (prefill): the published flash-attention work split.  A workgroup of NW wavefronts owns
 // 16 NW consecutive rows of ONE query head, 16 per wavefront, and walks the keys in tiles of 32 that the whole workgroup
@@ -1543,8 +1490,8 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
             if (xcd_map) { const int j = w >> 3, q = div_pow2(j, nsp); item = (w & 7) + 8 * q; split = j - q * nsp; if (item >= ph.att_items) continue; }
             else { item = div_pow2(w, nsp); split = w - item * nsp; }
             if constexpr (std::is_same<KT, f16_t>::value) {
-                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX, TYPE == PH_ATTN && EPI == ATTN_ONCE>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
-                else attn_wg_mfma<64, FUSED_RMAX, TYPE == PH_ATTN && EPI == ATTN_ONCE>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2, ph.frag);
+                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2);
+                else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2);
             } else {
                 // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
                 const bool one = ph.att.gh * ph.att.mi == 1;

@@ -43,6 +43,12 @@ __device__ __forceinline__ void store_afrag4(uint4* __restrict__ frag, int kblks
     at[128] = lo;
 }
 
+// 2 consecutive values of row `row` at k (even)
+__device__ __forceinline__ void store_afrag2(uint4* __restrict__ frag, int kblks, int row, int k, float a, float b) {
+    uint32_t* at = reinterpret_cast<uint32_t*>(frag + afrag_at(kblks, row, k)) + ((k >> 1) & 3);
+    f32_to_bf16x2_hilo(a, b, at[0], at[256]);
+}
+
 // rows of fp32 -> fragments; rows >= M of the last row tile become zeros
 __global__ void pack_afrag_kernel(const float* __restrict__ A, int lda, int M, int kblks, uint4* __restrict__ out) {
     const size_t total = (size_t)((M + 15) / 16) * 16 * kblks * 4;        // one thread per chunk of 8 values

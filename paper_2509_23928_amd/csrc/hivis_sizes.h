@@ -134,6 +134,14 @@ inline AttnCut attn_cut(int nseq, int m, int hq, int hkv, bool alone) {
 }
 // key splits of a launch over `keys` cached rows, of at most `most`
 inline int attn_splits(int keys, int most, int keys_per_split) { return std::max(1, std::min(most, (keys + keys_per_split - 1) / keys_per_split)); }
+// The same for half-precision caches, whose kernel takes 128 keys at a time (attn_split_kernel): as few blocks per workgroup as `most` splits allow, and no more
+// splits than that needs.  A block more costs 2 us, a split more 0.1: 32 heads over 650 keys in 4 splits of two blocks 11.0 us, in 6 of one 10.6; one head group over
+// 130..190 keys in one split 7.7, in two 7.2; but 28 heads over 1130 keys (8 splits at most: two blocks) in 6 splits 12.8, in 8 13.4.
+constexpr int ATTN_BLOCK_KEYS = 128;
+inline int attn_block_splits(int keys, int most) {
+    const int per = (keys + ATTN_BLOCK_KEYS * most - 1) / (ATTN_BLOCK_KEYS * most) * ATTN_BLOCK_KEYS;
+    return std::max(1, std::min(most, (keys + per - 1) / per));
+}
 // Whether the rows of an fp32 pass over `keys` cached rows of each of nseq sequences are items of their own.  The vector ALU works on an
 // item's rows one after the other, so that sharing an item costs a row about what 230 keys of 64 values cost.  Alone, rows leave fewer CUs
 // to split the keys over, and the items of a key head, dealt to all eight XCDs, fetch its cached rows up to eight times (a megabyte costs
