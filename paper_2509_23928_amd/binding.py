@@ -313,7 +313,7 @@ class Hivis:
 
     def tree_get_logits(self):
         k, depth, _ = self.tree_shape
-        out = np.zeros((1 + (depth - 1) * k, self.cfg.vocab), np.float32)
+        out = np.empty((1 + (depth - 1) * k, self.cfg.vocab), np.float32)
         self._check(self.lib.hivis_tree_get_logits(self.ctx, _ptr(out)))
         return out
 
@@ -321,13 +321,13 @@ class Hivis:
     def get_logits(self, which):
         V = self.cfg.vocab
         shape = {0: (self.B, self.K + 1, V), 1: (self.K, self.B, V), 2: (self.B, V)}[which]
-        out = np.zeros(shape, np.float32)
+        out = np.empty(shape, np.float32)
         self._check(self.lib.hivis_get_logits(self.ctx, which, _ptr(out)))
         return out
 
     def get_hidden(self, which):
         shape = {0: (self.B, self.K + 1, self.cfg.d), 1: (self.B, self.cfg.d)}[which]
-        out = np.zeros(shape, np.float32)
+        out = np.empty(shape, np.float32)
         self._check(self.lib.hivis_get_hidden(self.ctx, which, _ptr(out)))
         return out
 
