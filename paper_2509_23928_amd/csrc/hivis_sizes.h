@@ -34,11 +34,13 @@ inline int frag_buffer(const PrefillSizes& s, int M, int K) {
     return n <= s.frag ? 1 : n <= s.frag2 ? 2 : 0;
 }
 
-// Column tiles per wavefront and K slices of a tall GEMM: the pair with the least estimated time.  A workgroup (one per CU)
-// takes 0.066 us per K block and column tile when it runs alone and about 1.3 times that when all CUs work (the card's
-// power limit), plus 7 us to start and finish; slices cost their partial sums, written once and read once.  (Measured at 640 rows,
-// K = 4096: 22016 columns 430 tiles 181 us / 495 tiles 172 us / 575 tiles, a third round, 205 us; 4096 columns as 80 tiles 75 us,
-// as 3 x 80 tiles 39 us.)  only: 6..8, that many column tiles (0: any).
+// Column tiles per wavefront and K slices of a tall GEMM: the pair with the least estimated time.  One workgroup per CU; a round of them takes 0.14 us
+// per K block (the rows' reads, the barrier) plus 0.048 per K block and column tile, and 4 to start and finish.  What all CUs together
+// switch comes on top (the card's power limit): 0.008 us per K block and column tile, 3 tiles more for the rows, times the share of a round that the tiles fill.
+// Slices cost their partial sums, written once and read once.  Fitted to all forms and slices of 15 products (widths 2048..5120, K to 18944) at 18 row
+// counts from 70 to 4000, for the choice: what it picks is 0.1 % over the best of them on average, 6 % at most.  (An estimate in proportion to
+// the column tiles, 0.066 us each, took narrow tiles for large products: 3008 rows of 4096 on 22016 columns 798 us with 6, 767 with 8;
+// 4096 columns of 11008 377 with 7, 369 with 8 in two slices; 0.7 % over the best on average, 18 % at most.)  only: 6..8, that many column tiles (0: any).
 constexpr int TALL_ROWS = 128;
 struct TallPlan { int cw, ksplit; double us; };
 inline TallPlan tall_plan(int num_cu, int M, int kblks, int ntiles, bool may_split, int only = 0) {
@@ -49,8 +51,8 @@ inline TallPlan tall_plan(int num_cu, int M, int kblks, int ntiles, bool may_spl
             const int kper = (kblks + S - 1) / S;
             if (S > 1 && ((S - 1) * kper >= kblks || kper < 8)) continue;        // no empty slice, no tiny ones
             const double tiles = (double)nrow * ((ntiles + 2 * cw - 1) / (2 * cw)) * S;
-            const double rounds = std::ceil(tiles / num_cu), fill = tiles / (rounds * num_cu);
-            double us = rounds * (kper * 0.066 * cw * (0.8 + 0.5 * fill) + 7.0);
+            const double rounds = std::ceil(tiles / num_cu);
+            double us = rounds * (kper * (0.14 + 0.048 * cw) + 4.0) + tiles / num_cu * kper * 0.008 * (cw + 3);
             if (S > 1) us += 2.0 * S * M * ntiles * 16 * 4.0 / 4.0e6;
             if (us < best.us - 1e-9) best = {cw, S, us};
         }
