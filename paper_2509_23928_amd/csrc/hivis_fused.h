@@ -1116,14 +1116,17 @@ constexpr int ATTN_ROWS_RM = 16;
 // maximum / sum / accumulator, and nothing is merged across wavefronts.  Operands are hi/lo pairs and each product is three
 // MFMA, as in attn_wg_mfma; the two 16-key score tiles of a trip lie side by side in the K dimension of the value product
 // (lane group g: keys 4 g .. + 3 of each, V^T read in that order), so that it runs as 16x16x32 MFMA as well.
-// Bound by the vector instructions and LDS latencies of a trip (scaling the sums, maximum across lanes, splitting the
-// probabilities), not by the MFMAs or the cache's rows: 32 keys per trip halve what a trip costs per key, and tiles that every row sees
-// skip the comparisons.
-// Per layer, 16-key trips and 128 rows per workgroup everywhere before -> now: 640 rows x 32 heads 46 -> 35 us, 3008 x 32
-// 328 -> 275, 1120 x 28 heads of 4 key heads 77 -> 56, two sequences of 378 x 32 heads of 64 22 -> 16.  Slower (485 us at 3008): 32 rows per
-// wavefront, tiles straight to LDS in a ring of four (too many registers; skipping the loads altogether changed nothing).
+// Bound by a trip's LDS reads (every wavefront reads the whole tile: 256 KB of 8 wavefronts, 1 us of the 1.6 that a CU takes) and vector instructions, not
+// by the MFMAs or the cache's rows: 32 keys per trip halve what a trip costs per key, tiles that every row sees skip the comparisons, and a
+// row's sums are scaled to a new reference (maximum across its lanes, alpha) only when a score outgrows the last one by ATTN_SHARED_GROWTH powers of two:
+// until then its weights are at most 2^11, which the hi/lo halves hold as exactly as those below 1.
+// Per layer, 16-key trips and 128 rows per workgroup everywhere -> 32-key trips -> scaled when needed: 640 rows x 32 heads 46 -> 35 -> 31.6 us,
+// 3008 x 32 328 -> 284 -> 242, two sequences of 378 x 32 heads of 64 22 -> 16 -> 14.7; 1120 x 28 heads of 4 key heads 77 -> 56 before the last.  Slower (485 us at
+// 3008): 32 rows per wavefront, tiles straight to LDS in a ring of four (too many registers; skipping the loads altogether changed nothing).
+// The same within noise: wave priority raised around the MFMAs.
 // Items: heads vary fastest, row blocks run from the last (most keys) to the first.
 constexpr int ATTN_SHARED_KEYS = 32;
+constexpr float ATTN_SHARED_GROWTH = 11.f;
 __host__ __device__ constexpr size_t attn_shared_lds_bytes(int hd) { return 2 * ATTN_SHARED_KEYS * ((size_t)hd * 4 + 16 + (size_t)hd * 4 + 32); }
 
 template <int HD, int NW>
@@ -1136,6 +1139,7 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_rows_shared_kernel(const
     constexpr int VSTRIDE = ROWB + 32, KSTRIDE = ROWB + 16;
     constexpr int KTB = TK * KSTRIDE, BUFB = KTB + TK * VSTRIDE;
     constexpr int LK = NT / NCH, PER = TK / LK;                      // keys the workgroup loads per instruction; instructions per tile
+    constexpr float LOG2E = 1.44269504f;
     constexpr int GB = NW == 8 ? 2 : 4;                              // 16-dim blocks whose products are interleaved
     static_assert(LK * NCH == NT && PER * LK == TK, "a tile is loaded by whole instructions of the workgroup");
     char* bufs = reinterpret_cast<char*>(attn_shared_lds);          // [2][K tile | V tile]
@@ -1190,7 +1194,7 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_rows_shared_kernel(const
     }
     const int qpos = valid ? pos0 + i0 + r : 0x7FFFFFFF;
 
-    float mrun = -INFINITY, lrun = 0.f;
+    float mrun = -INFINITY, mref = 0.f, lrun = 0.f;                 // the row's reference, in powers of two (the same in its four lanes), and 0 instead of -inf
     f32x4_t acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -1240,23 +1244,26 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_rows_shared_kernel(const
         float tmax = sv[0];
 #pragma unroll
         for (int e = 1; e < 8; ++e) tmax = fmaxf(tmax, sv[e]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-        const float mnew = fmaxf(mrun, tmax);
-        const float mref = (mnew == -INFINITY) ? 0.f : mnew;
-        const float alpha = __expf(mrun - mref);
+        if (__any(tmax * LOG2E > mrun + ATTN_SHARED_GROWTH)) {                   // uniform: some row's scores outgrow its reference
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+            tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+            const float mnew = fmaxf(mrun, tmax * LOG2E);
+            mref = (mnew == -INFINITY) ? 0.f : mnew;
+            const float alpha = __builtin_amdgcn_exp2f(mrun - mref);
+            mrun = mnew;
+            lrun *= alpha;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[nb] *= alpha;
+        }
         float psum = 0.f;
         f16x8_t pbh, pbl;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float p = __expf(sv[e] - mref);
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[e], LOG2E, -mref));
             psum += p;
             pbh[e] = (_Float16)p; pbl[e] = (_Float16)(p - (float)pbh[e]);
         }
-        mrun = mnew;
-        lrun = lrun * alpha + psum;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[nb] *= alpha;
+        lrun += psum;
 #pragma unroll
         for (int n0 = 0; n0 < NB; n0 += GB) {
             f16x8_t v[GB][2];                                        // hi, lo: keys 4 g + 0..3 of both 16-key halves (transposing reads, see attn_wg_mfma)

@@ -70,6 +70,29 @@ def test_shared_attention(kw):
     check_prefill(cfg_of(**kw))
 
 
+# query weights times 1, 16, 32, 128: over the key tiles a row's largest score grows by up to 0.7, 11, 22, 86 powers of two, below and above the growth (11) at
+# which the shared-tile attention scales its sums.  A score s carries relative errors like any other result, and its weight that error times |s|:
+# REL, and REL for each unit of the largest score (0.65 per factor of the weights).
+@pytest.mark.parametrize("times", [1, 16, 32, 128])
+@pytest.mark.parametrize("kw", [dict(n_vis=480, n_text=32, batch=1), dict(n_vis=400, n_text=33, batch=4)], ids=["64rows", "128rows"])
+def test_shared_attention_of_growing_scores(kw, times):
+    from paper_2509_23928_amd import Hivis
+    cfg = cfg_of(n_q_heads=32, n_kv_heads=8, head_dim=128, **kw)
+    w = synth.make_weights(cfg, seed=0)
+    for layer in w["layers"] + [w["draft_layer"]]:
+        layer["wq"] = layer["wq"] * np.float32(times)
+    vis, ids = synth.make_prompt(cfg, seed=0)
+    hv = Hivis(cfg, w)
+    hv.prefill(vis, ids)
+    logits, hidden = hv.get_logits(2), hv.get_hidden(1)
+    hv.close()
+    for b in range(cfg.batch):
+        o = HivisOracle(cfg, w)
+        _, ref = o.prefill(vis[b], ids[b])
+        assert rel(logits[b], ref) <= REL * (1 + 0.65 * times)
+        assert rel(hidden[b], o.f_next) <= REL * (1 + 0.65 * times)
+
+
 @pytest.mark.parametrize("n_text", [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17])
 @pytest.mark.parametrize("heads", [(4, 4, 64), (6, 2, 64), (5, 1, 128)], ids=str)
 def test_fp32_rows_of_an_attention_item(n_text, heads):
