@@ -342,13 +342,18 @@ int attention(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, const int*
     const int group = g.n_q_heads / g.n_kv_heads;
     if (m >= ATT_RMAX) { sh.mi = ATT_RMAX; sh.gh = 1; }
     else { sh.mi = m; sh.gh = std::max(1, std::min(group, ATT_RMAX / m)); }
-    sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
     sh.seq0 = seq0; sh.offset = offset; sh.maxL = kv.maxL; sh.ldq = ldq; sh.qrows = qrows; sh.nwaves = 4; sh.tmask = tmask;
-    const int items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
-    // enough workgroups to occupy the chip, at most one 64-key tile per wavefront slot
+    // enough workgroups to occupy the chip, at most one 64-key tile per wavefront slot; and half as many (head,row) pairs per item, again and again,
+    // as long as that leaves one workgroup to a CU at most: an item's rows go one after the other (32 rows x 4 heads of 64 over 100 keys, us: 8 items of 16 rows
+    // 24.8 and 5.7 to merge, 128 items of one row 6.1 and under 4).  What an item reads of the cache comes from L2; beyond a workgroup per CU nothing is idle.
     const int tiles = (max_keys + 63) / 64;
-    int nsplit = std::max(1, std::min((2 * c->num_cu + items - 1) / items, (tiles + 3) / 4));
-    nsplit = std::min(nsplit, 16);
+    int items = 0, nsplit = 0;
+    for (;; sh.gh > 1 ? sh.gh = (sh.gh + 1) / 2 : sh.mi = (sh.mi + 1) / 2) {
+        sh.n_hblk = (group + sh.gh - 1) / sh.gh; sh.n_rblk = (m + sh.mi - 1) / sh.mi;
+        items = nseq * g.n_kv_heads * sh.n_hblk * sh.n_rblk;
+        nsplit = std::max(1, std::min({(2 * c->num_cu + items - 1) / items, (tiles + 3) / 4, 16}));
+        if (sh.mi * sh.gh == 1 || 2 * items * nsplit > c->num_cu) break;
+    }
     sh.nsplit = nsplit;
     const size_t need = (size_t)items * nsplit * 4 * ATT_RMAX * (g.head_dim + 2);
     if (need > c->attn_ws_floats) return fail(c, HIVIS_EINVAL, "attention workspace too small (%zu > %zu)", need, c->attn_ws_floats);

@@ -102,6 +102,13 @@ def test_fp32_rows_of_an_attention_item(n_text, heads):
     check_prefill(cfg_of(dtype="f32", n_vis=0, n_text=n_text, d=128, n_q_heads=q, n_kv_heads=kv, head_dim=hd, ffn=176), tol=1e-5)
 
 
+# fp32 passes of many rows: 16, 8, 4, 2 and one (head,row) pairs per item, halved heads first, from even and odd counts, with one and with several key splits
+@pytest.mark.parametrize("hq,hkv,hd,n_text", [(80, 80, 64, 32), (64, 64, 64, 31), (32, 32, 64, 32), (16, 16, 128, 32), (4, 4, 64, 32), (64, 8, 64, 4), (80, 40, 64, 5), (12, 4, 64, 11),
+                                              (8, 8, 64, 333), (48, 16, 128, 290)], ids=str)
+def test_fp32_rows_halved(hq, hkv, hd, n_text):
+    check_prefill(cfg_of(dtype="f32", n_vis=0, n_text=n_text, d=128, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, ffn=176), tol=1e-5)
+
+
 def test_room_for_slices_grows_once(monkeypatch):
     """Without a reserve the first product that is cut into K slices allocates the room, for every row count of the context: the
     prompts after it, more and fewer rows, find it there."""
