@@ -474,6 +474,20 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
     return fail(c, HIVIS_EINVAL, "attention on the matrix cores needs half-precision caches");
 }
 
+void launch_attn_f32(hivis_ctx* c, const Phase& ph, int rows, unsigned long long* prof2, hipEvent_t ev0, hipEvent_t ev1) {
+    AttnF32Args a{};
+    a.q = ph.A; a.kc = (const float*)ph.kc; a.vc = (const float*)ph.vc; a.base = ph.base; a.ws = ph.ws; a.cnt = ph.cnt; a.y = ph.Y; a.rows_out = ph.F;
+    a.ldo = ph.ldy; a.rows = rows; a.items = ph.att_items; a.sh = ph.att; a.prof2 = prof2;
+    a.by_rblk = FastDiv::by(a.sh.n_rblk); a.by_hblk = FastDiv::by(a.sh.n_hblk); a.by_hkv = FastDiv::by(a.sh.Hkv);
+    const dim3 grid = (a.sh.flags & 2) ? dim3(8, a.sh.nsplit, (a.items + 7) / 8) : dim3(a.items, a.sh.nsplit);
+    const bool one = a.sh.gh * a.sh.mi == 1;         // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
+#define HIVIS_ATTN_F32(HD_, RC_) hipExtLaunchKernelGGL((attn_f32_kernel<HD_, RC_>), grid, dim3(FUSED_NT), 0, c->stream, ev0, ev1, 0, a)
+    if (c->cfg.head_dim == 128) { if (one) HIVIS_ATTN_F32(128, 1); else HIVIS_ATTN_F32(128, FUSED_RMAX); }
+    else if (one) HIVIS_ATTN_F32(64, 1);
+    else HIVIS_ATTN_F32(64, FUSED_RMAX);
+#undef HIVIS_ATTN_F32
+}
+
 // One decoder layer on M = nseq*m rows.  h: residual stream [M][d] (in place).  `pending` (may be null) is a delta
 // from the previous layer that has not been added to h yet; on return *pending_out is this layer's MLP output, still
 // to be added by the caller (the next layer's first norm, or a final norm/add, fuses that addition).
@@ -1083,7 +1097,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             }
             break;
         case PH_ATTN:
-            if constexpr (std::is_same<WT, float>::value) HIVIS_LAUNCH(PH_ATTN, 0);
+            if constexpr (std::is_same<WT, float>::value) launch_attn_f32(c, ph, pp.M, ppl.prof2, kev0, kev1);
             else if (int rc = launch_attn_split(c, ph.att, ph.att_items, FUSED_RMAX, ph.A, ph.kc, ph.vc, ph.base, AttnOut{ph.Y, ph.ldy, ph.F, pp.M}, nullptr, ph.ws, ph.cnt,
                                                 once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1, ppl.prof3, kev0, kev1)) return rc;
             break;
@@ -1255,7 +1269,7 @@ int fused_setup(hivis_ctx* c) {
     if constexpr (std::is_same<WT, float>::value) {
         const void* ks[] = {(const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV, true>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB, true>,
                             (const void*)phase_kernel<WT, PH_GEMM, FEPI_QKV_TAB4, true>, (const void*)phase_kernel<WT, PH_GEMM, FEPI_SILU, true>,
-                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, true>, (const void*)phase_kernel<WT, PH_ATTN, 0, false>};
+                            (const void*)phase_kernel<WT, PH_GEMM, FEPI_LOGITS, true>};
         for (const void* k : ks) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_limit));
     }
     if constexpr (std::is_same<WT, bf16_t>::value) {

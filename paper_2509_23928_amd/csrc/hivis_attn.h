@@ -303,4 +303,32 @@ __global__ __launch_bounds__(FUSED_NT) void attn_split_kernel(AttnArgs a) {
     }
 }
 
+// One (item, key split) of an fp32 pass per workgroup (attn_wg_partial), launched by itself: its arguments come in one batch of scalar loads and what follows from the
+// workgroup's index without a division.  Short passes are a chain of such latencies: 4 heads
+// of 64 over 100..180 keys, one row 5.2 -> 4.0 us, five 6.1 -> 4.9 (as a phase of the general launch before).
+struct AttnF32Args {
+    const float* q; const float* kc; const float* vc; const int* base; float* ws; int* cnt; float* y; uint4* rows_out;
+    int ldo, rows, items;
+    FastDiv by_rblk, by_hblk, by_hkv;
+    AttnShape sh;
+    unsigned long long* prof2;
+};
+
+template <int HD, int RC>
+__global__ __launch_bounds__(FUSED_NT) void attn_f32_kernel(AttnF32Args a) {
+    __shared__ __align__(16) float lds[FUSED_RMAX * HD + FUSED_NW * FUSED_RMAX * 16 + FUSED_NW * FUSED_RMAX * (HD + 2)];
+    asm volatile("" :: "s"(a.q), "s"(a.kc), "s"(a.vc), "s"(a.base), "s"(a.ws), "s"(a.cnt), "s"(a.y), "s"(a.rows_out), "s"(a.ldo), "s"(a.rows), "s"(a.items), "s"(a.by_rblk.mul),
+                      "s"(a.by_hblk.mul), "s"(a.by_hkv.mul));
+    asm volatile("" :: "s"(a.sh.Hq), "s"(a.sh.Hkv), "s"(a.sh.m), "s"(a.sh.gh), "s"(a.sh.mi), "s"(a.sh.n_hblk), "s"(a.sh.n_rblk), "s"(a.sh.seq0), "s"(a.sh.offset), "s"(a.sh.maxL),
+                      "s"(a.sh.nsplit), "s"(a.sh.ldq), "s"(a.sh.qrows), "s"(a.sh.flags), "s"(a.sh.nbase), "s"(a.prof2));
+    const auto scalar = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    // (grids as in attn_split_kernel)
+    const bool xcd_map = (a.sh.flags & 2) != 0;
+    const int split = blockIdx.y, item = scalar(xcd_map ? blockIdx.x + 8 * blockIdx.z : blockIdx.x);
+    if (item >= a.items) return;
+    const int i1 = scalar(a.by_rblk(item)), i2 = scalar(a.by_hblk(i1)), sl = scalar(a.by_hkv(i2));
+    const AttnItem it = {item - i1 * a.sh.n_rblk, i1 - i2 * a.sh.n_hblk, i2 - sl * a.sh.Hkv, sl, a.sh.n_hblk == 1 && a.sh.Hq == a.sh.Hkv ? 1 : a.sh.Hq / a.sh.Hkv};
+    attn_wg_partial<float, HD, FUSED_RMAX, RC>(a.q, a.kc, a.vc, a.base, a.sh, it, item, split, lds, a.ws, a.cnt, AttnOut{a.y, a.ldo, a.rows_out, a.rows}, a.prof2);
+}
+
 }  // namespace hivis

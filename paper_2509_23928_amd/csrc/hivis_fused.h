@@ -1304,7 +1304,7 @@ __global__ __launch_bounds__(64 * NW, NW / 2) void attn_rows_shared_kernel(const
 // cross-lane step of an unrolled row (8.4 -> 6.7 us; always working on 8 rows instead of testing: 10.9 us for 5).
 template <typename KT, int HD, int RM, int RC>
 __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, const KT* __restrict__ kc, const KT* __restrict__ vc,
-                                                const int* __restrict__ base, const AttnShape& sh, int item_id, int split,
+                                                const int* __restrict__ base, const AttnShape& sh, const AttnItem& it, int item_id, int split,
                                                 float* __restrict__ lds, float* __restrict__ ws, int* __restrict__ cnt,
                                                 const AttnOut& dst, unsigned long long* marks = nullptr) {
     HIVIS_AMARK(0)
@@ -1321,7 +1321,6 @@ __device__ __forceinline__ void attn_wg_partial(const float* __restrict__ q, con
     float* pw_all = qs + RM * HD;                  // [NW][RM][16] probabilities of the wavefront's 16 keys
     float* mrg = pw_all + NW * RM * 16;            // [NW][RM][HD + 2] per-wavefront partials
 
-    const AttnItem it = attn_item(sh, item_id);
     const int rblk = it.rblk, hblk = it.hblk, kvh = it.kvh, sl = it.sl, group = it.group;
     const int seq = sh.seq0 + sl;
     const int h0 = hblk * sh.gh, nh = min(sh.gh, group - h0);
@@ -1502,7 +1501,7 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
             } else {
                 // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
                 const bool one = ph.att.gh * ph.att.mi == 1;
-#define HIVIS_ATTN_F32(HD_, RC_) attn_wg_partial<KT, HD_, FUSED_RMAX, RC_>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2)
+#define HIVIS_ATTN_F32(HD_, RC_) attn_wg_partial<KT, HD_, FUSED_RMAX, RC_>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, attn_item(ph.att, item), item, split, lds, ph.ws, ph.cnt, dst, pp.prof2)
                 if (pp.hd == 128) { if (one) HIVIS_ATTN_F32(128, 1); else HIVIS_ATTN_F32(128, FUSED_RMAX); }
                 else if (one) HIVIS_ATTN_F32(64, 1);
                 else HIVIS_ATTN_F32(64, FUSED_RMAX);
