@@ -15,7 +15,7 @@
 // so that a K block is M * 128 contiguous bytes, whatever M is, and a part of it M * 64 (with a row's parts side by side every load of the
 // 16-row form touched half of twice as many cache lines: 12 rows, 2048 wide, down 16.2 -> 14.1 us, O 7.4 -> 6.6).
 // Not for more than 16 rows: every workgroup reads all fragments, 717 MB through the L2s for the down projection of 61 rows, 53 us where the
-// K-sliced GEMM and its row kernel take 32.
+// K-sliced GEMM (gemm_wide_kernel) and its row kernel take 29.
 #pragma once
 #include "hivis_fused.h"
 

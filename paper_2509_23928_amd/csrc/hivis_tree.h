@@ -58,15 +58,45 @@ __device__ __forceinline__ int rank_of(const float* v, const int* i, int n, int 
     }
     return rank;
 }
-// ... entries whose index is their place
-__device__ __forceinline__ int rank_of(const float* v, int n, float mv, int mi) {
+// ... of consecutive entries, sixteen per trip in 16-byte reads: the arrays are 16-byte aligned and have room for n rounded up to sixteen
+__device__ __forceinline__ int rank_of(const float* v, const int* i, int n, float mv, int mi) {
     int rank = 0;
-    for (int c = 0; c < n; c += 8) {
-        float vv[8];
+    for (int c = 0; c < n; c += 16) {
+        float4 vv[4]; int4 ii[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) vv[u] = v[min(c + u, n - 1)];
+        for (int u = 0; u < 4; ++u) { vv[u] = *reinterpret_cast<const float4*>(v + c + 4 * u); ii[u] = *reinterpret_cast<const int4*>(i + c + 4 * u); }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) rank += (c + u < n && before(vv[u], c + u, mv, mi)) ? 1 : 0;
+        for (int u = 0; u < 4; ++u) {
+            const float x[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
+            const int y[4] = {ii[u].x, ii[u].y, ii[u].z, ii[u].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rank += (c + 4 * u + e < n && before(x[e], y[e], mv, mi)) ? 1 : 0;
+        }
+    }
+    return rank;
+}
+// ... entries whose index is their place, for lanes whose mi rise by one from lane to lane (alignment and room as above).  Bound by the comparisons: entries before
+// every lane's place or behind every lane's take one (510 entries, one workgroup ranking them all: 28.7 us with the order's three, 13.4 now).
+__device__ __forceinline__ int rank_of(const float* v, int n, float mv, int mi) {
+    const int first = __builtin_amdgcn_readfirstlane(mi);
+    int rank = 0;
+    for (int c = 0; c < n; c += 16) {
+        float4 vv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) vv[u] = *reinterpret_cast<const float4*>(v + c + 4 * u);
+        float x[16];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { x[4 * u] = vv[u].x; x[4 * u + 1] = vv[u].y; x[4 * u + 2] = vv[u].z; x[4 * u + 3] = vv[u].w; }
+        if (c + 16 <= first) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) rank += x[e] >= mv ? 1 : 0;
+        } else if (c >= first + 64 && c + 16 <= n) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) rank += x[e] > mv ? 1 : 0;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) rank += (c + e < n && before(x[e], c + e, mv, mi)) ? 1 : 0;
+        }
     }
     return rank;
 }
@@ -76,8 +106,10 @@ __global__ __launch_bounds__(TOPK_NT) void tree_topk_part_kernel(const float* __
                                                                  float* __restrict__ seg_ms) {
     constexpr int NWV = TOPK_NT / 64, MAXS = NWV * TREE_MAX_TOPK * TOPK_PER;      // survivors: at most k lanes per wavefront
     constexpr int NONE = 0x7FFFFFFF;
-    __shared__ float smf[NWV], lv[TOPK_NT], thr_v[NWV], sv[MAXS];
-    __shared__ int li[TOPK_NT], thr_i[NWV], si[MAXS], cnt;
+    __shared__ float smf[NWV], thr_v[NWV];
+    __shared__ __align__(16) float lv[TOPK_NT], sv[MAXS];
+    __shared__ __align__(16) int li[TOPK_NT], si[MAXS];
+    __shared__ int thr_i[NWV], cnt;
     const int r = blockIdx.x, seg = blockIdx.y, nseg = gridDim.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float* x = logits + (size_t)r * V;
@@ -100,7 +132,7 @@ __global__ __launch_bounds__(TOPK_NT) void tree_topk_part_kernel(const float* __
 #pragma unroll
     for (int e = 0; e < TOPK_PER; ++e) sum += j0 + TOPK_NT * e < V ? expf(v[e] - m) : 0.f;
     sum = wave_sum(sum);
-    const int rank = rank_of(lv + wave * 64, li + wave * 64, 64, 1, bv, bi);
+    const int rank = rank_of(lv + wave * 64, li + wave * 64, 64, bv, bi);
     if (rank == k - 1 && bi != NONE) { thr_v[wave] = bv; thr_i[wave] = bi; }
     __syncthreads();
     if (lane == 0) smf[wave] = sum;
@@ -120,7 +152,7 @@ __global__ __launch_bounds__(TOPK_NT) void tree_topk_part_kernel(const float* __
     const int live = cnt;
     for (int i = threadIdx.x; i < live; i += TOPK_NT) {
         const float mv = sv[i]; const int mi = si[i];
-        const int rk = rank_of(sv, si, live, 1, mv, mi);
+        const int rk = rank_of(sv, si, live, mv, mi);
         if (rk < k) { cand_v[o + rk] = mv; cand_i[o + rk] = mi; }
     }
     // a segment with fewer than k elements pads with (-inf, INT_MAX)
@@ -136,8 +168,10 @@ __global__ __launch_bounds__(CHILD_NT) void tree_children_kernel(const float* __
     // all of them): at most k * k
     constexpr int MAXS = TREE_MAX_TOPK * TREE_MAX_TOPK, NONE = 0x7FFFFFFF;
     extern __shared__ float child_lds[];                     // [nseg k] values, [nseg k] indices
-    __shared__ float sv[MAXS], thr_v, lz;
-    __shared__ int si[MAXS], thr_i, cnt;
+    __shared__ __align__(16) float sv[MAXS];
+    __shared__ __align__(16) int si[MAXS];
+    __shared__ float thr_v, lz;
+    __shared__ int thr_i, cnt;
     const int r = blockIdx.x, n = nseg * k, lane = threadIdx.x & 63;
     float* cv = child_lds; int* ci = reinterpret_cast<int*>(child_lds + n);
     const float* ms = seg_ms + (size_t)r * nseg * 2;
@@ -172,7 +206,7 @@ __global__ __launch_bounds__(CHILD_NT) void tree_children_kernel(const float* __
     const int live = min(cnt, MAXS);
     for (int i = threadIdx.x; i < live; i += CHILD_NT) {
         const float vi = sv[i]; const int ii = si[i];
-        const int rank = rank_of(sv, si, live, 1, vi, ii);
+        const int rank = rank_of(sv, si, live, vi, ii);
         if (rank < k) {
             const int node = first + r * k + rank;
             t.pool_tok[node] = ii; t.pool_par[node] = parent; t.pool_depth[node] = depth; t.pool_hid[node] = hid_row0 + r;
@@ -191,30 +225,41 @@ template <typename WT>
 __global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, int n_prev, int level, TreeDev t, const float* __restrict__ H,
                                                           const WT* __restrict__ table, float* __restrict__ cat, int32_t* __restrict__ tok, int d,
                                                           uint4* __restrict__ frag) {
-    __shared__ float s[256];
+    __shared__ __align__(16) float s[256];
     __shared__ int pick[2];                  // hidden row, token
     const int i = threadIdx.x, want = blockIdx.x;
-    s[i] = i < n ? t.pool_score[lo + i] : -INFINITY;
+    // (what a picked node needs is requested by every node's thread before the ranks are known)
+    const int node = lo + min(i, n - 1);
+    const float si = t.pool_score[node];
+    const int parent = t.pool_par[node], hid = t.pool_hid[node], token = t.pool_tok[node];
+    const int pslot = t.pool_slot[max(parent, 0)];
+    const unsigned long long above = t.dmask[max(pslot, 0)];
+    s[i] = i < n ? si : -INFINITY;
     if (i == 0) { pick[0] = 0; pick[1] = 0; }          // (stays so only with NaN scores, where ranks are no permutation)
     __syncthreads();
     if (i < n) {
-        const float si = s[i];
         const int rank = rank_of(s, n, si, i);
         if (rank == want) {
-            const int slot = n_prev + rank, node = lo + i;
+            const int slot = n_prev + rank;
             t.expand[(level - 1) * k + rank] = node;
             t.pool_slot[node] = slot;
-            const int parent = t.pool_par[node];      // expanded at the level before (or the root): its row and mask already exist
-            t.dmask[slot] = (parent >= 0 ? t.dmask[t.pool_slot[parent]] : 0ull) | (1ull << slot);
+            // (the parent was expanded at the level before, or is the root: its row and mask already exist)
+            t.dmask[slot] = (parent >= 0 ? above : 0ull) | (1ull << slot);
             t.dpos[slot] = level - 1;
-            pick[0] = t.pool_hid[node]; pick[1] = t.pool_tok[node];
-            tok[rank] = pick[1];
+            pick[0] = hid; pick[1] = token;
+            tok[rank] = token;
         }
     }
     __syncthreads();
     const float4* h = reinterpret_cast<const float4*>(H + (size_t)pick[0] * d);
     if (frag) {
-        for (int c = i; c < d / 4; c += 256) { const float4 x = h[c]; st_row_quad(frag, k, want, 4 * c, x.x, x.y, x.z, x.w); }
+        for (int c0 = i; c0 < d / 4; c0 += 4 * 256) {                // four loads in flight
+            float4 x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = h[min(c0 + 256 * u, d / 4 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { const int c = c0 + 256 * u; if (c < d / 4) st_row_quad(frag, k, want, 4 * c, x[u].x, x[u].y, x[u].z, x[u].w); }
+        }
         return;
     }
     float* o = cat + (size_t)want * 2 * d;
@@ -229,7 +274,7 @@ __global__ __launch_bounds__(256) void tree_expand_kernel(int lo, int n, int k, 
 // One workgroup of 1024 threads, P <= 2048.
 __global__ __launch_bounds__(1024) void tree_select_kernel(int P, int N, const int32_t* __restrict__ text,
                                                            const int* __restrict__ dlen, TreeDev t) {
-    __shared__ float s[TREE_MAX_POOL];
+    __shared__ __align__(16) float s[TREE_MAX_POOL];
     __shared__ short rowof[TREE_MAX_POOL];      // verify row of a pool node, 0 if not a candidate
     __shared__ int count[32];                   // candidates per 64 pool nodes
     for (int i = threadIdx.x; i < P; i += 1024) s[i] = t.pool_score[i];

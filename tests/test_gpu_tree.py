@@ -377,6 +377,30 @@ def test_tree_maximum_sizes(dtype):
     print(dtype, "maximum-size tree max error / tolerance:", t.max_err, "accepted:", t.n_hist)
 
 
+@pytest.mark.parametrize("k,depth,nodes", [(3, 2, 5), (4, 3, 20), (8, 5, 30), (10, 6, 60), (15, 5, 63), (16, 5, 63)], ids=str)
+def test_tree_equal_scores(k, depth, nodes, monkeypatch):
+    """Ranks where values are equal: every four consecutive tokens share their LM-head column and their embedding, so that logits, and the scores of nodes below
+    them, come in fours; 9 to 256 nodes of a level and 12 to 1040 of the pool, one to three segments of the vocabulary.  Every decision is re-taken by (value, index)."""
+    make_weights = synth.make_weights
+
+    def in_fours(cfg, seed):
+        w = make_weights(cfg, seed=seed)
+        for name in ("lm_head", "embed"):
+            a = np.array(w[name])
+            if a.shape[0] != cfg.vocab:
+                a = a.T.copy()
+            for e in (1, 2, 3):
+                a[e::4] = a[0::4]
+            w[name] = a if np.array(w[name]).shape[0] == cfg.vocab else np.ascontiguousarray(a.T)
+        return w
+
+    monkeypatch.setattr(synth, "make_weights", in_fours)
+    t = TreeSideBySide(small_bf16(vocab=4096 + 4128 * (k % 2), n_vis=20, n_text=9), 5)
+    t.cycle(k, depth, nodes)
+    t.cycle(k, depth, nodes)
+    t.hv.close()
+
+
 @pytest.mark.parametrize("seed", list(range(40, 50)))
 def test_tree_random_shape_sweep(seed):
     """Seeded random model shapes and tree shapes inside the documented limits: both head sizes, grouped heads, odd tile
