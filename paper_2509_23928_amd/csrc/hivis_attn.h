@@ -14,7 +14,8 @@
 //   * Key splits are merged by the workgroup that arrives last (attn_merge_splits).
 // Kernel traces, eight softmaxes merged at the end -> now: 32 heads of 128, 6 rows over 650 keys 11.6 -> 10.6 us, over 3010 (98 MB) 23.1 -> 21.7; a draft step over
 // 70..110 keys 7.2 -> 5.9; 28 heads of 4 key heads, 7 rows over 1130 keys 14.2 -> 12.8; two sequences, 64-wide heads, 6 rows over 380 keys 10.5 -> 8.8; items of 16
-// pairs, which were not split before: 61 rows over 650 keys 18.8 -> 15.9 (2 splits), 31 rows of 28 heads over 1080 keys 24.4 -> 15.2 (4).
+// pairs, which were not split before: 61 rows over 650 keys 18.8 -> 15.9 (2 splits), 31 rows of 28 heads over 1080 keys 24.4 -> 15.2 (4).  Slower where a workgroup walks
+// many blocks, whose barriers the one workgroup of a CU waits out: a prompt's last 128 of 3008 rows, 256 items of 24 blocks, 66 -> 77 us, once per prompt.
 #pragma once
 #include "hivis_fused.h"
 
