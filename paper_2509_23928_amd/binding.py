@@ -165,6 +165,7 @@ class Hivis:
         if rc:
             raise HivisError(rc, self.lib.hivis_last_error(None).decode())
         self.K = 0
+        self._draft_K = self._verify_rows = 0        # steps of the last chain round, rows of the last verify pass: what the read-back calls copy
 
     def _check(self, rc):
         if rc:
@@ -215,20 +216,21 @@ class Hivis:
 
     def draft(self, K):
         self._check(self.lib.hivis_draft(self.ctx, K))
-        self.K = K
+        self.K = self._draft_K = K
 
     def draft_noalloc(self, K):
         """draft() with every intermediate buffer in the library's static scratch array (no device allocation)."""
         self._check(self.lib.hivis_draft_noalloc(self.ctx, K))
-        self.K = K
+        self.K = self._draft_K = K
 
     def set_drafts(self, tokens):
         t = np.ascontiguousarray(tokens, dtype=np.int32).reshape(self.B, -1)
         self._check(self.lib.hivis_set_drafts(self.ctx, _ptr(t), t.shape[1]))
-        self.K = t.shape[1]
+        self.K = self._draft_K = t.shape[1]
 
     def verify(self):
         self._check(self.lib.hivis_verify(self.ctx))
+        self._verify_rows = self.B * (self._draft_K + 1)
 
     def accept(self):
         """Returns (n_accepted [B], tokens [B][k_max+1], -1 beyond n_b+1 entries)."""
@@ -241,7 +243,7 @@ class Hivis:
         """u: [B][K] uniform numbers in [0, 1) (None after rng_seed: drawn on the device)."""
         u = None if u is None else np.ascontiguousarray(u, dtype=np.float32).reshape(self.B, K)
         self._check(self.lib.hivis_draft_sample(self.ctx, K, float(temperature), _ptr(u)))
-        self.K = K
+        self.K = self._draft_K = K
 
     def accept_sample(self, temperature, u_accept=None, u_resample=None):
         """u_accept: [B][K], u_resample: [B] (both None after rng_seed: drawn on the device).  Returns (n_accepted [B], tokens [B][k_max+1])."""
@@ -271,6 +273,7 @@ class Hivis:
 
     def tree_verify(self):
         self._check(self.lib.hivis_tree_verify(self.ctx))
+        self._verify_rows = self.tree_shape[2] + 1
 
     def tree_accept(self):
         """Returns (n_accepted, tokens [depth+1], -1 beyond n+1 entries)."""
@@ -318,18 +321,24 @@ class Hivis:
         return out
 
     # -- hooks -----------------------------------------------------------------------
+    def _read_back(self, shape, written, call):
+        """An array of `shape` (its leading dimensions are rows) filled by a call that copies `written` rows.  Those are the rows of the pass that the values belong
+        to, and K may have changed since: rows beyond them are zeros, rows that the shape has no room for are left out."""
+        n = int(np.prod(shape[:-1]))
+        out = np.empty((max(n, written), shape[-1]), np.float32)
+        out[written:] = 0
+        self._check(call(_ptr(out)))
+        return out[:n].reshape(shape)
+
     def get_logits(self, which):
         V = self.cfg.vocab
-        shape = {0: (self.B, self.K + 1, V), 1: (self.K, self.B, V), 2: (self.B, V)}[which]
-        out = np.empty(shape, np.float32)
-        self._check(self.lib.hivis_get_logits(self.ctx, which, _ptr(out)))
-        return out
+        shape, written = {0: ((self.B, self.K + 1, V), self._verify_rows), 1: ((self.K, self.B, V), self._draft_K * self.B), 2: ((self.B, V), self.B)}[which]
+        return self._read_back(shape, written, lambda p: self.lib.hivis_get_logits(self.ctx, which, p))
 
     def get_hidden(self, which):
-        shape = {0: (self.B, self.K + 1, self.cfg.d), 1: (self.B, self.cfg.d)}[which]
-        out = np.empty(shape, np.float32)
-        self._check(self.lib.hivis_get_hidden(self.ctx, which, _ptr(out)))
-        return out
+        d = self.cfg.d
+        shape, written = {0: ((self.B, self.K + 1, d), self._verify_rows), 1: ((self.B, d), self.B)}[which]
+        return self._read_back(shape, written, lambda p: self.lib.hivis_get_hidden(self.ctx, which, p))
 
     def kv_lengths(self):
         t = np.zeros(self.B, np.int32)
@@ -338,10 +347,12 @@ class Hivis:
         return t, d
 
     def get_tokens(self):
-        dr = np.zeros((self.B, self.K), np.int32)
-        tt = np.zeros((self.B, self.K + 1), np.int32)
+        # (copied for the K of the last chain round; behind a tree round the binding's K is the tree's)
+        n, k = max(self.K, self._draft_K), self.K
+        dr = np.zeros(self.B * n, np.int32)
+        tt = np.zeros(self.B * (n + 1), np.int32)
         self._check(self.lib.hivis_get_tokens(self.ctx, _ptr(dr), _ptr(tt)))
-        return dr, tt
+        return dr[:self.B * k].reshape(self.B, k), tt[:self.B * (k + 1)].reshape(self.B, k + 1)
 
     def timing(self, enable):
         self._check(self.lib.hivis_timing(self.ctx, int(enable)))
