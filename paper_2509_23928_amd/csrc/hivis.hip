@@ -382,7 +382,7 @@ int key_splits(const hivis_ctx* c, int keys, int most, bool half) { return half 
 // One launch of attn_split_kernel.  rm: (head,row) pairs an item may hold, 8 or 16 (the partials' and the kernel's); once: cached rows with the
 // non-temporal hint.
 int launch_attn_split(hivis_ctx* c, const AttnShape& sh, int items, int rm, const float* q, const void* kc, const void* vc, const int* base, const AttnOut& out,
-                      uint4* frag_out, float* ws, int* cnt, bool once, unsigned long long* prof3 = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
+                      uint4* frag_out, float* ws, int* cnt, bool once, unsigned long long* prof2 = nullptr, unsigned long long* prof3 = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
     const int hd = c->cfg.head_dim;
     AttnArgs a{};
     a.q = q; a.kc = (const f16_t*)kc; a.vc = (const f16_t*)vc; a.base = base; a.tmask = sh.tmask; a.ws = ws; a.cnt = cnt;
@@ -391,7 +391,7 @@ int launch_attn_split(hivis_ctx* c, const AttnShape& sh, int items, int rm, cons
     a.group = sh.Hq / sh.Hkv; a.n_rblk = sh.n_rblk; a.n_hblk = sh.n_hblk; a.items = items; a.nsplit = sh.nsplit; a.flags = sh.flags; a.nbase = sh.nbase;
     a.by_rblk = FastDiv::by(sh.n_rblk); a.by_hblk = FastDiv::by(sh.n_hblk); a.by_hkv = FastDiv::by(sh.Hkv); a.by_split = FastDiv::by(sh.nsplit); a.by_mi = FastDiv::by(sh.mi);
     for (int b = 0; b < sh.nbase; ++b) a.base_val[b] = sh.base_val[b];
-    a.prof3 = prof3;
+    a.prof2 = prof2; a.prof3 = prof3;
     const int heads = items / sh.n_rblk;
     const dim3 grid = (sh.flags & 2) ? dim3(8, sh.nsplit, (heads + 7) / 8 * sh.n_rblk) : dim3(sh.nsplit, items);
 #define HIVIS_SPLIT(HD_, RM_, ONCE_)                                                                                                          \
@@ -474,10 +474,10 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
     return fail(c, HIVIS_EINVAL, "attention on the matrix cores needs half-precision caches");
 }
 
-void launch_attn_f32(hivis_ctx* c, const Phase& ph, int rows, unsigned long long* prof2, hipEvent_t ev0, hipEvent_t ev1) {
+void launch_attn_f32(hivis_ctx* c, const Phase& ph, int rows, unsigned long long* prof2, unsigned long long* prof3, hipEvent_t ev0, hipEvent_t ev1) {
     AttnF32Args a{};
     a.q = ph.A; a.kc = (const float*)ph.kc; a.vc = (const float*)ph.vc; a.base = ph.base; a.ws = ph.ws; a.cnt = ph.cnt; a.y = ph.Y; a.rows_out = ph.F;
-    a.ldo = ph.ldy; a.rows = rows; a.items = ph.att_items; a.sh = ph.att; a.prof2 = prof2;
+    a.ldo = ph.ldy; a.rows = rows; a.items = ph.att_items; a.sh = ph.att; a.prof2 = prof2; a.prof3 = prof3;
     a.by_rblk = FastDiv::by(a.sh.n_rblk); a.by_hblk = FastDiv::by(a.sh.n_hblk); a.by_hkv = FastDiv::by(a.sh.Hkv);
     const dim3 grid = (a.sh.flags & 2) ? dim3(8, a.sh.nsplit, (a.items + 7) / 8) : dim3(a.items, a.sh.nsplit);
     const bool one = a.sh.gh * a.sh.mi == 1;         // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
@@ -963,15 +963,14 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             if (ph.type == PH_ATTN_MERGE && ph.att.nsplit == 1) continue;
         }
         int grid = c->fused_grid;
-        if (ph.type == PH_ATTN) grid = std::min(grid, ((ph.att.flags & 2) ? 8 * ((ph.att_items + 7) / 8) : ph.att_items) * ph.att.nsplit);
-        else if (ph.type == PH_ATTN_MERGE) grid = std::min(grid, ph.att_items);
+        if (ph.type == PH_ATTN_MERGE) grid = std::min(grid, ph.att_items);
         else if (ph.type == PH_PREP) grid = std::min(grid, pp.M);
         else if (ph.type == PH_NORM_ROWS) grid = std::min(grid, pp.M);
         else if (ph.type == PH_ARGMAX) grid = std::min(grid, (pp.M + FUSED_NW - 1) / FUSED_NW);
         else if (ph.type == PH_SAMPLE) grid = std::min(grid, pp.M);
         else if (ph.type == PH_GEMM) grid = std::min(grid, ph.N / 16);      // (the LM head's number of greedy candidates per row: lm_candidates)
         PassParams ppl = pp;
-        if (do_prof) { ppl.prof2 = pp.prof2 + (size_t)p * 8; if (p >= n / 2 && p < n / 2 + 8) ppl.prof3 = c->prof + 4096 * 11 + (size_t)(p - n / 2) * 4096; }
+        if (do_prof) { ppl.prof2 = pp.prof2 + (size_t)p * 8; if (p >= n / 2 && p < n / 2 + 8) ppl.prof3 = c->prof + 4096 * 11 + (size_t)(p - n / 2) * PROF_WGS * 4; }
         // kev0/kev1 (null unless this launch is timed) are attached to the dispatch itself: they read the kernel's own
         // start and end timestamps, with no marker packets before or after it in the queue
         // (bf16w has GEMM kernels only: the other phases work on fp32 rows)
@@ -1097,9 +1096,9 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             }
             break;
         case PH_ATTN:
-            if constexpr (std::is_same<WT, float>::value) launch_attn_f32(c, ph, pp.M, ppl.prof2, kev0, kev1);
+            if constexpr (std::is_same<WT, float>::value) launch_attn_f32(c, ph, pp.M, ppl.prof2, ppl.prof3, kev0, kev1);
             else if (int rc = launch_attn_split(c, ph.att, ph.att_items, FUSED_RMAX, ph.A, ph.kc, ph.vc, ph.base, AttnOut{ph.Y, ph.ldy, ph.F, pp.M}, nullptr, ph.ws, ph.cnt,
-                                                once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1, ppl.prof3, kev0, kev1)) return rc;
+                                                once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1, ppl.prof2, ppl.prof3, kev0, kev1)) return rc;
             break;
         case PH_ATTN_MERGE: HIVIS_LAUNCH(PH_ATTN_MERGE, 0); break;
         case PH_PREP: HIVIS_LAUNCH(PH_PREP, 0); break;
@@ -1141,10 +1140,15 @@ int run_program(hivis_ctx* c, int kind, int K, int nseq, int m) {
             HIP_TRY(c, hipStreamSynchronize(c->stream));
             HIP_TRY(c, hipMemcpy(t2.data(), pp.prof2, t2.size() * 8, hipMemcpyDeviceToHost));
             const int p0 = std::min(pg.n / 2, pg.n - 1);
+            const auto after = [](unsigned long long t, unsigned long long from) { return ((double)t - (double)from) * 0.01; };
             for (int p = p0; p < std::min(pg.n, p0 + 14); ++p) {
                 const Phase& P = (*pg.host)[p];
-                fprintf(stderr, "[hivis prof] phase %d type %d epi %d: entry %+.2f us after previous entry;", p, P.type, P.epi, ((double)t2[p * 8] - (double)t2[(p - 1) * 8]) * 0.01);
-                for (int k = 1; k < 7; ++k) fprintf(stderr, " m%d %+.2f", k, ((double)t2[p * 8 + k] - (double)t2[p * 8]) * 0.01);
+                const unsigned long long* m = &t2[(size_t)p * 8];
+                int before = p - 1;                                        // (row kernels write no marks)
+                while (before >= 0 && !t2[(size_t)before * 8]) --before;
+                if (!m[0] || before < 0) { fprintf(stderr, "[hivis prof] phase %d type %d epi %d: no marks\n", p, P.type, P.epi); continue; }
+                fprintf(stderr, "[hivis prof] phase %d type %d epi %d: entry %+.2f us after the entry of phase %d;", p, P.type, P.epi, after(m[0], t2[(size_t)before * 8]), before);
+                for (int k = 1; k < 7; ++k) if (m[k]) fprintf(stderr, " m%d %+.2f", k, after(m[k], m[0]));
                 fprintf(stderr, "\n");
             }
             // per-workgroup entry/exit of the same launches: spread of the exits, the latest workgroups and where they ran
@@ -1152,10 +1156,11 @@ int run_program(hivis_ctx* c, int kind, int K, int nseq, int m) {
             HIP_TRY(c, hipMemcpy(t3.data(), c->prof + 4096 * 11, t3.size() * 8, hipMemcpyDeviceToHost));
             for (int p = p0; p < std::min(pg.n, p0 + 8); ++p) {
                 const Phase& P = (*pg.host)[p];
-                const unsigned long long* w = t3.data() + (size_t)(p - p0) * 4096;
+                const unsigned long long* w = t3.data() + (size_t)(p - p0) * PROF_WGS * 4;
                 std::vector<std::pair<double, int>> ends; double s0 = 1e300, s1 = 0;
-                for (int b = 0; b < c->fused_grid && b < 1024; ++b) if (w[b * 4]) { s0 = std::min(s0, (double)w[b * 4]); s1 = std::max(s1, (double)w[b * 4]); }
-                for (int b = 0; b < c->fused_grid && b < 1024; ++b) if (w[b * 4]) ends.push_back({((double)w[b * 4 + 1] - s0) * 0.01, b});
+                const auto ran = [&](int b) { return w[b * 4] && w[b * 4 + 1]; };          // (not workgroups without an item)
+                for (int b = 0; b < PROF_WGS; ++b) if (ran(b)) { s0 = std::min(s0, (double)w[b * 4]); s1 = std::max(s1, (double)w[b * 4]); }
+                for (int b = 0; b < PROF_WGS; ++b) if (ran(b)) ends.push_back({((double)w[b * 4 + 1] - s0) * 0.01, b});
                 if (ends.empty()) continue;
                 std::sort(ends.begin(), ends.end());
                 const size_t n = ends.size();
@@ -1167,12 +1172,12 @@ int run_program(hivis_ctx* c, int kind, int K, int nseq, int m) {
                 }
                 double xs[8] = {}; int xn[8] = {};
                 for (auto& e : ends) { const int x = (int)(w[e.second * 4 + 2] >> 32) & 7; xs[x] += e.first; xn[x]++; }
-                fprintf(stderr, "; wg0: entry->mark0 %.2f, mark0->exit %.2f us", ((double)t2[p * 8] - (double)w[0]) * 0.01, ((double)w[1] - (double)t2[p * 8]) * 0.01);
+                if (t2[p * 8] && ran(0)) fprintf(stderr, "; wg0: entry->mark0 %.2f, mark0->exit %.2f us", after(t2[p * 8], w[0]), after(w[1], t2[p * 8]));
                 fprintf(stderr, "; mean exit per xcc:");
                 for (int x = 0; x < 8; ++x) fprintf(stderr, " %.1f(%d)", xn[x] ? xs[x] / xn[x] : 0.0, xn[x]);
                 fprintf(stderr, "\n");
             }
-            HIP_TRY(c, hipMemset(c->prof + 4096 * 11, 0, (size_t)8 * 4096 * 8));
+            HIP_TRY(c, hipMemset(c->prof + 4096 * 3, 0, (size_t)16 * 4096 * 8));
             c->prof_left--;
         }
         return HIVIS_OK;

@@ -36,7 +36,7 @@ struct AttnArgs {
     int mi, gh, Hkv, group, n_rblk, n_hblk, items, nsplit, flags, nbase;
     FastDiv by_rblk, by_hblk, by_hkv, by_split, by_mi;
     int base_val[8];
-    unsigned long long* prof3;
+    unsigned long long *prof2, *prof3;  // marks (PassParams)
 };
 
 template <int HD, int RM> struct AttnSplitCfg {
@@ -63,12 +63,12 @@ __global__ __launch_bounds__(FUSED_NT) void attn_split_kernel(AttnArgs a) {
     asm volatile("" :: "s"(a.q), "s"(a.kc), "s"(a.vc), "s"(a.base), "s"(a.tmask), "s"(a.ldq), "s"(a.maxL), "s"(a.offset), "s"(a.seq0), "s"(a.m), "s"(a.qrows),
                       "s"(a.rows), "s"(a.mi), "s"(a.gh), "s"(a.Hkv));
     asm volatile("" :: "s"(a.group), "s"(a.n_rblk), "s"(a.n_hblk), "s"(a.items), "s"(a.nsplit), "s"(a.flags), "s"(a.nbase), "s"(a.by_rblk.mul), "s"(a.by_hblk.mul),
-                      "s"(a.by_hkv.mul), "s"(a.by_split.mul), "s"(a.by_mi.mul), "s"(a.prof3));
+                      "s"(a.by_hkv.mul), "s"(a.by_split.mul), "s"(a.by_mi.mul), "s"(a.prof2), "s"(a.prof3));
     asm volatile("" :: "s"(a.ws), "s"(a.cnt), "s"(a.y), "s"(a.rows_out), "s"(a.frag_out), "s"(a.ldo));
-    if (a.prof3 && threadIdx.x == 0) {
-        const int b = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-        a.prof3[b * 4] = wall_clock64();
-    }
+    const int wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    prof_enter(a.prof3, wg);
+#define HIVIS_SMARK(k) if (a.prof2 && wg == 0 && threadIdx.x == 0) a.prof2[k] = wall_clock64();
+    HIVIS_SMARK(0)
     // Grid: (8, splits, rounds of 8 heads x row blocks): workgroup b runs on XCD b % 8, so that all row blocks and splits of a head share one
     // (the row blocks of 61 rows otherwise each fetch the head's cache rows: 86 MB per layer for 23); or (splits, heads x row blocks)
     const auto scalar = [](int x) { return __builtin_amdgcn_readfirstlane(x); };         // (what is the same for all lanes stays in scalar registers)
@@ -137,6 +137,7 @@ __global__ __launch_bounds__(FUSED_NT) void attn_split_kernel(AttnArgs a) {
         stage_queries();
         asm volatile("; none");
     }
+    HIVIS_SMARK(1)
     lds_barrier();
     f16x8_t qh[KS], qlo[KS];
 #pragma unroll
@@ -247,6 +248,7 @@ __global__ __launch_bounds__(FUSED_NT) void attn_split_kernel(AttnArgs a) {
     };
     while (kbb + KEYS < k1) block(std::false_type());
     if (kbb < k1) block(std::true_type());
+    HIVIS_SMARK(3)
     // ---- denominators (and the halves of 64-wide heads) meet in LDS
     float lsum = lrun;
     lsum += __shfl_xor(lsum, 16, 64);
@@ -298,10 +300,9 @@ __global__ __launch_bounds__(FUSED_NT) void attn_split_kernel(AttnArgs a) {
             }
         }
     }
-    if (a.prof3) {
-        lds_barrier();
-        if (threadIdx.x == 0) a.prof3[(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) * 4 + 1] = wall_clock64();
-    }
+    HIVIS_SMARK(5)
+#undef HIVIS_SMARK
+    prof_leave(a.prof3, wg);
 }
 
 // One (item, key split) of an fp32 pass per workgroup (attn_wg_partial), launched by itself: its arguments come in one batch of scalar loads and what follows from the
@@ -312,7 +313,7 @@ struct AttnF32Args {
     int ldo, rows, items;
     FastDiv by_rblk, by_hblk, by_hkv;
     AttnShape sh;
-    unsigned long long* prof2;
+    unsigned long long *prof2, *prof3;
 };
 
 template <int HD, int RC>
@@ -321,15 +322,18 @@ __global__ __launch_bounds__(FUSED_NT) void attn_f32_kernel(AttnF32Args a) {
     asm volatile("" :: "s"(a.q), "s"(a.kc), "s"(a.vc), "s"(a.base), "s"(a.ws), "s"(a.cnt), "s"(a.y), "s"(a.rows_out), "s"(a.ldo), "s"(a.rows), "s"(a.items), "s"(a.by_rblk.mul),
                       "s"(a.by_hblk.mul), "s"(a.by_hkv.mul));
     asm volatile("" :: "s"(a.sh.Hq), "s"(a.sh.Hkv), "s"(a.sh.m), "s"(a.sh.gh), "s"(a.sh.mi), "s"(a.sh.n_hblk), "s"(a.sh.n_rblk), "s"(a.sh.seq0), "s"(a.sh.offset), "s"(a.sh.maxL),
-                      "s"(a.sh.nsplit), "s"(a.sh.ldq), "s"(a.sh.qrows), "s"(a.sh.flags), "s"(a.sh.nbase), "s"(a.prof2));
+                      "s"(a.sh.nsplit), "s"(a.sh.ldq), "s"(a.sh.qrows), "s"(a.sh.flags), "s"(a.sh.nbase), "s"(a.prof2), "s"(a.prof3));
     const auto scalar = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    const int wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    prof_enter(a.prof3, wg);
     // (grids as in attn_split_kernel)
     const bool xcd_map = (a.sh.flags & 2) != 0;
     const int split = blockIdx.y, item = scalar(xcd_map ? blockIdx.x + 8 * blockIdx.z : blockIdx.x);
     if (item >= a.items) return;
     const int i1 = scalar(a.by_rblk(item)), i2 = scalar(a.by_hblk(i1)), sl = scalar(a.by_hkv(i2));
     const AttnItem it = {item - i1 * a.sh.n_rblk, i1 - i2 * a.sh.n_hblk, i2 - sl * a.sh.Hkv, sl, a.sh.n_hblk == 1 && a.sh.Hq == a.sh.Hkv ? 1 : a.sh.Hq / a.sh.Hkv};
-    attn_wg_partial<float, HD, FUSED_RMAX, RC>(a.q, a.kc, a.vc, a.base, a.sh, it, item, split, lds, a.ws, a.cnt, AttnOut{a.y, a.ldo, a.rows_out, a.rows}, a.prof2);
+    attn_wg_partial<float, HD, FUSED_RMAX, RC>(a.q, a.kc, a.vc, a.base, a.sh, it, item, split, lds, a.ws, a.cnt, AttnOut{a.y, a.ldo, a.rows_out, a.rows}, wg == 0 ? a.prof2 : nullptr);
+    prof_leave(a.prof3, wg);
 }
 
 }  // namespace hivis

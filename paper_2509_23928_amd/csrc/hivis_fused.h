@@ -81,6 +81,22 @@ struct Phase {
     uint4* F; const void* fgain; float* ssq_out;
 };
 
+// Marks of HIVIS_PROF (100 MHz): workgroups of a launch that are recorded, and what the first thread of one writes when it enters (its hardware id: wave, SIMD,
+// CU, shader array and engine, and the XCC) and leaves
+constexpr int PROF_WGS = 1024;
+__device__ __forceinline__ void prof_enter(unsigned long long* prof3, int wg) {
+    if (prof3 && threadIdx.x == 0 && wg < PROF_WGS) {
+        prof3[wg * 4] = wall_clock64();
+        prof3[wg * 4 + 2] = (unsigned long long)__builtin_amdgcn_s_getreg((31 << 11) | 4) | ((unsigned long long)__builtin_amdgcn_s_getreg((3 << 11) | 20) << 32);
+    }
+}
+__device__ __forceinline__ void prof_leave(unsigned long long* prof3, int wg) {
+    if (prof3) {
+        lds_barrier();
+        if (threadIdx.x == 0 && wg < PROF_WGS) prof3[wg * 4 + 1] = wall_clock64();
+    }
+}
+
 struct PassParams {
     const Phase* phases; int nphases;
     int M, nseq, m;                 // rows of the pass = nseq * m
@@ -90,7 +106,7 @@ struct PassParams {
     unsigned* bar;                  // [0] arrival counter (zeroed before launch), [1] abort flag
     int* bad;                       // set to 1 when a row has no greedy token (no logit above -inf: NaN input); may be null
     unsigned spin_limit;
-    unsigned long long* prof3;      // optional [grid][4] per-workgroup entry time, exit time, hardware id of one launch (one launch per phase only)
+    unsigned long long* prof3;      // optional [PROF_WGS][4] per-workgroup entry time, exit time, hardware id of one launch (one launch per phase only)
     unsigned long long* prof2;      // optional [nphases][8] finer timestamps inside GEMM phases (workgroup 0)
     unsigned long long* prof;       // optional [nphases][3] timestamps of workgroup 0 (phase start, phase end, barrier end), 100 MHz
 };
@@ -1622,16 +1638,9 @@ __global__ __launch_bounds__(FUSED_NT) void phase_kernel(Phase ph, PassParams pp
     kernarg_warm<sizeof(Phase) + sizeof(PassParams)>();
     uint4 head[FusedCfg<WT>::KBW], wb1[FusedCfg<WT>::KBW];
     bool head_valid = false, wb1_valid = false;
-    if (pp.prof3 && threadIdx.x == 0) {
-        pp.prof3[blockIdx.x * 4] = wall_clock64();
-        // HW_ID (wave, SIMD, CU, shader array, shader engine) and XCC_ID of the wavefront
-        pp.prof3[blockIdx.x * 4 + 2] = (unsigned long long)__builtin_amdgcn_s_getreg((31 << 11) | 4) | ((unsigned long long)__builtin_amdgcn_s_getreg((3 << 11) | 20) << 32);
-    }
+    prof_enter(pp.prof3, blockIdx.x);
     run_phase<WT, TYPE, EPI, SINGLE, KEEP>(ph, pp, lds, head, head_valid, wb1, wb1_valid, 0);
-    if (pp.prof3) {
-        lds_barrier();
-        if (threadIdx.x == 0) pp.prof3[blockIdx.x * 4 + 1] = wall_clock64();
-    }
+    prof_leave(pp.prof3, blockIdx.x);
 }
 
 }  // namespace hivis

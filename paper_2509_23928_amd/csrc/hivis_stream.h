@@ -362,15 +362,9 @@ template <typename WT, int EPI, int G, bool SHORT, bool KEEP = false>
 __global__ __launch_bounds__(FUSED_NT) void stream_kernel(Phase ph, PassParams pp) {
     extern __shared__ __align__(16) float lds[];
     kernarg_warm<sizeof(Phase) + sizeof(PassParams)>();
-    if (pp.prof3 && threadIdx.x == 0) {
-        pp.prof3[blockIdx.x * 4] = wall_clock64();
-        pp.prof3[blockIdx.x * 4 + 2] = (unsigned long long)__builtin_amdgcn_s_getreg((31 << 11) | 4) | ((unsigned long long)__builtin_amdgcn_s_getreg((3 << 11) | 20) << 32);
-    }
+    prof_enter(pp.prof3, blockIdx.x);
     stream_gemm<WT, EPI, G, SHORT, KEEP>(ph, pp, lds);
-    if (pp.prof3) {
-        lds_barrier();
-        if (threadIdx.x == 0) pp.prof3[blockIdx.x * 4 + 1] = wall_clock64();
-    }
+    prof_leave(pp.prof3, blockIdx.x);
 }
 
 // Final norm of a verify pass: rows A * gain / rms as fp32 rows Y (the features) and as row fragments F.  One workgroup per row.

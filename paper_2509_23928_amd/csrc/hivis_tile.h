@@ -17,6 +17,8 @@ constexpr int TILE_MAX_BLOCKS = 8 * FUSED_NW;       // K blocks of 16 values
 
 template <int EPI, int U>
 __device__ __forceinline__ void tile_gemm(const Phase& ph, const PassParams& pp) {
+#define HIVIS_MARK(k) if (pp.prof2 && blockIdx.x == 0 && threadIdx.x == 0) pp.prof2[k] = wall_clock64();
+    HIVIS_MARK(0)
     constexpr int NW = FUSED_NW;
     constexpr bool TAB = EPI == FEPI_QKV_TAB, QKV = EPI == FEPI_QKV || TAB, RMS = QKV || EPI == FEPI_SILU;       // (RMS: the rows' norm is applied here)
     __shared__ __align__(16) float red[NW * 64 * 4];
@@ -99,6 +101,7 @@ __device__ __forceinline__ void tile_gemm(const Phase& ph, const PassParams& pp)
             }
         } else e_a = ph.add_rows[(size_t)clamp_token(tok_e, pp.V) * N + col];
     }
+    HIVIS_MARK(1)
     // ---- products
     f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
     float ss = 0.f;
@@ -119,6 +122,7 @@ __device__ __forceinline__ void tile_gemm(const Phase& ph, const PassParams& pp)
         ss += __shfl_xor(ss, 32, 64);
         if (lane < 16) ssq[wave * 16 + lane] = ss;
     }
+    HIVIS_MARK(3)
     lds_barrier();
     // ---- epilogue: 16 lanes per row
     if (er < M) {
@@ -165,17 +169,16 @@ __device__ __forceinline__ void tile_gemm(const Phase& ph, const PassParams& pp)
         }
     }
     if constexpr (EPI == FEPI_LOGITS) { if (ph.cnt) lm_head_elect(ph, pp, flag); }
+    HIVIS_MARK(6)
+#undef HIVIS_MARK
 }
 
 template <int EPI, int U>
 __global__ __launch_bounds__(FUSED_NT) void tile_kernel(Phase ph, PassParams pp) {
     kernarg_warm<sizeof(Phase) + sizeof(PassParams)>();
-    if (pp.prof3 && threadIdx.x == 0) pp.prof3[blockIdx.x * 4] = wall_clock64();
+    prof_enter(pp.prof3, blockIdx.x);
     tile_gemm<EPI, U>(ph, pp);
-    if (pp.prof3) {
-        lds_barrier();
-        if (threadIdx.x == 0) pp.prof3[blockIdx.x * 4 + 1] = wall_clock64();
-    }
+    prof_leave(pp.prof3, blockIdx.x);
 }
 
 }  // namespace hivis
