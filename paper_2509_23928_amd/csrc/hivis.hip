@@ -379,28 +379,42 @@ AttnShape fused_attn_shape(hivis_ctx* c, int nseq, int m, int offset, int maxL, 
 
 int key_splits(const hivis_ctx* c, int keys, int most, bool half) { return half && !c->keys_forced ? attn_block_splits(keys, most) : attn_splits(keys, most, c->keys_per_split); }
 
-// One launch of attn_split_kernel.  rm: (head,row) pairs an item may hold, 8 or 16 (the partials' and the kernel's); once: cached rows with the
-// non-temporal hint.
-int launch_attn_split(hivis_ctx* c, const AttnShape& sh, int items, int rm, const float* q, const void* kc, const void* vc, const int* base, const AttnOut& out,
-                      uint4* frag_out, float* ws, int* cnt, bool once, unsigned long long* prof2 = nullptr, unsigned long long* prof3 = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
-    const int hd = c->cfg.head_dim;
-    AttnArgs a{};
-    a.q = q; a.kc = (const f16_t*)kc; a.vc = (const f16_t*)vc; a.base = base; a.tmask = sh.tmask; a.ws = ws; a.cnt = cnt;
-    a.y = out.y; a.ldo = out.ldo; a.rows_out = out.frag; a.rows = out.rows; a.frag_out = frag_out;
-    a.ldq = sh.ldq; a.maxL = sh.maxL; a.offset = sh.offset; a.seq0 = sh.seq0; a.m = sh.m; a.qrows = sh.qrows; a.mi = sh.mi; a.gh = sh.gh; a.Hkv = sh.Hkv;
-    a.group = sh.Hq / sh.Hkv; a.n_rblk = sh.n_rblk; a.n_hblk = sh.n_hblk; a.items = items; a.nsplit = sh.nsplit; a.flags = sh.flags; a.nbase = sh.nbase;
-    a.by_rblk = FastDiv::by(sh.n_rblk); a.by_hblk = FastDiv::by(sh.n_hblk); a.by_hkv = FastDiv::by(sh.Hkv); a.by_split = FastDiv::by(sh.nsplit); a.by_mi = FastDiv::by(sh.mi);
-    for (int b = 0; b < sh.nbase; ++b) a.base_val[b] = sh.base_val[b];
-    a.prof2 = prof2; a.prof3 = prof3;
-    const int heads = items / sh.n_rblk;
+// One launch of attention over half-precision caches, in blocks of keys (attn_split_kernel) or in tiles (attn_tiles_kernel) as attn_walks has it.  rm: (head,row) pairs an item
+// may hold, 8 or 16 (the partials' and the kernel's); keys: cached rows of the longest sequence, with those of the pass; once: cached rows with the non-temporal hint.
+int launch_attn_half(hivis_ctx* c, const AttnShape& sh, int items, int rm, int keys, const float* q, const void* kc, const void* vc, const int* base, const AttnOut& out,
+                     uint4* frag_out, float* ws, int* cnt, bool once, unsigned long long* prof2 = nullptr, unsigned long long* prof3 = nullptr, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
+    const int hd = c->cfg.head_dim, heads = items / sh.n_rblk;
     const dim3 grid = (sh.flags & 2) ? dim3(8, sh.nsplit, (heads + 7) / 8 * sh.n_rblk) : dim3(sh.nsplit, items);
+    const FastDiv by_rblk = FastDiv::by(sh.n_rblk), by_hblk = FastDiv::by(sh.n_hblk), by_hkv = FastDiv::by(sh.Hkv);
+#define HIVIS_ATTN_FORMS(LAUNCH_)                                                                                                             \
+    if (rm > FUSED_RMAX) { if (hd == 128) LAUNCH_(128, ATTN_ROWS_RM, false); else LAUNCH_(64, ATTN_ROWS_RM, false); }                         \
+    else if (hd == 128) { if (once) LAUNCH_(128, FUSED_RMAX, true); else LAUNCH_(128, FUSED_RMAX, false); }                                   \
+    else { if (once) LAUNCH_(64, FUSED_RMAX, true); else LAUNCH_(64, FUSED_RMAX, false); }
+    if (attn_walks(c->num_cu, hd, items, rm, attn_blocks(keys, sh.nsplit))) {
+        AttnTilesArgs a{};
+        a.q = q; a.kc = (const f16_t*)kc; a.vc = (const f16_t*)vc; a.base = base; a.ws = ws; a.cnt = cnt; a.out = out; a.out.afrag = frag_out; a.items = items;
+        a.by_rblk = by_rblk; a.by_hblk = by_hblk; a.by_hkv = by_hkv; a.sh = sh; a.prof2 = prof2; a.prof3 = prof3;
+#define HIVIS_TILES(HD_, RM_, ONCE_)                                                                                                          \
+        do { constexpr int lds_ = (int)(fused_attn_mfma_lds_floats(HD_, FUSED_NW, RM_) * sizeof(float));                                      \
+             hipExtLaunchKernelGGL((attn_tiles_kernel<HD_, RM_, ONCE_>), grid, dim3(FUSED_NT), lds_, c->stream, ev0, ev1, 0, a); } while (0)
+        HIVIS_ATTN_FORMS(HIVIS_TILES)
+#undef HIVIS_TILES
+    } else {
+        AttnArgs a{};
+        a.q = q; a.kc = (const f16_t*)kc; a.vc = (const f16_t*)vc; a.base = base; a.tmask = sh.tmask; a.ws = ws; a.cnt = cnt;
+        a.y = out.y; a.ldo = out.ldo; a.rows_out = out.frag; a.rows = out.rows; a.frag_out = frag_out;
+        a.ldq = sh.ldq; a.maxL = sh.maxL; a.offset = sh.offset; a.seq0 = sh.seq0; a.m = sh.m; a.qrows = sh.qrows; a.mi = sh.mi; a.gh = sh.gh; a.Hkv = sh.Hkv;
+        a.group = sh.Hq / sh.Hkv; a.n_rblk = sh.n_rblk; a.n_hblk = sh.n_hblk; a.items = items; a.nsplit = sh.nsplit; a.flags = sh.flags; a.nbase = sh.nbase;
+        a.by_rblk = by_rblk; a.by_hblk = by_hblk; a.by_hkv = by_hkv; a.by_split = FastDiv::by(sh.nsplit); a.by_mi = FastDiv::by(sh.mi);
+        for (int b = 0; b < sh.nbase; ++b) a.base_val[b] = sh.base_val[b];
+        a.prof2 = prof2; a.prof3 = prof3;
 #define HIVIS_SPLIT(HD_, RM_, ONCE_)                                                                                                          \
-    do { constexpr int lds_ = AttnSplitCfg<HD_, RM_>::LDS;                                                                                    \
-         hipExtLaunchKernelGGL((attn_split_kernel<HD_, RM_, ONCE_>), grid, dim3(FUSED_NT), lds_, c->stream, ev0, ev1, 0, a); } while (0)
-    if (rm > FUSED_RMAX) { if (hd == 128) HIVIS_SPLIT(128, ATTN_ROWS_RM, false); else HIVIS_SPLIT(64, ATTN_ROWS_RM, false); }
-    else if (hd == 128) { if (once) HIVIS_SPLIT(128, FUSED_RMAX, true); else HIVIS_SPLIT(128, FUSED_RMAX, false); }
-    else { if (once) HIVIS_SPLIT(64, FUSED_RMAX, true); else HIVIS_SPLIT(64, FUSED_RMAX, false); }
+        do { constexpr int lds_ = AttnSplitCfg<HD_, RM_>::LDS;                                                                                \
+             hipExtLaunchKernelGGL((attn_split_kernel<HD_, RM_, ONCE_>), grid, dim3(FUSED_NT), lds_, c->stream, ev0, ev1, 0, a); } while (0)
+        HIVIS_ATTN_FORMS(HIVIS_SPLIT)
 #undef HIVIS_SPLIT
+    }
+#undef HIVIS_ATTN_FORMS
     HIP_TRY(c, hipGetLastError());
     return HIVIS_OK;
 }
@@ -456,12 +470,13 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
         sh.seq0 = seq0; sh.tmask = tmask; sh.flags = c->attn_flags; sh.qrows = qrows; sh.nsplit = 1;
         if (base == c->zeros && nseq <= 8) sh.nbase = nseq;             // (base_val: zeros)
         float* ws = nullptr; int* cnt = nullptr;
+        // (the host mirrors the cache lengths that `base` holds)
+        const std::vector<int>* hl = base == c->tlen ? &c->h_tlen : base == c->dlen ? &c->h_dlen : nullptr;
+        int max_keys = 0;
+        for (int s = 0; s < nseq; ++s) max_keys = std::max(max_keys, (hl ? (*hl)[seq0 + s] : 0) + offset + m);
         if (c->attn_elect && items <= c->rows_cnt_n) {
-            // the key range of an item is split over workgroups and the last one to arrive merges (as in the phase programs); the host mirrors the
-            // cache lengths that `base` holds.  No more workgroups than CUs: with more, 160 items of 32 rows got slower (8.8 -> 9.6 ms per verify).
-            const std::vector<int>* hl = base == c->tlen ? &c->h_tlen : base == c->dlen ? &c->h_dlen : nullptr;
-            int max_keys = 0;
-            for (int s = 0; s < nseq; ++s) max_keys = std::max(max_keys, (hl ? (*hl)[seq0 + s] : 0) + offset + m);
+            // the key range of an item is split over workgroups and the last one to arrive merges (as in the phase programs).  No more workgroups than CUs: with
+            // more, 160 items of 32 rows got slower (8.8 -> 9.6 ms per verify).
             const int wgs = (sh.flags & 2) ? (items / sh.n_rblk + 7) / 8 * 8 * sh.n_rblk : items;
             int nsplit = key_splits(c, max_keys, std::min(ATTN_MAX_SPLITS, std::max(1, c->fused_grid / wgs)), true);
             while (nsplit > 1 && (size_t)items * nsplit * rm * (g.head_dim + 2) > c->attn_ws_floats) --nsplit;
@@ -469,7 +484,7 @@ int attention_rows_mfma(hivis_ctx* c, const float* q, int ldq, const KVDev& kv, 
         }
         uint4* frag = (frag_out && wrote_frag && ldo % 32 == 0) ? frag_out : nullptr;
         if (frag) *wrote_frag = true;
-        return launch_attn_split(c, sh, items, rm, q, kv.k, kv.v, base, AttnOut{out, ldo, row_frag, nseq * m}, frag, ws, cnt, false);
+        return launch_attn_half(c, sh, items, rm, max_keys, q, kv.k, kv.v, base, AttnOut{out, ldo, row_frag, nseq * m}, frag, ws, cnt, false);
     }
     return fail(c, HIVIS_EINVAL, "attention on the matrix cores needs half-precision caches");
 }
@@ -1097,7 +1112,7 @@ int launch_phases(hivis_ctx* c, const Phase* phases, int n, int kind, int K, con
             break;
         case PH_ATTN:
             if constexpr (std::is_same<WT, float>::value) launch_attn_f32(c, ph, pp.M, ppl.prof2, ppl.prof3, kev0, kev1);
-            else if (int rc = launch_attn_split(c, ph.att, ph.att_items, FUSED_RMAX, ph.A, ph.kc, ph.vc, ph.base, AttnOut{ph.Y, ph.ldy, ph.F, pp.M}, nullptr, ph.ws, ph.cnt,
+            else if (int rc = launch_attn_half(c, ph.att, ph.att_items, FUSED_RMAX, max_keys, ph.A, ph.kc, ph.vc, ph.base, AttnOut{ph.Y, ph.ldy, ph.F, pp.M}, nullptr, ph.ws, ph.cnt,
                                                 once && ph.att.n_hblk == 1 && ph.att.n_rblk == 1, ppl.prof2, ppl.prof3, kev0, kev1)) return rc;
             break;
         case PH_ATTN_MERGE: HIVIS_LAUNCH(PH_ATTN_MERGE, 0); break;
@@ -1386,7 +1401,8 @@ int prefill_lds_setup(hivis_ctx* c) {
         HIVIS_WIDE_LDS(2, 4, 2), HIVIS_WIDE_LDS(2, 4, 3), HIVIS_WIDE_LDS(2, 2, 2), HIVIS_WIDE_LDS(2, 4, 5), HIVIS_WIDE_LDS(2, 2, 3), HIVIS_WIDE_LDS(2, 2, 4), HIVIS_WIDE_LDS(2, 2, 5),
         HIVIS_WIDE_LDS(4, 4, 2), HIVIS_WIDE_LDS(4, 4, 3), HIVIS_WIDE_LDS(4, 2, 2), HIVIS_WIDE_LDS(4, 4, 5), HIVIS_WIDE_LDS(4, 2, 3), HIVIS_WIDE_LDS(4, 2, 4),
 #undef HIVIS_WIDE_LDS
-#define HIVIS_SPLIT_LDS(HD_, RM_, ONCE_) {(const void*)attn_split_kernel<HD_, RM_, ONCE_>, (size_t)AttnSplitCfg<HD_, RM_>::LDS}
+#define HIVIS_SPLIT_LDS(HD_, RM_, ONCE_) {(const void*)attn_split_kernel<HD_, RM_, ONCE_>, (size_t)AttnSplitCfg<HD_, RM_>::LDS}, \
+                                         {(const void*)attn_tiles_kernel<HD_, RM_, ONCE_>, fused_attn_mfma_lds_floats(HD_, FUSED_NW, RM_) * sizeof(float)}
         HIVIS_SPLIT_LDS(128, ATTN_ROWS_RM, false), HIVIS_SPLIT_LDS(64, ATTN_ROWS_RM, false), HIVIS_SPLIT_LDS(128, FUSED_RMAX, true), HIVIS_SPLIT_LDS(128, FUSED_RMAX, false),
         HIVIS_SPLIT_LDS(64, FUSED_RMAX, true), HIVIS_SPLIT_LDS(64, FUSED_RMAX, false),
 #undef HIVIS_SPLIT_LDS

@@ -14,8 +14,8 @@
 //   * Key splits are merged by the workgroup that arrives last (attn_merge_splits).
 // Kernel traces, eight softmaxes merged at the end -> now: 32 heads of 128, 6 rows over 650 keys 11.6 -> 10.6 us, over 3010 (98 MB) 23.1 -> 21.7; a draft step over
 // 70..110 keys 7.2 -> 5.9; 28 heads of 4 key heads, 7 rows over 1130 keys 14.2 -> 12.8; two sequences, 64-wide heads, 6 rows over 380 keys 10.5 -> 8.8; items of 16
-// pairs, which were not split before: 61 rows over 650 keys 18.8 -> 15.9 (2 splits), 31 rows of 28 heads over 1080 keys 24.4 -> 15.2 (4).  Slower where a workgroup walks
-// many blocks, whose barriers the one workgroup of a CU waits out: a prompt's last 128 of 3008 rows, 256 items of 24 blocks, 66 -> 77 us, once per prompt.
+// pairs, which were not split before: 61 rows over 650 keys 18.8 -> 15.9 (2 splits), 31 rows of 28 heads over 1080 keys 24.4 -> 15.2 (4).  Where a
+// workgroup walks many blocks, the two barriers of each cost more than the merge that they save: attn_tiles_kernel below.
 #pragma once
 #include "hivis_fused.h"
 
@@ -333,6 +333,34 @@ __global__ __launch_bounds__(FUSED_NT) void attn_f32_kernel(AttnF32Args a) {
     const int i1 = scalar(a.by_rblk(item)), i2 = scalar(a.by_hblk(i1)), sl = scalar(a.by_hkv(i2));
     const AttnItem it = {item - i1 * a.sh.n_rblk, i1 - i2 * a.sh.n_hblk, i2 - sl * a.sh.Hkv, sl, a.sh.n_hblk == 1 && a.sh.Hq == a.sh.Hkv ? 1 : a.sh.Hq / a.sh.Hkv};
     attn_wg_partial<float, HD, FUSED_RMAX, RC>(a.q, a.kc, a.vc, a.base, a.sh, it, item, split, lds, a.ws, a.cnt, AttnOut{a.y, a.ldo, a.rows_out, a.rows}, wg == 0 ? a.prof2 : nullptr);
+    prof_leave(a.prof3, wg);
+}
+
+// The same with every wavefront on its own (attn_wg_mfma: tiles of 16 keys, a softmax per wavefront, merged at the end), for workgroups that walk many blocks of 128 keys
+// (attn_walks): a prompt's last 128 of 3008 rows, 32 heads, 78 -> 63 us in a traced request.
+struct AttnTilesArgs {
+    const float* q; const f16_t* kc; const f16_t* vc; const int* base; float* ws; int* cnt;
+    AttnOut out;
+    int items;
+    FastDiv by_rblk, by_hblk, by_hkv;
+    AttnShape sh;
+    unsigned long long *prof2, *prof3;
+};
+
+template <int HD, int RM, bool ONCE>
+__global__ __launch_bounds__(FUSED_NT) void attn_tiles_kernel(AttnTilesArgs a) {
+    extern __shared__ __align__(16) char attn_lds[];
+    const auto scalar = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    const int wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    prof_enter(a.prof3, wg);
+    // (grids as in attn_split_kernel)
+    const bool xcd_map = (a.sh.flags & 2) != 0;
+    const int z = scalar(xcd_map ? blockIdx.z : blockIdx.y), split = scalar(xcd_map ? blockIdx.y : blockIdx.x);
+    const int zh = scalar(a.by_rblk(z)), rblk = z - zh * a.sh.n_rblk, i1 = scalar(xcd_map ? blockIdx.x + 8 * zh : zh), item = i1 * a.sh.n_rblk + rblk;
+    if (item >= a.items) return;
+    const int i2 = scalar(a.by_hblk(i1)), sl = scalar(a.by_hkv(i2));
+    const AttnItem it = {rblk, i1 - i2 * a.sh.n_hblk, i2 - sl * a.sh.Hkv, sl, a.sh.Hq == a.sh.Hkv ? 1 : a.sh.Hq / a.sh.Hkv};
+    attn_wg_mfma<HD, RM, ONCE>(a.q, a.kc, a.vc, a.base, a.sh, it, item, split, reinterpret_cast<float*>(attn_lds), a.ws, a.cnt, a.out, wg == 0 ? a.prof2 : nullptr);
     prof_leave(a.prof3, wg);
 }
 

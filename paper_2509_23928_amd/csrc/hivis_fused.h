@@ -915,7 +915,7 @@ __device__ __forceinline__ void attn_wg_finish(const float* __restrict__ mrg, in
     lds_barrier();
 }
 
-// ---- attention on the matrix cores (half-precision caches) in the single-launch program; launches of their own: attn_split_kernel -------
+// ---- attention on the matrix cores (half-precision caches) in the single-launch program and in attn_tiles_kernel; other launches: attn_split_kernel -------
 // Same work split as attn_wg_partial, but both contractions run as MFMA with the (head,row) pairs as the 16-wide
 // N dimension, so the queries live in registers instead of LDS and a 16-key tile costs a few dozen MFMA instead of
 // ~500 scalar FMAs:
@@ -942,9 +942,9 @@ __host__ __device__ constexpr size_t fused_attn_mfma_lds_floats(int hd, int nw, 
     return (tiles > mrg ? tiles : mrg) + 16;
 }
 
-template <int HD, int RM>
+template <int HD, int RM, bool ONCE = false>
 __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const f16_t* __restrict__ kc, const f16_t* __restrict__ vc,
-                                             const int* __restrict__ base, const AttnShape& sh, int item_id, int split,
+                                             const int* __restrict__ base, const AttnShape& sh, const AttnItem& it, int item_id, int split,
                                              float* __restrict__ lds, float* __restrict__ ws, int* __restrict__ cnt,
                                              const AttnOut& dst, unsigned long long* marks = nullptr) {
     HIVIS_AMARK(0)
@@ -968,7 +968,6 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
     float* mrg = lds;                                               // [NW][RM][HD + 2] per-wavefront partials: same space, after the loop
     int* flag = reinterpret_cast<int*>(lds + fused_attn_mfma_lds_floats(HD, NW, RM) - 16);
 
-    const AttnItem it = attn_item(sh, item_id);
     const int rblk = it.rblk, hblk = it.hblk, kvh = it.kvh, sl = it.sl, group = it.group;
     const int seq = sh.seq0 + sl;
     const int h0 = hblk * sh.gh, nh = min(sh.gh, group - h0);
@@ -996,8 +995,13 @@ __device__ __forceinline__ void attn_wg_mfma(const float* __restrict__ q, const 
     {                                                                                                              \
         _Pragma("unroll") for (int t = 0; t < VT; ++t) {                                                           \
             const size_t off_ = (size_t)min((kb_) + t * KPI + vks, nkeys - 1) * ROWB + vdc * 16;                   \
-            knext[t] = *reinterpret_cast<const u32x4_t*>(kbase + off_);                                            \
-            vnext[t] = *reinterpret_cast<const u32x4_t*>(vbase + off_);                                            \
+            if constexpr (ONCE) {                                                                                  \
+                knext[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(kbase + off_));             \
+                vnext[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(vbase + off_));             \
+            } else {                                                                                               \
+                knext[t] = *reinterpret_cast<const u32x4_t*>(kbase + off_);                                        \
+                vnext[t] = *reinterpret_cast<const u32x4_t*>(vbase + off_);                                        \
+            }                                                                                                      \
         }                                                                                                          \
     }
     if (k0 + 16 * wave < k1) HIVIS_ATTN_LOADS(k0 + 16 * wave)
@@ -1512,8 +1516,8 @@ __device__ __forceinline__ void run_phase(const Phase& ph, const PassParams& pp,
             if (xcd_map) { const int j = w >> 3, q = div_pow2(j, nsp); item = (w & 7) + 8 * q; split = j - q * nsp; if (item >= ph.att_items) continue; }
             else { item = div_pow2(w, nsp); split = w - item * nsp; }
             if constexpr (std::is_same<KT, f16_t>::value) {
-                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2);
-                else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, item, split, lds, ph.ws, ph.cnt, dst, pp.prof2);
+                if (pp.hd == 128) attn_wg_mfma<128, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, attn_item(ph.att, item), item, split, lds, ph.ws, ph.cnt, dst, pp.prof2);
+                else attn_wg_mfma<64, FUSED_RMAX>(ph.A, (const KT*)ph.kc, (const KT*)ph.vc, ph.base, ph.att, attn_item(ph.att, item), item, split, lds, ph.ws, ph.cnt, dst, pp.prof2);
             } else {
                 // (head,row) pairs an item holds at most: one for a draft step of one query head per key head, else up to 8
                 const bool one = ph.att.gh * ph.att.mi == 1;

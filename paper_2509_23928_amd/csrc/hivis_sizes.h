@@ -144,6 +144,16 @@ inline int attn_block_splits(int keys, int most) {
     const int per = (keys + ATTN_BLOCK_KEYS * most - 1) / (ATTN_BLOCK_KEYS * most) * ATTN_BLOCK_KEYS;
     return std::max(1, std::min(most, (keys + per - 1) / per));
 }
+inline int attn_blocks(int keys, int splits) { return ((keys + splits - 1) / splits + ATTN_BLOCK_KEYS - 1) / ATTN_BLOCK_KEYS; }       // of a workgroup
+// Whether the workgroups of such a launch walk so many blocks that the form without a barrier per block is faster (attn_tiles_kernel): its wavefronts run on by
+// themselves, but merge eight softmaxes at the end.  rm: (head,row) pairs an item may hold.  us, block form -> tiles: a prompt's last 128 of 3000 rows, 32 heads (256 items of 24
+// blocks) 74 -> 66, two such prompts (512 items) 138 -> 104, 32 heads of 64 of four (1024 items) 142 -> 88; 128 rows over 400 keys the same in 4 blocks, over 200 keys 0.84 times as long in the block
+// form.  Eight rows or fewer: 40 heads of eight sequences over 4000 keys (320 items) 266 -> 254, below a workgroup per CU within 3 % either way.  More items than CUs pay for
+// every block that a CU's one workgroup waits at, and two workgroups of the tiles form of 64-wide heads fit a CU.
+inline bool attn_walks(int num_cu, int hd, int items, int rm, int blocks) {
+    if (items > num_cu) return blocks >= (hd == 64 ? 2 : 4);
+    return rm > FUSED_RMAX && blocks >= (hd == 64 ? 3 : 6);
+}
 // Whether the rows of an fp32 pass over `keys` cached rows of each of nseq sequences are items of their own.  The vector ALU works on an
 // item's rows one after the other, so that sharing an item costs a row about what 230 keys of 64 values cost.  Alone, rows leave fewer CUs
 // to split the keys over, and the items of a key head, dealt to all eight XCDs, fetch its cached rows up to eight times (a megabyte costs

@@ -65,3 +65,49 @@ def test_fp32_cache_lengths(hq, hkv, hd, K, batch):
 def test_last_rows_of_a_prompt(n_vis, heads, n_text):
     hq, hkv, hd = heads
     check_prefill(cfg_of(n_vis=n_vis, n_text=n_text, d=64, ffn=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd))
+
+
+# ---- launches whose workgroups walk many blocks: the form without a barrier per block (attn_tiles_kernel)
+
+def walks(tmp_path, hd, items, rm, keys, most):
+    """Whether such a launch takes that form on 256 CUs."""
+    lib = load("""#include "hivis_sizes.h"
+using namespace hivis;
+extern "C" int walks(int hd, int items, int rm, int keys, int most) { return attn_walks(256, hd, items, rm, attn_blocks(keys, attn_block_splits(keys, most))); }""", tmp_path)
+    return bool(lib.walks(hd, items, rm, keys, most))
+
+
+def test_walked_blocks_rule(tmp_path):
+    for hd, items, rm, keys, most, want in [(128, 256, 16, 640, 1, False), (128, 256, 16, 641, 1, True), (64, 256, 16, 256, 1, False), (64, 256, 16, 257, 1, True), (128, 257, 8, 384, 1, False),
+                                            (128, 257, 8, 385, 1, True), (64, 257, 8, 128, 1, False), (64, 257, 8, 129, 1, True), (128, 256, 8, 4000, 1, False), (128, 32, 16, 4000, 8, False)]:
+        assert walks(tmp_path, hd, items, rm, keys, most) == want, (hd, items, rm, keys, most)
+
+
+# a prompt's last rows, 16 pairs per item: more items than CUs, as many, and fewer (two key splits each); a short last block and row block
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads,n_vis,n_text,items,most", [((40, 40, 128), 600, 127, 320, 1), ((32, 32, 128), 700, 113, 256, 1), ((36, 36, 64), 130, 127, 288, 1), ((32, 8, 64), 700, 61, 128, 2)], ids=str)
+def test_walked_blocks_of_a_prompt(heads, n_vis, n_text, items, most, tmp_path):
+    hq, hkv, hd = heads
+    assert walks(tmp_path, hd, items, 16, n_vis + n_text, most)
+    check_prefill(cfg_of(n_vis=n_vis, n_text=n_text, d=64, ffn=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd))
+
+
+# decode passes of eight sequences, one and two rows each (K = 1); at 800 keys of 40 heads the caches outgrow the memory-side cache (256 MB) and are read with the hint
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads,lengths", [((40, 40, 128), (385, 500, 800)), ((36, 36, 64), (129, 255, 300))], ids=str)
+def test_walked_blocks_of_many_sequences(heads, lengths, tmp_path, monkeypatch):
+    hq, hkv, hd = heads
+    assert all(walks(tmp_path, hd, 8 * hkv, 8, n, 1) for n in lengths)
+    monkeypatch.setitem(globals(), "LENGTHS", list(lengths))
+    test_cache_lengths(hq, hkv, hd, 1, 8)
+
+
+# rows of a draft tree: 61 rows of 36 heads over 3 and 4 blocks
+@pytest.mark.gpu
+def test_walked_blocks_of_a_tree(tmp_path):
+    from test_gpu_tree import TreeSideBySide, small_bf16
+    assert walks(tmp_path, 64, 36 * 4, 16, 300 + 9 + 61, 1)
+    t = TreeSideBySide(small_bf16(n_q_heads=36, n_kv_heads=36, head_dim=64, n_vis=300, n_text=9), 3)
+    t.cycle(10, 6, 60)
+    t.cycle(10, 6, 60)
+    t.hv.close()
