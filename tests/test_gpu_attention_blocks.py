@@ -67,6 +67,18 @@ def test_last_rows_of_a_prompt(n_vis, heads, n_text):
     check_prefill(cfg_of(n_vis=n_vis, n_text=n_text, d=64, ffn=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd))
 
 
+# the switches of the key splits: partials merged by a launch of their own; an item's splits over all XCDs (bit 1 clear), fences around its counter (bit 0 clear)
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,value", [("HIVIS_ATTN_ELECT", "0"), ("HIVIS_ATTN_FLAGS", "0"), ("HIVIS_ATTN_FLAGS", "1"), ("HIVIS_ATTN_FLAGS", "2")])
+def test_split_switches(name, value, monkeypatch):
+    monkeypatch.setenv(name, value)
+    monkeypatch.setitem(globals(), "LENGTHS", [9, 124, 381, 650])
+    for hq, hkv, hd, K, batch in [(32, 32, 128, 5, 1), (7, 1, 64, 1, 2)]:
+        test_cache_lengths(hq, hkv, hd, K, batch)
+    test_fp32_cache_lengths(28, 4, 128, 6, 1)
+    check_prefill(cfg_of(n_vis=600, n_text=61, d=64, ffn=64, n_q_heads=28, n_kv_heads=4, head_dim=128))        # items of 16 pairs
+
+
 # ---- launches whose workgroups walk many blocks: the form without a barrier per block (attn_tiles_kernel)
 
 def walks(tmp_path, hd, items, rm, keys, most):
