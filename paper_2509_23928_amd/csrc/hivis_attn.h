@@ -305,9 +305,9 @@ __global__ __launch_bounds__(FUSED_NT) void attn_split_kernel(AttnArgs a) {
     prof_leave(a.prof3, wg);
 }
 
-// One (item, key split) of an fp32 pass per workgroup (attn_wg_partial), launched by itself: its arguments come in one batch of scalar loads and what follows from the
-// workgroup's index without a division.  Short passes are a chain of such latencies: 4 heads
-// of 64 over 100..180 keys, one row 5.2 -> 4.0 us, five 6.1 -> 4.9 (as a phase of the general launch before).
+// One (item, key split) of an fp32 pass per workgroup (attn_wg_partial), launched by itself: its arguments come in one batch of scalar loads and item, head and
+// sequence by reciprocals from the host.  (Divisions left: the group of grouped heads, and a split's keys where the splits are no power of two.)  Short passes are a
+// chain of such latencies: 4 heads of 64 over 100..180 keys, one row 5.2 -> 4.0 us, five 6.1 -> 4.9 (as a phase of the general launch before).
 struct AttnF32Args {
     const float* q; const float* kc; const float* vc; const int* base; float* ws; int* cnt; float* y; uint4* rows_out;
     int ldo, rows, items;

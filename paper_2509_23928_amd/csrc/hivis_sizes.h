@@ -61,6 +61,8 @@ inline TallPlan tall_plan(int num_cu, int M, int kblks, int ntiles, bool may_spl
 
 // The q|k|v and the gate|up product end in the GEMM itself unless K slices win back more than the row kernel costs
 // (ROW_KERNEL_US: its launch and ramp; its traffic is in the slices' estimate).  At most 64 rows: gate|up likewise, q|k|v never.
+// (Gate|up of ten models 256 to 8192 wide at 17..61 rows: in the GEMM 0.5 to 8.5 us faster than slices and row kernel, 5.0 against 7.1 us for 1408 columns of 256 at 17 rows, 17.1 and 19.0 for
+// 11264 of 2048 and 39.3 and 41.7 for 22016 of 4096 at 61, 140 and 144 for 57344 of 8192 at 17; the rule takes the GEMM for all of them.)
 constexpr double ROW_KERNEL_US = 8.0;
 template <typename Plan> bool tall_fused(const Plan& whole, const Plan& sliced) { return whole.us <= sliced.us + ROW_KERNEL_US; }
 
@@ -70,7 +72,10 @@ template <typename Plan> bool tall_fused(const Plan& whole, const Plan& sliced) 
 // 7.7 MB of weights per us and 24 of activations (read once per column block), the less of both the fewer CUs work; writing a
 // slice costs its bytes at 2 MB per us, reading it again in the consumer at 3.5.  Fitted to 286 launches (15 products of the 7B and 13B widths at 31, 32, 61 and 64
 // rows, all forms and slices): 4.7 % off on average; what it picks is at most 4 % slower than the best of them, but for the down projection of 18944 rows
-// at 64 rows (8 %).
+// at 64 rows (8 %).  Elsewhere (42 products of widths 256 to 8192 at 17..61 rows, all forms and slices) the pick is within 7 % of the best (launches under 5 us: as far as two runs
+// of one differ), but for products whose workgroups begin a power of two of 512 KB or more of weights apart, which the estimate does not see: LM head of 2048 x 32000 16..19 % (17 rows 29.5 us,
+// 24.8 with 10 column tiles), of 4096 x 32000 up to 9 %, O of 8192 14..19 % (29.7, 24.8), down of 8192 x 2048 3..11 %.  The kernel before this one (128 columns, up to 16
+// slices) took 31.7 us for the first and 29.9 for O; of all these products it was faster only on matrices of up to 2 MB, by up to 0.4 us.
 constexpr int WIDE_STAGE = 4;       // K blocks that a workgroup takes at a time
 struct WideForm { int kw, ct; };
 constexpr WideForm WIDE_FORMS[] = {{4, 2}, {4, 3}, {2, 2}, {4, 5}, {2, 3}, {2, 4}, {2, 5}};       // 4, 6, 8, 10, 12, 16, 20 column tiles
@@ -138,7 +143,7 @@ inline AttnCut attn_cut(int nseq, int m, int hq, int hkv, bool alone) {
 inline int attn_splits(int keys, int most, int keys_per_split) { return std::max(1, std::min(most, (keys + keys_per_split - 1) / keys_per_split)); }
 // The same for half-precision caches, whose kernel takes 128 keys at a time (attn_split_kernel): as few blocks per workgroup as `most` splits allow, and no more
 // splits than that needs.  A block more costs 2 us, a split more 0.1: 32 heads over 650 keys in 4 splits of two blocks 11.0 us, in 6 of one 10.6; one head group over
-// 130..190 keys in one split 7.7, in two 7.2; but 28 heads over 1130 keys (8 splits at most: two blocks) in 6 splits 12.8, in 8 13.4.
+// 130..190 keys in one split 7.7, in two 7.2; but 28 heads over 1130 keys (8 splits at most: two blocks) in 5 splits 13.4, in 6 13.5, in 8 13.8.
 constexpr int ATTN_BLOCK_KEYS = 128;
 inline int attn_block_splits(int keys, int most) {
     const int per = (keys + ATTN_BLOCK_KEYS * most - 1) / (ATTN_BLOCK_KEYS * most) * ATTN_BLOCK_KEYS;
