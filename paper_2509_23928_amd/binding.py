@@ -321,24 +321,24 @@ class Hivis:
         return out
 
     # -- hooks -----------------------------------------------------------------------
-    def _read_back(self, shape, written, call):
-        """An array of `shape` (its leading dimensions are rows) filled by a call that copies `written` rows.  Those are the rows of the pass that the values belong
-        to, and K may have changed since: rows beyond them are zeros, rows that the shape has no room for are left out."""
-        n = int(np.prod(shape[:-1]))
-        out = np.empty((max(n, written), shape[-1]), np.float32)
-        out[written:] = 0
-        self._check(call(_ptr(out)))
-        return out[:n].reshape(shape)
+    def _read_back(self, call, which, shape, rows, written):
+        """An array of `shape` (`rows` rows) filled by a call that copies `written` rows.  Those are the rows of the pass that the values belong to, and K may
+        have changed since: rows beyond them are zeros, rows that the shape has no room for are left out."""
+        out = np.empty(shape if rows == written else (max(rows, written), shape[-1]), np.float32)
+        if rows > written:
+            out[written:] = 0
+        self._check(call(self.ctx, which, _ptr(out)))
+        return out if rows == written else out[:rows].reshape(shape)
 
     def get_logits(self, which):
-        V = self.cfg.vocab
-        shape, written = {0: ((self.B, self.K + 1, V), self._verify_rows), 1: ((self.K, self.B, V), self._draft_K * self.B), 2: ((self.B, V), self.B)}[which]
-        return self._read_back(shape, written, lambda p: self.lib.hivis_get_logits(self.ctx, which, p))
+        V, B, K = self.cfg.vocab, self.B, self.K
+        shape, rows, written = {0: ((B, K + 1, V), B * (K + 1), self._verify_rows), 1: ((K, B, V), K * B, self._draft_K * B), 2: ((B, V), B, B)}[which]
+        return self._read_back(self.lib.hivis_get_logits, which, shape, rows, written)
 
     def get_hidden(self, which):
-        d = self.cfg.d
-        shape, written = {0: ((self.B, self.K + 1, d), self._verify_rows), 1: ((self.B, d), self.B)}[which]
-        return self._read_back(shape, written, lambda p: self.lib.hivis_get_hidden(self.ctx, which, p))
+        d, B, K = self.cfg.d, self.B, self.K
+        shape, rows, written = {0: ((B, K + 1, d), B * (K + 1), self._verify_rows), 1: ((B, d), B, B)}[which]
+        return self._read_back(self.lib.hivis_get_hidden, which, shape, rows, written)
 
     def kv_lengths(self):
         t = np.zeros(self.B, np.int32)
